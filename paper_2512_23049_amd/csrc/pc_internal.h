@@ -24,7 +24,7 @@ struct PcAppendItem {
     int32_t msg;
     int32_t slot_start;
     int32_t len;
-    int32_t pad;
+    int32_t rows;             // >= len: slots written; those behind the last token get zeros (see pc_append_rows)
 };
 
 // One token appended to an existing message (staged by the host).

@@ -4,12 +4,13 @@
 
 #include "pc_internal.h"
 
-void pc_launch_append(int dtype, const void *k, const void *v, int len, int n_kv_heads, int D,
+// rows >= len: slots written, zeros behind the last token
+void pc_launch_append(int dtype, const void *k, const void *v, int len, int rows, int n_kv_heads, int D,
                       int64_t slot_start, int64_t slots, const double *inv_freq, void *k_store,
                       void *v_store, PcMsgEntry *table, int msg_id, hipStream_t st);
 
 // several whole messages in one launch
-void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_len, int n_kv_heads, int D,
+void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_rows, int n_kv_heads, int D,
                             int64_t slots, const double *inv_freq, void *k_store, void *v_store, PcMsgEntry *table,
                             hipStream_t st);
 

@@ -15,6 +15,11 @@
 // first share out the (token, frequency) rotations, one fp64 sincos each, into LDS, then each moves
 // 16 bytes of the lower and of the upper half of a (token, KV head) row), blockIdx.y == 1 the V part
 // (a thread transposes 8 tokens x 2 dims of one KV head).  k and v must be 16-byte aligned.
+// `rows` >= len slots are written: what lies behind the last token is filled with zeros where the span may hold
+// what a freed message left (pc_append_rows in pc_lib.hip says how far).  The attention kernels need finite values
+// there: they mask those keys by adding -inf to their scores and multiply their V rows by exact zeros.  The zeros
+// ride in this launch; as two launches per message in front of it they took 2 to 4.5 us each, 272 us of a batch of
+// 58 re-used tails and a quarter of the multi-agent workload's time.
 // fp32 caches (small reference configurations): one thread per (token, frequency pair) and per element.
 // ----------------------------------------------------------------------------------
 template <typename T> struct Pair2;
@@ -31,14 +36,14 @@ template <> struct Pair2<__hip_bfloat16> {
 
 #define APP_TB 4               // tokens per block step of the K part: 4 x 64 rotations = one sincos per thread
 
-// K part: tokens [t0, t0 + APP_TB) of one message.  s_cs: APP_TB * 64 rotations.
+// K part: slots [t0, t0 + APP_TB) of one message.  s_cs: APP_TB * 64 rotations.
 __device__ __forceinline__ void append_bf16_k_block(
-    const uint16_t *__restrict__ k, int len, int t0, int n_kv_heads, int D, int64_t slot_start, int64_t slots,
+    const uint16_t *__restrict__ k, int len, int rows, int t0, int n_kv_heads, int D, int64_t slot_start, int64_t slots,
     const double *__restrict__ inv_freq, uint16_t *__restrict__ k_store, float2 *s_cs)
 {
     const int half = D / 2;
-    const int nt = min(APP_TB, len - t0);
-    for (int e = threadIdx.x; e < nt * half; e += blockDim.x) {
+    const int nt = min(APP_TB, rows - t0);
+    for (int e = threadIdx.x; e < min(nt, len - t0) * half; e += blockDim.x) {
         const int tt = e / half, i = e - tt * half;
         double s, c;
         sincos((double)(t0 + tt) * inv_freq[i], &s, &c);
@@ -53,17 +58,20 @@ __device__ __forceinline__ void append_bf16_k_block(
         const int h = (e / chunks) % n_kv_heads;
         const int tt = e / (chunks * n_kv_heads);
         const int t = t0 + tt;
-        const uint16_t *src = k + ((int64_t)t * n_kv_heads + h) * D + 8 * c8;
-        uint4 lo = *reinterpret_cast<const uint4 *>(src);
-        uint4 hi = *reinterpret_cast<const uint4 *>(src + half);
-        uint32_t *lw = reinterpret_cast<uint32_t *>(&lo), *hw = reinterpret_cast<uint32_t *>(&hi);
-        const float2 *cs = s_cs + tt * 64 + 8 * c8;
+        uint4 lo = make_uint4(0, 0, 0, 0), hi = lo;
+        if (t < len) {
+            const uint16_t *src = k + ((int64_t)t * n_kv_heads + h) * D + 8 * c8;
+            lo = *reinterpret_cast<const uint4 *>(src);
+            hi = *reinterpret_cast<const uint4 *>(src + half);
+            uint32_t *lw = reinterpret_cast<uint32_t *>(&lo), *hw = reinterpret_cast<uint32_t *>(&hi);
+            const float2 *cs = s_cs + tt * 64 + 8 * c8;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float fc0 = cs[2 * u].x, fs0 = cs[2 * u].y, fc1 = cs[2 * u + 1].x, fs1 = cs[2 * u + 1].y;
-            const float a0 = P::lo(lw[u]), a1 = P::hi(lw[u]), b0 = P::lo(hw[u]), b1 = P::hi(hw[u]);
-            lw[u] = P::pack(a0 * fc0 - b0 * fs0, a1 * fc1 - b1 * fs1);
-            hw[u] = P::pack(a0 * fs0 + b0 * fc0, a1 * fs1 + b1 * fc1);
+            for (int u = 0; u < 4; ++u) {
+                const float fc0 = cs[2 * u].x, fs0 = cs[2 * u].y, fc1 = cs[2 * u + 1].x, fs1 = cs[2 * u + 1].y;
+                const float a0 = P::lo(lw[u]), a1 = P::hi(lw[u]), b0 = P::lo(hw[u]), b1 = P::hi(hw[u]);
+                lw[u] = P::pack(a0 * fc0 - b0 * fs0, a1 * fc1 - b1 * fs1);
+                hw[u] = P::pack(a0 * fs0 + b0 * fc0, a1 * fs1 + b1 * fc1);
+            }
         }
         uint16_t *dst = k_store + ((int64_t)h * slots + slot_start + t) * D + 8 * c8;
         *reinterpret_cast<uint4 *>(dst) = lo;
@@ -75,11 +83,11 @@ __device__ __forceinline__ void append_bf16_k_block(
 // V part: thread tid = (token group tg, KV head h, dim pair d0): 8 tokens x 2 dims, zero padded behind
 // the message's last token, written key-transposed ([H_kv][slots/8][D][8]) as two 16-byte stores.
 __device__ __forceinline__ void append_bf16_v_thread(
-    int64_t tid, const uint16_t *__restrict__ v, int len, int n_kv_heads, int D, int64_t slot_start, int64_t slots,
+    int64_t tid, const uint16_t *__restrict__ v, int len, int rows, int n_kv_heads, int D, int64_t slot_start, int64_t slots,
     uint16_t *__restrict__ v_store)
 {
     const int dp = D / 2;
-    const int n_groups = (len + PC_VGROUP - 1) / PC_VGROUP;
+    const int n_groups = (rows + PC_VGROUP - 1) / PC_VGROUP;
     if (tid >= (int64_t)n_groups * n_kv_heads * dp) return;
     const int d0 = 2 * (int)(tid % dp);
     const int h = (int)((tid / dp) % n_kv_heads);
@@ -103,36 +111,36 @@ __device__ __forceinline__ void append_bf16_v_thread(
 }
 
 __device__ __forceinline__ void append_f32_thread(
-    int part, int64_t tid, const float *__restrict__ k, const float *__restrict__ v, int len, int n_kv_heads, int D,
+    int part, int64_t tid, const float *__restrict__ k, const float *__restrict__ v, int len, int rows, int n_kv_heads, int D,
     int64_t slot_start, int64_t slots, const double *__restrict__ inv_freq,
     float *__restrict__ k_store, float *__restrict__ v_store)
 {
     const int half = D / 2;
     if (part == 0) {
-        if (tid >= (int64_t)len * half) return;
+        if (tid >= (int64_t)rows * half) return;
         const int t = (int)(tid / half);
         const int i = (int)(tid % half);
-        double s, c;
-        sincos((double)t * inv_freq[i], &s, &c);
+        double s = 0., c = 0.;
+        if (t < len) sincos((double)t * inv_freq[i], &s, &c);
         const float fc = (float)c, fs = (float)s;
         for (int h = 0; h < n_kv_heads; ++h) {
             const float *src = k + ((int64_t)t * n_kv_heads + h) * D;
-            const float a = src[i], b = src[i + half];
+            const float a = t < len ? src[i] : 0.f, b = t < len ? src[i + half] : 0.f;
             float *dst = k_store + ((int64_t)h * slots + slot_start + t) * D;
             dst[i] = a * fc - b * fs;
             dst[i + half] = a * fs + b * fc;
         }
     } else {
-        if (tid >= (int64_t)len * n_kv_heads * D) return;
+        if (tid >= (int64_t)rows * n_kv_heads * D) return;
         const int d = (int)(tid % D);
         const int h = (int)((tid / D) % n_kv_heads);
         const int t = (int)(tid / ((int64_t)D * n_kv_heads));
-        v_store[((int64_t)h * slots + slot_start + t) * D + d] = v[tid];
+        v_store[((int64_t)h * slots + slot_start + t) * D + d] = t < len ? v[tid] : 0.f;
     }
 }
 
 __global__ __launch_bounds__(256) void pc_append_bf16_kernel(
-    const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int len, int n_kv_heads, int D,
+    const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int len, int rows, int n_kv_heads, int D,
     int64_t slot_start, int64_t slots, const double *__restrict__ inv_freq,
     uint16_t *__restrict__ k_store, uint16_t *__restrict__ v_store,
     PcMsgEntry *__restrict__ table, int msg_id)
@@ -141,21 +149,21 @@ __global__ __launch_bounds__(256) void pc_append_bf16_kernel(
     if (blockIdx.y == 0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) { table[msg_id].slot_start = (int32_t)slot_start; table[msg_id].len = len; table[msg_id].base_pos = 0; }
         const int t0 = (int)blockIdx.x * APP_TB;
-        if (t0 < len) append_bf16_k_block(k, len, t0, n_kv_heads, D, slot_start, slots, inv_freq, k_store, s_cs);
+        if (t0 < rows) append_bf16_k_block(k, len, rows, t0, n_kv_heads, D, slot_start, slots, inv_freq, k_store, s_cs);
     } else {
-        append_bf16_v_thread((int64_t)blockIdx.x * blockDim.x + threadIdx.x, v, len, n_kv_heads, D, slot_start, slots, v_store);
+        append_bf16_v_thread((int64_t)blockIdx.x * blockDim.x + threadIdx.x, v, len, rows, n_kv_heads, D, slot_start, slots, v_store);
     }
 }
 
 __global__ __launch_bounds__(256) void pc_append_f32_kernel(
-    const float *__restrict__ k, const float *__restrict__ v, int len, int n_kv_heads, int D,
+    const float *__restrict__ k, const float *__restrict__ v, int len, int rows, int n_kv_heads, int D,
     int64_t slot_start, int64_t slots, const double *__restrict__ inv_freq,
     float *__restrict__ k_store, float *__restrict__ v_store,
     PcMsgEntry *__restrict__ table, int msg_id)
 {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.y == 0 && tid == 0) { table[msg_id].slot_start = (int32_t)slot_start; table[msg_id].len = len; table[msg_id].base_pos = 0; }
-    append_f32_thread((int)blockIdx.y, tid, k, v, len, n_kv_heads, D, slot_start, slots, inv_freq, k_store, v_store);
+    append_f32_thread((int)blockIdx.y, tid, k, v, len, rows, n_kv_heads, D, slot_start, slots, inv_freq, k_store, v_store);
 }
 
 // Several messages in one launch (Sec. 2.4 "Parallel API Calls": the new messages of parallel
@@ -173,28 +181,28 @@ __global__ __launch_bounds__(256) void pc_append_batch_kernel(
     if constexpr (sizeof(T) == 2) {
         __shared__ float2 s_cs[APP_TB * 64];
         if (blockIdx.y == 0) {
-            for (int t0 = (int)blockIdx.x * APP_TB; t0 < it.len; t0 += (int)gridDim.x * APP_TB)
-                append_bf16_k_block((const uint16_t *)it.k, it.len, t0, n_kv_heads, D, it.slot_start, slots, inv_freq, k_store, s_cs);
+            for (int t0 = (int)blockIdx.x * APP_TB; t0 < it.rows; t0 += (int)gridDim.x * APP_TB)
+                append_bf16_k_block((const uint16_t *)it.k, it.len, it.rows, t0, n_kv_heads, D, it.slot_start, slots, inv_freq, k_store, s_cs);
         } else {
-            const int64_t total = (int64_t)((it.len + PC_VGROUP - 1) / PC_VGROUP) * n_kv_heads * (D / 2);
+            const int64_t total = (int64_t)((it.rows + PC_VGROUP - 1) / PC_VGROUP) * n_kv_heads * (D / 2);
             for (int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; tid < total; tid += (int64_t)gridDim.x * blockDim.x)
-                append_bf16_v_thread(tid, (const uint16_t *)it.v, it.len, n_kv_heads, D, it.slot_start, slots, v_store);
+                append_bf16_v_thread(tid, (const uint16_t *)it.v, it.len, it.rows, n_kv_heads, D, it.slot_start, slots, v_store);
         }
     } else {
-        const int64_t total = blockIdx.y == 0 ? (int64_t)it.len * (D / 2) : (int64_t)it.len * n_kv_heads * D;
+        const int64_t total = blockIdx.y == 0 ? (int64_t)it.rows * (D / 2) : (int64_t)it.rows * n_kv_heads * D;
         for (int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; tid < total; tid += (int64_t)gridDim.x * blockDim.x)
-            append_f32_thread((int)blockIdx.y, tid, (const float *)it.k, (const float *)it.v, it.len, n_kv_heads, D,
+            append_f32_thread((int)blockIdx.y, tid, (const float *)it.k, (const float *)it.v, it.len, it.rows, n_kv_heads, D,
                               it.slot_start, slots, inv_freq, k_store, v_store);
     }
 }
 
-void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_len, int n_kv_heads, int D,
+void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_rows, int n_kv_heads, int D,
                             int64_t slots, const double *inv_freq, void *k_store, void *v_store, PcMsgEntry *table,
                             hipStream_t st)
 {
     // enough blocks per (part, message) for the longest message at one pass, within reason
     // (bf16: the K part takes APP_TB tokens per block step, which is more blocks than the V part needs)
-    const int64_t per = dtype == 1 ? ((int64_t)max_len + APP_TB - 1) / APP_TB : ((int64_t)max_len * n_kv_heads * D + 255) / 256;
+    const int64_t per = dtype == 1 ? ((int64_t)max_rows + APP_TB - 1) / APP_TB : ((int64_t)max_rows * n_kv_heads * D + 255) / 256;
     const unsigned bx = (unsigned)std::min<int64_t>(std::max<int64_t>(per, 1), 256);
     for (int first = 0; first < n_items; first += 65535) {            // grid.z is limited to 65535
         const int n = n_items - first < 65535 ? n_items - first : 65535;
@@ -208,23 +216,23 @@ void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, i
     }
 }
 
-void pc_launch_append(int dtype, const void *k, const void *v, int len, int n_kv_heads, int D,
+void pc_launch_append(int dtype, const void *k, const void *v, int len, int rows, int n_kv_heads, int D,
                       int64_t slot_start, int64_t slots, const double *inv_freq, void *k_store,
                       void *v_store, PcMsgEntry *table, int msg_id, hipStream_t st)
 {
     if (dtype == 1) {
-        const int64_t bk = ((int64_t)len + APP_TB - 1) / APP_TB;
-        const int64_t bv = ((int64_t)((len + PC_VGROUP - 1) / PC_VGROUP) * n_kv_heads * (D / 2) + 255) / 256;
+        const int64_t bk = ((int64_t)rows + APP_TB - 1) / APP_TB;
+        const int64_t bv = ((int64_t)((rows + PC_VGROUP - 1) / PC_VGROUP) * n_kv_heads * (D / 2) + 255) / 256;
         dim3 grid((unsigned)(bk > bv ? bk : bv), 2);
-        pc_append_bf16_kernel<<<grid, 256, 0, st>>>((const uint16_t *)k, (const uint16_t *)v, len, n_kv_heads, D,
+        pc_append_bf16_kernel<<<grid, 256, 0, st>>>((const uint16_t *)k, (const uint16_t *)v, len, rows, n_kv_heads, D,
                                                     slot_start, slots, inv_freq, (uint16_t *)k_store,
                                                     (uint16_t *)v_store, table, msg_id);
     } else {
-        const int64_t nk = (int64_t)len * (D / 2);
-        const int64_t nv = (int64_t)len * n_kv_heads * D;
+        const int64_t nk = (int64_t)rows * (D / 2);
+        const int64_t nv = (int64_t)rows * n_kv_heads * D;
         const int64_t n = nk > nv ? nk : nv;
         dim3 grid((unsigned)((n + 255) / 256), 2);
-        pc_append_f32_kernel<<<grid, 256, 0, st>>>((const float *)k, (const float *)v, len, n_kv_heads, D,
+        pc_append_f32_kernel<<<grid, 256, 0, st>>>((const float *)k, (const float *)v, len, rows, n_kv_heads, D,
                                                    slot_start, slots, inv_freq, (float *)k_store,
                                                    (float *)v_store, table, msg_id);
     }
@@ -850,7 +858,8 @@ void pc_launch_attend_f32(const PcLaunch &L, const int32_t *row_call, int total_
 }
 
 // ----------------------------------------------------------------------------------------
-// Zero the K or V rows of a span of slots that is taken again after a free.  The attention kernels
+// Zero the K or V rows of a span of slots that is taken again after a free by a message's further extent (a whole
+// message's append kernel clears its own span).  The attention kernels
 // read whole 32-key tiles: behind a message's last token the scores are masked (the prefill kernel
 // adds -inf to them) and the V side meets probabilities that are exactly zero, both of which only
 // work if what lies there is finite.  A span never used before is zero from the cache's creation;

@@ -176,14 +176,24 @@ static bool take_slots(std::vector<FreeSpan> &spans, int64_t &next, int64_t capa
     return true;
 }
 
-// A span taken where a freed or swapped-out message may have lived: its K and V rows are cleared before the new
-// owner's append kernel runs (the attention kernels mask what lies behind a message's last token, inside its last
-// tile, by adding -inf to its scores and multiply its V rows by exact zeros, both of which need finite values there).
+// A span taken where a freed or swapped-out message may have lived has to be cleared behind the new owner's last token:
+// the attention kernels mask what lies there, inside a message's last tile, by adding -inf to its scores and multiply
+// its V rows by exact zeros, both of which need finite values.  (Slots below dirty_end may hold leftovers; both are
+// multiples of PC_SLOT_ALIGN.)
+static int64_t reused_slots(const pc_cache *c, int64_t start, int32_t res)
+{
+    return std::max<int64_t>(0, std::min((int64_t)align_up((size_t)res, PC_SLOT_ALIGN), c->dirty_end - start));
+}
+// Slots a whole message's append kernel writes: its tokens, and zeros up to where its span may hold leftovers.
+static int32_t pc_append_rows(const pc_cache *c, int64_t start, int32_t len, int32_t res)
+{
+    return (int32_t)std::max<int64_t>(len, reused_slots(c, start, res));
+}
+// A further extent's tokens come one by one: its span is cleared by launches of their own in front of them.
 static void clear_if_reused(pc_cache *c, int64_t start, int32_t res, hipStream_t st)
 {
-    if (c->host_only || start >= c->dirty_end) return;
-    const int64_t need = (int64_t)align_up((size_t)res, PC_SLOT_ALIGN);
-    const int64_t n = std::min(need, c->dirty_end - start);
+    const int64_t n = c->host_only ? 0 : reused_slots(c, start, res);
+    if (n == 0) return;
     pc_launch_zero_span(c->cfg.dtype, c->k_store, c->slots, c->cfg.n_kv_heads, c->D, start, n, st);
     pc_launch_zero_span(c->cfg.dtype, c->v_store, c->slots, c->cfg.n_kv_heads, c->D, start, n, st);
 }
@@ -208,9 +218,8 @@ int32_t pc_append_message(pc_cache *c, const void *k, const void *v, int32_t len
     const int id = (int)c->msgs.size();
     if (!c->host_only) {
         hipStream_t st = (hipStream_t)stream;
-        clear_if_reused(c, start, res, st);
         ProfScope ps(c, 0, st);
-        pc_launch_append(c->cfg.dtype, k, v, len, c->cfg.n_kv_heads, c->D, start, c->slots, c->inv_freq_dev,
+        pc_launch_append(c->cfg.dtype, k, v, len, pc_append_rows(c, start, len, res), c->cfg.n_kv_heads, c->D, start, c->slots, c->inv_freq_dev,
                          c->k_store, c->v_store, c->table_dev, id, st);
         PC_HIP(c, hipGetLastError());
     }
@@ -260,7 +269,7 @@ int32_t pc_append_messages(pc_cache *c, int32_t n, const void *const *k, const v
     int64_t next = c->next_slot;
     std::vector<PcAppendItem> items((size_t)n);
     std::vector<HostMsg> fresh((size_t)n);
-    int max_len = 0;
+    int max_rows = 0;
     for (int j = 0; j < n; ++j) {
         if (lens[j] < 1) return pc_fail(c, PC_ERR_INVALID_ARG, "append_messages: message %d has len = %d", j, lens[j]);
         if (!c->host_only && (!k[j] || !v[j])) return pc_fail(c, PC_ERR_INVALID_ARG, "append_messages: message %d has null k or v", j);
@@ -273,16 +282,15 @@ int32_t pc_append_messages(pc_cache *c, int32_t n, const void *const *k, const v
                         (long long)c->slots);
         fresh[(size_t)j] = HostMsg{start, lens[j], res, 0, true};
         items[(size_t)j] = PcAppendItem{c->host_only ? nullptr : k[j], c->host_only ? nullptr : v[j],
-                                        (int32_t)c->msgs.size() + j, (int32_t)start, lens[j], 0};
-        max_len = std::max(max_len, lens[j]);
+                                        (int32_t)c->msgs.size() + j, (int32_t)start, lens[j], pc_append_rows(c, start, lens[j], res)};
+        max_rows = std::max(max_rows, items[(size_t)j].rows);
     }
     if (!c->host_only) {
         hipStream_t st = (hipStream_t)stream;
         const int32_t rc = pc_stage_items(c, items.data(), sizeof(PcAppendItem) * (size_t)n, st);
         if (rc != PC_OK) return rc;
-        for (int j = 0; j < n; ++j) clear_if_reused(c, fresh[(size_t)j].slot_start, fresh[(size_t)j].reserve, st);
         ProfScope ps(c, 0, st);
-        pc_launch_append_batch(c->cfg.dtype, (const PcAppendItem *)c->tok_dev, n, max_len, c->cfg.n_kv_heads, c->D, c->slots,
+        pc_launch_append_batch(c->cfg.dtype, (const PcAppendItem *)c->tok_dev, n, max_rows, c->cfg.n_kv_heads, c->D, c->slots,
                                c->inv_freq_dev, c->k_store, c->v_store, c->table_dev, st);
         PC_HIP(c, hipGetLastError());
     }

@@ -91,3 +91,44 @@ def test_stored_form_after_every_kind_of_append(h_kv):
     v_by_slot = np.transpose(v_bits, (0, 1, 3, 2)).reshape(h_kv, slots, D)
     assert not v_by_slot[:, free, :].any()
     cache.close()
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_reused_span_is_zero_behind_the_last_token(dtype, batch):
+    """A span that held a message full of NaN is taken again by shorter ones: whatever of their reserves lies behind
+    their last tokens reads as zeros, and the slots of the span that nobody took keep what they held."""
+    import torch
+    from paper_2512_23049_amd import binding
+    h_kv, D = 3, 64 if dtype == "f32" else 128
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    cfg = binding.pc_config(h_kv, h_kv, D, binding.PC_F32 if dtype == "f32" else binding.PC_BF16, 1e4, 0.0, 1024, 32, 1 << 20, 0, None, 0)
+    nbytes = binding.lib().pc_cache_storage_bytes(C.byref(cfg))
+    arena = torch.zeros(nbytes // td.itemsize, dtype=td, device="cuda:0")
+    cache = binding.Cache(h_kv, h_kv, D, cfg.dtype, 1e4, 1024, 32, max_position=1 << 20, arena=arena.data_ptr(), arena_bytes=nbytes)
+    bad = torch.full((700, h_kv, D), float("nan"), dtype=td, device="cuda:0")
+    first = cache.append_message(bad.data_ptr(), bad.data_ptr(), 700)
+    cache.message_free(first)
+    # (len, reserve): one token, a whole tile, one past a tile, a group remainder, far beyond the message, past the freed span
+    want = [(1, 0), (32, 0), (33, 0), (7, 8), (5, 200), (300, 600)]
+    kv = [torch.ones((L, h_kv, D), dtype=td, device="cuda:0") for L, _ in want]
+    if batch:
+        ids = cache.append_messages([t.data_ptr() for t in kv], [t.data_ptr() for t in kv], [L for L, _ in want], [r for _, r in want])
+    else:
+        ids = [cache.append_message(t.data_ptr(), t.data_ptr(), L, r) for t, (L, r) in zip(kv, want)]
+    torch.cuda.synchronize()
+    n = h_kv * 1024 * D
+    k = arena[:n].view(h_kv, 1024, D).float()
+    v = arena[n:2 * n]
+    v = (v.view(h_kv, 128, D, 8).transpose(2, 3).reshape(h_kv, 1024, D) if dtype == "bf16" else v.view(h_kv, 1024, D)).float()
+    end = 0
+    for m, (L, r) in zip(ids, want):
+        _, s0, _ = cache.message_info(m)
+        stop = s0 + (max(L, r) + 31) // 32 * 32
+        end = max(end, stop)
+        say(f"  message {m}: len {L} reserve {r} slots [{s0}, {stop})")
+        assert torch.isfinite(k[:, s0:stop]).all() and torch.isfinite(v[:, s0:stop]).all()
+        assert not k[:, s0 + L:stop].any() and not v[:, s0 + L:stop].any()
+        assert (v[:, s0:s0 + L] == 1).all() and (k[:, s0, :] == 1).all()       # (token 0 sits at position 0: not turned)
+    assert torch.isnan(k[:, end:704]).sum() == torch.isnan(k[:, end:700]).numel()
+    cache.close()
