@@ -602,7 +602,7 @@ def section_reposition(cx):
 
 
 def section_backward(cx):
-    """Gradient path (functional, untuned) on a small shape."""
+    """Gradient path on a small shape."""
     args, torch, gen, harness, line = cx.args, cx.torch, cx.gen, cx.harness, cx.line
     wb = gen.single_prefill(n_msgs=24, len_lo=40, len_hi=300, n_sel=6, n_new=200)
     cache = harness.make_cache(wb)
@@ -626,8 +626,7 @@ def section_backward(cx):
     pairs_b = sum(v[3] for v in visible_pairs(wb, wb.events[-1]))
     line.setdefault("extras", {})["backward"] = {
         "workload": "scaled single prefill (200 causal rows over 6 parents of 40-300 tokens + the new message, 32/8 heads, "
-                    "bf16 cache): pc_attend_backward + pc_grad_keys_finalize; a functional path (plain fp32 vector "
-                    "kernels, no matrix cores), not tuned",
+                    "bf16 cache): pc_attend_backward + pc_grad_keys_finalize, fp32 precision on the bf16 matrix cores",
         "ms_per_call": t_b * 1e3,
         "gflops": 2.5 * 4.0 * wb.head_dim * wb.n_q_heads * pairs_b / t_b / 1e9,
     }

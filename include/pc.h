@@ -314,8 +314,9 @@ int32_t pc_set_key_gather(pc_cache *c, int32_t mode);
  * STORED (turned to their stored base; in a PC_BF16 cache also rounded once more); once every
  * backward call has been enqueued, pc_grad_keys_finalize(d_k) turns the rows of every live
  * message into the gradient w.r.t. the K that was appended.  No message may be repositioned,
- * freed or swapped between the first backward call into a buffer and its finalize.  A
- * functional path (plain fp32 vector kernels, no matrix cores): not tuned. */
+ * freed or swapped between the first backward call into a buffer and its finalize.  All
+ * arithmetic is at fp32 precision for both dtypes (PC_BF16: on the bf16 matrix cores, every
+ * fp32 factor as the exact sum of three bf16 pieces). */
 int32_t pc_attend_backward(pc_cache *c, const pc_call *calls, int32_t n_calls, const void *q, const float *lse,
                            const void *d_out, float *d_q, float *d_k, float *d_v, void *stream);
 int32_t pc_grad_keys_finalize(pc_cache *c, float *d_k, void *stream);

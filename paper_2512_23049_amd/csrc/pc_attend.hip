@@ -204,11 +204,13 @@ int32_t pc_attend_backward(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         return pc_fail(c, PC_ERR_INVALID_ARG, "attend_backward: null argument");
     hipStream_t st = (hipStream_t)stream;
     Planned P;
+    P.backward = true;
     const int32_t rc = pc_plan_and_stage(c, calls, n_calls, false, st, P);
     if (rc != PC_OK || c->host_only) return rc;
     char *w = (char *)P.ws;
     PcLaunch L{};
     L.calls = (const PcCallDesc *)(w + P.lay.calls);
+    L.tiles = (const PcTile *)(w + P.lay.tiles);
     L.segs = (const PcSegment *)(w + P.lay.segs);
     L.rot_seg = (const float2 *)(w + P.lay.rot_seg);
     L.rot_q = (const float2 *)(w + P.lay.rot_q);
@@ -217,15 +219,29 @@ int32_t pc_attend_backward(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     L.slots = c->slots; L.n_q_heads = c->cfg.n_q_heads; L.n_kv_heads = c->cfg.n_kv_heads;
     L.scale_log2 = c->scale * 1.4426950408889634f;
     ProfScope ps(c, 5, st);
+    if (c->cfg.dtype == PC_BF16) {
+        PcBwd B{};
+        B.row_blocks = (const int2 *)(w + P.lay.bwd_rb);
+        B.q_turned = (float4 *)(w + P.lay.bwd_qt); B.q_pieces = (uint16_t *)(w + P.lay.bwd_qp);
+        B.delta_part = (float *)(w + P.lay.bwd_delta); B.dq_part = (float4 *)(w + P.lay.bwd_dq); B.stat = (float2 *)(w + P.lay.bwd_stat);
+        B.lse = lse; B.d_out = (const uint16_t *)d_out; B.d_q = d_q; B.d_k = d_k; B.d_v = d_v; B.scale = c->scale;
+        for (const Planned::BwdChunk &ch : P.chunks) {
+            L.items = (const PcItem *)(w + P.lay.items_pre) + ch.item0;
+            B.key_items = (const PcBwdKeyItem *)(w + P.lay.bwd_keys) + ch.key0;
+            B.rb0 = ch.rb0; B.n_rb = ch.n_rb; B.n_units = (int64_t)ch.n_rb * c->cfg.n_q_heads;
+            pc_launch_attend_bwd_bf16(L, B, ch.n_items, ch.n_keys, st);
+            PC_HIP(c, hipGetLastError());
+        }
+        return PC_OK;
+    }
     int max_seg_len = 0;
     for (const Resolved &r : P.res) {
         for (const int2 &e : r.sel) max_seg_len = std::max(max_seg_len, c->msgs[(size_t)e.x].len);
         max_seg_len = std::max(max_seg_len, r.self_len);
     }
     if ((max_seg_len + 15) / 16 > 65535) return pc_fail(c, PC_ERR_SHAPE, "attend_backward: a message of %d tokens is too long", max_seg_len);
-    L.calls = (const PcCallDesc *)(w + P.lay.calls);
-    pc_launch_attend_bwd(c->cfg.dtype, L, (const int32_t *)(w + P.lay.row_call), n_calls, P.total_q, P.total_seg, max_seg_len, c->D,
-                         lse, d_out, c->scale, (float *)(w + P.lay.row_scalar), d_q, d_k, d_v, st);
+    pc_launch_attend_bwd_f32(L, (const int32_t *)(w + P.lay.row_call), n_calls, P.total_q, P.total_seg, max_seg_len, c->D,
+                             lse, (const float *)d_out, c->scale, (float *)(w + P.lay.row_scalar), d_q, d_k, d_v, st);
     PC_HIP(c, hipGetLastError());
     return PC_OK;
 }

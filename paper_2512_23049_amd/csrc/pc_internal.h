@@ -66,7 +66,8 @@ struct PcCallDesc {
                               // the call gives them) and values were copied there token after token, the parents'
                               // part padded to whole tiles, then the new message
     int32_t n_par;            // tokens of the parents' part (all segments but the new message)
-    int32_t pad[2];
+    int32_t rb_off;           // gradient: the call's first 32-row block among those of the batch
+    int32_t pad;
 };
 
 // One call whose keys the gather pass copies (staged by the host).
@@ -108,6 +109,15 @@ struct PcItem {
     int32_t tile_tab0;        // the call's first entry in the tile table (a copy of its PcCallDesc::tile_off, so that
                               // the first tile descriptors can be requested without waiting for the call descriptor)
     int32_t pad[2];
+};
+
+// Gradient, key-major kernel: one workgroup's key tiles and units (32-row block x head of the KV head, head fastest).
+struct PcBwdKeyItem {
+    int32_t call;
+    int32_t tile0;            // first of up to 4 consecutive tiles of the call
+    int32_t n_tiles;
+    int32_t rt_begin, rt_end; // units [begin, end) of the call
+    int32_t pad[3];
 };
 
 // One output row whose KV splits the merge kernel combines (staged by the host).
@@ -181,6 +191,26 @@ struct PcLaunch {
     int64_t           slots;      // capacity in slots (stride between KV heads)
     int32_t           n_q_heads, n_kv_heads;
     float             scale_log2; // softmax scale * log2(e)
+};
+
+// Gradient of a bf16 batch: what its kernels need besides PcLaunch (whose items are the row-major kernels').  A unit is
+// a 32-row block of one head; the blocks [rb0, rb0 + n_rb) are processed by one set of launches, and the per-unit
+// buffers are indexed by (block - rb0) * n_q_heads + head.
+struct PcBwd {
+    const int2         *row_blocks;   // [blocks of the batch] (call, block within the call)
+    const PcBwdKeyItem *key_items;
+    int32_t             rb0, n_rb;
+    int64_t             n_units;      // n_rb * n_q_heads
+    float4             *q_turned;     // [unit][4 ks][4][64 lanes] queries turned by their positions, fp32: lane (n, hh) of entry
+                                      // (ks, j): row n, dims 16 ks + 8 hh + 4 j + 0..3 (j < 2) and their partners 64 up (j >= 2)
+    uint16_t           *q_pieces;     // [unit][4][32 rows][128] the same as three bf16 pieces; fourth: the output gradients
+    float              *delta_part;   // [split][unit][32]
+    float4             *dq_part;      // [split][unit][16][64 lanes]
+    float2             *stat;         // [unit][32] (lse * log2 e, Delta)
+    const float        *lse;
+    const uint16_t     *d_out;
+    float              *d_q, *d_k, *d_v;
+    float               scale;
 };
 
 #endif

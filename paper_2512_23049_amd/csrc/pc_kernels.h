@@ -58,11 +58,13 @@ void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, 
 
 void pc_launch_attend_f32(const PcLaunch &L, const int32_t *row_call, int total_q, int D, hipStream_t st);
 
-// gradient of the attention (dtype of q, d_out and the cache: 0 fp32, 1 bf16; gradients fp32); d_k collects the
-// gradient w.r.t. the stored keys until the finalize pass
-void pc_launch_attend_bwd(int dtype, const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,
-                          int max_seg_len, int D, const float *lse, const void *d_out, float scale, float *delta,
-                          float *d_q, float *d_k, float *d_v, hipStream_t st);
+// gradient of the attention for fp32 caches; d_k collects the gradient w.r.t. the stored keys until the finalize pass
+void pc_launch_attend_bwd_f32(const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,
+                              int max_seg_len, int D, const float *lse, const float *d_out, float scale, float *delta,
+                              float *d_q, float *d_k, float *d_v, hipStream_t st);
+// the same for bf16 caches on the matrix cores: the row blocks [B.rb0, B.rb0 + B.n_rb), their row-major work items L.items
+// and key-major work items B.key_items
+void pc_launch_attend_bwd_bf16(const PcLaunch &L, const PcBwd &B, int n_items, int n_key_items, hipStream_t st);
 void pc_launch_grad_keys_finalize(const PcMsgEntry *msgs, int n_msgs, int n_kv_heads, int D, const double *inv_freq,
                                   float *d_k, hipStream_t st);
 

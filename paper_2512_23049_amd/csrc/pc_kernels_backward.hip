@@ -1,8 +1,8 @@
-// Gradient kernels (plain fp32 vector code; this path is not a hot one).
+// Gradient kernels of fp32 caches (plain vector code; bf16 caches: pc_kernels_bwd_mfma.hip) and the finalize pass.
 #include "pc_kernels.h"
 
 // ----------------------------------------------------------------------------------
-// Gradient of the attention, for both cache dtypes, in fp32 arithmetic (Sec. 2.4: in fine-tuning a position update is applied
+// Gradient of the attention in fp32 arithmetic (Sec. 2.4: in fine-tuning a position update is applied
 // non-destructively, so gradients flow through it to the cached keys).  One wave per
 // (query row, head), keys lane-strided as in the forward kernel.  With p_j = exp(s_j - LSE)
 // from the forward's LSE and dp_j = dO . v_j:
@@ -15,20 +15,9 @@
 // gives Delta and the gradient of the query; the key-major one below gives those of the keys and values.
 // Plain fp32 vector code: this path is not a hot one.
 // ----------------------------------------------------------------------------------
-// element access for the two cache dtypes: fp32 as it is, bf16 widened; V of a bf16 cache is stored
-// key-transposed in groups of 8 slots
-template <typename T> __device__ __forceinline__ float bwd_ld(const T *p);
-template <> __device__ __forceinline__ float bwd_ld<float>(const float *p) { return *p; }
-template <> __device__ __forceinline__ float bwd_ld<uint16_t>(const uint16_t *p) { return __uint_as_float((uint32_t)*p << 16); }
-template <typename T> __device__ __forceinline__ float bwd_v(const T *vbase, int64_t slot, int d, int D)
-{
-    if constexpr (sizeof(T) == 2) return bwd_ld(vbase + ((slot / PC_VGROUP) * D + d) * PC_VGROUP + (slot % PC_VGROUP));
-    else return vbase[slot * D + d];
-}
-
-template <int D, typename T>
+template <int D>
 __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int32_t *__restrict__ row_call,
-                                                           const float *__restrict__ lse, const T *__restrict__ d_out,
+                                                           const float *__restrict__ lse, const float *__restrict__ d_out,
                                                            float scale, float *__restrict__ d_q,
                                                            float *__restrict__ delta_out)
 {
@@ -41,14 +30,14 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int
     const int g = L.n_q_heads / L.n_kv_heads;
     const int kh = h / g;
     const int64_t rh = (int64_t)R * L.n_q_heads + h;
-    const T *q = (const T *)L.q + rh * D;
+    const float *q = (const float *)L.q + rh * D;
     for (int i = lane; i < HALF; i += 64) {
         const float2 cs = L.rot_q[(int64_t)R * HALF + i];
-        const float a = bwd_ld(q + i), b = bwd_ld(q + i + HALF);
+        const float a = *(q + i), b = *(q + i + HALF);
         s_qhat[i] = a * cs.x - b * cs.y;
         s_qhat[i + HALF] = a * cs.y + b * cs.x;
     }
-    for (int d = lane; d < D; d += 64) { s_do[d] = bwd_ld(d_out + rh * D + d); s_dqhat[d] = 0.f; }
+    for (int d = lane; d < D; d += 64) { s_do[d] = *(d_out + rh * D + d); s_dqhat[d] = 0.f; }
     const float row_lse = lse[rh];
     float *dq = d_q + rh * D;
     if (!(row_lse > -INFINITY)) {                          // the row saw nothing: no gradient anywhere
@@ -57,8 +46,8 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int
         return;
     }
     __syncthreads();
-    const T *kbase = (const T *)L.k_store + (int64_t)kh * L.slots * D;
-    const T *vbase = (const T *)L.v_store + (int64_t)kh * L.slots * D;
+    const float *kbase = (const float *)L.k_store + (int64_t)kh * L.slots * D;
+    const float *vbase = (const float *)L.v_store + (int64_t)kh * L.slots * D;
     auto visible = [&](const PcSegment &sg, int e) {
         int n_vis = sg.len;
         if (cd.self_msg >= 0 && e == cd.n_seg - 1) {
@@ -86,10 +75,10 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int
         turn(e);
         for (int t = lane; t < n_vis; t += 64) {
             const int64_t slot = sg.slot_start + t;
-            const T *kr = kbase + slot * D;
+            const float *kr = kbase + slot * D;
             float s = 0.f, dp = 0.f;
 #pragma unroll 8
-            for (int d = 0; d < D; ++d) { s = fmaf(s_qe[d], bwd_ld(kr + d), s); dp = fmaf(s_do[d], bwd_v(vbase, slot, d, D), dp); }
+            for (int d = 0; d < D; ++d) { s = fmaf(s_qe[d], *(kr + d), s); dp = fmaf(s_do[d], vbase[slot * D + d], dp); }
             delta += expf(s * scale - row_lse) * dp;
         }
     }
@@ -106,14 +95,14 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int
         for (int d = 0; d < D; ++d) dqe[d] = 0.f;
         for (int t = lane; t < n_vis; t += 64) {
             const int64_t slot = sg.slot_start + t;
-            const T *kr = kbase + slot * D;
+            const float *kr = kbase + slot * D;
             float s = 0.f, dp = 0.f;
 #pragma unroll 8
-            for (int d = 0; d < D; ++d) { s = fmaf(s_qe[d], bwd_ld(kr + d), s); dp = fmaf(s_do[d], bwd_v(vbase, slot, d, D), dp); }
+            for (int d = 0; d < D; ++d) { s = fmaf(s_qe[d], *(kr + d), s); dp = fmaf(s_do[d], vbase[slot * D + d], dp); }
             const float p = expf(s * scale - row_lse);
             const float ds = p * (dp - delta) * scale;
 #pragma unroll 8
-            for (int d = 0; d < D; ++d) dqe[d] = fmaf(ds, bwd_ld(kr + d), dqe[d]);
+            for (int d = 0; d < D; ++d) dqe[d] = fmaf(ds, *(kr + d), dqe[d]);
         }
         // sum the lanes' dqe, turn it back by +(start - base), add to the gradient of the position-turned query
         __syncthreads();
@@ -142,9 +131,9 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kernel(PcLaunch L, const int
 // the g heads of the group: the sums over rows and heads stay in registers, and a token's gradient meets
 // those of its other placements (other calls, repeated listings) in d_k, d_v through one float atomic per
 // element at the end.
-template <int D, typename T>
+template <int D>
 __global__ __launch_bounds__(64) void pc_attend_bwd_kv_kernel(PcLaunch L, int n_calls, const float *__restrict__ lse,
-                                                              const T *__restrict__ d_out, const float *__restrict__ delta,
+                                                              const float *__restrict__ d_out, const float *__restrict__ delta,
                                                               float scale, float *__restrict__ d_k, float *__restrict__ d_v)
 {
     constexpr int HALF = D / 2, Q = D / 4;
@@ -166,13 +155,13 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kv_kernel(PcLaunch L, int n_
     const bool is_self = cd.self_msg >= 0 && e == cd.n_seg - 1;
     const int g = L.n_q_heads / L.n_kv_heads;
     const int64_t slot = sg.slot_start + (t_ok ? t : 0);
-    const T *kbase = (const T *)L.k_store + (int64_t)kh * L.slots * D;
-    const T *vbase = (const T *)L.v_store + (int64_t)kh * L.slots * D;
+    const float *kbase = (const float *)L.k_store + (int64_t)kh * L.slots * D;
+    const float *vbase = (const float *)L.v_store + (int64_t)kh * L.slots * D;
     float kq[Q], vq[Q], dk[Q], dv[Q];
 #pragma unroll
     for (int d = 0; d < Q; ++d) {
-        kq[d] = bwd_ld(kbase + slot * D + part * Q + d);
-        vq[d] = bwd_v(vbase, slot, part * Q + d, D);
+        kq[d] = *(kbase + slot * D + part * Q + d);
+        vq[d] = vbase[slot * D + part * Q + d];
         dk[d] = 0.f; dv[d] = 0.f;
     }
     // rows that can see this block's tokens at all: in the new message a row sees tokens up to its own
@@ -185,15 +174,15 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kv_kernel(PcLaunch L, int n_
             const int64_t rh = (int64_t)R * L.n_q_heads + h;
             __syncthreads();
             if (tid < HALF) {                              // the query of (row, head) turned for this segment
-                const T *q = (const T *)L.q + rh * D;
+                const float *q = (const float *)L.q + rh * D;
                 const float2 cq = L.rot_q[(int64_t)R * HALF + tid];
-                const float a = bwd_ld(q + tid), b = bwd_ld(q + tid + HALF);
+                const float a = *(q + tid), b = *(q + tid + HALF);
                 const float qa = a * cq.x - b * cq.y, qb = a * cq.y + b * cq.x;
                 const float2 cs = L.rot_seg[(int64_t)seg * HALF + tid];
                 s_qe[tid] = qa * cs.x + qb * cs.y;
                 s_qe[tid + HALF] = -qa * cs.y + qb * cs.x;
             }
-            for (int d = tid; d < D; d += 64) s_do[d] = bwd_ld(d_out + rh * D + d);
+            for (int d = tid; d < D; d += 64) s_do[d] = *(d_out + rh * D + d);
             __syncthreads();
             const float row_lse = lse[rh];
             if (!(row_lse > -INFINITY)) continue;          // (uniform over the block)
@@ -215,32 +204,20 @@ __global__ __launch_bounds__(64) void pc_attend_bwd_kv_kernel(PcLaunch L, int n_
     for (int d = 0; d < Q; ++d) { atomicAdd(gk + d, dk[d]); atomicAdd(gv + d, dv[d]); }
 }
 
-void pc_launch_attend_bwd(int dtype, const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,
-                          int max_seg_len, int D, const float *lse, const void *d_out, float scale, float *delta,
-                          float *d_q, float *d_k, float *d_v, hipStream_t st)
+void pc_launch_attend_bwd_f32(const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,
+                              int max_seg_len, int D, const float *lse, const float *d_out, float scale, float *delta,
+                              float *d_q, float *d_k, float *d_v, hipStream_t st)
 {
     if (total_q <= 0) return;
     dim3 grid(total_q, L.n_q_heads);
     dim3 grid_kv((unsigned)total_seg, (unsigned)((max_seg_len + 15) / 16), (unsigned)L.n_kv_heads);
     const bool kv = total_seg > 0 && max_seg_len > 0;
-    if (dtype == 1) {
-        const uint16_t *go = (const uint16_t *)d_out;
-        if (D == 64) {
-            pc_attend_bwd_kernel<64, uint16_t><<<grid, 64, 0, st>>>(L, row_call, lse, go, scale, d_q, delta);
-            if (kv) pc_attend_bwd_kv_kernel<64, uint16_t><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, go, delta, scale, d_k, d_v);
-        } else {
-            pc_attend_bwd_kernel<128, uint16_t><<<grid, 64, 0, st>>>(L, row_call, lse, go, scale, d_q, delta);
-            if (kv) pc_attend_bwd_kv_kernel<128, uint16_t><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, go, delta, scale, d_k, d_v);
-        }
+    if (D == 64) {
+        pc_attend_bwd_kernel<64><<<grid, 64, 0, st>>>(L, row_call, lse, d_out, scale, d_q, delta);
+        if (kv) pc_attend_bwd_kv_kernel<64><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, d_out, delta, scale, d_k, d_v);
     } else {
-        const float *go = (const float *)d_out;
-        if (D == 64) {
-            pc_attend_bwd_kernel<64, float><<<grid, 64, 0, st>>>(L, row_call, lse, go, scale, d_q, delta);
-            if (kv) pc_attend_bwd_kv_kernel<64, float><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, go, delta, scale, d_k, d_v);
-        } else {
-            pc_attend_bwd_kernel<128, float><<<grid, 64, 0, st>>>(L, row_call, lse, go, scale, d_q, delta);
-            if (kv) pc_attend_bwd_kv_kernel<128, float><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, go, delta, scale, d_k, d_v);
-        }
+        pc_attend_bwd_kernel<128><<<grid, 64, 0, st>>>(L, row_call, lse, d_out, scale, d_q, delta);
+        if (kv) pc_attend_bwd_kv_kernel<128><<<grid_kv, 64, 0, st>>>(L, n_calls, lse, d_out, delta, scale, d_k, d_v);
     }
 }
 

@@ -80,7 +80,8 @@ int32_t pc_resolve(pc_cache *c, const pc_call *call, int idx, Resolved &out)
 PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, int n_dec, int n_pre, int n_pre_pk,
                        int64_t part_rows, int64_t total_tiles, int H_q, int D,
                        size_t n_sh_groups = 0, size_t n_sh_segs = 0, size_t n_sh_items = 0, size_t n_sh_pos = 0,
-                       size_t n_kg_items = 0, int64_t kg_tiles = 0, int H_kv = 1, size_t n_tok = 0)
+                       size_t n_kg_items = 0, int64_t kg_tiles = 0, int H_kv = 1, size_t n_tok = 0,
+                       size_t n_bwd_rb = 0, size_t n_bwd_keys = 0, size_t bwd_units = 0, size_t bwd_splits = 0)
 {
     PlanLayout L{};
     size_t o = 0;
@@ -99,6 +100,8 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
     L.sh_pos = take(sizeof(int32_t) * std::max<size_t>(n_sh_pos, 1));
     L.kg_items = take(sizeof(PcGatherItem) * std::max<size_t>(n_kg_items, 1));
     L.tok_items = take(sizeof(PcTokenItem) * std::max<size_t>(n_tok, 1));
+    L.bwd_rb = take(sizeof(int2) * n_bwd_rb);
+    L.bwd_keys = take(sizeof(PcBwdKeyItem) * n_bwd_keys);
     L.h2d_bytes = o;
     L.segs = take(sizeof(PcSegment) * (size_t)std::max(total_seg, 1));
     L.seg_kvoff = take(sizeof(int32_t) * (size_t)std::max(total_seg, 1));
@@ -113,6 +116,11 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
     L.k_gather = take((size_t)std::max<int64_t>(kg_tiles, 0) * PC_TILE * (size_t)H_kv * (size_t)D * 2);   // bf16 keys ...
     L.v_gather = take((size_t)std::max<int64_t>(kg_tiles, 0) * PC_TILE * (size_t)H_kv * (size_t)D * 2);   // ... and values of the calls that gather
     L.kg_norm = take(sizeof(float) * (size_t)std::max<int64_t>(kg_tiles, 0) * (size_t)H_kv);             // ... and the largest key norm of each of their tiles
+    L.bwd_qt = take(sizeof(float4) * 1024 * bwd_units);                          // gradient: per-unit buffers of one set of launches
+    L.bwd_qp = take((size_t)4 * 8192 * bwd_units);
+    L.bwd_delta = take(sizeof(float) * 32 * bwd_units * bwd_splits);
+    L.bwd_dq = take(sizeof(float4) * 1024 * bwd_units * bwd_splits);
+    L.bwd_stat = take(sizeof(float2) * 32 * bwd_units);
     L.total = o;
     return L;
 }
@@ -256,6 +264,78 @@ static void plan_shared(const pc_cache *c, std::vector<Resolved> &res, const std
     }
 }
 
+// Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head) and
+// as many splits of the tiles as fill the chip once (a workgroup fills a compute unit); the key-major kernel takes 4 key
+// tiles a workgroup and splits their units until there are about four workgroups for every compute unit, which evens out
+// the last round (BWD_KEY_WGS).  Per-unit buffers take 64 KB a unit (16 more per further split): a batch with more units
+// than BWD_UNITS is cut into runs of row blocks with launches of their own, at multiples of 8 blocks of a call, so that
+// no workgroup's 8 units lie in two of them.
+constexpr int64_t BWD_UNITS = 16384, BWD_KEY_WGS = 1024;
+struct BwdPlan { std::vector<PcItem> items; std::vector<PcBwdKeyItem> keys; std::vector<int2> row_blocks; size_t units = 0, splits = 1; };
+
+static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc> &cds, BwdPlan &bp)
+{
+    const int g = c->g, H_q = c->cfg.n_q_heads, H_kv = c->cfg.n_kv_heads;
+    const int rb_max = (int)std::max<int64_t>(8, BWD_UNITS / H_q / 8 * 8);
+    int64_t groups = 0, quads = 0;
+    for (const Resolved &r : P.res) { groups += (int64_t)(((r.n_q + 31) / 32) * g + 7) / 8 * H_kv; quads += (int64_t)((r.tiles + 3) / 4) * H_kv; }
+    Planned::BwdChunk ch{0, 0, 0, 0, 0, 0};
+    auto close = [&]() {
+        if (ch.n_rb == 0) return;
+        ch.n_items = (int)bp.items.size() - ch.item0; ch.n_keys = (int)bp.keys.size() - ch.key0;
+        bp.units = std::max(bp.units, (size_t)ch.n_rb * (size_t)H_q);
+        P.chunks.push_back(ch);
+        ch = Planned::BwdChunk{ch.rb0 + ch.n_rb, 0, (int)bp.items.size(), 0, (int)bp.keys.size(), 0};
+    };
+    for (size_t i = 0; i < P.res.size(); ++i) {
+        const Resolved &r = P.res[i];
+        PcCallDesc &cd = cds[i];
+        const int n_rb = (r.n_q + 31) / 32, T = r.tiles;
+        const int self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0, parent_tiles = T - self_tiles;
+        int ns = (int)std::max<int64_t>(1, std::min<int64_t>({(256 + groups - 1) / groups, (int64_t)T / 8, (int64_t)MAX_SPLITS}));
+        cd.n_splits = ns;
+        cd.rb_off = (int32_t)bp.row_blocks.size();
+        bp.splits = std::max(bp.splits, (size_t)ns);
+        for (int b = 0; b < n_rb; ++b) bp.row_blocks.push_back(make_int2((int)i, b));
+        for (int b0 = 0; b0 < n_rb;) {
+            if (ch.n_rb > 0 && ch.n_rb + std::min(n_rb - b0, 8) > rb_max) close();
+            int nb = n_rb - b0;
+            if (nb > rb_max - ch.n_rb) nb = (rb_max - ch.n_rb) / 8 * 8;                   // (at least 8: see close above; rb_max is a multiple of 8)
+            if (nb == 0) { close(); continue; }
+            const int b1 = b0 + nb;
+            // rows by tiles: a split's share is cut at the causal limit of the workgroup's last row
+            for (int u0 = b0 * g; u0 < b1 * g; u0 += 8) {
+                int Tg = T;
+                if (r.self_msg >= 0) {
+                    const int last_unit = std::min(u0 + 7, b1 * g - 1);
+                    const int lim = (r.self_len - r.n_q) + std::min(32 * (last_unit / g) + 31, r.n_q - 1);
+                    Tg = parent_tiles + std::min(self_tiles, lim / PC_TILE + 1);
+                }
+                const int chunk = std::max(1, (Tg + ns - 1) / ns);
+                for (int s = 0; s < ns; ++s) {
+                    PcItem it{}; it.call = (int32_t)i; it.unit0 = u0; it.split = s; it.tile_tab0 = cd.tile_off;
+                    it.tile_begin = std::min(Tg, s * chunk); it.tile_end = s == ns - 1 ? Tg : std::min(Tg, (s + 1) * chunk);
+                    bp.items.push_back(it);
+                }
+            }
+            // tiles by units: own tiles are seen from the block of their first key on
+            for (int t = 0; t < T; t += 4) {
+                int first = b0;
+                if (t >= parent_tiles) first = std::max(first, ((t - parent_tiles) * PC_TILE - (r.self_len - r.n_q)) / 32);
+                if (first >= b1) continue;
+                const int n_rt = (b1 - first) * g;
+                const int sp = (int)std::max<int64_t>(1, std::min<int64_t>((BWD_KEY_WGS + quads - 1) / quads, n_rt / 8));
+                const int per = (n_rt + sp - 1) / sp;
+                for (int a = 0; a < n_rt; a += per)
+                    bp.keys.push_back(PcBwdKeyItem{(int32_t)i, t, std::min(4, T - t), first * g + a, first * g + std::min(n_rt, a + per), {0, 0, 0}});
+            }
+            ch.n_rb += nb;
+            b0 = b1;
+        }
+    }
+    close();
+}
+
 int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bool want_items,
                               hipStream_t st, Planned &P)
 {
@@ -303,7 +383,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         cd.self_msg = own_plan ? r.self_msg : -1; cd.self_start = r.self_start;
         cd.n_q = r.n_q; cd.q_off = q_off; cd.seg_off = seg_off; cd.n_seg = cd.n_sel + (cd.self_msg >= 0 ? 1 : 0);
         cd.self_len = own_plan ? r.self_len : 0; cd.n_splits = 1; cd.part_off = 0; cd.tile_off = (int32_t)total_tiles;
-        cd.kg_tile0 = -1; cd.n_par = 0; cd.pad[0] = cd.pad[1] = 0;
+        cd.kg_tile0 = -1; cd.n_par = 0; cd.rb_off = 0; cd.pad = 0;
         if (own_plan) total_tiles += r.tiles;
         sel_off += cd.n_sel; q_off += cd.n_q; seg_off += cd.n_seg;
         if (!want_items || !bf16 || !own_plan) continue;
@@ -396,15 +476,19 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             sp.items.push_back(PcShItem{(int32_t)gi, t0, std::min(T, (sidx + 1) * chunk), sidx, seg, {0, 0, 0}});
         }
     }
+    BwdPlan bp;
+    if (P.backward && bf16) plan_backward(c, P, cds, bp);
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     P.total_sel = sel_off; P.total_seg = seg_off;
+    if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
     P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
     P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
-                        sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size());
+                        sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
+                        bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits);
     if (c->host_only) return PC_OK;
 
     int32_t rc = PC_OK;
@@ -452,6 +536,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     if (!pre_pk.empty()) std::memcpy(h + P.lay.items_pk, pre_pk.data(), sizeof(PcItem) * pre_pk.size());
     if (!kg.empty()) std::memcpy(h + P.lay.kg_items, kg.data(), sizeof(PcGatherItem) * kg.size());
     if (!P.tok_items.empty()) std::memcpy(h + P.lay.tok_items, P.tok_items.data(), sizeof(PcTokenItem) * P.tok_items.size());
+    if (!bp.row_blocks.empty()) std::memcpy(h + P.lay.bwd_rb, bp.row_blocks.data(), sizeof(int2) * bp.row_blocks.size());
+    if (!bp.keys.empty()) std::memcpy(h + P.lay.bwd_keys, bp.keys.data(), sizeof(PcBwdKeyItem) * bp.keys.size());
     if (!sp.items.empty()) {
         std::memcpy(h + P.lay.sh_groups, sp.groups.data(), sizeof(PcShGroup) * sp.groups.size());
         std::memcpy(h + P.lay.sh_segs, sp.segs.data(), sizeof(PcShSeg) * sp.segs.size());
