@@ -9,8 +9,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpc.so")
 PROBE_LIB = os.path.join(HERE, "libpc_probe.so")
 PROBE_SOURCES = ["pc_probe.hip"]
-SOURCES = ["pc_lib.hip", "pc_plan.hip", "pc_attend.hip", "pc_kernels_basic.hip", "pc_kernels_backward.hip", "pc_kernels_bwd_mfma.hip",
-           "pc_kernels_mfma.hip", "pc_kernels_prefill.hip",
+SOURCES = ["pc_lib.hip", "pc_plan.hip", "pc_attend.hip", "pc_kernels_basic.hip", "pc_kernels_f32.hip", "pc_kernels_backward.hip",
+           "pc_kernels_bwd_mfma.hip", "pc_kernels_mfma.hip", "pc_kernels_prefill.hip",
            "pc_kernels_shared.hip"]
 # the prefill kernel never produces NaNs in its max reductions: let the compiler drop the
 # canonicalising v_max x, x in front of every fmax

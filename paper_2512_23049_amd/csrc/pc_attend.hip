@@ -50,11 +50,18 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     L.scale_log2 = c->scale * 1.4426950408889634f;
     L.k_gather = w + P.lay.k_gather; L.v_gather = w + P.lay.v_gather; L.kg_slots = P.kg_tiles * PC_TILE;
     L.kg_norm = (float *)(w + P.lay.kg_norm);
-    const int32_t *row_call = (const int32_t *)(w + P.lay.row_call);
     if (c->cfg.dtype == PC_F32) {
-        ProfScope ps(c, 5, st);
-        pc_launch_attend_f32(L, row_call, P.total_q, c->D, st);
-        PC_HIP(c, hipGetLastError());
+        {
+            ProfScope ps(c, 5, st);
+            L.items = (const PcItem *)(w + P.lay.items_pre);
+            pc_launch_attend_f32(L, P.n_pre, c->D, st);
+            PC_HIP(c, hipGetLastError());
+        }
+        if (P.n_merge_rows > 0) {
+            ProfScope ps(c, 4, st);
+            pc_launch_merge_f32((const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
+            PC_HIP(c, hipGetLastError());
+        }
         return PC_OK;
     }
     // A mixed batch (Sec. 2.4 "Parallel API Calls": prefill and decode calls in one batch): the one-row calls run on a

@@ -102,7 +102,7 @@ struct PcTile {
 // One workgroup's share of an attention launch.
 struct PcItem {
     int32_t call;
-    int32_t unit0;            // prefill: first row unit of the workgroup; decode: 0
+    int32_t unit0;            // prefill: first row unit of the workgroup; decode: 0; fp32: block of 32 (row, head) columns
     int32_t tile_begin;       // KV tile range [begin, end) within the call
     int32_t tile_end;
     int32_t split;            // split index within the call
@@ -182,7 +182,7 @@ struct PcLaunch {
     const void       *q;          // [total_q][H_q][D]
     void             *out;        // [total_q][H_q][D]
     float            *lse;        // [total_q][H_q] or null
-    uint16_t         *part_o;     // [part rows][H_q][D]   partial outputs, each normalised by its own sum, fp16
+    uint16_t         *part_o;     // [part rows][H_q][D]   partial outputs: bf16 caches fp16, each normalised by its own sum; fp32 caches fp32, not normalised
     float            *part_ml;    // [part rows][H_q][2]   running max (scaled log2 domain), sum
     void             *k_gather;   // [H_kv][kg_slots][D]       keys of the calls that gather, turned to their positions
     void             *v_gather;   // [H_kv][kg_slots/8][D][8]  their values, in the cache's group-of-8 layout

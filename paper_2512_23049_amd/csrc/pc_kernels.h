@@ -56,7 +56,11 @@ void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, in
 void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, const uint16_t *part_o,
                      const float *part_ml, void *out, float *lse, int n_q_heads, int D, hipStream_t st);
 
-void pc_launch_attend_f32(const PcLaunch &L, const int32_t *row_call, int total_q, int D, hipStream_t st);
+// fp32 caches: the work items L.items (unit0: block of 32 (row, head) columns of the KV head), partials in fp32; then the
+// rows whose tiles were split
+void pc_launch_attend_f32(const PcLaunch &L, int n_items, int D, hipStream_t st);
+void pc_launch_merge_f32(const PcMergeRow *rows, int n_rows, const void *part_o, const float *part_ml, void *out, float *lse, int n_q_heads, int D,
+                         hipStream_t st);
 
 // gradient of the attention for fp32 caches; d_k collects the gradient w.r.t. the stored keys until the finalize pass
 void pc_launch_attend_bwd_f32(const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,

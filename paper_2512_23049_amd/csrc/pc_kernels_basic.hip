@@ -1,5 +1,4 @@
-// Cache append, plan builder, table expansion, split merge and the fp32 attention
-// kernel.  gfx950 only.
+// Cache append, plan builder, table expansion, split merge and gather.  gfx950 only.
 #include "pc_kernels.h"
 
 #include <hip/hip_bf16.h>
@@ -752,7 +751,7 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
         lse[(int64_t)mr.row * n_q_heads + h] = (l > 0.f) ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-// only bf16 caches with D = 128 split their work (the fp32 kernel never does)
+// bf16 caches (D = 128; fp32: pc_launch_merge_f32)
 void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, const uint16_t *part_o,
                      const float *part_ml, void *out, float *lse, int n_q_heads, int D, hipStream_t st)
 {
@@ -762,99 +761,6 @@ void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, 
         pc_merge_kernel<4><<<(n_pairs + 3) / 4, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
     else
         pc_merge_kernel<1><<<(n_pairs + 15) / 16, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
-}
-
-// ----------------------------------------------------------------------------------
-// K6: fp32 attention, one wave per (query row, query head).  Plain vector arithmetic,
-// meant for fp32 caches (small reference-precision configurations).
-// For each segment the query is turned by (q_pos - segment start) and dotted with the
-// stored keys; online softmax per lane over the keys that lane visits; lanes are
-// combined at the end.
-// ----------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void pc_attend_f32_kernel(PcLaunch L, const int32_t *__restrict__ row_call)
-{
-    constexpr int HALF = D / 2;
-    __shared__ float s_qhat[D];
-    __shared__ float s_qe[D];
-    __shared__ float s_red[64 * (D + 1)];
-    const int R = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const PcCallDesc cd = L.calls[row_call[R]];
-    const int r = R - cd.q_off;
-    const int g = L.n_q_heads / L.n_kv_heads;
-    const int kh = h / g;
-    const float *q = (const float *)L.q + ((int64_t)R * L.n_q_heads + h) * D;
-    for (int i = lane; i < HALF; i += 64) {
-        const float2 cs = L.rot_q[(int64_t)R * HALF + i];
-        const float a = q[i], b = q[i + HALF];
-        s_qhat[i] = a * cs.x - b * cs.y;
-        s_qhat[i + HALF] = a * cs.y + b * cs.x;
-    }
-    __syncthreads();
-    const float *kbase = (const float *)L.k_store + (int64_t)kh * L.slots * D;
-    const float *vbase = (const float *)L.v_store + (int64_t)kh * L.slots * D;
-    float m = -INFINITY, l = 0.f;
-    float acc[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = 0.f;
-    for (int e = 0; e < cd.n_seg; ++e) {
-        const PcSegment sg = L.segs[cd.seg_off + e];
-        int n_vis = sg.len;
-        if (cd.self_msg >= 0 && e == cd.n_seg - 1) {
-            const int lim = cd.self_len - cd.n_q + r + 1;
-            n_vis = lim < n_vis ? lim : n_vis;
-        }
-        if (n_vis <= 0) continue;
-        __syncthreads();
-        for (int i = lane; i < HALF; i += 64) {
-            const float2 cs = L.rot_seg[(int64_t)(cd.seg_off + e) * HALF + i];
-            const float a = s_qhat[i], b = s_qhat[i + HALF];
-            s_qe[i] = a * cs.x + b * cs.y;              // turn by -pos_start
-            s_qe[i + HALF] = -a * cs.y + b * cs.x;
-        }
-        __syncthreads();
-        for (int t = lane; t < n_vis; t += 64) {
-            const float *kr = kbase + (int64_t)(sg.slot_start + t) * D;
-            float s = 0.f;
-#pragma unroll 8
-            for (int d = 0; d < D; ++d) s = fmaf(s_qe[d], kr[d], s);
-            s *= L.scale_log2;
-            const float mn = fmaxf(m, s);
-            const float alpha = exp2f(m - mn);          // m = -inf -> 0
-            const float p = exp2f(s - mn);
-            l = l * alpha + p;
-            const float *vr = vbase + (int64_t)(sg.slot_start + t) * D;
-#pragma unroll
-            for (int d = 0; d < D; ++d) acc[d] = fmaf(acc[d], alpha, p * vr[d]);
-            m = mn;
-        }
-    }
-    // combine the 64 lanes
-    float mw = m;
-    for (int off = 32; off > 0; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
-    const float w = (m > -INFINITY) ? exp2f(m - mw) : 0.f;
-    float lw = l * w;
-    for (int off = 32; off > 0; off >>= 1) lw += __shfl_xor(lw, off);
-    __syncthreads();
-#pragma unroll
-    for (int d = 0; d < D; ++d) s_red[lane * (D + 1) + d] = acc[d] * w;
-    __syncthreads();
-    float *out = (float *)L.out + ((int64_t)R * L.n_q_heads + h) * D;
-    for (int d = lane; d < D; d += 64) {
-        float o = 0.f;
-        for (int j = 0; j < 64; ++j) o += s_red[j * (D + 1) + d];
-        out[d] = (lw > 0.f) ? o / lw : 0.f;
-    }
-    if (L.lse && lane == 0)
-        L.lse[(int64_t)R * L.n_q_heads + h] = (lw > 0.f) ? (mw + log2f(lw)) * 0.6931471805599453f : -INFINITY;
-}
-
-void pc_launch_attend_f32(const PcLaunch &L, const int32_t *row_call, int total_q, int D, hipStream_t st)
-{
-    if (total_q <= 0) return;
-    dim3 grid(total_q, L.n_q_heads);
-    if (D == 64) pc_attend_f32_kernel<64><<<grid, 64, 0, st>>>(L, row_call);
-    else pc_attend_f32_kernel<128><<<grid, 64, 0, st>>>(L, row_call);
 }
 
 // ----------------------------------------------------------------------------------------

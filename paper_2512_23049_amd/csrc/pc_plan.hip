@@ -81,7 +81,7 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
                        int64_t part_rows, int64_t total_tiles, int H_q, int D,
                        size_t n_sh_groups = 0, size_t n_sh_segs = 0, size_t n_sh_items = 0, size_t n_sh_pos = 0,
                        size_t n_kg_items = 0, int64_t kg_tiles = 0, int H_kv = 1, size_t n_tok = 0,
-                       size_t n_bwd_rb = 0, size_t n_bwd_keys = 0, size_t bwd_units = 0, size_t bwd_splits = 0)
+                       size_t n_bwd_rb = 0, size_t n_bwd_keys = 0, size_t bwd_units = 0, size_t bwd_splits = 0, size_t part_esize = sizeof(uint16_t))
 {
     PlanLayout L{};
     size_t o = 0;
@@ -110,7 +110,7 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
     L.rot_qw = take(D == 128 ? sizeof(float2) * (size_t)((std::max(total_q, 1) + 31) / 32) * 32 * (D / 2) : 0);   // whole blocks of 32 rows
     L.tiles = take(sizeof(PcTile) * (size_t)std::max<int64_t>(total_tiles, 1));
     L.sh_rot = take(sizeof(float2) * std::max<size_t>(n_sh_pos, 1) * (D / 2));
-    L.part_o = take(sizeof(uint16_t) * (size_t)std::max<int64_t>(part_rows, 1) * H_q * D);
+    L.part_o = take(part_esize * (size_t)std::max<int64_t>(part_rows, 1) * H_q * D);
     L.part_ml = take(sizeof(float) * (size_t)std::max<int64_t>(part_rows, 1) * H_q * 2);
     L.row_scalar = take(sizeof(float) * (size_t)std::max(total_q, 1) * H_q);      // one float per (row, head): the gradient path's Delta
     L.k_gather = take((size_t)std::max<int64_t>(kg_tiles, 0) * PC_TILE * (size_t)H_kv * (size_t)D * 2);   // bf16 keys ...
@@ -336,6 +336,42 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
     close();
 }
 
+// Work items of an fp32 batch.  A workgroup takes 32 (row, head) columns of a KV head and all of its tiles (eight waves, an
+// eighth each) unless the batch has fewer such blocks than half the compute units: then the tiles are split over as many
+// workgroups as fill the chip once, 16 tiles (two a wave) at least, and a second launch adds the parts.  A wave's tile is
+// 7 us at D = 128 beside the other wave of its SIMD, the merge launch 5: with 8 tiles a split, 23 tiles of 40 blocks took
+// 14 + 5 us, unsplit 22, and every split writes its part to memory.
+static void plan_f32(const pc_cache *c, const Planned &P, std::vector<PcCallDesc> &cds, bool may_split, std::vector<PcItem> &items, int64_t &part_rows)
+{
+    const int g = c->g, H_kv = c->cfg.n_kv_heads;
+    auto blocks_of = [&](const Resolved &r) { return ((int64_t)r.n_q * g + 31) / 32; };
+    int64_t groups = 0;
+    for (const Resolved &r : P.res) groups += blocks_of(r) * H_kv;
+    items.clear();
+    part_rows = 0;
+    for (size_t i = 0; i < P.res.size(); ++i) {
+        const Resolved &r = P.res[i];
+        PcCallDesc &cd = cds[i];
+        const int T = r.tiles, self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0;
+        const int ns = may_split ? (int)std::max<int64_t>(1, std::min<int64_t>({256 / std::max<int64_t>(groups, 1), (int64_t)T / 16, (int64_t)MAX_SPLITS})) : 1;
+        cd.n_splits = ns; cd.part_off = 0;
+        if (ns > 1) { cd.part_off = (int32_t)part_rows; part_rows += (int64_t)ns * cd.n_q; }
+        for (int64_t b = 0; b < blocks_of(r); ++b) {
+            int Tg = T;
+            if (r.self_msg >= 0) {                       // cut at the causal limit of the block's last row
+                const int last_row = (int)(std::min<int64_t>(32 * b + 31, (int64_t)r.n_q * g - 1) / g);
+                Tg = T - self_tiles + std::min(self_tiles, (r.self_len - r.n_q + last_row) / PC_TILE + 1);
+            }
+            const int chunk = std::max(1, (Tg + ns - 1) / ns);
+            for (int s = 0; s < ns; ++s) {
+                PcItem it{}; it.call = (int32_t)i; it.unit0 = (int32_t)b; it.split = s; it.tile_tab0 = cd.tile_off;
+                it.tile_begin = std::min(Tg, s * chunk); it.tile_end = std::min(Tg, (s + 1) * chunk);
+                items.push_back(it);
+            }
+        }
+    }
+}
+
 int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bool want_items,
                               hipStream_t st, Planned &P)
 {
@@ -478,6 +514,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     BwdPlan bp;
     if (P.backward && bf16) plan_backward(c, P, cds, bp);
+    if (want_items && !bf16) plan_f32(c, P, cds, true, pre, part_rows);
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     P.total_sel = sel_off; P.total_seg = seg_off;
     if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
@@ -486,9 +523,17 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
-    P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
-                        sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
-                        bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits);
+    auto lay_out = [&]() {
+        P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
+                            sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
+                            bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float));
+    };
+    lay_out();
+    if (!bf16 && part_rows > 0 && P.fixed_ws && P.lay.total > P.fixed_cap) {     // the partials are what does not fit: an unsplit walk needs none
+        plan_f32(c, P, cds, false, pre, part_rows);
+        P.n_pre = (int)pre.size();
+        lay_out();
+    }
     if (c->host_only) return PC_OK;
 
     int32_t rc = PC_OK;
