@@ -125,7 +125,7 @@ inline int32_t chain_last(const pc_cache *c, int32_t m)
 
 // layout of the staged (host -> device) block and of the device-built block
 struct PlanLayout {
-    size_t calls, sel, q_pos, row_call, merge_rows, items_dec, items_pre, items_pk, sh_groups, sh_segs, sh_items, sh_pos, kg_items, tok_items, bwd_rb, bwd_keys, h2d_bytes;
+    size_t calls, sel, q_pos, merge_rows, items_dec, items_pre, items_pk, sh_groups, sh_segs, sh_items, sh_pos, kg_items, tok_items, bwd_rb, bwd_keys, h2d_bytes;
     size_t segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, sh_rot, part_o, part_ml, row_scalar, k_gather, v_gather, kg_norm, bwd_qt, bwd_qp, bwd_delta, bwd_dq, bwd_stat, total;
 };
 
@@ -144,6 +144,7 @@ struct Planned {
     bool backward = false;
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
+    int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)
     // Where the call's workspace lives.  On entry: fixed_ws != nullptr names a buffer of fixed_cap bytes the plan
     // must fit into (nothing is allocated then: a plan or staging block that does not fit is an error); nullptr
     // means the cache's own workspace, which grows on demand.  On return ws is the buffer the plan was staged to.

@@ -111,7 +111,8 @@ struct PcItem {
     int32_t pad[2];
 };
 
-// Gradient, key-major kernel: one workgroup's key tiles and units (32-row block x head of the KV head, head fastest).
+// Gradient, key-major kernel: one workgroup's key tiles and units (bf16: 32-row block x head of the KV head, head fastest;
+// fp32: block of 32 (row, head) columns).
 struct PcBwdKeyItem {
     int32_t call;
     int32_t tile0;            // first of up to 4 consecutive tiles of the call

@@ -63,9 +63,9 @@ void pc_launch_merge_f32(const PcMergeRow *rows, int n_rows, const void *part_o,
                          hipStream_t st);
 
 // gradient of the attention for fp32 caches; d_k collects the gradient w.r.t. the stored keys until the finalize pass
-void pc_launch_attend_bwd_f32(const PcLaunch &L, const int32_t *row_call, int n_calls, int total_q, int total_seg,
-                              int max_seg_len, int D, const float *lse, const float *d_out, float scale, float *delta,
-                              float *d_q, float *d_k, float *d_v, hipStream_t st);
+// (row-major items L.items as in pc_launch_attend_f32, unsplit; key-major items over blocks of 32 columns)
+void pc_launch_attend_bwd_f32(const PcLaunch &L, int n_items, const PcBwdKeyItem *key_items, int n_key_items, int D, const float *lse,
+                              const float *d_out, float scale, float *delta, float *d_q, float *d_k, float *d_v, hipStream_t st);
 // the same for bf16 caches on the matrix cores: the row blocks [B.rb0, B.rb0 + B.n_rb), their row-major work items L.items
 // and key-major work items B.key_items
 void pc_launch_attend_bwd_bf16(const PcLaunch &L, const PcBwd &B, int n_items, int n_key_items, hipStream_t st);

@@ -89,7 +89,6 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
     L.calls = take(sizeof(PcCallDesc) * (size_t)std::max(n_calls, 1));
     L.sel = take(sizeof(int2) * (size_t)std::max(total_sel, 1));
     L.q_pos = take(sizeof(int32_t) * (size_t)std::max(total_q, 1));
-    L.row_call = take(sizeof(int32_t) * (size_t)std::max(total_q, 1));
     L.merge_rows = take(sizeof(PcMergeRow) * (size_t)std::max(total_q, 1));
     L.items_dec = take(sizeof(PcItem) * (size_t)std::max(n_dec, 1));
     L.items_pre = take(sizeof(PcItem) * (size_t)std::max(n_pre, 1));
@@ -372,6 +371,31 @@ static void plan_f32(const pc_cache *c, const Planned &P, std::vector<PcCallDesc
     }
 }
 
+// Key-major work items of the gradient of an fp32 batch: 4 key tiles a workgroup (one a wave), which fills a compute unit,
+// and the column blocks that see them split until the chip is full twice over, two blocks a split at least (a split ends in
+// one atomic per element of its tiles' dK and dV, about what one more block costs).
+static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vector<PcBwdKeyItem> &keys)
+{
+    const int g = c->g;
+    int64_t quads = 0;
+    for (const Resolved &r : P.res) quads += (int64_t)((r.tiles + 3) / 4) * c->cfg.n_kv_heads;
+    for (size_t i = 0; i < P.res.size(); ++i) {
+        const Resolved &r = P.res[i];
+        const int T = r.tiles, self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0, parent_tiles = T - self_tiles;
+        const int blocks = (int)(((int64_t)r.n_q * g + 31) / 32);
+        for (int t = 0; t < T; t += 4) {
+            int first = 0;                               // own tiles are seen from the block of their first key's row on
+            if (t >= parent_tiles) first = (int)((int64_t)std::max(0, (t - parent_tiles) * PC_TILE - (r.self_len - r.n_q)) * g / 32);
+            if (first >= blocks) continue;
+            const int n = blocks - first;
+            const int sp = (int)std::max<int64_t>(1, std::min<int64_t>((512 + quads - 1) / quads, n / 2));
+            const int per = (n + sp - 1) / sp;
+            for (int a = 0; a < n; a += per)
+                keys.push_back(PcBwdKeyItem{(int32_t)i, t, std::min(4, T - t), first + a, first + std::min(n, a + per), {0, 0, 0}});
+        }
+    }
+}
+
 int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bool want_items,
                               hipStream_t st, Planned &P)
 {
@@ -515,6 +539,11 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     BwdPlan bp;
     if (P.backward && bf16) plan_backward(c, P, cds, bp);
     if (want_items && !bf16) plan_f32(c, P, cds, true, pre, part_rows);
+    if (P.backward && !bf16) {
+        plan_f32(c, P, cds, false, pre, part_rows);
+        plan_backward_keys_f32(c, P, bp.keys);
+        P.n_bwd_keys = (int)bp.keys.size();
+    }
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     P.total_sel = sel_off; P.total_seg = seg_off;
     if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
@@ -556,13 +585,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     char *h = (char *)slot->host;
     std::memcpy(h + P.lay.calls, cds.data(), sizeof(PcCallDesc) * cds.size());
     int2 *hs = (int2 *)(h + P.lay.sel);
-    int32_t *hq = (int32_t *)(h + P.lay.q_pos), *hr = (int32_t *)(h + P.lay.row_call);
+    int32_t *hq = (int32_t *)(h + P.lay.q_pos);
     PcMergeRow *hm = (PcMergeRow *)(h + P.lay.merge_rows);
     for (int i = 0; i < n_calls; ++i) {
         const Resolved &r = P.res[i];
         if (cds[i].n_sel > 0) std::memcpy(hs + cds[i].sel_off, r.sel.data(), sizeof(int2) * (size_t)cds[i].n_sel);
         std::memcpy(hq + cds[i].q_off, r.q_pos.data(), sizeof(int32_t) * r.q_pos.size());
-        for (int q = 0; q < r.n_q; ++q) hr[cds[i].q_off + q] = i;
     }
     // rows to merge: those with few splits first, then those with many (they get four lanes per 8 dimensions)
     for (int pass = 0; pass < 2; ++pass) {

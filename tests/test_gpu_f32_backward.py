@@ -1,0 +1,60 @@
+"""The gradient of an fp32 batch against fp64 gradients of the same stored keys and values, at the edges of its tiles: 32
+(row, head) columns, 32-key tiles shared out over eight waves (rows) or one a wave (keys), column blocks split over
+workgroups.  Bound as in test_gpu_backward_precision: fp32 sums, 5e-7 measured, the bar is 3e-6."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_backward_precision import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("h_q,h_kv,D", [(2, 2, 64), (6, 2, 64), (32, 2, 64), (4, 4, 128), (3, 1, 128), (40, 2, 128)])
+@pytest.mark.parametrize("n_q", [1, 31, 33, 70])
+def test_columns_and_tiles(h_q, h_kv, D, n_q):
+    lens = [31, 1, 64, 33, 100, max(n_q, 5) + 3]
+    run_case(lens, [([(0, 0), (4, 40), (1, 7), (2, 300), (0, 500), (3, 140)], 5, 600, n_q)], h_q, h_kv, dtype="f32", D=D)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_batch(D):
+    """Calls that share messages, list nothing, have no new message, fewer rows than the new message; moved messages."""
+    lens = [70, 128, 9, 40, 257, 96, 17]
+    calls = [([(0, 0), (1, 70), (2, 210)], 3, 220, 40), ([], 4, 0, 257), ([(1, 5), (4, 900), (0, 100)], 5, 300, 61),
+             ([(4, -20), (2, 400)], -1, 500, 34), ([], -1, 3, 2), ([(5, 0), (5, 30)], 6, 300, 1)]
+    run_case(lens, calls, 8, 2, dtype="f32", D=D, bases=[(0, 50), (4, -7)])
+
+
+def test_many_blocks_over_a_long_history():
+    lens = [int(x) for x in np.random.default_rng(3).integers(20, 300, size=30)] + [300]
+    run_case(lens, [([(m, 300 * m) for m in range(30)], 30, 13000, 300)], 8, 2, dtype="f32", D=64)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_later_tokens_that_are_not_finite(D):
+    """What stands behind a row's own token does not reach its gradient."""
+    import torch
+    from paper_2512_23049_amd import binding
+    from pc_inputs import Call
+    h_q, h_kv, n, at = 4, 2, 64, 37
+    rng = torch.Generator(device="cuda:0")
+    rng.manual_seed(2)
+    k, v, q, g = (torch.randn((n, h, D), generator=rng, device="cuda:0") for h in (h_kv, h_kv, h_q, h_q))
+    grads = []
+    for bad in (False, True):
+        if bad:
+            k[at, :, 3] = float("inf")
+            v[at, :, 5] = float("nan")
+        cache = binding.Cache(h_q, h_kv, D, binding.PC_F32, 10000.0, 128, 2)
+        m = cache.append_message(k.data_ptr(), v.data_ptr(), n)
+        call = [Call([], m, 0, n, None)]
+        out, lse = torch.empty((n, h_q, D), device="cuda:0"), torch.empty((n, h_q), device="cuda:0")
+        cache.attend(call, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        d_q = torch.empty((n, h_q, D), device="cuda:0")
+        d_k, d_v = (torch.zeros((128, h_kv, D), device="cuda:0") for _ in range(2))
+        cache.attend_backward(call, q.data_ptr(), lse.data_ptr(), g.data_ptr(), d_q.data_ptr(), d_k.data_ptr(), d_v.data_ptr())
+        torch.cuda.synchronize()
+        cache.close()
+        grads.append(d_q[:at].clone())
+    assert torch.isfinite(grads[1]).all()
+    assert float((grads[1] - grads[0]).norm() / grads[0].norm()) <= 3e-6
