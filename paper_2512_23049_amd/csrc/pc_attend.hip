@@ -151,12 +151,13 @@ int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, cons
     // table) and a message that needs a further extent (a new table row).  Then the append gets a launch of its own.
     bool fuse = !c->host_only && n_msgs > 0 && n_calls > 0;
     if (fuse) {
-        std::vector<char> grows(c->msgs.size(), 0);
-        for (int32_t m : ids) grows[(size_t)m] = 1;
+        const uint32_t grows = new_marks(c);
+        for (int32_t m : ids) c->marks[(size_t)m].epoch = grows;
+        const int32_t n_rows = (int32_t)c->msgs.size();
         for (int i = 0; i < n_calls && fuse; ++i)
-            for (int e = 0; e < calls[i].n_sel && calls[i].sel && fuse; ++e) {
+            for (int e = 0; e < calls[i].n_sel && calls[i].sel; ++e) {
                 const int32_t m = calls[i].sel[e].msg_id;
-                if (m >= 0 && m < (int32_t)grows.size() && grows[(size_t)m]) fuse = false;
+                if (m >= 0 && m < n_rows && c->marks[(size_t)m].epoch == grows) { fuse = false; break; }
             }
     }
     Planned P;

@@ -67,12 +67,27 @@ struct pc_cache {
     // a mixed batch runs its one-row calls beside its prefill calls: a second stream (default priority) forked from
     // and joined to the caller's with these two events
     hipStream_t side = nullptr; hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    // one record per table row for work that marks messages (a value is valid under the epoch it was written in): a plan
+    // touches the rows its lists name, however many ids the cache has given out
+    struct Mark { uint32_t epoch; int32_t value; };
+    std::vector<Mark> marks; uint32_t mark_epoch = 0;
     std::string err;
 };
 
 #define PC_HIP(c, expr)                                                                        \
     do { hipError_t e_ = (expr);                                                               \
          if (e_ != hipSuccess) return pc_fail((c), PC_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); } while (0)
+
+// a fresh epoch: no row is marked
+inline uint32_t new_marks(pc_cache *c)
+{
+    if (c->marks.size() < c->msgs.size()) c->marks.resize(std::max(c->msgs.size(), c->marks.size() * 2), pc_cache::Mark{0, 0});
+    if (++c->mark_epoch == 0) {
+        std::fill(c->marks.begin(), c->marks.end(), pc_cache::Mark{0, 0});
+        c->mark_epoch = 1;
+    }
+    return c->mark_epoch;
+}
 
 int32_t pc_fail(pc_cache *c, int32_t code, const char *fmt, ...);
 size_t pc_storage_bytes(const pc_config *cfg);

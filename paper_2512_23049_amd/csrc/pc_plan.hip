@@ -10,27 +10,43 @@ int32_t pc_resolve(pc_cache *c, const pc_call *call, int idx, Resolved &out)
     if (call->n_q < 1) return pc_fail(c, PC_ERR_INVALID_ARG, "call %d: n_q = %d must be >= 1", idx, call->n_q);
     const int64_t maxp = c->cfg.max_position;
     // a listed message becomes one (extent record, start) pair per extent that holds tokens
-    out.sel.clear();
-    out.sel.reserve((size_t)call->n_sel);
+    out.sel.resize((size_t)call->n_sel);
     out.entry_start.resize((size_t)call->n_sel);
+    size_t n_out = 0;
     int64_t nxt = 0, n_kv = 0, tiles = 0;
+    const HostMsg *msgs = c->msgs.data();                // (raw pointers: long lists are resolved on every step of a decode loop)
+    const int32_t n_msgs = (int32_t)c->msgs.size();
+    const pc_sel *list = call->sel;
+    int32_t *starts = out.entry_start.data();
+    int2 *dst = out.sel.data();
     for (int e = 0; e < call->n_sel; ++e) {
-        const int32_t m = call->sel[e].msg_id;
-        if (!known(c, m)) return pc_fail(c, PC_ERR_BAD_MSG_ID, "call %d: parent %d names unknown message %d", idx, e, m);
-        const int64_t len = chain_len(c, m);
-        const int64_t s = call->sel[e].start_pos == PC_POS_AUTO ? nxt : (int64_t)call->sel[e].start_pos;
+        const int32_t m = list[e].msg_id;
+        if ((uint32_t)m >= (uint32_t)n_msgs || !msgs[m].live || msgs[m].is_ext)
+            return pc_fail(c, PC_ERR_BAD_MSG_ID, "call %d: parent %d names unknown message %d", idx, e, m);
+        const HostMsg &hm = msgs[m];
+        const int64_t len = hm.next < 0 ? hm.len : chain_len(c, m);
+        const int64_t s = list[e].start_pos == PC_POS_AUTO ? nxt : (int64_t)list[e].start_pos;
         if (s < -maxp || s + len - 1 > maxp)
             return pc_fail(c, PC_ERR_INVALID_ARG, "call %d: parent %d spans positions [%lld, %lld], limit is +-%lld", idx, e,
                         (long long)s, (long long)(s + len - 1), (long long)maxp);
-        out.entry_start[(size_t)e] = (int32_t)s;
-        int64_t at = s;
-        for (int32_t r = m; r >= 0; r = c->msgs[(size_t)r].next) {
-            const int32_t rl = c->msgs[(size_t)r].len;
-            if (rl > 0 || r == m) out.sel.push_back(make_int2(r, (int)at));
-            at += rl; tiles += (rl + PC_TILE - 1) / PC_TILE;
+        starts[e] = (int32_t)s;
+        dst[n_out++] = make_int2(m, (int)s);
+        tiles += (hm.len + PC_TILE - 1) / PC_TILE;
+        if (hm.next >= 0) {                              // its further extents
+            int64_t at = s + hm.len;
+            for (int32_t r = hm.next; r >= 0; r = msgs[r].next) {
+                const int32_t rl = msgs[r].len;
+                if (rl > 0) {
+                    out.sel.resize(out.sel.size() + 1);
+                    dst = out.sel.data();
+                    dst[n_out++] = make_int2(r, (int)at);
+                }
+                at += rl; tiles += (rl + PC_TILE - 1) / PC_TILE;
+            }
         }
         nxt = s + len; n_kv += len;
     }
+    out.sel.resize(n_out);
     out.self_msg = -1; out.self_len = 0;
     int64_t s_self = call->self_start == PC_POS_AUTO ? nxt : (int64_t)call->self_start;
     int64_t self_total = 0;
@@ -174,91 +190,118 @@ constexpr double SHARE_MIN = 6.0;
 // rows with more splits than this are merged by four lanes per 8 dimensions
 constexpr int MERGE_MANY_SPLITS = 8;
 
-static void plan_shared(const pc_cache *c, std::vector<Resolved> &res, const std::vector<int> &q_off, int g, SharedPlan &sp)
+static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vector<int> &q_off, int g, SharedPlan &sp)
 {
     const int n_calls = (int)res.size();
     sp.in_shared.assign((size_t)n_calls, 0);
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return;
     const int rows_max = 32 * (8 / g);
-    std::vector<int32_t> useg_of_msg(c->msgs.size(), -1);
-    struct USeg { int32_t msg, occ; int64_t slot; int32_t len; };
-    struct Entry { int32_t useg, row, pos; };
-    std::vector<USeg> usegs;
-    std::vector<Entry> entries;
+    struct USeg { int32_t occ, len; int64_t slot; uint32_t vis[8]; };
+    const HostMsg *msgs = c->msgs.data();
+    std::vector<USeg> usegs;                              // the union's messages as they turn up
+    std::vector<int32_t> pos;                             // [useg][row] rotation positions
     std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> useg, for repeats within a call
-    std::vector<int32_t> order, new_index;
+    std::vector<int32_t> order;
     for (int i = 0; i < n_calls;) {
         if (res[i].n_q != 1) { ++i; continue; }
         int j = i;
         while (j < n_calls && res[j].n_q == 1 && j - i < rows_max) ++j;
-        usegs.clear(); entries.clear(); extra.clear();
+        const int n_rows = j - i;
+        // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
+        const size_t usegs_max = ((size_t)1 << 19) / (size_t)n_rows;
+        usegs.clear(); pos.clear(); extra.clear();
+        const uint32_t epoch = new_marks(c);             // value: the message's place in usegs
         int64_t call_tiles = 0;
+        auto add = [&](int32_t m, int32_t occ) {
+            const HostMsg &hm = c->msgs[(size_t)m];
+            usegs.push_back(USeg{occ, hm.len, hm.slot_start, {0, 0, 0, 0, 0, 0, 0, 0}});
+            pos.resize(pos.size() + (size_t)n_rows, PC_SH_ABSENT);
+            return (int32_t)usegs.size() - 1;
+        };
+        auto first_of = [&](int32_t m) -> int32_t {
+            pc_cache::Mark &mk = c->marks[(size_t)m];
+            if (mk.epoch != epoch) mk = pc_cache::Mark{epoch, add(m, 0)};
+            return mk.value;
+        };
         auto lookup = [&](int32_t m, int32_t occ) -> int32_t {
-            if (occ == 0) {
-                if (useg_of_msg[(size_t)m] < 0) {
-                    useg_of_msg[(size_t)m] = (int32_t)usegs.size();
-                    usegs.push_back({m, 0, c->msgs[(size_t)m].slot_start, c->msgs[(size_t)m].len});
-                }
-                return useg_of_msg[(size_t)m];
-            }
+            if (occ == 0) return first_of(m);
             const int64_t key = ((int64_t)m << 20) | occ;
             for (auto &kv : extra) if (kv.first == key) return kv.second;
-            extra.push_back({key, (int32_t)usegs.size()});
-            usegs.push_back({m, occ, c->msgs[(size_t)m].slot_start, c->msgs[(size_t)m].len});
-            return extra.back().second;
+            const int32_t u = add(m, occ);
+            extra.push_back({key, u});
+            return u;
         };
-        for (int r = 0; r < j - i; ++r) {
+        auto enter = [&](int32_t u, int32_t r, int32_t p) {
+            usegs[(size_t)u].vis[r >> 5] |= 1u << (r & 31);
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = p;
+        };
+        for (int r = 0; r < n_rows && usegs.size() <= usegs_max; ++r) {
             Resolved &rc = res[(size_t)(i + r)];
-            sort_by_slot(c, rc);
             call_tiles += rc.tiles;
-            int32_t prev = -1, occ = 0, self_occ = 0;
+            // the union is sorted once, below: a call's own list is needed in slot order only where it names a message
+            // twice (its occurrences are told apart by their starts)
+            int32_t self_occ = 0;
+            bool once = true;
+            const pc_cache::Mark *marks = c->marks.data();
+            const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
             for (const int2 &e : rc.sel) {
-                occ = (e.x == prev) ? occ + 1 : 0;
-                prev = e.x;
-                if (e.x == rc.self_msg) ++self_occ;
-                if (c->msgs[(size_t)e.x].len > 0)
-                    entries.push_back({lookup(e.x, occ), r, e.y - c->msgs[(size_t)e.x].base_pos});
+                const HostMsg &hm = msgs[e.x];
+                if (hm.len <= 0) continue;
+                self_occ += e.x == rc.self_msg;
+                const int32_t u = marks[e.x].epoch == epoch ? marks[e.x].value : first_of(e.x);
+                uint32_t &vis = usegs[(size_t)u].vis[word];
+                once &= (vis & bit) == 0;
+                vis |= bit;
+                pos[(size_t)u * (size_t)n_rows + (size_t)r] = e.y - hm.base_pos;
+            }
+            if (!once) {
+                for (size_t u = 0; u < usegs.size(); ++u) {               // the row again, from nothing
+                    usegs[u].vis[r >> 5] &= ~(1u << (r & 31));
+                    pos[u * (size_t)n_rows + (size_t)r] = PC_SH_ABSENT;
+                }
+                sort_by_slot(c, rc);
+                int32_t prev = -1, occ = 0;
+                for (const int2 &e : rc.sel) {
+                    occ = (e.x == prev) ? occ + 1 : 0;
+                    prev = e.x;
+                    if (c->msgs[(size_t)e.x].len > 0) enter(lookup(e.x, occ), r, e.y - c->msgs[(size_t)e.x].base_pos);
+                }
             }
             if (rc.self_msg >= 0 && rc.self_len > 0)      // the call's own tail: one row, one token from the end -> all of it visible
-                entries.push_back({lookup(rc.self_msg, self_occ), r, rc.self_start - c->msgs[(size_t)rc.self_msg].base_pos});
+                enter(lookup(rc.self_msg, self_occ), r, rc.self_start - c->msgs[(size_t)rc.self_msg].base_pos);
         }
         int64_t union_tiles = 0;
         for (const USeg &u : usegs) union_tiles += (u.len + PC_TILE - 1) / PC_TILE;
-        // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
-        const bool take = union_tiles > 0 && union_tiles < INT32_MAX / 2 &&
-                          (int64_t)usegs.size() * (j - i) <= ((int64_t)1 << 19) &&
-                          (c->decode_sharing == 2 || (j - i >= 2 && (double)call_tiles >= SHARE_MIN * (double)union_tiles));
+        const bool take = union_tiles > 0 && union_tiles < INT32_MAX / 2 && usegs.size() <= usegs_max &&
+                          (c->decode_sharing == 2 || (n_rows >= 2 && (double)call_tiles >= SHARE_MIN * (double)union_tiles));
         if (take) {
             // union in cache-slot order
-            order.resize(usegs.size()); new_index.resize(usegs.size());
+            order.resize(usegs.size());
             for (size_t u = 0; u < usegs.size(); ++u) order[u] = (int32_t)u;
             std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
                 return usegs[(size_t)a].slot != usegs[(size_t)b].slot ? usegs[(size_t)a].slot < usegs[(size_t)b].slot
                                                                       : usegs[(size_t)a].occ < usegs[(size_t)b].occ; });
             PcShGroup gr{};
             gr.seg_off = (int32_t)sp.segs.size(); gr.n_seg = (int32_t)usegs.size();
-            gr.row0 = q_off[(size_t)i]; gr.n_rows = j - i; gr.rot_off = (int32_t)sp.pos.size();
+            gr.row0 = q_off[(size_t)i]; gr.n_rows = n_rows; gr.rot_off = (int32_t)sp.pos.size();
             gr.n_splits = 1; gr.part_off = 0;
             int32_t tile_off = 0;
-            for (size_t k = 0; k < order.size(); ++k) {
-                const USeg &u = usegs[(size_t)order[k]];
-                new_index[(size_t)order[k]] = (int32_t)k;
+            sp.segs.reserve(sp.segs.size() + usegs.size());
+            sp.pos.reserve(sp.pos.size() + pos.size());
+            for (int32_t k : order) {
+                const USeg &u = usegs[(size_t)k];
                 PcShSeg sg{};
                 sg.slot_start = (int32_t)u.slot; sg.len = u.len; sg.tile_off = tile_off;
+                std::copy(u.vis, u.vis + 8, sg.vis);
                 tile_off += (u.len + PC_TILE - 1) / PC_TILE;
                 sp.segs.push_back(sg);
+                const int32_t *row = pos.data() + (size_t)k * (size_t)n_rows;
+                sp.pos.insert(sp.pos.end(), row, row + n_rows);
             }
             gr.n_tiles = tile_off;
-            sp.pos.resize(sp.pos.size() + usegs.size() * (size_t)gr.n_rows, PC_SH_ABSENT);
-            for (const Entry &en : entries) {
-                const int32_t k = new_index[(size_t)en.useg];
-                sp.segs[(size_t)gr.seg_off + (size_t)k].vis[en.row >> 5] |= 1u << (en.row & 31);
-                sp.pos[(size_t)gr.rot_off + (size_t)k * (size_t)gr.n_rows + (size_t)en.row] = en.pos;
-            }
             sp.groups.push_back(gr);
             for (int k = i; k < j; ++k) sp.in_shared[(size_t)k] = 1;
         }
-        for (const USeg &u : usegs) if (u.occ == 0) useg_of_msg[(size_t)u.msg] = -1;
         i = j;
     }
 }
