@@ -67,7 +67,7 @@ struct PcCallDesc {
                               // part padded to whole tiles, then the new message
     int32_t n_par;            // tokens of the parents' part (all segments but the new message)
     int32_t rb_off;           // gradient: the call's first 32-row block among those of the batch
-    int32_t pad;
+    int32_t part_wide;        // bf16 caches, n_splits > 1: 1 = partial outputs in fp32, a row takes two units of part_off
 };
 
 // One call whose keys the gather pass copies (staged by the host).
@@ -121,11 +121,12 @@ struct PcBwdKeyItem {
     int32_t pad[3];
 };
 
+#define PC_MERGE_WIDE 0x10000     // partial outputs in fp32 (bf16 caches)
 // One output row whose KV splits the merge kernel combines (staged by the host).
 struct PcMergeRow {
     int32_t row;              // packed query row
-    int32_t part_row0;        // partial row of split 0 (split s is n_q rows further)
-    int32_t n_splits;
+    int32_t part_row0;        // partial row of split 0 (split s is n_q rows further; twice that if the rows are fp32, see PcCallDesc::part_wide)
+    int32_t n_splits;         // | PC_MERGE_WIDE
     int32_t n_q;
 };
 
@@ -183,7 +184,7 @@ struct PcLaunch {
     const void       *q;          // [total_q][H_q][D]
     void             *out;        // [total_q][H_q][D]
     float            *lse;        // [total_q][H_q] or null
-    uint16_t         *part_o;     // [part rows][H_q][D]   partial outputs: bf16 caches fp16, each normalised by its own sum; fp32 caches fp32, not normalised
+    uint16_t         *part_o;     // [part rows][H_q][D]   partial outputs, each normalised by its own sum: fp16, or fp32 in rows of two units; fp32 caches: fp32, not normalised
     float            *part_ml;    // [part rows][H_q][2]   running max (scaled log2 domain), sum
     void             *k_gather;   // [H_kv][kg_slots][D]       keys of the calls that gather, turned to their positions
     void             *v_gather;   // [H_kv][kg_slots/8][D][8]  their values, in the cache's group-of-8 layout

@@ -4,6 +4,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 // ----------------------------------------------------------------------------------
 // K1: fused cache append (Sec. 2.4: new messages are appended at the end of the
@@ -664,7 +665,7 @@ void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, in
 
 // ----------------------------------------------------------------------------------
 // K5: merge of KV splits.  Each split s of a row holds its own normalised output O_s
-// (fp16), a running maximum m_s (scaled log2 domain) and a sum l_s; the result is
+// (fp16 or fp32), a running maximum m_s (scaled log2 domain) and a sum l_s; the result is
 //   m = max m_s,  w_s = l_s 2^(m_s - m),  l = sum w_s,  O = sum w_s O_s / l
 // in a fixed order (deterministic; no atomics).
 // SL * 16 threads per (row, head): a thread = (one of SL equal parts of the splits, eight of the 128
@@ -687,45 +688,60 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
     const int sub = threadIdx.x & 15, sg = ((int)threadIdx.x % TPP) >> 4;
     const int h = pair % n_q_heads;
     const PcMergeRow mr = merge_rows[pair / n_q_heads];
-    const int part = (mr.n_splits + SL - 1) / SL;
-    const int s_begin = sg * part, s_end = min(s_begin + part, mr.n_splits);
+    const int n_splits = mr.n_splits & (PC_MERGE_WIDE - 1);
+    const int part = (n_splits + SL - 1) / SL;
+    const int s_begin = sg * part, s_end = min(s_begin + part, n_splits);
     float m = -INFINITY, l = 0.f, o[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] = 0.f;
-    for (int s0 = s_begin; s0 < s_end; s0 += 4) {
-        float2 ml[4];
-        uint4 v[4];
+    auto fold = [&](auto is_wide) __attribute__((always_inline)) {
+        constexpr int WIDE = decltype(is_wide)::value ? 1 : 0;
+        for (int s0 = s_begin; s0 < s_end; s0 += 4) {
+            float2 ml[4];
+            uint4 v[4][1 + WIDE];                        // eight fp16, or eight fp32
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            ml[u] = make_float2(-INFINITY, 0.f);
-            v[u] = make_uint4(0, 0, 0, 0);
-            if (s0 + u < s_end) {
-                const int64_t pr = (int64_t)mr.part_row0 + (int64_t)(s0 + u) * mr.n_q;
-                ml[u] = *reinterpret_cast<const float2 *>(part_ml + (pr * n_q_heads + h) * 2);
-                v[u] = *reinterpret_cast<const uint4 *>(part_o + (pr * n_q_heads + h) * D + 8 * sub);
+            for (int u = 0; u < 4; ++u) {
+                ml[u] = make_float2(-INFINITY, 0.f);
+#pragma unroll
+                for (int k = 0; k <= WIDE; ++k) v[u][k] = make_uint4(0, 0, 0, 0);
+                if (s0 + u < s_end) {
+                    const int64_t pr = (int64_t)mr.part_row0 + (((int64_t)(s0 + u) * mr.n_q) << WIDE);
+                    ml[u] = *reinterpret_cast<const float2 *>(part_ml + (pr * n_q_heads + h) * 2);
+                    const uint4 *src = reinterpret_cast<const uint4 *>(part_o + (pr * n_q_heads + ((int64_t)h << WIDE)) * D + ((8 * sub) << WIDE));
+#pragma unroll
+                    for (int k = 0; k <= WIDE; ++k) v[u][k] = src[k];
+                }
+            }
+            float m_new = m;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, ml[u].x);
+            if (m_new == -INFINITY) continue;
+            const float keep = (m > -INFINITY) ? exp2f(m - m_new) : 0.f;
+            l *= keep;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] *= keep;
+            m = m_new;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {                // in split order
+                const float w = (ml[u].x > -INFINITY) ? ml[u].y * exp2f(ml[u].x - m) : 0.f;
+                l += w;
+                const uint32_t d[4] = {v[u][0].x, v[u][0].y, v[u][0].z, v[u][0].w};
+                if constexpr (WIDE) {
+                    const uint32_t e[4] = {v[u][WIDE].x, v[u][WIDE].y, v[u][WIDE].z, v[u][WIDE].w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { o[j] += __uint_as_float(d[j]) * w; o[j + 4] += __uint_as_float(e[j]) * w; }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        o[2 * j] += (float)__builtin_bit_cast(_Float16, (uint16_t)(d[j] & 0xFFFF)) * w;
+                        o[2 * j + 1] += (float)__builtin_bit_cast(_Float16, (uint16_t)(d[j] >> 16)) * w;
+                    }
+                }
             }
         }
-        float m_new = m;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, ml[u].x);
-        if (m_new == -INFINITY) continue;
-        const float keep = (m > -INFINITY) ? exp2f(m - m_new) : 0.f;
-        l *= keep;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o[j] *= keep;
-        m = m_new;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {                    // in split order
-            const float w = (ml[u].x > -INFINITY) ? ml[u].y * exp2f(ml[u].x - m) : 0.f;
-            l += w;
-            const uint32_t d[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                o[2 * j] += (float)__builtin_bit_cast(_Float16, (uint16_t)(d[j] & 0xFFFF)) * w;
-                o[2 * j + 1] += (float)__builtin_bit_cast(_Float16, (uint16_t)(d[j] >> 16)) * w;
-            }
-        }
-    }
+    };
+    if (mr.n_splits & PC_MERGE_WIDE) fold(std::true_type{});
+    else fold(std::false_type{});
     // parts 0+1 and 2+3, then the two halves; only the lanes of part 0 keep the result
 #pragma unroll
     for (int mask = 16; mask < TPP; mask <<= 1) {

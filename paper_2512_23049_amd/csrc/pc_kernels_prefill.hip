@@ -754,7 +754,29 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     const int ub_e = unit_ok_e ? unit_e / g : 0;
     const int h_e = kh * g + (unit_ok_e ? unit_e - ub_e * g : 0);
     const int row_e = 32 * ub_e + n_e;
-    {
+    if (!whole && cd.part_wide) {                        // fp32 partials: half a row is 256 bytes
+        unsigned char *stg = reinterpret_cast<unsigned char *>(&s_qm[0][0][0]) + wave_s * 8192;
+        const int64_t row0 = (int64_t)cd.part_off + 2 * (int64_t)item.split * cd.n_q;
+        unsigned char *dst = reinterpret_cast<unsigned char *>(L.part_o) + (row0 * L.n_q_heads + 2 * h_e) * (PC_D * 2);
+        const int r4 = lane_e >> 4, c = lane_e & 15;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const f32x16 &a = acc[2 * half + db];
+                    *reinterpret_cast<float4 *>(stg + n_e * 256 + (((8 * db + 2 * q4 + hh_e) ^ (n_e & 15)) << 4)) =
+                        make_float4(a[4 * q4] * inv, a[4 * q4 + 1] * inv, a[4 * q4 + 2] * inv, a[4 * q4 + 3] * inv);
+                }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int r = 4 * i + r4, rw = 32 * ub_e + r;
+                const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * 256 + ((c ^ (r & 15)) << 4));
+                if (unit_ok_e && rw < cd.n_q) *reinterpret_cast<uint4 *>(dst + (int64_t)rw * L.n_q_heads * (PC_D * 4) + half * 256 + 16 * c) = v;
+            }
+        }
+    } else {
         unsigned char *stg = reinterpret_cast<unsigned char *>(&s_qm[0][0][0]) + wave_s * 8192;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -780,7 +802,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     if (whole) {
         if (L.lse) L.lse[((int64_t)cd.q_off + row_e) * L.n_q_heads + h_e] = (l > 0.f) ? (m_ref + log2f(l)) * 0.6931471805599453f : -INFINITY;
     } else {
-        const int64_t pr = (int64_t)cd.part_off + (int64_t)item.split * cd.n_q + row_e;
+        const int64_t pr = (int64_t)cd.part_off + (((int64_t)item.split * cd.n_q + row_e) << cd.part_wide);
         L.part_ml[(pr * L.n_q_heads + h_e) * 2] = (l > 0.f) ? m_ref : -INFINITY;
         L.part_ml[(pr * L.n_q_heads + h_e) * 2 + 1] = l;
     }

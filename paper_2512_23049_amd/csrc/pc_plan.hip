@@ -306,6 +306,51 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
     }
 }
 
+// Tiles a split of the batch's prefill calls takes.  A workgroup fills a compute unit and takes about a start and an end of
+// PRE_FIXED and PRE_TILE a tile (packed walk: PRE_TILE_PACKED), so a launch takes rounds of 256 of them: more splits shorten
+// a round until there is one more of them, and their parts are written, read again and added by one more launch.
+// (us; measured over 20 to 512 rows, 0.3 to 30 thousand tokens, one to four calls.  The rule before, as many splits as
+// reach 256 workgroups, 16 tiles at least, put 1.1 rounds where one does: 200 rows x 64 heads over 3000 tokens
+// 49 us for 5 splits of 56 groups, 33 us for 4.)
+static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups)
+{
+    constexpr double PRE_FIXED = 9.0, PRE_TILE = 1.0, PRE_TILE_PACKED = 0.75, MERGE_FIXED = 4.5, PART_BYTES_US = 3.5e6;
+    constexpr int LEAST = 4;                             // tiles: below, the start is all there is
+    if (pre_groups >= 256) return INT32_MAX;             // the chip is full
+    struct Shape { int64_t groups; int n_q, tiles; };    // consecutive calls of the same rows and tiles
+    std::vector<Shape> shapes;
+    int longest = 0;
+    bool packed = false;
+    for (size_t i = 0; i < P.res.size(); ++i) {
+        const Resolved &r = P.res[i];
+        if (sp.in_shared[i] || (int64_t)r.n_q * c->g <= 16) continue;
+        const int64_t groups = (int64_t)((((r.n_q + 31) / 32) * c->g + P.pre_waves - 1) / P.pre_waves) * c->cfg.n_kv_heads;
+        if (!shapes.empty() && shapes.back().tiles == r.tiles && shapes.back().n_q == r.n_q) shapes.back().groups += groups;
+        else shapes.push_back(Shape{groups, r.n_q, r.tiles});
+        longest = std::max(longest, r.tiles);
+        packed |= !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
+    }
+    const double tile = packed ? PRE_TILE_PACKED : PRE_TILE;
+    int best = std::max(longest, 1), last = 0;
+    double best_us = 0;
+    const int most = (int)std::min<int64_t>({(int64_t)MAX_SPLITS, (int64_t)longest / LEAST, std::max<int64_t>(2, 1024 / pre_groups)});
+    for (int k = 1; k <= std::max(most, 1); ++k) {
+        const int chunk = (std::max(longest, 1) + k - 1) / k;
+        if (chunk == last) continue;
+        last = chunk;
+        int64_t wgs = 0, part = 0;
+        for (const Shape &sh : shapes) {
+            const int ns = std::max(1, (sh.tiles + chunk - 1) / chunk);
+            wgs += sh.groups * ns;
+            if (ns > 1) part += sh.groups * ns * (sh.tiles < 32 ? 2 : 1);
+        }
+        // (a group is 8 units of 32 rows: 8 * 32 * 128 partial outputs of 2 bytes, or 4, written and read)
+        const double us = (double)((wgs + 255) / 256) * (PRE_FIXED + tile * chunk) + (part ? MERGE_FIXED + (double)part * 131072.0 / PART_BYTES_US : 0.0);
+        if (k == 1 || us < best_us) { best_us = us; best = chunk; }
+    }
+    return best;
+}
+
 // Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head) and
 // as many splits of the tiles as fill the chip once (a workgroup fills a compute unit); the key-major kernel takes 4 key
 // tiles a workgroup and splits their units until there are about four workgroups for every compute unit, which evens out
@@ -473,113 +518,136 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         for (int i = 0; i < n_calls; ++i) {
             const Resolved &r = P.res[(size_t)i];
             if (sp.in_shared[(size_t)i]) continue;
-            if (r.n_q * g > 16) pre_groups += (int64_t)(((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves * H_kv;
+            if (r.n_q * g > 16) pre_groups += (int64_t)((((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves) * H_kv;
             else dec_groups += H_kv;
         }
-    for (int i = 0; i < n_calls; ++i) {
-        Resolved &r = P.res[i];
-        PcCallDesc &cd = cds[i];
-        // a call served by the shared walk needs no segments, tiles or rotation rows of its own: the plan
-        // builder sees it as a call that lists nothing
-        const bool own_plan = !sp.in_shared[(size_t)i];
-        cd.sel_off = sel_off; cd.n_sel = own_plan ? (int)r.sel.size() : 0;
-        cd.self_msg = own_plan ? r.self_msg : -1; cd.self_start = r.self_start;
-        cd.n_q = r.n_q; cd.q_off = q_off; cd.seg_off = seg_off; cd.n_seg = cd.n_sel + (cd.self_msg >= 0 ? 1 : 0);
-        cd.self_len = own_plan ? r.self_len : 0; cd.n_splits = 1; cd.part_off = 0; cd.tile_off = (int32_t)total_tiles;
-        cd.kg_tile0 = -1; cd.n_par = 0; cd.rb_off = 0; cd.pad = 0;
-        if (own_plan) total_tiles += r.tiles;
-        sel_off += cd.n_sel; q_off += cd.n_q; seg_off += cd.n_seg;
-        if (!want_items || !bf16 || !own_plan) continue;
-        const int T = r.tiles;
-        if (r.n_q * g <= 16) {                       // decode-shaped: all rows x heads of a KV head in one wave
-            // Attention does not depend on the order the keys are visited in (each keeps its own
-            // position), so a decode call walks its parents in ascending cache-slot order: calls that
-            // share messages then touch them at about the same time and the later ones hit in L2.
-            sort_by_slot(c, r);
-            // as few splits as fill the chip (256 workgroups): the kernel is bound by memory, and every
-            // split beyond that only adds partial results to write and merge
+    auto self_tiles_of = [&](const Resolved &r) { return r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0; };
+    auto parent_tokens = [&](const Resolved &r) { int64_t n = 0; for (const int2 &e : r.sel) n += c->msgs[(size_t)e.x].len; return n; };
+    auto gathers = [&](const Resolved &r) {
+        return r.tiles > 0 && !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
+    };
+    auto pre_groups_of = [&](const Resolved &r) { return (((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves; };
+    int pre_chunk = 1;                                   // tiles a prefill split takes
+    if (want_items && bf16 && pre_groups > 0 && c->prefill_tiles_per_split == 0) pre_chunk = prefill_chunk(c, P, sp, pre_groups);
+    // small_splits: the rules for the number of splits as they stand.  Without it: at least 16 tiles a split and no more
+    // splits than bring the batch to 256 workgroups, which bounds the partial results (see below).
+    auto plan_calls = [&](bool small_splits) {
+        dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear();
+        kg_tiles = part_rows = total_tiles = 0;
+        sel_off = q_off = seg_off = 0;
+        for (int i = 0; i < n_calls; ++i) {
+            Resolved &r = P.res[i];
+            PcCallDesc &cd = cds[i];
+            // a call served by the shared walk needs no segments, tiles or rotation rows of its own: the plan
+            // builder sees it as a call that lists nothing
+            const bool own_plan = !sp.in_shared[(size_t)i];
+            cd.sel_off = sel_off; cd.n_sel = own_plan ? (int)r.sel.size() : 0;
+            cd.self_msg = own_plan ? r.self_msg : -1; cd.self_start = r.self_start;
+            cd.n_q = r.n_q; cd.q_off = q_off; cd.seg_off = seg_off; cd.n_seg = cd.n_sel + (cd.self_msg >= 0 ? 1 : 0);
+            cd.self_len = own_plan ? r.self_len : 0; cd.n_splits = 1; cd.part_off = 0; cd.tile_off = (int32_t)total_tiles;
+            cd.kg_tile0 = -1; cd.n_par = 0; cd.rb_off = 0; cd.part_wide = 0;
+            if (own_plan) total_tiles += r.tiles;
+            sel_off += cd.n_sel; q_off += cd.n_q; seg_off += cd.n_seg;
+            if (!want_items || !bf16 || !own_plan) continue;
+            const int T = r.tiles;
+            if (r.n_q * g <= 16) {                       // decode-shaped: all rows x heads of a KV head in one wave
+                // Attention does not depend on the order the keys are visited in (each keeps its own
+                // position), so a decode call walks its parents in ascending cache-slot order: calls that
+                // share messages then touch them at about the same time and the later ones hit in L2.
+                sort_by_slot(c, r);
+                // as few splits as fill the chip (256 workgroups): the kernel is bound by memory, and every split beyond
+                // that only adds partial results to write and merge.  A split has 4 tiles at least, one a wave: a small
+                // call is a chain of latencies, which shorter runs of tiles shorten by more than the merge launch costs from
+                // 16 tiles on (4 calls over 1300 tokens, 8 KV heads: 18 + 5 us at 16 tiles a split, 10 + 5 at 4).
+                const int least = small_splits ? (T >= 16 ? 4 : T + 1) : 16;
+                int ns = c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
+                                                       : (int)std::min<int64_t>((256 + dec_groups - 1) / dec_groups, std::max(1, T / least));
+                ns = std::max(1, std::min(MAX_SPLITS, ns));
+                const int chunk = std::max(1, (T + ns - 1) / ns);
+                ns = std::max(1, (T + chunk - 1) / chunk);
+                cd.n_splits = ns;
+                for (int s = 0; s < ns; ++s) {
+                    PcItem it{}; it.call = i; it.unit0 = 0; it.tile_begin = s * chunk; it.tile_end = std::min(T, (s + 1) * chunk); it.split = s;
+                    it.tile_tab0 = cd.tile_off;
+                    dec.push_back(it);
+                }
+            } else {
+                // Gather: a call with many query rows reads its keys and values from a packed copy (the gather pass: keys
+                // turned to the call's positions, no padding between messages), which moves 8192 bytes per listed token once
+                // (about 1.8 ns) and saves the turns of the queries at every message, the ragged tile at every message's end
+                // and the per-tile lookups: 15 to 25 % of the attention's own time, which is rows x heads x 0.47 ps per token.
+                // The copy pays from rows x query heads of about 20 thousand on; taken from 32768 on.  (Not with a fixed
+                // workspace, which the copy may not fit into.)
+                const int self_tiles = self_tiles_of(r);
+                const int64_t n_par = parent_tokens(r);
+                const int p_tiles = (int)((n_par + PC_TILE - 1) / PC_TILE);
+                const bool packed = gathers(r) && kg_tiles + p_tiles + self_tiles < ((int64_t)1 << 24);
+                if (packed) {
+                    cd.kg_tile0 = (int32_t)kg_tiles; cd.n_par = (int32_t)n_par;
+                    kg.push_back(PcGatherItem{i, (int32_t)kg_tiles, p_tiles + self_tiles, (int32_t)n_par});
+                    kg_tiles += p_tiles + self_tiles;
+                }
+                const int Tc = packed ? p_tiles + self_tiles : T;        // tiles the attention kernel walks for this call
+                const int units = ((r.n_q + 31) / 32) * g;
+                const int groups = pre_groups_of(r);
+                int ns = 1;
+                if (c->prefill_tiles_per_split > 0) ns = (Tc + c->prefill_tiles_per_split - 1) / c->prefill_tiles_per_split;
+                else if (small_splits) ns = (int)(((int64_t)Tc + pre_chunk - 1) / pre_chunk);
+                else if (pre_groups < 256) ns = (int)std::min<int64_t>((256 + pre_groups - 1) / pre_groups, std::max(1, Tc / 16));
+                ns = std::max(1, std::min(MAX_SPLITS, ns));
+                const int chunk = std::max(1, (Tc + ns - 1) / ns);
+                ns = std::max(1, (Tc + chunk - 1) / chunk);
+                cd.n_splits = ns;
+                // A group of row units walks the parents' tiles and the tiles of the new message up to the
+                // causal limit of its last row (the kernel relies on tile_end being cut there); its splits
+                // divide THAT count evenly, so the groups with early rows do not end up with a nearly empty
+                // last split.
+                const int parent_tiles = Tc - self_tiles;
+                for (int gidx = 0; gidx < groups; ++gidx) {
+                    int Tg = Tc;
+                    if (r.self_msg >= 0) {
+                        const int last_unit = std::min(gidx * P.pre_waves + P.pre_waves - 1, units - 1);
+                        const int lim = (r.self_len - r.n_q) + std::min(32 * (last_unit / g) + 31, r.n_q - 1);   // last own token seen
+                        Tg = parent_tiles + std::min(self_tiles, lim / PC_TILE + 1);
+                    }
+                    const int chunk_g = std::max(1, (Tg + ns - 1) / ns);
+                    for (int s = 0; s < ns; ++s) {
+                        PcItem it{}; it.call = i; it.unit0 = gidx * P.pre_waves; it.split = s; it.tile_tab0 = cd.tile_off;
+                        it.tile_begin = std::min(Tg, s * chunk_g);
+                        it.tile_end = s == ns - 1 ? Tg : std::min(Tg, (s + 1) * chunk_g);
+                        (packed ? pre_pk : pre).push_back(it);
+                    }
+                }
+            }
+            // Partial results are fp32 where 16 tiles a split would not have split the call at all, so that no sum is held
+            // in fewer bits for being split; the others, fp16, are bound by the bytes they move (512 rows x 32 heads in
+            // 4 splits: 17 MB, 8 us).
+            const int tuned = r.n_q * g <= 16 ? c->decode_tiles_per_split : c->prefill_tiles_per_split;
+            cd.part_wide = cd.n_splits > 1 && small_splits && tuned == 0 && T < 32;
+            if (cd.n_splits > 1) { cd.part_off = (int32_t)part_rows; part_rows += ((int64_t)cd.n_splits * cd.n_q) << cd.part_wide; }
+        }
+        // shared groups: as many splits of the union as fill the chip together
+        for (size_t gi = 0; gi < sp.groups.size(); ++gi) {
+            PcShGroup &gr = sp.groups[gi];
+            const int T = gr.n_tiles;
             int ns = c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
-                                                   : (int)std::min<int64_t>((256 + dec_groups - 1) / dec_groups, std::max(1, T / 16));
+                                                   : (int)std::min<int64_t>((256 + (int64_t)sp.groups.size() * H_kv - 1) / ((int64_t)sp.groups.size() * H_kv),
+                                                                            std::max(1, T / 8));
             ns = std::max(1, std::min(MAX_SPLITS, ns));
             const int chunk = std::max(1, (T + ns - 1) / ns);
             ns = std::max(1, (T + chunk - 1) / chunk);
-            cd.n_splits = ns;
-            for (int s = 0; s < ns; ++s) {
-                PcItem it{}; it.call = i; it.unit0 = 0; it.tile_begin = s * chunk; it.tile_end = std::min(T, (s + 1) * chunk); it.split = s;
-                it.tile_tab0 = cd.tile_off;
-                dec.push_back(it);
-            }
-        } else {
-            // Gather: a call with many query rows reads its keys and values from a packed copy (the gather pass: keys
-            // turned to the call's positions, no padding between messages), which moves 8192 bytes per listed token once
-            // (about 1.8 ns) and saves the turns of the queries at every message, the ragged tile at every message's end
-            // and the per-tile lookups: 15 to 25 % of the attention's own time, which is rows x heads x 0.47 ps per token.
-            // The copy pays from rows x query heads of about 20 thousand on; taken from 32768 on.  (Not with a fixed
-            // workspace, which the copy may not fit into.)
-            const int self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0;
-            int64_t n_par = 0;
-            for (const int2 &e : r.sel) n_par += c->msgs[(size_t)e.x].len;
-            const int p_tiles = (int)((n_par + PC_TILE - 1) / PC_TILE);
-            const bool packed = T > 0 && !P.fixed_ws && kg_tiles + p_tiles + self_tiles < ((int64_t)1 << 24) &&
-                                (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
-            if (packed) {
-                cd.kg_tile0 = (int32_t)kg_tiles; cd.n_par = (int32_t)n_par;
-                kg.push_back(PcGatherItem{i, (int32_t)kg_tiles, p_tiles + self_tiles, (int32_t)n_par});
-                kg_tiles += p_tiles + self_tiles;
-            }
-            const int Tc = packed ? p_tiles + self_tiles : T;        // tiles the attention kernel walks for this call
-            const int units = ((r.n_q + 31) / 32) * g;
-            const int groups = (units + P.pre_waves - 1) / P.pre_waves;
-            int ns = 1;
-            if (c->prefill_tiles_per_split > 0) ns = (Tc + c->prefill_tiles_per_split - 1) / c->prefill_tiles_per_split;
-            else if (pre_groups < 256) ns = (int)std::min<int64_t>((256 + pre_groups - 1) / pre_groups, std::max(1, Tc / 16));
-            ns = std::max(1, std::min(MAX_SPLITS, ns));
-            const int chunk = std::max(1, (Tc + ns - 1) / ns);
-            ns = std::max(1, (Tc + chunk - 1) / chunk);
-            cd.n_splits = ns;
-            // A group of row units walks the parents' tiles and the tiles of the new message up to the
-            // causal limit of its last row (the kernel relies on tile_end being cut there); its splits
-            // divide THAT count evenly, so the groups with early rows do not end up with a nearly empty
-            // last split.
-            const int parent_tiles = Tc - self_tiles;
-            for (int gidx = 0; gidx < groups; ++gidx) {
-                int Tg = Tc;
-                if (r.self_msg >= 0) {
-                    const int last_unit = std::min(gidx * P.pre_waves + P.pre_waves - 1, units - 1);
-                    const int lim = (r.self_len - r.n_q) + std::min(32 * (last_unit / g) + 31, r.n_q - 1);   // last own token seen
-                    Tg = parent_tiles + std::min(self_tiles, lim / PC_TILE + 1);
-                }
-                const int chunk_g = std::max(1, (Tg + ns - 1) / ns);
-                for (int s = 0; s < ns; ++s) {
-                    PcItem it{}; it.call = i; it.unit0 = gidx * P.pre_waves; it.split = s; it.tile_tab0 = cd.tile_off;
-                    it.tile_begin = std::min(Tg, s * chunk_g);
-                    it.tile_end = s == ns - 1 ? Tg : std::min(Tg, (s + 1) * chunk_g);
-                    (packed ? pre_pk : pre).push_back(it);
-                }
+            gr.n_splits = ns;
+            if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += (int64_t)ns * gr.n_rows; }
+            int seg = 0;                                     // the message that owns a split's first tile (splits ascend)
+            for (int sidx = 0; sidx < ns; ++sidx) {
+                const int t0 = sidx * chunk;
+                while (seg + 1 < gr.n_seg && sp.segs[(size_t)gr.seg_off + (size_t)seg + 1].tile_off <= t0) ++seg;
+                sp.items.push_back(PcShItem{(int32_t)gi, t0, std::min(T, (sidx + 1) * chunk), sidx, seg, {0, 0, 0}});
             }
         }
-        if (cd.n_splits > 1) { cd.part_off = (int32_t)part_rows; part_rows += (int64_t)cd.n_splits * cd.n_q; }
-    }
-    // shared groups: as many splits of the union as fill the chip together
-    for (size_t gi = 0; gi < sp.groups.size(); ++gi) {
-        PcShGroup &gr = sp.groups[gi];
-        const int T = gr.n_tiles;
-        int ns = c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
-                                               : (int)std::min<int64_t>((256 + (int64_t)sp.groups.size() * H_kv - 1) / ((int64_t)sp.groups.size() * H_kv),
-                                                                        std::max(1, T / 8));
-        ns = std::max(1, std::min(MAX_SPLITS, ns));
-        const int chunk = std::max(1, (T + ns - 1) / ns);
-        ns = std::max(1, (T + chunk - 1) / chunk);
-        gr.n_splits = ns;
-        if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += (int64_t)ns * gr.n_rows; }
-        int seg = 0;                                     // the message that owns a split's first tile (splits ascend)
-        for (int sidx = 0; sidx < ns; ++sidx) {
-            const int t0 = sidx * chunk;
-            while (seg + 1 < gr.n_seg && sp.segs[(size_t)gr.seg_off + (size_t)seg + 1].tile_off <= t0) ++seg;
-            sp.items.push_back(PcShItem{(int32_t)gi, t0, std::min(T, (sidx + 1) * chunk), sidx, seg, {0, 0, 0}});
-        }
-    }
+    };
     BwdPlan bp;
+    plan_calls(true);
     if (P.backward && bf16) plan_backward(c, P, cds, bp);
     if (want_items && !bf16) plan_f32(c, P, cds, true, pre, part_rows);
     if (P.backward && !bf16) {
@@ -587,25 +655,35 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         plan_backward_keys_f32(c, P, bp.keys);
         P.n_bwd_keys = (int)bp.keys.size();
     }
-    if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
-    P.total_sel = sel_off; P.total_seg = seg_off;
     if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
-    P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-    P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
-    P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
-    if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
     auto lay_out = [&]() {
+        P.total_sel = sel_off; P.total_seg = seg_off;
+        P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
+        P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
+        P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
         P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
                             sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
                             bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float));
     };
     lay_out();
-    if (!bf16 && part_rows > 0 && P.fixed_ws && P.lay.total > P.fixed_cap) {     // the partials are what does not fit: an unsplit walk needs none
-        plan_f32(c, P, cds, false, pre, part_rows);
-        P.n_pre = (int)pre.size();
-        lay_out();
+    // A fixed workspace holds what it held under the bounded rule, which decides whether a batch fits; one that fits takes
+    // the splits of pc_attend (and returns the same bits) as long as their partial results fit as well.
+    if (P.fixed_ws && want_items && !c->host_only) {
+        auto fits = [&]() { return P.lay.total <= P.fixed_cap && P.lay.h2d_bytes <= c->stage[c->stage_next].cap; };
+        auto plan_items = [&](bool small_splits) {
+            plan_calls(small_splits);
+            if (!bf16) plan_f32(c, P, cds, small_splits, pre, part_rows);
+            lay_out();
+        };
+        plan_items(false);
+        if (fits()) {
+            plan_items(true);
+            if (!fits()) plan_items(false);
+        }
     }
+    if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
+    if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (c->host_only) return PC_OK;
 
     int32_t rc = PC_OK;
@@ -641,7 +719,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         for (int i = 0; i < n_calls; ++i)
             if (wanted(cds[i].n_splits))
                 for (int q = 0; q < P.res[i].n_q; ++q)
-                    hm[P.n_merge_rows++] = PcMergeRow{cds[i].q_off + q, cds[i].part_off + q, cds[i].n_splits, P.res[i].n_q};
+                    hm[P.n_merge_rows++] = PcMergeRow{cds[i].q_off + q, cds[i].part_off + (q << cds[i].part_wide),
+                                                      cds[i].n_splits | (cds[i].part_wide ? PC_MERGE_WIDE : 0), P.res[i].n_q};
         for (const PcShGroup &gr : sp.groups)
             if (wanted(gr.n_splits))
                 for (int q = 0; q < gr.n_rows; ++q) hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + q, gr.n_splits, gr.n_rows};
