@@ -35,6 +35,11 @@ struct PcTokenItem {
     int32_t new_len;          // the message's length once this token is in
 };
 
+// Small host-built lists travel in a kernel's arguments: no staging buffer, copy or event (a copy and its event cost the host
+// 8 us and the stream 3 us of copy kernel and a gap).  The limit of a kernel's arguments is 4 KB.
+#define PC_ARG_BYTES 3584
+struct PcArgBlob { uint4 w[PC_ARG_BYTES / 16]; };
+
 #define PC_TOKEN_PACK 128     // token items that travel in a kernel's arguments (2 KB)
 struct PcTokenPack { PcTokenItem it[PC_TOKEN_PACK]; };
 

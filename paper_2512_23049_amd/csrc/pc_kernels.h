@@ -10,7 +10,8 @@ void pc_launch_append(int dtype, const void *k, const void *v, int len, int rows
                       void *v_store, PcMsgEntry *table, int msg_id, hipStream_t st);
 
 // several whole messages in one launch
-void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_rows, int n_kv_heads, int D,
+// (host_items: the same list in host memory, or null; short lists are then passed in the kernel's arguments and `items` is not read)
+void pc_launch_append_batch(int dtype, const PcAppendItem *items, const PcAppendItem *host_items, int n_items, int max_rows, int n_kv_heads, int D,
                             int64_t slots, const double *inv_freq, void *k_store, void *v_store, PcMsgEntry *table,
                             hipStream_t st);
 
@@ -48,6 +49,12 @@ void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
                           float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st);
+// the same with the staged block (h2d_bytes <= PC_ARG_BYTES, at the start of the workspace) in the kernel's arguments: calls,
+// sel, q_pos and tok.items are addresses within the workspace, which the kernel fills for the kernels behind it
+void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
+                              PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
+                              int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
+                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st);
 
 void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, int n_seg, int64_t n_kv,
                              int32_t *kv_slot, int32_t *kv_pos, hipStream_t st);

@@ -4,6 +4,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 // ----------------------------------------------------------------------------------
@@ -169,12 +170,20 @@ __global__ __launch_bounds__(256) void pc_append_f32_kernel(
 // Several messages in one launch (Sec. 2.4 "Parallel API Calls": the new messages of parallel
 // calls arrive together): blockIdx.z names the message, the blocks of a (part, message) walk
 // its threads with a grid stride.
-template <typename T>
+// List: a device pointer, or the items themselves as the kernel's first arguments.
+template <typename T, typename List>
 __global__ __launch_bounds__(256) void pc_append_batch_kernel(
-    const PcAppendItem *__restrict__ items, int n_kv_heads, int D, int64_t slots,
+    const List items, int n_kv_heads, int D, int64_t slots,
     const double *__restrict__ inv_freq, T *__restrict__ k_store, T *__restrict__ v_store, PcMsgEntry *__restrict__ table)
 {
-    const PcAppendItem it = items[blockIdx.z];
+    PcAppendItem it;
+    if constexpr (std::is_same<List, PcArgBlob>::value) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        static_assert(sizeof(PcAppendItem) == 32, "two 16-byte pieces");
+        const __attribute__((address_space(4))) i32x4 *p = (const __attribute__((address_space(4))) i32x4 *)__builtin_amdgcn_kernarg_segment_ptr() + 2 * blockIdx.z;
+        const struct { i32x4 a, b; } w = {p[0], p[1]};
+        it = __builtin_bit_cast(PcAppendItem, w);
+    } else it = items[blockIdx.z];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         table[it.msg].slot_start = it.slot_start; table[it.msg].len = it.len; table[it.msg].base_pos = 0;
     }
@@ -196,7 +205,7 @@ __global__ __launch_bounds__(256) void pc_append_batch_kernel(
     }
 }
 
-void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, int max_rows, int n_kv_heads, int D,
+void pc_launch_append_batch(int dtype, const PcAppendItem *items, const PcAppendItem *host_items, int n_items, int max_rows, int n_kv_heads, int D,
                             int64_t slots, const double *inv_freq, void *k_store, void *v_store, PcMsgEntry *table,
                             hipStream_t st)
 {
@@ -204,16 +213,24 @@ void pc_launch_append_batch(int dtype, const PcAppendItem *items, int n_items, i
     // (bf16: the K part takes APP_TB tokens per block step, which is more blocks than the V part needs)
     const int64_t per = dtype == 1 ? ((int64_t)max_rows + APP_TB - 1) / APP_TB : ((int64_t)max_rows * n_kv_heads * D + 255) / 256;
     const unsigned bx = (unsigned)std::min<int64_t>(std::max<int64_t>(per, 1), 256);
-    for (int first = 0; first < n_items; first += 65535) {            // grid.z is limited to 65535
-        const int n = n_items - first < 65535 ? n_items - first : 65535;
+    auto launch = [&](const auto &list, int n) {
+        using List = std::decay_t<decltype(list)>;
         dim3 grid(bx, 2, (unsigned)n);
         if (dtype == 1)
-            pc_append_batch_kernel<uint16_t><<<grid, 256, 0, st>>>(items + first, n_kv_heads, D, slots, inv_freq,
-                                                                   (uint16_t *)k_store, (uint16_t *)v_store, table);
+            pc_append_batch_kernel<uint16_t, List><<<grid, 256, 0, st>>>(list, n_kv_heads, D, slots, inv_freq,
+                                                                         (uint16_t *)k_store, (uint16_t *)v_store, table);
         else
-            pc_append_batch_kernel<float><<<grid, 256, 0, st>>>(items + first, n_kv_heads, D, slots, inv_freq,
-                                                                (float *)k_store, (float *)v_store, table);
+            pc_append_batch_kernel<float, List><<<grid, 256, 0, st>>>(list, n_kv_heads, D, slots, inv_freq,
+                                                                      (float *)k_store, (float *)v_store, table);
+    };
+    if (host_items) {                                    // (the caller checked that they fit)
+        PcArgBlob blob;
+        std::memcpy(blob.w, host_items, sizeof(PcAppendItem) * (size_t)n_items);
+        launch(blob, n_items);
+        return;
     }
+    for (int first = 0; first < n_items; first += 65535)             // grid.z is limited to 65535
+        launch(items + first, n_items - first < 65535 ? n_items - first : 65535);
 }
 
 void pc_launch_append(int dtype, const void *k, const void *v, int len, int rows, int n_kv_heads, int D,
@@ -478,12 +495,12 @@ void pc_launch_reposition_batch(int dtype, const PcMoveItem *items, int n_items,
 // ----------------------------------------------------------------------------------
 // Blocks [tok_block0, ...) (a decode step only): the step's new tokens go into the cache in the same launch; the plan
 // blocks never read what they write (the grown messages' new lengths travel with the calls from the host).
-__global__ __launch_bounds__(256) void pc_build_plan_kernel(
-    const PcCallDesc *__restrict__ calls, int n_calls, const int2 *__restrict__ sel,
-    const int32_t *__restrict__ q_pos, PcMsgEntry *__restrict__ table,
+__device__ __forceinline__ void build_plan_block(
+    const PcCallDesc *calls, int n_calls, const int2 *sel,
+    const int32_t *q_pos, const PcTokenItem *tok_items, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
-    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0)
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, const PcTokenWork &tok, int tok_block0)
 {
     if ((int)blockIdx.x >= tok_block0) {
         const int per_row = tok.D / 4;
@@ -492,10 +509,10 @@ __global__ __launch_bounds__(256) void pc_build_plan_kernel(
         const int j = (int)(tid / ((int64_t)per_row * tok.n_kv_heads));
         const int hh = (int)((tid / per_row) % tok.n_kv_heads), i0 = 2 * (int)(tid % per_row);
         if (tok.dtype == 1)
-            append_token_thread<uint16_t>(tok.items[j], j, hh, i0, (const uint16_t *)tok.k, (const uint16_t *)tok.v, tok.n_kv_heads, tok.D,
+            append_token_thread<uint16_t>(tok_items[j], j, hh, i0, (const uint16_t *)tok.k, (const uint16_t *)tok.v, tok.n_kv_heads, tok.D,
                                           tok.slots, inv_freq, (uint16_t *)tok.k_store, (uint16_t *)tok.v_store, table);
         else
-            append_token_thread<float>(tok.items[j], j, hh, i0, (const float *)tok.k, (const float *)tok.v, tok.n_kv_heads, tok.D,
+            append_token_thread<float>(tok_items[j], j, hh, i0, (const float *)tok.k, (const float *)tok.v, tok.n_kv_heads, tok.D,
                                        tok.slots, inv_freq, (float *)tok.k_store, (float *)tok.v_store, table);
         return;
     }
@@ -621,17 +638,72 @@ __global__ __launch_bounds__(256) void pc_build_plan_kernel(
     }
 }
 
+__global__ __launch_bounds__(256) void pc_build_plan_kernel(
+    const PcCallDesc *__restrict__ calls, int n_calls, const int2 *__restrict__ sel,
+    const int32_t *__restrict__ q_pos, PcMsgEntry *__restrict__ table,
+    const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
+    PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0)
+{
+    build_plan_block(calls, n_calls, sel, q_pos, tok.items, table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles,
+                     tok, tok_block0);
+}
+
+// The staged block comes in the kernel's arguments (its first ones: the start of the kernarg segment).  Every block takes it
+// to LDS, 16 bytes a thread, and works from there; the last one writes it to the workspace, where the attention kernels read
+// their work items.
+__global__ __launch_bounds__(256) void pc_build_plan_arg_kernel(
+    const PcArgBlob blob, uint4 *__restrict__ ws, int n16, int off_calls, int n_calls, int off_sel, int off_q_pos, int off_tok, PcMsgEntry *__restrict__ table,
+    const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
+    PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0)
+{
+    __shared__ uint4 s_blob[PC_ARG_BYTES / 16];
+    static_assert(PC_ARG_BYTES <= 256 * 16, "one piece a thread");
+    if ((int)threadIdx.x < n16) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        const i32x4 w = ((const __attribute__((address_space(4))) i32x4 *)__builtin_amdgcn_kernarg_segment_ptr())[threadIdx.x];
+        const uint4 u = make_uint4((unsigned)w.x, (unsigned)w.y, (unsigned)w.z, (unsigned)w.w);
+        if (blockIdx.x == gridDim.x - 1) ws[threadIdx.x] = u;
+        s_blob[threadIdx.x] = u;
+    }
+    if (blockIdx.x == gridDim.x - 1) return;
+    __syncthreads();
+    const char *b = reinterpret_cast<const char *>(s_blob);
+    build_plan_block(reinterpret_cast<const PcCallDesc *>(b + off_calls), n_calls, reinterpret_cast<const int2 *>(b + off_sel),
+                     reinterpret_cast<const int32_t *>(b + off_q_pos), reinterpret_cast<const PcTokenItem *>(b + off_tok), table, inv_freq, half, total_seg,
+                     total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
+}
+
+static unsigned plan_blocks(int n_calls, int half, int total_seg, int total_q, const PcTokenWork &tok, int &tok_block0)
+{
+    const int64_t n_rot = ((int64_t)total_seg + total_q) * half;
+    tok_block0 = (int)(n_calls + (n_rot + 255) / 256);
+    const int64_t tok_threads = (int64_t)tok.n * tok.n_kv_heads * (tok.D / 4);
+    return (unsigned)tok_block0 + (unsigned)((tok_threads + 255) / 256);
+}
+
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
                           float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st)
 {
-    const int64_t n_rot = ((int64_t)total_seg + total_q) * half;
-    const unsigned plan_blocks = (unsigned)(n_calls + (n_rot + 255) / 256);
-    const int64_t tok_threads = (int64_t)tok.n * tok.n_kv_heads * (tok.D / 4);
-    const unsigned grid = plan_blocks + (unsigned)((tok_threads + 255) / 256);
+    int tok_block0 = 0;
+    const unsigned grid = plan_blocks(n_calls, half, total_seg, total_q, tok, tok_block0);
     pc_build_plan_kernel<<<grid, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
-                                               total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, (int)plan_blocks);
+                                               total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
+}
+
+void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
+                              PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
+                              int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
+                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st)
+{
+    int tok_block0 = 0;
+    const unsigned grid = plan_blocks(n_calls, half, total_seg, total_q, tok, tok_block0) + 1;
+    auto off = [&](const void *p) { return p ? (int)((const char *)p - (const char *)ws) : 0; };
+    pc_build_plan_arg_kernel<<<grid, 256, 0, st>>>(blob, (uint4 *)ws, (int)((h2d_bytes + 15) / 16), off(calls), n_calls, off(sel), off(q_pos), off(tok.items),
+                                                   table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
 }
 
 // ----------------------------------------------------------------------------------

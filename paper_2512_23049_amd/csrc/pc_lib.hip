@@ -287,10 +287,11 @@ int32_t pc_append_messages(pc_cache *c, int32_t n, const void *const *k, const v
     }
     if (!c->host_only) {
         hipStream_t st = (hipStream_t)stream;
-        const int32_t rc = pc_stage_items(c, items.data(), sizeof(PcAppendItem) * (size_t)n, st);
+        const bool in_args = sizeof(PcAppendItem) * (size_t)n <= PC_ARG_BYTES;
+        const int32_t rc = in_args ? PC_OK : pc_stage_items(c, items.data(), sizeof(PcAppendItem) * (size_t)n, st);
         if (rc != PC_OK) return rc;
         ProfScope ps(c, 0, st);
-        pc_launch_append_batch(c->cfg.dtype, (const PcAppendItem *)c->tok_dev, n, max_rows, c->cfg.n_kv_heads, c->D, c->slots,
+        pc_launch_append_batch(c->cfg.dtype, (const PcAppendItem *)c->tok_dev, in_args ? items.data() : nullptr, n, max_rows, c->cfg.n_kv_heads, c->D, c->slots,
                                c->inv_freq_dev, c->k_store, c->v_store, c->table_dev, st);
         PC_HIP(c, hipGetLastError());
     }

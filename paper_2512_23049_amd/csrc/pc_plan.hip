@@ -97,27 +97,30 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
                        int64_t part_rows, int64_t total_tiles, int H_q, int D,
                        size_t n_sh_groups = 0, size_t n_sh_segs = 0, size_t n_sh_items = 0, size_t n_sh_pos = 0,
                        size_t n_kg_items = 0, int64_t kg_tiles = 0, int H_kv = 1, size_t n_tok = 0,
-                       size_t n_bwd_rb = 0, size_t n_bwd_keys = 0, size_t bwd_units = 0, size_t bwd_splits = 0, size_t part_esize = sizeof(uint16_t))
+                       size_t n_bwd_rb = 0, size_t n_bwd_keys = 0, size_t bwd_units = 0, size_t bwd_splits = 0, size_t part_esize = sizeof(uint16_t), size_t n_merge = 0)
 {
     PlanLayout L{};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    L.calls = take(sizeof(PcCallDesc) * (size_t)std::max(n_calls, 1));
-    L.sel = take(sizeof(int2) * (size_t)std::max(total_sel, 1));
-    L.q_pos = take(sizeof(int32_t) * (size_t)std::max(total_q, 1));
-    L.merge_rows = take(sizeof(PcMergeRow) * (size_t)std::max(total_q, 1));
-    L.items_dec = take(sizeof(PcItem) * (size_t)std::max(n_dec, 1));
-    L.items_pre = take(sizeof(PcItem) * (size_t)std::max(n_pre, 1));
-    L.items_pk = take(sizeof(PcItem) * (size_t)std::max(n_pre_pk, 1));
-    L.sh_groups = take(sizeof(PcShGroup) * std::max<size_t>(n_sh_groups, 1));
-    L.sh_segs = take(sizeof(PcShSeg) * std::max<size_t>(n_sh_segs, 1));
-    L.sh_items = take(sizeof(PcShItem) * std::max<size_t>(n_sh_items, 1));
-    L.sh_pos = take(sizeof(int32_t) * std::max<size_t>(n_sh_pos, 1));
-    L.kg_items = take(sizeof(PcGatherItem) * std::max<size_t>(n_kg_items, 1));
-    L.tok_items = take(sizeof(PcTokenItem) * std::max<size_t>(n_tok, 1));
-    L.bwd_rb = take(sizeof(int2) * n_bwd_rb);
-    L.bwd_keys = take(sizeof(PcBwdKeyItem) * n_bwd_keys);
+    // staged: arrays in 32-byte steps, nothing for a list that is empty (small blocks travel in the plan builder's arguments)
+    auto put = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 32); return at; };
+    L.calls = put(sizeof(PcCallDesc) * (size_t)n_calls);
+    L.sel = put(sizeof(int2) * (size_t)total_sel);
+    L.q_pos = put(sizeof(int32_t) * (size_t)total_q);
+    L.merge_rows = put(sizeof(PcMergeRow) * n_merge);
+    L.items_dec = put(sizeof(PcItem) * (size_t)n_dec);
+    L.items_pre = put(sizeof(PcItem) * (size_t)n_pre);
+    L.items_pk = put(sizeof(PcItem) * (size_t)n_pre_pk);
+    L.sh_groups = put(sizeof(PcShGroup) * n_sh_groups);
+    L.sh_segs = put(sizeof(PcShSeg) * n_sh_segs);
+    L.sh_items = put(sizeof(PcShItem) * n_sh_items);
+    L.sh_pos = put(sizeof(int32_t) * n_sh_pos);
+    L.kg_items = put(sizeof(PcGatherItem) * n_kg_items);
+    L.tok_items = put(sizeof(PcTokenItem) * n_tok);
+    L.bwd_rb = put(sizeof(int2) * n_bwd_rb);
+    L.bwd_keys = put(sizeof(PcBwdKeyItem) * n_bwd_keys);
     L.h2d_bytes = o;
+    o = align_up(o, 256);
     L.segs = take(sizeof(PcSegment) * (size_t)std::max(total_seg, 1));
     L.seg_kvoff = take(sizeof(int32_t) * (size_t)std::max(total_seg, 1));
     L.rot_seg = take(sizeof(float2) * (size_t)std::max(total_seg, 1) * (D / 2));
@@ -662,9 +665,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
         P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
         P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
+        size_t n_merge = 0;
+        for (int i = 0; i < n_calls && want_items; ++i) if (cds[(size_t)i].n_splits > 1) n_merge += (size_t)cds[(size_t)i].n_q;
+        for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) n_merge += (size_t)gr.n_rows;
         P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
                             sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
-                            bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float));
+                            bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
     };
     lay_out();
     // A fixed workspace holds what it held under the bounded rule, which decides whether a batch fits; one that fits takes
@@ -701,9 +707,13 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         P.ws = c->ws;
     }
     StageSlot *slot = nullptr;
-    rc = pc_stage_acquire(c, P.lay.h2d_bytes, &slot);
-    if (rc != PC_OK) return rc;
-    char *h = (char *)slot->host;
+    PcArgBlob blob;
+    const bool in_args = P.lay.h2d_bytes <= PC_ARG_BYTES && P.n_sh_items == 0;
+    if (!in_args) {
+        rc = pc_stage_acquire(c, P.lay.h2d_bytes, &slot);
+        if (rc != PC_OK) return rc;
+    }
+    char *h = in_args ? (char *)blob.w : (char *)slot->host;
     std::memcpy(h + P.lay.calls, cds.data(), sizeof(PcCallDesc) * cds.size());
     int2 *hs = (int2 *)(h + P.lay.sel);
     int32_t *hq = (int32_t *)(h + P.lay.q_pos);
@@ -714,7 +724,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         std::memcpy(hq + cds[i].q_off, r.q_pos.data(), sizeof(int32_t) * r.q_pos.size());
     }
     // rows to merge: those with few splits first, then those with many (they get four lanes per 8 dimensions)
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < 2 && want_items; ++pass) {
         auto wanted = [&](int n_splits) { return n_splits > 1 && (n_splits > MERGE_MANY_SPLITS) == (pass == 1); };
         for (int i = 0; i < n_calls; ++i)
             if (wanted(cds[i].n_splits))
@@ -739,9 +749,11 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         std::memcpy(h + P.lay.sh_items, sp.items.data(), sizeof(PcShItem) * sp.items.size());
         std::memcpy(h + P.lay.sh_pos, sp.pos.data(), sizeof(int32_t) * sp.pos.size());
     }
-    PC_HIP(c, hipMemcpyAsync(P.ws, h, P.lay.h2d_bytes, hipMemcpyHostToDevice, st));
-    PC_HIP(c, hipEventRecord(slot->ev, st));
-    slot->used = true;
+    if (!in_args) {
+        PC_HIP(c, hipMemcpyAsync(P.ws, h, P.lay.h2d_bytes, hipMemcpyHostToDevice, st));
+        PC_HIP(c, hipEventRecord(slot->ev, st));
+        slot->used = true;
+    }
     {
         ProfScope ps(c, 1, st);
         char *w = (char *)P.ws;
@@ -751,11 +763,15 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             tok.k = P.tok_k; tok.v = P.tok_v; tok.k_store = c->k_store; tok.v_store = c->v_store;
             tok.slots = c->slots; tok.n_kv_heads = c->cfg.n_kv_heads; tok.D = c->D; tok.dtype = c->cfg.dtype;
         }
-        pc_launch_build_plan((const PcCallDesc *)(w + P.lay.calls), n_calls, (const int2 *)(w + P.lay.sel),
-                             (const int32_t *)(w + P.lay.q_pos), c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                             P.total_q, (PcSegment *)(w + P.lay.segs), (int32_t *)(w + P.lay.seg_kvoff),
-                             (float2 *)(w + P.lay.rot_seg), (float2 *)(w + P.lay.rot_q),
-                             c->cfg.head_dim == 128 ? (float2 *)(w + P.lay.rot_qw) : nullptr, (PcTile *)(w + P.lay.tiles), tok, st);
+        auto build = [&](auto launch, auto &&...first) {
+            launch(first..., (const PcCallDesc *)(w + P.lay.calls), n_calls, (const int2 *)(w + P.lay.sel),
+                   (const int32_t *)(w + P.lay.q_pos), c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
+                   P.total_q, (PcSegment *)(w + P.lay.segs), (int32_t *)(w + P.lay.seg_kvoff),
+                   (float2 *)(w + P.lay.rot_seg), (float2 *)(w + P.lay.rot_q),
+                   c->cfg.head_dim == 128 ? (float2 *)(w + P.lay.rot_qw) : nullptr, (PcTile *)(w + P.lay.tiles), tok, st);
+        };
+        if (in_args) build(pc_launch_build_plan_arg, blob, P.ws, P.lay.h2d_bytes);
+        else build(pc_launch_build_plan);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
         if (P.n_sh_items > 0) {
