@@ -14,7 +14,10 @@ SOURCES = ["pc_lib.hip", "pc_plan.hip", "pc_attend.hip", "pc_kernels_basic.hip",
            "pc_kernels_shared.hip"]
 # the prefill kernel never produces NaNs in its max reductions: let the compiler drop the
 # canonicalising v_max x, x in front of every fmax
-FILE_FLAGS = {"pc_kernels_prefill.hip": ["-fno-honor-nans"]}
+# the gradient's key kernels hold more than 256 registers: results of their matrix instructions stay in vector registers
+# (with the compiler's own choice all accumulators are copied between the two halves of the file for every column block)
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+FILE_FLAGS = {"pc_kernels_prefill.hip": ["-fno-honor-nans"], "pc_kernels_bwd_mfma.hip": VGPR_FORM, "pc_kernels_backward.hip": VGPR_FORM}
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-result"]

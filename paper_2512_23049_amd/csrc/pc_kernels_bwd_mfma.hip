@@ -21,8 +21,10 @@
 //   finish    sum of the dq partials, turned back by the rows' positions
 //   keys      per (4 key tiles, KV head, split of the row units): dK and dV         (128)
 // A unit is 32 rows of one head, a tile 32 keys.  The walks are bound by the matrix pipe (216 MFMAs of 32 cycles per
-// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads: prep 12, rows<0> 116,
-// rows<1> 249, finish 11, keys 442 us; plain vector kernels (a thread per key, an FMA per product, strided 2-byte reads
+// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads: prep 12, rows<0> 98,
+// rows<1> 209, finish 9, keys 373 us (116, 249 and 442 while the splits spilled into a second round of workgroups, every
+// piece of a flushed dq partial waited for the one before it and the key kernel's accumulators were copied between the
+// halves of the register file); plain vector kernels (a thread per key, an FMA per product, strided 2-byte reads
 // of V) took 31.4 ms.
 //
 // All operands that a product needs with its indices the other way round (V by dimension, keys, queries and output
@@ -109,6 +111,21 @@ struct RowMajor {
     {
         return read_tr((col_at[0] ^ (db << 6)) + tile + s * 4096, (col_at[1] ^ (db << 6)) + tile + s * 4096);
     }
+    // the same with the addresses of a tile made once: `at` the tile's position behind them, a constant
+    struct Cols { unsigned base[4][2]; };
+    __device__ Cols cols(unsigned tile) const
+    {
+        Cols c;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                c.base[db][e] = (col_at[e] ^ (db << 6)) + tile;
+                asm volatile("" : "+v"(c.base[db][e]));  // (or every read gets an addition of its own)
+            }
+        return c;
+    }
+    static __device__ bf16x8 by_col(const Cols &c, unsigned at, int s, int db) { return read_tr(c.base[db][0] + (at + s * 4096), c.base[db][1] + (at + s * 4096)); }
 };
 // the row of the first product's left operand this lane reads: rows are permuted so that result registers 0..7 / 8..15
 // of a lane are rows 8 hh + 0..7 / 16 + 8 hh + 0..7, the order in which the second product takes them
@@ -270,27 +287,30 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
     auto flush = [&](int seg) __attribute__((always_inline)) {
         if constexpr (DQ) {
             const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2) + 4 * hh);
+            // (all of the old partial is requested before any of the new one is stored: a store in between would make each
+            // load wait for the one before it, eight round trips to memory instead of one)
+            float4 old[16];
+            if (!first)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) old[i] = part[i * 64];
+            else
+#pragma unroll
+                for (int i = 0; i < 16; ++i) old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int db = 0; db < 2; ++db)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     const float4 c0 = rs[16 * db + 4 * q4], c1 = rs[16 * db + 4 * q4 + 1];
                     const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sx[4] = {c0.y, c0.w, c1.y, c1.w};
-                    float lo[4], hi[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const float a = acc[db][4 * q4 + i] * B.scale, b = acc[db + 2][4 * q4 + i] * B.scale;
-                        lo[i] = a * cx[i] - b * sx[i]; hi[i] = a * sx[i] + b * cx[i];
+                        float *ol = reinterpret_cast<float *>(&old[db * 4 + q4]), *oh = reinterpret_cast<float *>(&old[db * 4 + q4 + 8]);
+                        ol[i] += a * cx[i] - b * sx[i]; oh[i] += a * sx[i] + b * cx[i];
                     }
-                    float4 *pl = part + (db * 4 + q4) * 64, *ph = part + (db * 4 + q4 + 8) * 64;
-                    if (!first) {
-                        const float4 ol = *pl, oh = *ph;
-                        lo[0] += ol.x; lo[1] += ol.y; lo[2] += ol.z; lo[3] += ol.w;
-                        hi[0] += oh.x; hi[1] += oh.y; hi[2] += oh.z; hi[3] += oh.w;
-                    }
-                    *pl = make_float4(lo[0], lo[1], lo[2], lo[3]);
-                    *ph = make_float4(hi[0], hi[1], hi[2], hi[3]);
                 }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[i * 64] = old[i];
             first = false;
         }
     };
@@ -456,9 +476,11 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
         q_src[i] = (unsigned)(r * 256 + (((threadIdx.x & 15) ^ swz(r)) << 4));
     }
     const int64_t u_base = (int64_t)(cd.rb_off - B.rb0) * L.n_q_heads + kh * g;
-    auto unit_of = [&](int rt) { const int rb = rt / g; return u_base + (int64_t)rb * L.n_q_heads + (rt - rb * g); };
-    auto request = [&](int rt, int slot) {
-        const int64_t u = unit_of(__builtin_amdgcn_readfirstlane(min(rt, item.rt_end - 1)));
+    // the units are requested in order; beyond the last one it comes again, so that every wait counts the same requests
+    int req_rt = item.rt_begin, req_rb = item.rt_begin / g, req_h = item.rt_begin - req_rb * g;
+    auto request = [&](int slot) {
+        const int64_t u = u_base + (int64_t)req_rb * L.n_q_heads + req_h;
+        if (req_rt + 1 < item.rt_end) { ++req_rt; if (++req_h == g) { req_h = 0; ++req_rb; } }
         const unsigned char *src = (const unsigned char *)B.q_pieces + u * STAGE;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -472,8 +494,8 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
 #pragma unroll
         for (int i = 0; i < 8; ++i) dma16(vb, (unsigned)v_src_chunk(64 * i + lane) * 16, at + i * 1024);
     }
-    request(item.rt_begin, 0);
-    request(item.rt_begin + 1, 1);
+    request(0);
+    request(1);
     // the wave's keys turned by +(start - base): lane = key, dims 16 ks + 8 hh + 0..7
     bf16x8 kp[3][8], vf[8];
     const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2));
@@ -512,14 +534,19 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
         for (int r = 0; r < 16; ++r) dk[db][r] = dv[db][r] = 0.f;
 
     const RowMajor rq(perm_row(n), lane);
+    int rb = item.rt_begin / g, left = (rb + 1) * g - item.rt_begin, slot = 0;      // row block, its units still to come, ring slot
     for (int rt = item.rt_begin; rt < item.rt_end; ++rt) {
-        const int slot = (rt - item.rt_begin) % RING;
         wait_vm<N_DMA>();                                // this wave's share of the unit has landed
         ring_barrier();                                  // ... every wave's has, and the slot two ahead is no longer read
-        request(rt + 2, (slot + 2) % RING);
-        const int rb = rt / g, row0 = tok0 + 32 * rb;    // own token of the block's first row
+        request(slot >= 1 ? slot - 1 : RING - 1);        // unit rt + 2
+        const int row0 = tok0 + 32 * rb;                 // own token of the block's first row
+        const unsigned qt = lds_q + slot * STAGE;
+        const float4 *st = reinterpret_cast<const float4 *>(&s_stat[slot][8 * hh]);
+        if (--left == 0) { ++rb; left = g; }
+        slot = slot + 1 == RING ? 0 : slot + 1;
         if (!active || (self && key0 > row0 + 31)) continue;            // (uniform over the wave: no row of the block sees the tile)
-        const unsigned qt = lds_q + slot * STAGE, gt = qt + 3 * TILE_BYTES;
+        const int lim = self && key0 + PC_TILE - 1 > row0 ? key0 + n - row0 : -1;      // the first row that sees the lane's key
+        const RowMajor::Cols qc = rq.cols(qt);
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
@@ -534,10 +561,9 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
             s = MFMA32(a0, kp[0][ks], s);
         }
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rq.by_row(gt, ks), vf[ks], dp);
+        for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rq.by_row(qt + 3 * TILE_BYTES, ks), vf[ks], dp);
         // register r: row 16 (r / 8) + 8 hh + r % 8 of the block
         float p[16], w[16];
-        const float4 *st = reinterpret_cast<const float4 *>(&s_stat[slot][8 * hh]);
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
             const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
@@ -546,17 +572,15 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
             w[r] = dp[r] - x.y;
             w[r + 1] = dp[r + 1] - x.w;
         }
-        if (self && key0 + PC_TILE - 1 > row0) {         // causal tile (uniform)
-            const int lim = key0 + n - row0;             // the first row that sees the lane's key
+        // (no branch for the few causal tiles: it would cut the block the scheduler mixes matrix and vector work in)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) p[r] = (16 * (r >> 3) + 8 * hh + (r & 7) >= lim) ? p[r] : 0.f;
-        }
+        for (int r = 0; r < 16; ++r) p[r] = (16 * (r >> 3) + 8 * hh + (r & 7) >= lim) ? p[r] : 0.f;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const Pieces pp = split8(p + 8 * half);
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
-                const bf16x8 a = rq.by_col(gt, half, db);
+                const bf16x8 a = RowMajor::by_col(qc, 3 * TILE_BYTES, half, db);
                 dv[db] = MFMA32(a, pp.p[2], dv[db]);
                 dv[db] = MFMA32(a, pp.p[1], dv[db]);
                 dv[db] = MFMA32(a, pp.p[0], dv[db]);
@@ -569,7 +593,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
             const Pieces ds = split8(w + 8 * half);
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
-                const bf16x8 a0 = rq.by_col(qt, half, db), a1 = rq.by_col(qt + TILE_BYTES, half, db), a2 = rq.by_col(qt + 2 * TILE_BYTES, half, db);
+                const bf16x8 a0 = RowMajor::by_col(qc, 0, half, db), a1 = RowMajor::by_col(qc, TILE_BYTES, half, db), a2 = RowMajor::by_col(qc, 2 * TILE_BYTES, half, db);
                 dk[db] = MFMA32(a2, ds.p[0], dk[db]);
                 dk[db] = MFMA32(a1, ds.p[1], dk[db]);
                 dk[db] = MFMA32(a0, ds.p[2], dk[db]);

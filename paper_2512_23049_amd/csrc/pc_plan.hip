@@ -354,21 +354,47 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
     return best;
 }
 
-// Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head) and
-// as many splits of the tiles as fill the chip once (a workgroup fills a compute unit); the key-major kernel takes 4 key
-// tiles a workgroup and splits their units until there are about four workgroups for every compute unit, which evens out
-// the last round (BWD_KEY_WGS).  Per-unit buffers take 64 KB a unit (16 more per further split): a batch with more units
-// than BWD_UNITS is cut into runs of row blocks with launches of their own, at multiples of 8 blocks of a call, so that
+// Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head),
+// each of which fills a compute unit, and as many splits of the tiles as fill whole rounds of them; the key-major kernel
+// takes 4 key tiles a workgroup and splits their units where that evens the load out: a workgroup costs KEY_FIXED us (keys
+// turned and cut into pieces at the start, an atomic per gradient element at the end) and KEY_UNIT a unit.  (Four calls of
+// 150 to 320 rows over 2000 tokens, 32/8 heads: 426 us for 16 units a workgroup, 365 for 32.)  Per-unit buffers take 64 KB
+// a unit (16 more per further split): a batch with more units than BWD_UNITS is cut into runs of row blocks with launches of their own, at multiples of 8 blocks of a call, so that
 // no workgroup's 8 units lie in two of them.
-constexpr int64_t BWD_UNITS = 16384, BWD_KEY_WGS = 1024;
+constexpr int64_t BWD_UNITS = 16384;
+constexpr double KEY_FIXED = 30.0, KEY_UNIT = 2.5, ROWS_FIXED = 15.0, ROWS_TILE = 3.0;
 struct BwdPlan { std::vector<PcItem> items; std::vector<PcBwdKeyItem> keys; std::vector<int2> row_blocks; size_t units = 0, splits = 1; };
 
 static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc> &cds, BwdPlan &bp)
 {
     const int g = c->g, H_q = c->cfg.n_q_heads, H_kv = c->cfg.n_kv_heads;
     const int rb_max = (int)std::max<int64_t>(8, BWD_UNITS / H_q / 8 * 8);
-    int64_t groups = 0, quads = 0;
-    for (const Resolved &r : P.res) { groups += (int64_t)(((r.n_q + 31) / 32) * g + 7) / 8 * H_kv; quads += (int64_t)((r.tiles + 3) / 4) * H_kv; }
+    int64_t groups = 0;
+    int most_units = 1;
+    for (const Resolved &r : P.res) {
+        groups += (int64_t)(((r.n_q + 31) / 32) * g + 7) / 8 * H_kv;
+        most_units = std::max(most_units, (r.n_q + 31) / 32 * g);
+    }
+    int key_units = most_units;                          // units a key-major workgroup takes
+    double best_us = 0;
+    for (int k = 1; k <= 16 && (k == 1 || most_units / k >= 8); ++k) {
+        const int u = (most_units + k - 1) / k;
+        double total = 0;
+        for (const Resolved &r : P.res) {
+            const int n = (r.n_q + 31) / 32 * g;
+            total += (double)((r.tiles + 3) / 4) * H_kv * (KEY_FIXED * ((n + u - 1) / u) + KEY_UNIT * n);
+        }
+        const double us = total / 256 + 0.5 * (KEY_FIXED + KEY_UNIT * u);       // workgroups of unlike lengths: no whole rounds
+        if (k == 1 || us < best_us) { best_us = us; key_units = u; }
+    }
+    // splits of the row-major walk: the fewest rounds of 256 workgroups, each a start (ROWS_FIXED) and its tiles long
+    int row_splits = 1, most_tiles = 0;
+    for (const Resolved &r : P.res) most_tiles = std::max(most_tiles, r.tiles);
+    for (int k = 1; k <= std::min(MAX_SPLITS, most_tiles / 8); ++k) {
+        const double us = (double)((groups * k + 255) / 256) * (ROWS_FIXED + ROWS_TILE * ((most_tiles + k - 1) / k));
+        if (k == 1 || us < best_us) { best_us = us; row_splits = k; }
+        if (groups * k > 1024) break;
+    }
     Planned::BwdChunk ch{0, 0, 0, 0, 0, 0};
     auto close = [&]() {
         if (ch.n_rb == 0) return;
@@ -382,7 +408,7 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
         PcCallDesc &cd = cds[i];
         const int n_rb = (r.n_q + 31) / 32, T = r.tiles;
         const int self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0, parent_tiles = T - self_tiles;
-        int ns = (int)std::max<int64_t>(1, std::min<int64_t>({(256 + groups - 1) / groups, (int64_t)T / 8, (int64_t)MAX_SPLITS}));
+        const int ns = std::max(1, std::min(row_splits, T / 8));
         cd.n_splits = ns;
         cd.rb_off = (int32_t)bp.row_blocks.size();
         bp.splits = std::max(bp.splits, (size_t)ns);
@@ -414,8 +440,7 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
                 if (t >= parent_tiles) first = std::max(first, ((t - parent_tiles) * PC_TILE - (r.self_len - r.n_q)) / 32);
                 if (first >= b1) continue;
                 const int n_rt = (b1 - first) * g;
-                const int sp = (int)std::max<int64_t>(1, std::min<int64_t>((BWD_KEY_WGS + quads - 1) / quads, n_rt / 8));
-                const int per = (n_rt + sp - 1) / sp;
+                const int sp = (n_rt + key_units - 1) / key_units, per = (n_rt + sp - 1) / sp;
                 for (int a = 0; a < n_rt; a += per)
                     bp.keys.push_back(PcBwdKeyItem{(int32_t)i, t, std::min(4, T - t), first * g + a, first * g + std::min(n_rt, a + per), {0, 0, 0}});
             }
