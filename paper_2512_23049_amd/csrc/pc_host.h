@@ -28,6 +28,8 @@ struct ProfRec { int cls; hipEvent_t a, b; };
 
 constexpr int N_STAGE = 4;
 constexpr int MAX_SPLITS = 128;
+// staged blocks up to this size are read by the plan builder where they are, in pinned memory
+constexpr size_t HOST_READ_BYTES = 256 << 10;
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -149,7 +151,7 @@ struct PlanLayout {
 // -------------------------------------------------------------------------------------
 struct Planned {
     PlanLayout lay;
-    int n_calls = 0, total_sel = 0, total_q = 0, total_seg = 0, n_dec = 0, n_pre = 0, n_pre_pk = 0, pre_waves = 4;
+    int n_calls = 0, total_q = 0, total_seg = 0, n_dec = 0, n_pre = 0, n_pre_pk = 0, pre_waves = 4;
     int n_merge_rows = 0, n_merge_few = 0;               // rows to merge; the first n_merge_few have few splits
     int n_sh_items = 0;
     size_t n_sh_pos = 0;

@@ -55,7 +55,7 @@ struct PcMoveItem {
 
 // One call of a batch as staged by the host.
 struct PcCallDesc {
-    int32_t sel_off;          // first entry in the packed (msg, start) list
+    int32_t sel_off;          // first entry in the packed (msg, start) list (= seg_off: the new message is a call's last entry there)
     int32_t n_sel;
     int32_t self_msg;         // -1: none
     int32_t self_start;       // resolved

@@ -533,9 +533,8 @@ __device__ __forceinline__ void build_plan_block(
             const int e = base + threadIdx.x;
             int len = 0, slot = 0, pos = 0, rot = 0;
             if (e < cd.n_seg) {
-                int m, p;
-                if (e < cd.n_sel) { const int2 s = sel[cd.sel_off + e]; m = s.x; p = s.y; }
-                else { m = cd.self_msg; p = cd.self_start; }
+                const int2 ms = sel[cd.seg_off + e];     // (the new message is the last entry)
+                const int m = ms.x, p = ms.y;
                 const PcMsgEntry me = table[m];
                 // (the new message's length comes from the host: a decode step appends its token beside this kernel)
                 len = e < cd.n_sel ? me.len : cd.self_len; slot = me.slot_start; pos = p; rot = p - me.base_pos;
@@ -603,29 +602,23 @@ __device__ __forceinline__ void build_plan_block(
         }
         return;
     }
-    // rotation tables: entity = segment (position from the staged lists) or query row
+    // rotation tables: entity = segment (position from the staged lists) or query row; a block's 256 / half entities are
+    // looked up once (the staged block may lie in host memory, where a request per wave would count)
     const int64_t tid = (int64_t)(blockIdx.x - n_calls) * 256 + threadIdx.x;
     const int64_t n_ent = (int64_t)total_seg + total_q;
+    const int ent0 = (int)((int64_t)(blockIdx.x - n_calls) * 256 / half);
+    if ((int)threadIdx.x < 256 / half && ent0 + (int)threadIdx.x < n_ent) {
+        const int e = ent0 + (int)threadIdx.x;
+        int p;
+        if (e < total_seg) { const int2 ms = sel[e]; p = ms.y - table[ms.x].base_pos; }      // the stored key of token t already sits at base_pos + t
+        else p = q_pos[e - total_seg];
+        s_rot[threadIdx.x] = p;
+    }
+    __syncthreads();
     if (tid >= n_ent * half) return;
     const int ent = (int)(tid / half);
     const int i = (int)(tid % half);
-    int pos;
-    if (ent < total_seg) {
-        // find the call that owns this segment (calls are few; segments are laid out call by call)
-        int lo = 0, hi = n_calls - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (calls[mid].seg_off <= ent) lo = mid; else hi = mid - 1;
-        }
-        const PcCallDesc cd = calls[lo];
-        const int e = ent - cd.seg_off;
-        int m;
-        if (e < cd.n_sel) { const int2 s = sel[cd.sel_off + e]; m = s.x; pos = s.y; }
-        else { m = cd.self_msg; pos = cd.self_start; }
-        pos -= table[m].base_pos;                        // the stored key of token t already sits at base_pos + t
-    } else {
-        pos = q_pos[ent - total_seg];
-    }
+    const int pos = s_rot[ent - ent0];
     double s, c;
     sincos((double)pos * inv_freq[i], &s, &c);
     const float2 r = make_float2((float)c, (float)s);
@@ -643,8 +636,14 @@ __global__ __launch_bounds__(256) void pc_build_plan_kernel(
     const int32_t *__restrict__ q_pos, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
-    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0)
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0,
+    const uint4 *__restrict__ staged, uint4 *__restrict__ ws, int n16, int copy_block0)
 {
+    if ((int)blockIdx.x >= copy_block0) {                // the staged block, from host memory to the workspace
+        const int i = ((int)blockIdx.x - copy_block0) * 256 + (int)threadIdx.x;
+        if (i < n16) ws[i] = staged[i];
+        return;
+    }
     build_plan_block(calls, n_calls, sel, q_pos, tok.items, table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles,
                      tok, tok_block0);
 }
@@ -686,12 +685,15 @@ static unsigned plan_blocks(int n_calls, int half, int total_seg, int total_q, c
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st)
+                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
+                          hipStream_t st)
 {
     int tok_block0 = 0;
     const unsigned grid = plan_blocks(n_calls, half, total_seg, total_q, tok, tok_block0);
-    pc_build_plan_kernel<<<grid, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
-                                               total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
+    const unsigned n16 = staged ? (unsigned)((h2d_bytes + 15) / 16) : 0;
+    pc_build_plan_kernel<<<grid + (n16 + 255) / 256, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
+                                                                   total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0,
+                                                                   (const uint4 *)staged, (uint4 *)ws, (int)n16, (int)grid);
 }
 
 void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,

@@ -55,7 +55,7 @@ int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out)
         if (s.host) PC_HIP(c, hipHostFree(s.host));
         s.host = nullptr; s.cap = 0;
         const size_t cap = align_up(bytes * 2, 4096);
-        PC_HIP(c, hipHostMalloc(&s.host, cap, hipHostMallocDefault));
+        PC_HIP(c, hipHostMalloc(&s.host, cap, hipHostMallocCoherent));
         s.cap = cap;
     }
     *out = &s;
@@ -120,7 +120,7 @@ int32_t pc_cache_create(const pc_config *cfg, pc_cache **out)
     if (hipMalloc(&c->tok_dev, (size_t)1 << 16) != hipSuccess) return bail(PC_ERR_HIP);
     c->tok_cap = (size_t)1 << 16;
     for (int i = 0; i < N_STAGE; ++i) {
-        if (hipHostMalloc(&c->stage[i].host, (size_t)1 << 20, hipHostMallocDefault) != hipSuccess) return bail(PC_ERR_HIP);
+        if (hipHostMalloc(&c->stage[i].host, (size_t)1 << 20, hipHostMallocCoherent) != hipSuccess) return bail(PC_ERR_HIP);
         c->stage[i].cap = (size_t)1 << 20;
         if (hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming) != hipSuccess) return bail(PC_ERR_HIP);
     }

@@ -93,7 +93,7 @@ int32_t pc_resolve(pc_cache *c, const pc_call *call, int idx, Resolved &out)
     return PC_OK;
 }
 
-PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, int n_dec, int n_pre, int n_pre_pk,
+PlanLayout make_layout(int n_calls, int total_q, int total_seg, int n_dec, int n_pre, int n_pre_pk,
                        int64_t part_rows, int64_t total_tiles, int H_q, int D,
                        size_t n_sh_groups = 0, size_t n_sh_segs = 0, size_t n_sh_items = 0, size_t n_sh_pos = 0,
                        size_t n_kg_items = 0, int64_t kg_tiles = 0, int H_kv = 1, size_t n_tok = 0,
@@ -105,7 +105,7 @@ PlanLayout make_layout(int n_calls, int total_sel, int total_q, int total_seg, i
     // staged: arrays in 32-byte steps, nothing for a list that is empty (small blocks travel in the plan builder's arguments)
     auto put = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 32); return at; };
     L.calls = put(sizeof(PcCallDesc) * (size_t)n_calls);
-    L.sel = put(sizeof(int2) * (size_t)total_sel);
+    L.sel = put(sizeof(int2) * (size_t)total_seg);
     L.q_pos = put(sizeof(int32_t) * (size_t)total_q);
     L.merge_rows = put(sizeof(PcMergeRow) * n_merge);
     L.items_dec = put(sizeof(PcItem) * (size_t)n_dec);
@@ -531,7 +531,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     std::vector<PcGatherItem> kg;
     int64_t kg_tiles = 0;
     int64_t part_rows = 0, total_tiles = 0;
-    int sel_off = 0, q_off = 0, seg_off = 0;
+    int q_off = 0, seg_off = 0;
     // groups of one-row calls that share enough of their messages take the shared walk
     SharedPlan sp;
     sp.in_shared.assign((size_t)n_calls, 0);
@@ -562,20 +562,20 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     auto plan_calls = [&](bool small_splits) {
         dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear();
         kg_tiles = part_rows = total_tiles = 0;
-        sel_off = q_off = seg_off = 0;
+        q_off = seg_off = 0;
         for (int i = 0; i < n_calls; ++i) {
             Resolved &r = P.res[i];
             PcCallDesc &cd = cds[i];
             // a call served by the shared walk needs no segments, tiles or rotation rows of its own: the plan
             // builder sees it as a call that lists nothing
             const bool own_plan = !sp.in_shared[(size_t)i];
-            cd.sel_off = sel_off; cd.n_sel = own_plan ? (int)r.sel.size() : 0;
+            cd.sel_off = seg_off; cd.n_sel = own_plan ? (int)r.sel.size() : 0;
             cd.self_msg = own_plan ? r.self_msg : -1; cd.self_start = r.self_start;
             cd.n_q = r.n_q; cd.q_off = q_off; cd.seg_off = seg_off; cd.n_seg = cd.n_sel + (cd.self_msg >= 0 ? 1 : 0);
             cd.self_len = own_plan ? r.self_len : 0; cd.n_splits = 1; cd.part_off = 0; cd.tile_off = (int32_t)total_tiles;
             cd.kg_tile0 = -1; cd.n_par = 0; cd.rb_off = 0; cd.part_wide = 0;
             if (own_plan) total_tiles += r.tiles;
-            sel_off += cd.n_sel; q_off += cd.n_q; seg_off += cd.n_seg;
+            q_off += cd.n_q; seg_off += cd.n_seg;
             if (!want_items || !bf16 || !own_plan) continue;
             const int T = r.tiles;
             if (r.n_q * g <= 16) {                       // decode-shaped: all rows x heads of a KV head in one wave
@@ -686,14 +686,14 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
     auto lay_out = [&]() {
-        P.total_sel = sel_off; P.total_seg = seg_off;
+        P.total_seg = seg_off;
         P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
         P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
         P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
         size_t n_merge = 0;
         for (int i = 0; i < n_calls && want_items; ++i) if (cds[(size_t)i].n_splits > 1) n_merge += (size_t)cds[(size_t)i].n_q;
         for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) n_merge += (size_t)gr.n_rows;
-        P.lay = make_layout(n_calls, P.total_sel, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
+        P.lay = make_layout(n_calls, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
                             sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
                             bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
     };
@@ -745,7 +745,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     PcMergeRow *hm = (PcMergeRow *)(h + P.lay.merge_rows);
     for (int i = 0; i < n_calls; ++i) {
         const Resolved &r = P.res[i];
-        if (cds[i].n_sel > 0) std::memcpy(hs + cds[i].sel_off, r.sel.data(), sizeof(int2) * (size_t)cds[i].n_sel);
+        if (cds[i].n_sel > 0) std::memcpy(hs + cds[i].seg_off, r.sel.data(), sizeof(int2) * (size_t)cds[i].n_sel);
+        if (cds[i].self_msg >= 0) hs[cds[i].seg_off + cds[i].n_sel] = make_int2(cds[i].self_msg, cds[i].self_start);
         std::memcpy(hq + cds[i].q_off, r.q_pos.data(), sizeof(int32_t) * r.q_pos.size());
     }
     // rows to merge: those with few splits first, then those with many (they get four lanes per 8 dimensions)
@@ -774,31 +775,44 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         std::memcpy(h + P.lay.sh_items, sp.items.data(), sizeof(PcShItem) * sp.items.size());
         std::memcpy(h + P.lay.sh_pos, sp.pos.data(), sizeof(int32_t) * sp.pos.size());
     }
-    if (!in_args) {
+    // A block too large for the arguments is read by the plan builder where it is and copied to the workspace by further
+    // blocks of the same launch (a copy in front of it took 4 us on the stream, 8 from 16 KB on, and a gap); beyond
+    // HOST_READ_BYTES the copy engine is the faster way.
+    const bool in_place = !in_args && P.lay.h2d_bytes <= HOST_READ_BYTES;
+    if (!in_args && !in_place) {
         PC_HIP(c, hipMemcpyAsync(P.ws, h, P.lay.h2d_bytes, hipMemcpyHostToDevice, st));
         PC_HIP(c, hipEventRecord(slot->ev, st));
         slot->used = true;
     }
     {
         ProfScope ps(c, 1, st);
-        char *w = (char *)P.ws;
+        char *w = (char *)P.ws, *from = in_place ? h : w;
         PcTokenWork tok;
         if (!P.tok_items.empty()) {
-            tok.items = (const PcTokenItem *)(w + P.lay.tok_items); tok.n = (int)P.tok_items.size();
+            tok.items = (const PcTokenItem *)(from + P.lay.tok_items); tok.n = (int)P.tok_items.size();
             tok.k = P.tok_k; tok.v = P.tok_v; tok.k_store = c->k_store; tok.v_store = c->v_store;
             tok.slots = c->slots; tok.n_kv_heads = c->cfg.n_kv_heads; tok.D = c->D; tok.dtype = c->cfg.dtype;
         }
-        auto build = [&](auto launch, auto &&...first) {
-            launch(first..., (const PcCallDesc *)(w + P.lay.calls), n_calls, (const int2 *)(w + P.lay.sel),
-                   (const int32_t *)(w + P.lay.q_pos), c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                   P.total_q, (PcSegment *)(w + P.lay.segs), (int32_t *)(w + P.lay.seg_kvoff),
-                   (float2 *)(w + P.lay.rot_seg), (float2 *)(w + P.lay.rot_q),
-                   c->cfg.head_dim == 128 ? (float2 *)(w + P.lay.rot_qw) : nullptr, (PcTile *)(w + P.lay.tiles), tok, st);
-        };
-        if (in_args) build(pc_launch_build_plan_arg, blob, P.ws, P.lay.h2d_bytes);
-        else build(pc_launch_build_plan);
+        auto *calls_at = (const PcCallDesc *)(from + P.lay.calls);
+        auto *sel_at = (const int2 *)(from + P.lay.sel);
+        auto *q_pos_at = (const int32_t *)(from + P.lay.q_pos);
+        auto *segs = (PcSegment *)(w + P.lay.segs);
+        auto *seg_kvoff = (int32_t *)(w + P.lay.seg_kvoff);
+        auto *rot_seg = (float2 *)(w + P.lay.rot_seg), *rot_q = (float2 *)(w + P.lay.rot_q);
+        auto *rot_qw = c->cfg.head_dim == 128 ? (float2 *)(w + P.lay.rot_qw) : nullptr;
+        auto *tiles = (PcTile *)(w + P.lay.tiles);
+        if (in_args)
+            pc_launch_build_plan_arg(blob, P.ws, P.lay.h2d_bytes, calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
+                                     P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, st);
+        else
+            pc_launch_build_plan(calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
+                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
+        if (in_place) {                                  // the ring slot is free again once the plan builder is done
+            PC_HIP(c, hipEventRecord(slot->ev, st));
+            slot->used = true;
+        }
         if (P.n_sh_items > 0) {
             pc_launch_shared_rot((const int32_t *)(w + P.lay.sh_pos), (int64_t)P.n_sh_pos, c->inv_freq_dev, c->half,
                                  (float2 *)(w + P.lay.sh_rot), st);
