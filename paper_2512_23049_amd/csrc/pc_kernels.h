@@ -45,10 +45,11 @@ struct PcTokenWork {
     void *k_store = nullptr, *v_store = nullptr;
     int64_t slots = 0; int n_kv_heads = 0, D = 0, dtype = 0;
 };
+// tile_blocks: blocks that share out a call's tile table
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
+                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
                           hipStream_t st);
 // (staged != null: calls, sel, q_pos and tok.items lie in that block of pinned host memory, which the kernel copies to the workspace)
 // the same with the staged block (h2d_bytes <= PC_ARG_BYTES, at the start of the workspace) in the kernel's arguments: calls,
@@ -56,7 +57,7 @@ void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel,
 void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                               PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                               int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st);
+                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, hipStream_t st);
 
 void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, int n_seg, int64_t n_kv,
                              int32_t *kv_slot, int32_t *kv_pos, hipStream_t st);

@@ -486,10 +486,10 @@ void pc_launch_reposition_batch(int dtype, const PcMoveItem *items, int n_items,
 }
 
 // ----------------------------------------------------------------------------------
-// K2: plan builder.  Blocks [0, n_calls): per call, look each listed message up in the
+// K2: plan builder.  Blocks [0, n_calls * tile_blocks): per call, look each listed message up in the
 // device message table and scan lengths into the segment list (Sec. 2.4 "Dynamic
 // Masking": what a call sees is computed on the fly from message membership; here in
-// gather form).  Blocks [n_calls, ...): rotation tables (cos, sin)(p * theta_i) for
+// gather form).  Blocks behind those: rotation tables (cos, sin)(p * theta_i) for
 // every segment start and every query row, in fp64 rounded to fp32 (Sec. 2.4
 // "Position Updates": a lookup table of rotations).
 // ----------------------------------------------------------------------------------
@@ -500,7 +500,7 @@ __device__ __forceinline__ void build_plan_block(
     const int32_t *q_pos, const PcTokenItem *tok_items, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
-    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, const PcTokenWork &tok, int tok_block0)
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles_out, const PcTokenWork &tok, int tok_block0, int tile_blocks)
 {
     if ((int)blockIdx.x >= tok_block0) {
         const int per_row = tok.D / 4;
@@ -516,19 +516,23 @@ __device__ __forceinline__ void build_plan_block(
                                        tok.slots, inv_freq, (float *)tok.k_store, (float *)tok.v_store, table);
         return;
     }
-    __shared__ int s_len[256];
-    __shared__ int s_tiles[256];
-    __shared__ int s_carry[2];
+    __shared__ int s_wave[4][2];                         // tokens and tiles of a wave's 64 segments
     __shared__ int s_rot[257];                           // query rotation (position - stored base) of the chunk's segments
     // the call's segment list as the tile loop needs it, kept in LDS when it fits (it nearly always
     // does): the per-tile binary search then costs LDS latencies, not a chain of global loads
     constexpr int SEG_LDS = 1024;
     __shared__ int s_seg_tile[SEG_LDS], s_seg_slot[SEG_LDS], s_seg_len[SEG_LDS];
     __shared__ unsigned char s_seg_same[SEG_LDS];
-    if ((int)blockIdx.x < n_calls) {
-        const PcCallDesc cd = calls[blockIdx.x];
-        if (threadIdx.x == 0) { s_carry[0] = 0; s_carry[1] = 0; s_rot[0] = 0; }
-        __syncthreads();
+    const int call_blocks = n_calls * tile_blocks;
+    if ((int)blockIdx.x < call_blocks) {
+        // tile_blocks blocks a call: each makes the segment list, the first writes it, and they share out the tile table
+        const int part = (int)blockIdx.x % tile_blocks;
+        const PcCallDesc cd = calls[blockIdx.x / tile_blocks];
+        const bool in_lds = cd.n_seg <= SEG_LDS;
+        if (part > 0 && !in_lds) return;                 // (the first block's own entries are read back from memory then)
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        int c_len = 0, n_tiles = 0;                      // of the segments before this chunk
+        if (threadIdx.x == 0) s_rot[0] = 0;
         for (int base = 0; base < cd.n_seg; base += 256) {
             const int e = base + threadIdx.x;
             int len = 0, slot = 0, pos = 0, rot = 0;
@@ -539,42 +543,44 @@ __device__ __forceinline__ void build_plan_block(
                 // (the new message's length comes from the host: a decode step appends its token beside this kernel)
                 len = e < cd.n_sel ? me.len : cd.self_len; slot = me.slot_start; pos = p; rot = p - me.base_pos;
             }
-            s_rot[threadIdx.x + 1] = rot;                // s_rot[0]: last segment of the chunk before
             const int tiles = (len + PC_TILE - 1) / PC_TILE;
-            s_len[threadIdx.x] = len;
-            s_tiles[threadIdx.x] = tiles;
-            __syncthreads();
-            // Hillis-Steele inclusive scan over the 256 entries of this chunk
-            for (int off = 1; off < 256; off <<= 1) {
-                int a = 0, b = 0;
-                if ((int)threadIdx.x >= off) { a = s_len[threadIdx.x - off]; b = s_tiles[threadIdx.x - off]; }
-                __syncthreads();
-                s_len[threadIdx.x] += a;
-                s_tiles[threadIdx.x] += b;
-                __syncthreads();
+            // inclusive sums over the wave, then over the waves before it (a scan through LDS with a barrier per step took
+            // 1 us of the kernel)
+            int i_len = len, i_tiles = tiles;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int a = __shfl_up(i_len, off), b = __shfl_up(i_tiles, off);
+                if (lane >= off) { i_len += a; i_tiles += b; }
             }
-            const int c_len = s_carry[0], c_tiles = s_carry[1];
+            if (lane == 63) { s_wave[wave][0] = i_len; s_wave[wave][1] = i_tiles; }
+            s_rot[threadIdx.x + 1] = rot;                // s_rot[0]: last segment of the chunk before
+            __syncthreads();
+            int b_len = c_len, b_tiles = n_tiles;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (w < wave) { b_len += s_wave[w][0]; b_tiles += s_wave[w][1]; }
+                c_len += s_wave[w][0]; n_tiles += s_wave[w][1];
+            }
             if (e < cd.n_seg) {
                 PcSegment sg;
                 sg.slot_start = slot; sg.len = len; sg.pos_start = pos;
-                sg.tile_off = c_tiles + s_tiles[threadIdx.x] - tiles;
+                sg.tile_off = b_tiles + i_tiles - tiles;
                 sg.rot_pos = rot;
                 sg.same_rot = (e > 0 && s_rot[threadIdx.x] == rot) ? 1 : 0;
                 sg.pad[0] = sg.pad[1] = 0;
-                segs[cd.seg_off + e] = sg;
-                seg_kvoff[cd.seg_off + e] = c_len + s_len[threadIdx.x] - len;
+                if (part == 0) {
+                    segs[cd.seg_off + e] = sg;
+                    seg_kvoff[cd.seg_off + e] = b_len + i_len - len;
+                }
                 if (e < SEG_LDS) { s_seg_tile[e] = sg.tile_off; s_seg_slot[e] = slot; s_seg_len[e] = len; s_seg_same[e] = (unsigned char)sg.same_rot; }
             }
             __syncthreads();
-            if (threadIdx.x == 255) { s_carry[0] = c_len + s_len[255]; s_carry[1] = c_tiles + s_tiles[255]; s_rot[0] = rot; }
-            __syncthreads();
+            if (threadIdx.x == 255) s_rot[0] = rot;      // (read behind the next chunk's barrier)
         }
         // tile table of this call: one entry per 32-key tile, in gathered order (the segment
         // entries written above by this block are visible after the barrier)
-        const int n_tiles = s_carry[1];
         const PcSegment *sg = segs + cd.seg_off;
-        const bool in_lds = cd.n_seg <= SEG_LDS;
-        for (int t = threadIdx.x; t < n_tiles; t += 256) {
+        for (int t = part * 256 + (int)threadIdx.x; t < n_tiles; t += in_lds ? 256 * tile_blocks : 256) {
             int lo = 0, hi = cd.n_seg - 1;
             int g_tile, g_slot, g_len, g_same;
             if (in_lds) {
@@ -598,15 +604,15 @@ __device__ __forceinline__ void build_plan_block(
             const int valid = g_len - tl.key0 < PC_TILE ? g_len - tl.key0 : PC_TILE;
             tl.valid_flags = valid | ((t == g_tile && !g_same) ? PC_TILE_FRESH : 0) |
                              ((cd.self_msg >= 0 && lo == cd.n_seg - 1) ? PC_TILE_SELF : 0);
-            tiles[cd.tile_off + t] = tl;
+            tiles_out[cd.tile_off + t] = tl;
         }
         return;
     }
     // rotation tables: entity = segment (position from the staged lists) or query row; a block's 256 / half entities are
     // looked up once (the staged block may lie in host memory, where a request per wave would count)
-    const int64_t tid = (int64_t)(blockIdx.x - n_calls) * 256 + threadIdx.x;
+    const int64_t tid = (int64_t)((int)blockIdx.x - call_blocks) * 256 + threadIdx.x;
     const int64_t n_ent = (int64_t)total_seg + total_q;
-    const int ent0 = (int)((int64_t)(blockIdx.x - n_calls) * 256 / half);
+    const int ent0 = (int)((int64_t)((int)blockIdx.x - call_blocks) * 256 / half);
     if ((int)threadIdx.x < 256 / half && ent0 + (int)threadIdx.x < n_ent) {
         const int e = ent0 + (int)threadIdx.x;
         int p;
@@ -636,7 +642,7 @@ __global__ __launch_bounds__(256) void pc_build_plan_kernel(
     const int32_t *__restrict__ q_pos, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
-    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0,
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0, int tile_blocks,
     const uint4 *__restrict__ staged, uint4 *__restrict__ ws, int n16, int copy_block0)
 {
     if ((int)blockIdx.x >= copy_block0) {                // the staged block, from host memory to the workspace
@@ -645,7 +651,7 @@ __global__ __launch_bounds__(256) void pc_build_plan_kernel(
         return;
     }
     build_plan_block(calls, n_calls, sel, q_pos, tok.items, table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles,
-                     tok, tok_block0);
+                     tok, tok_block0, tile_blocks);
 }
 
 // The staged block comes in the kernel's arguments (its first ones: the start of the kernarg segment).  Every block takes it
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(256) void pc_build_plan_arg_kernel(
     const PcArgBlob blob, uint4 *__restrict__ ws, int n16, int off_calls, int n_calls, int off_sel, int off_q_pos, int off_tok, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
-    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0)
+    float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0, int tile_blocks)
 {
     __shared__ uint4 s_blob[PC_ARG_BYTES / 16];
     static_assert(PC_ARG_BYTES <= 256 * 16, "one piece a thread");
@@ -671,13 +677,13 @@ __global__ __launch_bounds__(256) void pc_build_plan_arg_kernel(
     const char *b = reinterpret_cast<const char *>(s_blob);
     build_plan_block(reinterpret_cast<const PcCallDesc *>(b + off_calls), n_calls, reinterpret_cast<const int2 *>(b + off_sel),
                      reinterpret_cast<const int32_t *>(b + off_q_pos), reinterpret_cast<const PcTokenItem *>(b + off_tok), table, inv_freq, half, total_seg,
-                     total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
+                     total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks);
 }
 
-static unsigned plan_blocks(int n_calls, int half, int total_seg, int total_q, const PcTokenWork &tok, int &tok_block0)
+static unsigned plan_blocks(int n_calls, int tile_blocks, int half, int total_seg, int total_q, const PcTokenWork &tok, int &tok_block0)
 {
     const int64_t n_rot = ((int64_t)total_seg + total_q) * half;
-    tok_block0 = (int)(n_calls + (n_rot + 255) / 256);
+    tok_block0 = (int)((int64_t)n_calls * tile_blocks + (n_rot + 255) / 256);
     const int64_t tok_threads = (int64_t)tok.n * tok.n_kv_heads * (tok.D / 4);
     return (unsigned)tok_block0 + (unsigned)((tok_threads + 255) / 256);
 }
@@ -685,27 +691,27 @@ static unsigned plan_blocks(int n_calls, int half, int total_seg, int total_q, c
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
+                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
                           hipStream_t st)
 {
     int tok_block0 = 0;
-    const unsigned grid = plan_blocks(n_calls, half, total_seg, total_q, tok, tok_block0);
+    const unsigned grid = plan_blocks(n_calls, tile_blocks, half, total_seg, total_q, tok, tok_block0);
     const unsigned n16 = staged ? (unsigned)((h2d_bytes + 15) / 16) : 0;
     pc_build_plan_kernel<<<grid + (n16 + 255) / 256, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
-                                                                   total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0,
+                                                                   total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks,
                                                                    (const uint4 *)staged, (uint4 *)ws, (int)n16, (int)grid);
 }
 
 void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                               PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                               int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, const PcTokenWork &tok, hipStream_t st)
+                              float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, hipStream_t st)
 {
     int tok_block0 = 0;
-    const unsigned grid = plan_blocks(n_calls, half, total_seg, total_q, tok, tok_block0) + 1;
+    const unsigned grid = plan_blocks(n_calls, tile_blocks, half, total_seg, total_q, tok, tok_block0) + 1;
     auto off = [&](const void *p) { return p ? (int)((const char *)p - (const char *)ws) : 0; };
     pc_build_plan_arg_kernel<<<grid, 256, 0, st>>>(blob, (uint4 *)ws, (int)((h2d_bytes + 15) / 16), off(calls), n_calls, off(sel), off(q_pos), off(tok.items),
-                                                   table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0);
+                                                   table, inv_freq, half, total_seg, total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks);
 }
 
 // ----------------------------------------------------------------------------------

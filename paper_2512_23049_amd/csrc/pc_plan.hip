@@ -801,12 +801,16 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         auto *rot_seg = (float2 *)(w + P.lay.rot_seg), *rot_q = (float2 *)(w + P.lay.rot_q);
         auto *rot_qw = c->cfg.head_dim == 128 ? (float2 *)(w + P.lay.rot_qw) : nullptr;
         auto *tiles = (PcTile *)(w + P.lay.tiles);
+        // a block writes 256 tiles in one go: the longest call decides, within reason for a batch of many
+        int longest = 0;
+        for (const PcCallDesc &cd : cds) if (cd.n_seg > 0) longest = std::max(longest, P.res[(size_t)(&cd - cds.data())].tiles);
+        const int tile_blocks = std::max(1, std::min((longest + 255) / 256, std::max(1, 256 / n_calls)));
         if (in_args)
             pc_launch_build_plan_arg(blob, P.ws, P.lay.h2d_bytes, calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                                     P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, st);
+                                     P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, st);
         else
             pc_launch_build_plan(calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
+                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
         if (in_place) {                                  // the ring slot is free again once the plan builder is done
