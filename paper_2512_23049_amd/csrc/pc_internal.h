@@ -113,7 +113,8 @@ struct PcItem {
     int32_t split;            // split index within the call
     int32_t tile_tab0;        // the call's first entry in the tile table (a copy of its PcCallDesc::tile_off, so that
                               // the first tile descriptors can be requested without waiting for the call descriptor)
-    int32_t pad[2];
+    int32_t n_splits;         // prefill: splits of this item's rows
+    int32_t part_base;        // prefill, n_splits > 1: partial row of the call's row 0 in this split (row r: part_base + (r << part_wide))
 };
 
 // Gradient, key-major kernel: one workgroup's key tiles and units (bf16: 32-row block x head of the KV head, head fastest;

@@ -746,7 +746,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     // the wave's number in a scalar register: held in vector registers across the loops they would cost a spill.)
     const float l = sum_across_halves(l_run);
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    const bool whole = cd.n_splits == 1;
+    const bool whole = item.n_splits == 1;
     const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int n_e = lane_e & 31, hh_e = lane_e >> 5;
     const int unit_e = item.unit0 + wave_s;
@@ -756,8 +756,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     const int row_e = 32 * ub_e + n_e;
     if (!whole && cd.part_wide) {                        // fp32 partials: half a row is 256 bytes
         unsigned char *stg = reinterpret_cast<unsigned char *>(&s_qm[0][0][0]) + wave_s * 8192;
-        const int64_t row0 = (int64_t)cd.part_off + 2 * (int64_t)item.split * cd.n_q;
-        unsigned char *dst = reinterpret_cast<unsigned char *>(L.part_o) + (row0 * L.n_q_heads + 2 * h_e) * (PC_D * 2);
+        unsigned char *dst = reinterpret_cast<unsigned char *>(L.part_o) + ((int64_t)item.part_base * L.n_q_heads + 2 * h_e) * (PC_D * 2);
         const int r4 = lane_e >> 4, c = lane_e & 15;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -788,7 +787,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
                 w.y = whole ? pack_bf16(a2, a3) : pack_f16(a2, a3);
                 *reinterpret_cast<uint2 *>(stg + n_e * 256 + (((4 * db + q4) ^ (n_e & 15)) << 4) + 8 * hh_e) = w;
             }
-        const int64_t row0 = whole ? (int64_t)cd.q_off : (int64_t)cd.part_off + (int64_t)item.split * cd.n_q;
+        const int64_t row0 = whole ? (int64_t)cd.q_off : (int64_t)item.part_base;
         unsigned char *dst = reinterpret_cast<unsigned char *>(whole ? (uint16_t *)L.out : L.part_o) + ((row0 * L.n_q_heads + h_e) * PC_D) * 2;
         const int r4 = lane_e >> 4, c = lane_e & 15;
 #pragma unroll
@@ -802,7 +801,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     if (whole) {
         if (L.lse) L.lse[((int64_t)cd.q_off + row_e) * L.n_q_heads + h_e] = (l > 0.f) ? (m_ref + log2f(l)) * 0.6931471805599453f : -INFINITY;
     } else {
-        const int64_t pr = (int64_t)cd.part_off + (((int64_t)item.split * cd.n_q + row_e) << cd.part_wide);
+        const int64_t pr = (int64_t)item.part_base + ((int64_t)row_e << cd.part_wide);
         L.part_ml[(pr * L.n_q_heads + h_e) * 2] = (l > 0.f) ? m_ref : -INFINITY;
         L.part_ml[(pr * L.n_q_heads + h_e) * 2 + 1] = l;
     }

@@ -315,11 +315,11 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
 // (us; measured over 20 to 512 rows, 0.3 to 30 thousand tokens, one to four calls.  The rule before, as many splits as
 // reach 256 workgroups, 16 tiles at least, put 1.1 rounds where one does: 200 rows x 64 heads over 3000 tokens
 // 49 us for 5 splits of 56 groups, 33 us for 4.)
+constexpr double PRE_FIXED = 9.0, PRE_TILE = 1.0, PRE_TILE_PACKED = 0.75, MERGE_FIXED = 4.5, PART_BYTES_US = 3.5e6;
+constexpr int PRE_LEAST = 4;                             // tiles of a split: below, the start is all there is
 static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups)
 {
-    constexpr double PRE_FIXED = 9.0, PRE_TILE = 1.0, PRE_TILE_PACKED = 0.75, MERGE_FIXED = 4.5, PART_BYTES_US = 3.5e6;
-    constexpr int LEAST = 4;                             // tiles: below, the start is all there is
-    if (pre_groups >= 256) return INT32_MAX;             // the chip is full
+    if (pre_groups >= 256) return INT32_MAX;             // the chip is full (prefill_tail sees to the last round)
     struct Shape { int64_t groups; int n_q, tiles; };    // consecutive calls of the same rows and tiles
     std::vector<Shape> shapes;
     int longest = 0;
@@ -336,7 +336,7 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
     const double tile = packed ? PRE_TILE_PACKED : PRE_TILE;
     int best = std::max(longest, 1), last = 0;
     double best_us = 0;
-    const int most = (int)std::min<int64_t>({(int64_t)MAX_SPLITS, (int64_t)longest / LEAST, std::max<int64_t>(2, 1024 / pre_groups)});
+    const int most = (int)std::min<int64_t>({(int64_t)MAX_SPLITS, (int64_t)longest / PRE_LEAST, std::max<int64_t>(2, 1024 / pre_groups)});
     for (int k = 1; k <= std::max(most, 1); ++k) {
         const int chunk = (std::max(longest, 1) + k - 1) / k;
         if (chunk == last) continue;
@@ -352,6 +352,33 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
         if (k == 1 || us < best_us) { best_us = us; best = chunk; }
     }
     return best;
+}
+
+// A batch of more than 256 prefill groups runs in rounds, and a last round of a few groups takes as long as a full one: 280
+// groups, 2 rounds for 1.1 rounds of work.  The items of that last round are split, so that it fills the chip as well.
+// Returns how many of the last items (each n_kv_heads groups) are split, and into how many parts.
+static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups)
+{
+    const int H_kv = c->cfg.n_kv_heads, g = c->g, per_round = 256 / H_kv;
+    // (a row's heads must lie in one item, and a round hold whole items)
+    if (pre_groups <= 256 || 8 % g != 0 || 256 % H_kv != 0 || c->prefill_tiles_per_split != 0) return {0, 1};
+    int tiles = 0, kinds = 0;
+    for (size_t i = 0; i < P.res.size(); ++i) {
+        const Resolved &r = P.res[i];
+        if (sp.in_shared[i] || (int64_t)r.n_q * g <= 16) continue;
+        tiles = std::max(tiles, r.tiles);
+        kinds |= !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768)) ? 2 : 1;
+    }
+    const int tail = (int)(pre_groups / H_kv % per_round);
+    if (tail == 0 || kinds == 3) return {0, 1};          // (two kinds of calls are two launches)
+    int best = 1;
+    double best_us = 0;
+    for (int k = 1; k <= std::min({MAX_SPLITS, tiles / PRE_LEAST, std::max(1, 4 * per_round / tail)}); ++k) {
+        const double us = (double)((tail * k + per_round - 1) / per_round) * (PRE_FIXED + (kinds == 2 ? PRE_TILE_PACKED : PRE_TILE) * ((tiles + k - 1) / k)) +
+                          (k > 1 ? MERGE_FIXED + (double)tail * H_kv * k * 262144.0 / PART_BYTES_US : 0.0);
+        if (k == 1 || us < best_us) { best_us = us; best = k; }
+    }
+    return {best > 1 ? tail : 0, best};
 }
 
 // Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head),
@@ -557,10 +584,14 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     auto pre_groups_of = [&](const Resolved &r) { return (((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves; };
     int pre_chunk = 1;                                   // tiles a prefill split takes
     if (want_items && bf16 && pre_groups > 0 && c->prefill_tiles_per_split == 0) pre_chunk = prefill_chunk(c, P, sp, pre_groups);
+    std::pair<int, int> tail{0, 1};                      // last prefill items that are split, and into how many parts
+    if (want_items && bf16) tail = prefill_tail(c, P, sp, pre_groups);
+    std::vector<PcMergeRow> tail_rows;
     // small_splits: the rules for the number of splits as they stand.  Without it: at least 16 tiles a split and no more
     // splits than bring the batch to 256 workgroups, which bounds the partial results (see below).
     auto plan_calls = [&](bool small_splits) {
-        dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear();
+        dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear(); tail_rows.clear();
+        int64_t items_left = pre_groups / H_kv;          // prefill items still to come
         kg_tiles = part_rows = total_tiles = 0;
         q_off = seg_off = 0;
         for (int i = 0; i < n_calls; ++i) {
@@ -578,6 +609,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             q_off += cd.n_q; seg_off += cd.n_seg;
             if (!want_items || !bf16 || !own_plan) continue;
             const int T = r.tiles;
+            int wide = 0;
             if (r.n_q * g <= 16) {                       // decode-shaped: all rows x heads of a KV head in one wave
                 // Attention does not depend on the order the keys are visited in (each keeps its own
                 // position), so a decode call walks its parents in ascending cache-slot order: calls that
@@ -594,6 +626,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 const int chunk = std::max(1, (T + ns - 1) / ns);
                 ns = std::max(1, (T + chunk - 1) / chunk);
                 cd.n_splits = ns;
+                wide = ns > 1 && small_splits && c->decode_tiles_per_split == 0 && T < 32;
                 for (int s = 0; s < ns; ++s) {
                     PcItem it{}; it.call = i; it.unit0 = 0; it.tile_begin = s * chunk; it.tile_end = std::min(T, (s + 1) * chunk); it.split = s;
                     it.tile_tab0 = cd.tile_off;
@@ -631,27 +664,41 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 // divide THAT count evenly, so the groups with early rows do not end up with a nearly empty
                 // last split.
                 const int parent_tiles = Tc - self_tiles;
-                for (int gidx = 0; gidx < groups; ++gidx) {
+                wide = ns > 1 && small_splits && c->prefill_tiles_per_split == 0 && T < 32;
+                for (int gidx = 0; gidx < groups; ++gidx, --items_left) {
                     int Tg = Tc;
                     if (r.self_msg >= 0) {
                         const int last_unit = std::min(gidx * P.pre_waves + P.pre_waves - 1, units - 1);
                         const int lim = (r.self_len - r.n_q) + std::min(32 * (last_unit / g) + 31, r.n_q - 1);   // last own token seen
                         Tg = parent_tiles + std::min(self_tiles, lim / PC_TILE + 1);
                     }
-                    const int chunk_g = std::max(1, (Tg + ns - 1) / ns);
-                    for (int s = 0; s < ns; ++s) {
+                    // partial rows: those of the whole call, or of an item of the last round alone
+                    int parts = ns, row0 = 0, n_rows = r.n_q;
+                    int64_t part0 = part_rows;
+                    if (small_splits && items_left <= tail.first) {
+                        parts = tail.second;
+                        wide = 1;
+                        row0 = 32 * (gidx * P.pre_waves / g);
+                        n_rows = std::min(r.n_q - row0, 32 * P.pre_waves / g);
+                        for (int q = 0; q < n_rows; ++q)
+                            tail_rows.push_back(PcMergeRow{cd.q_off + row0 + q, (int32_t)(part_rows + 2 * q), parts | PC_MERGE_WIDE, n_rows});
+                        part_rows += 2 * (int64_t)parts * n_rows;
+                    }
+                    const int chunk_g = std::max(1, (Tg + parts - 1) / parts);
+                    for (int s = 0; s < parts; ++s) {
                         PcItem it{}; it.call = i; it.unit0 = gidx * P.pre_waves; it.split = s; it.tile_tab0 = cd.tile_off;
                         it.tile_begin = std::min(Tg, s * chunk_g);
-                        it.tile_end = s == ns - 1 ? Tg : std::min(Tg, (s + 1) * chunk_g);
+                        it.tile_end = s == parts - 1 ? Tg : std::min(Tg, (s + 1) * chunk_g);
+                        it.n_splits = parts;
+                        it.part_base = (int32_t)(part0 + (((int64_t)s * n_rows - row0) << wide));
                         (packed ? pre_pk : pre).push_back(it);
                     }
                 }
             }
-            // Partial results are fp32 where 16 tiles a split would not have split the call at all, so that no sum is held
-            // in fewer bits for being split; the others, fp16, are bound by the bytes they move (512 rows x 32 heads in
-            // 4 splits: 17 MB, 8 us).
-            const int tuned = r.n_q * g <= 16 ? c->decode_tiles_per_split : c->prefill_tiles_per_split;
-            cd.part_wide = cd.n_splits > 1 && small_splits && tuned == 0 && T < 32;
+            // Partial results are fp32 where 16 tiles a split and whole batches of 256 workgroups would not have split the rows
+            // at all, so that no sum is held in fewer bits for being split; the others, fp16, are bound by the bytes they
+            // move (512 rows x 32 heads in 4 splits: 17 MB, 8 us).
+            cd.part_wide = wide;
             if (cd.n_splits > 1) { cd.part_off = (int32_t)part_rows; part_rows += ((int64_t)cd.n_splits * cd.n_q) << cd.part_wide; }
         }
         // shared groups: as many splits of the union as fill the chip together
@@ -693,6 +740,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         size_t n_merge = 0;
         for (int i = 0; i < n_calls && want_items; ++i) if (cds[(size_t)i].n_splits > 1) n_merge += (size_t)cds[(size_t)i].n_q;
         for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) n_merge += (size_t)gr.n_rows;
+        n_merge += tail_rows.size();
         P.lay = make_layout(n_calls, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
                             sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
                             bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
@@ -757,6 +805,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 for (int q = 0; q < P.res[i].n_q; ++q)
                     hm[P.n_merge_rows++] = PcMergeRow{cds[i].q_off + q, cds[i].part_off + (q << cds[i].part_wide),
                                                       cds[i].n_splits | (cds[i].part_wide ? PC_MERGE_WIDE : 0), P.res[i].n_q};
+        if (!tail_rows.empty() && wanted(tail.second))
+            for (const PcMergeRow &mr : tail_rows) hm[P.n_merge_rows++] = mr;
         for (const PcShGroup &gr : sp.groups)
             if (wanted(gr.n_splits))
                 for (int q = 0; q < gr.n_rows; ++q) hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + q, gr.n_splits, gr.n_rows};
