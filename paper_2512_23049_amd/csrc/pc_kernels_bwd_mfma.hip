@@ -60,6 +60,18 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t &w0, uint32_t 
     a -= bf_lo(w1); b -= bf_hi(w1);
     w2 = pack_bf16(a, b);
 }
+// zeros in the place of Inf and NaN
+__device__ __forceinline__ bf16x8 finite8(bf16x8 x)
+{
+    uint4 u = __builtin_bit_cast(uint4, x);
+    uint32_t *w = reinterpret_cast<uint32_t *>(&u);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        w[j] = (w[j] & 0x7F80u) == 0x7F80u ? w[j] & 0xFFFF0000u : w[j];
+        w[j] = (w[j] & 0x7F800000u) == 0x7F800000u ? w[j] & 0xFFFFu : w[j];
+    }
+    return __builtin_bit_cast(bf16x8, u);
+}
 struct Pieces { bf16x8 p[3]; };
 __device__ __forceinline__ Pieces split8(const float *v)
 {
@@ -168,7 +180,8 @@ __global__ __launch_bounds__(256) void pc_bwd_prep_kernel(PcLaunch L, PcBwd B)
     uint4 glo = make_uint4(0, 0, 0, 0), ghi = glo;
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = y[j] = 0.f;
-    if (row < cd.n_q) {
+    // (a row that saw nothing, or a score that is not a number, has no gradient: it is taken as zeros)
+    if (row < cd.n_q && B.lse[(int64_t)(cd.q_off + row) * L.n_q_heads + h] > -INFINITY) {
         const int64_t R = cd.q_off + row, at = (R * L.n_q_heads + h) * PC_D + 8 * c;
         const uint4 lo = ldg16((const uint16_t *)L.q + at), hi = ldg16((const uint16_t *)L.q + at + 64);
         glo = ldg16(B.d_out + at); ghi = ldg16(B.d_out + at + 64);
@@ -236,6 +249,7 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
     }
     if constexpr (DQ) { if (unit_ok && item.split == 0 && hh == 0) B.stat[U * 32 + n] = make_float2(lse2, delta); }
 
+    const bool some_dead = __builtin_amdgcn_ballot_w64(row_ok && lse2 == INFINITY) != 0;
     const RowMajor rk(perm_row(n), lane), rg(n, lane);
     const ValuesByKey<true> rv(lane);
     const unsigned lds_k = (unsigned)(uintptr_t)&s_k[0][0], lds_v = (unsigned)(uintptr_t)&s_v[0][0], lds_g = (unsigned)(uintptr_t)&s_g[0][0] + wave * TILE_BYTES;
@@ -342,6 +356,16 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
                 }
                 cur = seg;
             }
+            if (DQ && (flags & PC_TILE_SELF)) {
+                // A tile of the new message (uniform over the workgroup): a zero takes a key that stands behind a row's own
+                // token out of dq only while it is finite, which the caller's tokens need not be.  (A row that sees such a
+                // key has no gradient.)
+                uint4 *chunk = reinterpret_cast<uint4 *>(&s_k[slot][0]) + threadIdx.x;
+                const bf16x8 raw = __builtin_bit_cast(bf16x8, *chunk);
+                *chunk = __builtin_bit_cast(uint4, finite8(raw));
+                __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+                ring_barrier();
+            }
             d[AHEAD] = describe(t + AHEAD);
             request(d[AHEAD], (slot + AHEAD) & (RING - 1));
             if (unit_ok) {
@@ -360,17 +384,16 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
                 for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rv.get(vt, ks), rg.by_row(lds_g, ks), dp);
                 const int valid = flags & 0xFF;
                 const bool self = (flags & PC_TILE_SELF) != 0;
-                float w[16];
+                float w[16];                             // p dp, or p (dp - Delta)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) w[r] = ex2(__builtin_fmaf(s[r], L.scale_log2, -lse2));
-                if (valid < PC_TILE || (self && key0 + PC_TILE - 1 > blk_lim_lo)) {      // ragged or causal tile (uniform)
-                    const int lim = self ? min(valid, self_lim - key0 + 1) : valid;
+                for (int r = 0; r < 16; ++r) w[r] = ex2(__builtin_fmaf(s[r], L.scale_log2, -lse2)) * (DQ ? dp[r] - delta : dp[r]);
+                // (masked behind the product: the value of a token behind the row's own is the caller's and need not be finite)
+                if (valid < PC_TILE || some_dead || (self && key0 + PC_TILE - 1 > blk_lim_lo)) {      // ragged or causal tile (uniform)
+                    const int lim = lse2 == INFINITY ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) w[r] = (16 * (r >> 3) + 8 * hh + (r & 7) < lim) ? w[r] : 0.f;
                 }
                 if constexpr (DQ) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) w[r] *= dp[r] - delta;
 #pragma unroll
                     for (int st = 0; st < 2; ++st) {
                         const Pieces ds = split8(w + 8 * st);
@@ -384,7 +407,7 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
                     }
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) dsum = __builtin_fmaf(w[r], dp[r], dsum);
+                    for (int r = 0; r < 16; ++r) dsum += w[r];
                 }
             }
 #pragma unroll
@@ -432,7 +455,8 @@ __global__ __launch_bounds__(256) void pc_bwd_finish_kernel(PcLaunch L, PcBwd B)
         const int row = 32 * rb.y + r;
         if (row >= cd.n_q) continue;
         const int64_t R = cd.q_off + row;
-        const float4 a = *reinterpret_cast<const float4 *>(&s_o[r][4 * c]), b = *reinterpret_cast<const float4 *>(&s_o[r][4 * c + 64]);
+        float4 a = *reinterpret_cast<const float4 *>(&s_o[r][4 * c]), b = *reinterpret_cast<const float4 *>(&s_o[r][4 * c + 64]);
+        if (!(B.stat[U * 32 + r].x < INFINITY)) a = b = make_float4(0.f, 0.f, 0.f, 0.f);       // the row saw nothing
         const float4 *rot = reinterpret_cast<const float4 *>(L.rot_q + R * (PC_D / 2) + 4 * c);
         const float4 c0 = rot[0], c1 = rot[1];
         float *out = B.d_q + (R * L.n_q_heads + h) * PC_D + 4 * c;
@@ -567,8 +591,9 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
             const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
-            p[r] = ex2(__builtin_fmaf(s[r], L.scale_log2, -x.x));
-            p[r + 1] = ex2(__builtin_fmaf(s[r + 1], L.scale_log2, -x.z));
+            // (the maximum takes a NaN to 0: a key that is none leaves the rows that saw it without a gradient, see prep)
+            p[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -x.x), -1e30f));
+            p[r + 1] = ex2(fmaxf(__builtin_fmaf(s[r + 1], L.scale_log2, -x.z), -1e30f));
             w[r] = dp[r] - x.y;
             w[r + 1] = dp[r + 1] - x.w;
         }

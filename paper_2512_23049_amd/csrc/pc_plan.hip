@@ -252,6 +252,7 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
                 if (hm.len <= 0) continue;
                 self_occ += e.x == rc.self_msg;
                 const int32_t u = marks[e.x].epoch == epoch ? marks[e.x].value : first_of(e.x);
+                if (usegs.size() > usegs_max) break;
                 uint32_t &vis = usegs[(size_t)u].vis[word];
                 once &= (vis & bit) == 0;
                 vis |= bit;

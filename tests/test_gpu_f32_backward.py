@@ -30,8 +30,8 @@ def test_many_blocks_over_a_long_history():
     run_case(lens, [([(m, 300 * m) for m in range(30)], 30, 13000, 300)], 8, 2, dtype="f32", D=64)
 
 
-@pytest.mark.parametrize("D", [64, 128])
-def test_later_tokens_that_are_not_finite(D):
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 128)])
+def test_later_tokens_that_are_not_finite(dtype, D):
     """What stands behind a row's own token does not reach its gradient."""
     import torch
     from paper_2512_23049_amd import binding
@@ -39,17 +39,19 @@ def test_later_tokens_that_are_not_finite(D):
     h_q, h_kv, n, at = 4, 2, 64, 37
     rng = torch.Generator(device="cuda:0")
     rng.manual_seed(2)
-    k, v, q, g = (torch.randn((n, h, D), generator=rng, device="cuda:0") for h in (h_kv, h_kv, h_q, h_q))
-    grads = []
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    k, v, q, g = (torch.randn((n, h, D), generator=rng, device="cuda:0").to(td) for h in (h_kv, h_kv, h_q, h_q))
+    grads, lse = [], torch.empty((n, h_q), device="cuda:0")
     for bad in (False, True):
         if bad:
             k[at, :, 3] = float("inf")
             v[at, :, 5] = float("nan")
-        cache = binding.Cache(h_q, h_kv, D, binding.PC_F32, 10000.0, 128, 2)
+        cache = binding.Cache(h_q, h_kv, D, binding.PC_F32 if dtype == "f32" else binding.PC_BF16, 10000.0, 128, 2)
         m = cache.append_message(k.data_ptr(), v.data_ptr(), n)
         call = [Call([], m, 0, n, None)]
-        out, lse = torch.empty((n, h_q, D), device="cuda:0"), torch.empty((n, h_q), device="cuda:0")
-        cache.attend(call, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        if not bad or dtype == "f32":                    # (the bf16 forward asks for finite values in a whole tile)
+            out = torch.empty((n, h_q, D), dtype=td, device="cuda:0")
+            cache.attend(call, q.data_ptr(), out.data_ptr(), lse.data_ptr())
         d_q = torch.empty((n, h_q, D), device="cuda:0")
         d_k, d_v = (torch.zeros((128, h_kv, D), device="cuda:0") for _ in range(2))
         cache.attend_backward(call, q.data_ptr(), lse.data_ptr(), g.data_ptr(), d_q.data_ptr(), d_k.data_ptr(), d_v.data_ptr())
@@ -58,3 +60,36 @@ def test_later_tokens_that_are_not_finite(D):
         grads.append(d_q[:at].clone())
     assert torch.isfinite(grads[1]).all()
     assert float((grads[1] - grads[0]).norm() / grads[0].norm()) <= 3e-6
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 128)])
+def test_rows_that_saw_nothing(dtype, D):
+    """A log-sum-exp of -inf: no gradient, whatever the row's query and output gradient hold."""
+    import torch
+    from paper_2512_23049_amd import binding
+    from pc_inputs import Call
+    h_q, h_kv, n = 4, 2, 70
+    rng = torch.Generator(device="cuda:0")
+    rng.manual_seed(3)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    k, v, q, g = (torch.randn((n, h, D), generator=rng, device="cuda:0").to(td) for h in (h_kv, h_kv, h_q, h_q))
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_F32 if dtype == "f32" else binding.PC_BF16, 10000.0, 128, 2)
+    m = cache.append_message(k.data_ptr(), v.data_ptr(), n)
+    call = [Call([], m, 0, n, None)]
+    out, lse = torch.empty((n, h_q, D), dtype=td, device="cuda:0"), torch.empty((n, h_q), device="cuda:0")
+    cache.attend(call, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+    dead = [5, 33, 69]
+    lse[dead] = -float("inf")
+    res = []
+    for bad in (False, True):
+        if bad:
+            q[dead], g[dead] = float("nan"), float("inf")
+        d_q = torch.full((n, h_q, D), 7.0, device="cuda:0")
+        d_k, d_v = (torch.zeros((128, h_kv, D), device="cuda:0") for _ in range(2))
+        cache.attend_backward(call, q.data_ptr(), lse.data_ptr(), g.data_ptr(), d_q.data_ptr(), d_k.data_ptr(), d_v.data_ptr())
+        torch.cuda.synchronize()
+        res.append((d_q, d_k, d_v))
+    cache.close()
+    assert (res[1][0][dead] == 0).all()
+    for a, b in zip(*res):
+        assert torch.isfinite(b).all() and float((a - b).norm()) <= 1e-6 * float(a.norm())
