@@ -372,7 +372,8 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int c = 8 * (r >> 2) + 4 * hh + (r & 3);
-                const float x = expf(fmaf(p[r], scale, -s_lse[buf][c]));
+                // (the maximum: the components of an infinite key are turned into NaN; a row with a log-sum-exp saw it at a score of -inf)
+                const float x = expf(fmaxf(fmaf(p[r], scale, -s_lse[buf][c]), -1e30f));
                 const bool ok = s_lse[buf][c] < INFINITY && (!causal || key0 + n <= s_lim[buf][c]);
                 p[r] = ok ? x : 0.f;
                 w[r] = ok ? x * (w[r] - s_del[buf][c]) * scale : 0.f;

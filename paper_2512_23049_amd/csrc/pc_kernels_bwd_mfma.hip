@@ -60,15 +60,16 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t &w0, uint32_t 
     a -= bf_lo(w1); b -= bf_hi(w1);
     w2 = pack_bf16(a, b);
 }
-// zeros in the place of Inf and NaN
+// the largest finite numbers in the place of infinities, zeros in the place of NaN
 __device__ __forceinline__ bf16x8 finite8(bf16x8 x)
 {
     uint4 u = __builtin_bit_cast(uint4, x);
     uint32_t *w = reinterpret_cast<uint32_t *>(&u);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        w[j] = (w[j] & 0x7F80u) == 0x7F80u ? w[j] & 0xFFFF0000u : w[j];
-        w[j] = (w[j] & 0x7F800000u) == 0x7F800000u ? w[j] & 0xFFFFu : w[j];
+        const uint32_t lo = w[j] & 0x7FFFu, hi = w[j] & 0x7FFF0000u;
+        w[j] = lo > 0x7F80u ? w[j] & 0xFFFF0000u : w[j] - (lo == 0x7F80u ? 1u : 0u);
+        w[j] = hi > 0x7F800000u ? w[j] & 0xFFFFu : w[j] - (hi == 0x7F800000u ? 0x10000u : 0u);
     }
     return __builtin_bit_cast(bf16x8, u);
 }
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
             if (DQ && (flags & PC_TILE_SELF)) {
                 // A tile of the new message (uniform over the workgroup): a zero takes a key that stands behind a row's own
                 // token out of dq only while it is finite, which the caller's tokens need not be.  (A row that sees such a
-                // key has no gradient.)
+                // key has no gradient, or, where its score is -inf, a probability of 0: a score of -1e38 gives the same.)
                 uint4 *chunk = reinterpret_cast<uint4 *>(&s_k[slot][0]) + threadIdx.x;
                 const bf16x8 raw = __builtin_bit_cast(bf16x8, *chunk);
                 *chunk = __builtin_bit_cast(uint4, finite8(raw));
@@ -386,7 +387,8 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
                 const bool self = (flags & PC_TILE_SELF) != 0;
                 float w[16];                             // p dp, or p (dp - Delta)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) w[r] = ex2(__builtin_fmaf(s[r], L.scale_log2, -lse2)) * (DQ ? dp[r] - delta : dp[r]);
+                for (int r = 0; r < 16; ++r)             // (the maximum: an infinite key times a piece that is 0 is a NaN, see the key-major kernel)
+                    w[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -lse2), -1e30f)) * (DQ ? dp[r] - delta : dp[r]);
                 // (masked behind the product: the value of a token behind the row's own is the caller's and need not be finite)
                 if (valid < PC_TILE || some_dead || (self && key0 + PC_TILE - 1 > blk_lim_lo)) {      // ragged or causal tile (uniform)
                     const int lim = lse2 == INFINITY ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
@@ -591,7 +593,8 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
             const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
-            // (the maximum takes a NaN to 0: a key that is none leaves the rows that saw it without a gradient, see prep)
+            // (The maximum takes a NaN to a probability of 0.  A row that saw a NaN or +inf has no gradient, see prep; where a row
+            // that has one meets an infinite key its score is -inf, which the pieces' products turn into NaN.)
             p[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -x.x), -1e30f));
             p[r + 1] = ex2(fmaxf(__builtin_fmaf(s[r + 1], L.scale_log2, -x.z), -1e30f));
             w[r] = dp[r] - x.y;
