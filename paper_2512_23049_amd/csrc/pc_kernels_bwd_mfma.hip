@@ -553,6 +553,20 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(vf[ks]));        // (read before the slot is requested again)
     }
+    // A value that is not finite makes dp a NaN for every row of a block, and no zero takes the rows without a gradient out of dK
+    // again (a select per probability would: 24 us of 740 for a training step).  It is taken as zeros here, and its key's dK is
+    // a NaN at the end if a row with a gradient sees it.
+    uint64_t odd = 0;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        const uint4 u = __builtin_bit_cast(uint4, vf[ks]);
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bad |= (w[j] & 0x7F80u) == 0x7F80u || (w[j] & 0x7F800000u) == 0x7F800000u;
+        odd |= __builtin_amdgcn_ballot_w64(bad);
+        if (bad) vf[ks] = frag4(0, 0, 0, 0);
+    }
     f32x16 dk[4], dv[4];
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -634,6 +648,19 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
     wait_vm<0>();
     ring_barrier();                                      // the ring is free: each wave turns its sums round in 17 KB of it
     if (!active) return;
+    if (odd != 0) {
+        bool hit = false;
+        for (int rt = item.rt_begin; rt < item.rt_end; ++rt) {
+            const int b = rt / g;
+            const float2 *stat = B.stat + (u_base + (int64_t)b * L.n_q_heads + (rt - b * g)) * 32;
+            for (int r = 0; r < 32; ++r) hit |= stat[r].x < INFINITY && (!self || key0 + n <= tok0 + 32 * b + r);
+        }
+        if (hit && (((odd | odd >> 32) >> n) & 1) != 0)
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) dk[db][r] = __builtin_nanf("");
+    }
     float *stg = reinterpret_cast<float *>(&s_q[0][0]) + wave * (32 * (PC_D + 4));
     const int valid = flags & 0xFF;
 #pragma unroll

@@ -1,5 +1,6 @@
 """Infinite and NaN keys and values in the gradient, both cache types.  A row whose log-sum-exp is finite gives a key with a score
-of -inf a probability of exactly zero, so the key leaves no trace in the gradients of anything else."""
+of -inf a probability of exactly zero, so the key leaves no trace in the gradients of anything else; a row that saw nothing (or a score that is no
+number) leaves no trace at all, whatever the values hold that it would have met."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,38 @@ def test_infinite_key_with_a_score_of_minus_infinity(dtype, D):
     for a, b in zip(k_a + v_a, k_b + v_b):
         assert same(a, b)
     assert not k_b[0][37].any() and not v_b[1][33].any()
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("n_dead", [1, 33])
+def test_dead_rows_leave_no_trace_of_values_that_are_not_finite(dtype, D, n_dead):
+    import torch
+    from pc_inputs import Call
+    h_q, h_kv, n = 4, 2, 33
+    k, v, q, g = tensors(dtype, D, [(n, h_kv), (n, h_kv), (n, h_q), (n, h_q)], 6)
+    call = Call([], 0, 0, n, None)
+    lse = gradients(dtype, D, h_q, h_kv, [(k, v)], call, q, g)[0]
+    lse[n - n_dead:] = -float("inf")
+    res = []
+    for bad in (False, True):
+        if bad:
+            k[n - n_dead:, :, 3], v[n - n_dead:, 1, 7], v[n - n_dead:, 0, 7] = float("nan"), float("nan"), float("inf")
+        res.append(gradients(dtype, D, h_q, h_kv, [(k, v)], call, q, g, lse)[1:])
+    (q_a, k_a, v_a), (q_b, k_b, v_b) = res
+    assert not q_b[n - n_dead:].any() and not k_b[0][n - n_dead:].any() and not v_b[0][n - n_dead:].any()
+    for a, b in ((q_a, q_b), (k_a[0], k_b[0]), (v_a[0], v_b[0])):
+        assert same(a, b)
+
+
+def test_values_that_are_not_finite_reach_their_own_gradient():
+    """A row with a gradient that sees such a value has none that is a number, and neither has the value's key."""
+    import torch
+    from pc_inputs import Call
+    D, h_q, h_kv = 128, 4, 2
+    k, v, q, g = tensors("bf16", D, [(70, h_kv), (70, h_kv), (70, h_q), (70, h_q)], 7)
+    call = Call([], 0, 0, 70, None)
+    lse, q_a, k_a, v_a = gradients("bf16", D, h_q, h_kv, [(k, v)], call, q, g)
+    v[40, 0, 5], v[40, 1, 6] = float("nan"), float("inf")
+    _, q_b, k_b, v_b = gradients("bf16", D, h_q, h_kv, [(k, v)], call, q, g, lse)
+    assert same(q_a[:40], q_b[:40]) and same(v_a[0], v_b[0])
+    assert torch.isnan(k_b[0][40]).all() and not torch.isfinite(q_b[40:]).any()
