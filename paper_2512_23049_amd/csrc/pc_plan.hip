@@ -583,6 +583,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         return r.tiles > 0 && !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
     };
     auto pre_groups_of = [&](const Resolved &r) { return (((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves; };
+    // the plain rule: as many splits as bring the batch to 256 workgroups, of 16 of the tiles that are walked at least
+    auto plain_splits = [](int64_t groups, int tiles) { return (int)std::min<int64_t>((256 + groups - 1) / groups, std::max(1, tiles / 16)); };
     int pre_chunk = 1;                                   // tiles a prefill split takes
     if (want_items && bf16 && pre_groups > 0 && c->prefill_tiles_per_split == 0) pre_chunk = prefill_chunk(c, P, sp, pre_groups);
     std::pair<int, int> tail{0, 1};                      // last prefill items that are split, and into how many parts
@@ -627,7 +629,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 const int chunk = std::max(1, (T + ns - 1) / ns);
                 ns = std::max(1, (T + chunk - 1) / chunk);
                 cd.n_splits = ns;
-                wide = ns > 1 && small_splits && c->decode_tiles_per_split == 0 && T < 32;
+                wide = ns > 1 && small_splits && c->decode_tiles_per_split == 0 && plain_splits(dec_groups, T) == 1;
                 for (int s = 0; s < ns; ++s) {
                     PcItem it{}; it.call = i; it.unit0 = 0; it.tile_begin = s * chunk; it.tile_end = std::min(T, (s + 1) * chunk); it.split = s;
                     it.tile_tab0 = cd.tile_off;
@@ -655,7 +657,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 int ns = 1;
                 if (c->prefill_tiles_per_split > 0) ns = (Tc + c->prefill_tiles_per_split - 1) / c->prefill_tiles_per_split;
                 else if (small_splits) ns = (int)(((int64_t)Tc + pre_chunk - 1) / pre_chunk);
-                else if (pre_groups < 256) ns = (int)std::min<int64_t>((256 + pre_groups - 1) / pre_groups, std::max(1, Tc / 16));
+                else ns = plain_splits(pre_groups, Tc);
                 ns = std::max(1, std::min(MAX_SPLITS, ns));
                 const int chunk = std::max(1, (Tc + ns - 1) / ns);
                 ns = std::max(1, (Tc + chunk - 1) / chunk);
@@ -665,7 +667,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 // divide THAT count evenly, so the groups with early rows do not end up with a nearly empty
                 // last split.
                 const int parent_tiles = Tc - self_tiles;
-                wide = ns > 1 && small_splits && c->prefill_tiles_per_split == 0 && T < 32;
+                wide = ns > 1 && small_splits && c->prefill_tiles_per_split == 0 && plain_splits(pre_groups, Tc) == 1;
                 for (int gidx = 0; gidx < groups; ++gidx, --items_left) {
                     int Tg = Tc;
                     if (r.self_msg >= 0) {
@@ -696,9 +698,9 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                     }
                 }
             }
-            // Partial results are fp32 where 16 tiles a split and whole batches of 256 workgroups would not have split the rows
-            // at all, so that no sum is held in fewer bits for being split; the others, fp16, are bound by the bytes they
-            // move (512 rows x 32 heads in 4 splits: 17 MB, 8 us).
+            // Partial results are fp32 where the plain rule would not have split the rows at all, so that no sum is held in fewer
+            // bits for being split; the others, fp16, are bound by the bytes they move (512 rows x 32 heads in 4 splits: 17 MB,
+            // 8 us).
             cd.part_wide = wide;
             if (cd.n_splits > 1) { cd.part_off = (int32_t)part_rows; part_rows += ((int64_t)cd.n_splits * cd.n_q) << cd.part_wide; }
         }
