@@ -310,6 +310,30 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
     }
 }
 
+// Tokens of a call's parents; tiles of its new message (its last extent)
+static int64_t parent_tokens(const pc_cache *c, const Resolved &r)
+{
+    int64_t n = 0;
+    for (const int2 &e : r.sel) n += c->msgs[(size_t)e.x].len;
+    return n;
+}
+static int own_tiles_of(const Resolved &r) { return r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0; }
+// Gather: a call with many query rows reads its keys and values from a packed copy (the gather pass: keys
+// turned to the call's positions, no padding between messages), which moves 8192 bytes per listed token once
+// (about 1.8 ns) and saves the turns of the queries at every message, the ragged tile at every message's end
+// and the per-tile lookups: 15 to 25 % of the attention's own time, which is rows x heads x 0.47 ps per token.
+// The copy pays from rows x query heads of about 20 thousand on; taken from 32768 on.  (Not with a fixed
+// workspace, which the copy may not fit into.)
+static bool gathers(const pc_cache *c, const Planned &P, const Resolved &r)
+{
+    return r.tiles > 0 && !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
+}
+// Tiles the prefill kernel walks for a call: those of the copy, or those of the cache
+static int walked_tiles(const pc_cache *c, const Planned &P, const Resolved &r)
+{
+    return gathers(c, P, r) ? (int)((parent_tokens(c, r) + PC_TILE - 1) / PC_TILE) + own_tiles_of(r) : r.tiles;
+}
+
 // Tiles a split of the batch's prefill calls takes.  A workgroup fills a compute unit and takes about a start and an end of
 // PRE_FIXED and PRE_TILE a tile (packed walk: PRE_TILE_PACKED), so a launch takes rounds of 256 of them: more splits shorten
 // a round until there is one more of them, and their parts are written, read again and added by one more launch.
@@ -329,10 +353,11 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
         const Resolved &r = P.res[i];
         if (sp.in_shared[i] || (int64_t)r.n_q * c->g <= 16) continue;
         const int64_t groups = (int64_t)((((r.n_q + 31) / 32) * c->g + P.pre_waves - 1) / P.pre_waves) * c->cfg.n_kv_heads;
-        if (!shapes.empty() && shapes.back().tiles == r.tiles && shapes.back().n_q == r.n_q) shapes.back().groups += groups;
-        else shapes.push_back(Shape{groups, r.n_q, r.tiles});
-        longest = std::max(longest, r.tiles);
-        packed |= !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
+        const int tiles = walked_tiles(c, P, r);
+        if (!shapes.empty() && shapes.back().tiles == tiles && shapes.back().n_q == r.n_q) shapes.back().groups += groups;
+        else shapes.push_back(Shape{groups, r.n_q, tiles});
+        longest = std::max(longest, tiles);
+        packed |= gathers(c, P, r);
     }
     const double tile = packed ? PRE_TILE_PACKED : PRE_TILE;
     int best = std::max(longest, 1), last = 0;
@@ -367,8 +392,8 @@ static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, con
     for (size_t i = 0; i < P.res.size(); ++i) {
         const Resolved &r = P.res[i];
         if (sp.in_shared[i] || (int64_t)r.n_q * g <= 16) continue;
-        tiles = std::max(tiles, r.tiles);
-        kinds |= !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768)) ? 2 : 1;
+        tiles = std::max(tiles, walked_tiles(c, P, r));
+        kinds |= gathers(c, P, r) ? 2 : 1;
     }
     const int tail = (int)(pre_groups / H_kv % per_round);
     if (tail == 0 || kinds == 3) return {0, 1};          // (two kinds of calls are two launches)
@@ -577,11 +602,6 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             if (r.n_q * g > 16) pre_groups += (int64_t)((((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves) * H_kv;
             else dec_groups += H_kv;
         }
-    auto self_tiles_of = [&](const Resolved &r) { return r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0; };
-    auto parent_tokens = [&](const Resolved &r) { int64_t n = 0; for (const int2 &e : r.sel) n += c->msgs[(size_t)e.x].len; return n; };
-    auto gathers = [&](const Resolved &r) {
-        return r.tiles > 0 && !P.fixed_ws && (c->key_gather == 2 || (c->key_gather == 0 && (int64_t)r.n_q * c->cfg.n_q_heads >= 32768));
-    };
     auto pre_groups_of = [&](const Resolved &r) { return (((r.n_q + 31) / 32) * g + P.pre_waves - 1) / P.pre_waves; };
     // the plain rule: as many splits as bring the batch to 256 workgroups, of 16 of the tiles that are walked at least
     auto plain_splits = [](int64_t groups, int tiles) { return (int)std::min<int64_t>((256 + groups - 1) / groups, std::max(1, tiles / 16)); };
@@ -636,22 +656,16 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                     dec.push_back(it);
                 }
             } else {
-                // Gather: a call with many query rows reads its keys and values from a packed copy (the gather pass: keys
-                // turned to the call's positions, no padding between messages), which moves 8192 bytes per listed token once
-                // (about 1.8 ns) and saves the turns of the queries at every message, the ragged tile at every message's end
-                // and the per-tile lookups: 15 to 25 % of the attention's own time, which is rows x heads x 0.47 ps per token.
-                // The copy pays from rows x query heads of about 20 thousand on; taken from 32768 on.  (Not with a fixed
-                // workspace, which the copy may not fit into.)
-                const int self_tiles = self_tiles_of(r);
-                const int64_t n_par = parent_tokens(r);
+                const int own_tiles = own_tiles_of(r);
+                const int64_t n_par = parent_tokens(c, r);
                 const int p_tiles = (int)((n_par + PC_TILE - 1) / PC_TILE);
-                const bool packed = gathers(r) && kg_tiles + p_tiles + self_tiles < ((int64_t)1 << 24);
+                const bool packed = gathers(c, P, r) && kg_tiles + p_tiles + own_tiles < ((int64_t)1 << 24);
                 if (packed) {
                     cd.kg_tile0 = (int32_t)kg_tiles; cd.n_par = (int32_t)n_par;
-                    kg.push_back(PcGatherItem{i, (int32_t)kg_tiles, p_tiles + self_tiles, (int32_t)n_par});
-                    kg_tiles += p_tiles + self_tiles;
+                    kg.push_back(PcGatherItem{i, (int32_t)kg_tiles, p_tiles + own_tiles, (int32_t)n_par});
+                    kg_tiles += p_tiles + own_tiles;
                 }
-                const int Tc = packed ? p_tiles + self_tiles : T;        // tiles the attention kernel walks for this call
+                const int Tc = packed ? p_tiles + own_tiles : T;        // tiles the attention kernel walks for this call
                 const int units = ((r.n_q + 31) / 32) * g;
                 const int groups = pre_groups_of(r);
                 int ns = 1;
@@ -666,14 +680,14 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 // causal limit of its last row (the kernel relies on tile_end being cut there); its splits
                 // divide THAT count evenly, so the groups with early rows do not end up with a nearly empty
                 // last split.
-                const int parent_tiles = Tc - self_tiles;
+                const int parent_tiles = Tc - own_tiles;
                 wide = ns > 1 && small_splits && c->prefill_tiles_per_split == 0 && plain_splits(pre_groups, Tc) == 1;
                 for (int gidx = 0; gidx < groups; ++gidx, --items_left) {
                     int Tg = Tc;
                     if (r.self_msg >= 0) {
                         const int last_unit = std::min(gidx * P.pre_waves + P.pre_waves - 1, units - 1);
                         const int lim = (r.self_len - r.n_q) + std::min(32 * (last_unit / g) + 31, r.n_q - 1);   // last own token seen
-                        Tg = parent_tiles + std::min(self_tiles, lim / PC_TILE + 1);
+                        Tg = parent_tiles + std::min(own_tiles, lim / PC_TILE + 1);
                     }
                     // partial rows: those of the whole call, or of an item of the last round alone
                     int parts = ns, row0 = 0, n_rows = r.n_q;

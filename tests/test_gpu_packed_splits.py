@@ -54,3 +54,11 @@ def test_parts_of_a_short_walk_are_fp32(h_q, h_kv, n_q, n_msgs, msg_len, gather)
     rel = float((a - b).norm() / b.norm())
     print("split against whole:", rel, float((lse_a - lse_b).abs().max()), flush=True)
     assert rel <= 6.6e-4
+
+
+# 512 rows x 64 heads over 480 (300) tokens in 31 (26) tiles: whole, one round of workgroups and no merge, costs less than two parts
+@pytest.mark.parametrize("n_msgs,msg_len", [(24, 20), (30, 10)])
+def test_split_follows_the_tiles_that_are_walked(n_msgs, msg_len):
+    (_, _, many), = walk(64, 8, [msg_len] * n_msgs, 512, 0, (0,))
+    (_, _, one), = walk(64, 8, [msg_len * n_msgs], 512, 0, (0,))
+    assert many == one == 0
