@@ -186,11 +186,12 @@ int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, cons
                        const pc_call *calls, int32_t n_calls, const void *q, void *out, float *lse, void *stream);
 
 /* pc_attend for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same arguments, same kernels, same results (bit for bit) as pc_attend; the
- * per-call workspace (staged descriptors, the device-built plan, split partials) lives in a fixed array of
- * PC_STATIC_WS_BYTES (32 MiB) that the library holds on every GPU it runs on until the process ends, and the
- * function calls no hipMalloc, hipFree or other allocating routine.  A batch whose workspace exceeds that size, or
- * whose staged descriptors exceed one slot of the cache's pinned staging ring (1 MiB), is rejected with
+ * harnesses that forbid hipMalloc.  Same arguments, same kernels, same results (bit for bit) as pc_attend, but for calls
+ * that pc_attend gathers (see pc_set_key_gather); the per-call workspace (staged descriptors, the device-built plan, split
+ * partials) lives in a fixed array of PC_STATIC_WS_BYTES (32 MiB) that the library holds on every GPU it runs on until the
+ * process ends, and the function calls no hipMalloc, hipFree or other allocating routine.  A batch whose workspace exceeds
+ * that size with its calls split by the plain rule (at least 16 tiles of 32 keys a split, as many splits as bring the batch
+ * to 256 workgroups), or whose staged descriptors then exceed one slot of the cache's pinned staging ring (1 MiB), is rejected with
  * PC_ERR_NO_SPACE before anything is enqueued (pc_last_error names both sizes).  Kernel timing (pc_profile_enable)
  * does not cover it.  Every cache on a GPU shares that GPU's array, which keeps the last call's contents (nothing
  * in it has to start at zero: every call writes what it reads): calls on one GPU that overlap in time - two

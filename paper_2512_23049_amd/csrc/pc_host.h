@@ -28,6 +28,7 @@ struct ProfRec { int cls; hipEvent_t a, b; };
 
 constexpr int N_STAGE = 4;
 constexpr int MAX_SPLITS = 128;
+constexpr size_t STAGE_BYTES = (size_t)1 << 20;          // a slot of the pinned ring at the cache's creation
 // staged blocks up to this size are read by the plan builder where they are, in pinned memory
 constexpr size_t HOST_READ_BYTES = 256 << 10;
 

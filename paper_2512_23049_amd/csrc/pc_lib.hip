@@ -120,8 +120,8 @@ int32_t pc_cache_create(const pc_config *cfg, pc_cache **out)
     if (hipMalloc(&c->tok_dev, (size_t)1 << 16) != hipSuccess) return bail(PC_ERR_HIP);
     c->tok_cap = (size_t)1 << 16;
     for (int i = 0; i < N_STAGE; ++i) {
-        if (hipHostMalloc(&c->stage[i].host, (size_t)1 << 20, hipHostMallocCoherent) != hipSuccess) return bail(PC_ERR_HIP);
-        c->stage[i].cap = (size_t)1 << 20;
+        if (hipHostMalloc(&c->stage[i].host, STAGE_BYTES, hipHostMallocCoherent) != hipSuccess) return bail(PC_ERR_HIP);
+        c->stage[i].cap = STAGE_BYTES;
         if (hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming) != hipSuccess) return bail(PC_ERR_HIP);
     }
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) return bail(PC_ERR_HIP);

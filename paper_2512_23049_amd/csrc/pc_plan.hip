@@ -342,7 +342,10 @@ static int walked_tiles(const pc_cache *c, const Planned &P, const Resolved &r)
 // 49 us for 5 splits of 56 groups, 33 us for 4.)
 constexpr double PRE_FIXED = 9.0, PRE_TILE = 1.0, PRE_TILE_PACKED = 0.75, MERGE_FIXED = 4.5, PART_BYTES_US = 3.5e6;
 constexpr int PRE_LEAST = 4;                             // tiles of a split: below, the start is all there is
-static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups)
+// Partial results of a group (8 units of 32 rows: outputs of 2 bytes, a maximum and a sum) in one split; twice that in fp32.
+// part_max: bytes all of them may take.
+constexpr int64_t GROUP_PART_BYTES = 8 * 32 * (128 * 2 + 8);
+static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups, int64_t part_max)
 {
     if (pre_groups >= 256) return INT32_MAX;             // the chip is full (prefill_tail sees to the last round)
     struct Shape { int64_t groups; int n_q, tiles; };    // consecutive calls of the same rows and tiles
@@ -373,7 +376,8 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
             wgs += sh.groups * ns;
             if (ns > 1) part += sh.groups * ns * (sh.tiles < 32 ? 2 : 1);
         }
-        // (a group is 8 units of 32 rows: 8 * 32 * 128 partial outputs of 2 bytes, or 4, written and read)
+        if (k > 1 && part * GROUP_PART_BYTES > part_max) continue;
+        // (8 * 32 * 128 partial outputs of 2 bytes, or 4, written and read)
         const double us = (double)((wgs + 255) / 256) * (PRE_FIXED + tile * chunk) + (part ? MERGE_FIXED + (double)part * 131072.0 / PART_BYTES_US : 0.0);
         if (k == 1 || us < best_us) { best_us = us; best = chunk; }
     }
@@ -383,7 +387,7 @@ static int prefill_chunk(const pc_cache *c, const Planned &P, const SharedPlan &
 // A batch of more than 256 prefill groups runs in rounds, and a last round of a few groups takes as long as a full one: 280
 // groups, 2 rounds for 1.1 rounds of work.  The items of that last round are split, so that it fills the chip as well.
 // Returns how many of the last items (each n_kv_heads groups) are split, and into how many parts.
-static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups)
+static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, const SharedPlan &sp, int64_t pre_groups, int64_t part_max)
 {
     const int H_kv = c->cfg.n_kv_heads, g = c->g, per_round = 256 / H_kv;
     // (a row's heads must lie in one item, and a round hold whole items)
@@ -400,6 +404,7 @@ static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, con
     int best = 1;
     double best_us = 0;
     for (int k = 1; k <= std::min({MAX_SPLITS, tiles / PRE_LEAST, std::max(1, 4 * per_round / tail)}); ++k) {
+        if (k > 1 && (int64_t)tail * H_kv * k * 2 * GROUP_PART_BYTES > part_max) break;
         const double us = (double)((tail * k + per_round - 1) / per_round) * (PRE_FIXED + (kinds == 2 ? PRE_TILE_PACKED : PRE_TILE) * ((tiles + k - 1) / k)) +
                           (k > 1 ? MERGE_FIXED + (double)tail * H_kv * k * 262144.0 / PART_BYTES_US : 0.0);
         if (k == 1 || us < best_us) { best_us = us; best = k; }
@@ -606,16 +611,14 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     // the plain rule: as many splits as bring the batch to 256 workgroups, of 16 of the tiles that are walked at least
     auto plain_splits = [](int64_t groups, int tiles) { return (int)std::min<int64_t>((256 + groups - 1) / groups, std::max(1, tiles / 16)); };
     int pre_chunk = 1;                                   // tiles a prefill split takes
-    if (want_items && bf16 && pre_groups > 0 && c->prefill_tiles_per_split == 0) pre_chunk = prefill_chunk(c, P, sp, pre_groups);
     std::pair<int, int> tail{0, 1};                      // last prefill items that are split, and into how many parts
-    if (want_items && bf16) tail = prefill_tail(c, P, sp, pre_groups);
+    int64_t pre_part_rows = 0;                           // partial rows of prefill items among part_rows
     std::vector<PcMergeRow> tail_rows;
-    // small_splits: the rules for the number of splits as they stand.  Without it: at least 16 tiles a split and no more
-    // splits than bring the batch to 256 workgroups, which bounds the partial results (see below).
+    // small_splits: the rules for the number of splits as they stand.  Without it: the plain rule (see below).
     auto plan_calls = [&](bool small_splits) {
         dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear(); tail_rows.clear();
         int64_t items_left = pre_groups / H_kv;          // prefill items still to come
-        kg_tiles = part_rows = total_tiles = 0;
+        kg_tiles = part_rows = pre_part_rows = total_tiles = 0;
         q_off = seg_off = 0;
         for (int i = 0; i < n_calls; ++i) {
             Resolved &r = P.res[i];
@@ -700,6 +703,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                         for (int q = 0; q < n_rows; ++q)
                             tail_rows.push_back(PcMergeRow{cd.q_off + row0 + q, (int32_t)(part_rows + 2 * q), parts | PC_MERGE_WIDE, n_rows});
                         part_rows += 2 * (int64_t)parts * n_rows;
+                        pre_part_rows += 2 * (int64_t)parts * n_rows;
                     }
                     const int chunk_g = std::max(1, (Tg + parts - 1) / parts);
                     for (int s = 0; s < parts; ++s) {
@@ -716,7 +720,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             // bits for being split; the others, fp16, are bound by the bytes they move (512 rows x 32 heads in 4 splits: 17 MB,
             // 8 us).
             cd.part_wide = wide;
-            if (cd.n_splits > 1) { cd.part_off = (int32_t)part_rows; part_rows += ((int64_t)cd.n_splits * cd.n_q) << cd.part_wide; }
+            if (cd.n_splits > 1) {
+                const int64_t n = ((int64_t)cd.n_splits * cd.n_q) << cd.part_wide;
+                cd.part_off = (int32_t)part_rows;
+                part_rows += n;
+                if (r.n_q * g > 16) pre_part_rows += n;
+            }
         }
         // shared groups: as many splits of the union as fill the chip together
         for (size_t gi = 0; gi < sp.groups.size(); ++gi) {
@@ -738,10 +747,18 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             }
         }
     };
+    // the batch's work items; part_max: bytes the partial results of its prefill calls may take
+    auto plan_items = [&](bool small_splits, int64_t part_max) {
+        if (want_items && bf16 && c->prefill_tiles_per_split == 0) {
+            if (pre_groups > 0) pre_chunk = prefill_chunk(c, P, sp, pre_groups, part_max);
+            tail = prefill_tail(c, P, sp, pre_groups, part_max);
+        }
+        plan_calls(small_splits);
+        if (want_items && !bf16) plan_f32(c, P, cds, small_splits, pre, part_rows);
+    };
     BwdPlan bp;
-    plan_calls(true);
+    plan_items(true, INT64_MAX);
     if (P.backward && bf16) plan_backward(c, P, cds, bp);
-    if (want_items && !bf16) plan_f32(c, P, cds, true, pre, part_rows);
     if (P.backward && !bf16) {
         plan_f32(c, P, cds, false, pre, part_rows);
         plan_backward_keys_f32(c, P, bp.keys);
@@ -749,35 +766,39 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
-    auto lay_out = [&]() {
-        P.total_seg = seg_off;
-        P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-        P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
-        P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
+    auto layout = [&](size_t n_tok) {
         size_t n_merge = 0;
         for (int i = 0; i < n_calls && want_items; ++i) if (cds[(size_t)i].n_splits > 1) n_merge += (size_t)cds[(size_t)i].n_q;
         for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) n_merge += (size_t)gr.n_rows;
         n_merge += tail_rows.size();
-        P.lay = make_layout(n_calls, P.total_q, P.total_seg, P.n_dec, P.n_pre, P.n_pre_pk, part_rows, total_tiles, c->cfg.n_q_heads, c->D,
-                            sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, P.tok_items.size(),
-                            bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
+        return make_layout(n_calls, P.total_q, seg_off, (int)dec.size(), (int)pre.size(), (int)pre_pk.size(), part_rows, total_tiles, c->cfg.n_q_heads, c->D,
+                           sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, n_tok,
+                           bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
     };
-    lay_out();
-    // A fixed workspace holds what it held under the bounded rule, which decides whether a batch fits; one that fits takes
-    // the splits of pc_attend (and returns the same bits) as long as their partial results fit as well.
-    if (P.fixed_ws && want_items && !c->host_only) {
-        auto fits = [&]() { return P.lay.total <= P.fixed_cap && P.lay.h2d_bytes <= c->stage[c->stage_next].cap; };
-        auto plan_items = [&](bool small_splits) {
-            plan_calls(small_splits);
-            if (!bf16) plan_f32(c, P, cds, small_splits, pre, part_rows);
-            lay_out();
-        };
-        plan_items(false);
-        if (fits()) {
-            plan_items(true);
-            if (!fits()) plan_items(false);
+    // pc_attend_static takes a batch that fits its workspace under the plain rule, which bounds the partial results, and
+    // returns pc_attend's bits: where the partial results of the splits above would not fit as well, both keep those of the
+    // prefill calls to what is left of that workspace, or take the plain rule.  (The same sizes decide in both: a decode
+    // step's tokens and a ring slot that has grown are left out.  A call that gathers has other bits in any case.)
+    if (want_items && !c->host_only && (P.fixed_ws || kg.empty())) {
+        auto fits = [](const PlanLayout &l) { return l.total <= PC_STATIC_WS_BYTES && l.h2d_bytes <= STAGE_BYTES; };
+        const PlanLayout small = layout(0);
+        const int64_t other = (int64_t)small.total - pre_part_rows * c->cfg.n_q_heads * (c->D * 2 + 8);
+        if (P.fixed_ws || !fits(small)) {
+            plan_items(false, INT64_MAX);
+            const PlanLayout plain = layout(0);
+            const bool refused = P.fixed_ws && (plain.total > P.fixed_cap || plain.h2d_bytes > c->stage[c->stage_next].cap);
+            if (!refused) {
+                const bool free = fits(small) || plain.total > PC_STATIC_WS_BYTES;
+                plan_items(true, free ? INT64_MAX : (int64_t)PC_STATIC_WS_BYTES - other);
+                if (!free && !fits(layout(0))) plan_items(false, INT64_MAX);
+            }
         }
     }
+    P.lay = layout(P.tok_items.size());
+    P.total_seg = seg_off;
+    P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
+    P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
+    P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (c->host_only) return PC_OK;
