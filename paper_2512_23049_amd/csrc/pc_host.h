@@ -54,6 +54,7 @@ struct pc_cache {
     PcMsgEntry *table_dev = nullptr;
     double *inv_freq_dev = nullptr;
     void *ws = nullptr; size_t ws_cap = 0;
+    size_t ws_refused = SIZE_MAX;                        // a gradient's workspace the device had no room for
     void *tok_dev = nullptr; size_t tok_cap = 0;          // staged items of pc_append_tokens* / pc_reposition_batch (bytes)
     StageSlot stage[N_STAGE]; int stage_next = 0;
     // profiling

@@ -38,10 +38,18 @@ int32_t pc_ensure_ws(pc_cache *c, size_t bytes, hipStream_t st)
         PC_HIP(c, hipDeviceSynchronize());
         PC_HIP(c, hipFree(c->ws));
     }
+    const size_t before = c->ws_cap;
     c->ws = nullptr; c->ws_cap = 0;
-    const size_t cap = align_up(bytes + bytes / 4, 1 << 20);
-    PC_HIP(c, hipMalloc(&c->ws, cap));
-    c->ws_cap = cap;
+    hipError_t e = hipSuccess;
+    for (size_t cap : {align_up(bytes + bytes / 4, 1 << 20), bytes, before}) {      // (the last: as it was, for calls that need no more)
+        if (cap == 0) break;
+        const hipError_t got = hipMalloc(&c->ws, cap);
+        if (got == hipSuccess) { c->ws_cap = cap; break; }
+        c->ws = nullptr;
+        (void)hipGetLastError();                         // (it would be taken for that of the next launch)
+        e = got;
+    }
+    if (c->ws_cap < bytes) return pc_fail(c, PC_ERR_HIP, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     return PC_OK;
 }
 

@@ -2,6 +2,8 @@
 // work items (prefill, per-call decode, shared decode), staging, and the launch of the plan builder.
 #include "pc_host.h"
 
+#include <numeric>
+
 int32_t pc_resolve(pc_cache *c, const pc_call *call, int idx, Resolved &out)
 {
     if (!call) return pc_fail(c, PC_ERR_INVALID_ARG, "call %d: null", idx);
@@ -416,23 +418,30 @@ static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, con
 // each of which fills a compute unit, and as many splits of the tiles as fill whole rounds of them; the key-major kernel
 // takes 4 key tiles a workgroup and splits their units where that evens the load out: a workgroup costs KEY_FIXED us (keys
 // turned and cut into pieces at the start, an atomic per gradient element at the end) and KEY_UNIT a unit.  (Four calls of
-// 150 to 320 rows over 2000 tokens, 32/8 heads: 426 us for 16 units a workgroup, 365 for 32.)  Per-unit buffers take 64 KB
-// a unit (16 more per further split): a batch with more units than BWD_UNITS is cut into runs of row blocks with launches of their own, at multiples of 8 blocks of a call, so that
-// no workgroup's 8 units lie in two of them.
-constexpr int64_t BWD_UNITS = 16384;
+// 150 to 320 rows over 2000 tokens, 32/8 heads: 426 us for 16 units a workgroup, 365 for 32.)
+// Per-unit buffers take 64 KB a unit (16 more per further split, of which there are several only in batches of few units).  A
+// batch with more units than BWD_UNITS (256 MB) is cut into even runs of row blocks with launches of their own, inside a call
+// only where whole workgroups of 8 units end.  2048 rows x 64 heads over 4000 tokens, 4096 x 128 over themselves, six calls of
+// 700 x 64 over 2000: 4.50, 7.66, 4.79 ms in runs of 4096 units, 4.50, 7.74, 4.63 of 8192, 4.71, 8.60, 5.06 of 2048.
+constexpr int64_t BWD_UNITS = 4096;
 constexpr double KEY_FIXED = 30.0, KEY_UNIT = 2.5, ROWS_FIXED = 15.0, ROWS_TILE = 3.0;
 struct BwdPlan { std::vector<PcItem> items; std::vector<PcBwdKeyItem> keys; std::vector<int2> row_blocks; size_t units = 0, splits = 1; };
 
-static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc> &cds, BwdPlan &bp)
+static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc> &cds, BwdPlan &bp, int64_t max_units)
 {
     const int g = c->g, H_q = c->cfg.n_q_heads, H_kv = c->cfg.n_kv_heads;
-    const int rb_max = (int)std::max<int64_t>(8, BWD_UNITS / H_q / 8 * 8);
-    int64_t groups = 0;
+    const int step = 8 / std::gcd(8, g);                 // row blocks of whole workgroups
+    bp = BwdPlan{};
+    P.chunks.clear();
+    int64_t groups = 0, blocks = 0;
     int most_units = 1;
     for (const Resolved &r : P.res) {
+        blocks += (r.n_q + 31) / 32;
         groups += (int64_t)(((r.n_q + 31) / 32) * g + 7) / 8 * H_kv;
         most_units = std::max(most_units, (r.n_q + 31) / 32 * g);
     }
+    const int64_t most_blocks = std::max<int64_t>(step, max_units / H_q / step * step), runs = (blocks + most_blocks - 1) / most_blocks;
+    const int rb_max = (int)std::max<int64_t>(step, (int64_t)align_up((size_t)((blocks + runs - 1) / runs), (size_t)step));
     int key_units = most_units;                          // units a key-major workgroup takes
     double best_us = 0;
     for (int k = 1; k <= 16 && (k == 1 || most_units / k >= 8); ++k) {
@@ -442,13 +451,15 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
             const int n = (r.n_q + 31) / 32 * g;
             total += (double)((r.tiles + 3) / 4) * H_kv * (KEY_FIXED * ((n + u - 1) / u) + KEY_UNIT * n);
         }
-        const double us = total / 256 + 0.5 * (KEY_FIXED + KEY_UNIT * u);       // workgroups of unlike lengths: no whole rounds
+        const double us = total / 256 + 0.5 * runs * (KEY_FIXED + KEY_UNIT * u);      // workgroups of unlike lengths: no whole rounds
         if (k == 1 || us < best_us) { best_us = us; key_units = u; }
     }
     // splits of the row-major walk: the fewest rounds of 256 workgroups, each a start (ROWS_FIXED) and its tiles long
     int row_splits = 1, most_tiles = 0;
     for (const Resolved &r : P.res) most_tiles = std::max(most_tiles, r.tiles);
+    groups = (groups + runs - 1) / runs;                 // (of a run)
     for (int k = 1; k <= std::min(MAX_SPLITS, most_tiles / 8); ++k) {
+        if (k > 1 && std::min<int64_t>(rb_max, blocks) * H_q * (3 + k) > 4 * max_units) break;      // (64 KB a unit for k = 1, 16 a split)
         const double us = (double)((groups * k + 255) / 256) * (ROWS_FIXED + ROWS_TILE * ((most_tiles + k - 1) / k));
         if (k == 1 || us < best_us) { best_us = us; row_splits = k; }
         if (groups * k > 1024) break;
@@ -472,9 +483,9 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
         bp.splits = std::max(bp.splits, (size_t)ns);
         for (int b = 0; b < n_rb; ++b) bp.row_blocks.push_back(make_int2((int)i, b));
         for (int b0 = 0; b0 < n_rb;) {
-            if (ch.n_rb > 0 && ch.n_rb + std::min(n_rb - b0, 8) > rb_max) close();
+            if (ch.n_rb > 0 && ch.n_rb + std::min(n_rb - b0, step) > rb_max) close();
             int nb = n_rb - b0;
-            if (nb > rb_max - ch.n_rb) nb = (rb_max - ch.n_rb) / 8 * 8;                   // (at least 8: see close above; rb_max is a multiple of 8)
+            if (nb > rb_max - ch.n_rb) nb = (rb_max - ch.n_rb) / step * step;             // (at least a step: see close above; rb_max is a multiple of it)
             if (nb == 0) { close(); continue; }
             const int b1 = b0 + nb;
             // rows by tiles: a split's share is cut at the causal limit of the workgroup's last row
@@ -758,13 +769,13 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     };
     BwdPlan bp;
     plan_items(true, INT64_MAX);
-    if (P.backward && bf16) plan_backward(c, P, cds, bp);
+    if (P.backward && bf16) plan_backward(c, P, cds, bp, BWD_UNITS);
     if (P.backward && !bf16) {
         plan_f32(c, P, cds, false, pre, part_rows);
         plan_backward_keys_f32(c, P, bp.keys);
         P.n_bwd_keys = (int)bp.keys.size();
     }
-    if (!bp.items.empty()) pre.swap(bp.items);           // (the gradient's row-major items are staged where the prefill items go)
+    if (P.backward && bf16) pre = std::move(bp.items);   // (the gradient's row-major items are staged where the prefill items go)
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
     auto layout = [&](size_t n_tok) {
         size_t n_merge = 0;
@@ -795,6 +806,16 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         }
     }
     P.lay = layout(P.tok_items.size());
+    if (P.backward && bf16 && !c->host_only && P.lay.total > c->ws_cap &&
+        (P.lay.total >= c->ws_refused || pc_ensure_ws(c, P.lay.total, st) != PC_OK)) {
+        // the device has no room for that (and is not asked again): shorter runs, in the workspace there is
+        c->ws_refused = std::min(c->ws_refused, P.lay.total);
+        for (int64_t units = BWD_UNITS / 2; units >= 8 && P.lay.total > c->ws_cap; units /= 2) {
+            plan_backward(c, P, cds, bp, units);
+            pre = std::move(bp.items);
+            P.lay = layout(0);
+        }
+    }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
     P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
