@@ -242,12 +242,6 @@ int32_t pc_attend_backward(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         }
         return PC_OK;
     }
-    int max_seg_len = 0;
-    for (const Resolved &r : P.res) {
-        for (const int2 &e : r.sel) max_seg_len = std::max(max_seg_len, c->msgs[(size_t)e.x].len);
-        max_seg_len = std::max(max_seg_len, r.self_len);
-    }
-    if ((max_seg_len + 15) / 16 > 65535) return pc_fail(c, PC_ERR_SHAPE, "attend_backward: a message of %d tokens is too long", max_seg_len);
     L.items = (const PcItem *)(w + P.lay.items_pre);
     pc_launch_attend_bwd_f32(L, P.n_pre, (const PcBwdKeyItem *)(w + P.lay.bwd_keys), P.n_bwd_keys, c->D, lse, (const float *)d_out, c->scale,
                              (float *)(w + P.lay.row_scalar), d_q, d_k, d_v, st);

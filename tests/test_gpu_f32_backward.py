@@ -93,3 +93,8 @@ def test_rows_that_saw_nothing(dtype, D):
     assert (res[1][0][dead] == 0).all()
     for a, b in zip(*res):
         assert torch.isfinite(b).all() and float((a - b).norm()) <= 1e-6 * float(a.norm())
+
+
+def test_message_of_more_than_a_million_tokens():
+    # dq: a wave adds the terms of an eighth of the keys in one chain, 131 thousand fp32 roundings: sqrt(131e3) * 2^-24 = 2.2e-5
+    run_case([1048600, 3], [([(0, -500000)], 1, 600000, 3)], 1, 1, dtype="f32", D=64, bar=2.2e-5)
