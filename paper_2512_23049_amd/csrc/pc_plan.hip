@@ -840,6 +840,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     StageSlot *slot = nullptr;
     PcArgBlob blob;
+    // (Batches with shared groups stay with the ring, where they were measured: they need six calls at least over the same
+    // messages, and their lists, 50 bytes a message and 4 more a row of it, seldom fit.)
     const bool in_args = P.lay.h2d_bytes <= PC_ARG_BYTES && P.n_sh_items == 0;
     if (!in_args) {
         rc = pc_stage_acquire(c, P.lay.h2d_bytes, &slot);

@@ -130,3 +130,32 @@ def test_shared_walk_hand_made_cases(hip):
 
 
 # (configs[2] and configs[4] at full size through this walk: tests/test_gpu_full_configs.py)
+
+
+@pytest.mark.parametrize("per_row", [8, 9])
+def test_union_as_long_as_its_table_and_longer(hip, per_row):
+    """256 rows, the most of a group, that list 2048 messages between them, as many as the rotation table of the union has room for,
+    and 2304: then every call streams on its own, with the very bits of the per-call walk."""
+    import torch
+    from paper_2512_23049_amd.binding import PC_BF16, Cache
+    rows, L, D = 256, 8, 128
+    n = rows * per_row
+    rng = torch.Generator(device="cuda:0")
+    rng.manual_seed(per_row)
+    k, v = (torch.randn((n * L, 1, D), generator=rng, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((rows, 1, D), generator=rng, device="cuda:0").to(torch.bfloat16)
+    cache = Cache(1, 1, D, PC_BF16, 10000.0, 32 * n, n)
+    cache.append_messages([k.data_ptr() + 2 * D * L * i for i in range(n)], [v.data_ptr() + 2 * D * L * i for i in range(n)], [L] * n)
+    calls = [Call([(rows * j + r, 9 * j) for j in range(per_row)], -1, 80, 1, None) for r in range(rows)]
+    res = []
+    for mode in (ALWAYS, NEVER):
+        cache.set_decode_sharing(mode)
+        out, lse = torch.full_like(q, 7.0), torch.full((rows, 1), 7.0, device="cuda:0")
+        cache.attend(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        torch.cuda.synchronize()
+        res.append((out.float(), lse))
+    cache.close()
+    d = (res[0][0] - res[1][0]).abs()
+    assert float(d.max()) <= 2e-2 and float(d.mean()) <= 1e-3
+    if per_row == 9:
+        assert not d.any() and torch.equal(res[0][1], res[1][1])
