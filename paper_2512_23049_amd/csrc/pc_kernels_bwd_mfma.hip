@@ -21,11 +21,11 @@
 //   finish    sum of the dq partials, turned back by the rows' positions
 //   keys      per (4 key tiles, KV head, split of the row units): dK and dV         (128)
 // A unit is 32 rows of one head, a tile 32 keys.  The walks are bound by the matrix pipe (216 MFMAs of 32 cycles per
-// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, means over a kernel trace: prep 13,
-// rows<0> 104, rows<1> 214, finish 9, keys 380 us (the least of 16 launches: 12, 98, 205, 9, 367); plain vector kernels (a
-// thread per key, an FMA per product, strided 2-byte reads of V) took 31.4 ms.  What the walks gained on the way, least
-// times: 116, 249 and 442 us while the splits spilled into a second round of workgroups, every piece of a flushed dq
-// partial waited for the one before it and the key kernel's accumulators were copied between the halves of the register file.
+// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, means over kernel traces on three
+// boxes: prep 12 to 13, rows<0> 103 to 104, rows<1> 209 to 214, finish 9, keys 373 to 386 us; plain vector kernels (a thread
+// per key, an FMA per product, strided 2-byte reads of V) took 31.4 ms.  (Least times 98, 205 and 367 us on a box where they
+// were 116, 249 and 442 while the splits spilled into a second round of workgroups, every piece of a flushed dq partial
+// waited for the one before it and the key kernel's accumulators were copied between the halves of the register file.)
 //
 // All operands that a product needs with its indices the other way round (V by dimension, keys, queries and output
 // gradients by token) come from the same LDS tile through ds_read_b64_tr_b16: within 16 lanes, lane l points at row
