@@ -794,7 +794,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         auto fits = [](const PlanLayout &l) { return l.total <= PC_STATIC_WS_BYTES && l.h2d_bytes <= STAGE_BYTES; };
         const PlanLayout small = layout(0);
         const int64_t other = (int64_t)small.total - pre_part_rows * c->cfg.n_q_heads * (c->D * 2 + 8);
-        if (P.fixed_ws || !fits(small)) {
+        const size_t tables = (small.part_o - small.segs) + (small.total - small.row_scalar);     // the same under every rule
+        if (P.fixed_ws || (!fits(small) && tables <= PC_STATIC_WS_BYTES)) {
             plan_items(false, INT64_MAX);
             const PlanLayout plain = layout(0);
             const bool refused = P.fixed_ws && (plain.total > P.fixed_cap || plain.h2d_bytes > c->stage[c->stage_next].cap);
