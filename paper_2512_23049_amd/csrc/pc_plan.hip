@@ -625,6 +625,25 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     std::pair<int, int> tail{0, 1};                      // last prefill items that are split, and into how many parts
     int64_t pre_part_rows = 0;                           // partial rows of prefill items among part_rows
     std::vector<PcMergeRow> tail_rows;
+    // splits of a call over the tiles it walks, none of them empty.  small: the rules as they stand; else the plain rule
+    auto whole_splits = [](int tiles, int ns) {
+        ns = std::max(1, std::min(MAX_SPLITS, ns));
+        const int chunk = std::max(1, (tiles + ns - 1) / ns);
+        return std::max(1, (tiles + chunk - 1) / chunk);
+    };
+    // Decode: as few splits as fill the chip (256 workgroups): the kernel is bound by memory, and every split beyond
+    // that only adds partial results to write and merge.  A split has 4 tiles at least, one a wave: a small
+    // call is a chain of latencies, which shorter runs of tiles shorten by more than the merge launch costs from
+    // 16 tiles on (4 calls over 1300 tokens, 8 KV heads: 18 + 5 us at 16 tiles a split, 10 + 5 at 4).
+    auto decode_splits = [&](int T, bool small) {
+        const int least = small ? (T >= 16 ? 4 : T + 1) : 16;
+        return whole_splits(T, c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
+                                                             : (int)std::min<int64_t>((256 + dec_groups - 1) / dec_groups, std::max(1, T / least)));
+    };
+    auto prefill_splits = [&](int Tc, bool small) {
+        return whole_splits(Tc, c->prefill_tiles_per_split > 0 ? (Tc + c->prefill_tiles_per_split - 1) / c->prefill_tiles_per_split
+                                : small ? (int)(((int64_t)Tc + pre_chunk - 1) / pre_chunk) : plain_splits(pre_groups, Tc));
+    };
     // small_splits: the rules for the number of splits as they stand.  Without it: the plain rule (see below).
     auto plan_calls = [&](bool small_splits) {
         dec.clear(); pre.clear(); pre_pk.clear(); kg.clear(); sp.items.clear(); tail_rows.clear();
@@ -652,16 +671,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 // position), so a decode call walks its parents in ascending cache-slot order: calls that
                 // share messages then touch them at about the same time and the later ones hit in L2.
                 sort_by_slot(c, r);
-                // as few splits as fill the chip (256 workgroups): the kernel is bound by memory, and every split beyond
-                // that only adds partial results to write and merge.  A split has 4 tiles at least, one a wave: a small
-                // call is a chain of latencies, which shorter runs of tiles shorten by more than the merge launch costs from
-                // 16 tiles on (4 calls over 1300 tokens, 8 KV heads: 18 + 5 us at 16 tiles a split, 10 + 5 at 4).
-                const int least = small_splits ? (T >= 16 ? 4 : T + 1) : 16;
-                int ns = c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
-                                                       : (int)std::min<int64_t>((256 + dec_groups - 1) / dec_groups, std::max(1, T / least));
-                ns = std::max(1, std::min(MAX_SPLITS, ns));
-                const int chunk = std::max(1, (T + ns - 1) / ns);
-                ns = std::max(1, (T + chunk - 1) / chunk);
+                const int ns = decode_splits(T, small_splits), chunk = std::max(1, (T + ns - 1) / ns);
                 cd.n_splits = ns;
                 wide = ns > 1 && small_splits && c->decode_tiles_per_split == 0 && plain_splits(dec_groups, T) == 1;
                 for (int s = 0; s < ns; ++s) {
@@ -682,13 +692,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 const int Tc = packed ? p_tiles + own_tiles : T;        // tiles the attention kernel walks for this call
                 const int units = ((r.n_q + 31) / 32) * g;
                 const int groups = pre_groups_of(r);
-                int ns = 1;
-                if (c->prefill_tiles_per_split > 0) ns = (Tc + c->prefill_tiles_per_split - 1) / c->prefill_tiles_per_split;
-                else if (small_splits) ns = (int)(((int64_t)Tc + pre_chunk - 1) / pre_chunk);
-                else ns = plain_splits(pre_groups, Tc);
-                ns = std::max(1, std::min(MAX_SPLITS, ns));
-                const int chunk = std::max(1, (Tc + ns - 1) / ns);
-                ns = std::max(1, (Tc + chunk - 1) / chunk);
+                const int ns = prefill_splits(Tc, small_splits);
                 cd.n_splits = ns;
                 // A group of row units walks the parents' tiles and the tiles of the new message up to the
                 // causal limit of its last row (the kernel relies on tile_end being cut there); its splits
@@ -777,14 +781,16 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     if (P.backward && bf16) pre = std::move(bp.items);   // (the gradient's row-major items are staged where the prefill items go)
     if (sp.pos.size() > (size_t)INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: shared decode table too large");
+    auto layout_of = [&](size_t n_dec, size_t n_pre, int64_t n_part, size_t n_merge, size_t n_tok) {
+        return make_layout(n_calls, P.total_q, seg_off, (int)n_dec, (int)n_pre, (int)pre_pk.size(), n_part, total_tiles, c->cfg.n_q_heads, c->D,
+                           sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, n_tok,
+                           bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
+    };
     auto layout = [&](size_t n_tok) {
         size_t n_merge = 0;
         for (int i = 0; i < n_calls && want_items; ++i) if (cds[(size_t)i].n_splits > 1) n_merge += (size_t)cds[(size_t)i].n_q;
         for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) n_merge += (size_t)gr.n_rows;
-        n_merge += tail_rows.size();
-        return make_layout(n_calls, P.total_q, seg_off, (int)dec.size(), (int)pre.size(), (int)pre_pk.size(), part_rows, total_tiles, c->cfg.n_q_heads, c->D,
-                           sp.groups.size(), sp.segs.size(), sp.items.size(), sp.pos.size(), kg.size(), kg_tiles, H_kv, n_tok,
-                           bp.row_blocks.size(), bp.keys.size(), bp.units, bp.splits, bf16 ? sizeof(uint16_t) : sizeof(float), n_merge);
+        return layout_of(dec.size(), pre.size(), part_rows, n_merge + tail_rows.size(), n_tok);
     };
     // pc_attend_static takes a batch that fits its workspace under the plain rule, which bounds the partial results, and
     // returns pc_attend's bits: where the partial results of the splits above would not fit as well, both keep those of the
@@ -796,13 +802,26 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         const int64_t other = (int64_t)small.total - pre_part_rows * c->cfg.n_q_heads * (c->D * 2 + 8);
         const size_t tables = (small.part_o - small.segs) + (small.total - small.row_scalar);     // the same under every rule
         if (P.fixed_ws || (!fits(small) && tables <= PC_STATIC_WS_BYTES)) {
-            plan_items(false, INT64_MAX);
-            const PlanLayout plain = layout(0);
+            // the layout under the plain rule, counted: planning a batch twice more for it took a quarter of the host time of a
+            // static call (200 one-row calls over 20 messages: 57 us, 42 counted)
+            size_t n_dec = 0, n_pre = 0, n_merge = 0;
+            int64_t rows = 0;
+            for (int i = 0; i < n_calls; ++i) {
+                const Resolved &r = P.res[(size_t)i];
+                if (sp.in_shared[(size_t)i]) continue;
+                int ns = 1;
+                if (!bf16) n_pre += (size_t)(((int64_t)r.n_q * g + 31) / 32);
+                else if (r.n_q * g <= 16) n_dec += (size_t)(ns = decode_splits(r.tiles, false));
+                else n_pre += (size_t)(ns = prefill_splits(r.tiles, false)) * (size_t)pre_groups_of(r);
+                if (ns > 1) { rows += (int64_t)ns * r.n_q; n_merge += (size_t)r.n_q; }
+            }
+            for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) { rows += (int64_t)gr.n_splits * gr.n_rows; n_merge += (size_t)gr.n_rows; }
+            const PlanLayout plain = layout_of(n_dec, n_pre, rows, n_merge, 0);
             const bool refused = P.fixed_ws && (plain.total > P.fixed_cap || plain.h2d_bytes > c->stage[c->stage_next].cap);
-            if (!refused) {
-                const bool free = fits(small) || plain.total > PC_STATIC_WS_BYTES;
-                plan_items(true, free ? INT64_MAX : (int64_t)PC_STATIC_WS_BYTES - other);
-                if (!free && !fits(layout(0))) plan_items(false, INT64_MAX);
+            if (refused) plan_items(false, INT64_MAX);
+            else if (!fits(small) && plain.total <= PC_STATIC_WS_BYTES) {
+                plan_items(true, (int64_t)PC_STATIC_WS_BYTES - other);
+                if (!fits(layout(0))) plan_items(false, INT64_MAX);
             }
         }
     }
