@@ -50,6 +50,13 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     L.scale_log2 = c->scale * 1.4426950408889634f;
     L.k_gather = w + P.lay.k_gather; L.v_gather = w + P.lay.v_gather; L.kg_slots = P.kg_tiles * PC_TILE;
     L.kg_norm = (float *)(w + P.lay.kg_norm);
+    if (P.one_bytes > 0) {
+        ProfScope ps(c, 3, st);
+        pc_launch_decode_one_bf16(P.one_blob, P.one_bytes, L, P.one, st);
+        PC_HIP(c, hipGetLastError());
+        P.tok_done = !P.tok_items.empty();
+        return PC_OK;
+    }
     if (c->cfg.dtype == PC_F32) {
         {
             ProfScope ps(c, 5, st);

@@ -52,6 +52,7 @@ struct pc_cache {
     void *storage = nullptr; bool owns_storage = false;
     void *k_store = nullptr, *v_store = nullptr;
     PcMsgEntry *table_dev = nullptr;
+    uint32_t *counters_dev = nullptr;                    // PcOne::counters
     double *inv_freq_dev = nullptr;
     void *ws = nullptr; size_t ws_cap = 0;
     size_t ws_refused = SIZE_MAX;                        // a gradient's workspace the device had no room for
@@ -161,6 +162,8 @@ struct Planned {
     std::vector<Resolved> res;
     // The gradient of a bf16 batch (set backward before planning): its launches, each over a run of row blocks
     bool backward = false;
+    // A decode batch that goes to one launch (one_bytes > 0): nothing was staged or launched for it yet
+    PcArgBlob one_blob; size_t one_bytes = 0; PcOne one;
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
     int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)

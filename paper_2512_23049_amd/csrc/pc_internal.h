@@ -127,6 +127,25 @@ struct PcBwdKeyItem {
     int32_t pad[3];
 };
 
+// ---- a decode batch in one launch: its lists travel in the kernel's arguments, calls first ----
+struct PcOneCall {
+    uint16_t seg_off, n_seg;  // its entries of the (msg, start) list; the new message is the last one if self_len > 0
+    uint16_t n_q, n_splits;
+    int32_t q_off;            // first packed query row
+    int32_t self_len;         // tokens of the new message (0: none)
+    int32_t n_tiles, chunk;   // KV tiles, and how many a split takes
+    int32_t part_off;         // first partial row (fp32; split s is n_q rows further) when n_splits > 1
+    int32_t tok;              // row of the step's tokens that is the new message's last token, -1: none
+};
+struct PcOneItem {
+    uint16_t call_split;      // call | split << 8
+    uint16_t seg0;            // the call's entry that owns the split's first tile
+    uint32_t tile0 : 24;      // the call's tiles before that entry
+    uint32_t n_seg : 8;       // entries the split's tiles come from
+};
+#define PC_ONE_SEGS 64        // most of them (a wave holds them, one a lane)
+#define PC_ONE_COUNTERS 4096  // (call, KV head) pairs a launch can merge itself
+
 #define PC_MERGE_WIDE 0x10000     // partial outputs in fp32 (bf16 caches)
 // One output row whose KV splits the merge kernel combines (staged by the host).
 struct PcMergeRow {
@@ -199,6 +218,16 @@ struct PcLaunch {
     int64_t           slots;      // capacity in slots (stride between KV heads)
     int32_t           n_q_heads, n_kv_heads;
     float             scale_log2; // softmax scale * log2(e)
+};
+
+// A decode batch in one launch: what the kernel needs besides its lists and PcLaunch.
+struct PcOne {
+    PcMsgEntry   *table;
+    const double *inv_freq;
+    const uint16_t *tok_k, *tok_v;    // [tokens][H_kv][D] rows the step appends
+    uint32_t     *counters;           // [call][H_kv] splits that are done: zero between launches
+    int32_t       off_sel, off_q_pos, off_items;      // of the lists in the arguments, in bytes
+    int32_t       n_items;
 };
 
 // Gradient of a bf16 batch: what its kernels need besides PcLaunch (whose items are the row-major kernels').  A unit is

@@ -38,10 +38,11 @@ __device__ __forceinline__ float max_lanes_xor32(float x)
 struct DecTile {
     uint4 k[2][4];      // [16-key half][d step of 32]
     uint4 v[8];         // [16-d block]
-    int seg;            // segment index within the call
+    int seg;            // which rotation row turns the query for it
     int key0;           // first in-message token of the tile
     int valid;          // tokens of the tile that exist (1..32)
     bool fresh;         // first tile of a segment whose query rotation differs from the one before
+    bool self;          // a tile of the new message
 };
 
 __device__ __forceinline__ void dec_load(DecTile &T, const uint16_t *__restrict__ kb, const uint16_t *__restrict__ vb,
@@ -61,14 +62,18 @@ __device__ __forceinline__ void dec_load(DecTile &T, const uint16_t *__restrict_
     for (int db = 0; db < 8; ++db) T.v[db] = (8 * a < valid) ? ldg16(vg + 16 * db * PC_VGROUP) : z;
 }
 
-__global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
-{
-    __shared__ float s_acc[4][PC_D][17];
-    __shared__ float s_m[4][16], s_l[4][16];
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-    const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
-    const PcItem item = L.items[blockIdx.x / L.n_kv_heads];
-    const PcCallDesc cd = L.calls[item.call];
+// The walk of one workgroup: this wave's run of tiles of the columns (row, head) of KV head kh, then its NW waves' results
+// combined and written: the finished rows if the call is not split, else the split's part.
+// describe(t): {slot0, key0, rotation row, valid | flags} of the call's tile t.  Rotation rows (cos, sin): seg_rot(row of the
+// tile), q_rot(query row of the call, f), which calls f once to request the wave's first tile.
+// ONE: the launch merges its splits itself; a part is fp32 then and is stored at agent scope, for the workgroup that merges.
+struct DecCall { int n_q, q_off, self_lim0, n_splits, split, part_off, part_wide; };      // self_lim0: own tokens before the query rows
+template <bool ONE, int NW, class Describe, class SegRot, class QRot>
+__device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd, int kh, int tile, int tile_stop, Describe describe, SegRot seg_rot, QRot q_rot,
+                                            float (&s_acc)[NW][PC_D][17], float (&s_m)[NW][16], float (&s_l)[NW][16])
+{
     const int g = L.n_q_heads / L.n_kv_heads;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, a = lane >> 4;
@@ -77,34 +82,29 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
     const bool col_ok = n < n_cols;
     const int R = cd.q_off + (col_ok ? qr : 0);
     const int h = kh * g + (col_ok ? qj : 0);
-    const int self_seg = cd.self_msg >= 0 ? cd.n_seg - 1 : -1;
-    const int self_lim = cd.self_len - cd.n_q + qr;      // last own token this column sees
-
-    // this wave's contiguous run of tiles
-    const int n_tiles = item.tile_end - item.tile_begin;
-    const int per_wave = (n_tiles + 3) >> 2;
-    int tile = item.tile_begin + wave * per_wave;
-    const int tile_stop = min(item.tile_end, tile + per_wave);
-    // Where a tile lives comes from the call's tile table (written by the plan builder), read with a
-    // scalar load one tile ahead of the loads it steers; the first one is requested here, in front of
-    // the query, so that the wave's first K/V loads do not wait behind a search through the segments.
-    typedef int i32x4 __attribute__((ext_vector_type(4)));
-    const PcTile *tile_tab = L.tiles + item.tile_tab0;   // (from the work item: requested beside the call descriptor, not behind it)
-    auto describe = [&](int t) {
-        const int tc = __builtin_amdgcn_readfirstlane(max(0, min(t, item.tile_end - 1)));
-        if (item.tile_end <= 0) return (i32x4){0, 0, 0, 0};                   // a call that sees nothing has no table
-        return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(tile_tab + tc));
-    };
+    const int self_lim = cd.self_lim0 + qr;              // last own token this column sees
     i32x4 next_desc = describe(tile);                    // {slot0, key0, seg, valid | flags}
 
+    const uint16_t *kb = (const uint16_t *)L.k_store + (int64_t)kh * L.slots * PC_D;
+    const uint16_t *vb = (const uint16_t *)L.v_store + (int64_t)kh * L.slots * PC_D;
+    auto fetch = [&](DecTile &T, int t) {                // t is the tile next_desc describes
+        const i32x4 d = next_desc;
+        next_desc = describe(t + 1);
+        T.seg = d.z; T.key0 = d.y; T.valid = d.w & 0xFF; T.fresh = (d.w & PC_TILE_FRESH) != 0; T.self = (d.w & PC_TILE_SELF) != 0;
+        dec_load(T, kb, vb, d.x, T.valid, lane);
+    };
     // query turned by its own position, kept in fp32: element (ks, j) is dim 32*ks + 8*a + j
     float qh[4][8];
+    DecTile A, B;
     {
         const uint16_t *qp = (const uint16_t *)L.q + ((int64_t)R * L.n_q_heads + h) * PC_D + 8 * a;
-        const float2 *rq = L.rot_q + (int64_t)R * (PC_D / 2) + 8 * a;
+        uint4 raw[2][2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) { raw[ks][0] = ldg16(qp + 32 * ks); raw[ks][1] = ldg16(qp + 32 * ks + 64); }
+        const float2 *rq = q_rot(col_ok ? qr : 0, [&]() { if (tile < tile_stop) fetch(A, tile); }) + 8 * a;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            uint4 lo = ldg16(qp + 32 * ks), hi = ldg16(qp + 32 * ks + 64);
+            const uint4 lo = raw[ks][0], hi = raw[ks][1];
             const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -118,27 +118,17 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
         }
     }
 
-    const uint16_t *kb = (const uint16_t *)L.k_store + (int64_t)kh * L.slots * PC_D;
-    const uint16_t *vb = (const uint16_t *)L.v_store + (int64_t)kh * L.slots * PC_D;
-
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 acc[8];
 #pragma unroll
     for (int db = 0; db < 8; ++db) acc[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-    auto fetch = [&](DecTile &T, int t) {                // t is the tile next_desc describes
-        const i32x4 d = next_desc;
-        next_desc = describe(t + 1);
-        T.seg = d.z; T.key0 = d.y; T.valid = d.w & 0xFF; T.fresh = (d.w & PC_TILE_FRESH) != 0;
-        dec_load(T, kb, vb, d.x, T.valid, lane);
-    };
 
     int cur_seg = -1;
     bf16x8 qop[4];
     auto compute = [&](const DecTile &T) {
         if (T.fresh || cur_seg < 0) {                    // turn the query by -(segment start - stored base): a new
             cur_seg = T.seg;                             // rotation starts here, or the wave starts inside a segment
-            const float2 *rs = L.rot_seg + (int64_t)(cd.seg_off + cur_seg) * (PC_D / 2) + 8 * a;
+            const float2 *rs = seg_rot(cur_seg) + 8 * a;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 uint32_t lo[4], hi[4];
@@ -162,11 +152,11 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
                 s[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, T.k[tau][ks]), qop[ks], s[tau], 0, 0, 0);
         }
         // lane holds keys 8a + 0..7 of column n
-        const int lim = (T.seg == self_seg) ? min(T.valid, self_lim - T.key0 + 1) : T.valid;
+        const int lim = T.self ? min(T.valid, self_lim - T.key0 + 1) : T.valid;
         float sc[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) sc[j] = s[j >> 2][j & 3];
-        if (T.valid < PC_TILE || T.seg == self_seg) {      // ragged or causal tile (uniform over the wave): mask
+        if (T.valid < PC_TILE || T.self) {      // ragged or causal tile (uniform over the wave): mask
 #pragma unroll
             for (int j = 0; j < 8; ++j) sc[j] = (8 * a + j < lim) ? sc[j] : -INFINITY;
         }
@@ -196,8 +186,6 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
         }
     };
 
-    DecTile A, B;
-    if (tile < tile_stop) fetch(A, tile);
     while (tile < tile_stop) {
         if (tile + 1 < tile_stop) fetch(B, tile + 1);
         compute(A);
@@ -208,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
         ++tile;
     }
 
-    // combine lane groups, then the 4 waves
+    // combine lane groups, then the waves
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
     if (a == 0) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
@@ -217,31 +205,261 @@ __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
 #pragma unroll
         for (int r = 0; r < 4; ++r) s_acc[wave][16 * db + 4 * a + r][n] = acc[db][r];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < n_cols * PC_D; idx += 256) {
-        const int col = idx / PC_D, d = idx - col * PC_D;
-        float mm = fmaxf(fmaxf(s_m[0][col], s_m[1][col]), fmaxf(s_m[2][col], s_m[3][col]));
-        float o = 0.f, l = 0.f;
+    for (int idx = threadIdx.x; idx < n_cols * (PC_D / 2); idx += 64 * NW) {
+        const int col = idx / (PC_D / 2), d = 2 * (idx - col * (PC_D / 2));
+        float mm = s_m[0][col];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][col]);
+        float o0 = 0.f, o1 = 0.f, l = 0.f;
         if (mm > -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 const float sc = (s_m[w][col] > -INFINITY) ? exp2f(s_m[w][col] - mm) : 0.f;
-                o += s_acc[w][d][col] * sc;
+                o0 += s_acc[w][d][col] * sc;
+                o1 += s_acc[w][d + 1][col] * sc;
                 l += s_l[w][col] * sc;
             }
         }
+        const float x0 = l > 0.f ? o0 / l : 0.f, x1 = l > 0.f ? o1 / l : 0.f;
         const int r = col / g, hq = kh * g + (col - r * g);
         const int64_t Rr = cd.q_off + r;
         if (cd.n_splits == 1) {
-            ((uint16_t *)L.out)[(Rr * L.n_q_heads + hq) * PC_D + d] = to_bf16(l > 0.f ? o / l : 0.f);
+            *reinterpret_cast<uint32_t *>((uint16_t *)L.out + (Rr * L.n_q_heads + hq) * PC_D + d) = pack_bf16(x0, x1);
             if (L.lse && d == 0) L.lse[Rr * L.n_q_heads + hq] = (l > 0.f) ? (mm + log2f(l)) * 0.6931471805599453f : -INFINITY;
+        } else if constexpr (ONE) {
+            const int64_t pr = (int64_t)cd.part_off + (int64_t)cd.split * cd.n_q + r;
+            uint64_t *po = reinterpret_cast<uint64_t *>(L.part_o) + ((pr * L.n_q_heads + hq) * PC_D + d) / 2;
+            __hip_atomic_store(po, (uint64_t)__float_as_uint(x0) | (uint64_t)__float_as_uint(x1) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (d == 0)
+                __hip_atomic_store(reinterpret_cast<uint64_t *>(L.part_ml) + pr * L.n_q_heads + hq,
+                                   (uint64_t)__float_as_uint(mm) | (uint64_t)__float_as_uint(l) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-            const int64_t pr = (int64_t)cd.part_off + (((int64_t)item.split * cd.n_q + r) << cd.part_wide);
-            const float x = l > 0.f ? o / l : 0.f;
-            if (cd.part_wide) reinterpret_cast<float *>(L.part_o + pr * L.n_q_heads * PC_D)[hq * PC_D + d] = x;
-            else L.part_o[(pr * L.n_q_heads + hq) * PC_D + d] = to_f16(x);
-            if (d == 0) { L.part_ml[(pr * L.n_q_heads + hq) * 2] = mm; L.part_ml[(pr * L.n_q_heads + hq) * 2 + 1] = l; }
+            const int64_t pr = (int64_t)cd.part_off + (((int64_t)cd.split * cd.n_q + r) << cd.part_wide);
+            if (cd.part_wide) *reinterpret_cast<float2 *>(reinterpret_cast<float *>(L.part_o + pr * L.n_q_heads * PC_D) + hq * PC_D + d) = make_float2(x0, x1);
+            else *reinterpret_cast<uint32_t *>(L.part_o + (pr * L.n_q_heads + hq) * PC_D + d) = pack_f16(x0, x1);
+            if (d == 0) *reinterpret_cast<float2 *>(L.part_ml + (pr * L.n_q_heads + hq) * 2) = make_float2(mm, l);
         }
     }
+}
+
+__global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
+{
+    __shared__ float s_acc[4][PC_D][17];
+    __shared__ float s_m[4][16], s_l[4][16];
+
+    const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
+    const PcItem item = L.items[blockIdx.x / L.n_kv_heads];
+    const PcCallDesc cd = L.calls[item.call];
+    const int wave = threadIdx.x >> 6;
+    // this wave's contiguous run of tiles
+    const int per_wave = (item.tile_end - item.tile_begin + 3) >> 2;
+    const int tile = item.tile_begin + wave * per_wave;
+    const int tile_stop = min(item.tile_end, tile + per_wave);
+    // Where a tile lives comes from the call's tile table (written by the plan builder), read with a
+    // scalar load one tile ahead of the loads it steers; the first one is requested in front of
+    // the query, so that the wave's first K/V loads do not wait behind a search through the segments.
+    const PcTile *tile_tab = L.tiles + item.tile_tab0;   // (from the work item: requested beside the call descriptor, not behind it)
+    auto describe = [&](int t) {
+        const int tc = __builtin_amdgcn_readfirstlane(max(0, min(t, item.tile_end - 1)));
+        if (item.tile_end <= 0) return (i32x4){0, 0, 0, 0};                   // a call that sees nothing has no table
+        return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(tile_tab + tc));
+    };
+    const DecCall dc{cd.n_q, cd.q_off, cd.self_len - cd.n_q, cd.n_splits, item.split, cd.part_off, cd.part_wide};
+    decode_walk<false, 4>(L, dc, kh, tile, tile_stop, describe,
+                       [&](int seg) { return L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2); },
+                       [&](int r, auto first_tile) { first_tile(); return L.rot_q + (int64_t)(cd.q_off + r) * (PC_D / 2); }, s_acc, s_m, s_l);
+}
+
+// The splits of a (call, KV head) merged by one workgroup of ONE_WAVES waves, as pc_merge_kernel does it for a row: 16 * SL threads a
+// column, eight dimensions and one of SL parts of the splits each, in split order.  What counts is one round trip to memory: SL
+// is as large as the threads allow, and eight splits of a part are requested together.
+#define ONE_WAVES 4
+__device__ __forceinline__ void merge_cols(const PcLaunch &L, const DecCall &cd, int kh)
+{
+    const int g = L.n_q_heads / L.n_kv_heads, n_cols = cd.n_q * g;
+    const int SL = n_cols > 8 ? 1 : n_cols > 4 ? 2 : 4;  // (16 columns at most, 256 threads)
+    static_assert(ONE_WAVES * 64 == 256, "as SL has it");
+    const int sub = threadIdx.x & 15, sg = (threadIdx.x >> 4) & (SL - 1), col = (int)threadIdx.x / (16 * SL);
+    const int part = (cd.n_splits + SL - 1) / SL, s_begin = sg * part, s_end = col < n_cols ? min(s_begin + part, cd.n_splits) : 0;
+    const int r = col / g, h = kh * g + (col - r * g);
+    const int64_t at0 = ((int64_t)cd.part_off + r) * L.n_q_heads + h, step = (int64_t)cd.n_q * L.n_q_heads;
+    const float2 *ml_at = reinterpret_cast<const float2 *>(L.part_ml) + at0;
+    const float4 *o_at = reinterpret_cast<const float4 *>(L.part_o) + at0 * (PC_D / 4) + 2 * sub;
+    float m = -INFINITY, l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int s0 = s_begin; s0 < s_end; s0 += 8) {
+        float2 ml[8];
+        float4 v[8][2];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            ml[u] = make_float2(-INFINITY, 0.f);
+            v[u][0] = v[u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (s0 + u < s_end) {
+                ml[u] = ml_at[(s0 + u) * step];
+                v[u][0] = o_at[(s0 + u) * step * (PC_D / 4)];
+                v[u][1] = o_at[(s0 + u) * step * (PC_D / 4) + 1];
+            }
+        }
+        float m_new = m;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m_new = fmaxf(m_new, ml[u].x);
+        if (m_new == -INFINITY) continue;
+        const float keep = m > -INFINITY ? exp2f(m - m_new) : 0.f;
+        l *= keep;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] *= keep;
+        m = m_new;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float w = ml[u].x > -INFINITY ? ml[u].y * exp2f(ml[u].x - m) : 0.f;
+            l += w;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) { o[4 * k] += v[u][k].x * w; o[4 * k + 1] += v[u][k].y * w; o[4 * k + 2] += v[u][k].z * w; o[4 * k + 3] += v[u][k].w * w; }
+        }
+    }
+    for (int mask = 16; mask < 16 * SL; mask <<= 1) {
+        const float m_o = __shfl_xor(m, mask), l_o = __shfl_xor(l, mask);
+        const float m_c = fmaxf(m, m_o);
+        const float w_own = m > -INFINITY ? exp2f(m - m_c) : 0.f, w_oth = m_o > -INFINITY ? exp2f(m_o - m_c) : 0.f;
+        l = l * w_own + l_o * w_oth;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = o[j] * w_own + __shfl_xor(o[j], mask) * w_oth;
+        m = m_c;
+    }
+    if (sg != 0 || col >= n_cols) return;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const int64_t Rr = (int64_t)(cd.q_off + r) * L.n_q_heads + h;
+    *reinterpret_cast<uint4 *>((uint16_t *)L.out + Rr * PC_D + 8 * sub) =
+        make_uint4(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv), pack_bf16(o[4] * inv, o[5] * inv), pack_bf16(o[6] * inv, o[7] * inv));
+    if (L.lse && sub == 0) L.lse[Rr] = l > 0.f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
+}
+
+// A batch of few decode calls in ONE launch: no plan builder in front, no merge behind.  Such a batch is a chain of latencies:
+// as three launches, 4 calls over 700 tokens took 4.2 us of plan, 8 of attention and 3.6 of merge, most of each the start and
+// the end of a kernel; one launch takes 12.  The lists come in the kernel's arguments.  Every wave looks the split's messages
+// up in the device table itself, one a lane (the host says which entry owns the split's first tile), and finds a tile's place
+// by a ballot over them; the rotations of the split's messages and query rows are shared out over the waves and computed into
+// LDS while the first tiles are on their way (fp64, rounded to fp32, as in the plan builder).  A decode step's new token is
+// written by the wave that reads it.  The workgroup whose split of a (call, KV head) is done last merges them, in split order
+// whichever comes last.  (By time stamps: 1.2 us until a wave knows its tiles, 1 to 2 for rotations and queries, 0.28 a tile
+// and workgroup -- 57 GB/s is what a compute unit draws with these loads, with four waves or eight --, 1.5 to combine the
+// waves, 2 to publish a part and learn that it is the last, 2.5 to merge.)
+template <int BYTES> struct PcArgs { uint4 w[BYTES / 16]; };
+template <int BYTES>
+__global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(const PcArgs<BYTES> blob, PcLaunch L, PcOne O)
+{
+    __shared__ float s_acc[ONE_WAVES][PC_D][17];
+    __shared__ float s_m[ONE_WAVES][16], s_l[ONE_WAVES][16];
+    __shared__ float2 s_rot[PC_ONE_SEGS + 16][PC_D / 2]; // (cos, sin) of the split's messages, then of the query rows' positions
+    __shared__ int s_last;
+
+    typedef const __attribute__((address_space(4))) char *KernArg;
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    typedef int i32x8 __attribute__((ext_vector_type(8)));
+    typedef const __attribute__((address_space(4))) i32x2 *KernArg2;
+    const KernArg args = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+    const int kh = blockIdx.x % L.n_kv_heads;            // consecutive workgroups (one per XCD) take different KV heads
+    const PcOneItem item = __builtin_bit_cast(PcOneItem, ((KernArg2)(args + O.off_items))[blockIdx.x / L.n_kv_heads]);
+    const int call = item.call_split & 0xFF, split = item.call_split >> 8;
+    const PcOneCall cd = __builtin_bit_cast(PcOneCall, ((const __attribute__((address_space(4))) i32x8 *)args)[call]);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile_begin = split * cd.chunk, tile_end = min(cd.n_tiles, tile_begin + cd.chunk);
+    const int per_wave = (tile_end - tile_begin + ONE_WAVES - 1) / ONE_WAVES;
+    const int tile = tile_begin + wave * per_wave;
+    const int tile_stop = min(tile_end, tile + per_wave);
+    const double freq = O.inv_freq[lane];                // (a lane is a frequency pair wherever rotations are made)
+
+    // the split's messages, one a lane
+    const bool have = lane < item.n_seg;
+    int m = 0, m_slot = 0, m_len = 0, m_rot = 0, m_base = 0;
+    if (have) {
+        const i32x2 ms = ((KernArg2)(args + O.off_sel))[cd.seg_off + item.seg0 + lane];
+        m = ms.x;
+        const PcMsgEntry me = O.table[m];
+        m_slot = me.slot_start; m_base = me.base_pos; m_rot = ms.y - me.base_pos;
+        // (the new message's length comes from the host: its last token may be appended by this launch)
+        m_len = (cd.self_len > 0 && item.seg0 + lane == cd.n_seg - 1) ? cd.self_len : me.len;
+    }
+    const int tiles = (m_len + PC_TILE - 1) / PC_TILE;
+    int m_tile = tiles;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int x = __shfl_up(m_tile, off);
+        if (lane >= off) m_tile += x;
+    }
+    m_tile += item.tile0 - tiles;                        // the call's tiles before the lane's message
+    const int self_lane = cd.self_len > 0 ? cd.n_seg - 1 - item.seg0 : -1;
+    auto describe = [&](int t) {
+        const int e = 63 - (int)__builtin_clzll(__builtin_amdgcn_ballot_w64(have && m_tile <= t) | 1ull);
+        i32x4 d;
+        d.y = (t - __builtin_amdgcn_readlane(m_tile, e)) * PC_TILE;
+        d.x = __builtin_amdgcn_readlane(m_slot, e) + d.y;
+        d.z = e;
+        d.w = min(__builtin_amdgcn_readlane(m_len, e) - d.y, PC_TILE) | (d.y == 0 ? PC_TILE_FRESH : 0) | (e == self_lane ? PC_TILE_SELF : 0);
+        return d;
+    };
+    // the step's token goes to the call's last tile, which one wave alone reads
+    const bool token = cd.tok >= 0 && tile < tile_stop && tile_stop == cd.n_tiles;
+    uint16_t tok[4];                                     // lane = dims lane and lane + 64 of the KV head's row: K, then V
+    if (token) {
+        const int64_t row = ((int64_t)cd.tok * L.n_kv_heads + kh) * PC_D + lane;
+        tok[0] = O.tok_k[row]; tok[1] = O.tok_k[row + PC_D / 2]; tok[2] = O.tok_v[row]; tok[3] = O.tok_v[row + PC_D / 2];
+    }
+    auto prepare = [&](int r, auto first_tile) {
+        if (!token) first_tile();
+        typedef const __attribute__((address_space(4))) int32_t *KernArgInt;
+        const KernArgInt q_pos = (KernArgInt)(args + O.off_q_pos) + cd.q_off;
+        const int n_ent = item.n_seg + cd.n_q;
+        for (int e = token ? -1 : wave; e < n_ent; e = e < 0 ? wave : e + ONE_WAVES) {      // -1: the token
+            const int at = cd.self_len - 1;
+            const int pos = e < 0 ? __builtin_amdgcn_readlane(m_base, self_lane) + at : e < item.n_seg ? __builtin_amdgcn_readlane(m_rot, e) : q_pos[e - item.n_seg];
+            const double x = (double)pos * freq;
+            if (!(fabs(x) < 0x1.0p+30)) __builtin_unreachable();     // (the host keeps positions below that: no code for larger arguments)
+            double s, c;
+            sincos(x, &s, &c);
+            const float2 cs = make_float2((float)c, (float)s);
+            if (e >= 0) { s_rot[e < item.n_seg ? e : e - item.n_seg + PC_ONE_SEGS][lane] = cs; continue; }
+            const int64_t slot = __builtin_amdgcn_readlane(m_slot, self_lane) + at;
+            const float kx = bf_lo(tok[0]), ky = bf_lo(tok[1]);
+            uint16_t *kd = (uint16_t *)const_cast<void *>(L.k_store) + (kh * L.slots + slot) * PC_D + lane;
+            kd[0] = to_bf16(kx * cs.x - ky * cs.y);
+            kd[PC_D / 2] = to_bf16(kx * cs.y + ky * cs.x);
+            uint16_t *vd = (uint16_t *)const_cast<void *>(L.v_store) + ((kh * L.slots + slot) / PC_VGROUP * PC_D + lane) * PC_VGROUP + slot % PC_VGROUP;
+            vd[0] = tok[2];
+            vd[PC_D / 2 * PC_VGROUP] = tok[3];
+            if (kh == 0 && lane == 0) O.table[__builtin_amdgcn_readlane(m, self_lane)].len = cd.self_len;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // the token is written before this wave reads its tile
+            first_tile();
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): the rows are in LDS (tiles may still be on their way)
+        asm volatile("s_barrier" ::: "memory");
+        return (const float2 *)s_rot[PC_ONE_SEGS + r];
+    };
+    const DecCall dc{cd.n_q, cd.q_off, cd.self_len - cd.n_q, cd.n_splits, split, cd.part_off, 1};
+    decode_walk<true, ONE_WAVES>(L, dc, kh, tile, tile_stop, describe, [&](int seg) { return (const float2 *)s_rot[seg]; }, prepare, s_acc, s_m, s_l);
+    if (cd.n_splits == 1) return;
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wave's part is out
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        // (wraps to zero with the last split: ready for the next launch)
+        s_last = atomicInc(&O.counters[call * L.n_kv_heads + kh], (unsigned)cd.n_splits - 1) == (unsigned)cd.n_splits - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    merge_cols(L, dc, kh);
+}
+
+void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaunch &L, const PcOne &O, hipStream_t st)
+{
+    const dim3 grid((unsigned)O.n_items * L.n_kv_heads);
+    auto launch = [&](auto args) {
+        __builtin_memcpy(args.w, blob.w, sizeof args < bytes ? sizeof args : bytes);
+        pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(args, L, O);
+    };
+    if (bytes <= 768) launch(PcArgs<768>());
+    else launch(PcArgs<PC_ARG_BYTES>());
 }
 
 void pc_launch_decode_bf16(const PcLaunch &L, int n_items, hipStream_t st)

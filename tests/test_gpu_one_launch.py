@@ -1,0 +1,116 @@
+"""Decode batches that go to one launch (their lists fit its arguments), at the sizes where it can go wrong: a split of one tile,
+waves without a tile, calls with several rows, nothing to see, the same message twice, as many messages in a split as a wave has
+lanes and one more (then the plan builder's way), against the oracle to the bf16 bars of test_gpu_parity and against the same
+calls the plan builder's way (which a split size set by hand selects).  Decode steps: the token it appends is the one
+pc_append_tokens_batch stores."""
+import numpy as np
+import pytest
+
+import pc_inputs as gen
+from pc_inputs import Call
+
+pytestmark = pytest.mark.gpu
+D, THETA = 128, 10000.0
+
+
+def rnd(rng, *shape):
+    return gen.round_to_bf16(rng.standard_normal(shape).astype(np.float32))
+
+
+def fill(lens, h_q, h_kv, rng, reserves=None):
+    import torch
+    from paper_2512_23049_amd import binding, harness as hip
+    ks, vs = [rnd(rng, L, h_kv, D) for L in lens], [rnd(rng, L, h_kv, D) for L in lens]
+    cap = sum((max(L, r) + 31) // 32 * 32 for L, r in zip(lens, reserves or lens))
+    arena = torch.zeros(2 * cap * h_kv * D, dtype=torch.bfloat16, device="cuda:0")
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, THETA, cap, len(lens), arena=arena.data_ptr(), arena_bytes=2 * arena.numel())
+    for i, (k, v) in enumerate(zip(ks, vs)):
+        kd, vd = hip.to_device(k, "bf16"), hip.to_device(v, "bf16")
+        cache.append_message(kd.data_ptr(), vd.data_ptr(), len(k), (reserves or lens)[i])
+        torch.cuda.synchronize()
+    cache.set_decode_sharing(1)
+    return ks, vs, cache, arena
+
+
+def check(ks, vs, calls, q, got, lse):
+    from oracle import choreo_oracle as orc
+    at = 0
+    for c in calls:
+        o, l = orc.attend_call(ks, vs, c.sel, c.self_msg, c.self_start, c.n_q, c.q_pos, q[at:at + c.n_q], THETA, rows=list(range(c.n_q)))
+        d = np.abs(got[at:at + c.n_q] - o)
+        assert d.max() <= 2e-2 and d.mean() <= 1e-3 + np.abs(o).mean() / 512, (d.max(), d.mean())
+        seen = np.isfinite(l)
+        assert (np.isfinite(lse[at:at + c.n_q]) == seen).all() and (np.abs(lse[at:at + c.n_q][seen] - l[seen]) <= 2e-2).all()
+        at += c.n_q
+
+
+@pytest.mark.parametrize("h_q,h_kv,n_q", [(8, 2, 1), (8, 1, 2), (32, 2, 1), (2, 2, 13), (12, 4, 3)])
+@pytest.mark.parametrize("lens,n_calls", [([1], 1), ([31, 33, 32], 2), ([20] * 63, 3), ([20] * 64, 1), ([2100], 1), ([2100, 900, 5], 5), ([9] * 70, 1)])
+def test_one_launch(h_q, h_kv, n_q, lens, n_calls):
+    import torch
+    from paper_2512_23049_amd import harness as hip
+    rng = np.random.default_rng(len(lens) + n_q)
+    own = [n_q + 40 * i for i in range(n_calls)]
+    ks, vs, cache, arena = fill(lens + own, h_q, h_kv, rng)
+    n = len(lens)
+    calls = [Call([(int(m), int(rng.integers(-50, 3000))) for m in rng.permutation(n)], n + i, 2500, n_q, None) for i in range(n_calls)]
+    calls.append(Call([(0, 5), (0, 900)], -1, 70, n_q, list(range(3, 3 + n_q))))       # a message twice, no message of its own
+    calls.append(Call([], -1, 0, n_q, None))                                         # nothing to see
+    rows = sum(c.n_q for c in calls)
+    q = rnd(rng, rows, h_q, D)
+    qd = hip.to_device(q, "bf16")
+    outs = []
+    for tiles_per_split in (0, 7):
+        cache.set_tuning(tiles_per_split, 0)
+        for _ in range(2):                                                           # (the second finds the counters as the first left them)
+            out, lse = torch.full_like(qd, 7.0), torch.full((rows, h_q), 7.0, device="cuda:0")
+            cache.attend(calls, qd.data_ptr(), out.data_ptr(), lse.data_ptr())
+            torch.cuda.synchronize()
+            outs.append((out.float().cpu().numpy(), lse.cpu().numpy()))
+    cache.close()
+    for out, lse in outs:
+        check(ks, vs, calls, q, out, lse)
+    assert (outs[0][0] == outs[1][0]).all() and (outs[0][1] == outs[1][1]).all()
+
+
+@pytest.mark.parametrize("h_q,h_kv", [(8, 2), (64, 8), (4, 4)])
+@pytest.mark.parametrize("first", [1, 30, 31, 32, 95])
+def test_step_appends_its_tokens(h_q, h_kv, first):
+    """Tails of `first` tokens and one more per step, over the edge of a tile; after three steps the stores are those of the
+    two separate calls (V bit for bit, K to a rounding)."""
+    import torch
+    from paper_2512_23049_amd import harness as hip
+    lens, steps = [70, 300, first, first + 2, 40], 3
+    stores, results = [], []
+    for fused in (True, False):
+        rng = np.random.default_rng(first)
+        ks, vs, cache, arena = fill(lens, h_q, h_kv, rng, reserves=[70, 300, first + 8, first + 8, 40])
+        cache.reposition(3, 11)
+        ids, rows = [2, 3], 2
+        for s in range(steps):
+            tk, tv, q = rnd(rng, 2, h_kv, D), rnd(rng, 2, h_kv, D), rnd(rng, rows, h_q, D)
+            for j, m in enumerate(ids):
+                ks[m], vs[m] = np.concatenate([ks[m], tk[j:j + 1]]), np.concatenate([vs[m], tv[j:j + 1]])
+            kd, vd, qd = (hip.to_device(x, "bf16") for x in (tk, tv, q))
+            calls = [Call([(0, 3), (1, 80)], 3, 400, 1, None), Call([(4, 9)], 2, 60, 1, None)]
+            out, lse = torch.full_like(qd, 7.0), torch.full((rows, h_q), 7.0, device="cuda:0")
+            if fused:
+                cache.decode_step(ids, kd.data_ptr(), vd.data_ptr(), calls, qd.data_ptr(), out.data_ptr(), lse.data_ptr())
+            else:
+                cache.set_tuning(7, 0)
+                cache.append_tokens_batch(ids, kd.data_ptr(), vd.data_ptr())
+                cache.attend(calls, qd.data_ptr(), out.data_ptr(), lse.data_ptr())
+            torch.cuda.synchronize()
+            check(ks, vs, calls, q, out.float().cpu().numpy(), lse.cpu().numpy())
+            assert cache.message_info(3)[0] == first + 3 + s
+        results.append((out, lse))
+        # the grown message as another call's parent: its length in the device table
+        calls = [Call([(3, 5)], -1, 600, 1, None)]
+        cache.attend(calls, qd.data_ptr(), out.data_ptr(), lse.data_ptr())
+        torch.cuda.synchronize()
+        check(ks, vs, calls, q[:1], out.float().cpu().numpy(), lse.cpu().numpy())
+        stores.append(arena.float().cpu().numpy().reshape(2, -1))
+        cache.close()
+    assert (stores[0][1] == stores[1][1]).all()
+    assert np.abs(stores[0][0] - stores[1][0]).max() <= 2.0 ** -7 * np.abs(stores[1][0]).max()
+    assert torch.allclose(results[0][0].float(), results[1][0].float(), atol=2e-2) and torch.allclose(results[0][1], results[1][1], atol=2e-2)
