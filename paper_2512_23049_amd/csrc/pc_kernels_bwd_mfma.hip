@@ -16,16 +16,15 @@
 // Kernels, in launch order:
 //   prep      per (32-row block, head): the queries turned by their positions, as fp32 in the lanes' order and as three
 //             bf16 pieces, and the output gradients, rows past the call's end as zeros
-//   rows<0>   per (8 row units, KV head, split of the tiles): Delta partials        (32 MFMAs a tile and unit)
-//   rows<1>   the same walk with Delta known: dq partials                           (56)
+//   delta     per (8 row units, KV head, split of the tiles): Delta partials        (32 MFMAs a tile and unit)
+//   dq        per half of those units, the same walk with Delta known: dq partials  (56)
 //   finish    sum of the dq partials, turned back by the rows' positions
 //   keys      per (4 key tiles, KV head, split of the row units): dK and dV         (128)
 // A unit is 32 rows of one head, a tile 32 keys.  The walks are bound by the matrix pipe (216 MFMAs of 32 cycles per
-// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, means over kernel traces on three
-// boxes: prep 12 to 13, rows<0> 103 to 104, rows<1> 209 to 214, finish 9, keys 373 to 386 us; plain vector kernels (a thread
-// per key, an FMA per product, strided 2-byte reads of V) took 31.4 ms.  (Least times 98, 205 and 367 us on a box where they
-// were 116, 249 and 442 while the splits spilled into a second round of workgroups, every piece of a flushed dq partial
-// waited for the one before it and the key kernel's accumulators were copied between the halves of the register file.)
+// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, means over a kernel trace:
+// prep 12, delta 102, dq 184, finish 9, keys 316 us (dq 208, keys 369 with one wave a unit or tile; plain vector kernels, a
+// thread per key and an FMA per product, took 31.4 ms).  delta: 46 us of it are the pipe, 9 the turns; running the vector
+// work of one of a SIMD's two waves beside the matrix work of the other took 3 off.  keys: longest workgroups first, 9 us more.
 //
 // All operands that a product needs with its indices the other way round (V by dimension, keys, queries and output
 // gradients by token) come from the same LDS tile through ds_read_b64_tr_b16: within 16 lanes, lane l points at row
@@ -211,14 +210,11 @@ __global__ __launch_bounds__(256) void pc_bwd_prep_kernel(PcLaunch L, PcBwd B)
 }
 
 // ----------------------------------------------------------------------------------------------- row-major kernels
-// A workgroup is 8 waves = 8 consecutive units (heads of a KV head fastest), which share the staged K and V tiles: a
+// Delta.  A workgroup is 8 waves = 8 consecutive units (heads of a KV head fastest), which share the staged K and V tiles: a
 // ring of four, requested three tiles ahead by direct loads, one barrier a tile.  S^T = K Q^T and dP^T = V dO^T leave a
-// row's values in one lane column and in the order in which dq^T = K^T dS^T takes them.  The turned queries (three
-// pieces) live in registers and are made anew from the fp32 copy at every segment; the output gradients are read from
-// LDS, which is what keeps the kernel at two waves per SIMD.  dq is collected in the frame of the segment's keys and
-// turned into the rows' frame whenever the rotation changes, by adding to the unit's fp32 partial in memory.
-template <bool DQ>
-__global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B)
+// row's values in one lane column.  The turned queries (three pieces) live in registers and are made anew from the fp32 copy
+// at every segment; the output gradients are read from LDS, which is what keeps the kernel at two waves per SIMD.
+__global__ __launch_bounds__(512, 1) void pc_bwd_delta_kernel(PcLaunch L, PcBwd B)
 {
     constexpr int RING = 4, AHEAD = 3;
     __shared__ __attribute__((aligned(1024))) unsigned char s_k[RING][TILE_BYTES];
@@ -242,13 +238,11 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
     const int64_t U = (int64_t)(cd.rb_off + ub - B.rb0) * L.n_q_heads + h;
 
     // the row's scalars; rows that saw nothing or do not exist get a log-sum-exp of +inf, which makes their p zero
-    float lse2 = INFINITY, delta = 0.f;
+    float lse2 = INFINITY;
     if (row_ok) {
         const float v = B.lse[(int64_t)(cd.q_off + row) * L.n_q_heads + h];
         if (v > -INFINITY) lse2 = v * 1.4426950408889634f;
-        if constexpr (DQ) for (int s = 0; s < cd.n_splits; ++s) delta += B.delta_part[((int64_t)s * B.n_units + U) * 32 + n];
     }
-    if constexpr (DQ) { if (unit_ok && item.split == 0 && hh == 0) B.stat[U * 32 + n] = make_float2(lse2, delta); }
 
     const bool some_dead = __builtin_amdgcn_ballot_w64(row_ok && lse2 == INFINITY) != 0;
     const RowMajor rk(perm_row(n), lane), rg(n, lane);
@@ -287,50 +281,7 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
             for (int i = 0; i < 3; ++i) { qp[i][ks] = pu.p[i]; qp[i][ks + 4] = pv.p[i]; }
         }
     };
-    f32x16 acc[DQ ? 4 : 1];
     float dsum = 0.f;
-    bool first = true;                                   // nothing written to the unit's dq partial yet
-    float4 *part = B.dq_part + ((int64_t)item.split * B.n_units + U) * 1024 + lane;
-    auto clear = [&]() {
-        if constexpr (DQ)
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
-    };
-    // dq of the segment, turned by +(start - base), into the partial: float4 (db, q4) of a lane is dims 32 db + 8 q4 + 4 hh + 0..3
-    auto flush = [&](int seg) __attribute__((always_inline)) {
-        if constexpr (DQ) {
-            const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2) + 4 * hh);
-            // (all of the old partial is requested before any of the new one is stored: a store in between would make each
-            // load wait for the one before it, eight round trips to memory instead of one)
-            float4 old[16];
-            if (!first)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) old[i] = part[i * 64];
-            else
-#pragma unroll
-                for (int i = 0; i < 16; ++i) old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const float4 c0 = rs[16 * db + 4 * q4], c1 = rs[16 * db + 4 * q4 + 1];
-                    const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sx[4] = {c0.y, c0.w, c1.y, c1.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float a = acc[db][4 * q4 + i] * B.scale, b = acc[db + 2][4 * q4 + i] * B.scale;
-                        float *ol = reinterpret_cast<float *>(&old[db * 4 + q4]), *oh = reinterpret_cast<float *>(&old[db * 4 + q4 + 8]);
-                        ol[i] += a * cx[i] - b * sx[i]; oh[i] += a * sx[i] + b * cx[i];
-                    }
-                }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) part[i * 64] = old[i];
-            first = false;
-        }
-    };
-    clear();
-
     const int t0 = item.tile_begin, t1 = item.tile_end;
     if (t0 < t1) {
         {   // the unit's output gradients: 4 rows per instruction, whole lines
@@ -351,21 +302,8 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
             ring_barrier();                              // ... every wave's has, and tile t - 1 is no longer read
             const int seg = __builtin_amdgcn_readfirstlane(d[0].z), flags = __builtin_amdgcn_readfirstlane(d[0].w), key0 = __builtin_amdgcn_readfirstlane(d[0].y);
             if (cur < 0 || (flags & PC_TILE_FRESH)) {
-                if (unit_ok) {
-                    if (cur >= 0) { flush(cur); clear(); }
-                    turn(seg);
-                }
+                if (unit_ok) turn(seg);
                 cur = seg;
-            }
-            if (DQ && (flags & PC_TILE_SELF)) {
-                // A tile of the new message (uniform over the workgroup): a zero takes a key that stands behind a row's own
-                // token out of dq only while it is finite, which the caller's tokens need not be.  (A row that sees such a
-                // key has no gradient, or, where its score is -inf, a probability of 0: a score of -1e38 gives the same.)
-                uint4 *chunk = reinterpret_cast<uint4 *>(&s_k[slot][0]) + threadIdx.x;
-                const bf16x8 raw = __builtin_bit_cast(bf16x8, *chunk);
-                *chunk = __builtin_bit_cast(uint4, finite8(raw));
-                __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
-                ring_barrier();
             }
             d[AHEAD] = describe(t + AHEAD);
             request(d[AHEAD], (slot + AHEAD) & (RING - 1));
@@ -385,46 +323,281 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_rows_kernel(PcLaunch L, PcBwd B
                 for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rv.get(vt, ks), rg.by_row(lds_g, ks), dp);
                 const int valid = flags & 0xFF;
                 const bool self = (flags & PC_TILE_SELF) != 0;
-                float w[16];                             // p dp, or p (dp - Delta)
+                float w[16];                             // p dp
 #pragma unroll
                 for (int r = 0; r < 16; ++r)             // (the maximum: an infinite key times a piece that is 0 is a NaN, see the key-major kernel)
-                    w[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -lse2), -1e30f)) * (DQ ? dp[r] - delta : dp[r]);
+                    w[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -lse2), -1e30f)) * dp[r];
                 // (masked behind the product: the value of a token behind the row's own is the caller's and need not be finite)
                 if (valid < PC_TILE || some_dead || (self && key0 + PC_TILE - 1 > blk_lim_lo)) {      // ragged or causal tile (uniform)
                     const int lim = lse2 == INFINITY ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) w[r] = (16 * (r >> 3) + 8 * hh + (r & 7) < lim) ? w[r] : 0.f;
                 }
-                if constexpr (DQ) {
 #pragma unroll
-                    for (int st = 0; st < 2; ++st) {
-                        const Pieces ds = split8(w + 8 * st);
-#pragma unroll
-                        for (int db = 0; db < 4; ++db) {
-                            const bf16x8 k = rk.by_col(kt, st, db);
-                            acc[db] = MFMA32(k, ds.p[2], acc[db]);
-                            acc[db] = MFMA32(k, ds.p[1], acc[db]);
-                            acc[db] = MFMA32(k, ds.p[0], acc[db]);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) dsum += w[r];
-                }
+                for (int r = 0; r < 16; ++r) dsum += w[r];
             }
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) d[i] = d[i + 1];
         }
         wait_vm<0>();
-        if (unit_ok) flush(cur);
-    } else if (DQ && unit_ok) {                          // nothing to see: a partial of zeros
+    }
+    dsum += __shfl_xor(dsum, 32);
+    if (unit_ok && hh == 0) B.delta_part[((int64_t)item.split * B.n_units + U) * 32 + n] = dsum;
+}
+
+// dq, with Delta known.  Two waves a unit, on the same SIMD: the first holds the unit's turned queries and output gradients and
+// makes ds = p (dp - Delta), which it leaves in LDS in fp32; the second follows one tile behind and adds dq^T = K^T dS^T, collected
+// in the frame of the segment's keys and turned into the rows' frame whenever the rotation changes, by adding to the unit's
+// fp32 partial in memory.  (With one wave a unit, eight units a workgroup, both waves of a SIMD did their matrix work and then
+// their vector work at the same time, and all waited while any of them turned its queries or its sums: 208 us, now 184, for the
+// batch above.)  A workgroup
+// takes half of an item's eight units; ring of four tiles: the one of the second waves, that of the first, two on their way.
+__global__ __launch_bounds__(512, 2) void pc_bwd_dq_kernel(PcLaunch L, PcBwd B)
+{
+    constexpr int RING = 4, AHEAD = 2, W_BYTES = 4096;
+    __shared__ __attribute__((aligned(1024))) unsigned char s_k[RING][TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_v[RING][TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_w[2][4][W_BYTES];       // ds of two tiles: float4 j of lane l at 1024 j + 16 l
+
+    const int kh = blockIdx.x % L.n_kv_heads;
+    const int idx = blockIdx.x / L.n_kv_heads;
+    const PcItem item = L.items[idx >> 1];
+    const PcCallDesc cd = L.calls[item.call];
+    const int g = L.n_q_heads / L.n_kv_heads;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hh = lane >> 5;
+    const int pair = wave & 3, unit0 = item.unit0 + 4 * (idx & 1);
+    const bool is_dq = wave >= 4;                        // the second wave of the unit
+    const int n_units = ((cd.n_q + 31) >> 5) * g;
+    if (unit0 >= n_units) return;                        // (the whole workgroup)
+    const bool unit_ok = unit0 + pair < n_units;
+    const int unit = unit_ok ? unit0 + pair : unit0;
+    const int ub = unit / g, h = kh * g + (unit - ub * g);
+    const int64_t U = (int64_t)(cd.rb_off + ub - B.rb0) * L.n_q_heads + h;
+
+    const RowMajor rk(perm_row(n), lane);
+    const unsigned lds_k = (unsigned)(uintptr_t)&s_k[0][0], lds_v = (unsigned)(uintptr_t)&s_v[0][0];
+    const unsigned k_src = (threadIdx.x >> 4) * 256 + (((threadIdx.x & 15) ^ swz(threadIdx.x >> 4)) << 4);
+    const unsigned v_src = (unsigned)v_src_chunk(threadIdx.x) * 16;
+    const unsigned char *kb = (const unsigned char *)L.k_store + (int64_t)kh * L.slots * PC_D * 2;
+    const unsigned char *vb = (const unsigned char *)L.v_store + (int64_t)kh * L.slots * PC_D * 2;
+    const PcTile *tab = L.tiles + item.tile_tab0;
+    const int t0 = item.tile_begin, t1 = item.tile_end, last = t1 - 1;
+    float4 *part = B.dq_part + ((int64_t)item.split * B.n_units + U) * 1024 + lane;
+    if (t0 >= t1) {                                      // nothing to see: a partial of zeros, and the row's scalars
+        if (is_dq && unit_ok)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) part[64 * i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = 0; i < 16; ++i) part[64 * i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if constexpr (!DQ) {
-        dsum += __shfl_xor(dsum, 32);
-        if (unit_ok && hh == 0) B.delta_part[((int64_t)item.split * B.n_units + U) * 32 + n] = dsum;
+    auto describe = [&](int t) { return scalar16(tab + __builtin_amdgcn_readfirstlane(min(t, last))); };   // {slot0, key0, seg, valid | flags}
+    auto request = [&](const i32x4 &d, int slot) {
+        const int64_t at = (int64_t)__builtin_amdgcn_readfirstlane(d.x) * 256;
+        dma16(kb + at, k_src, lds_k + slot * TILE_BYTES + wave * 1024);
+        dma16(vb + at, v_src, lds_v + slot * TILE_BYTES + wave * 1024);
+    };
+    i32x4 d[AHEAD + 1];
+    if (t0 < t1)
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) { d[i] = describe(t0 + i); request(d[i], i); }
+    // tile t, of the first waves: it and its successor have landed (so that fragments can be read a tile ahead), the second waves
+    // have its predecessor's ds, and nobody reads the one before that, whose slot the next request takes
+    auto next_tile = [&](int t) {
+        __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0), lgkmcnt(0)
+        ring_barrier();
+        if (t < t1 && (__builtin_amdgcn_readfirstlane(d[0].w) & PC_TILE_SELF)) {
+            // A tile of the new message (uniform over the workgroup): a zero takes a key that stands behind a row's own
+            // token out of dq only while it is finite, which the caller's tokens need not be.  (A row that sees such a
+            // key has no gradient, or, where its score is -inf, a probability of 0: a score of -1e38 gives the same.)
+            uint4 *chunk = reinterpret_cast<uint4 *>(&s_k[(t - t0) & (RING - 1)][0]) + threadIdx.x;
+            const bf16x8 raw = __builtin_bit_cast(bf16x8, *chunk);
+            *chunk = __builtin_bit_cast(uint4, finite8(raw));
+            __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0)
+            ring_barrier();
+        }
+        d[AHEAD] = describe(t + AHEAD);
+        request(d[AHEAD], (t - t0 + AHEAD) & (RING - 1));
+    };
+
+    if (!is_dq) {
+        const int row = 32 * ub + n;
+        const bool row_ok = unit_ok && row < cd.n_q;
+        const int self_lim = cd.self_len - cd.n_q + row; // last own token this row sees
+        const int blk_lim_lo = cd.self_len - cd.n_q + 32 * ub;
+        // the row's scalars; rows that saw nothing or do not exist get a log-sum-exp of +inf, which makes their p zero
+        float lse2 = INFINITY, delta = 0.f;
+        if (row_ok) {
+            const float v = B.lse[(int64_t)(cd.q_off + row) * L.n_q_heads + h];
+            if (v > -INFINITY) lse2 = v * 1.4426950408889634f;
+            for (int s = 0; s < cd.n_splits; ++s) delta += B.delta_part[((int64_t)s * B.n_units + U) * 32 + n];
+        }
+        if (unit_ok && item.split == 0 && hh == 0) B.stat[U * 32 + n] = make_float2(lse2, delta);
+        if (t0 >= t1) return;
+        const bool some_dead = __builtin_amdgcn_ballot_w64(row_ok && lse2 == INFINITY) != 0;
+        const ValuesByKey<true> rv(lane);
+        bf16x8 go[8];                                    // the unit's output gradients: the lane's row, dims 16 ks + 8 hh + 0..7
+        {
+            const unsigned char *src = (const unsigned char *)B.q_pieces + U * (4 * TILE_BYTES) + 3 * TILE_BYTES + n * 256 + hh * 16;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) go[ks] = __builtin_bit_cast(bf16x8, ldg16(src + 32 * ks));
+        }
+        bf16x8 qp[3][8];
+        auto turn = [&](int seg) __attribute__((always_inline)) {       // the unit's queries turned by -(start - base) of a segment
+            const float4 *qt = B.q_turned + U * 1024 + hh * 32 + n;
+            const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2) + 8 * hh);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const float4 xa = qt[ks * 256], xb = qt[ks * 256 + 64], ya = qt[ks * 256 + 128], yb = qt[ks * 256 + 192];
+                const float x[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w}, y[8] = {ya.x, ya.y, ya.z, ya.w, yb.x, yb.y, yb.z, yb.w};
+                float u[8], v[8];
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    const float4 cs = rs[8 * ks + (j >> 1)];
+                    u[j] = x[j] * cs.x + y[j] * cs.y; v[j] = y[j] * cs.x - x[j] * cs.y;
+                    u[j + 1] = x[j + 1] * cs.z + y[j + 1] * cs.w; v[j + 1] = y[j + 1] * cs.z - x[j + 1] * cs.w;
+                }
+                const Pieces pu = split8(u), pv = split8(v);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) { qp[i][ks] = pu.p[i]; qp[i][ks + 4] = pv.p[i]; }
+            }
+        };
+        int cur = -1;
+        bf16x8 kf[8];                                    // the tile's keys, read while its predecessor is worked on
+        for (int t = t0; t < t1; ++t) {
+            next_tile(t);
+            const int slot = (t - t0) & (RING - 1);
+            const int seg = __builtin_amdgcn_readfirstlane(d[0].z), flags = __builtin_amdgcn_readfirstlane(d[0].w), key0 = __builtin_amdgcn_readfirstlane(d[0].y);
+            if (cur < 0 || (flags & PC_TILE_FRESH)) {
+                if (unit_ok) turn(seg);
+                cur = seg;
+            }
+            if (unit_ok) {
+                const unsigned kt = lds_k + slot * TILE_BYTES, vt = lds_v + slot * TILE_BYTES, kn = lds_k + ((slot + 1) & (RING - 1)) * TILE_BYTES;
+                if (t == t0 || (flags & PC_TILE_SELF))   // (a tile of the new message was made finite since)
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks) kf[ks] = rk.by_row(kt, ks);
+                f32x16 s, dp;
+                bf16x8 vf[4];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    s = MFMA32(kf[ks], qp[2][ks], s);
+                    s = MFMA32(kf[ks], qp[1][ks], s);
+                    s = MFMA32(kf[ks], qp[0][ks], s);
+                    if (ks >= 4) vf[ks - 4] = rv.get(vt, ks - 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    dp = MFMA32(vf[ks & 3], go[ks], dp);
+                    if (ks < 4) vf[ks] = rv.get(vt, ks + 4);
+                    kf[ks] = rk.by_row(kn, ks);          // (behind the last tile: what the ring holds there, which is not used)
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int valid = flags & 0xFF;
+                const bool self = (flags & PC_TILE_SELF) != 0;
+                float w[16];                             // p (dp - Delta)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)             // (the maximum: an infinite key times a piece that is 0 is a NaN, see the key-major kernel)
+                    w[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -lse2), -1e30f)) * (dp[r] - delta);
+                // (masked behind the product: the value of a token behind the row's own is the caller's and need not be finite)
+                if (valid < PC_TILE || some_dead || (self && key0 + PC_TILE - 1 > blk_lim_lo)) {      // ragged or causal tile (uniform)
+                    const int lim = lse2 == INFINITY ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) w[r] = (16 * (r >> 3) + 8 * hh + (r & 7) < lim) ? w[r] : 0.f;
+                }
+                float4 *out = reinterpret_cast<float4 *>(&s_w[(t - t0) & 1][pair][0]) + lane;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) out[64 * j] = make_float4(w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) d[i] = d[i + 1];
+        }
+        next_tile(t1);                                   // (the second waves' last tile)
+        wait_vm<0>();
+        return;
     }
+    if (t0 >= t1) return;
+    f32x16 acc[4];
+    bool first = true;                                   // nothing written to the unit's dq partial yet
+    auto clear = [&]() {
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+    };
+    // dq of the segment, turned by +(start - base), into the partial: float4 (db, q4) of a lane is dims 32 db + 8 q4 + 4 hh + 0..3
+    auto flush = [&](int seg) __attribute__((always_inline)) {
+        const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2) + 4 * hh);
+        // (all of the old partial is requested before any of the new one is stored: a store in between would make each
+        // load wait for the one before it, eight round trips to memory instead of one)
+        float4 old[16];
+        if (!first)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) old[i] = part[i * 64];
+        else
+#pragma unroll
+            for (int i = 0; i < 16; ++i) old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 c0 = rs[16 * db + 4 * q4], c1 = rs[16 * db + 4 * q4 + 1];
+                const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sx[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a = acc[db][4 * q4 + i] * B.scale, b = acc[db + 2][4 * q4 + i] * B.scale;
+                    float *ol = reinterpret_cast<float *>(&old[db * 4 + q4]), *oh = reinterpret_cast<float *>(&old[db * 4 + q4 + 8]);
+                    ol[i] += a * cx[i] - b * sx[i]; oh[i] += a * sx[i] + b * cx[i];
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[i * 64] = old[i];
+        first = false;
+    };
+    clear();
+    int cur = -1;
+    next_tile(t0);                                       // (the first waves' first tile)
+    bf16x8 kf[2][4];
+    auto read_keys = [&](int t) {
+        const unsigned kt = lds_k + ((t - t0) & (RING - 1)) * TILE_BYTES;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) kf[st][db] = rk.by_col(kt, st, db);
+    };
+    read_keys(t0);
+    for (int t = t0; t < t1; ++t) {
+        const int seg = __builtin_amdgcn_readfirstlane(d[0].z), flags = __builtin_amdgcn_readfirstlane(d[0].w);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) d[i] = d[i + 1];
+        next_tile(t + 1);
+        if (!unit_ok) continue;
+        if (cur < 0 || (flags & PC_TILE_FRESH)) {
+            if (cur >= 0) { flush(cur); clear(); }
+            cur = seg;
+        }
+        const float4 *in = reinterpret_cast<const float4 *>(&s_w[(t - t0) & 1][pair][0]) + lane;
+        float w[16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 x = in[64 * j];
+            w[4 * j] = x.x; w[4 * j + 1] = x.y; w[4 * j + 2] = x.z; w[4 * j + 3] = x.w;
+        }
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            const Pieces ds = split8(w + 8 * st);
+#pragma unroll
+            for (int db = 0; db < 4; ++db) {
+                acc[db] = MFMA32(kf[st][db], ds.p[2], acc[db]);
+                acc[db] = MFMA32(kf[st][db], ds.p[1], acc[db]);
+                acc[db] = MFMA32(kf[st][db], ds.p[0], acc[db]);
+            }
+        }
+        read_keys(t + 1);                                // (behind the last tile: not used)
+    }
+    wait_vm<0>();
+    if (unit_ok) flush(cur);
 }
 
 // dq: the splits' partials summed in order and turned back by the row's own position
@@ -468,17 +641,21 @@ __global__ __launch_bounds__(256) void pc_bwd_finish_kernel(PcLaunch L, PcBwd B)
 }
 
 // ----------------------------------------------------------------------------------------------------- key-major
-// A workgroup is 4 waves, one per SIMD with all of its 512 registers; a wave owns one 32-key tile of the call (one
-// placement of a message): its keys turned to the call's positions (three pieces), its values, and the sums of dK and
-// dV stay in registers while the call's units of this KV head go by, staged through LDS in a ring of three (queries in
-// three pieces, output gradients, row scalars: 32 KB a unit).  Here the keys are turned, not the queries: the waves of a
-// workgroup hold tiles of different messages, and the staged queries then serve all of them.  At the end dK is turned
-// back to the stored frame and both sums meet those of the tokens' other placements (other calls, repeated listings,
-// other splits of the units) through one fp32 atomic per element, whole cache lines at a time.
-__global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B)
+// A workgroup takes four 32-key tiles of the call (each one placement of a message), with two waves a tile that sit on the
+// same SIMD: the first holds the tile's keys turned to the call's positions (three pieces) and the sums of dV, and makes the
+// probabilities, which it leaves in LDS in fp32; the second holds the values and the sums of dK and follows one unit behind.  The
+// units of this KV head go by, staged through LDS in a ring of three (queries in three pieces, output gradients, row
+// scalars: 32 KB a unit).  Keys, values and both sums fill 256 registers: with one wave a tile, one a SIMD, all of that wave's
+// vector work and every wait for LDS stood in its matrix work's way (3.9 us a unit, 128 MFMAs of 32 cycles = 1.8; with two waves
+// a tile 3.1, which is 1.4 PFLOP/s of the 1.73 that a bare MFMA loop reaches on such operands).  Here the keys are turned, not the queries: the waves of a workgroup hold tiles of different messages, and the
+// staged queries then serve all of them.  At the end dK is turned back to the stored frame and both sums meet those of the
+// tokens' other placements (other calls, repeated listings, other splits of the units) through one fp32 atomic per
+// element, whole cache lines at a time.
+__global__ __launch_bounds__(512, 2) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B)
 {
-    constexpr int RING = 3, STAGE = 4 * TILE_BYTES, N_DMA = 9;
-    __shared__ __attribute__((aligned(1024))) unsigned char s_q[RING][STAGE];
+    constexpr int RING = 3, STAGE = 4 * TILE_BYTES, P_BYTES = 4096, TURN = 32 * (PC_D + 4) * 4;
+    constexpr int MEM = RING * STAGE + 2 * 4 * P_BYTES > 8 * TURN ? RING * STAGE + 2 * 4 * P_BYTES : 8 * TURN;
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[MEM];   // ring, probabilities of two units; at the end the sums being turned round
     __shared__ __attribute__((aligned(256))) float2 s_stat[RING][32];
 
     const int kh = blockIdx.x % L.n_kv_heads;
@@ -487,165 +664,200 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
     const int g = L.n_q_heads / L.n_kv_heads;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hh = lane >> 5;
-    const bool active = wave < item.n_tiles;
-    const i32x4 d = scalar16(L.tiles + cd.tile_off + item.tile0 + (active ? wave : 0));
+    const int tile = wave & 3;
+    const bool is_dk = wave >= 4;                        // the second wave of the tile
+    const bool active = tile < item.n_tiles;
+    const i32x4 d = scalar16(L.tiles + cd.tile_off + item.tile0 + (active ? tile : 0));
     const int slot0 = __builtin_amdgcn_readfirstlane(d.x), key0 = __builtin_amdgcn_readfirstlane(d.y);
     const int seg = __builtin_amdgcn_readfirstlane(d.z), flags = __builtin_amdgcn_readfirstlane(d.w);
     const bool self = (flags & PC_TILE_SELF) != 0;
     const int tok0 = cd.self_len - cd.n_q;
 
-    const unsigned lds_q = (unsigned)(uintptr_t)&s_q[0][0], lds_stat = (unsigned)(uintptr_t)&s_stat[0][0];
-    unsigned q_src[2];                                   // rows 16 i + tid / 16 of a 32-row tile
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = 16 * i + (int)(threadIdx.x >> 4);
-        q_src[i] = (unsigned)(r * 256 + (((threadIdx.x & 15) ^ swz(r)) << 4));
-    }
+    const unsigned lds_q = (unsigned)(uintptr_t)&s_mem[0], lds_stat = (unsigned)(uintptr_t)&s_stat[0][0];
+    const unsigned q_src = (unsigned)((threadIdx.x >> 4) * 256 + (((threadIdx.x & 15) ^ swz(threadIdx.x >> 4)) << 4));
     const int64_t u_base = (int64_t)(cd.rb_off - B.rb0) * L.n_q_heads + kh * g;
-    // the units are requested in order; beyond the last one it comes again, so that every wait counts the same requests
-    int req_rt = item.rt_begin, req_rb = item.rt_begin / g, req_h = item.rt_begin - req_rb * g;
-    auto request = [&](int slot) {
+    int req_rt = item.rt_begin, req_rb = item.rt_begin / g, req_h = item.rt_begin - req_rb * g, req_slot = 0;
+    auto request = [&]() {                               // the next unit, if there is one
+        if (req_rt >= item.rt_end) return;
         const int64_t u = u_base + (int64_t)req_rb * L.n_q_heads + req_h;
-        if (req_rt + 1 < item.rt_end) { ++req_rt; if (++req_h == g) { req_h = 0; ++req_rb; } }
+        ++req_rt;
+        if (++req_h == g) { req_h = 0; ++req_rb; }
         const unsigned char *src = (const unsigned char *)B.q_pieces + u * STAGE;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            dma16(src + (i >> 1) * TILE_BYTES, q_src[i & 1], lds_q + slot * STAGE + (i >> 1) * TILE_BYTES + (i & 1) * 4096 + wave * 1024);
-        dma4(B.stat + u * 32, lane * 4, lds_stat + slot * 256);       // (every wave brings the same 256 bytes)
+        for (int i = 0; i < 4; ++i) dma16(src + i * TILE_BYTES, q_src, lds_q + req_slot * STAGE + i * TILE_BYTES + wave * 1024);
+        if (wave == 0) dma4(B.stat + u * 32, lane * 4, lds_stat + req_slot * 256);
+        req_slot = req_slot + 1 == RING ? 0 : req_slot + 1;
     };
-    // the wave's values, through the ring's last slot
-    {
+    // the values, through the ring's last slot
+    if (is_dk) {
         const unsigned char *vb = (const unsigned char *)L.v_store + ((int64_t)kh * L.slots + slot0) * PC_D * 2;
-        const unsigned at = lds_q + (RING - 1) * STAGE + wave * TILE_BYTES;
+        const unsigned at = lds_q + (RING - 1) * STAGE + tile * TILE_BYTES;
 #pragma unroll
         for (int i = 0; i < 8; ++i) dma16(vb, (unsigned)v_src_chunk(64 * i + lane) * 16, at + i * 1024);
     }
-    request(0);
-    request(1);
-    // the wave's keys turned by +(start - base): lane = key, dims 16 ks + 8 hh + 0..7
-    bf16x8 kp[3][8], vf[8];
+    request();
     const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + seg) * (PC_D / 2));
-    {
-        const uint16_t *kr = (const uint16_t *)L.k_store + ((int64_t)kh * L.slots + slot0 + n) * PC_D + 8 * hh;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const uint4 lo = ldg16(kr + 16 * ks), hi = ldg16(kr + 16 * ks + 64);
-            const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
-            float x[8], y[8];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float4 cs = rs[8 * ks + 4 * hh + u];
-                const float a0 = bf_lo(lw[u]), a1 = bf_hi(lw[u]), b0 = bf_lo(hw[u]), b1 = bf_hi(hw[u]);
-                x[2 * u] = a0 * cs.x - b0 * cs.y; y[2 * u] = a0 * cs.y + b0 * cs.x;
-                x[2 * u + 1] = a1 * cs.z - b1 * cs.w; y[2 * u + 1] = a1 * cs.w + b1 * cs.z;
-            }
-            const Pieces px = split8(x), py = split8(y);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) { kp[i][ks] = px.p[i]; kp[i][ks + 4] = py.p[i]; }
-        }
-    }
-    wait_vm<0>();
-    ring_barrier();
-    {
-        const ValuesByKey<false> rv(lane);
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) vf[ks] = rv.get(lds_q + (RING - 1) * STAGE + wave * TILE_BYTES, ks);
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(vf[ks]));        // (read before the slot is requested again)
-    }
-    // A value that is not finite makes dp a NaN for every row of a block, and no zero takes the rows without a gradient out of dK
-    // again (a select per probability would: 24 us of 740 for a training step).  It is taken as zeros here, and its key's dK is
-    // a NaN at the end if a row with a gradient sees it.
-    uint64_t odd = 0;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        const uint4 u = __builtin_bit_cast(uint4, vf[ks]);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bad |= (w[j] & 0x7F80u) == 0x7F80u || (w[j] & 0x7F800000u) == 0x7F800000u;
-        odd |= __builtin_amdgcn_ballot_w64(bad);
-        if (bad) vf[ks] = frag4(0, 0, 0, 0);
-    }
-    f32x16 dk[4], dv[4];
+    const RowMajor rq(perm_row(n), lane);
+    f32x16 sum[4];                                       // dV, or dK
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dk[db][r] = dv[db][r] = 0.f;
+        for (int r = 0; r < 16; ++r) sum[db][r] = 0.f;
+    // the probabilities of a unit: float4 j of lane l at 1024 j + 16 l
+    float4 *const s_p = reinterpret_cast<float4 *>(&s_mem[RING * STAGE + tile * P_BYTES]) + lane;
+    uint64_t odd = 0;                                    // second wave: keys whose values are not finite
+    // A unit's turn: every wave's share of it has landed, the probabilities of the unit before are written, and the slot of the
+    // one before that, which the next request takes, is no longer read.
+    auto next_unit = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0), lgkmcnt(0)
+        ring_barrier();
+        request();
+    };
+    int rb = item.rt_begin / g, left = (rb + 1) * g - item.rt_begin, slot = 0, odd_unit = 0;      // row block, its units still to come, ring slot
 
-    const RowMajor rq(perm_row(n), lane);
-    int rb = item.rt_begin / g, left = (rb + 1) * g - item.rt_begin, slot = 0;      // row block, its units still to come, ring slot
-    for (int rt = item.rt_begin; rt < item.rt_end; ++rt) {
-        wait_vm<N_DMA>();                                // this wave's share of the unit has landed
-        ring_barrier();                                  // ... every wave's has, and the slot two ahead is no longer read
-        request(slot >= 1 ? slot - 1 : RING - 1);        // unit rt + 2
-        const int row0 = tok0 + 32 * rb;                 // own token of the block's first row
-        const unsigned qt = lds_q + slot * STAGE;
-        const float4 *st = reinterpret_cast<const float4 *>(&s_stat[slot][8 * hh]);
-        if (--left == 0) { ++rb; left = g; }
-        slot = slot + 1 == RING ? 0 : slot + 1;
-        if (!active || (self && key0 > row0 + 31)) continue;            // (uniform over the wave: no row of the block sees the tile)
-        const int lim = self && key0 + PC_TILE - 1 > row0 ? key0 + n - row0 : -1;      // the first row that sees the lane's key
-        const RowMajor::Cols qc = rq.cols(qt);
-        f32x16 s, dp;
+    if (!is_dk) {
+        // the keys turned by +(start - base): lane = key, dims 16 ks + 8 hh + 0..7
+        bf16x8 kp[3][8];
+        {
+            const uint16_t *kr = (const uint16_t *)L.k_store + ((int64_t)kh * L.slots + slot0 + n) * PC_D + 8 * hh;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+            for (int ks = 0; ks < 4; ++ks) {
+                const uint4 lo = ldg16(kr + 16 * ks), hi = ldg16(kr + 16 * ks + 64);
+                const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
+                float x[8], y[8];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 a0 = rq.by_row(qt, ks), a1 = rq.by_row(qt + TILE_BYTES, ks), a2 = rq.by_row(qt + 2 * TILE_BYTES, ks);
-            s = MFMA32(a2, kp[0][ks], s);
-            s = MFMA32(a1, kp[1][ks], s);
-            s = MFMA32(a0, kp[2][ks], s);
-            s = MFMA32(a1, kp[0][ks], s);
-            s = MFMA32(a0, kp[1][ks], s);
-            s = MFMA32(a0, kp[0][ks], s);
-        }
+                for (int u = 0; u < 4; ++u) {
+                    const float4 cs = rs[8 * ks + 4 * hh + u];
+                    const float a0 = bf_lo(lw[u]), a1 = bf_hi(lw[u]), b0 = bf_lo(hw[u]), b1 = bf_hi(hw[u]);
+                    x[2 * u] = a0 * cs.x - b0 * cs.y; y[2 * u] = a0 * cs.y + b0 * cs.x;
+                    x[2 * u + 1] = a1 * cs.z - b1 * cs.w; y[2 * u + 1] = a1 * cs.w + b1 * cs.z;
+                }
+                const Pieces px = split8(x), py = split8(y);
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rq.by_row(qt + 3 * TILE_BYTES, ks), vf[ks], dp);
-        // register r: row 16 (r / 8) + 8 hh + r % 8 of the block
-        float p[16], w[16];
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
-            // (The maximum takes a NaN to a probability of 0.  A row that saw a NaN or +inf has no gradient, see prep; where a row
-            // that has one meets an infinite key its score is -inf, which the pieces' products turn into NaN.)
-            p[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -x.x), -1e30f));
-            p[r + 1] = ex2(fmaxf(__builtin_fmaf(s[r + 1], L.scale_log2, -x.z), -1e30f));
-            w[r] = dp[r] - x.y;
-            w[r + 1] = dp[r + 1] - x.w;
-        }
-        // (no branch for the few causal tiles: it would cut the block the scheduler mixes matrix and vector work in)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = (16 * (r >> 3) + 8 * hh + (r & 7) >= lim) ? p[r] : 0.f;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const Pieces pp = split8(p + 8 * half);
-#pragma unroll
-            for (int db = 0; db < 4; ++db) {
-                const bf16x8 a = RowMajor::by_col(qc, 3 * TILE_BYTES, half, db);
-                dv[db] = MFMA32(a, pp.p[2], dv[db]);
-                dv[db] = MFMA32(a, pp.p[1], dv[db]);
-                dv[db] = MFMA32(a, pp.p[0], dv[db]);
+                for (int i = 0; i < 3; ++i) { kp[i][ks] = px.p[i]; kp[i][ks + 4] = py.p[i]; }
             }
         }
+        for (int rt = item.rt_begin; rt < item.rt_end; ++rt) {
+            next_unit();
+            const int row0 = tok0 + 32 * rb;             // own token of the block's first row
+            const unsigned qt = lds_q + slot * STAGE;
+            const float4 *st = reinterpret_cast<const float4 *>(&s_stat[slot][8 * hh]);
+            float4 *const pw = s_p + odd_unit * (4 * P_BYTES / 16);
+            if (--left == 0) { ++rb; left = g; }
+            slot = slot + 1 == RING ? 0 : slot + 1;
+            odd_unit ^= 1;
+            if (!active || (self && key0 > row0 + 31)) continue;        // (uniform over the wave: no row of the block sees the tile)
+            const int lim = self && key0 + PC_TILE - 1 > row0 ? key0 + n - row0 : -1;      // the first row that sees the lane's key
+            f32x16 s;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) w[r] *= p[r];
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const Pieces ds = split8(w + 8 * half);
+            for (int ks = 0; ks < 8; ++ks) {
+                const bf16x8 a0 = rq.by_row(qt, ks), a1 = rq.by_row(qt + TILE_BYTES, ks), a2 = rq.by_row(qt + 2 * TILE_BYTES, ks);
+                s = MFMA32(a2, kp[0][ks], s);
+                s = MFMA32(a1, kp[1][ks], s);
+                s = MFMA32(a0, kp[2][ks], s);
+                s = MFMA32(a1, kp[0][ks], s);
+                s = MFMA32(a0, kp[1][ks], s);
+                s = MFMA32(a0, kp[0][ks], s);
+            }
+            // register r: row 16 (r / 8) + 8 hh + r % 8 of the block
+            float p[16];
 #pragma unroll
-            for (int db = 0; db < 4; ++db) {
-                const bf16x8 a0 = RowMajor::by_col(qc, 0, half, db), a1 = RowMajor::by_col(qc, TILE_BYTES, half, db), a2 = RowMajor::by_col(qc, 2 * TILE_BYTES, half, db);
-                dk[db] = MFMA32(a2, ds.p[0], dk[db]);
-                dk[db] = MFMA32(a1, ds.p[1], dk[db]);
-                dk[db] = MFMA32(a0, ds.p[2], dk[db]);
-                dk[db] = MFMA32(a1, ds.p[0], dk[db]);
-                dk[db] = MFMA32(a0, ds.p[1], dk[db]);
-                dk[db] = MFMA32(a0, ds.p[0], dk[db]);
+            for (int r = 0; r < 16; r += 2) {
+                const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
+                // (The maximum takes a NaN to a probability of 0.  A row that saw a NaN or +inf has no gradient, see prep; where a row
+                // that has one meets an infinite key its score is -inf, which the pieces' products turn into NaN.)
+                p[r] = ex2(fmaxf(__builtin_fmaf(s[r], L.scale_log2, -x.x), -1e30f));
+                p[r + 1] = ex2(fmaxf(__builtin_fmaf(s[r + 1], L.scale_log2, -x.z), -1e30f));
+            }
+            // (no branch for the few causal tiles: it would cut the block the scheduler mixes matrix and vector work in)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[r] = (16 * (r >> 3) + 8 * hh + (r & 7) >= lim) ? p[r] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pw[j * 64] = make_float4(p[4 * j], p[4 * j + 1], p[4 * j + 2], p[4 * j + 3]);
+            const RowMajor::Cols qc = rq.cols(qt);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Pieces pp = split8(p + 8 * half);
+#pragma unroll
+                for (int db = 0; db < 4; ++db) {
+                    const bf16x8 a = RowMajor::by_col(qc, 3 * TILE_BYTES, half, db);
+                    sum[db] = MFMA32(a, pp.p[2], sum[db]);
+                    sum[db] = MFMA32(a, pp.p[1], sum[db]);
+                    sum[db] = MFMA32(a, pp.p[0], sum[db]);
+                }
+            }
+        }
+        next_unit();                                     // (the second waves' last unit)
+    } else {
+        bf16x8 vf[8];
+        wait_vm<0>();                                    // (each brought its own tile's)
+        {
+            const ValuesByKey<false> rv(lane);
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) vf[ks] = rv.get(lds_q + (RING - 1) * STAGE + tile * TILE_BYTES, ks);
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(vf[ks]));    // (read before the slot is requested again)
+        }
+        // A value that is not finite makes dp a NaN for every row of a block, and no zero takes the rows without a gradient out of
+        // dK again (a select per probability would: 24 us of 740 for a training step).  It is taken as zeros here, and its key's
+        // dK is a NaN at the end if a row with a gradient sees it.
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const uint4 u = __builtin_bit_cast(uint4, vf[ks]);
+            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bad |= (w[j] & 0x7F80u) == 0x7F80u || (w[j] & 0x7F800000u) == 0x7F800000u;
+            odd |= __builtin_amdgcn_ballot_w64(bad);
+            if (bad) vf[ks] = frag4(0, 0, 0, 0);
+        }
+        next_unit();                                     // (the first waves' first unit)
+        for (int rt = item.rt_begin; rt < item.rt_end; ++rt) {
+            next_unit();
+            const int row0 = tok0 + 32 * rb;
+            const unsigned qt = lds_q + slot * STAGE;
+            const float4 *st = reinterpret_cast<const float4 *>(&s_stat[slot][8 * hh]);
+            const float4 *const pr = s_p + odd_unit * (4 * P_BYTES / 16);
+            if (--left == 0) { ++rb; left = g; }
+            slot = slot + 1 == RING ? 0 : slot + 1;
+            odd_unit ^= 1;
+            if (!active || (self && key0 > row0 + 31)) continue;
+            f32x16 dp;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dp[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) dp = MFMA32(rq.by_row(qt + 3 * TILE_BYTES, ks), vf[ks], dp);
+            float w[16];
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                const float4 x = st[(r >> 3) * 8 + ((r & 7) >> 1)];
+                w[r] = dp[r] - x.y;
+                w[r + 1] = dp[r + 1] - x.w;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 p = pr[j * 64];
+                w[4 * j] *= p.x; w[4 * j + 1] *= p.y; w[4 * j + 2] *= p.z; w[4 * j + 3] *= p.w;
+            }
+            const RowMajor::Cols qc = rq.cols(qt);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const Pieces ds = split8(w + 8 * half);
+#pragma unroll
+                for (int db = 0; db < 4; ++db) {
+                    const bf16x8 a0 = RowMajor::by_col(qc, 0, half, db), a1 = RowMajor::by_col(qc, TILE_BYTES, half, db), a2 = RowMajor::by_col(qc, 2 * TILE_BYTES, half, db);
+                    sum[db] = MFMA32(a2, ds.p[0], sum[db]);
+                    sum[db] = MFMA32(a1, ds.p[1], sum[db]);
+                    sum[db] = MFMA32(a0, ds.p[2], sum[db]);
+                    sum[db] = MFMA32(a1, ds.p[0], sum[db]);
+                    sum[db] = MFMA32(a0, ds.p[1], sum[db]);
+                    sum[db] = MFMA32(a0, ds.p[0], sum[db]);
+                }
             }
         }
     }
-    wait_vm<0>();
     ring_barrier();                                      // the ring is free: each wave turns its sums round in 17 KB of it
     if (!active) return;
     if (odd != 0) {
@@ -659,40 +871,37 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) dk[db][r] = __builtin_nanf("");
+                for (int r = 0; r < 16; ++r) sum[db][r] = __builtin_nanf("");
     }
-    float *stg = reinterpret_cast<float *>(&s_q[0][0]) + wave * (32 * (PC_D + 4));
+    float *stg = reinterpret_cast<float *>(&s_mem[wave * TURN]);
     const int valid = flags & 0xFF;
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
+    for (int db = 0; db < 2; ++db)
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int dim = 32 * db + 8 * q4 + 4 * hh;
+            float lo[4], hi[4];
+            if (is_dk) {                                 // dK back to the stored frame
+                const float4 c0 = rs[dim >> 1], c1 = rs[(dim >> 1) + 1];
+                const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sx[4] = {c0.y, c0.w, c1.y, c1.w};
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int dim = 32 * db + 8 * q4 + 4 * hh;
-                float lo[4], hi[4];
-                if (which == 0) {                        // dK back to the stored frame
-                    const float4 c0 = rs[dim >> 1], c1 = rs[(dim >> 1) + 1];
-                    const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sx[4] = {c0.y, c0.w, c1.y, c1.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float a = dk[db][4 * q4 + i] * B.scale, b = dk[db + 2][4 * q4 + i] * B.scale;
-                        lo[i] = a * cx[i] + b * sx[i]; hi[i] = b * cx[i] - a * sx[i];
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { lo[i] = dv[db][4 * q4 + i]; hi[i] = dv[db + 2][4 * q4 + i]; }
+                for (int i = 0; i < 4; ++i) {
+                    const float a = sum[db][4 * q4 + i] * B.scale, b = sum[db + 2][4 * q4 + i] * B.scale;
+                    lo[i] = a * cx[i] + b * sx[i]; hi[i] = b * cx[i] - a * sx[i];
                 }
-                *reinterpret_cast<float4 *>(stg + n * (PC_D + 4) + dim) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-                *reinterpret_cast<float4 *>(stg + n * (PC_D + 4) + dim + 64) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { lo[i] = sum[db][4 * q4 + i]; hi[i] = sum[db + 2][4 * q4 + i]; }
             }
-        // (a wave's own LDS writes and reads are ordered; the other waves use other parts)
-        float *out = (which == 0 ? B.d_k : B.d_v) + ((int64_t)slot0 * L.n_kv_heads + kh) * PC_D + lane;
-        for (int k = 0; k < valid; ++k) {
-            const int64_t at = (int64_t)k * L.n_kv_heads * PC_D;
-            unsafeAtomicAdd(out + at, stg[k * (PC_D + 4) + lane]);
-            unsafeAtomicAdd(out + at + 64, stg[k * (PC_D + 4) + lane + 64]);
+            *reinterpret_cast<float4 *>(stg + n * (PC_D + 4) + dim) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+            *reinterpret_cast<float4 *>(stg + n * (PC_D + 4) + dim + 64) = make_float4(hi[0], hi[1], hi[2], hi[3]);
         }
+    // (a wave's own LDS writes and reads are ordered; the other waves use other parts)
+    float *out = (is_dk ? B.d_k : B.d_v) + ((int64_t)slot0 * L.n_kv_heads + kh) * PC_D + lane;
+    for (int k = 0; k < valid; ++k) {
+        const int64_t at = (int64_t)k * L.n_kv_heads * PC_D;
+        unsafeAtomicAdd(out + at, stg[k * (PC_D + 4) + lane]);
+        unsafeAtomicAdd(out + at + 64, stg[k * (PC_D + 4) + lane + 64]);
     }
 }
 
@@ -702,8 +911,8 @@ void pc_launch_attend_bwd_bf16(const PcLaunch &L, const PcBwd &B, int n_items, i
     const dim3 blocks((unsigned)B.n_rb, (unsigned)L.n_q_heads);
     pc_bwd_prep_kernel<<<blocks, 256, 0, st>>>(L, B);
     const unsigned rows = (unsigned)n_items * L.n_kv_heads;
-    pc_bwd_rows_kernel<false><<<rows, 512, 0, st>>>(L, B);
-    pc_bwd_rows_kernel<true><<<rows, 512, 0, st>>>(L, B);
+    pc_bwd_delta_kernel<<<rows, 512, 0, st>>>(L, B);
+    pc_bwd_dq_kernel<<<2 * rows, 512, 0, st>>>(L, B);
     pc_bwd_finish_kernel<<<blocks, 256, 0, st>>>(L, B);
-    if (n_key_items > 0) pc_bwd_keys_kernel<<<(unsigned)n_key_items * L.n_kv_heads, 256, 0, st>>>(L, B);
+    if (n_key_items > 0) pc_bwd_keys_kernel<<<(unsigned)n_key_items * L.n_kv_heads, 512, 0, st>>>(L, B);
 }
