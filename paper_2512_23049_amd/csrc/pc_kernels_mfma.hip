@@ -72,7 +72,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 struct DecCall { int n_q, q_off, self_lim0, n_splits, split, part_off, part_wide; };      // self_lim0: own tokens before the query rows
 template <bool ONE, int NW, class Describe, class SegRot, class QRot>
 __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd, int kh, int tile, int tile_stop, Describe describe, SegRot seg_rot, QRot q_rot,
-                                            float (&s_acc)[NW][PC_D][17], float (&s_m)[NW][16], float (&s_l)[NW][16])
+                                            float (&s_acc)[NW][16][PC_D + 4], float (&s_m)[NW][16], float (&s_l)[NW][16])
 {
     const int g = L.n_q_heads / L.n_kv_heads;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -200,10 +200,11 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
     if (a == 0) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
+    int at = threadIdx.x;
+    asm volatile("" : "+v"(at));                         // (the address is made here: in front of the loop its registers would be spilled)
+    f32x4 *const to = reinterpret_cast<f32x4 *>(&s_acc[at >> 6][at & 15][(at >> 4 & 3) * 4]);      // dims 16 db + 4 a + 0..3 of column n
 #pragma unroll
-    for (int db = 0; db < 8; ++db)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s_acc[wave][16 * db + 4 * a + r][n] = acc[db][r];
+    for (int db = 0; db < 8; ++db) to[4 * db] = acc[db];
     __syncthreads();
     for (int idx = threadIdx.x; idx < n_cols * (PC_D / 2); idx += 64 * NW) {
         const int col = idx / (PC_D / 2), d = 2 * (idx - col * (PC_D / 2));
@@ -215,8 +216,9 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 const float sc = (s_m[w][col] > -INFINITY) ? exp2f(s_m[w][col] - mm) : 0.f;
-                o0 += s_acc[w][d][col] * sc;
-                o1 += s_acc[w][d + 1][col] * sc;
+                const float2 x = *reinterpret_cast<const float2 *>(&s_acc[w][col][d]);
+                o0 += x.x * sc;
+                o1 += x.y * sc;
                 l += s_l[w][col] * sc;
             }
         }
@@ -244,7 +246,7 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
 
 __global__ __launch_bounds__(256, 2) void pc_decode_bf16_kernel(PcLaunch L)
 {
-    __shared__ float s_acc[4][PC_D][17];
+    __shared__ __attribute__((aligned(16))) float s_acc[4][16][PC_D + 4];
     __shared__ float s_m[4][16], s_l[4][16];
 
     const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
@@ -316,15 +318,19 @@ __device__ __forceinline__ void merge_cols(const PcLaunch &L, const DecCall &cd,
             for (int k = 0; k < 2; ++k) { o[4 * k] += v[u][k].x * w; o[4 * k + 1] += v[u][k].y * w; o[4 * k + 2] += v[u][k].z * w; o[4 * k + 3] += v[u][k].w * w; }
         }
     }
-    for (int mask = 16; mask < 16 * SL; mask <<= 1) {
-        const float m_o = __shfl_xor(m, mask), l_o = __shfl_xor(l, mask);
-        const float m_c = fmaxf(m, m_o);
-        const float w_own = m > -INFINITY ? exp2f(m - m_c) : 0.f, w_oth = m_o > -INFINITY ? exp2f(m_o - m_c) : 0.f;
-        l = l * w_own + l_o * w_oth;
+    // parts 0+1 and 2+3 (16 lanes apart), then the two halves (32 apart); the swaps give both values of a pair to both lanes
+    auto fold = [&](auto swap) __attribute__((always_inline)) {
+        const auto mm = swap(m), ll = swap(l);
+        m = fmaxf(mm.x, mm.y);
+        const float w0 = mm.x > -INFINITY ? exp2f(mm.x - m) : 0.f, w1 = mm.y > -INFINITY ? exp2f(mm.y - m) : 0.f;
+        l = ll.x * w0 + ll.y * w1;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o[j] = o[j] * w_own + __shfl_xor(o[j], mask) * w_oth;
-        m = m_c;
-    }
+        for (int j = 0; j < 8; ++j) { const auto x = swap(o[j]); o[j] = x.x * w0 + x.y * w1; }
+    };
+    if (SL > 1) fold([](float x) { const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                                   return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1])); });
+    if (SL > 2) fold([](float x) { const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                                   return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1])); });
     if (sg != 0 || col >= n_cols) return;
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const int64_t Rr = (int64_t)(cd.q_off + r) * L.n_q_heads + h;
@@ -347,7 +353,7 @@ template <int BYTES> struct PcArgs { uint4 w[BYTES / 16]; };
 template <int BYTES>
 __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(const PcArgs<BYTES> blob, PcLaunch L, PcOne O)
 {
-    __shared__ float s_acc[ONE_WAVES][PC_D][17];
+    __shared__ __attribute__((aligned(16))) float s_acc[ONE_WAVES][16][PC_D + 4];
     __shared__ float s_m[ONE_WAVES][16], s_l[ONE_WAVES][16];
     __shared__ float2 s_rot[PC_ONE_SEGS + 16][PC_D / 2]; // (cos, sin) of the split's messages, then of the query rows' positions
     __shared__ int s_last;
@@ -381,8 +387,7 @@ __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(c
     }
     const int tiles = (m_len + PC_TILE - 1) / PC_TILE;
     int m_tile = tiles;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
+    for (int off = 1; off < item.n_seg; off <<= 1) {
         const int x = __shfl_up(m_tile, off);
         if (lane >= off) m_tile += x;
     }
