@@ -55,6 +55,10 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         pc_launch_decode_one_bf16(P.one_blob, P.one_bytes, L, P.one, st);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
+        if (P.one_slot) {                                // the ring slot is free again once the launch is done
+            PC_HIP(c, hipEventRecord(P.one_slot->ev, st));
+            P.one_slot->used = true;
+        }
         return PC_OK;
     }
     if (c->cfg.dtype == PC_F32) {

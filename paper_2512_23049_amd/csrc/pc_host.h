@@ -163,7 +163,7 @@ struct Planned {
     // The gradient of a bf16 batch (set backward before planning): its launches, each over a run of row blocks
     bool backward = false;
     // A decode batch that goes to one launch (one_bytes > 0): nothing was staged or launched for it yet
-    PcArgBlob one_blob; size_t one_bytes = 0; PcOne one;
+    PcArgBlob one_blob; size_t one_bytes = 0; PcOne one{}; StageSlot *one_slot = nullptr;      // (one_slot: its lists are in the pinned ring)
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
     int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)

@@ -127,7 +127,7 @@ struct PcBwdKeyItem {
     int32_t pad[3];
 };
 
-// ---- a decode batch in one launch: its lists travel in the kernel's arguments, calls first ----
+// ---- a decode batch in one launch: its lists, calls first, travel in the kernel's arguments or lie in pinned memory ----
 struct PcOneCall {
     uint16_t seg_off, n_seg;  // its entries of the (msg, start) list; the new message is the last one if self_len > 0
     uint16_t n_q, n_splits;
@@ -138,8 +138,8 @@ struct PcOneCall {
     int32_t tok;              // row of the step's tokens that is the new message's last token, -1: none
 };
 struct PcOneItem {
-    uint16_t call_split;      // call | split << 8
-    uint16_t seg0;            // the call's entry that owns the split's first tile
+    uint32_t call : 12, split : 8;
+    uint32_t seg0 : 12;       // the call's entry that owns the split's first tile
     uint32_t tile0 : 24;      // the call's tiles before that entry
     uint32_t n_seg : 8;       // entries the split's tiles come from
 };
@@ -226,7 +226,8 @@ struct PcOne {
     const double *inv_freq;
     const uint16_t *tok_k, *tok_v;    // [tokens][H_kv][D] rows the step appends
     uint32_t     *counters;           // [call][H_kv] splits that are done: zero between launches
-    int32_t       off_sel, off_q_pos, off_items;      // of the lists in the arguments, in bytes
+    const void   *lists;              // pinned host memory, or null: in the arguments
+    int32_t       off_sel, off_q_pos, off_items;      // within the lists, in bytes
     int32_t       n_items;
 };
 

@@ -89,7 +89,7 @@ void pc_launch_gather(const PcLaunch &L, const PcGatherItem *items, int n_items,
 
 // bf16 MFMA kernels (D = 128)
 void pc_launch_decode_bf16(const PcLaunch &L, int n_items, hipStream_t st);
-// a batch of decode calls whose lists (blob: bytes of them) fit a kernel's arguments: plan, token append, attention and merge in one launch
+// a batch of decode calls: plan, token append, attention and merge in one launch (blob: bytes of its lists, unless O.lists has them)
 void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaunch &L, const PcOne &O, hipStream_t st);
 void pc_launch_prefill_bf16(const PcLaunch &L, int n_items, bool packed, hipStream_t st);   // packed: the items of calls that gathered
 

@@ -339,9 +339,10 @@ __device__ __forceinline__ void merge_cols(const PcLaunch &L, const DecCall &cd,
     if (L.lse && sub == 0) L.lse[Rr] = l > 0.f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-// A batch of few decode calls in ONE launch: no plan builder in front, no merge behind.  Such a batch is a chain of latencies:
+// A batch of decode calls in ONE launch: no plan builder in front, no merge behind.  Such a batch is a chain of latencies:
 // as three launches, 4 calls over 700 tokens took 4.2 us of plan, 8 of attention and 3.6 of merge, most of each the start and
-// the end of a kernel; one launch takes 12.  The lists come in the kernel's arguments.  Every wave looks the split's messages
+// the end of a kernel; one launch takes 11.  The lists come in the kernel's arguments, or are read in pinned memory (a few
+// hundred bytes a workgroup; the plan builder did the same, then copied them for the others).  Every wave looks the split's messages
 // up in the device table itself, one a lane (the host says which entry owns the split's first tile), and finds a tile's place
 // by a ballot over them; the rotations of the split's messages and query rows are shared out over the waves and computed into
 // LDS while the first tiles are on their way (fp64, rounded to fp32, as in the plan builder).  A decode step's new token is
@@ -350,6 +351,7 @@ __device__ __forceinline__ void merge_cols(const PcLaunch &L, const DecCall &cd,
 // and workgroup -- 57 GB/s is what a compute unit draws with these loads, with four waves or eight --, 1.5 to combine the
 // waves, 2 to publish a part and learn that it is the last, 2.5 to merge.)
 template <int BYTES> struct PcArgs { uint4 w[BYTES / 16]; };
+template <> struct PcArgs<0> {};
 template <int BYTES>
 __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(const PcArgs<BYTES> blob, PcLaunch L, PcOne O)
 {
@@ -362,10 +364,10 @@ __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(c
     typedef int i32x2 __attribute__((ext_vector_type(2)));
     typedef int i32x8 __attribute__((ext_vector_type(8)));
     typedef const __attribute__((address_space(4))) i32x2 *KernArg2;
-    const KernArg args = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+    const KernArg args = BYTES ? (KernArg)__builtin_amdgcn_kernarg_segment_ptr() : (KernArg)(uintptr_t)O.lists;
     const int kh = blockIdx.x % L.n_kv_heads;            // consecutive workgroups (one per XCD) take different KV heads
     const PcOneItem item = __builtin_bit_cast(PcOneItem, ((KernArg2)(args + O.off_items))[blockIdx.x / L.n_kv_heads]);
-    const int call = item.call_split & 0xFF, split = item.call_split >> 8;
+    const int call = item.call, split = item.split;
     const PcOneCall cd = __builtin_bit_cast(PcOneCall, ((const __attribute__((address_space(4))) i32x8 *)args)[call]);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile_begin = split * cd.chunk, tile_end = min(cd.n_tiles, tile_begin + cd.chunk);
@@ -463,7 +465,8 @@ void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaun
         __builtin_memcpy(args.w, blob.w, sizeof args < bytes ? sizeof args : bytes);
         pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(args, L, O);
     };
-    if (bytes <= 768) launch(PcArgs<768>());
+    if (O.lists) pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(PcArgs<0>(), L, O);
+    else if (bytes <= 768) launch(PcArgs<768>());
     else launch(PcArgs<PC_ARG_BYTES>());
 }
 

@@ -212,6 +212,10 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
         int j = i;
         while (j < n_calls && res[j].n_q == 1 && j - i < rows_max) ++j;
         const int n_rows = j - i;
+        // (the union holds each call's list: calls that list less than SHARE_MIN times the longest list cannot take this walk)
+        int64_t sum_tiles = 0, longest = 0;
+        for (int r = i; r < j; ++r) { sum_tiles += res[(size_t)r].tiles; longest = std::max<int64_t>(longest, res[(size_t)r].tiles); }
+        if (c->decode_sharing != 2 && (double)sum_tiles < SHARE_MIN * (double)longest) { i = j; continue; }
         // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
         const size_t usegs_max = ((size_t)1 << 19) / (size_t)n_rows;
         usegs.clear(); pos.clear(); extra.clear();
@@ -581,28 +585,37 @@ static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vec
     }
 }
 
-// A batch of nothing but decode calls that walk their own lists goes to one launch (pc_decode_one_bf16_kernel) when its lists
-// fit the kernel's arguments, no split takes its tiles from more messages than a wave has lanes, and every token of a decode
-// step is the last one of exactly one call's new message.  (Not where the splits are tuned by hand.)  Fills P.one_*; false: the
-// plan builder's way.
+// A batch of nothing but decode calls that walk their own lists goes to one launch (pc_decode_one_bf16_kernel) when no split takes
+// its tiles from more messages than a wave has lanes and every token of a decode step is the last one of exactly one call's new
+// message.  Not where the splits are tuned by hand, nor where lists or tables might not fit what pc_attend_static has, so that
+// it refuses what it refused.  rc != PC_OK: an error; else false: the plan builder's way.  Fills P.one_*.
+// (us a step of 64 calls over 9 messages each: 136 the plan builder's way, 131; of 5 over 220: 141 and 93.  Batches that share
+// enough stay with the shared walk: 14 calls over 27 messages each of 40: 38 us there, 47 in one launch of their own walks.)
 // Splits: those with the least of ONE_TILE us a tile for each round of 256 workgroups, plus, if there is more than one, a merge
 // of ONE_MERGE and ONE_PART a workgroup (us; 1 to 16 calls over 8 to 400 tiles, 1 to 32 splits: this choice is within 5 % of the
 // best of them.  One call over 200 tiles: 63 us unsplit, 13.6 in 32; eight over 16: 11.7 unsplit, 13.3 in 2 or 4).
 constexpr double ONE_TILE = 0.28, ONE_MERGE = 2.0, ONE_PART = 0.009;
-static bool plan_one(pc_cache *c, Planned &P)
+static bool plan_one(pc_cache *c, Planned &P, int32_t &rc)
 {
     const int n_calls = (int)P.res.size(), g = c->g, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads;
-    if (c->decode_tiles_per_split != 0 || n_calls > 255 || n_calls * H_kv > PC_ONE_COUNTERS || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
-    size_t n_seg = 0, n_q = 0;
+    if (c->decode_tiles_per_split != 0 || n_calls > 4095 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
+    size_t n_seg = 0, n_q = 0, n_tiles = 0;
     for (const Resolved &r : P.res) {
-        if (r.n_q * g > 16 || r.tiles >= 1 << 24) return false;
+        if (r.n_q * g > 16 || r.tiles >= 1 << 24 || r.sel.size() > 4094) return false;
+        n_tiles += (size_t)r.tiles;
         n_seg += r.sel.size() + (r.self_msg >= 0 ? 1 : 0);
         n_q += (size_t)r.n_q;
     }
+    {   // at most what the plan builder's way stages and keeps under the plain rule
+        const size_t wgs = (size_t)(n_calls * H_kv) + 256, staged = 64 * (size_t)n_calls + 8 * n_seg + 20 * n_q + 32 * ((size_t)n_calls + 256) + 16 * P.tok_items.size();
+        const size_t tables = n_seg * 548 + n_q * (1536 + 4 * (size_t)H_q) + n_tiles * sizeof(PcTile) + wgs * 16 * 264;
+        if (staged > HOST_READ_BYTES || staged + tables > PC_STATIC_WS_BYTES - (1 << 20)) return false;
+    }
+    const int most = std::max(1, std::min(MAX_SPLITS, 512 / (n_calls * H_kv)));      // (two rounds; further splits never pay)
     auto splits_of = [&](int T) {
         int best = 1;
         double best_us = 1e30;
-        for (int ns = 1; ns <= std::min(MAX_SPLITS, std::max(1, T / 4)); ++ns) {
+        for (int ns = 1; ns <= std::min(most, std::max(1, T / 4)); ++ns) {
             const int wgs = n_calls * H_kv * ns;
             const double us = ONE_TILE * ((T + ns - 1) / ns) * ((wgs + 255) / 256) + (ns > 1 ? ONE_MERGE + ONE_PART * wgs : 0.0);
             if (us < best_us) { best_us = us; best = ns; }
@@ -611,24 +624,33 @@ static bool plan_one(pc_cache *c, Planned &P)
         return std::max(1, (T + chunk - 1) / chunk);
     };
     size_t n_items = 0;
-    for (const Resolved &r : P.res) n_items += (size_t)splits_of(r.tiles);
+    std::vector<int> splits((size_t)n_calls);
+    for (int i = 0; i < n_calls; ++i) n_items += (size_t)(splits[(size_t)i] = splits_of(P.res[(size_t)i].tiles));
     const size_t off_sel = sizeof(PcOneCall) * (size_t)n_calls, off_items = off_sel + sizeof(int2) * n_seg;
     const size_t off_q_pos = off_items + sizeof(PcOneItem) * n_items, bytes = off_q_pos + sizeof(int32_t) * n_q;
-    if (bytes > PC_ARG_BYTES) return false;
+    if (n_items > (size_t)n_calls && n_calls * H_kv > PC_ONE_COUNTERS) return false;
+    std::vector<int32_t> tok((size_t)n_calls, -1);
     if (!P.tok_items.empty()) {
-        const uint32_t epoch = new_marks(c);             // value: how many calls have it as their new message and no token for it yet
-        for (const Resolved &r : P.res)
-            if (r.self_msg >= 0) {
-                pc_cache::Mark &mk = c->marks[(size_t)r.self_msg];
-                mk = pc_cache::Mark{epoch, mk.epoch == epoch ? 2 : 1};
+        const uint32_t epoch = new_marks(c);             // value: the call that has it as its new message and no token for it yet, -1: several
+        for (int i = 0; i < n_calls; ++i)
+            if (P.res[(size_t)i].self_msg >= 0) {
+                pc_cache::Mark &mk = c->marks[(size_t)P.res[(size_t)i].self_msg];
+                mk = pc_cache::Mark{epoch, mk.epoch == epoch ? -1 : i};
             }
-        for (const PcTokenItem &t : P.tok_items) {
+        for (size_t k = 0; k < P.tok_items.size(); ++k) {
+            const PcTokenItem &t = P.tok_items[k];
             pc_cache::Mark &mk = c->marks[(size_t)t.msg];
-            if (mk.epoch != epoch || mk.value != 1 || t.new_len != c->msgs[(size_t)t.msg].len) return false;
-            mk.value = 0;
+            if (mk.epoch != epoch || mk.value < 0 || t.new_len != c->msgs[(size_t)t.msg].len) return false;
+            tok[(size_t)mk.value] = (int32_t)k;
+            mk.value = -1;
         }
     }
     char *h = (char *)P.one_blob.w;
+    if (bytes > PC_ARG_BYTES) {                          // (a slot of the ring holds four times HOST_READ_BYTES: nothing is allocated)
+        rc = pc_stage_acquire(c, bytes, &P.one_slot);
+        if (rc != PC_OK) return false;
+        h = (char *)P.one_slot->host;
+    }
     PcOneCall *calls = (PcOneCall *)h;
     int2 *sel = (int2 *)(h + off_sel);
     int32_t *q_pos = (int32_t *)(h + off_q_pos);
@@ -638,11 +660,11 @@ static bool plan_one(pc_cache *c, Planned &P)
     for (int i = 0; i < n_calls; ++i) {
         Resolved &r = P.res[(size_t)i];
         sort_by_slot(c, r);                              // (as in pc_plan_and_stage)
-        const int T = r.tiles, ns = splits_of(T), n_sel = (int)r.sel.size(), n = n_sel + (r.self_msg >= 0 ? 1 : 0);
+        const int T = r.tiles, ns = splits[(size_t)i], n_sel = (int)r.sel.size(), n = n_sel + (r.self_msg >= 0 ? 1 : 0);
         PcOneCall &oc = calls[i];
         oc.seg_off = (uint16_t)seg_off; oc.n_seg = (uint16_t)n; oc.n_q = (uint16_t)r.n_q; oc.n_splits = (uint16_t)ns;
         oc.q_off = q_off; oc.self_len = r.self_msg >= 0 ? r.self_len : 0; oc.n_tiles = T; oc.chunk = std::max(1, (T + ns - 1) / ns);
-        oc.part_off = (int32_t)part_rows; oc.tok = -1;
+        oc.part_off = (int32_t)part_rows; oc.tok = tok[(size_t)i];
         if (ns > 1) part_rows += (int64_t)ns * r.n_q;
         std::copy(r.sel.begin(), r.sel.end(), sel + seg_off);
         if (r.self_msg >= 0) sel[seg_off + n_sel] = make_int2(r.self_msg, r.self_start);
@@ -654,20 +676,19 @@ static bool plan_one(pc_cache *c, Planned &P)
             int last = e;
             for (int end = before + (n > 0 ? tiles_of(e) : 0); last + 1 < n && end < std::min(T, (s + 1) * oc.chunk); end += tiles_of(++last)) {}
             const int count = n > 0 ? last - e + 1 : 0;
-            if (count > PC_ONE_SEGS) return false;
+            if (count > PC_ONE_SEGS) { P.one_slot = nullptr; return false; }
             PcOneItem it{};
-            it.call_split = (uint16_t)(i | s << 8); it.seg0 = (uint16_t)e; it.tile0 = (uint32_t)before; it.n_seg = (uint32_t)count;
+            it.call = (uint32_t)i; it.split = (uint32_t)s; it.seg0 = (uint32_t)e; it.tile0 = (uint32_t)before; it.n_seg = (uint32_t)count;
             *items++ = it;
         }
         seg_off += n; q_off += r.n_q;
     }
-    for (size_t k = 0; k < P.tok_items.size(); ++k)
-        for (int i = 0; i < n_calls; ++i) if (P.res[(size_t)i].self_msg == P.tok_items[k].msg) calls[i].tok = (int32_t)k;
     P.lay = PlanLayout{};
     P.lay.part_ml = align_up(sizeof(float) * (size_t)part_rows * H_q * c->D, 256);       // (part_o comes first)
     P.lay.total = P.lay.part_ml + sizeof(float) * 2 * (size_t)part_rows * H_q;
     P.total_seg = seg_off;
     P.one_bytes = bytes;
+    P.one.lists = P.one_slot ? P.one_slot->host : nullptr;
     P.one.off_sel = (int32_t)off_sel; P.one.off_q_pos = (int32_t)off_q_pos; P.one.off_items = (int32_t)off_items; P.one.n_items = (int32_t)n_items;
     P.one.table = c->table_dev; P.one.inv_freq = c->inv_freq_dev; P.one.counters = c->counters_dev;
     P.one.tok_k = (const uint16_t *)P.tok_k; P.one.tok_v = (const uint16_t *)P.tok_v;
@@ -702,15 +723,17 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         for (int i = 0, o = 0; i < n_calls; ++i) { q_offs[(size_t)i] = o; o += P.res[(size_t)i].n_q; }
         plan_shared(c, P.res, q_offs, g, sp);
     }
-    if (want_items && bf16 && !c->host_only && sp.groups.empty() && plan_one(c, P)) {
+    int32_t rc = PC_OK;
+    if (want_items && bf16 && !c->host_only && sp.groups.empty() && plan_one(c, P, rc)) {
         if (!P.fixed_ws) {
-            const int32_t rc = pc_ensure_ws(c, P.lay.total, st);
+            rc = pc_ensure_ws(c, P.lay.total, st);
             if (rc != PC_OK) return rc;
         } else if (P.lay.total > P.fixed_cap)
             return pc_fail(c, PC_ERR_NO_SPACE, "attend: this batch needs %zu bytes of workspace, the fixed one holds %zu", P.lay.total, P.fixed_cap);
         P.ws = P.fixed_ws ? P.fixed_ws : c->ws;
         return PC_OK;
     }
+    if (rc != PC_OK) return rc;
     // first pass: how many prefill groups without splitting (to decide on KV splits)
     int64_t pre_groups = 0, dec_groups = 0;
     if (want_items && bf16)
@@ -946,7 +969,6 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
     if (c->host_only) return PC_OK;
 
-    int32_t rc = PC_OK;
     if (P.fixed_ws) {                                    // nothing may be allocated: the plan fits or the call fails
         if (P.lay.total > P.fixed_cap)
             return pc_fail(c, PC_ERR_NO_SPACE, "attend: this batch needs %zu bytes of workspace, the fixed one holds %zu",

@@ -1,4 +1,4 @@
-"""Decode batches that go to one launch (their lists fit its arguments), at the sizes where it can go wrong: a split of one tile,
+"""Decode batches that go to one launch (their lists in its arguments, or for 60 calls in pinned memory), at the sizes where it can go wrong: a split of one tile,
 waves without a tile, calls with several rows, nothing to see, the same message twice, as many messages in a split as a wave has
 lanes and one more (then the plan builder's way), against the oracle to the bf16 bars of test_gpu_parity and against the same
 calls the plan builder's way (which a split size set by hand selects).  Decode steps: the token it appends is the one
@@ -45,7 +45,7 @@ def check(ks, vs, calls, q, got, lse):
 
 
 @pytest.mark.parametrize("h_q,h_kv,n_q", [(8, 2, 1), (8, 1, 2), (32, 2, 1), (2, 2, 13), (12, 4, 3)])
-@pytest.mark.parametrize("lens,n_calls", [([1], 1), ([31, 33, 32], 2), ([20] * 63, 3), ([20] * 64, 1), ([2100], 1), ([2100, 900, 5], 5), ([9] * 70, 1)])
+@pytest.mark.parametrize("lens,n_calls", [([1], 1), ([31, 33, 32], 2), ([20] * 63, 3), ([20] * 64, 1), ([2100], 1), ([2100, 900, 5], 5), ([9] * 70, 1), ([70, 33], 60)])
 def test_one_launch(h_q, h_kv, n_q, lens, n_calls):
     import torch
     from paper_2512_23049_amd import harness as hip
