@@ -114,3 +114,35 @@ def test_step_appends_its_tokens(h_q, h_kv, first):
     assert (stores[0][1] == stores[1][1]).all()
     assert np.abs(stores[0][0] - stores[1][0]).max() <= 2.0 ** -7 * np.abs(stores[1][0]).max()
     assert torch.allclose(results[0][0].float(), results[1][0].float(), atol=2e-2) and torch.allclose(results[0][1], results[1][1], atol=2e-2)
+
+
+@pytest.mark.parametrize("n_calls,tokens", [(1, 6000), (4, 700)])
+def test_replays_of_a_captured_call(n_calls, tokens):
+    """pc_attend_static in a HIP graph (lists in the arguments, splits that the launch merges itself): every replay, with eager calls
+    on other queries in between, returns the eager result for the queries it finds."""
+    import torch
+    from paper_2512_23049_amd import harness as hip
+    h_q, h_kv = 32, 8
+    rng = np.random.default_rng(tokens)
+    ks, vs, cache, arena = fill([tokens // 2, tokens // 2 + 5] + [3] * n_calls, h_q, h_kv, rng)
+    calls = [Call([(0, 40 * i), (1, tokens)], 2 + i, 2 * tokens, 1, None) for i in range(n_calls)]
+    queries = [hip.to_device(rnd(rng, n_calls, h_q, D), "bf16") for _ in range(4)]
+    q, out, lse = torch.empty_like(queries[0]), torch.empty_like(queries[0]), torch.empty((n_calls, h_q), device="cuda:0")
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        cache.attend_static(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr(), stream.cuda_stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        cache.attend_static(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr(), stream.cuda_stream)
+    for x in queries:
+        want, want_lse = torch.empty_like(out), torch.empty_like(lse)
+        cache.attend(calls, x.data_ptr(), want.data_ptr(), want_lse.data_ptr())
+        torch.cuda.synchronize()
+        q.copy_(x)
+        out.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
+    cache.close()
