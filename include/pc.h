@@ -192,8 +192,9 @@ int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, cons
  * process ends, and the function calls no hipMalloc, hipFree or other allocating routine.  A batch whose workspace exceeds
  * that size with its calls split by the plain rule (at least 16 tiles of 32 keys a split, as many splits as bring the batch
  * to 256 workgroups), or whose staged descriptors then exceed one slot of the cache's pinned staging ring (1 MiB), is rejected with
- * PC_ERR_NO_SPACE before anything is enqueued (pc_last_error names both sizes).  Kernel timing (pc_profile_enable)
- * does not cover it.  Every cache on a GPU shares that GPU's array, which keeps the last call's contents (nothing
+ * PC_ERR_NO_SPACE before anything is enqueued (pc_last_error names both sizes).  Under capture the graph holds the
+ * whole call: lists too long for one kernel's arguments (about 3.5 KB) are recorded as further small launches that
+ * bring them, so that a replay depends on no host memory.  Kernel timing (pc_profile_enable) does not cover it.  Every cache on a GPU shares that GPU's array, which keeps the last call's contents (nothing
  * in it has to start at zero: every call writes what it reads): calls on one GPU that overlap in time - two
  * streams, or two caches - race; order them on one stream or with events. */
 #define PC_STATIC_WS_BYTES ((size_t)32 << 20)

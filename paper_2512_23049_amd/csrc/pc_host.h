@@ -164,6 +164,7 @@ struct Planned {
     bool backward = false;
     // A decode batch that goes to one launch (one_bytes > 0): nothing was staged or launched for it yet
     PcArgBlob one_blob; size_t one_bytes = 0; PcOne one{}; StageSlot *one_slot = nullptr;      // (one_slot: its lists are in the pinned ring)
+    std::vector<char> recorded;                          // staged lists of a call that is recorded into a graph (see pc_recorded)
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
     int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)
@@ -183,6 +184,7 @@ extern "C" int32_t pc_append_token_items(pc_cache *c, const std::vector<int32_t>
                                          std::vector<PcTokenItem> *defer);
 int32_t pc_ensure_ws(pc_cache *c, size_t bytes, hipStream_t st);
 int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out);
+bool pc_recorded(hipStream_t st);
 extern "C" int32_t pc_stage_items(pc_cache *c, const void *items, size_t bytes, hipStream_t st);
 // pc_attend.hip: the address, on the current device, of the library's fixed scratch array (looked up once per device)
 int32_t pc_static_scratch(void **ptr, size_t *bytes);

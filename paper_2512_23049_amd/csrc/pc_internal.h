@@ -226,7 +226,7 @@ struct PcOne {
     const double *inv_freq;
     const uint16_t *tok_k, *tok_v;    // [tokens][H_kv][D] rows the step appends
     uint32_t     *counters;           // [call][H_kv] splits that are done: zero between launches
-    const void   *lists;              // pinned host memory, or null: in the arguments
+    const void   *lists;              // in pinned host memory or the workspace, or null: in the arguments
     int32_t       off_sel, off_q_pos, off_items;      // within the lists, in bytes
     int32_t       n_items;
 };

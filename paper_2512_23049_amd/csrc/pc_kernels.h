@@ -59,6 +59,9 @@ void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes,
                               int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
                               float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, hipStream_t st);
 
+// `bytes` of host memory to dst (16-byte aligned) through kernels' arguments, read before the function returns
+void pc_launch_store_args(const void *host, size_t bytes, void *dst, hipStream_t st);
+
 void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, int n_seg, int64_t n_kv,
                              int32_t *kv_slot, int32_t *kv_pos, hipStream_t st);
 

@@ -702,6 +702,25 @@ void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel,
                                                                    (const uint4 *)staged, (uint4 *)ws, (int)n16, (int)grid);
 }
 
+// Lists of a call that is recorded into a graph: whatever pinned memory held them would have to stay as it is for as long as the
+// graph is replayed, a kernel's arguments are the graph's own.  PC_ARG_BYTES a launch.  (us a replay, and an eager call that reads the ring: 60
+// decode calls over 2 messages, 2 launches, 27 and 17; 20 over 2000, 92 launches, 765 and 1264, which is the host's planning.)
+__global__ __launch_bounds__(256) void pc_store_args_kernel(const PcArgBlob blob, uint4 *__restrict__ dst, int n16)
+{
+    if ((int)threadIdx.x < n16) dst[threadIdx.x] = blob.w[threadIdx.x];
+}
+
+void pc_launch_store_args(const void *host, size_t bytes, void *dst, hipStream_t st)
+{
+    static_assert(PC_ARG_BYTES / 16 <= 256, "a thread for every 16 bytes");
+    for (size_t at = 0; at < bytes; at += PC_ARG_BYTES) {
+        const size_t n = bytes - at < PC_ARG_BYTES ? bytes - at : PC_ARG_BYTES;
+        PcArgBlob blob;
+        std::memcpy(blob.w, (const char *)host + at, n);
+        pc_store_args_kernel<<<1, 256, 0, st>>>(blob, (uint4 *)((char *)dst + at), (int)((n + 15) / 16));
+    }
+}
+
 void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                               PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                               int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,

@@ -53,6 +53,16 @@ int32_t pc_ensure_ws(pc_cache *c, size_t bytes, hipStream_t st)
     return PC_OK;
 }
 
+// Work on the stream is being captured into a graph.  Its kernels must not read the pinned ring: a slot is free again for the
+// next call once its event has passed, whose work on the stream here is only done at a replay, and at every further one.
+bool pc_recorded(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusActive;
+    (void)hipGetLastError();                             // (the null stream, while another one is captured)
+    return false;
+}
+
 int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out)
 {
     StageSlot &s = c->stage[c->stage_next];

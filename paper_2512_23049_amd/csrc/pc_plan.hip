@@ -595,7 +595,7 @@ static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vec
 // of ONE_MERGE and ONE_PART a workgroup (us; 1 to 16 calls over 8 to 400 tiles, 1 to 32 splits: this choice is within 5 % of the
 // best of them.  One call over 200 tiles: 63 us unsplit, 13.6 in 32; eight over 16: 11.7 unsplit, 13.3 in 2 or 4).
 constexpr double ONE_TILE = 0.28, ONE_MERGE = 2.0, ONE_PART = 0.009;
-static bool plan_one(pc_cache *c, Planned &P, int32_t &rc)
+static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
 {
     const int n_calls = (int)P.res.size(), g = c->g, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads;
     if (c->decode_tiles_per_split != 0 || n_calls > 4095 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
@@ -646,7 +646,10 @@ static bool plan_one(pc_cache *c, Planned &P, int32_t &rc)
         }
     }
     char *h = (char *)P.one_blob.w;
-    if (bytes > PC_ARG_BYTES) {                          // (a slot of the ring holds four times HOST_READ_BYTES: nothing is allocated)
+    if (bytes > PC_ARG_BYTES && pc_recorded(st)) {
+        P.recorded.resize(align_up(bytes, 16));
+        h = P.recorded.data();
+    } else if (bytes > PC_ARG_BYTES) {                   // (a slot of the ring holds four times HOST_READ_BYTES: nothing is allocated)
         rc = pc_stage_acquire(c, bytes, &P.one_slot);
         if (rc != PC_OK) return false;
         h = (char *)P.one_slot->host;
@@ -676,7 +679,7 @@ static bool plan_one(pc_cache *c, Planned &P, int32_t &rc)
             int last = e;
             for (int end = before + (n > 0 ? tiles_of(e) : 0); last + 1 < n && end < std::min(T, (s + 1) * oc.chunk); end += tiles_of(++last)) {}
             const int count = n > 0 ? last - e + 1 : 0;
-            if (count > PC_ONE_SEGS) { P.one_slot = nullptr; return false; }
+            if (count > PC_ONE_SEGS) { P.one_slot = nullptr; P.recorded.clear(); return false; }
             PcOneItem it{};
             it.call = (uint32_t)i; it.split = (uint32_t)s; it.seg0 = (uint32_t)e; it.tile0 = (uint32_t)before; it.n_seg = (uint32_t)count;
             *items++ = it;
@@ -685,7 +688,8 @@ static bool plan_one(pc_cache *c, Planned &P, int32_t &rc)
     }
     P.lay = PlanLayout{};
     P.lay.part_ml = align_up(sizeof(float) * (size_t)part_rows * H_q * c->D, 256);       // (part_o comes first)
-    P.lay.total = P.lay.part_ml + sizeof(float) * 2 * (size_t)part_rows * H_q;
+    P.lay.calls = align_up(P.lay.part_ml + sizeof(float) * 2 * (size_t)part_rows * H_q, 256);       // (a recorded call's lists)
+    P.lay.total = P.lay.calls + P.recorded.size();
     P.total_seg = seg_off;
     P.one_bytes = bytes;
     P.one.lists = P.one_slot ? P.one_slot->host : nullptr;
@@ -724,13 +728,18 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         plan_shared(c, P.res, q_offs, g, sp);
     }
     int32_t rc = PC_OK;
-    if (want_items && bf16 && !c->host_only && sp.groups.empty() && plan_one(c, P, rc)) {
+    if (want_items && bf16 && !c->host_only && sp.groups.empty() && plan_one(c, P, st, rc)) {
         if (!P.fixed_ws) {
             rc = pc_ensure_ws(c, P.lay.total, st);
             if (rc != PC_OK) return rc;
         } else if (P.lay.total > P.fixed_cap)
             return pc_fail(c, PC_ERR_NO_SPACE, "attend: this batch needs %zu bytes of workspace, the fixed one holds %zu", P.lay.total, P.fixed_cap);
         P.ws = P.fixed_ws ? P.fixed_ws : c->ws;
+        if (!P.recorded.empty()) {
+            pc_launch_store_args(P.recorded.data(), P.recorded.size(), (char *)P.ws + P.lay.calls, st);
+            PC_HIP(c, hipGetLastError());
+            P.one.lists = (char *)P.ws + P.lay.calls;
+        }
         return PC_OK;
     }
     if (rc != PC_OK) return rc;
@@ -987,11 +996,13 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     // (Batches with shared groups stay with the ring, where they were measured: they need six calls at least over the same
     // messages, and their lists, 50 bytes a message and 4 more a row of it, seldom fit.)
     const bool in_args = P.lay.h2d_bytes <= PC_ARG_BYTES && P.n_sh_items == 0;
-    if (!in_args) {
+    const bool recorded = !in_args && pc_recorded(st);
+    if (recorded) P.recorded.resize(P.lay.h2d_bytes);
+    if (!in_args && !recorded) {
         rc = pc_stage_acquire(c, P.lay.h2d_bytes, &slot);
         if (rc != PC_OK) return rc;
     }
-    char *h = in_args ? (char *)blob.w : (char *)slot->host;
+    char *h = in_args ? (char *)blob.w : recorded ? P.recorded.data() : (char *)slot->host;
     std::memcpy(h + P.lay.calls, cds.data(), sizeof(PcCallDesc) * cds.size());
     int2 *hs = (int2 *)(h + P.lay.sel);
     int32_t *hq = (int32_t *)(h + P.lay.q_pos);
@@ -1033,8 +1044,11 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     // A block too large for the arguments is read by the plan builder where it is and copied to the workspace by further
     // blocks of the same launch (a copy in front of it took 4 us on the stream, 8 from 16 KB on, and a gap); beyond
     // HOST_READ_BYTES the copy engine is the faster way.
-    const bool in_place = !in_args && P.lay.h2d_bytes <= HOST_READ_BYTES;
-    if (!in_args && !in_place) {
+    const bool in_place = !in_args && !recorded && P.lay.h2d_bytes <= HOST_READ_BYTES;
+    if (recorded) {
+        pc_launch_store_args(h, P.lay.h2d_bytes, P.ws, st);
+        PC_HIP(c, hipGetLastError());
+    } else if (!in_args && !in_place) {
         PC_HIP(c, hipMemcpyAsync(P.ws, h, P.lay.h2d_bytes, hipMemcpyHostToDevice, st));
         PC_HIP(c, hipEventRecord(slot->ev, st));
         slot->used = true;
