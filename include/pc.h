@@ -194,9 +194,14 @@ int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, cons
  * to 256 workgroups), or whose staged descriptors then exceed one slot of the cache's pinned staging ring (1 MiB), is rejected with
  * PC_ERR_NO_SPACE before anything is enqueued (pc_last_error names both sizes).  Under capture the graph holds the
  * whole call: lists too long for one kernel's arguments (about 3.5 KB) are recorded as further small launches that
- * bring them, so that a replay depends on no host memory.  Kernel timing (pc_profile_enable) does not cover it.  Every cache on a GPU shares that GPU's array, which keeps the last call's contents (nothing
- * in it has to start at zero: every call writes what it reads): calls on one GPU that overlap in time - two
- * streams, or two caches - race; order them on one stream or with events. */
+ * bring them, so that a replay depends on no host memory.  Kernel timing (pc_profile_enable) does not cover it.  Every cache on a GPU shares
+ * that GPU's array, which keeps the last call's contents (nothing in it has to start at zero: every call writes what it
+ * reads): calls of pc_attend_static on one GPU that overlap in time - two streams, or two caches - race; order them on
+ * one stream or with events.  It shares no scratch memory with pc_attend, beside which replays of a captured call may run.
+ * State besides the arrays: for each of the two entry points the cache holds counters of the splits of a decode batch
+ * that are done.  They are zero between its calls (each call leaves them so).  Two calls of one entry point on one cache
+ * that overlap in time, which this interface excludes, can leave them off zero: the outputs of later calls are then wrong
+ * as well, for the rest of the cache's life. */
 #define PC_STATIC_WS_BYTES ((size_t)32 << 20)
 int32_t pc_attend_static(pc_cache *c, const pc_call *calls, int32_t n_calls,
                          const void *q, void *out, float *lse, void *stream);

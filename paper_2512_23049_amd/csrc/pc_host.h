@@ -52,7 +52,7 @@ struct pc_cache {
     void *storage = nullptr; bool owns_storage = false;
     void *k_store = nullptr, *v_store = nullptr;
     PcMsgEntry *table_dev = nullptr;
-    uint32_t *counters_dev = nullptr;                    // PcOne::counters
+    uint32_t *counters_dev = nullptr;                    // PcOne::counters of pc_attend, then those of pc_attend_static
     double *inv_freq_dev = nullptr;
     void *ws = nullptr; size_t ws_cap = 0;
     size_t ws_refused = SIZE_MAX;                        // a gradient's workspace the device had no room for

@@ -128,8 +128,8 @@ int32_t pc_cache_create(const pc_config *cfg, pc_cache **out)
     c->v_store = (char *)c->storage + bytes / 2;
     if (hipMalloc((void **)&c->table_dev, sizeof(PcMsgEntry) * (size_t)cfg->max_messages) != hipSuccess) return bail(PC_ERR_HIP);
     if (hipMemset(c->table_dev, 0, sizeof(PcMsgEntry) * (size_t)cfg->max_messages) != hipSuccess) return bail(PC_ERR_HIP);
-    if (hipMalloc((void **)&c->counters_dev, sizeof(uint32_t) * PC_ONE_COUNTERS) != hipSuccess) return bail(PC_ERR_HIP);
-    if (hipMemset(c->counters_dev, 0, sizeof(uint32_t) * PC_ONE_COUNTERS) != hipSuccess) return bail(PC_ERR_HIP);
+    if (hipMalloc((void **)&c->counters_dev, sizeof(uint32_t) * 2 * PC_ONE_COUNTERS) != hipSuccess) return bail(PC_ERR_HIP);
+    if (hipMemset(c->counters_dev, 0, sizeof(uint32_t) * 2 * PC_ONE_COUNTERS) != hipSuccess) return bail(PC_ERR_HIP);
     std::vector<double> f((size_t)c->half);
     for (int i = 0; i < c->half; ++i) f[i] = std::pow((double)cfg->rope_theta, -2.0 * i / c->D);
     if (hipMalloc((void **)&c->inv_freq_dev, sizeof(double) * f.size()) != hipSuccess) return bail(PC_ERR_HIP);

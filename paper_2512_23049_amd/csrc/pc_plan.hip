@@ -694,7 +694,9 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
     P.one_bytes = bytes;
     P.one.lists = P.one_slot ? P.one_slot->host : nullptr;
     P.one.off_sel = (int32_t)off_sel; P.one.off_q_pos = (int32_t)off_q_pos; P.one.off_items = (int32_t)off_items; P.one.n_items = (int32_t)n_items;
-    P.one.table = c->table_dev; P.one.inv_freq = c->inv_freq_dev; P.one.counters = c->counters_dev;
+    P.one.table = c->table_dev; P.one.inv_freq = c->inv_freq_dev;
+    // (like the workspaces: a replay of a captured pc_attend_static may run beside a pc_attend)
+    P.one.counters = c->counters_dev + (P.fixed_ws ? PC_ONE_COUNTERS : 0);
     P.one.tok_k = (const uint16_t *)P.tok_k; P.one.tok_v = (const uint16_t *)P.tok_v;
     return true;
 }

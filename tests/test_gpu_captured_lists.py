@@ -1,7 +1,8 @@
 """pc_attend_static recorded into a HIP graph with lists longer than a kernel's arguments: every replay returns what pc_attend returns
 for the queries it finds, bit for bit, though calls with other lists went through the pinned staging ring and the fixed workspace
 in between.  Decode in one launch, a split over more messages than that takes, prefill beside decode, shared decode, and lists
-that the copy engine brings to an ordinary call."""
+that the copy engine brings to an ordinary call.  And replays beside pc_attend calls on another stream: the two entry points share
+neither workspace nor counters."""
 import numpy as np
 import pytest
 
@@ -70,4 +71,38 @@ def test_replays_with_other_calls_in_between(kind):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
+    cache.close()
+
+
+def test_replays_beside_pc_attend():
+    import torch
+    from paper_2512_23049_amd import harness as hip
+    rng = np.random.default_rng(8)
+    n = 4                                                # calls over 60 tiles, each in several splits that the last one merges
+    ks, vs, cache, arena = fill([900, 1000] + [3] * n, H_Q, H_KV, rng)
+    calls = [Call([(0, 40 * i), (1, 1500)], 2 + i, 4000, 1, None) for i in range(n)]
+    others = [Call([(1, 7 * i), (0, 1500), (1, 2600)], 2 + i, 4000, 1, None) for i in range(n)]      # another number of splits
+    q = [hip.to_device(rnd(rng, n, H_Q, D), "bf16") for _ in range(2)]
+    wants = [torch.empty_like(q[0]) for _ in range(2)]
+    for want, x, which in zip(wants, q, (calls, others)):
+        cache.attend(which, x.data_ptr(), want.data_ptr())
+    rounds = 300
+    out, outs = torch.empty_like(q[0]), torch.empty((rounds, *q[0].shape), dtype=torch.bfloat16, device="cuda:0")
+    graph = torch.cuda.CUDAGraph()
+    replays, eager = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=replays):
+        cache.attend_static(calls, q[0].data_ptr(), out.data_ptr(), 0, replays.cuda_stream)
+    torch.cuda.synchronize()
+    for i in range(rounds):
+        with torch.cuda.stream(replays):
+            graph.replay()
+        cache.attend(others, q[1].data_ptr(), outs[i].data_ptr(), 0, eager.cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), wants[0].view(torch.int16))
+    assert (outs.view(torch.int16) == wants[1].view(torch.int16)).all()
+    out.fill_(7.0)
+    torch.cuda.synchronize()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), wants[0].view(torch.int16))
     cache.close()
