@@ -144,7 +144,7 @@ struct PcOneItem {
     uint32_t n_seg : 8;       // entries the split's tiles come from
 };
 #define PC_ONE_SEGS 64        // most of them (a wave holds them, one a lane)
-#define PC_ONE_COUNTERS 4096  // (call, KV head) pairs a launch can merge itself
+#define PC_ONE_COUNTERS 256   // (call, KV head) pairs of a batch whose calls are split (two splits each: two rounds of workgroups)
 
 #define PC_MERGE_WIDE 0x10000     // partial outputs in fp32 (bf16 caches)
 // One output row whose KV splits the merge kernel combines (staged by the host).

@@ -611,7 +611,8 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
         const size_t tables = n_seg * 548 + n_q * (1536 + 4 * (size_t)H_q) + n_tiles * sizeof(PcTile) + wgs * 16 * 264;
         if (staged > HOST_READ_BYTES || staged + tables > PC_STATIC_WS_BYTES - (1 << 20)) return false;
     }
-    const int most = std::max(1, std::min(MAX_SPLITS, 512 / (n_calls * H_kv)));      // (two rounds; further splits never pay)
+    // (two rounds; further splits never pay.  Above PC_ONE_COUNTERS pairs of a call and a KV head there is none, and no counter in use)
+    const int most = std::max(1, std::min(MAX_SPLITS, 2 * PC_ONE_COUNTERS / (n_calls * H_kv)));
     auto splits_of = [&](int T) {
         int best = 1;
         double best_us = 1e30;
@@ -628,7 +629,6 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
     for (int i = 0; i < n_calls; ++i) n_items += (size_t)(splits[(size_t)i] = splits_of(P.res[(size_t)i].tiles));
     const size_t off_sel = sizeof(PcOneCall) * (size_t)n_calls, off_items = off_sel + sizeof(int2) * n_seg;
     const size_t off_q_pos = off_items + sizeof(PcOneItem) * n_items, bytes = off_q_pos + sizeof(int32_t) * n_q;
-    if (n_items > (size_t)n_calls && n_calls * H_kv > PC_ONE_COUNTERS) return false;
     std::vector<int32_t> tok((size_t)n_calls, -1);
     if (!P.tok_items.empty()) {
         const uint32_t epoch = new_marks(c);             // value: the call that has it as its new message and no token for it yet, -1: several
