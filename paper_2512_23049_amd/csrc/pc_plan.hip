@@ -626,7 +626,11 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
     };
     size_t n_items = 0;
     std::vector<int> splits((size_t)n_calls);
-    for (int i = 0; i < n_calls; ++i) n_items += (size_t)(splits[(size_t)i] = splits_of(P.res[(size_t)i].tiles));
+    for (int i = 0; i < n_calls; ++i) {
+        n_items += (size_t)(splits[(size_t)i] = splits_of(P.res[(size_t)i].tiles));
+        // (some split has more: known here before any list is sorted)
+        if (P.res[(size_t)i].sel.size() + (P.res[(size_t)i].self_msg >= 0 ? 1 : 0) > (size_t)splits[(size_t)i] * PC_ONE_SEGS) return false;
+    }
     const size_t off_sel = sizeof(PcOneCall) * (size_t)n_calls, off_items = off_sel + sizeof(int2) * n_seg;
     const size_t off_q_pos = off_items + sizeof(PcOneItem) * n_items, bytes = off_q_pos + sizeof(int32_t) * n_q;
     std::vector<int32_t> tok((size_t)n_calls, -1);
@@ -645,6 +649,27 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
             mk.value = -1;
         }
     }
+    // which messages a split takes its tiles from (before a slot of the ring is taken: the plan builder's way takes one itself)
+    std::vector<PcOneItem> items;
+    items.reserve(n_items);
+    for (int i = 0; i < n_calls; ++i) {
+        Resolved &r = P.res[(size_t)i];
+        sort_by_slot(c, r);                              // (as in pc_plan_and_stage)
+        const int T = r.tiles, ns = splits[(size_t)i], n_sel = (int)r.sel.size(), n = n_sel + (r.self_msg >= 0 ? 1 : 0);
+        const int chunk = std::max(1, (T + ns - 1) / ns);
+        auto tiles_of = [&](int e) { return ((e < n_sel ? c->msgs[(size_t)r.sel[(size_t)e].x].len : r.self_len) + PC_TILE - 1) / PC_TILE; };
+        int e = 0, before = 0;                           // an entry, and the tiles before it
+        for (int s = 0; s < ns; ++s) {
+            while (e + 1 < n && before + tiles_of(e) <= s * chunk) before += tiles_of(e++);
+            int last = e;
+            for (int end = before + (n > 0 ? tiles_of(e) : 0); last + 1 < n && end < std::min(T, (s + 1) * chunk); end += tiles_of(++last)) {}
+            const int count = n > 0 ? last - e + 1 : 0;
+            if (count > PC_ONE_SEGS) return false;
+            PcOneItem it{};
+            it.call = (uint32_t)i; it.split = (uint32_t)s; it.seg0 = (uint32_t)e; it.tile0 = (uint32_t)before; it.n_seg = (uint32_t)count;
+            items.push_back(it);
+        }
+    }
     char *h = (char *)P.one_blob.w;
     if (bytes > PC_ARG_BYTES && pc_recorded(st)) {
         P.recorded.resize(align_up(bytes, 16));
@@ -657,12 +682,11 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
     PcOneCall *calls = (PcOneCall *)h;
     int2 *sel = (int2 *)(h + off_sel);
     int32_t *q_pos = (int32_t *)(h + off_q_pos);
-    PcOneItem *items = (PcOneItem *)(h + off_items);
+    std::memcpy(h + off_items, items.data(), sizeof(PcOneItem) * items.size());
     int64_t part_rows = 0;
     int seg_off = 0, q_off = 0;
     for (int i = 0; i < n_calls; ++i) {
-        Resolved &r = P.res[(size_t)i];
-        sort_by_slot(c, r);                              // (as in pc_plan_and_stage)
+        const Resolved &r = P.res[(size_t)i];
         const int T = r.tiles, ns = splits[(size_t)i], n_sel = (int)r.sel.size(), n = n_sel + (r.self_msg >= 0 ? 1 : 0);
         PcOneCall &oc = calls[i];
         oc.seg_off = (uint16_t)seg_off; oc.n_seg = (uint16_t)n; oc.n_q = (uint16_t)r.n_q; oc.n_splits = (uint16_t)ns;
@@ -672,18 +696,6 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
         std::copy(r.sel.begin(), r.sel.end(), sel + seg_off);
         if (r.self_msg >= 0) sel[seg_off + n_sel] = make_int2(r.self_msg, r.self_start);
         std::copy(r.q_pos.begin(), r.q_pos.end(), q_pos + q_off);
-        auto tiles_of = [&](int e) { return ((e < n_sel ? c->msgs[(size_t)r.sel[(size_t)e].x].len : r.self_len) + PC_TILE - 1) / PC_TILE; };
-        int e = 0, before = 0;                           // an entry, and the tiles before it
-        for (int s = 0; s < ns; ++s) {
-            while (e + 1 < n && before + tiles_of(e) <= s * oc.chunk) before += tiles_of(e++);
-            int last = e;
-            for (int end = before + (n > 0 ? tiles_of(e) : 0); last + 1 < n && end < std::min(T, (s + 1) * oc.chunk); end += tiles_of(++last)) {}
-            const int count = n > 0 ? last - e + 1 : 0;
-            if (count > PC_ONE_SEGS) { P.one_slot = nullptr; P.recorded.clear(); return false; }
-            PcOneItem it{};
-            it.call = (uint32_t)i; it.split = (uint32_t)s; it.seg0 = (uint32_t)e; it.tile0 = (uint32_t)before; it.n_seg = (uint32_t)count;
-            *items++ = it;
-        }
         seg_off += n; q_off += r.n_q;
     }
     P.lay = PlanLayout{};

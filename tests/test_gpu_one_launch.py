@@ -146,3 +146,31 @@ def test_replays_of_a_captured_call(n_calls, tokens):
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
     cache.close()
+
+
+def test_the_host_runs_four_calls_ahead():
+    """A split over more messages than a wave has lanes goes the plan builder's way, and takes one slot of the four of the staging
+    ring a call like every other: four calls are enqueued while the stream is still busy with work in front of them."""
+    import torch
+    from paper_2512_23049_amd import binding, harness as hip
+    h_q, h_kv, n_calls = 32, 8, 33                       # 264 (call, KV head) pairs: no call is split
+    rng = np.random.default_rng(3)
+    ks, vs, cache, arena = fill([5] * 70 + [2] * n_calls, h_q, h_kv, rng)
+    calls = [Call([(int(m), 7 * j) for j, m in enumerate(rng.permutation(70))], 70 + i, 900, 1, None) for i in range(n_calls)]
+    lists = binding.marshal_calls(calls)
+    q = hip.to_device(rnd(rng, n_calls, h_q, D), "bf16")
+    out = torch.empty_like(q)
+    cache.attend(calls, q.data_ptr(), out.data_ptr(), marshalled=lists)
+    x = torch.ones(8192, 8192, dtype=torch.bfloat16, device="cuda:0")
+    y = torch.empty_like(x)
+    torch.mm(x, x, out=y)
+    torch.cuda.synchronize()
+    for _ in range(200):                                 # at least 0.1 s
+        torch.mm(x, x, out=y)
+    in_front = torch.cuda.Event()
+    in_front.record()
+    for _ in range(4):
+        cache.attend(calls, q.data_ptr(), out.data_ptr(), marshalled=lists)
+    assert not in_front.query()
+    torch.cuda.synchronize()
+    cache.close()
