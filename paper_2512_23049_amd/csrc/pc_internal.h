@@ -35,6 +35,13 @@ struct PcTokenItem {
     int32_t new_len;          // the message's length once this token is in
 };
 
+// A decode step's token: one frequency's pair of its key, turned.  The launches that append tokens and the decode launch that
+// writes them itself store the same bits: the roundings are spelled out.
+__device__ __forceinline__ float2 turn_token(float x, float y, float c, float s)
+{
+    return make_float2(__builtin_fmaf(x, c, -(y * s)), __builtin_fmaf(x, s, y * c));
+}
+
 // Small host-built lists travel in a kernel's arguments: no staging buffer, copy or event (a copy and its event cost the host
 // 8 us and the stream 3 us of copy kernel and a gap).  The limit of a kernel's arguments is 4 KB.
 #define PC_ARG_BYTES 3584

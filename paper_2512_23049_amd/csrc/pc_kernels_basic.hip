@@ -280,8 +280,9 @@ __device__ __forceinline__ void append_token_thread(const PcTokenItem it, int j,
         const uint32_t lo = *reinterpret_cast<const uint32_t *>(ksrc + i0);
         const uint32_t hi = *reinterpret_cast<const uint32_t *>(ksrc + half + i0);
         const float a0 = P::lo(lo), a1 = P::hi(lo), b0 = P::lo(hi), b1 = P::hi(hi);
-        *reinterpret_cast<uint32_t *>(kdst + i0) = P::pack(a0 * fc0 - b0 * fs0, a1 * fc1 - b1 * fs1);
-        *reinterpret_cast<uint32_t *>(kdst + half + i0) = P::pack(a0 * fs0 + b0 * fc0, a1 * fs1 + b1 * fc1);
+        const float2 t0 = turn_token(a0, b0, fc0, fs0), t1 = turn_token(a1, b1, fc1, fs1);
+        *reinterpret_cast<uint32_t *>(kdst + i0) = P::pack(t0.x, t1.x);
+        *reinterpret_cast<uint32_t *>(kdst + half + i0) = P::pack(t0.y, t1.y);
         // V: [H_kv][slots/8][D][8]; this thread moves dims i0, i0+1 and half+i0, half+i0+1
         T *vg = v_store + ((int64_t)h * (slots / PC_VGROUP) + it.slot / PC_VGROUP) * D * PC_VGROUP + (it.slot % PC_VGROUP);
         vg[(int64_t)i0 * PC_VGROUP] = vsrc[i0];
@@ -290,8 +291,9 @@ __device__ __forceinline__ void append_token_thread(const PcTokenItem it, int j,
         vg[(int64_t)(half + i0 + 1) * PC_VGROUP] = vsrc[half + i0 + 1];
     } else {
         const float a0 = ksrc[i0], a1 = ksrc[i0 + 1], b0 = ksrc[half + i0], b1 = ksrc[half + i0 + 1];
-        kdst[i0] = a0 * fc0 - b0 * fs0; kdst[i0 + 1] = a1 * fc1 - b1 * fs1;
-        kdst[half + i0] = a0 * fs0 + b0 * fc0; kdst[half + i0 + 1] = a1 * fs1 + b1 * fc1;
+        const float2 t0 = turn_token(a0, b0, fc0, fs0), t1 = turn_token(a1, b1, fc1, fs1);
+        kdst[i0] = t0.x; kdst[i0 + 1] = t1.x;
+        kdst[half + i0] = t0.y; kdst[half + i0 + 1] = t1.y;
         T *vdst = v_store + ((int64_t)h * slots + it.slot) * D;
         vdst[i0] = vsrc[i0]; vdst[i0 + 1] = vsrc[i0 + 1];
         vdst[half + i0] = vsrc[half + i0]; vdst[half + i0 + 1] = vsrc[half + i0 + 1];

@@ -426,10 +426,10 @@ __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(c
             const float2 cs = make_float2((float)c, (float)s);
             if (e >= 0) { s_rot[e < item.n_seg ? e : e - item.n_seg + PC_ONE_SEGS][lane] = cs; continue; }
             const int64_t slot = __builtin_amdgcn_readlane(m_slot, self_lane) + at;
-            const float kx = bf_lo(tok[0]), ky = bf_lo(tok[1]);
+            const float2 turned = turn_token(bf_lo(tok[0]), bf_lo(tok[1]), cs.x, cs.y);
             uint16_t *kd = (uint16_t *)const_cast<void *>(L.k_store) + (kh * L.slots + slot) * PC_D + lane;
-            kd[0] = to_bf16(kx * cs.x - ky * cs.y);
-            kd[PC_D / 2] = to_bf16(kx * cs.y + ky * cs.x);
+            kd[0] = to_bf16(turned.x);
+            kd[PC_D / 2] = to_bf16(turned.y);
             uint16_t *vd = (uint16_t *)const_cast<void *>(L.v_store) + ((kh * L.slots + slot) / PC_VGROUP * PC_D + lane) * PC_VGROUP + slot % PC_VGROUP;
             vd[0] = tok[2];
             vd[PC_D / 2 * PC_VGROUP] = tok[3];
