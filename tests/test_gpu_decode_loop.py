@@ -72,8 +72,8 @@ def test_tail_crossing_tile_and_group_boundaries(hip):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_decode_steps_in_one_call(hip, dtype):
-    """pc_decode_step (token append and attention of a parallel decode step in one call, the append running beside
-    the plan builder) against the oracle at every step: plain tails, tails crossing tile and group boundaries, the
+    """pc_decode_step (token append and attention of a parallel decode step in one call, the append running in
+    the attention launch or beside the plan builder) against the oracle at every step: plain tails, tails crossing tile and group boundaries, the
     shared walk, and tails that grow into further extents (which makes the step fall back to one after the other)."""
     from paper_2512_23049_amd import PC_FLAG_GROW_EXTENTS
     kw = dict(n_q_heads=4, n_kv_heads=2, head_dim=64) if dtype == "f32" else dict(n_q_heads=8, n_kv_heads=2)

@@ -216,3 +216,21 @@ def test_the_host_runs_four_calls_ahead():
     assert not in_front.query()
     torch.cuda.synchronize()
     cache.close()
+
+
+def test_outputs_at_any_element():
+    """Outputs that start at an odd element: unsplit calls and calls whose splits the launch merges."""
+    import torch
+    from paper_2512_23049_amd import harness as hip
+    h_q, h_kv, n_calls = 32, 8, 4
+    rng = np.random.default_rng(1)
+    ks, vs, cache, arena = fill([90, 2100] + [3] * n_calls, h_q, h_kv, rng)
+    q = hip.to_device(rnd(rng, n_calls, h_q, D), "bf16")
+    for parent in (0, 1):
+        calls = [Call([(parent, 5 * i)], 2 + i, 3000, 1, None) for i in range(n_calls)]
+        want, buf = torch.empty_like(q), torch.full((q.numel() + 2,), 7.0, dtype=torch.bfloat16, device="cuda:0")
+        cache.attend(calls, q.data_ptr(), want.data_ptr())
+        cache.attend(calls, q.data_ptr(), buf[1:].data_ptr())
+        torch.cuda.synchronize()
+        assert torch.equal(buf[1:-1].view(torch.int16), want.view(torch.int16).flatten()) and (buf[[0, -1]] == 7.0).all()
+    cache.close()
