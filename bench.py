@@ -532,8 +532,8 @@ def section_decode_loop(cx):
     n_calls6 = len(w6.events[-1].calls)
     line.setdefault("extras", {})["decode_loop"] = {
         "workload": "configs[2]-shaped parallel decode as a loop: 64 calls (2048-token system + 8 pool messages each), "
-                    "tails grow from 1 to 64 tokens; a step = one pc_decode_step (one token per call appended beside the plan "
-                    "builder, then the attention); us_per_step_two_calls: the same step as pc_append_tokens_batch + pc_attend",
+                    "tails grow from 1 to 64 tokens; a step = one pc_decode_step (one token per call, written by the "
+                    "attention launch); us_per_step_two_calls: the same step as pc_append_tokens_batch + pc_attend",
         "steps": n_steps, "us_per_step": sec6 / n_steps * 1e6, "us_per_step_two_calls": sec6_two / n_steps * 1e6,
         "tokens_per_s": n_calls6 * n_steps / sec6,
         "gbs_logical": b6 / sec6 / 1e9, "B_logical_total": b6}

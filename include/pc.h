@@ -177,10 +177,11 @@ int32_t pc_attend(pc_cache *c, const pc_call *calls, int32_t n_calls,
 
 /* One decode step of parallel calls in one call (Sec. 2.4 "Parallel API Calls" and the interleaved decoding of
  * parallel calls): pc_append_tokens_batch(msg_ids, n_msgs, k, v) followed by pc_attend(calls, ...), with the same
- * arguments, results and errors as the two.  What the fused form saves: the tokens are written by the plan builder's
- * own launch and their item list rides in the same staging copy as the call list (one launch and one copy fewer per
- * step).  The append keeps a launch of its own when a grown message is listed as a PARENT by one of the calls or
- * needs a further extent.  If the append is refused nothing is enqueued; if the call list is refused the tokens
+ * arguments, results and errors as the two.  What the fused form saves is the append's launch and its item list: where
+ * the step is one launch (a PC_BF16 batch of decode calls that walk their own lists, every token the last one of exactly
+ * one call's new message) the attention kernel writes a token in front of the tile it belongs to, else the plan
+ * builder's launch does.  The append keeps a launch of its own when a grown message is listed as a PARENT by one of
+ * the calls or needs a further extent.  If the append is refused nothing is enqueued; if the call list is refused the tokens
  * stay appended, as with the two separate calls. */
 int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, const void *k, const void *v,
                        const pc_call *calls, int32_t n_calls, const void *q, void *out, float *lse, void *stream);
@@ -288,7 +289,8 @@ int32_t pc_cache_info(pc_cache *c, int32_t *n_messages, int64_t *slots_used,
  * bracketed by events on the caller's stream.  pc_profile_read waits for the stream
  * work recorded so far, then returns per-kernel-class totals since the last reset.
  * Classes: 0 append, 1 plan builder, 2 prefill attention, 3 decode attention,
- * 4 split merge, 5 fp32 attention, 6 table expansion, 7 reposition, 8 key gather. */
+ * 4 split merge, 5 fp32 attention, 6 table expansion, 7 reposition, 8 key gather.
+ * A decode batch that goes to one launch counts under 3 as a whole: plan, a step's tokens, attention and merge. */
 #define PC_N_KERNEL_CLASSES 9
 int32_t pc_profile_enable(pc_cache *c, int32_t on);
 int32_t pc_profile_read(pc_cache *c, double ms_total[PC_N_KERNEL_CLASSES],

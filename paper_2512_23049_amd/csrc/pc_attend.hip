@@ -31,7 +31,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
                            hipStream_t st, void *fixed_ws, size_t fixed_cap, Planned *with_tokens = nullptr)
 {
     Planned own;
-    Planned &P = with_tokens ? *with_tokens : own;       // (a decode step hands in the tokens the plan builder's launch appends)
+    Planned &P = with_tokens ? *with_tokens : own;       // (a decode step hands in the tokens that the attend's first launch appends)
     P.fixed_ws = fixed_ws; P.fixed_cap = fixed_cap;
     const int32_t rc = pc_plan_and_stage(c, calls, n_calls, true, st, P);
     if (rc != PC_OK || c->host_only) return rc;
@@ -156,8 +156,8 @@ int32_t pc_decode_step(pc_cache *c, const int32_t *msg_ids, int32_t n_msgs, cons
     if (rc != PC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const std::vector<int32_t> ids(msg_ids, msg_ids + std::max(n_msgs, 0));
-    // The tokens can be written by the plan builder's own launch (one launch and one staging copy for the whole step) when
-    // nothing the plan builder reads from the device table changes under it: the new message's length travels with the
+    // The tokens can be written by a launch of the attend itself (the one launch of a decode batch, else the plan builder's)
+    // when nothing that launch reads from the device table changes under it: the new message's length travels with the
     // call (host side), so what remains is a grown message that some call lists as a PARENT (its length is read from the
     // table) and a message that needs a further extent (a new table row).  Then the append gets a launch of its own.
     bool fuse = !c->host_only && n_msgs > 0 && n_calls > 0;

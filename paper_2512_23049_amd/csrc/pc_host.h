@@ -173,7 +173,7 @@ struct Planned {
     // means the cache's own workspace, which grows on demand.  On return ws is the buffer the plan was staged to.
     void *fixed_ws = nullptr; size_t fixed_cap = 0;
     void *ws = nullptr;
-    // pc_decode_step: tokens the plan builder's launch writes into the cache beside its own work (device k, v rows in
+    // pc_decode_step: tokens the first launch (plan builder, or the one launch) writes into the cache beside its own work (device k, v rows in
     // item order); tok_done: that launch was enqueued
     std::vector<PcTokenItem> tok_items; const void *tok_k = nullptr, *tok_v = nullptr; bool tok_done = false;
 };

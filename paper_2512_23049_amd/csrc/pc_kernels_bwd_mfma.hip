@@ -21,10 +21,11 @@
 //   finish    sum of the dq partials, turned back by the rows' positions
 //   keys      per (4 key tiles, KV head, split of the row units): dK and dV         (128)
 // A unit is 32 rows of one head, a tile 32 keys.  The walks are bound by the matrix pipe (216 MFMAs of 32 cycles per
-// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, means over a kernel trace:
-// prep 12, delta 102, dq 184, finish 9, keys 316 us (dq 208, keys 369 with one wave a unit or tile; plain vector kernels, a
-// thread per key and an FMA per product, took 31.4 ms).  delta: 46 us of it are the pipe, 9 the turns; running the vector
-// work of one of a SIMD's two waves beside the matrix work of the other took 3 off.  keys: longest workgroups first, 9 us more.
+// unit and tile).  Four calls of 150 to 320 rows over about 2000 tokens each, 32/8 heads, least and mean us of a kernel trace
+// of 16 passes: prep 12 / 12, delta 100 / 106, dq 181 / 189 to 199, finish 9 / 9, keys 312 / 327 (with one wave a unit or tile
+// dq 201 / 209, keys 354 / 373; plain vector kernels, a thread per key and an FMA per product, took 31.4 ms).  delta: 46 us of
+// it are the pipe, 9 the turns; running the vector work of one of a SIMD's two waves beside the matrix work of the other took
+// 3 off.  keys: longest workgroups first, 9 us more.
 //
 // All operands that a product needs with its indices the other way round (V by dimension, keys, queries and output
 // gradients by token) come from the same LDS tile through ds_read_b64_tr_b16: within 16 lanes, lane l points at row
@@ -349,9 +350,9 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_delta_kernel(PcLaunch L, PcBwd 
 // makes ds = p (dp - Delta), which it leaves in LDS in fp32; the second follows one tile behind and adds dq^T = K^T dS^T, collected
 // in the frame of the segment's keys and turned into the rows' frame whenever the rotation changes, by adding to the unit's
 // fp32 partial in memory.  (With one wave a unit, eight units a workgroup, both waves of a SIMD did their matrix work and then
-// their vector work at the same time, and all waited while any of them turned its queries or its sums: 208 us, now 184, for the
-// batch above.)  A workgroup
-// takes half of an item's eight units; ring of four tiles: the one of the second waves, that of the first, two on their way.
+// their vector work at the same time, and all waited while any of them turned its queries or its sums: 201 us at
+// least, now 181, for the batch above.)  A workgroup takes half of an item's eight units; ring of four tiles: the one of the
+// second waves, that of the first, two on their way.  All 256 registers are in use, 4 of the wave's values are spilled (20 bytes).
 __global__ __launch_bounds__(512, 2) void pc_bwd_dq_kernel(PcLaunch L, PcBwd B)
 {
     constexpr int RING = 4, AHEAD = 2, W_BYTES = 4096;

@@ -347,9 +347,10 @@ __device__ __forceinline__ void merge_cols(const PcLaunch &L, const DecCall &cd,
 // by a ballot over them; the rotations of the split's messages and query rows are shared out over the waves and computed into
 // LDS while the first tiles are on their way (fp64, rounded to fp32, as in the plan builder).  A decode step's new token is
 // written by the wave that reads it.  The workgroup whose split of a (call, KV head) is done last merges them, in split order
-// whichever comes last.  (By time stamps: 1.2 us until a wave knows its tiles, 1 to 2 for rotations and queries, 0.28 a tile
-// and workgroup -- 57 GB/s is what a compute unit draws with these loads, with four waves or eight --, 1.5 to combine the
-// waves, 2 to publish a part and learn that it is the last, 2.5 to merge.)
+// whichever comes last.  (By time stamps of a workgroup's first wave, for 4 calls over 700 tokens and one over 23 thousand:
+// 1.4 and 1.6 us until it knows its tiles, 1.9 and 3.1 for rotations and queries, 0.28 a tile and workgroup -- 57 GB/s is what
+// a compute unit draws with these loads, with four waves or eight --, 1.0 and 1.6 to combine the waves, 1.4 to publish a part
+// and learn that it is the last, 2.3 and 3.5 to merge.)
 template <int BYTES> struct PcArgs { uint4 w[BYTES / 16]; };
 template <> struct PcArgs<0> {};
 template <int BYTES>
@@ -465,6 +466,8 @@ void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaun
         __builtin_memcpy(args.w, blob.w, sizeof args < bytes ? sizeof args : bytes);
         pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(args, L, O);
     };
+    // (three forms: the host copies all of a launch's arguments, 0.1 us of a step of 1 to 4 calls between the two sizes: passes of
+    // 16 steps 131 and 134, 143 and 144, 176.5 and 178 us)
     if (O.lists) pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(PcArgs<0>(), L, O);
     else if (bytes <= 768) launch(PcArgs<768>());
     else launch(PcArgs<PC_ARG_BYTES>());

@@ -418,11 +418,15 @@ static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, con
     return {best > 1 ? tail : 0, best};
 }
 
-// Work items of the gradient of a bf16 batch.  The row-major kernels take workgroups of 8 units (32-row block x head),
-// each of which fills a compute unit, and as many splits of the tiles as fill whole rounds of them; the key-major kernel
-// takes 4 key tiles a workgroup and splits their units where that evens the load out: a workgroup costs KEY_FIXED us (keys
-// turned and cut into pieces at the start, an atomic per gradient element at the end) and KEY_UNIT a unit.  (Four calls of
-// 150 to 320 rows over 2000 tokens, 32/8 heads: 426 us for 16 units a workgroup, 365 for 32.)
+// Work items of the gradient of a bf16 batch.  An item of the row-major walk is 8 units (32-row block x head): a workgroup of
+// the Delta kernel, two of dq's, each of which fills a compute unit.  It gets as many splits of the tiles as fill whole rounds of
+// 256 items; the key-major kernel takes 4 key tiles a workgroup and splits their units where that evens the load out: a
+// workgroup costs KEY_FIXED us (keys turned and cut into pieces at the start, an atomic per gradient element at the end) and
+// KEY_UNIT a unit.  (Four calls of 150 to 320 rows over 2000 tokens, 32/8 heads: a training step takes 714 us with 16 units a
+// workgroup, 656 with 32.)  The four constants are those of kernels with one wave a unit or tile.  With the present ones, over 16
+// batches of 1 to 16 row blocks a call and 12 to 104 tiles, 32 and 64 heads over 8: the splits they give are within 3 % of the
+// best of 1, 2, 3, 4, 5, 6, 8 and 12 everywhere; the units a workgroup within 3 % of the best of 4 to 64 in nine, 4 to 11 %
+// of the step behind in seven (one call of 320 rows over 78 tiles: 20 units 323 us, 16 units 292).
 // Per-unit buffers take 64 KB a unit (16 more per further split, of which there are several only in batches of few units).  A
 // batch with more units than BWD_UNITS (256 MB) is cut into even runs of row blocks with launches of their own, inside a call
 // only where whole workgroups of 8 units end.  2048 rows x 64 heads over 4000 tokens, 4096 x 128 over themselves, six calls of
@@ -586,8 +590,8 @@ static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vec
 }
 
 // A batch of nothing but decode calls that walk their own lists goes to one launch (pc_decode_one_bf16_kernel) when no split takes
-// its tiles from more messages than a wave has lanes and every token of a decode step is the last one of exactly one call's new
-// message.  Not where the splits are tuned by hand, nor where lists or tables might not fit what pc_attend_static has, so that
+// its tiles from more messages than a wave has lanes (it looks them up one a lane, once) and every token of a decode step is the
+// last one of exactly one call's new message.  Not where the splits are tuned by hand, nor where lists or tables might not fit what pc_attend_static has, so that
 // it refuses what it refused.  rc != PC_OK: an error; else false: the plan builder's way.  Fills P.one_*.
 // (us a step of 64 calls over 9 messages each: 136 the plan builder's way, 131; of 5 over 220: 141 and 93.  Batches that share
 // enough stay with the shared walk: 14 calls over 27 messages each of 40: 38 us there, 47 in one launch of their own walks.)
