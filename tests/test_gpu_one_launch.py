@@ -234,3 +234,62 @@ def test_outputs_at_any_element():
         torch.cuda.synchronize()
         assert torch.equal(buf[1:-1].view(torch.int16), want.view(torch.int16).flatten()) and (buf[[0, -1]] == 7.0).all()
     cache.close()
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_forms_of_calls(seed):
+    """Random batches over every form a decode call takes (any order, repeats, messages that are nobody's, freed and re-used spans, stored
+    bases, further extents, positions up to the limit, rows' positions given, one frequency for all dimensions, 1 to 16
+    columns a KV head): one launch against the plan builder's way, attended at once and after a step's tokens."""
+    import torch
+    from paper_2512_23049_amd import binding
+    r = np.random.default_rng(seed)
+    h_kv, g, grow = int(r.choice([1, 2, 8])), int(r.choice([1, 3, 4, 8, 16])), seed % 3 == 0
+    h_q, n_q = h_kv * g, 1 if grow else int(r.integers(1, max(2, 16 // g + 1)))
+    lens, n_calls = [int(x) for x in r.integers(1, int(r.choice([20, 200, 1500])), int(r.integers(5, 100)))], int(r.choice([1, 3, 7, 40]))
+    max_position = (0, (1 << 28) - 1)[seed % 2]
+    far = (4000, (max_position or 1 << 24) - 5000)[seed % 4 // 2]
+    cap = sum(L + 31 for L in lens) + 256 * n_calls + 8192
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, (1.0, 10000.0)[seed % 5 > 0], cap, len(lens) + 2 * n_calls + 50, max_position,
+                          flags=binding.PC_FLAG_GROW_EXTENTS if grow else 0)
+    gen_dev = torch.Generator(device="cuda:0").manual_seed(seed)
+    kept = []
+
+    def normal(*shape):
+        kept.append(torch.randn(shape, generator=gen_dev, device="cuda:0").to(torch.bfloat16))
+        return kept[-1]
+
+    def append(n, reserve=0):
+        return cache.append_message(normal(n, h_kv, D).data_ptr(), normal(n, h_kv, D).data_ptr(), n, reserve)
+    ids = [append(n) for n in lens]
+    for m in ids[1::3]:
+        cache.message_free(m)
+    ids = [m for i, m in enumerate(ids) if i % 3 != 1] + [append(int(n)) for n in r.integers(1, 40, 3)]
+    for m in ids[:4]:
+        cache.reposition(m, int(r.integers(-far, far)))
+    own = [append(n, n if grow else n + 8) for n in (int(x) for x in r.integers(n_q, n_q + 70, n_calls))]
+    cache.set_decode_sharing(1)
+    for step in range(3):
+        calls = []
+        for m in own:
+            n = int(r.integers(0, min(len(ids), 100) + 1))
+            pick = r.permutation(len(ids))[:n] if r.random() < 0.8 else r.integers(0, len(ids), n)
+            calls.append(Call([(ids[int(p)], int(r.integers(-far, far))) for p in pick], m if r.random() < 0.9 else -1, int(r.integers(-far, far)),
+                              n_q, [int(x) for x in r.integers(-far, far, n_q)] if r.random() < 0.3 else None))
+        q = normal(n_calls * n_q, h_q, D)
+        got = [(torch.full_like(q, 7.0), torch.full((n_calls * n_q, h_q), 7.0, device="cuda:0")) for _ in range(2)]
+        if step:
+            tk, tv = normal(n_calls, h_kv, D), normal(n_calls, h_kv, D)
+            cache.decode_step(own, tk.data_ptr(), tv.data_ptr(), calls, q.data_ptr(), got[0][0].data_ptr(), got[0][1].data_ptr())
+        else:
+            cache.attend(calls, q.data_ptr(), got[0][0].data_ptr(), got[0][1].data_ptr())
+        cache.set_tuning(5, 0)
+        cache.attend(calls, q.data_ptr(), got[1][0].data_ptr(), got[1][1].data_ptr())
+        cache.set_tuning(0, 0)
+        torch.cuda.synchronize()
+        (one, one_lse), (two, two_lse) = got
+        seen = torch.isfinite(two_lse)
+        assert torch.equal(torch.isfinite(one_lse), seen) and (one_lse[seen] - two_lse[seen]).abs().max().item() <= 2e-2
+        # (each side rounds probabilities and an output below 4 to bf16: half of 2^-6 either side)
+        assert (one.float() - two.float()).abs().max().item() <= 2e-2
+    cache.close()
