@@ -1,21 +1,22 @@
-// Attention of fp32 caches on the fp32 matrix instructions (gfx950).
+// Attention of fp32 caches on the bf16 matrix instructions (gfx950), at fp32 precision.
 //
 // The transposed problem of the bf16 kernels: scores S^T = K~ . Q^T (rows = 32 keys, columns = 32 (query row, head) pairs
-// of one KV head), O^T = V^T . P^T, both with v_mfma_f32_32x32x2_f32, whose products and sums are plain fp32.  Its operands
-// are one float a lane (row or column lane % 32, index lane / 32 of the two), its result has 16 rows a lane:
-// 8 (r / 4) + 4 (lane / 32) + r % 4.  Register r of the scores is therefore the right operand of the second product for the
-// two keys of that register, and neither product needs its operands in any particular order of the summed index: a lane
-// reads K and V straight from memory, 16 bytes at a time, and no operand passes through LDS but the queries' master copy.
+// of one KV head), O^T = V^T . P^T.  An fp32 number is the exact sum of three bf16 pieces and a product of two bf16 numbers is
+// exact in fp32, so six bf16 MFMAs over the pieces are an fp32 product (see split8): a tile takes 96 of them, of 32 cycles (D = 128),
+// where v_mfma_f32_32x32x2_f32 took 128 of 64.  A result has 16 rows a lane: 8 (r / 4) + 4 (lane / 32) + r % 4, and the order of
+// the summed index is free as long as both operands agree: registers 8 kk .. 8 kk + 7 of the scores are the right operand of
+// the second product for the keys they stand for, and a lane reads those keys' values straight from memory, 16 bytes at a time.
 //
 // A workgroup is 8 waves, two per SIMD, over the same 32 columns; each walks a contiguous eighth of the item's tiles and
-// the results meet in LDS.  A tile is 128 MFMAs of 64 cycles (D = 128, 64 at D = 64), 3.4 us, against 32 KB of loads in
-// small pieces: one wave's loads, softmax and turns of the queries run under the other's matrix work.  A call with few columns is split over the tiles as well (see
-// pc_plan_and_stage) and pc_merge_f32_kernel adds the parts.  Bound: the fp32 matrix rate, 157 TFLOP/s nominal.
+// the results meet in LDS.  The columns' queries are turned by their positions, cut and kept in LDS; each wave turns its keys by
+// (start - stored base) and cuts them, and its values, as they come.  Bound: instruction issue.  Turning and cutting a tile are
+// 1000 vector instructions beside 96 MFMAs, about 4.5 cycles each of a SIMD's for its two waves together (6.5 thousand cycles a
+// tile and wave, 3 thousand of them matrix work).  A call with few columns is split over the tiles as well (see
+// pc_plan_and_stage) and pc_merge_f32_kernel adds the parts.
 //
-// 200 rows over 1400 keys, 32/8 heads, D = 128: 78 us (1115 us with one wave per (row, head), a lane per key and an FMA per
-// product); 40 us of them are matrix work, the rest is the start (work item, queries, first tile: one round trip to
-// memory after the other), the turns of the queries and 56 idle compute units of 256.  32 rows over 160 keys, 4/2 heads,
-// D = 64: 16.6 -> 12.6 us, all of it latency.
+// 200 rows over 1400 keys, 32/8 heads, D = 128: 49 us (77 with the fp32 instruction); 32 rows over 160 keys, 4/2 heads, D = 64:
+// 13.0 -> 10.1 us, all of it latency.  Distance to fp64 in the 2-norm 1.7e-7 to 3.0e-7 over ten shapes (2.2e-7 to 3.7e-7 with the
+// fp32 instruction: its chains are four times as long).
 #include "pc_mfma_common.h"
 
 #define NW 8                  // waves of a workgroup
@@ -31,18 +32,77 @@ __device__ __forceinline__ float other_half(float x)                        // t
     return __shfl_xor(x, 32);
 }
 template <int W> struct Vec;                                                // W consecutive floats of a row
-template <> struct Vec<2> { using type = float2; };
-template <> struct Vec<4> { using type = float4; };
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <> struct Vec<2> { using type = f32x2; };
+template <> struct Vec<4> { using type = f32x4; };
+
+
+// Eight fp32 numbers as three bf16 pieces each, whose sum the number is (round, subtract, round, subtract, round).  A product
+// of two bf16 numbers is exact in fp32, so six products of pieces, those whose orders sum to at most two, are a product of fp32
+// numbers: what is left out is below 2^-25 of it, half of what rounding it to fp32 costs.  Six bf16 MFMAs take 192 cycles for
+// 32 x 32 x 16, the fp32 instruction 512.
+struct Pieces { bf16x8 p[3]; };
+template <bool ODD = false>                              // ODD: an Inf or NaN is its own first piece, the others are zeros
+__device__ __forceinline__ Pieces split8(const float (&v)[8])
+{
+    uint32_t w[3][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float a = v[2 * j], b = v[2 * j + 1];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            w[i][j] = pack_bf16(a, b);
+            asm("" : "+v"(w[i][j]));                     // (or the lower piece is rounded a second time, by an instruction of its own)
+            a = ODD && !(fabsf(a) < INFINITY) ? 0.f : a - bf_lo(w[i][j]);
+            b = ODD && !(fabsf(b) < INFINITY) ? 0.f : b - bf_hi(w[i][j]);
+        }
+    }
+    Pieces r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]));
+    return r;
+}
+#define MFMA_BF(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
+__device__ __forceinline__ f32x16 product(const Pieces &a, const bf16x8 (&b)[3], f32x16 c)     // small terms first
+{
+    c = MFMA_BF(a.p[2], b[0], c); c = MFMA_BF(a.p[0], b[2], c); c = MFMA_BF(a.p[1], b[1], c);
+    c = MFMA_BF(a.p[1], b[0], c); c = MFMA_BF(a.p[0], b[1], c);
+    return MFMA_BF(a.p[0], b[0], c);
+}
+// N times: a matrix instruction, then V vector ones
+template <int N, int V>
+__device__ __forceinline__ void beside()
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+}
+
+// One 16-byte per lane direct load: lane l's bytes land at lds_wave_base + 16 l.  Assembly, so that the compiler keeps no
+// record of the LDS write and does not drain every request in front of later LDS reads; completion is awaited with wait_vm0().
+__device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 ::"s"(lds_wave_base), "v"(lane_off), "s"(gbase_uniform) : "memory", "m0");
+}
+__device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 }  // namespace
 
 template <int D>
 __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
 {
-    constexpr int NJ = D / 8, VW = D / 32, HALF = D / 2, PITCH = D + 4;
-    __shared__ __attribute__((aligned(16))) float s_q[32 * PITCH];          // the columns' queries turned by their positions
-    __shared__ __attribute__((aligned(16))) float s_acc[NW][32 * PITCH];
+    constexpr int NJ = D / 8, VW = D / 32, HALF = D / 2, PITCH = D + 4, NP = D / 32;        // NP: steps of 16 dims and their partners
+    constexpr int TILE_B = 32 * D * 4, ROW_CHUNKS = D / 4;                  // a tile's bytes; a row's 16-byte chunks
+    // during the walk: the columns' queries turned by their positions, in pieces, and each wave's present tile of keys; then the waves' results
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[3 * 2 * NP * 1024 + NW * TILE_B];
+    __shared__ __attribute__((aligned(16))) float2 s_rot[NW][HALF];         // the rotation of each wave's segment
     __shared__ float s_m[NW][32], s_l[NW][32];
+    bf16x8 (*const s_qp)[2 * NP][64] = reinterpret_cast<bf16x8 (*)[2 * NP][64]>(s_mem);     // [piece][16 dims][lane]
+    float (*const s_acc)[32 * PITCH] = reinterpret_cast<float (*)[32 * PITCH]>(s_mem);
+    static_assert(sizeof(float) * NW * 32 * PITCH <= sizeof s_mem, "");
 
     const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
     const PcItem item = L.items[blockIdx.x / L.n_kv_heads];
@@ -54,8 +114,9 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     const int col0 = item.unit0 * 32;       // column c: query row c / g, head c % g of the group
 
     // this wave's contiguous run of tiles
-    const int per_wave = (item.tile_end - item.tile_begin + NW - 1) / NW;
-    const int t0 = item.tile_begin + wave * per_wave, t1 = min(item.tile_end, t0 + per_wave);
+    const int n_tiles = item.tile_end - item.tile_begin;
+    // (waves 0 to 3 are on four SIMDs: what does not divide by eight goes to the first ones)
+    const int t0 = item.tile_begin + wave * (n_tiles / NW) + min(wave, n_tiles % NW), t1 = t0 + n_tiles / NW + (wave < n_tiles % NW);
     const PcTile *tab = L.tiles + item.tile_tab0;
     auto describe = [&](int t) {
         const int tc = __builtin_amdgcn_readfirstlane(max(0, min(t, item.tile_end - 1)));
@@ -64,98 +125,93 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     };
     i32x4 next = describe(t0);                           // {slot0, key0, seg, valid | flags}
 
-    for (int e = threadIdx.x; e < 32 * (HALF / 4); e += 64 * NW) {          // 4 pairs of a column a step
-        const int c = e / (HALF / 4), i = 4 * (e % (HALF / 4));
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    using VV = typename Vec<VW>::type;
+    const float *kb = (const float *)L.k_store + (int64_t)kh * L.slots * D, *vb = (const float *)L.v_store + (int64_t)kh * L.slots * D;
+    const unsigned v_at = 4 * hh * D + VW * n;           // within a tile: the lane's dims VW n + 0..VW-1
+    // A tile of keys comes by direct loads, whole rows (a lane that fetches its own row's pieces touches 32 lines an
+    // instruction: two cycles each of the CU's memory pipeline, more than the products take).  Chunk c of row r sits at
+    // position c ^ (r % ROW_CHUNKS) of the row: 16 lanes that read one chunk of 16 rows hit different banks.
+    unsigned char *const s_k = s_mem + 3 * 2 * NP * 1024 + wave * TILE_B;
+    const unsigned lds_k = (unsigned)(uintptr_t)s_k;
+    const unsigned k_src = (lane / ROW_CHUNKS) * (D * 4) + (((lane % ROW_CHUNKS) ^ (lane / ROW_CHUNKS)) << 4);
+    auto request_k = [&](int slot0) {
+        constexpr int STEP = 64 / ROW_CHUNKS;            // rows of an instruction
+#pragma unroll
+        for (int i = 0; i < 32 / STEP; ++i)
+            dma16(kb + ((int64_t)slot0 + STEP * i) * D, k_src ^ (((STEP * i) % ROW_CHUNKS) << 4), lds_k + i * 1024);
+    };
+    float4 k[4];                                         // step p of the present tile: dims 16 p + 8 hh + 0..7 of the lane's key and their partners
+    auto read_k = [&](int p) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) k[j] = *reinterpret_cast<const float4 *>(s_k + n * (D * 4) + (((4 * p + 2 * hh + (j & 1) + (j >> 1) * (HALF / 4)) ^ (n % ROW_CHUNKS)) << 4));
+    };
+    f32x4 rot;                                           // two pairs of a segment's rotation
+    const unsigned rot_at = lane & (HALF / 2 - 1);
+    auto load_rot = [&](const i32x4 &d) { rot = reinterpret_cast<const f32x4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF)[rot_at]; };
+    auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot; };          // (a wave's own LDS accesses are in order)
+    if (t0 < t1) { request_k(next.x); load_rot(next); }
+
+    for (int e = threadIdx.x; e < 32 * (HALF / 8); e += 64 * NW) {          // 8 pairs of a column a step
+        const int c = e / (HALF / 8), i = 8 * (e % (HALF / 8));
+        float x[8], y[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = y[j] = 0.f;
         if (col0 + c < n_cols) {
             const int col = col0 + c;
             const int64_t R = cd.q_off + col / g;
-            const float *q = (const float *)L.q + (R * L.n_q_heads + kh * g + col % g) * D;
-            const float4 x = make_float4(q[i], q[i + 1], q[i + 2], q[i + 3]);
-            const float4 y = make_float4(q[i + HALF], q[i + HALF + 1], q[i + HALF + 2], q[i + HALF + 3]);
+            const float *q = (const float *)L.q + (R * L.n_q_heads + kh * g + col % g) * D + i;
             const float4 *rot = reinterpret_cast<const float4 *>(L.rot_q + R * HALF + i);
-            const float4 c0 = rot[0], c1 = rot[1];
-            a = make_float4(x.x * c0.x - y.x * c0.y, x.y * c0.z - y.y * c0.w, x.z * c1.x - y.z * c1.y, x.w * c1.z - y.w * c1.w);
-            b = make_float4(x.x * c0.y + y.x * c0.x, x.y * c0.w + y.y * c0.z, x.z * c1.y + y.z * c1.x, x.w * c1.w + y.w * c1.z);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                const float4 cs = rot[j / 2];
+                const float x0 = q[j], x1 = q[j + 1], y0 = q[j + HALF], y1 = q[j + HALF + 1];
+                x[j] = x0 * cs.x - y0 * cs.y; x[j + 1] = x1 * cs.z - y1 * cs.w;
+                y[j] = x0 * cs.y + y0 * cs.x; y[j + 1] = x1 * cs.w + y1 * cs.z;
+            }
         }
-        *reinterpret_cast<float4 *>(s_q + c * PITCH + i) = a;
-        *reinterpret_cast<float4 *>(s_q + c * PITCH + i + HALF) = b;
+        const Pieces px = split8<true>(x), py = split8<true>(y);
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+            s_qp[w][i / 16][(i / 8 % 2) * 32 + c] = px.p[w];
+            s_qp[w][i / 16 + NP][(i / 8 % 2) * 32 + c] = py.p[w];
+        }
+    }
+    float x[8], y[8];
+    auto turn = [&](int p) __attribute__((always_inline)) {                 // step p of the keys, in k, into x, y
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            const float4 cs = *reinterpret_cast<const float4 *>(&s_rot[wave][16 * p + 8 * hh + j]);
+            const float *kx = reinterpret_cast<const float *>(&k[0]) + j, *ky = reinterpret_cast<const float *>(&k[2]) + j;
+            x[j] = kx[0] * cs.x - ky[0] * cs.y; x[j + 1] = kx[1] * cs.z - ky[1] * cs.w;
+            y[j] = kx[0] * cs.y + ky[0] * cs.x; y[j + 1] = kx[1] * cs.w + ky[1] * cs.z;
+        }
+    };
+    Pieces kx;
+    if (t0 < t1) {
+        put_rot();
+        wait_vm0();
+        read_k(0);
+        turn(0);
+        kx = split8(x);
     }
     __syncthreads();
 
-    using VV = typename Vec<VW>::type;
-    const float *kb = (const float *)L.k_store + (int64_t)kh * L.slots * D + n * D + 4 * hh;          // lane's key row, dims 8 j + 4 hh + 0..3
-    const float *vb = (const float *)L.v_store + (int64_t)kh * L.slots * D + 4 * hh * D + VW * n;     // lane's dims VW n + 0..VW-1
     const int row = (col0 + n) / g;
     const int self_lim = cd.self_len - cd.n_q + row;     // last own token this column sees
     const int lo_lim = cd.self_len - cd.n_q + col0 / g;              // ... the item's first column
     float m_run = -INFINITY, l_run = 0.f;
     f32x16 acc[VW];
+    auto clear = [&]() {
+        m_run = -INFINITY; l_run = 0.f;
 #pragma unroll
-    for (int i = 0; i < VW; ++i)
+        for (int i = 0; i < VW; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-
-    float4 q[NJ];
-    int cur = -1;
-    bool odd = false;                                    // an Inf or NaN was left out
-    for (int t = t0; t < t1; ++t) {
-        const i32x4 d = next;
-        if (t + 1 < t1) next = describe(t + 1);
-        // K and V come in pieces of 16 registers, two of them in flight
-        float4 k[2][4];
-        const float *kr = kb + (int64_t)d.x * D;
-        auto load_k = [&](int p) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) k[p & 1][j] = *reinterpret_cast<const float4 *>(kr + 8 * (4 * p + j));
-        };
-        load_k(0); load_k(1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (cur < 0 || (d.w & PC_TILE_FRESH)) {          // turn the queries by -(segment start - stored base)
-            cur = d.z;
-            const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + cur) * HALF) + 2 * hh;
-#pragma unroll
-            for (int j = 0; j < NJ / 2; ++j) {
-                const float4 a = *reinterpret_cast<const float4 *>(s_q + n * PITCH + 8 * j + 4 * hh);
-                const float4 b = *reinterpret_cast<const float4 *>(s_q + n * PITCH + HALF + 8 * j + 4 * hh);
-                const float4 c0 = rs[4 * j], c1 = rs[4 * j + 1];
-                q[j] = make_float4(a.x * c0.x + b.x * c0.y, a.y * c0.z + b.y * c0.w, a.z * c1.x + b.z * c1.y, a.w * c1.z + b.w * c1.w);
-                q[j + NJ / 2] = make_float4(b.x * c0.x - a.x * c0.y, b.y * c0.z - a.y * c0.w, b.z * c1.x - a.z * c1.y, b.w * c1.z - a.w * c1.w);
-            }
-        }
-        f32x16 s, s1;                                    // (two chains of D / 2 terms round less than one of D)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = s1[r] = 0.f;
-#pragma unroll
-        for (int p = 0; p < NJ / 4; ++p) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                f32x16 &c = (j & 1) ? s1 : s;
-                const float4 x = k[p & 1][j], y = q[4 * p + j];
-                c = MFMA_F32(x.x, y.x, c);
-                c = MFMA_F32(x.y, y.y, c);
-                c = MFMA_F32(x.z, y.z, c);
-                c = MFMA_F32(x.w, y.w, c);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (p + 2 < NJ / 4) load_k(p + 2);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        constexpr int VP = 16 / VW;                      // keys (registers of the scores) of a piece of V
-        VV v[2][VP];
-        const float *vr = vb + (int64_t)d.x * D;         // register r: key 8 (r / 4) + 4 hh + r % 4
-        auto load_v = [&](int p) {
-#pragma unroll
-            for (int i = 0; i < VP; ++i) { const int r = VP * p + i; v[p & 1][i] = *reinterpret_cast<const VV *>(vr + (8 * (r >> 2) + (r & 3)) * D); }
-        };
-        load_v(0);
-        if constexpr (VP < 16) load_v(1);
-        __builtin_amdgcn_sched_barrier(0);
-        s += s1;
-        const int valid = d.w & 0xFF, key0 = d.y;
-        const bool self = (d.w & PC_TILE_SELF) != 0;
-        const bool causal = self && key0 + valid - 1 > lo_lim;      // some column does not see some key
-        const int lim = self ? min(valid, self_lim - key0 + 1) : valid;
+            for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    };
+    clear();
+    // scores scaled and masked, the running maximum and sum, the accumulators' factor: s becomes the probabilities
+    auto softmax = [&](f32x16 &s, const i32x4 &d, bool causal) __attribute__((always_inline)) {
+        const int valid = d.w & 0xFF, lim = (d.w & PC_TILE_SELF) ? min(valid, self_lim - d.y + 1) : valid;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] *= L.scale_log2;
         if (valid < PC_TILE || causal) {                 // (uniform over the wave)
@@ -180,29 +236,153 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][r] *= alpha;
         }
-        // A probability of zero takes a key out of the second product only while its value is finite.  What lies behind a
-        // message's last token is (the store is kept that way), but a later token of the new message is the caller's own
-        // data: in a tile on the causal limit an Inf or NaN is left out here and added at the end, for the columns that
-        // see its key.
+    };
+    // some column of the item does not see some key of the tile
+    auto on_limit = [&](const i32x4 &d) { return (d.w & PC_TILE_SELF) != 0 && d.y + (d.w & 0xFF) - 1 > lo_lim; };
+
+    // The walk.  Every product of pieces stands beside the vector work that makes the pieces of the next one (`beside` pins the
+    // order: a matrix instruction, a few vector ones): keys are turned and cut a step of 16 + 16 dims ahead, values a block ahead.
+    bf16x8 qn[3];                                        // the next product's right operand
+    auto load_q = [&](int j) {
 #pragma unroll
-        for (int p = 0; p < 16 / VP; ++p) {
-            float x[16];
+        for (int w = 0; w < 3; ++w) qn[w] = s_qp[w][j][lane];
+    };
+    if (t0 < t1) load_q(0);
+    for (int t = t0; t < t1; ++t) {
+        const i32x4 d = next;
+        next = describe(t + 1);
+        VV v[16];                                        // register r: key 8 (r / 4) + 4 hh + r % 4
+        const float *vt = vb + (int64_t)d.x * D;         // (wave uniform)
+        auto load_v = [&](int half) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = reinterpret_cast<const float *>(&v[p & 1][0])[e];
-            if (causal)
+            for (int r = 8 * half; r < 8 * half + 8; ++r) v[r] = *reinterpret_cast<const VV *>(vt + (8 * (r >> 2) + (r & 3)) * D + v_at);
+        };
+        auto column = [&](int i) {                       // block i % VW of the values of keys 16 (i / VW) + ...
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const bool ok = fabsf(x[e]) < INFINITY;
-                    odd |= !ok;
-                    x[e] = ok ? x[e] : 0.f;
-                }
+            for (int j = 0; j < 8; ++j) x[j] = reinterpret_cast<const float *>(&v[8 * (i / VW) + j])[i % VW];
+        };
+        f32x16 s, s1;                                    // (two chains of D / 2 terms round less than one of D)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[e % VW] = MFMA_F32(x[e], s[VP * p + e / VW], acc[e % VW]);
+        for (int r = 0; r < 16; ++r) s[r] = s1[r] = 0.f;
+        Pieces vp;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
             __builtin_amdgcn_sched_barrier(0);
-            if ((p + 2) * VP < 16) load_v(p + 2);
+            if (p == NP / 4) { load_v(0); load_rot(next); }
+            if (p == NP / 2) load_v(1);
+            if (p + 1 < NP) read_k(p + 1);
+            bf16x8 qc[3] = {qn[0], qn[1], qn[2]};
+            load_q(p + NP);
+            s = product(kx, qc, s);
+            const Pieces ky = split8(y);
+            beside<6, 7>();
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int w = 0; w < 3; ++w) qc[w] = qn[w];
+            if (p + 1 < NP) load_q(p + 1);
+            s1 = product(ky, qc, s1);
+            if (p + 1 < NP) {
+                turn(p + 1);
+                kx = split8(x);
+            } else {
+                column(0);
+                vp = split8(x);
+            }
+            beside<6, 12>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        s += s1;
+        softmax(s, d, on_limit(d));
+        // the next tile's keys: the values and the rotation have landed by then, so that no wait for them waits for the keys as well
+        // (behind the last tile the present one is turned and cut once more, and not used)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(v[r]));
+        asm volatile("" : "+v"(rot));
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < t1) request_k(next.x);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = s[j];
+        Pieces pr = split8(x), pr1;
+#pragma unroll
+        for (int i = 0; i < 2 * VW; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 == 2 * VW) {
+                put_rot();
+                wait_vm0();
+                read_k(0);
+            }
+            acc[i % VW] = product(vp, pr.p, acc[i % VW]);
+            if (i == 0) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = s[8 + j];
+                pr1 = split8(x);
+            }
+            if (i + 1 < 2 * VW) {
+                column(i + 1);
+                vp = split8(x);
+            } else {
+                turn(0);
+                kx = split8(x);
+                load_q(0);
+            }
+            if (i + 1 == VW) pr = pr1;
+            beside<6, 8>();
         }
     }
+    // The pieces of an Inf or NaN are not its parts: a wave that met one, be it in a key that counts or in the value of a token
+    // behind a row's own, which no probability of zero takes out of a product, walks its tiles again on the fp32 instruction.
+    // There a probability of zero takes a key out of the second product only while its value is finite.  What lies behind a
+    // message's last token is (the store is kept that way), but a later token of the new message is the caller's own
+    // data: in a tile on the causal limit an Inf or NaN is left out and added at the end, for the columns that see its key.
+    bool odd = false;
+    float odd_sum = 0.f * l_run;
+#pragma unroll
+    for (int i = 0; i < VW; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) odd_sum = fmaf(acc[i][r], 0.f, odd_sum);
+    if (__builtin_amdgcn_ballot_w64(odd_sum != 0.f) != 0) {
+        auto query = [&](int dim) {                      // dims dim .. dim + 3 of the lane's column, from their pieces
+            float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < 3; ++w) {
+                const uint2 u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(&s_qp[w][dim / 16][(dim / 8 % 2) * 32 + n]) + 2 * (dim % 8));
+                r.x += bf_lo(u.x); r.y += bf_hi(u.x); r.z += bf_lo(u.y); r.w += bf_hi(u.y);
+            }
+            return r;
+        };
+        clear();
+        for (int t = t0; t < t1; ++t) {
+            const i32x4 d = describe(t);
+            const bool causal = on_limit(d);
+            const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + 2 * hh;
+            const float *kr = kb + ((int64_t)d.x + n) * D + 4 * hh, *vr = vb + (int64_t)d.x * D + v_at;
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+            for (int j = 0; j < NJ / 2; ++j) {           // the queries turned by -(segment start - stored base)
+                const float4 a = query(8 * j + 4 * hh), b = query(HALF + 8 * j + 4 * hh);
+                const float4 c0 = rs[4 * j], c1 = rs[4 * j + 1], x = *reinterpret_cast<const float4 *>(kr + 8 * j), y = *reinterpret_cast<const float4 *>(kr + 8 * j + HALF);
+                s = MFMA_F32(x.x, a.x * c0.x + b.x * c0.y, s); s = MFMA_F32(x.y, a.y * c0.z + b.y * c0.w, s);
+                s = MFMA_F32(x.z, a.z * c1.x + b.z * c1.y, s); s = MFMA_F32(x.w, a.w * c1.z + b.w * c1.w, s);
+                s = MFMA_F32(y.x, b.x * c0.x - a.x * c0.y, s); s = MFMA_F32(y.y, b.y * c0.z - a.y * c0.w, s);
+                s = MFMA_F32(y.z, b.z * c1.x - a.z * c1.y, s); s = MFMA_F32(y.w, b.w * c1.z - a.w * c1.w, s);
+            }
+            softmax(s, d, causal);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const VV vv = *reinterpret_cast<const VV *>(vr + (8 * (r >> 2) + (r & 3)) * D);
+#pragma unroll
+                for (int i = 0; i < VW; ++i) {
+                    float x = reinterpret_cast<const float *>(&vv)[i];
+                    const bool skip = causal && !(fabsf(x) < INFINITY);
+                    odd |= skip;
+                    x = skip ? 0.f : x;
+                    acc[i] = MFMA_F32(x, s[r], acc[i]);
+                }
+            }
+        }
+    }
+    __syncthreads();                                     // (the queries' pieces make room for the results)
 
     // the waves' results: element (i, r) of a lane is dim VW (8 (r / 4) + 4 hh + r % 4) + i of column n
     l_run += other_half(l_run);
@@ -228,37 +408,43 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 32 * (D / 4); e += 64 * NW) {
-        const int c = e / (D / 4), dim = 4 * (e % (D / 4));
-        const int col = col0 + c;
-        if (col >= n_cols) break;                        // (columns ascend with e)
+    {                                                    // 16 threads a column: dims 4 sub + 64 i
+        const int c = threadIdx.x >> 4, sub = threadIdx.x & 15, col = col0 + c;
+        if (col >= n_cols) return;
         float mm = s_m[0][c], l = 0.f;
 #pragma unroll
         for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][c]);
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 o[D / 64];
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (mm > -INFINITY) {
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 if (!(s_m[w][c] > -INFINITY)) { l += s_l[w][c]; continue; }        // saw nothing: a sum of 0 (or NaN, which stays)
                 const float f = ex2(s_m[w][c] - mm);
-                const float4 a = *reinterpret_cast<const float4 *>(&s_acc[w][c * PITCH + dim]);
-                o.x = fmaf(a.x, f, o.x); o.y = fmaf(a.y, f, o.y); o.z = fmaf(a.z, f, o.z); o.w = fmaf(a.w, f, o.w);
                 l = fmaf(s_l[w][c], f, l);
+#pragma unroll
+                for (int i = 0; i < D / 64; ++i) {
+                    const float4 a = *reinterpret_cast<const float4 *>(&s_acc[w][c * PITCH + 64 * i + 4 * sub]);
+                    o[i].x = fmaf(a.x, f, o[i].x); o[i].y = fmaf(a.y, f, o[i].y); o[i].z = fmaf(a.z, f, o[i].z); o[i].w = fmaf(a.w, f, o[i].w);
+                }
             }
         }
         const int r = col / g, h = kh * g + col % g;
-        if (cd.n_splits == 1) {
-            const int64_t at = (int64_t)(cd.q_off + r) * L.n_q_heads + h;
-            if (l > 0.f) { o.x /= l; o.y /= l; o.z /= l; o.w /= l; }
-            else o = make_float4(0.f, 0.f, 0.f, 0.f);    // nothing visible (or a NaN score)
-            float *out = (float *)L.out + at * D + dim;
-            out[0] = o.x; out[1] = o.y; out[2] = o.z; out[3] = o.w;
-            if (L.lse && dim == 0) L.lse[at] = (l > 0.f) ? (mm + log2f(l)) * 0.6931471805599453f : -INFINITY;
-        } else {
-            const int64_t at = ((int64_t)cd.part_off + (int64_t)item.split * cd.n_q + r) * L.n_q_heads + h;
-            *reinterpret_cast<float4 *>((float *)L.part_o + at * D + dim) = o;
-            if (dim == 0) { L.part_ml[at * 2] = mm; L.part_ml[at * 2 + 1] = l; }
+        const bool whole = cd.n_splits == 1;
+        const int64_t at = (whole ? (int64_t)(cd.q_off + r) : (int64_t)cd.part_off + (int64_t)item.split * cd.n_q + r) * L.n_q_heads + h;
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) {
+            if (whole) {
+                if (l > 0.f) { o[i].x /= l; o[i].y /= l; o[i].z /= l; o[i].w /= l; }
+                else o[i] = make_float4(0.f, 0.f, 0.f, 0.f);                // nothing visible (or a NaN score)
+                float *out = (float *)L.out + at * D + 64 * i + 4 * sub;
+                out[0] = o[i].x; out[1] = o[i].y; out[2] = o[i].z; out[3] = o[i].w;
+            } else *reinterpret_cast<float4 *>((float *)L.part_o + at * D + 64 * i + 4 * sub) = o[i];
         }
+        if (sub != 0) return;
+        if (!whole) { L.part_ml[at * 2] = mm; L.part_ml[at * 2 + 1] = l; }
+        else if (L.lse) L.lse[at] = (l > 0.f) ? (mm + log2f(l)) * 0.6931471805599453f : -INFINITY;
     }
 }
 

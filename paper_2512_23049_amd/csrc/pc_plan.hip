@@ -531,8 +531,7 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
 // Work items of an fp32 batch.  A workgroup takes 32 (row, head) columns of a KV head and all of its tiles (eight waves, an
 // eighth each) unless the batch has fewer such blocks than half the compute units: then the tiles are split over as many
 // workgroups as fill the chip once, 16 tiles (two a wave) at least, and a second launch adds the parts.  A wave's tile is
-// 7 us at D = 128 beside the other wave of its SIMD, the merge launch 5: with 8 tiles a split, 23 tiles of 40 blocks took
-// 14 + 5 us, unsplit 22, and every split writes its part to memory.
+// 6 us at D = 128 beside the other wave of its SIMD, the merge launch 5, and every split writes its part to memory.
 static void plan_f32(const pc_cache *c, const Planned &P, std::vector<PcCallDesc> &cds, bool may_split, std::vector<PcItem> &items, int64_t &part_rows)
 {
     const int g = c->g, H_kv = c->cfg.n_kv_heads;

@@ -1,0 +1,58 @@
+"""fp32 caches: numbers cut into three bf16 pieces.  Magnitudes far from one (the pieces carry their own exponents; bar as in
+test_gpu_f32_attend), and infinities, which have no pieces: a key whose score is -inf leaves no trace, one whose score is +inf
+makes the row a NaN, an infinite value reaches the rows that see it and no others."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_f32_attend import BAR, check, run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("size", [1e-30, 1e-3, 1e30])
+def test_magnitudes(D, size):
+    def spoil(ks, vs):                                   # (the values' size is the result's; keys: some dims large, some small)
+        for k in ks:
+            k[..., ::3] *= 1e-6
+        for v in vs:
+            v *= np.float32(size)
+    for got, got_lse, want, want_lse in run_case([200, 33, 90], [([(0, 5), (1, 300)], 2, 400, 90)], 8, 2, D, spoil):
+        want = want * np.float64(np.float32(size))
+        assert np.linalg.norm(got - want) <= BAR * np.linalg.norm(want)
+        assert np.abs(got_lse - want_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n_tok", [40, 700])
+def test_infinite_key(D, n_tok):
+    from oracle import choreo_oracle as orc
+    at, dim, theta = 17, 5, 10000.0
+
+    def spoil(ks, vs):
+        ks[0][at, :, dim] = np.inf
+    with np.errstate(invalid="ignore"):
+        (got, got_lse, _, _), = run_case([n_tok, 40], [([(0, 0)], 1, n_tok, 40)], 2, 1, D, spoil)
+    rng = np.random.default_rng(7)                       # run_case's data again: keys, values, queries
+    k0, k1, v0, v1 = [rng.standard_normal((L, 1, D)).astype(np.float32) for L in (n_tok, 40, n_tok, 40)]
+    q = rng.standard_normal((40, 2, D)).astype(np.float32)
+    want, want_lse = orc.attend_call([k0[:at], k0[at + 1:], k1], [v0[:at], v0[at + 1:], v1], [(0, 0), (1, at + 1)], 2, n_tok, 40, None, q, theta)
+    # the stored key is infinite in that dim and its partner; its score is -inf where both meet a query dim of the other sign
+    f = theta ** (-2.0 * dim / D)
+    a, t = ((n_tok + np.arange(40)) * f)[:, None], at * f
+    x, y = q[:, :, dim].astype(np.float64), q[:, :, dim + D // 2].astype(np.float64)
+    low = ((x * np.cos(a) - y * np.sin(a)) * np.cos(t) < 0) & ((x * np.sin(a) + y * np.cos(a)) * np.sin(t) < 0)
+    assert low.any() and not low.all()
+    assert (got[~low] == 0).all() and (got_lse[~low] == -np.inf).all()     # a score that is not a number, as ever
+    assert np.linalg.norm(got[low] - want[low]) <= BAR * np.linalg.norm(want[low])
+    assert np.abs(got_lse[low] - want_lse[low]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_infinite_value(D):
+    def spoil(ks, vs):
+        vs[0][3, :, 7] = np.inf
+    (got, got_lse, want, want_lse), = run_case([50, 64], [([(0, 0)], 1, 60, 64)], 4, 2, D, spoil)
+    assert (got[:, :, 7] == np.inf).all()
+    got[:, :, 7] = want[:, :, 7]
+    check([(got, got_lse, want, want_lse)])
