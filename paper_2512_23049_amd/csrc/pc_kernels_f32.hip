@@ -17,7 +17,7 @@
 // 200 rows over 1400 keys, 32/8 heads, D = 128: 49 us (77 with the fp32 instruction); 32 rows over 160 keys, 4/2 heads, D = 64:
 // 13.0 -> 10.1 us, all of it latency.  Distance to fp64 in the 2-norm 1.7e-7 to 3.0e-7 over ten shapes (2.2e-7 to 3.7e-7 with the
 // fp32 instruction: its chains are four times as long).
-#include "pc_mfma_common.h"
+#include "pc_pieces.h"
 
 #define NW 8                  // waves of a workgroup
 #define MFMA_F32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0)
@@ -32,62 +32,8 @@ __device__ __forceinline__ float other_half(float x)                        // t
     return __shfl_xor(x, 32);
 }
 template <int W> struct Vec;                                                // W consecutive floats of a row
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <> struct Vec<2> { using type = f32x2; };
 template <> struct Vec<4> { using type = f32x4; };
-
-
-// Eight fp32 numbers as three bf16 pieces each, whose sum the number is (round, subtract, round, subtract, round).  A product
-// of two bf16 numbers is exact in fp32, so six products of pieces, those whose orders sum to at most two, are a product of fp32
-// numbers: what is left out is below 2^-25 of it, half of what rounding it to fp32 costs.  Six bf16 MFMAs take 192 cycles for
-// 32 x 32 x 16, the fp32 instruction 512.
-struct Pieces { bf16x8 p[3]; };
-template <bool ODD = false>                              // ODD: an Inf or NaN is its own first piece, the others are zeros
-__device__ __forceinline__ Pieces split8(const float (&v)[8])
-{
-    uint32_t w[3][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float a = v[2 * j], b = v[2 * j + 1];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            w[i][j] = pack_bf16(a, b);
-            asm("" : "+v"(w[i][j]));                     // (or the lower piece is rounded a second time, by an instruction of its own)
-            a = ODD && !(fabsf(a) < INFINITY) ? 0.f : a - bf_lo(w[i][j]);
-            b = ODD && !(fabsf(b) < INFINITY) ? 0.f : b - bf_hi(w[i][j]);
-        }
-    }
-    Pieces r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]));
-    return r;
-}
-#define MFMA_BF(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
-__device__ __forceinline__ f32x16 product(const Pieces &a, const bf16x8 (&b)[3], f32x16 c)     // small terms first
-{
-    c = MFMA_BF(a.p[2], b[0], c); c = MFMA_BF(a.p[0], b[2], c); c = MFMA_BF(a.p[1], b[1], c);
-    c = MFMA_BF(a.p[1], b[0], c); c = MFMA_BF(a.p[0], b[1], c);
-    return MFMA_BF(a.p[0], b[0], c);
-}
-// N times: a matrix instruction, then V vector ones
-template <int N, int V>
-__device__ __forceinline__ void beside()
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
-    }
-}
-
-// One 16-byte per lane direct load: lane l's bytes land at lds_wave_base + 16 l.  Assembly, so that the compiler keeps no
-// record of the LDS write and does not drain every request in front of later LDS reads; completion is awaited with wait_vm0().
-__device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 ::"s"(lds_wave_base), "v"(lane_off), "s"(gbase_uniform) : "memory", "m0");
-}
-__device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 }  // namespace
 
@@ -95,9 +41,8 @@ template <int D>
 __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
 {
     constexpr int NJ = D / 8, VW = D / 32, HALF = D / 2, PITCH = D + 4, NP = D / 32;        // NP: steps of 16 dims and their partners
-    constexpr int TILE_B = 32 * D * 4, ROW_CHUNKS = D / 4;                  // a tile's bytes; a row's 16-byte chunks
     // during the walk: the columns' queries turned by their positions, in pieces, and each wave's present tile of keys; then the waves' results
-    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[3 * 2 * NP * 1024 + NW * TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_mem[3 * 2 * NP * 1024 + NW * RowTile<D>::BYTES];
     __shared__ __attribute__((aligned(16))) float2 s_rot[NW][HALF];         // the rotation of each wave's segment
     __shared__ float s_m[NW][32], s_l[NW][32];
     bf16x8 (*const s_qp)[2 * NP][64] = reinterpret_cast<bf16x8 (*)[2 * NP][64]>(s_mem);     // [piece][16 dims][lane]
@@ -128,22 +73,12 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     using VV = typename Vec<VW>::type;
     const float *kb = (const float *)L.k_store + (int64_t)kh * L.slots * D, *vb = (const float *)L.v_store + (int64_t)kh * L.slots * D;
     const unsigned v_at = 4 * hh * D + VW * n;           // within a tile: the lane's dims VW n + 0..VW-1
-    // A tile of keys comes by direct loads, whole rows (a lane that fetches its own row's pieces touches 32 lines an
-    // instruction: two cycles each of the CU's memory pipeline, more than the products take).  Chunk c of row r sits at
-    // position c ^ (r % ROW_CHUNKS) of the row: 16 lanes that read one chunk of 16 rows hit different banks.
-    unsigned char *const s_k = s_mem + 3 * 2 * NP * 1024 + wave * TILE_B;
-    const unsigned lds_k = (unsigned)(uintptr_t)s_k;
-    const unsigned k_src = (lane / ROW_CHUNKS) * (D * 4) + (((lane % ROW_CHUNKS) ^ (lane / ROW_CHUNKS)) << 4);
-    auto request_k = [&](int slot0) {
-        constexpr int STEP = 64 / ROW_CHUNKS;            // rows of an instruction
-#pragma unroll
-        for (int i = 0; i < 32 / STEP; ++i)
-            dma16(kb + ((int64_t)slot0 + STEP * i) * D, k_src ^ (((STEP * i) % ROW_CHUNKS) << 4), lds_k + i * 1024);
-    };
+    const RowTile<D> keys(s_mem + 3 * 2 * NP * 1024 + wave * RowTile<D>::BYTES, lane);      // the present tile's keys
+    auto request_k = [&](int slot0) { keys.request(kb + (int64_t)slot0 * D); };
     float4 k[4];                                         // step p of the present tile: dims 16 p + 8 hh + 0..7 of the lane's key and their partners
     auto read_k = [&](int p) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) k[j] = *reinterpret_cast<const float4 *>(s_k + n * (D * 4) + (((4 * p + 2 * hh + (j & 1) + (j >> 1) * (HALF / 4)) ^ (n % ROW_CHUNKS)) << 4));
+        for (int j = 0; j < 4; ++j) k[j] = keys.chunk(n, 4 * p + 2 * hh + (j & 1) + (j >> 1) * (HALF / 4));
     };
     f32x4 rot;                                           // two pairs of a segment's rotation
     const unsigned rot_at = lane & (HALF / 2 - 1);

@@ -1,0 +1,86 @@
+// fp32 products on the bf16 matrix instructions: device helpers shared by the kernels of fp32 caches (gfx950).
+#ifndef PC_PIECES_H_
+#define PC_PIECES_H_
+
+#include "pc_mfma_common.h"
+
+namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Eight fp32 numbers as three bf16 pieces each, whose sum the number is (round, subtract, round, subtract, round).  A product
+// of two bf16 numbers is exact in fp32, so six products of pieces, those whose orders sum to at most two, are a product of fp32
+// numbers: what is left out is below 2^-25 of it, half of what rounding it to fp32 costs.  Six bf16 MFMAs take 192 cycles for
+// 32 x 32 x 16, the fp32 instruction 512.
+struct Pieces { bf16x8 p[3]; };
+template <bool ODD = false>                              // ODD: an Inf or NaN is its own first piece, the others are zeros
+__device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        w[i] = pack_bf16(a, b);
+        asm("" : "+v"(w[i]));                            // (or the lower piece is rounded a second time, by an instruction of its own)
+        a = ODD && !(fabsf(a) < INFINITY) ? 0.f : a - bf_lo(w[i]);
+        b = ODD && !(fabsf(b) < INFINITY) ? 0.f : b - bf_hi(w[i]);
+    }
+}
+template <bool ODD = false>
+__device__ __forceinline__ Pieces split8(const float *v)
+{
+    uint32_t w[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split2<ODD>(v[2 * j], v[2 * j + 1], w[j]);
+    Pieces r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]));
+    return r;
+}
+#define MFMA_BF(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
+__device__ __forceinline__ f32x16 product(const Pieces &a, const bf16x8 (&b)[3], f32x16 c)     // small terms first
+{
+    c = MFMA_BF(a.p[2], b[0], c); c = MFMA_BF(a.p[0], b[2], c); c = MFMA_BF(a.p[1], b[1], c);
+    c = MFMA_BF(a.p[1], b[0], c); c = MFMA_BF(a.p[0], b[1], c);
+    return MFMA_BF(a.p[0], b[0], c);
+}
+// N times: a matrix instruction, then V vector ones
+template <int N, int V>
+__device__ __forceinline__ void beside()
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+}
+
+// One 16-byte per lane direct load: lane l's bytes land at lds_wave_base + 16 l.  Assembly, so that the compiler keeps no
+// record of the LDS write and does not drain every request in front of later LDS reads; completion is awaited with wait_vm0().
+__device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 ::"s"(lds_wave_base), "v"(lane_off), "s"(gbase_uniform) : "memory", "m0");
+}
+__device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A wave's tile of 32 fp32 rows of D, brought to LDS by direct loads of whole rows (a lane that fetches its own row's pieces
+// touches 32 lines an instruction: two cycles each of the CU's memory pipeline).  Chunk c (16 bytes) of row r sits at position
+// c ^ (r % CHUNKS) of the row: 16 lanes that read one chunk of 16 rows hit different banks.
+template <int D>
+struct RowTile {
+    static constexpr int BYTES = 32 * D * 4, CHUNKS = D / 4;
+    unsigned char *at;
+    unsigned lds, src;
+    __device__ RowTile(unsigned char *mem, int lane) : at(mem), lds((unsigned)(uintptr_t)mem),
+        src((lane / CHUNKS) * (D * 4) + (((lane % CHUNKS) ^ (lane / CHUNKS)) << 4)) {}
+    __device__ void request(const float *rows) const     // (wave uniform)
+    {
+        constexpr int STEP = 64 / CHUNKS;                // rows of an instruction
+#pragma unroll
+        for (int i = 0; i < 32 / STEP; ++i) dma16(rows + STEP * i * D, src ^ (((STEP * i) % CHUNKS) << 4), lds + i * 1024);
+    }
+    __device__ float4 chunk(int row, int c) const { return *reinterpret_cast<const float4 *>(at + row * (D * 4) + ((c ^ (row % CHUNKS)) << 4)); }
+};
+
+}  // namespace
+
+#endif

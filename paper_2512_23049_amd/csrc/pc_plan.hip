@@ -565,7 +565,7 @@ static void plan_f32(const pc_cache *c, const Planned &P, std::vector<PcCallDesc
 
 // Key-major work items of the gradient of an fp32 batch: 4 key tiles a workgroup (one a wave), which fills a compute unit,
 // and the column blocks that see them split until the chip is full twice over, two blocks a split at least (a split ends in
-// one atomic per element of its tiles' dK and dV, about what one more block costs).
+// one atomic per element of its tiles' dK and dV, about what one more block costs), or one where even so the chip is not full once.
 static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vector<PcBwdKeyItem> &keys)
 {
     const int g = c->g;
@@ -580,7 +580,7 @@ static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vec
             if (t >= parent_tiles) first = (int)((int64_t)std::max(0, (t - parent_tiles) * PC_TILE - (r.self_len - r.n_q)) * g / 32);
             if (first >= blocks) continue;
             const int n = blocks - first;
-            const int sp = (int)std::max<int64_t>(1, std::min<int64_t>((512 + quads - 1) / quads, n / 2));
+            const int sp = (int)std::max<int64_t>({1, std::min<int64_t>((512 + quads - 1) / quads, n / 2), std::min<int64_t>(256 / quads, n)});
             const int per = (n + sp - 1) / sp;
             for (int a = 0; a < n; a += per)
                 keys.push_back(PcBwdKeyItem{(int32_t)i, t, std::min(4, T - t), first + a, first + std::min(n, a + per), {0, 0, 0}});

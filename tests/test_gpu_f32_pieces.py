@@ -56,3 +56,36 @@ def test_infinite_value(D):
     assert (got[:, :, 7] == np.inf).all()
     got[:, :, 7] = want[:, :, 7]
     check([(got, got_lse, want, want_lse)])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_infinite_output_gradient(D):
+    """It reaches its row's dq, the keys' gradients through that row, and of dV only its own dim, with its sign."""
+    import torch
+    from paper_2512_23049_amd import binding
+    from pc_inputs import Call
+    h_q, h_kv, n, at, dim = 4, 2, 100, 41, 5
+    rng = torch.Generator(device="cuda:0")
+    rng.manual_seed(4)
+    k, v, q, g = (torch.randn((n, h, D), generator=rng, device="cuda:0") for h in (h_kv, h_kv, h_q, h_q))
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_F32, 10000.0, 128, 2)
+    m = cache.append_message(k.data_ptr(), v.data_ptr(), n)
+    call = [Call([], m, 0, n, None)]
+    out, lse = torch.empty((n, h_q, D), device="cuda:0"), torch.empty((n, h_q), device="cuda:0")
+    cache.attend(call, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+    res = []
+    for bad in (False, True):
+        if bad:
+            g[at, 0, dim] = float("inf")
+        d_q = torch.empty((n, h_q, D), device="cuda:0")
+        d_k, d_v = (torch.zeros((128, h_kv, D), device="cuda:0") for _ in range(2))
+        cache.attend_backward(call, q.data_ptr(), lse.data_ptr(), g.data_ptr(), d_q.data_ptr(), d_k.data_ptr(), d_v.data_ptr())
+        torch.cuda.synchronize()
+        res.append((d_q, d_k[:n], d_v[:n]))
+    cache.close()
+    (q0, k0, v0), (q1, k1, v1) = res
+    assert not torch.isfinite(q1[at, 0]).any() and not torch.isfinite(k1[:at + 1, 0]).any()
+    assert (v1[:at + 1, 0, dim] == float("inf")).all()
+    q1[at, 0], k1[:at + 1, 0], v1[:, 0, dim] = q0[at, 0], k0[:at + 1, 0], v0[:, 0, dim]    # (later keys: that row's zero times it)
+    for a, b in ((q0, q1), (k0, k1), (v0, v1)):
+        assert float((a - b).norm()) <= 3e-6 * float(a.norm())
