@@ -420,19 +420,21 @@ static std::pair<int, int> prefill_tail(const pc_cache *c, const Planned &P, con
 
 // Work items of the gradient of a bf16 batch.  An item of the row-major walk is 8 units (32-row block x head): a workgroup of
 // the Delta kernel, two of dq's, each of which fills a compute unit.  It gets as many splits of the tiles as fill whole rounds of
-// 256 items; the key-major kernel takes 4 key tiles a workgroup and splits their units where that evens the load out: a
-// workgroup costs KEY_FIXED us (keys turned and cut into pieces at the start, an atomic per gradient element at the end) and
-// KEY_UNIT a unit.  (Four calls of 150 to 320 rows over 2000 tokens, 32/8 heads: a training step takes 714 us with 16 units a
-// workgroup, 656 with 32.)  The four constants are those of kernels with one wave a unit or tile.  With the present ones, over 16
-// batches of 1 to 16 row blocks a call and 12 to 104 tiles, 32 and 64 heads over 8: the splits they give are within 3 % of the
-// best of 1, 2, 3, 4, 5, 6, 8 and 12 everywhere; the units a workgroup within 3 % of the best of 4 to 64 in nine, 4 to 11 %
-// of the step behind in seven (one call of 320 rows over 78 tiles: 20 units 323 us, 16 units 292).
+// 256 items.  The key-major kernel takes 4 key tiles a workgroup and splits their units: a workgroup costs KEY_FIXED us (keys
+// turned and cut into pieces at the start, an atomic per gradient element at the end) and KEY_UNIT a unit, and a launch ends
+// between the even share of a compute unit (workgroups of unlike lengths fill each other's gaps) and the whole rounds of the longest
+// ones: the mean of the two.  Fitted to the step's time over 22 batches of 1 to 8 calls (1 to 32 row blocks, 7 to 104 tiles) with
+// 4 to 128 units a workgroup: where the choice was among the measured ones it is 0.3 % behind the best in the mean, 3 % at most.
+// The rule before (even share and half a longest workgroup, 8 units at least) was 2 and 9 % behind.  Steps of 41 batches, 20 of them
+// not in the fit: 1.02 times as fast in the mean, 0.985 (launch-bound ones whose plan did not change) to 1.09 (one call of 320 rows
+// over 100 tiles 357 -> 329 us, 1000 rows 802 -> 776, 43 and 31 rows over 8 and 16 tiles 131 -> 120).  Splits of the row-major
+// walk: within 3 % of the best of 1, 2, 3, 4, 5, 6, 8 and 12 in 16 batches.
 // Per-unit buffers take 64 KB a unit (16 more per further split, of which there are several only in batches of few units).  A
 // batch with more units than BWD_UNITS (256 MB) is cut into even runs of row blocks with launches of their own, inside a call
 // only where whole workgroups of 8 units end.  2048 rows x 64 heads over 4000 tokens, 4096 x 128 over themselves, six calls of
 // 700 x 64 over 2000: 4.50, 7.66, 4.79 ms in runs of 4096 units, 4.50, 7.74, 4.63 of 8192, 4.71, 8.60, 5.06 of 2048.
 constexpr int64_t BWD_UNITS = 4096;
-constexpr double KEY_FIXED = 30.0, KEY_UNIT = 2.5, ROWS_FIXED = 15.0, ROWS_TILE = 3.0;
+constexpr double KEY_FIXED = 30.0, KEY_UNIT = 3.0, ROWS_FIXED = 15.0, ROWS_TILE = 3.0;
 struct BwdPlan { std::vector<PcItem> items; std::vector<PcBwdKeyItem> keys; std::vector<int2> row_blocks; size_t units = 0, splits = 1; };
 
 static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc> &cds, BwdPlan &bp, int64_t max_units)
@@ -450,16 +452,28 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
     }
     const int64_t most_blocks = std::max<int64_t>(step, max_units / H_q / step * step), runs = (blocks + most_blocks - 1) / most_blocks;
     const int rb_max = (int)std::max<int64_t>(step, (int64_t)align_up((size_t)((blocks + runs - 1) / runs), (size_t)step));
+    // tiles of the call in front of its own, and the first row block that sees one of four tiles from t on
+    auto parents_of = [](const Resolved &r) { return r.tiles - (r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0); };
+    auto first_block = [&](const Resolved &r, int t) { return t >= parents_of(r) ? std::max(0, ((t - parents_of(r)) * PC_TILE - (r.self_len - r.n_q)) / 32) : 0; };
     int key_units = most_units;                          // units a key-major workgroup takes
     double best_us = 0;
-    for (int k = 1; k <= 16 && (k == 1 || most_units / k >= 8); ++k) {
+    for (int k = 1; k <= 16 && (k == 1 || most_units / k >= 4); ++k) {
         const int u = (most_units + k - 1) / k;
-        double total = 0;
+        int64_t workgroups = 0, total = 0;               // (units of all of them together)
+        int longest = 0;
         for (const Resolved &r : P.res) {
-            const int n = (r.n_q + 31) / 32 * g;
-            total += (double)((r.tiles + 3) / 4) * H_kv * (KEY_FIXED * ((n + u - 1) / u) + KEY_UNIT * n);
+            const int n_rb = (r.n_q + 31) / 32;
+            auto add = [&](int64_t fours, int n) {       // so many groups of four tiles that n units see
+                const int sp = (n + u - 1) / u;
+                workgroups += fours * sp * H_kv; total += fours * n * H_kv;
+                longest = std::max(longest, (n + sp - 1) / sp);
+            };
+            int t = (parents_of(r) + 3) / 4 * 4;
+            if (t > 0 && n_rb > 0) add(t / 4, n_rb * g);
+            for (; t < r.tiles && first_block(r, t) < n_rb; t += 4) add(1, (n_rb - first_block(r, t)) * g);
         }
-        const double us = total / 256 + 0.5 * runs * (KEY_FIXED + KEY_UNIT * u);      // workgroups of unlike lengths: no whole rounds
+        const double even = (KEY_FIXED * workgroups + KEY_UNIT * total) / 256, rounds = (double)runs * ((workgroups + 256 * runs - 1) / (256 * runs));
+        const double us = 0.5 * even + 0.5 * rounds * (KEY_FIXED + KEY_UNIT * longest);
         if (k == 1 || us < best_us) { best_us = us; key_units = u; }
     }
     // splits of the row-major walk: the fewest rounds of 256 workgroups, each a start (ROWS_FIXED) and its tiles long
@@ -483,8 +497,7 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
     for (size_t i = 0; i < P.res.size(); ++i) {
         const Resolved &r = P.res[i];
         PcCallDesc &cd = cds[i];
-        const int n_rb = (r.n_q + 31) / 32, T = r.tiles;
-        const int self_tiles = r.self_msg >= 0 ? (r.self_len + PC_TILE - 1) / PC_TILE : 0, parent_tiles = T - self_tiles;
+        const int n_rb = (r.n_q + 31) / 32, T = r.tiles, parent_tiles = parents_of(r), self_tiles = T - parent_tiles;
         const int ns = std::max(1, std::min(row_splits, T / 8));
         cd.n_splits = ns;
         cd.rb_off = (int32_t)bp.row_blocks.size();
@@ -513,8 +526,7 @@ static void plan_backward(const pc_cache *c, Planned &P, std::vector<PcCallDesc>
             }
             // tiles by units: own tiles are seen from the block of their first key on
             for (int t = 0; t < T; t += 4) {
-                int first = b0;
-                if (t >= parent_tiles) first = std::max(first, ((t - parent_tiles) * PC_TILE - (r.self_len - r.n_q)) / 32);
+                const int first = std::max(b0, first_block(r, t));
                 if (first >= b1) continue;
                 const int n_rt = (b1 - first) * g;
                 const int sp = (n_rt + key_units - 1) / key_units, per = (n_rt + sp - 1) / sp;

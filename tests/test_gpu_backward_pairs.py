@@ -17,3 +17,15 @@ def test_units_and_tiles(h_q, h_kv, n_q, lens):
 
 def test_two_calls_over_the_same_messages():
     run_case([64, 3, 290, 45, 80], [([(0, 5), (2, 90), (1, 0)], 3, 700, 45), ([(2, 3), (0, 400), (0, 9)], 4, 512, 80)], 6, 2)
+
+
+# (8 units in workgroups of 4; units that the workgroups do not share evenly; a call whose rows are the last of a longer message; own
+#  tiles behind the parents' last group of four, and in it)
+@pytest.mark.parametrize("lens,calls", [
+    ([200, 43, 31], [([(0, 0)], 1, 200, 43), ([(0, 5), (0, 300)], 2, 600, 31)]),
+    ([96, 330], [([(0, 0)], 1, 100, 330)]),
+    ([128, 420], [([(0, 7)], 1, 140, 100)]),
+    ([330], [([], 0, 0, 330)]),
+])
+def test_units_split_over_workgroups(lens, calls):
+    run_case(lens, calls, 8, 2)
