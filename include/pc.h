@@ -324,8 +324,8 @@ int32_t pc_set_key_gather(pc_cache *c, int32_t mode);
  * backward call has been enqueued, pc_grad_keys_finalize(d_k) turns the rows of every live
  * message into the gradient w.r.t. the K that was appended.  No message may be repositioned,
  * freed or swapped between the first backward call into a buffer and its finalize.  All
- * arithmetic is at fp32 precision for both dtypes (PC_BF16: on the bf16 matrix cores, every
- * fp32 factor as the exact sum of three bf16 pieces).  Workspace of a PC_BF16 cache: 64 KB for
+ * arithmetic is at fp32 precision for both dtypes (on the bf16 matrix cores, every fp32 factor
+ * as the exact sum of three bf16 pieces).  Workspace of a PC_BF16 cache: 64 KB for
  * each block of 32 rows and query head, of at most 256 MB at a time (longer batches go in
  * several runs) and a quarter of that in reserve; it stays with the cache.  Where the device
  * has no room for it the batch goes in as many shorter runs as the workspace in hand allows. */
