@@ -24,6 +24,7 @@ namespace {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 template <int W> struct Vec;                             // W consecutive floats of a row
+template <> struct Vec<1> { using type = float; };
 template <> struct Vec<2> { using type = f32x2; };
 template <> struct Vec<4> { using type = f32x4; };
 
@@ -56,8 +57,12 @@ __device__ __forceinline__ i32x4 tile_at(const PcTile *tab, int t)
 // ------------------------------------------------------------------------------------------------------------ rows
 // A workgroup is one wave a SIMD (D = 128: all of its 512 registers) or two over the same 32 columns, whose queries (turned by their positions) and output
 // gradients lie in LDS as pieces; each wave walks a contiguous part of the item's tiles, once: its keys are turned to the call's
-// positions, and with w = p dp it collects Delta = sum w, sum w K and sum p K, of which dq = scale (sum w K - Delta sum p K)
-// once the waves' Deltas have met (a second walk with Delta known would make the scores again: five products a tile, not four).
+// positions, and with w = p (dp - c) it collects sum p, sum w, sum w K and sum p K.  Once the waves' Delta = sum w + c sum p have met,
+// dq = scale (sum w K - (Delta - c) sum p K)  (a second walk with Delta known would make the scores again: five products a tile, not four).
+// The centre c of a column is the wave's mean of dp under p, so that the sums grow and round like those of the centred terms p (dp - Delta):
+// values or output gradients with a common part make dp large against its spread, and keys have a mean under p.  It moves,
+// and the sums with it, whenever the walk is half as long again, and where sum w is more than half of sum |w|.  (1300 keys, D = 128, values
+// 3 + N(0,1), keys with +-1 a channel: dq 1.9e-6 from fp64, 4.9e-6 with c = 0, 2.0e-6 with two walks on the fp32 instruction.)
 // The vector work of a product's pieces stands beside the matrix work of the one before.  Two calls of 82 and 109 rows over 600
 // keys, 8/2 heads, D = 64: 27 us (52 with the fp32 instruction and two walks).
 template <int D> constexpr int row_waves = D == 64 ? 8 : 4;
@@ -92,7 +97,11 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
     const RowTile<D> keys(s_mem + 2 * PIECES_B + wave * RowTile<D>::BYTES, lane);           // the present tile's keys
     f32x4 rot;                                           // two pairs of a segment's rotation
     const unsigned rot_at = lane & (HALF / 2 - 1);
-    auto load_rot = [&](const i32x4 &d) { rot = reinterpret_cast<const f32x4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF)[rot_at]; };
+    auto load_rot = [&](const i32x4 &d) {
+        unsigned at = 16 * rot_at;
+        asm volatile("" : "+v"(at));
+        rot = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + at);
+    };
     auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot; };          // (a wave's own LDS accesses are in order)
     auto describe = [&](int t) { return tile_at(tab, min(t, item.tile_end - 1)); };
     i32x4 next = {0, 0, 0, 0};
@@ -123,18 +132,21 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         }
     }
     const bool live = alive(col0 + n);
-    const int64_t rh = row_head(live ? col0 + n : col0);
-    const float row_lse = live ? lse[rh] : 0.f;
+    const float row_lse = live ? lse[row_head(col0 + n)] : 0.f;
     const int row = (col0 + n) / g;
     const int self_lim = cd.self_len - cd.n_q + row;     // last own token this column sees
     const int lo_lim = cd.self_len - cd.n_q + col0 / g;  // ... the item's first column
     const bool some_dead = __builtin_amdgcn_ballot_w64(!live) != 0;
 
     // step j of the keys: dims 16 j + 8 hh + 0..7 of the lane's key and their partners, turned, into x and y
-    float4 k[4];
+    f32x4 k[4];
+    const unsigned dim_at = keys.lds + 4 * hh * (D * 4) + ((((HW * n) / 4) ^ (4 * hh)) << 4) + (HW * n) % 4 * 4;
+    const unsigned row_at = keys.lds + ((n * (D * 4) + ((n % RowTile<D>::CHUNKS) << 4)) ^ (hh << 5));
     auto read_k = [&](int p) {
+        unsigned at = row_at;
+        asm volatile("" : "+v"(at));                     // (one register, not one for every chunk)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) k[j] = keys.chunk(n, 4 * p + 2 * hh + (j & 1) + (j >> 1) * (HALF / 4));
+        for (int j = 0; j < 4; ++j) k[j] = from_lds<f32x4>(at ^ ((4 * p + (j & 1) + (j >> 1) * (HALF / 4)) << 4));
     };
     float x[8], y[8];
     auto turn = [&](int p) __attribute__((always_inline)) {
@@ -158,7 +170,8 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
     }
     __syncthreads();
 
-    float delta = 0.f;
+    float delta = 0.f, centre = 0.f, sum_w = 0.f, sum_p = 0.f, abs_w = 0.f;               // (sums of the lane's keys)
+    int due = t0;                                        // the tile at which the centre moves next
     f32x16 acc_w[VW], acc_p[VW];                         // sum w K and sum p K: block i (partners: i + HW), row nn: dim HW nn + i (+ HALF)
 #pragma unroll
     for (int i = 0; i < VW; ++i)
@@ -171,10 +184,12 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         f32x4 v[2 * NP][2];                              // step j of the values: dims 16 j + 8 hh + 0..7 of the lane's key
         {
             const float *vt = vb + (int64_t)d.x * D;     // (wave uniform)
+            unsigned v_at = 4 * (n * D + 8 * hh);
+            asm volatile("" : "+v"(v_at));               // (a 32-bit offset to a uniform address, not a pointer a lane)
 #pragma unroll
             for (int j = 0; j < 2 * NP; ++j)
 #pragma unroll
-                for (int u = 0; u < 2; ++u) v[j][u] = *reinterpret_cast<const f32x4 *>(vt + (16 * j + 4 * u) + (unsigned)(n * D + 8 * hh));
+                for (int u = 0; u < 2; ++u) v[j][u] = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(vt + (16 * j + 4 * u)) + v_at);
         }
         load_rot(next);
         auto value = [&](int j) {
@@ -204,6 +219,8 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
                 turn(p + 1);
                 kx = split8(x);
             } else {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(v[0][u]));           // (or they are cut, and waited for, as soon as they are requested)
                 value(0);
                 va = split8(x);
             }
@@ -212,18 +229,22 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         // the tile's keys once more, by dims: the lane's dims HW n .. + HW - 1 and their partners of key 8 (r / 4) + 4 hh + r % 4
         float kc[16][VW];
         float cs[2 * HW];                                // their rotation
+        unsigned dim_now = dim_at;
+        asm volatile("" : "+v"(dim_now));
         auto by_dim = [&](int r) {
-            const int key = 8 * (r >> 2) + 4 * hh + (r & 3);
+            constexpr int CHUNKS = RowTile<D>::CHUNKS;
+            const int c = 8 * (r >> 2) + (r & 3);        // (the key but for the lane's 4 hh)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const unsigned char *a = keys.at + key * (D * 4) + ((((HW * n) / 4 + u * (HALF / 4)) ^ (key % RowTile<D>::CHUNKS)) << 4) + (HW * n) % 4 * 4;
+                const auto x = from_lds<typename Vec<HW>::type>((dim_now ^ (((u * (HALF / 4)) ^ (c % CHUNKS)) << 4)) + c * (D * 4));
 #pragma unroll
-                for (int i = 0; i < HW; ++i) kc[r][u * HW + i] = reinterpret_cast<const float *>(a)[i];
+                for (int i = 0; i < HW; ++i) kc[r][u * HW + i] = reinterpret_cast<const float *>(&x)[i];
             }
         };
 #pragma unroll
         for (int j = 0; j < 2 * NP; ++j) {
             __builtin_amdgcn_sched_barrier(0);
+            if (j == 1) s += s1;                         // (16 registers less)
             bf16x8 b[3] = {bn[0], bn[1], bn[2]};
             if (j + 1 < 2 * NP) load_b(s_gp, j + 1);
 #pragma unroll
@@ -239,26 +260,46 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
 #pragma unroll
         for (int i = 0; i < 2 * HW; ++i) cs[i] = reinterpret_cast<const float *>(&s_rot[wave][HW * n])[i];
         __builtin_amdgcn_sched_barrier(0);
-        s += s1;
         dp += dp1;
         const int valid = d.w & 0xFF, key0 = d.y;
         const bool self = (d.w & PC_TILE_SELF) != 0;
         float ps[16], w[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { ps[r] = exp_x(fmaf(s[r], scale, -row_lse)); w[r] = ps[r] * dp[r]; }
+        for (int r = 0; r < 16; ++r) ps[r] = exp_x(fmaf(s[r], scale, -row_lse));
         if (valid < PC_TILE || some_dead || (self && key0 + valid - 1 > lo_lim)) {        // (uniform over the wave)
             const int lim = !live ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const bool seen = 8 * (r >> 2) + 4 * hh + (r & 3) < lim;
                 ps[r] = seen ? ps[r] : 0.f;
-                w[r] = seen ? w[r] : 0.f;
+                dp[r] = seen ? dp[r] : 0.f;
             }
         }
-        float w8[8];                                     // (a tile's terms in pairs: a chain of them would round 16 times as often)
+        auto sum16 = [](auto f) __attribute__((always_inline)) {            // (a tile's terms in pairs: a chain of them would round 16 times as often)
+            float a[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) w8[r] = w[r] + w[r + 8];
-        delta += ((w8[0] + w8[4]) + (w8[1] + w8[5])) + ((w8[2] + w8[6]) + (w8[3] + w8[7]));
+            for (int r = 0; r < 8; ++r) a[r] = f(r) + f(r + 8);
+            return ((a[0] + a[4]) + (a[1] + a[5])) + ((a[2] + a[6]) + (a[3] + a[7]));
+        };
+#pragma unroll
+        for (int r = 0; r < 16; ++r) w[r] = ps[r] * (dp[r] - centre);
+        sum_p += sum16([&](int r) { return ps[r]; });
+        sum_w += sum16([&](int r) { return w[r]; });
+        abs_w += sum16([&](int r) { return fabsf(w[r]); });
+        if (t >= due || __builtin_amdgcn_ballot_w64(fabsf(sum_w) > 0.5f * abs_w) != 0) {
+            due = t + 1 + (t - t0) / 2;
+            const float all_w = sum_w + __shfl_xor(sum_w, 32), all_p = sum_p + __shfl_xor(sum_p, 32);      // of the column: both halves of the wave
+            const float moved = centre + (all_p > 1e-30f ? all_w * __builtin_amdgcn_rcpf(all_p) : 0.f), by = moved - centre;
+            centre = moved;
+            sum_w = fmaf(-by, sum_p, sum_w);
+            abs_w = fmaxf(fmaf(-fabsf(by), sum_p, abs_w), 0.f);             // (what it is at least)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[r] = fmaf(-by, ps[r], w[r]);
+#pragma unroll
+            for (int i = 0; i < VW; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_w[i][r] = fmaf(-by, acc_p[i][r], acc_w[i][r]);
+        }
         // the next tile's keys: everything the wave has asked memory for has landed, and the present tile has been read
         asm volatile("" : "+v"(rot));
         __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
@@ -302,6 +343,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
             beside<12, 8>();
         }
     }
+    delta = fmaf(centre, sum_p, sum_w);
     delta += __shfl_xor(delta, 32);
     if (hh == 0) s_delta[wave][n] = delta;
     // The pieces of an Inf or NaN are not its parts: if a wave met one, be it behind a row's own token, all walk their tiles
@@ -313,25 +355,34 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         for (int r = 0; r < 16; ++r) odd = fmaf(acc_w[i][r], 0.f, fmaf(acc_p[i][r], 0.f, odd));
     if (__builtin_amdgcn_ballot_w64(odd != 0.f) != 0 && lane == 0) s_odd = 1;
     __syncthreads();
+    // (what follows is addressed anew: with the walk's own addresses the compiler keeps 40 registers for it through the walk, in scratch)
+    unsigned tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int end_n = tid & 31, end_hh = (tid >> 5) & 1;
     if (s_odd == 0) {
         delta = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) delta += s_delta[w][n];
+        for (int w = 0; w < NW; ++w) delta += s_delta[w][end_n];
+        const float off = delta - centre;
         if (t0 < t1)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                float *p = &s_dq[wave][n * PITCH + HW * (8 * (r >> 2) + 4 * hh + (r & 3))];
+                float *p = &s_dq[wave][end_n * PITCH + HW * (8 * (r >> 2) + 4 * end_hh + (r & 3))];
 #pragma unroll
                 for (int i = 0; i < HW; ++i) {
-                    p[i] = fmaf(-delta, acc_p[i][r], acc_w[i][r]) * scale;
-                    p[HALF + i] = fmaf(-delta, acc_p[HW + i][r], acc_w[HW + i][r]) * scale;
+                    p[i] = fmaf(-off, acc_p[i][r], acc_w[i][r]) * scale;
+                    p[HALF + i] = fmaf(-off, acc_p[HW + i][r], acc_w[HW + i][r]) * scale;
                 }
             }
     } else {
         // the queries are turned to a segment's frame at every new rotation; dq is collected in that frame and turned back into the
         // wave's own part of LDS
+        const int n = end_n, hh = end_hh, row = (col0 + n) / g, self_lim = cd.self_len - cd.n_q + row;
+        const bool live = alive(col0 + n);
+        const int64_t rh = row_head(live ? col0 + n : col0);
+        const float row_lse = live ? lse[rh] : 0.f;
         float *const s_g = reinterpret_cast<float *>(s_mem) + NW * 32 * PITCH;               // the columns' output gradients
-        for (int e = threadIdx.x; e < 32 * (D / 4); e += 64 * NW) {
+        for (int e = tid; e < 32 * (D / 4); e += 64 * NW) {
             const int c = e / (D / 4), i = 4 * (e % (D / 4));
             float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
             if (alive(col0 + c)) {
@@ -490,10 +541,10 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         }
         if (cur >= 0) flush(cur);
     }
-    if (wave == 0 && hh == 0 && col0 + n < n_cols) delta_out[row_head(col0 + n)] = live ? delta : 0.f;
+    if (tid < 32 && col0 + end_n < n_cols) delta_out[row_head(col0 + end_n)] = alive(col0 + end_n) ? delta : 0.f;
     __syncthreads();
     const int n_waves = min(NW, n_tiles);                // those that had tiles
-    for (int e = threadIdx.x; e < 32 * (D / 8); e += 64 * NW) {             // 4 pairs of a column a step
+    for (int e = tid; e < 32 * (D / 8); e += 64 * NW) {             // 4 pairs of a column a step
         const int c = e / (D / 8), i = 4 * (e % (D / 8)), col = col0 + c;
         if (col >= n_cols) break;                        // (columns ascend with e)
         float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;

@@ -62,6 +62,8 @@ __device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_o
 }
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+template <typename T> __device__ __forceinline__ T from_lds(unsigned at) { return *reinterpret_cast<const __attribute__((address_space(3))) T *>((uintptr_t)at); }
+
 // A wave's tile of 32 fp32 rows of D, brought to LDS by direct loads of whole rows (a lane that fetches its own row's pieces
 // touches 32 lines an instruction: two cycles each of the CU's memory pipeline).  Chunk c (16 bytes) of row r sits at position
 // c ^ (r % CHUNKS) of the row: 16 lanes that read one chunk of 16 rows hit different banks.
@@ -75,6 +77,8 @@ struct RowTile {
     __device__ void request(const float *rows) const     // (wave uniform)
     {
         constexpr int STEP = 64 / CHUNKS;                // rows of an instruction
+        unsigned src = this->src;
+        asm volatile("" : "+v"(src));                    // (or the exclusive ors below wait in registers, or in scratch, from tile to tile)
 #pragma unroll
         for (int i = 0; i < 32 / STEP; ++i) dma16(rows + STEP * i * D, src ^ (((STEP * i) % CHUNKS) << 4), lds + i * 1024);
     }

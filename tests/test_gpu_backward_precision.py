@@ -33,8 +33,8 @@ def rot(x, pos, theta):
     return torch.cat([lo * c - hi * s, lo * s + hi * c], -1)
 
 
-def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(), seed=5, capacity=None, bar=BAR):
-    """lens: messages; calls: (sel, self, self_start, n_q)."""
+def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(), seed=5, capacity=None, bar=BAR, off=(0.0, 0.0)):
+    """lens: messages; calls: (sel, self, self_start, n_q); off: what all values have in common, and the keys' channels (with either sign)."""
     import torch
     from paper_2512_23049_amd import binding
     from pc_inputs import Call
@@ -49,6 +49,8 @@ def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(
     cache = binding.Cache(h_q, h_kv, D, cfg.dtype, theta, cap, len(lens) + 1, max_position=1 << 20, arena=arena.data_ptr(), arena_bytes=nbytes)
     for L in lens:
         k, v = normal(L, h_kv, D), normal(L, h_kv, D)
+        k += off[1] * torch.tensor([1.0, -1.0, -1.0, 1.0], device="cuda:0").repeat(D // 4)
+        v += off[0]
         cache.append_message(k.data_ptr(), v.data_ptr(), L)
         torch.cuda.synchronize()
     for m, b in bases:

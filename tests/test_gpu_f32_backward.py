@@ -30,6 +30,17 @@ def test_many_blocks_over_a_long_history():
     run_case(lens, [([(m, 300 * m) for m in range(30)], 30, 13000, 300)], 8, 2, dtype="f32", D=64)
 
 
+# Values v0 + N(0,1) and keys k0 + N(0,1): dO . v is rounded at sqrt(1 + v0^2) times the size of its spread, which is all that ds = p (dp - Delta)
+# keeps of it, and times keys sqrt(1 + k0^2) times as large as their own spread: the ten roundings of 2^-24 times both factors.  (Sums of
+# p dp K and p K whose difference is taken at their end are at twice to three times that: 4.9e-6 for the last shape at 3, 1.)
+@pytest.mark.parametrize("off", [(1.0, 1.0), (3.0, 0.0), (3.0, 1.0), (10.0, 0.0), (0.0, 3.0)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_values_and_keys_with_a_common_part(D, off):
+    bar = 10 * 2.0 ** -24 * ((1 + off[0] ** 2) * (1 + off[1] ** 2)) ** 0.5
+    run_case([500, 90], [([(0, 0)], 1, 500, 90)], 4, 2, dtype="f32", D=D, off=off, bar=bar)
+    run_case([300, 1000, 40], [([(0, 3), (1, 300)], 2, 1400, 40)], 8, 2, dtype="f32", D=D, off=off, bar=bar)
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 128)])
 def test_later_tokens_that_are_not_finite(dtype, D):
     """What stands behind a row's own token does not reach its gradient."""
