@@ -63,6 +63,9 @@ __device__ __forceinline__ i32x4 tile_at(const PcTile *tab, int t)
 // values or output gradients with a common part make dp large against its spread, and keys have a mean under p.  It moves,
 // and the sums with it, whenever the walk is half as long again, and where sum w is more than half of sum |w|.  (1300 keys, D = 128, values
 // 3 + N(0,1), keys with +-1 a channel: dq 1.9e-6 from fp64, 4.9e-6 with c = 0, 2.0e-6 with two walks on the fp32 instruction.)
+// A product for sum w K is made from zero and added: a matrix instruction that takes the long sum along rounds it several times,
+// six times a product (100 thousand keys, D = 128: 1.0e-6 from fp64, 3.0e-6 with the sum taken along, 2.1e-6 with two walks on the fp32
+// instruction; a million, D = 64: 2.6e-6, 1.3e-5, 6.7e-6).  sum p K is all but cancelled by the centre and takes it along.
 // The vector work of a product's pieces stands beside the matrix work of the one before.  Two calls of 82 and 109 rows over 600
 // keys, 8/2 heads, D = 64: 27 us (52 with the fp32 instruction and two walks).
 template <int D> constexpr int row_waves = D == 64 ? 8 : 4;
@@ -312,6 +315,9 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
                 turn2(x[j], y[j], x[j + 1], y[j + 1], make_float4(cs[2 * i], cs[2 * i + 1], cs[2 * i], cs[2 * i + 1]));
             }
         };
+        f32x16 zero16;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) zero16[r] = 0.f;
         Pieces pw = split8(w), pp = split8(ps), pw1, pp1;
         column(0, 0);
         kx = split8(x);
@@ -319,7 +325,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         for (int u = 0; u < 2 * HW; ++u) {               // (16 keys, pair block)
             const int kk = u / HW, i = u % HW;
             __builtin_amdgcn_sched_barrier(0);
-            acc_w[i] = product(kx, pw.p, acc_w[i]);
+            acc_w[i] += product(kx, pw.p, zero16);
             acc_p[i] = product(kx, pp.p, acc_p[i]);
             const Pieces ky = split8(y);
             if (u == 0) pw1 = split8(w + 8);
@@ -330,7 +336,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
                 wait_vm0();
                 read_k(0);
             }
-            acc_w[HW + i] = product(ky, pw.p, acc_w[HW + i]);
+            acc_w[HW + i] += product(ky, pw.p, zero16);
             acc_p[HW + i] = product(ky, pp.p, acc_p[HW + i]);
             if (u == 0) pp1 = split8(ps + 8);
             if (u + 1 < 2 * HW) column((u + 1) / HW, (u + 1) % HW);

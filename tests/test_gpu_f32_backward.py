@@ -41,6 +41,12 @@ def test_values_and_keys_with_a_common_part(D, off):
     run_case([300, 1000, 40], [([(0, 3), (1, 300)], 2, 1400, 40)], 8, 2, dtype="f32", D=D, off=off, bar=bar)
 
 
+@pytest.mark.parametrize("D,h_kv", [(64, 2), (128, 2)])
+def test_long_walk(D, h_kv):
+    # the ten roundings a term, and the sum's own: one per 16 keys, of which a wave has 100 thousand in 8 (4) parts: sqrt(1563) * 2^-25 = 1.2e-6
+    run_case([100000, 9], [([(0, -500)], 1, 300000, 9)], 4, h_kv, dtype="f32", D=D, bar=10 * 2.0 ** -24 + 1563 ** 0.5 * 2.0 ** -25)
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 128)])
 def test_later_tokens_that_are_not_finite(dtype, D):
     """What stands behind a row's own token does not reach its gradient."""
