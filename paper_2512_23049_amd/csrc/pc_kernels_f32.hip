@@ -104,7 +104,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
                 y[j] = x0 * cs.y + y0 * cs.x; y[j + 1] = x1 * cs.w + y1 * cs.z;
             }
         }
-        const Pieces px = split8<true>(x), py = split8<true>(y);
+        const Pieces px = split8(x), py = split8(y);
 #pragma unroll
         for (int w = 0; w < 3; ++w) {
             s_qp[w][i / 16][(i / 8 % 2) * 32 + c] = px.p[w];
@@ -264,8 +264,9 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
             beside<6, 8>();
         }
     }
-    // The pieces of an Inf or NaN are not its parts: a wave that met one, be it in a key that counts or in the value of a token
-    // behind a row's own, which no probability of zero takes out of a product, walks its tiles again on the fp32 instruction.
+    // The pieces of an Inf or NaN are not its parts, nor are those of a number that rounds to one in bf16 (3.4e38): a wave that met one, be it in
+    // a query, a key that counts or the value of a token behind a row's own, which no probability of zero takes out of a
+    // product, walks its tiles again on the fp32 instruction, with the caller's queries.
     // There a probability of zero takes a key out of the second product only while its value is finite.  What lies behind a
     // message's last token is (the store is kept that way), but a later token of the new message is the caller's own
     // data: in a tile on the causal limit an Inf or NaN is left out and added at the end, for the columns that see its key.
@@ -276,14 +277,18 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
 #pragma unroll
         for (int r = 0; r < 16; ++r) odd_sum = fmaf(acc[i][r], 0.f, odd_sum);
     if (__builtin_amdgcn_ballot_w64(odd_sum != 0.f) != 0) {
-        auto query = [&](int dim) {                      // dims dim .. dim + 3 of the lane's column, from their pieces
-            float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int w = 0; w < 3; ++w) {
-                const uint2 u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(&s_qp[w][dim / 16][(dim / 8 % 2) * 32 + n]) + 2 * (dim % 8));
-                r.x += bf_lo(u.x); r.y += bf_hi(u.x); r.z += bf_lo(u.y); r.w += bf_hi(u.y);
-            }
-            return r;
+        const bool there = col0 + n < n_cols;
+        const int col = there ? col0 + n : col0;
+        const float *qr = (const float *)L.q + ((int64_t)(cd.q_off + col / g) * L.n_q_heads + kh * g + col % g) * D + 4 * hh;
+        const float4 *rq = reinterpret_cast<const float4 *>(L.rot_q + (int64_t)(cd.q_off + col / g) * HALF) + 2 * hh;
+        auto query = [&](float4 &a, float4 &b, int j) {                     // dims 8 j + 4 hh + 0..3 of the lane's column and their partners, turned by its position
+            a = b = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!there) return;
+            const float4 c0 = rq[4 * j], c1 = rq[4 * j + 1];
+            const float x[4] = {qr[8 * j], qr[8 * j + 1], qr[8 * j + 2], qr[8 * j + 3]};
+            const float y[4] = {qr[8 * j + HALF], qr[8 * j + HALF + 1], qr[8 * j + HALF + 2], qr[8 * j + HALF + 3]};
+            a = make_float4(x[0] * c0.x - y[0] * c0.y, x[1] * c0.z - y[1] * c0.w, x[2] * c1.x - y[2] * c1.y, x[3] * c1.z - y[3] * c1.w);
+            b = make_float4(x[0] * c0.y + y[0] * c0.x, x[1] * c0.w + y[1] * c0.z, x[2] * c1.y + y[2] * c1.x, x[3] * c1.w + y[3] * c1.z);
         };
         clear();
         for (int t = t0; t < t1; ++t) {
@@ -291,17 +296,20 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
             const bool causal = on_limit(d);
             const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + 2 * hh;
             const float *kr = kb + ((int64_t)d.x + n) * D + 4 * hh, *vr = vb + (int64_t)d.x * D + v_at;
-            f32x16 s;
+            f32x16 s, s1;                                // (two chains, as above)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+            for (int r = 0; r < 16; ++r) s[r] = s1[r] = 0.f;
+#pragma unroll 1
             for (int j = 0; j < NJ / 2; ++j) {           // the queries turned by -(segment start - stored base)
-                const float4 a = query(8 * j + 4 * hh), b = query(HALF + 8 * j + 4 * hh);
+                float4 a, b;
+                query(a, b, j);
                 const float4 c0 = rs[4 * j], c1 = rs[4 * j + 1], x = *reinterpret_cast<const float4 *>(kr + 8 * j), y = *reinterpret_cast<const float4 *>(kr + 8 * j + HALF);
                 s = MFMA_F32(x.x, a.x * c0.x + b.x * c0.y, s); s = MFMA_F32(x.y, a.y * c0.z + b.y * c0.w, s);
                 s = MFMA_F32(x.z, a.z * c1.x + b.z * c1.y, s); s = MFMA_F32(x.w, a.w * c1.z + b.w * c1.w, s);
-                s = MFMA_F32(y.x, b.x * c0.x - a.x * c0.y, s); s = MFMA_F32(y.y, b.y * c0.z - a.y * c0.w, s);
-                s = MFMA_F32(y.z, b.z * c1.x - a.z * c1.y, s); s = MFMA_F32(y.w, b.w * c1.z - a.w * c1.w, s);
+                s1 = MFMA_F32(y.x, b.x * c0.x - a.x * c0.y, s1); s1 = MFMA_F32(y.y, b.y * c0.z - a.y * c0.w, s1);
+                s1 = MFMA_F32(y.z, b.z * c1.x - a.z * c1.y, s1); s1 = MFMA_F32(y.w, b.w * c1.z - a.w * c1.w, s1);
             }
+            s += s1;
             softmax(s, d, causal);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {

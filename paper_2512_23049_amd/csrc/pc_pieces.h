@@ -13,23 +13,21 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // numbers: what is left out is below 2^-25 of it, half of what rounding it to fp32 costs.  Six bf16 MFMAs take 192 cycles for
 // 32 x 32 x 16, the fp32 instruction 512.
 struct Pieces { bf16x8 p[3]; };
-template <bool ODD = false>                              // ODD: an Inf or NaN is its own first piece, the others are zeros
 __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[3])
 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         w[i] = pack_bf16(a, b);
         asm("" : "+v"(w[i]));                            // (or the lower piece is rounded a second time, by an instruction of its own)
-        a = ODD && !(fabsf(a) < INFINITY) ? 0.f : a - bf_lo(w[i]);
-        b = ODD && !(fabsf(b) < INFINITY) ? 0.f : b - bf_hi(w[i]);
+        a -= bf_lo(w[i]);
+        b -= bf_hi(w[i]);
     }
 }
-template <bool ODD = false>
 __device__ __forceinline__ Pieces split8(const float *v)
 {
     uint32_t w[4][3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split2<ODD>(v[2 * j], v[2 * j + 1], w[j]);
+    for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], w[j]);
     Pieces r;
 #pragma unroll
     for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]));

@@ -1,9 +1,9 @@
 """The attention of fp32 caches against the oracle (numpy, fp64) at the edges of its tiles: columns are (row, head) pairs in
 blocks of 32, keys come in tiles of 32 of which eight waves take an eighth each, few columns split the tiles further.
 
-Bound: products are fp32 and sums of D = 128 terms, a few thousand keys follow each other, the keys are turned once and the
-queries twice by rotations rounded to fp32: about ten roundings of 2^-24 a term, 6e-7 in the 2-norm (4e-7 measured); the bar
-is 3e-6."""
+Bound: products are fp32 and sums of D = 128 terms, a few thousand keys follow each other, the keys are turned twice (as they are
+stored, and to the call's positions) and the queries once by rotations rounded to fp32: about ten roundings of 2^-24 a term, 6e-7 in the
+2-norm (4e-7 measured); the bar is 3e-6."""
 import sys
 
 import numpy as np
@@ -18,8 +18,8 @@ def say(*a):
     sys.stdout.flush()
 
 
-def run_case(lens, calls, h_q, h_kv, D, spoil=None, seed=7, static=False):
-    """lens: messages; calls: (sel, self, self_start, n_q); spoil(ks, vs): puts values into the caller's data."""
+def run_case(lens, calls, h_q, h_kv, D, spoil=None, seed=7, static=False, spoil_q=None):
+    """lens: messages; calls: (sel, self, self_start, n_q); spoil(ks, vs), spoil_q(q): put values into the caller's data."""
     import torch
     from oracle import choreo_oracle as orc
     from paper_2512_23049_amd import binding
@@ -37,6 +37,8 @@ def run_case(lens, calls, h_q, h_kv, D, spoil=None, seed=7, static=False):
         torch.cuda.synchronize()
     rows = sum(c[3] for c in calls)
     q = rng.standard_normal((rows, h_q, D)).astype(np.float32)
+    if spoil_q:
+        spoil_q(q)
     tq = torch.from_numpy(q).cuda()
     out = torch.full((rows, h_q, D), 7.0, device="cuda:0")
     lse = torch.full((rows, h_q), 7.0, device="cuda:0")

@@ -24,6 +24,28 @@ def test_magnitudes(D, size):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n_tok", [50])
+@pytest.mark.parametrize("where", ["query", "key"])
+def test_largest_numbers(D, n_tok, where):
+    """3.4e38 is finite but rounds to infinity in bf16.  In the slowest pair, where the other side holds numbers of 3e-38: scores of order one."""
+    big, half = np.float32(3.4e38), D // 2
+
+    def spoil(ks, vs):
+        if where == "key":
+            ks[0][7, :, half - 1], ks[0][7, :, D - 1] = big, 0
+        else:
+            for k in ks:
+                k[..., half - 1::half] *= np.float32(3e-38)
+
+    def spoil_q(q):
+        if where == "query":
+            q[5, 0, half - 1], q[5, 0, D - 1], q[33, 3, half - 1], q[33, 3, D - 1] = big, 0, -big, 0
+        else:
+            q[..., half - 1::half] *= np.float32(3e-38)
+    check(run_case([n_tok, 64], [([(0, 0)], 1, n_tok, 64)], 4, 2, D, spoil, spoil_q=spoil_q))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("n_tok", [40, 700])
 def test_infinite_key(D, n_tok):
     from oracle import choreo_oracle as orc
