@@ -45,6 +45,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     __shared__ __attribute__((aligned(1024))) unsigned char s_mem[3 * 2 * NP * 1024 + NW * RowTile<D>::BYTES];
     __shared__ __attribute__((aligned(16))) float2 s_rot[NW][HALF];         // the rotation of each wave's segment
     __shared__ float s_m[NW][32], s_l[NW][32];
+    __shared__ int s_again;
     bf16x8 (*const s_qp)[2 * NP][64] = reinterpret_cast<bf16x8 (*)[2 * NP][64]>(s_mem);     // [piece][16 dims][lane]
     float (*const s_acc)[32 * PITCH] = reinterpret_cast<float (*)[32 * PITCH]>(s_mem);
     static_assert(sizeof(float) * NW * 32 * PITCH <= sizeof s_mem, "");
@@ -69,21 +70,29 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(tab + tc));
     };
     i32x4 next = describe(t0);                           // {slot0, key0, seg, valid | flags}
+    if (threadIdx.x == 0) s_again = 0;
 
     using VV = typename Vec<VW>::type;
     const float *kb = (const float *)L.k_store + (int64_t)kh * L.slots * D, *vb = (const float *)L.v_store + (int64_t)kh * L.slots * D;
     const unsigned v_at = 4 * hh * D + VW * n;           // within a tile: the lane's dims VW n + 0..VW-1
     const RowTile<D> keys(s_mem + 3 * 2 * NP * 1024 + wave * RowTile<D>::BYTES, lane);      // the present tile's keys
     auto request_k = [&](int slot0) { keys.request(kb + (int64_t)slot0 * D); };
-    float4 k[4];                                         // step p of the present tile: dims 16 p + 8 hh + 0..7 of the lane's key and their partners
+    f32x4 k[4];                                          // step p of the present tile: dims 16 p + 8 hh + 0..7 of the lane's key and their partners
+    const unsigned row_at = keys.lds + ((n * (D * 4) + ((n % RowTile<D>::CHUNKS) << 4)) ^ (hh << 5));
     auto read_k = [&](int p) {
+        unsigned at = row_at;
+        asm volatile("" : "+v"(at));                     // (one register, not one for every chunk)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) k[j] = keys.chunk(n, 4 * p + 2 * hh + (j & 1) + (j >> 1) * (HALF / 4));
+        for (int j = 0; j < 4; ++j) k[j] = from_lds<f32x4>(at ^ ((4 * p + (j & 1) + (j >> 1) * (HALF / 4)) << 4));
     };
     f32x4 rot;                                           // two pairs of a segment's rotation
     const unsigned rot_at = lane & (HALF / 2 - 1);
-    auto load_rot = [&](const i32x4 &d) { rot = reinterpret_cast<const f32x4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF)[rot_at]; };
-    auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot; };          // (a wave's own LDS accesses are in order)
+    auto load_rot = [&](const i32x4 &d) {
+        unsigned at = 16 * rot_at;
+        asm volatile("" : "+v"(at));                     // (a 32-bit offset to a uniform address, not a pointer a lane)
+        rot = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + at);
+    };
+    auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot * UP; };     // (a wave's own LDS accesses are in order)
     if (t0 < t1) { request_k(next.x); load_rot(next); }
 
     for (int e = threadIdx.x; e < 32 * (HALF / 8); e += 64 * NW) {          // 8 pairs of a column a step
@@ -98,7 +107,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
             const float4 *rot = reinterpret_cast<const float4 *>(L.rot_q + R * HALF + i);
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {
-                const float4 cs = rot[j / 2];
+                const float4 cs = up(rot[j / 2]);
                 const float x0 = q[j], x1 = q[j + 1], y0 = q[j + HALF], y1 = q[j + HALF + 1];
                 x[j] = x0 * cs.x - y0 * cs.y; x[j + 1] = x1 * cs.z - y1 * cs.w;
                 y[j] = x0 * cs.y + y0 * cs.x; y[j + 1] = x1 * cs.w + y1 * cs.z;
@@ -134,6 +143,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     const int row = (col0 + n) / g;
     const int self_lim = cd.self_len - cd.n_q + row;     // last own token this column sees
     const int lo_lim = cd.self_len - cd.n_q + col0 / g;              // ... the item's first column
+    const bool sees = t0 < t1 && !((next.w & PC_TILE_SELF) != 0 && next.y > self_lim);      // a key of the wave's
     float m_run = -INFINITY, l_run = 0.f;
     f32x16 acc[VW];
     auto clear = [&]() {
@@ -145,10 +155,10 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     };
     clear();
     // scores scaled and masked, the running maximum and sum, the accumulators' factor: s becomes the probabilities
-    auto softmax = [&](f32x16 &s, const i32x4 &d, bool causal) __attribute__((always_inline)) {
+    auto softmax = [&](f32x16 &s, float scale, const i32x4 &d, bool causal) __attribute__((always_inline)) {
         const int valid = d.w & 0xFF, lim = (d.w & PC_TILE_SELF) ? min(valid, self_lim - d.y + 1) : valid;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] *= L.scale_log2;
+        for (int r = 0; r < 16; ++r) s[r] *= scale;
         if (valid < PC_TILE || causal) {                 // (uniform over the wave)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = (8 * (r >> 2) + 4 * hh + (r & 3) < lim) ? s[r] : -INFINITY;
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         }
         __builtin_amdgcn_sched_barrier(0);
         s += s1;
-        softmax(s, d, on_limit(d));
+        softmax(s, L.scale_log2 * (1.f / (UP * UP)), d, on_limit(d));
         // the next tile's keys: the values and the rotation have landed by then, so that no wait for them waits for the keys as well
         // (behind the last tile the present one is turned and cut once more, and not used)
 #pragma unroll
@@ -264,24 +274,108 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
             beside<6, 8>();
         }
     }
-    // The pieces of an Inf or NaN are not its parts, nor are those of a number that rounds to one in bf16 (3.4e38): a wave that met one, be it in
+    // The waves' results meet in LDS: element (i, r) of a lane is dim VW (8 (r / 4) + 4 hh + r % 4) + i of column n; then 16 threads a column take
+    // dims 4 sub + 64 i.
+    //
+    // The pieces of an Inf or NaN are not its parts, nor are those of a number that rounds to one in bf16 (3.4e38): a workgroup that met one, be it in
     // a query, a key that counts or the value of a token behind a row's own, which no probability of zero takes out of a
-    // product, walks its tiles again on the fp32 instruction, with the caller's queries.
+    // product, walks its tiles again on the fp32 instruction, with the caller's queries.  So does one with a result below 2^-100 that is not
+    // zero, whose values may be below 2^-110 and have bits behind their pieces' last ones, and one with a wave whose column sees keys and has met none:
+    // their scores may be below -2^96, infinities times UP twice.  What no number gives is found in the results: 8 (4) of them a thread there,
+    // 64 (32) in the waves' accumulators, which took 0.6 us to look through.
     // There a probability of zero takes a key out of the second product only while its value is finite.  What lies behind a
     // message's last token is (the store is kept that way), but a later token of the new message is the caller's own
     // data: in a tile on the causal limit an Inf or NaN is left out and added at the end, for the columns that see its key.
+    // (addressed anew: with the walk's own addresses the compiler keeps registers for all of this through the walk)
+    unsigned tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int c = tid >> 4, sub = tid & 15, end_col = col0 + c;
+    const int end_n = tid & 31, end_hh = (tid >> 5) & 1;
     bool odd = false;
-    float odd_sum = 0.f * l_run;
+    for (bool slow = false;; slow = true) {
+        __syncthreads();                                 // (the queries' pieces make room for the results)
+        l_run += other_half(l_run);
+        if (end_hh == 0) { s_m[wave][end_n] = m_run; s_l[wave][end_n] = l_run; }
+        if (sees && m_run == -INFINITY) s_again = 1;
 #pragma unroll
-    for (int i = 0; i < VW; ++i)
+        for (int r = 0; r < 16; ++r) {
+            VV z;
+            float *x = reinterpret_cast<float *>(&z);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) odd_sum = fmaf(acc[i][r], 0.f, odd_sum);
-    if (__builtin_amdgcn_ballot_w64(odd_sum != 0.f) != 0) {
+            for (int i = 0; i < VW; ++i) x[i] = acc[i][r];
+            *reinterpret_cast<VV *>(&s_acc[wave][end_n * PITCH + VW * (8 * (r >> 2) + 4 * end_hh + (r & 3))]) = z;
+        }
+        if (__builtin_amdgcn_ballot_w64(odd) != 0) {     // (the probability has no say in an Inf or NaN; a wave's own LDS accesses are in order)
+            for (int t = t0; t < t1; ++t) {
+                const i32x4 d = describe(t);
+                if (!(d.w & PC_TILE_SELF) || d.y + (d.w & 0xFF) - 1 <= lo_lim) continue;
+                const int lim = min(d.w & 0xFF, self_lim - d.y + 1);
+                const float *vr = (const float *)L.v_store + ((int64_t)kh * L.slots + d.x) * D;
+                for (int e = end_hh; e < lim * D; e += 2) {
+                    const float x = vr[e];
+                    if (!(fabsf(x) < INFINITY)) s_acc[wave][end_n * PITCH + e % D] += x;
+                }
+            }
+        }
+        __syncthreads();
+        float mm = s_m[0][c], l = 0.f;
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][c]);
+        float4 o[D / 64];
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (mm > -INFINITY) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (!(s_m[w][c] > -INFINITY)) { l += s_l[w][c]; continue; }        // saw nothing: a sum of 0 (or NaN, which stays)
+                const float f = ex2(s_m[w][c] - mm);
+                l = fmaf(s_l[w][c], f, l);
+#pragma unroll
+                for (int i = 0; i < D / 64; ++i) {
+                    const float4 a = *reinterpret_cast<const float4 *>(&s_acc[w][c * PITCH + 64 * i + 4 * sub]);
+                    o[i].x = fmaf(a.x, f, o[i].x); o[i].y = fmaf(a.y, f, o[i].y); o[i].z = fmaf(a.z, f, o[i].z); o[i].w = fmaf(a.w, f, o[i].w);
+                }
+            }
+        } else if (!slow) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) l += s_l[w][c]; // (only a NaN is seen in it)
+        }
+        bool again = false;
+        if (end_col < n_cols) {
+            const int r = end_col / g, h = kh * g + end_col % g;
+            again = !(l < INFINITY);
+            const bool whole = cd.n_splits == 1;
+            const int64_t at = (whole ? (int64_t)(cd.q_off + r) : (int64_t)cd.part_off + (int64_t)item.split * cd.n_q + r) * L.n_q_heads + h;
+#pragma unroll
+            for (int i = 0; i < D / 64; ++i) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float x = fabsf((&o[i].x)[j]);
+                    again |= !(x < INFINITY) || (x < 0x1p-100f && x > 0.f);
+                }
+                if (whole) {
+                    if (l > 0.f) { o[i].x /= l; o[i].y /= l; o[i].z /= l; o[i].w /= l; }
+                    else o[i] = make_float4(0.f, 0.f, 0.f, 0.f);            // nothing visible (or a NaN score)
+                    float *out = (float *)L.out + at * D + 64 * i + 4 * sub;
+                    out[0] = o[i].x; out[1] = o[i].y; out[2] = o[i].z; out[3] = o[i].w;
+                } else *reinterpret_cast<float4 *>((float *)L.part_o + at * D + 64 * i + 4 * sub) = o[i];
+            }
+            if (sub == 0) {
+                if (!whole) { L.part_ml[at * 2] = mm; L.part_ml[at * 2 + 1] = l; }
+                else if (L.lse) L.lse[at] = (l > 0.f) ? (mm + log2f(l)) * 0.6931471805599453f : -INFINITY;
+            }
+        }
+        if (slow) return;
+        if (again) s_again = 1;
+        __syncthreads();
+        if (__builtin_expect(s_again == 0, 1)) return;
+        const int n = end_n, hh = end_hh;
+        const unsigned v_at = 4 * hh * D + VW * n;
         const bool there = col0 + n < n_cols;
         const int col = there ? col0 + n : col0;
         const float *qr = (const float *)L.q + ((int64_t)(cd.q_off + col / g) * L.n_q_heads + kh * g + col % g) * D + 4 * hh;
         const float4 *rq = reinterpret_cast<const float4 *>(L.rot_q + (int64_t)(cd.q_off + col / g) * HALF) + 2 * hh;
-        auto query = [&](float4 &a, float4 &b, int j) {                     // dims 8 j + 4 hh + 0..3 of the lane's column and their partners, turned by its position
+        auto query = [&](float4 &a, float4 &b, int j) {  // dims 8 j + 4 hh + 0..3 of the lane's column and their partners, turned by its position
             a = b = make_float4(0.f, 0.f, 0.f, 0.f);
             if (!there) return;
             const float4 c0 = rq[4 * j], c1 = rq[4 * j + 1];
@@ -310,7 +404,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
                 s1 = MFMA_F32(y.z, b.z * c1.x - a.z * c1.y, s1); s1 = MFMA_F32(y.w, b.w * c1.z - a.w * c1.w, s1);
             }
             s += s1;
-            softmax(s, d, causal);
+            softmax(s, L.scale_log2, d, causal);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const VV vv = *reinterpret_cast<const VV *>(vr + (8 * (r >> 2) + (r & 3)) * D);
@@ -324,70 +418,6 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
                 }
             }
         }
-    }
-    __syncthreads();                                     // (the queries' pieces make room for the results)
-
-    // the waves' results: element (i, r) of a lane is dim VW (8 (r / 4) + 4 hh + r % 4) + i of column n
-    l_run += other_half(l_run);
-    if (hh == 0) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        VV o;
-        float *x = reinterpret_cast<float *>(&o);
-#pragma unroll
-        for (int i = 0; i < VW; ++i) x[i] = acc[i][r];
-        *reinterpret_cast<VV *>(&s_acc[wave][n * PITCH + VW * (8 * (r >> 2) + 4 * hh + (r & 3))]) = o;
-    }
-    if (__builtin_amdgcn_ballot_w64(odd) != 0) {         // (the probability has no say in an Inf or NaN; a wave's own LDS accesses are in order)
-        for (int t = t0; t < t1; ++t) {
-            const i32x4 d = describe(t);
-            if (!(d.w & PC_TILE_SELF) || d.y + (d.w & 0xFF) - 1 <= lo_lim) continue;
-            const int lim = min(d.w & 0xFF, self_lim - d.y + 1);
-            const float *vr = (const float *)L.v_store + ((int64_t)kh * L.slots + d.x) * D;
-            for (int e = hh; e < lim * D; e += 2) {
-                const float x = vr[e];
-                if (!(fabsf(x) < INFINITY)) s_acc[wave][n * PITCH + e % D] += x;
-            }
-        }
-    }
-    __syncthreads();
-    {                                                    // 16 threads a column: dims 4 sub + 64 i
-        const int c = threadIdx.x >> 4, sub = threadIdx.x & 15, col = col0 + c;
-        if (col >= n_cols) return;
-        float mm = s_m[0][c], l = 0.f;
-#pragma unroll
-        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][c]);
-        float4 o[D / 64];
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (mm > -INFINITY) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                if (!(s_m[w][c] > -INFINITY)) { l += s_l[w][c]; continue; }        // saw nothing: a sum of 0 (or NaN, which stays)
-                const float f = ex2(s_m[w][c] - mm);
-                l = fmaf(s_l[w][c], f, l);
-#pragma unroll
-                for (int i = 0; i < D / 64; ++i) {
-                    const float4 a = *reinterpret_cast<const float4 *>(&s_acc[w][c * PITCH + 64 * i + 4 * sub]);
-                    o[i].x = fmaf(a.x, f, o[i].x); o[i].y = fmaf(a.y, f, o[i].y); o[i].z = fmaf(a.z, f, o[i].z); o[i].w = fmaf(a.w, f, o[i].w);
-                }
-            }
-        }
-        const int r = col / g, h = kh * g + col % g;
-        const bool whole = cd.n_splits == 1;
-        const int64_t at = (whole ? (int64_t)(cd.q_off + r) : (int64_t)cd.part_off + (int64_t)item.split * cd.n_q + r) * L.n_q_heads + h;
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) {
-            if (whole) {
-                if (l > 0.f) { o[i].x /= l; o[i].y /= l; o[i].z /= l; o[i].w /= l; }
-                else o[i] = make_float4(0.f, 0.f, 0.f, 0.f);                // nothing visible (or a NaN score)
-                float *out = (float *)L.out + at * D + 64 * i + 4 * sub;
-                out[0] = o[i].x; out[1] = o[i].y; out[2] = o[i].z; out[3] = o[i].w;
-            } else *reinterpret_cast<float4 *>((float *)L.part_o + at * D + 64 * i + 4 * sub) = o[i];
-        }
-        if (sub != 0) return;
-        if (!whole) { L.part_ml[at * 2] = mm; L.part_ml[at * 2 + 1] = l; }
-        else if (L.lse) L.lse[at] = (l > 0.f) ? (mm + log2f(l)) * 0.6931471805599453f : -INFINITY;
     }
 }
 

@@ -10,8 +10,13 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Eight fp32 numbers as three bf16 pieces each, whose sum the number is (round, subtract, round, subtract, round).  A product
 // of two bf16 numbers is exact in fp32, so six products of pieces, those whose orders sum to at most two, are a product of fp32
-// numbers: what is left out is below 2^-25 of it, half of what rounding it to fp32 costs.  Six bf16 MFMAs take 192 cycles for
-// 32 x 32 x 16, the fp32 instruction 512.
+// numbers: what is left out is below 2^-24 of it, what rounding it to fp32 costs at most (a fifth of 2^-25 in the mean square).  Six bf16 MFMAs take
+// 192 cycles for 32 x 32 x 16, the fp32 instruction 512.
+// The pieces' exponents end at both ends: above 3.396e38 the first one is an infinity (the kernels look for what is not finite in their
+// results), below 2^-110 the last ones fall below 2^-133, bf16's least number.  Operands are cut times UP where that costs nothing or little: then
+// every fp32 number has its pieces, the subnormal ones too, and the upper end is at 5.2e33.
+constexpr float UP = 0x1p16f;
+__device__ __forceinline__ float4 up(float4 v) { return make_float4(v.x * UP, v.y * UP, v.z * UP, v.w * UP); }
 struct Pieces { bf16x8 p[3]; };
 __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[3])
 {

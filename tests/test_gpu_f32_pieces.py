@@ -24,7 +24,7 @@ def test_magnitudes(D, size):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("n_tok", [50])
+@pytest.mark.parametrize("n_tok", [50, 700])
 @pytest.mark.parametrize("where", ["query", "key"])
 def test_largest_numbers(D, n_tok, where):
     """3.4e38 is finite but rounds to infinity in bf16.  In the slowest pair, where the other side holds numbers of 3e-38: scores of order one."""
@@ -43,6 +43,46 @@ def test_largest_numbers(D, n_tok, where):
         else:
             q[..., half - 1::half] *= np.float32(3e-38)
     check(run_case([n_tok, 64], [([(0, 0)], 1, n_tok, 64)], 4, 2, D, spoil, spoil_q=spoil_q))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("size", [1e-32, 1e-34, 1e-36])
+@pytest.mark.parametrize("where", ["values", "queries", "keys"])
+def test_smallest_numbers(D, size, where):
+    """Below 2^-110 (8e-34) a number has bits below bf16's least.  Values: the result's size.  Queries and keys: in a third of the pairs, with
+    the other side as much larger."""
+    c, half = np.float32(size), D // 2
+    pairs = np.concatenate([np.arange(0, half, 3), half + np.arange(0, half, 3)])
+
+    def spoil(ks, vs):
+        for k in ks:
+            if where != "values":
+                k[..., pairs] *= c if where == "keys" else 1 / c
+        for v in vs:
+            if where == "values":
+                v *= c
+
+    def spoil_q(q):
+        if where != "values":
+            q[..., pairs] *= c if where == "queries" else 1 / c
+    for n_tok in (40, 700):
+        for got, got_lse, want, want_lse in run_case([n_tok, 33, 90], [([(0, 5), (1, 300)], 2, n_tok + 300, 90)], 8, 2, D, spoil, spoil_q=spoil_q):
+            want = want * (np.float64(c) if where == "values" else 1.0)
+            assert np.linalg.norm(got - want) <= BAR * np.linalg.norm(want)
+            assert np.abs(got_lse - want_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_a_key_with_a_score_of_minus_1e30(D):
+    """The only one a row sees: a probability of one."""
+    def spoil(ks, vs):
+        ks[0][..., D // 2 - 1], ks[0][..., D - 1] = 1e10, 0
+
+    def spoil_q(q):
+        q[..., D // 2 - 1], q[..., D - 1] = -1e20, 0
+    (got, got_lse, want, want_lse), = run_case([1], [([], 0, 0, 1)], 4, 2, D, spoil, spoil_q=spoil_q)
+    assert np.linalg.norm(got - want) <= BAR * np.linalg.norm(want)
+    assert (np.abs(got_lse - want_lse) <= 1e-6 * np.abs(want_lse)).all() and (want_lse < -1e28).all()
 
 
 @pytest.mark.parametrize("D", [64, 128])
