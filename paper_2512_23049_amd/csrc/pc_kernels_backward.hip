@@ -624,7 +624,6 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
     __shared__ __attribute__((aligned(1024))) unsigned char s_mem[MEM > MEM_END ? MEM : MEM_END];      // [buffer][queries, output gradients][piece]
     __shared__ __attribute__((aligned(16))) float s_lse[2][32], s_del[2][32];
     __shared__ __attribute__((aligned(16))) int s_lim[2][32];
-    __shared__ __attribute__((aligned(16))) int s_odd[2][4];                // [buffer][wave that made it]: an Inf or NaN in the block
     auto tile = [&](int buf, int which, int z) { return s_mem + ((buf * 2 + which) * 3 + z) * Tile::BYTES; };
 
     const int kh = blockIdx.x % L.n_kv_heads;
@@ -670,18 +669,12 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
         for (int z = 0; z < 3; ++z) *reinterpret_cast<uint2 *>(tile(buf, which, z) + Tile::at(sc, dim)) = make_uint2(lo[z], hi[z]);
     };
     auto put = [&](int u, int buf) __attribute__((always_inline)) {
-        float odd = 0.f;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             turn4(qa[i], qb[i], ra[i], rb[i]);
             put4(buf, 0, sp + 32 * i, qa[i]); put4(buf, 0, sp + 32 * i + HALF, qb[i]);
             put4(buf, 1, sp + 32 * i, ga[i]); put4(buf, 1, sp + 32 * i + HALF, gb[i]);
-            // (the pieces of an Inf or NaN are not its parts: such a block goes to the fp32 instruction)
-            auto sum0 = [](float4 v) { return v.x * 0.f + v.y * 0.f + (v.z * 0.f + v.w * 0.f); };
-            odd += sum0(qa[i]) + sum0(qb[i]) + (sum0(ga[i]) + sum0(gb[i]));
         }
-        const uint64_t some_odd = __builtin_amdgcn_ballot_w64(odd != 0.f);
-        if (lane == 0) s_odd[buf][wave] = some_odd != 0;
         if (sp == 0) { s_lse[buf][sc] = st_lse; s_del[buf][sc] = st_del; s_lim[buf][sc] = cd.self_len - cd.n_q + (32 * u + sc) / g; }
     };
     fetch(item.rt_begin);
@@ -714,8 +707,6 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
         const int buf = (u - item.rt_begin) & 1;
         fetch(u + 1);
         const int first_lim = s_lim[buf][0], last_lim = s_lim[buf][31];
-        const int4 od = *reinterpret_cast<const int4 *>(s_odd[buf]);
-        const bool slow = __builtin_amdgcn_readfirstlane(od.x | od.y | od.z | od.w) != 0;
         const bool seen = active && !(self && key0 > last_lim);             // (uniform over the wave: some row of the block sees the tile)
         const bool causal = self && key0 + PC_TILE - 1 > first_lim;
         // p and ds of the block: register r: column 8 (r / 4) + 4 hh + r % 4
@@ -729,8 +720,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * q4 + i;
-                    // (the maximum: an infinite key makes a NaN; a row with a log-sum-exp saw it at a score of -inf)
-                    const float x = exp_x(fmaxf(fmaf(p[r], scale, -ll[i]), -1e30f));
+                    const float x = exp_x(fmaf(p[r], scale, -ll[i]));
                     const bool ok = ll[i] < INFINITY && (!causal || key0 + n <= mm[i]);
                     p[r] = ok ? x : 0.f;
                     w[r] = ok ? x * (w[r] - dd[i]) * scale : 0.f;
@@ -738,7 +728,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
             }
         };
         f32x16 p, w;
-        if (seen && !slow) {
+        if (seen) {
             f32x16 s1, w1;                               // (two chains of D / 2 terms round less than one of D)
 #pragma unroll
             for (int r = 0; r < 16; ++r) p[r] = s1[r] = w[r] = w1[r] = 0.f;
@@ -763,7 +753,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
             weights(p, w);
         }
         if (u + 1 < item.rt_end) put(u + 1, buf ^ 1);    // (last read before the barrier behind the block before this one)
-        if (seen && !slow) {
+        if (seen) {
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
                 float x[8], y[8];
@@ -780,41 +770,76 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
                 }
             }
         }
-        if (seen && slow) {
-            auto col_of = [&](int c) { return min(32 * u + c, n_cols - 1); };
-            auto rows_of = [&](int c) { return (int64_t)(cd.q_off + col_of(c) / g) * L.n_q_heads + kh * g + col_of(c) % g; };
-            auto turned = [&](const float *v, const float2 *rot, int dim) { // one dim of a row, turned
-                const int i = dim & (HALF - 1);
-                const float a = v[i], b = v[i + HALF];
-                const float2 cs = rot[i];
-                return dim < HALF ? a * cs.x - b * cs.y : a * cs.y + b * cs.x;
-            };
-            auto q_at = [&](int c, int dim) {
-                const float v = turned((const float *)L.q + rows_of(c) * D, L.rot_q + (int64_t)(cd.q_off + col_of(c) / g) * HALF, dim);
-                return s_lse[buf][c] < INFINITY ? v : 0.f;
-            };
-            auto g_at = [&](int c, int dim) { const float v = d_out[rows_of(c) * D + dim]; return s_lse[buf][c] < INFINITY ? v : 0.f; };
-            const float *kr = (const float *)L.k_store + ((int64_t)kh * L.slots + slot0 + n) * D, *vr = (const float *)L.v_store + ((int64_t)kh * L.slots + slot0 + n) * D;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) p[r] = w[r] = 0.f;
-#pragma unroll 1
-            for (int j = 0; j < D; j += 2) {
-                p = MFMA_F32(q_at(n, j + hh), turned(kr, rs, j + hh), p);
-                w = MFMA_F32(g_at(n, j + hh), vr[j + hh], w);
-            }
-            weights(p, w);
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-                for (int i = 0; i < VW; ++i) {
-                    const int c = 8 * (r >> 2) + 4 * hh + (r & 3);
-                    dv[i] = MFMA_F32(g_at(c, 32 * i + n), p[r], dv[i]);
-                    dk[i] = MFMA_F32(q_at(c, 32 * i + n), w[r], dk[i]);
-                }
-        }
         __syncthreads();
     }
     if (!active) return;
+    // The pieces of an Inf or NaN are not its parts, nor are those of a number that rounds to one in bf16 (3.4e38).  Whatever holds one, a query, an output
+    // gradient, a key or a value, it leaves a NaN in the sums that it belongs to: such a wave goes through its column blocks again, on the fp32
+    // instruction, with the caller's numbers.
+    float odd = 0.f;
+#pragma unroll
+    for (int i = 0; i < VW; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) odd = fmaf(dk[i][r], 0.f, fmaf(dv[i][r], 0.f, odd));
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd != 0.f) != 0, 0)) {
+#pragma unroll
+        for (int i = 0; i < VW; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dk[i][r] = dv[i][r] = 0.f;
+        const float *kr = (const float *)L.k_store + ((int64_t)kh * L.slots + slot0 + n) * D, *vr = (const float *)L.v_store + ((int64_t)kh * L.slots + slot0 + n) * D;
+        auto turned = [&](const float *v, const float2 *rot, int dim) {     // one dim of a row, turned
+            const int i = dim & (HALF - 1);
+            const float a = v[i], b = v[i + HALF];
+            const float2 cs = rot[i];
+            return dim < HALF ? a * cs.x - b * cs.y : a * cs.y + b * cs.x;
+        };
+        struct Column { int64_t rh; const float2 *rot; float lse, delta; int lim; };
+        auto column = [&](int col) {                     // (no such column, or a row that saw nothing: a log-sum-exp of +inf)
+            const int cc = min(col, n_cols - 1);
+            Column r;
+            r.rh = (int64_t)(cd.q_off + cc / g) * L.n_q_heads + kh * g + cc % g;
+            r.rot = L.rot_q + (int64_t)(cd.q_off + cc / g) * HALF;
+            const float x = lse[r.rh];
+            r.lse = col < n_cols && x > -INFINITY ? x : INFINITY;
+            r.delta = r.lse < INFINITY ? delta[r.rh] : 0.f;
+            r.lim = cd.self_len - cd.n_q + col / g;
+            return r;
+        };
+        auto q_at = [&](const Column &c, int dim) { const float v = turned((const float *)L.q + c.rh * D, c.rot, dim); return c.lse < INFINITY ? v : 0.f; };
+        auto g_at = [&](const Column &c, int dim) { const float v = d_out[c.rh * D + dim]; return c.lse < INFINITY ? v : 0.f; };
+#pragma unroll 1
+        for (int u = item.rt_begin; u < item.rt_end; ++u) {
+            const int first_lim = cd.self_len - cd.n_q + 32 * u / g, last_lim = cd.self_len - cd.n_q + (32 * u + 31) / g;
+            if (self && key0 > last_lim) continue;
+            const bool causal = self && key0 + PC_TILE - 1 > first_lim;
+            const Column own = column(32 * u + n);
+            f32x16 p, w, p1, w1;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[r] = w[r] = p1[r] = w1[r] = 0.f;
+#pragma unroll 1
+            for (int j = 0; j < HALF; j += 2) {
+                p = MFMA_F32(q_at(own, j + hh), turned(kr, rs, j + hh), p);
+                w = MFMA_F32(g_at(own, j + hh), vr[j + hh], w);
+                p1 = MFMA_F32(q_at(own, j + HALF + hh), turned(kr, rs, j + HALF + hh), p1);
+                w1 = MFMA_F32(g_at(own, j + HALF + hh), vr[j + HALF + hh], w1);
+            }
+            p += p1;
+            w += w1;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const Column c = column(32 * u + 8 * (r >> 2) + 4 * hh + (r & 3));
+                // (the maximum: an infinite key makes a NaN; a row with a log-sum-exp saw it at a score of -inf)
+                const float x = exp_x(fmaxf(fmaf(p[r], scale, -c.lse), -1e30f));
+                const bool ok = c.lse < INFINITY && (!causal || key0 + n <= c.lim);
+                const float pp = ok ? x : 0.f, ww = ok ? x * (w[r] - c.delta) * scale : 0.f;
+#pragma unroll
+                for (int i = 0; i < VW; ++i) {
+                    dv[i] = MFMA_F32(g_at(c, 32 * i + n), pp, dv[i]);
+                    dk[i] = MFMA_F32(q_at(c, 32 * i + n), ww, dk[i]);
+                }
+            }
+        }
+    }
     // element (i, r) is dim 32 i + 8 (r / 4) + 4 hh + r % 4 of key n: turned round through the wave's quarter of the block buffers
     float *stg = reinterpret_cast<float *>(s_mem) + wave * 32 * PITCH;
 #pragma unroll

@@ -33,8 +33,9 @@ def rot(x, pos, theta):
     return torch.cat([lo * c - hi * s, lo * s + hi * c], -1)
 
 
-def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(), seed=5, capacity=None, bar=BAR, off=(0.0, 0.0)):
-    """lens: messages; calls: (sel, self, self_start, n_q); off: what all values have in common, and the keys' channels (with either sign)."""
+def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(), seed=5, capacity=None, bar=BAR, spoil=None):
+    """lens: messages; calls: (sel, self, self_start, n_q); spoil(name, tensor): changes the k and v of a message, q and do."""
+    spoil = spoil or (lambda name, t: None)
     import torch
     from paper_2512_23049_amd import binding
     from pc_inputs import Call
@@ -49,8 +50,8 @@ def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(
     cache = binding.Cache(h_q, h_kv, D, cfg.dtype, theta, cap, len(lens) + 1, max_position=1 << 20, arena=arena.data_ptr(), arena_bytes=nbytes)
     for L in lens:
         k, v = normal(L, h_kv, D), normal(L, h_kv, D)
-        k += off[1] * torch.tensor([1.0, -1.0, -1.0, 1.0], device="cuda:0").repeat(D // 4)
-        v += off[0]
+        spoil("k", k)
+        spoil("v", v)
         cache.append_message(k.data_ptr(), v.data_ptr(), L)
         torch.cuda.synchronize()
     for m, b in bases:
@@ -62,6 +63,8 @@ def run_case(lens, calls, h_q, h_kv, dtype="bf16", D=128, theta=10000.0, bases=(
     V = (arena[n:].view(h_kv, slots // 8, D, 8).transpose(2, 3).reshape(h_kv, slots, D) if dtype == "bf16" else arena[n:].view(h_kv, slots, D)).double()
     rows = sum(c[3] for c in calls)
     q, do = normal(rows, h_q, D), normal(rows, h_q, D)
+    spoil("q", q)
+    spoil("do", do)
     g, scale = h_q // h_kv, 1.0 / D ** 0.5
     want_q = torch.zeros(rows, h_q, D, dtype=torch.float64, device="cuda:0")
     want_k = torch.zeros(slots, h_kv, D, dtype=torch.float64, device="cuda:0")

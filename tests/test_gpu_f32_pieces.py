@@ -151,3 +151,21 @@ def test_infinite_output_gradient(D):
     q1[at, 0], k1[:at + 1, 0], v1[:, 0, dim] = q0[at, 0], k0[:at + 1, 0], v0[:, 0, dim]    # (later keys: that row's zero times it)
     for a, b in ((q0, q1), (k0, k1), (v0, v1)):
         assert float((a - b).norm()) <= 3e-6 * float(a.norm())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("where", ["q", "do", "k", "v"])
+def test_gradient_of_the_largest_numbers(D, where):
+    """As above: one number near the largest in the slowest pair of a row or key, what meets it there of 3e-38.  (Its own gradient's bound
+    is that of every other: a tensor's distance is that of its largest part, where it has one.)"""
+    from tests import test_gpu_backward_precision as precision
+    half, other = D // 2, {"q": "k", "k": "q", "do": "v", "v": "do"}[where]
+    done = []
+
+    def spoil(name, t):
+        if name == other:
+            t[..., half - 1::half] *= 3e-38
+        elif name == where and not done and len(t) > 60:
+            t[7, 0, half - 1], t[7, 0, D - 1] = 3.4e38, 0
+            done.append(1)
+    precision.run_case([90, 64], [([(0, 0)], 1, 100, 64)], 4, 2, dtype="f32", D=D, spoil=spoil, bar=precision.BAR)
