@@ -7,7 +7,10 @@
 // keys.)  Products and sums are fp32 throughout, on the bf16 matrix instructions: an fp32 number is the exact sum of three bf16
 // pieces, and six MFMAs over them are an fp32 product (see pc_pieces.h).  A result has 16 rows a lane, 8 (r / 4) + 4 (lane / 32) +
 // r % 4; the order of the summed index is free, so registers 8 kk .. 8 kk + 7 of a product, cut, are the operand of the next one
-// for the indices they stand for, as long as the other operand is read in that order.
+// for the indices they stand for, as long as the other operand is read in that order.  Queries, keys, values and output gradients are
+// cut times UP = 2^16, so that the smallest numbers have their pieces; scores and dp carry it twice, sums of ds K and ds q three times, those of
+// p dO twice (p is cut times UP as well), and powers of two take it back exactly.  (Values or output gradients of 1e-34 without it: dK 6e-5 to 9e-5
+// from fp64, dq 8e-6; of 1e-36 with it 2.2e-7 to 2.9e-7.)  A sum that overflows for it, or meets an Inf or NaN, is made again on the fp32 instruction.
 //
 // Two kernels.  rows: 32 (row, head) columns of a KV head against the call's tiles: Delta and dq.  keys: a wave owns one 32-key tile of
 // the call, its keys turned to the call's positions, and the sums of dK and dV, while the call's column blocks go by.  A
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         asm volatile("" : "+v"(at));
         rot = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + at);
     };
-    auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot; };          // (a wave's own LDS accesses are in order)
+    auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot * UP; };     // (a wave's own LDS accesses are in order)
     auto describe = [&](int t) { return tile_at(tab, min(t, item.tile_end - 1)); };
     i32x4 next = {0, 0, 0, 0};
     if (t0 < t1) { next = describe(t0); keys.request(kb + (int64_t)next.x * D); load_rot(next); }
@@ -123,9 +126,9 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
             const float *q = (const float *)L.q + at, *o = d_out + at;
             const float4 *rq = reinterpret_cast<const float4 *>(L.rot_q + (int64_t)(cd.q_off + (col0 + c) / g) * HALF + i);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) { x[j] = q[j]; y[j] = q[j + HALF]; u[j] = o[j]; w[j] = o[j + HALF]; }
+            for (int j = 0; j < 8; ++j) { x[j] = q[j]; y[j] = q[j + HALF]; u[j] = o[j] * UP; w[j] = o[j + HALF] * UP; }
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) turn2(x[j], y[j], x[j + 1], y[j + 1], rq[j / 2]);
+            for (int j = 0; j < 8; j += 2) turn2(x[j], y[j], x[j + 1], y[j + 1], up(rq[j / 2]));
         }
         const Pieces px = split8(x), py = split8(y), pu = split8(u), pw = split8(w);
 #pragma unroll
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         load_rot(next);
         auto value = [&](int j) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = v[j][e / 4][e % 4];
+            for (int e = 0; e < 8; ++e) x[e] = v[j][e / 4][e % 4] * UP;
         };
         f32x16 s, s1, dp, dp1;                           // (two chains of D / 2 terms round less than one of D)
 #pragma unroll
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         const bool self = (d.w & PC_TILE_SELF) != 0;
         float ps[16], w[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ps[r] = exp_x(fmaf(s[r], scale, -row_lse));
+        for (int r = 0; r < 16; ++r) ps[r] = exp_x(fmaf(s[r], scale * (1.f / (UP * UP)), -row_lse));
         if (valid < PC_TILE || some_dead || (self && key0 + valid - 1 > lo_lim)) {        // (uniform over the wave)
             const int lim = !live ? 0 : self ? min(valid, self_lim - key0 + 1) : valid;
 #pragma unroll
@@ -369,17 +372,18 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
         delta = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) delta += s_delta[w][end_n];
-        const float off = delta - centre;
+        const float off = delta - centre, down = scale * (1.f / (UP * UP * UP));
         if (t0 < t1)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 float *p = &s_dq[wave][end_n * PITCH + HW * (8 * (r >> 2) + 4 * end_hh + (r & 3))];
 #pragma unroll
                 for (int i = 0; i < HW; ++i) {
-                    p[i] = fmaf(-off, acc_p[i][r], acc_w[i][r]) * scale;
-                    p[HALF + i] = fmaf(-off, acc_p[HW + i][r], acc_w[HW + i][r]) * scale;
+                    p[i] = fmaf(-off, acc_p[i][r], acc_w[i][r]) * down;
+                    p[HALF + i] = fmaf(-off, acc_p[HW + i][r], acc_w[HW + i][r]) * down;
                 }
             }
+        delta *= 1.f / (UP * UP);
     } else {
         // the queries are turned to a segment's frame at every new rotation; dq is collected in that frame and turned back into the
         // wave's own part of LDS
@@ -659,7 +663,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
             const float4 *rot = reinterpret_cast<const float4 *>(L.rot_q + R * HALF + sp + 32 * i);
             qa[i] = make_float4(q[0], q[1], q[2], q[3]); qb[i] = make_float4(q[HALF], q[HALF + 1], q[HALF + 2], q[HALF + 3]);
             ga[i] = make_float4(o[0], o[1], o[2], o[3]); gb[i] = make_float4(o[HALF], o[HALF + 1], o[HALF + 2], o[HALF + 3]);
-            ra[i] = rot[0]; rb[i] = rot[1];
+            ra[i] = up(rot[0]); rb[i] = up(rot[1]);
         }
     };
     auto put4 = [&](int buf, int which, int dim, float4 v) __attribute__((always_inline)) {
@@ -673,9 +677,9 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
         for (int i = 0; i < NP; ++i) {
             turn4(qa[i], qb[i], ra[i], rb[i]);
             put4(buf, 0, sp + 32 * i, qa[i]); put4(buf, 0, sp + 32 * i + HALF, qb[i]);
-            put4(buf, 1, sp + 32 * i, ga[i]); put4(buf, 1, sp + 32 * i + HALF, gb[i]);
+            put4(buf, 1, sp + 32 * i, up(ga[i])); put4(buf, 1, sp + 32 * i + HALF, up(gb[i]));
         }
-        if (sp == 0) { s_lse[buf][sc] = st_lse; s_del[buf][sc] = st_del; s_lim[buf][sc] = cd.self_len - cd.n_q + (32 * u + sc) / g; }
+        if (sp == 0) { s_lse[buf][sc] = st_lse; s_del[buf][sc] = st_del * (UP * UP); s_lim[buf][sc] = cd.self_len - cd.n_q + (32 * u + sc) / g; }
     };
     fetch(item.rt_begin);
 
@@ -689,9 +693,9 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
         for (int j = 0; j < NK / 2; ++j) {
             float x[8], y[8], u[8], w[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { x[e] = kr[16 * j + e]; y[e] = kr[16 * j + e + HALF]; u[e] = vr[16 * j + e]; w[e] = vr[16 * j + e + HALF]; }
+            for (int e = 0; e < 8; ++e) { x[e] = kr[16 * j + e]; y[e] = kr[16 * j + e + HALF]; u[e] = vr[16 * j + e] * UP; w[e] = vr[16 * j + e + HALF] * UP; }
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) turn2(x[e], y[e], x[e + 1], y[e + 1], *reinterpret_cast<const float4 *>(rs + 16 * j + 8 * hh + e));
+            for (int e = 0; e < 8; e += 2) turn2(x[e], y[e], x[e + 1], y[e + 1], up(*reinterpret_cast<const float4 *>(rs + 16 * j + 8 * hh + e)));
             k[j] = split8(x); k[j + NK / 2] = split8(y); v[j] = split8(u); v[j + NK / 2] = split8(w);
         }
     }
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
         const int first_lim = s_lim[buf][0], last_lim = s_lim[buf][31];
         const bool seen = active && !(self && key0 > last_lim);             // (uniform over the wave: some row of the block sees the tile)
         const bool causal = self && key0 + PC_TILE - 1 > first_lim;
-        // p and ds of the block: register r: column 8 (r / 4) + 4 hh + r % 4
+        // p times UP and ds times UP twice of the block: register r: column 8 (r / 4) + 4 hh + r % 4
         auto weights = [&](f32x16 &p, f32x16 &w) __attribute__((always_inline)) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
@@ -720,10 +724,10 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * q4 + i;
-                    const float x = exp_x(fmaf(p[r], scale, -ll[i]));
+                    const float x = UP * exp_x(fmaf(p[r], scale * (1.f / (UP * UP)), -ll[i]));
                     const bool ok = ll[i] < INFINITY && (!causal || key0 + n <= mm[i]);
                     p[r] = ok ? x : 0.f;
-                    w[r] = ok ? x * (w[r] - dd[i]) * scale : 0.f;
+                    w[r] = ok ? x * (w[r] - dd[i]) * (scale * (1.f / UP)) : 0.f;
                 }
             }
         };
@@ -780,7 +784,11 @@ __global__ __launch_bounds__(256, 1) void pc_bwd_keys_f32_kernel(PcLaunch L, con
 #pragma unroll
     for (int i = 0; i < VW; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) odd = fmaf(dk[i][r], 0.f, fmaf(dv[i][r], 0.f, odd));
+        for (int r = 0; r < 16; ++r) {
+            odd = fmaf(dk[i][r], 0.f, fmaf(dv[i][r], 0.f, odd));
+            dk[i][r] *= 1.f / (UP * UP * UP);
+            dv[i][r] *= 1.f / (UP * UP);
+        }
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd != 0.f) != 0, 0)) {
 #pragma unroll
         for (int i = 0; i < VW; ++i)

@@ -169,3 +169,20 @@ def test_gradient_of_the_largest_numbers(D, where):
             t[7, 0, half - 1], t[7, 0, D - 1] = 3.4e38, 0
             done.append(1)
     precision.run_case([90, 64], [([(0, 0)], 1, 100, 64)], 4, 2, dtype="f32", D=D, spoil=spoil, bar=precision.BAR)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("size", [1e-30, 1e-34, 1e-36, 1e15])
+@pytest.mark.parametrize("where", ["q", "do", "k", "v"])
+def test_gradient_at_magnitudes_far_from_one(D, size, where):
+    """Values or output gradients all of that size, and with them products and gradients; queries or keys in a third of the pairs, with the
+    other side as much larger."""
+    from tests import test_gpu_backward_precision as precision
+    pairs = [d for d in range(D) if d % (D // 2) % 3 == 0]
+
+    def spoil(name, t):
+        if where in "qk" and name in "qk":
+            t[..., pairs] *= size if name == where else 1 / size
+        elif name == where:
+            t *= size
+    precision.run_case([90, 33, 64], [([(0, 0), (1, 95)], 2, 130, 64)], 4, 2, dtype="f32", D=D, spoil=spoil, bar=precision.BAR)
