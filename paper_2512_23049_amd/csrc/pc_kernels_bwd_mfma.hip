@@ -10,7 +10,7 @@
 // subtract, round, subtract, round).  A product of an fp32 factor with a bf16 one (dq: ds K, dV: p dO, the scores of
 // the row-major kernels: turned query times stored key) takes three MFMAs and is exact; two fp32 factors (dK: ds
 // times turned query, and the scores of the key-major kernel) take the six whose pieces' orders sum to at most two:
-// what is left out is below 2^-25 of a product, half of what rounding the product to fp32 costs.  Three to six
+// what is left out is below 2^-24 of a product, what rounding it to fp32 costs at most.  Three to six
 // bf16 MFMAs run at 2.5 to 5 times the rate of the fp32 ones.
 //
 // Kernels, in launch order:
@@ -30,7 +30,7 @@
 // All operands that a product needs with its indices the other way round (V by dimension, keys, queries and output
 // gradients by token) come from the same LDS tile through ds_read_b64_tr_b16: within 16 lanes, lane l points at row
 // l / 4, columns 4 (l % 4) .. + 3 of a 4 x 16 block and receives column l, rows 0 .. 3.
-#include "pc_mfma_common.h"
+#include "pc_pieces.h"
 
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
 #define TILE_BYTES 8192
@@ -51,15 +51,6 @@ __device__ __forceinline__ bf16x8 read_tr(unsigned at0, unsigned at1)       // r
     const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
     return frag4(x.x, x.y, y.x, y.y);
 }
-// two fp32 numbers into three bf16 pieces each, packed in pairs; the sum of the pieces is the number
-__device__ __forceinline__ void split2(float a, float b, uint32_t &w0, uint32_t &w1, uint32_t &w2)
-{
-    w0 = pack_bf16(a, b);
-    a -= bf_lo(w0); b -= bf_hi(w0);
-    w1 = pack_bf16(a, b);
-    a -= bf_lo(w1); b -= bf_hi(w1);
-    w2 = pack_bf16(a, b);
-}
 // the largest finite numbers in the place of infinities, zeros in the place of NaN
 __device__ __forceinline__ bf16x8 finite8(bf16x8 x)
 {
@@ -73,25 +64,7 @@ __device__ __forceinline__ bf16x8 finite8(bf16x8 x)
     }
     return __builtin_bit_cast(bf16x8, u);
 }
-struct Pieces { bf16x8 p[3]; };
-__device__ __forceinline__ Pieces split8(const float *v)
-{
-    uint32_t w[3][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], w[0][j], w[1][j], w[2][j]);
-    Pieces r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) r.p[i] = frag4(w[i][0], w[i][1], w[i][2], w[i][3]);
-    return r;
-}
-// One 16-byte (4-byte) per lane direct load: lane l's bytes land at lds_wave_base + 16 l (4 l).  Assembly, so that the
-// compiler keeps no record of the LDS write and does not drain every request in front of later LDS reads; completion
-// is awaited with an explicit s_waitcnt vmcnt(n).
-__device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 ::"s"(lds_wave_base), "v"(lane_off), "s"(gbase_uniform) : "memory", "m0");
-}
+// The 4-byte direct load beside dma16; completion is awaited with an explicit s_waitcnt vmcnt(n).
 __device__ __forceinline__ void dma4(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
@@ -199,7 +172,7 @@ __global__ __launch_bounds__(256) void pc_bwd_prep_kernel(PcLaunch L, PcBwd B)
     float4 *qt = B.q_turned + unit * 1024 + (c >> 1) * 256 + (c & 1) * 32 + r;
     qt[0] = make_float4(x[0], x[1], x[2], x[3]); qt[64] = make_float4(x[4], x[5], x[6], x[7]);
     qt[128] = make_float4(y[0], y[1], y[2], y[3]); qt[192] = make_float4(y[4], y[5], y[6], y[7]);
-    const Pieces px = split8(x), py = split8(y);
+    const Pieces px = split8<false>(x), py = split8<false>(y);
     unsigned char *dst = (unsigned char *)B.q_pieces + unit * (4 * TILE_BYTES) + r * 256 + c * 16;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -277,7 +250,7 @@ __global__ __launch_bounds__(512, 1) void pc_bwd_delta_kernel(PcLaunch L, PcBwd 
                 u[j] = x[j] * cs.x + y[j] * cs.y; v[j] = y[j] * cs.x - x[j] * cs.y;
                 u[j + 1] = x[j + 1] * cs.z + y[j + 1] * cs.w; v[j + 1] = y[j + 1] * cs.z - x[j + 1] * cs.w;
             }
-            const Pieces pu = split8(u), pv = split8(v);
+            const Pieces pu = split8<false>(u), pv = split8<false>(v);
 #pragma unroll
             for (int i = 0; i < 3; ++i) { qp[i][ks] = pu.p[i]; qp[i][ks + 4] = pv.p[i]; }
         }
@@ -456,7 +429,7 @@ __global__ __launch_bounds__(512, 2) void pc_bwd_dq_kernel(PcLaunch L, PcBwd B)
                     u[j] = x[j] * cs.x + y[j] * cs.y; v[j] = y[j] * cs.x - x[j] * cs.y;
                     u[j + 1] = x[j + 1] * cs.z + y[j + 1] * cs.w; v[j + 1] = y[j + 1] * cs.z - x[j + 1] * cs.w;
                 }
-                const Pieces pu = split8(u), pv = split8(v);
+                const Pieces pu = split8<false>(u), pv = split8<false>(v);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) { qp[i][ks] = pu.p[i]; qp[i][ks + 4] = pv.p[i]; }
             }
@@ -587,7 +560,7 @@ __global__ __launch_bounds__(512, 2) void pc_bwd_dq_kernel(PcLaunch L, PcBwd B)
         }
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            const Pieces ds = split8(w + 8 * st);
+            const Pieces ds = split8<false>(w + 8 * st);
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
                 acc[db] = MFMA32(kf[st][db], ds.p[2], acc[db]);
@@ -733,7 +706,7 @@ __global__ __launch_bounds__(512, 2) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
                     x[2 * u] = a0 * cs.x - b0 * cs.y; y[2 * u] = a0 * cs.y + b0 * cs.x;
                     x[2 * u + 1] = a1 * cs.z - b1 * cs.w; y[2 * u + 1] = a1 * cs.w + b1 * cs.z;
                 }
-                const Pieces px = split8(x), py = split8(y);
+                const Pieces px = split8<false>(x), py = split8<false>(y);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) { kp[i][ks] = px.p[i]; kp[i][ks + 4] = py.p[i]; }
             }
@@ -780,7 +753,7 @@ __global__ __launch_bounds__(512, 2) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
             const RowMajor::Cols qc = rq.cols(qt);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                const Pieces pp = split8(p + 8 * half);
+                const Pieces pp = split8<false>(p + 8 * half);
 #pragma unroll
                 for (int db = 0; db < 4; ++db) {
                     const bf16x8 a = RowMajor::by_col(qc, 3 * TILE_BYTES, half, db);
@@ -845,7 +818,7 @@ __global__ __launch_bounds__(512, 2) void pc_bwd_keys_kernel(PcLaunch L, PcBwd B
             const RowMajor::Cols qc = rq.cols(qt);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                const Pieces ds = split8(w + 8 * half);
+                const Pieces ds = split8<false>(w + 8 * half);
 #pragma unroll
                 for (int db = 0; db < 4; ++db) {
                     const bf16x8 a0 = RowMajor::by_col(qc, 0, half, db), a1 = RowMajor::by_col(qc, TILE_BYTES, half, db), a2 = RowMajor::by_col(qc, 2 * TILE_BYTES, half, db);

@@ -18,21 +18,25 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 constexpr float UP = 0x1p16f;
 __device__ __forceinline__ float4 up(float4 v) { return make_float4(v.x * UP, v.y * UP, v.z * UP, v.w * UP); }
 struct Pieces { bf16x8 p[3]; };
+// PIN: without it the compiler rounds the lower number of a pair a second time, by an instruction of its own, which takes fewer registers: the
+// bf16 caches' gradient, whose walk of dq fills its 256 (20 of them in scratch with PIN, 180 -> 208 us), goes without.
+template <bool PIN = true>
 __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[3])
 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         w[i] = pack_bf16(a, b);
-        asm("" : "+v"(w[i]));                            // (or the lower piece is rounded a second time, by an instruction of its own)
+        if constexpr (PIN) asm("" : "+v"(w[i]));
         a -= bf_lo(w[i]);
         b -= bf_hi(w[i]);
     }
 }
+template <bool PIN = true>
 __device__ __forceinline__ Pieces split8(const float *v)
 {
     uint32_t w[4][3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], w[j]);
+    for (int j = 0; j < 4; ++j) split2<PIN>(v[2 * j], v[2 * j + 1], w[j]);
     Pieces r;
 #pragma unroll
     for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]));
