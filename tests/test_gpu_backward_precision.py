@@ -2,7 +2,7 @@
 values (read back from the cache's memory, so that the keys' one bf16 rounding is not part of the difference) and the
 fp64 log-sum-exp of those.
 
-Bound: every product is exact or within 2^-25, what remains are the fp32 sums of the kernels, a sincos rounded to fp32
+Bound: every product is exact or within 2^-24, what remains are the fp32 sums of the kernels, a sincos rounded to fp32
 per rotation (two per side) and exp2's last bit: about ten roundings of 2^-24 per term in sequence, sums of up to a few
 thousand terms whose errors add like their square roots.  2-norm of the difference over that of the gradient: 10 * 2^-24 =
 6e-7 before cancellation (p (dp - Delta) loses up to another factor of a few); the bar is 3e-6, where arithmetic on

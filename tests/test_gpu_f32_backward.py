@@ -1,5 +1,5 @@
 """The gradient of an fp32 batch against fp64 gradients of the same stored keys and values, at the edges of its tiles: 32
-(row, head) columns, 32-key tiles shared out over eight waves (rows) or one a wave (keys), column blocks split over
+(row, head) columns, 32-key tiles shared out over eight waves (rows; four at D = 128) or one a wave (keys), column blocks split over
 workgroups.  Bound as in test_gpu_backward_precision: fp32 sums, 5e-7 measured, the bar is 3e-6."""
 import numpy as np
 import pytest

@@ -1,5 +1,5 @@
-"""fp32 caches: numbers cut into three bf16 pieces.  Magnitudes far from one (the pieces carry their own exponents; bar as in
-test_gpu_f32_attend), and infinities, which have no pieces: a key whose score is -inf leaves no trace, one whose score is +inf
+"""fp32 caches: numbers cut into three bf16 pieces.  Magnitudes far from one up to the ends of fp32's range, where the pieces of the number
+itself no longer hold it (bar as in test_gpu_f32_attend; finite inputs), and infinities, which have no pieces: a key whose score is -inf leaves no trace, one whose score is +inf
 makes the row a NaN, an infinite value reaches the rows that see it and no others."""
 import numpy as np
 import pytest
@@ -12,12 +12,17 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("size", [1e-30, 1e-3, 1e30])
 def test_magnitudes(D, size):
-    def spoil(ks, vs):                                   # (the values' size is the result's; keys: some dims large, some small)
-        for k in ks:
-            k[..., ::3] *= 1e-6
+    pairs = [d for d in range(D) if d % (D // 2) % 3 == 0]
+
+    def spoil(ks, vs):                                   # (the values' size is the result's; keys: small in a third of the pairs, where
+        for k in ks:                                     # queries are as much larger, so that those make as much of the scores)
+            k[..., pairs] *= 1e-6
         for v in vs:
             v *= np.float32(size)
-    for got, got_lse, want, want_lse in run_case([200, 33, 90], [([(0, 5), (1, 300)], 2, 400, 90)], 8, 2, D, spoil):
+
+    def spoil_q(q):
+        q[..., pairs] *= 1e6
+    for got, got_lse, want, want_lse in run_case([200, 33, 90], [([(0, 5), (1, 300)], 2, 400, 90)], 8, 2, D, spoil, spoil_q=spoil_q):
         want = want * np.float64(np.float32(size))
         assert np.linalg.norm(got - want) <= BAR * np.linalg.norm(want)
         assert np.abs(got_lse - want_lse).max() <= 1e-5
@@ -51,8 +56,8 @@ def test_largest_numbers(D, n_tok, where):
 def test_smallest_numbers(D, size, where):
     """Below 2^-110 (8e-34) a number has bits below bf16's least.  Values: the result's size.  Queries and keys: in a third of the pairs, with
     the other side as much larger."""
-    c, half = np.float32(size), D // 2
-    pairs = np.concatenate([np.arange(0, half, 3), half + np.arange(0, half, 3)])
+    c = np.float32(size)
+    pairs = [d for d in range(D) if d % (D // 2) % 3 == 0]
 
     def spoil(ks, vs):
         for k in ks:
