@@ -171,7 +171,8 @@ typedef struct {
  *   q    device, [sum n_q, n_q_heads, head_dim], rows packed in call order, unrotated.
  *   out  device, same shape and dtype as q.
  *   lse  device, optional fp32 [sum n_q, n_q_heads]: natural-log sum of exp(scores).
- * A row with nothing visible yields zeros and -inf. */
+ * A row with nothing visible yields zeros and -inf.  PC_F32 caches: fp32 precision over the whole
+ * range of fp32, but for values below 2^-134 (5e-41), which may count as zeros. */
 int32_t pc_attend(pc_cache *c, const pc_call *calls, int32_t n_calls,
                   const void *q, void *out, float *lse, void *stream);
 
@@ -325,7 +326,8 @@ int32_t pc_set_key_gather(pc_cache *c, int32_t mode);
  * message into the gradient w.r.t. the K that was appended.  No message may be repositioned,
  * freed or swapped between the first backward call into a buffer and its finalize.  All
  * arithmetic is at fp32 precision for both dtypes (on the bf16 matrix cores, every fp32 factor
- * as the exact sum of three bf16 pieces).  Workspace of a PC_BF16 cache: 64 KB for
+ * as the exact sum of three bf16 pieces; for PC_F32 caches over the whole range of fp32, for
+ * PC_BF16 caches factors below 2^-110, about 8e-34, lose their last bits).  Workspace of a PC_BF16 cache: 64 KB for
  * each block of 32 rows and query head, of at most 256 MB at a time (longer batches go in
  * several runs) and a quarter of that in reserve; it stays with the cache.  Where the device
  * has no room for it the batch goes in as many shorter runs as the workspace in hand allows. */

@@ -15,10 +15,11 @@
 // Two kernels.  rows: 32 (row, head) columns of a KV head against the call's tiles: Delta and dq.  keys: a wave owns one 32-key tile of
 // the call, its keys turned to the call's positions, and the sums of dK and dV, while the call's column blocks go by.  A
 // row that saw nothing has no gradient: its queries and output gradients are taken as zeros.  Two calls of 82 and 109 rows over
-// 600 keys, 8/2 heads, D = 64: rows 27, keys 21 us, with the fp32 instruction 52 and 28, with a wave per (row, head) and a thread per
-// quarter key 212 and 390; one call of 15 rows over 90 keys, 8/2 heads, D = 128: 17 and 18.5 (25.7 and 33).  Such sizes are
+// 600 keys, 8/2 heads, D = 64: rows 26, keys 22 us, with the fp32 instruction 52 and 28, with a wave per (row, head) and a thread per
+// quarter key 212 and 390; one call of 15 rows over 90 keys, 8/2 heads, D = 128: 17.5 and 19 (25.7 and 33).  Such sizes are
 // bound by latency: 50 workgroups of rows, three tiles a wave.  Distances to fp64 in the 2-norm over 14 batches: dq 3.1e-7 to
-// 4.5e-7, dK 3.3e-7 to 4.4e-7, dV 2.9e-7 to 4.1e-7 (3.7e-7 to 4.7e-7, 3.7e-7 to 4.6e-7, 3.4e-7 to 4.3e-7 with the fp32 instruction).
+// 4.5e-7, dK 3.3e-7 to 4.4e-7, dV 2.9e-7 to 4.1e-7 (3.7e-7 to 4.7e-7, 3.7e-7 to 4.6e-7, 3.4e-7 to 4.3e-7 with the fp32 instruction); dq
+// 1.8e-7 to 3.9e-7 over 67 others since its sums are centred and a tile's product is added to them.
 #include "pc_pieces.h"
 
 #define MFMA_F32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0)
@@ -70,7 +71,7 @@ __device__ __forceinline__ i32x4 tile_at(const PcTile *tab, int t)
 // six times a product (100 thousand keys, D = 128: 1.0e-6 from fp64, 3.0e-6 with the sum taken along, 2.1e-6 with two walks on the fp32
 // instruction; a million, D = 64: 2.6e-6, 1.3e-5, 6.7e-6).  sum p K is all but cancelled by the centre and takes it along.
 // The vector work of a product's pieces stands beside the matrix work of the one before.  Two calls of 82 and 109 rows over 600
-// keys, 8/2 heads, D = 64: 27 us (52 with the fp32 instruction and two walks).
+// keys, 8/2 heads, D = 64: 26 us (52 with the fp32 instruction and two walks).
 template <int D> constexpr int row_waves = D == 64 ? 8 : 4;
 template <int D>
 __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(PcLaunch L, const float *__restrict__ lse, const float *__restrict__ d_out,
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(64 * row_waves<D>, 1) void pc_bwd_rows_f32_kernel(P
 // ds_read_b64_tr_b16: within 16 lanes, lane l points at row l / 4, columns 4 (l % 4) .. + 3 of a 4 x 16 block and receives column l,
 // rows 0 .. 3.  The sums meet those of the tokens' other placements (other calls, repeated listings, other splits of the
 // blocks) through one fp32 atomic per element, whole cache lines at a time.  Two calls of 82 and 109 rows over 600 keys, 8/2 heads,
-// D = 64: 21 us (28 with the fp32 instruction).
+// D = 64: 22 us (28 with the fp32 instruction).  D = 128 fills the 512 registers; 13 stand in scratch memory, 4 of them read in the loop.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 // A bf16 tile of 32 rows of D in LDS: chunk c (16 bytes) of row r sits at position c ^ swz(r) of the row; the rows of a fragment
 // read, and the four rows of a transposing one, hit different banks.

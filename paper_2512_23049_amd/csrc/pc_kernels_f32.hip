@@ -15,7 +15,7 @@
 // pc_plan_and_stage) and pc_merge_f32_kernel adds the parts.
 //
 // 200 rows over 1400 keys, 32/8 heads, D = 128: 49 us (77 with the fp32 instruction); 32 rows over 160 keys, 4/2 heads, D = 64:
-// 13.0 -> 10.1 us, all of it latency.  Distance to fp64 in the 2-norm 1.7e-7 to 3.0e-7 over ten shapes (2.2e-7 to 3.7e-7 with the
+// 13.0 -> 10.4 us, all of it latency.  Distance to fp64 in the 2-norm 1.7e-7 to 3.0e-7 over ten shapes (2.2e-7 to 3.7e-7 with the
 // fp32 instruction: its chains are four times as long).
 #include "pc_pieces.h"
 
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     // product, walks its tiles again on the fp32 instruction, with the caller's queries.  So does one with a result below 2^-100 that is not
     // zero, whose values may be below 2^-110 and have bits behind their pieces' last ones, and one with a wave whose column sees keys and has met none:
     // their scores may be below -2^96, infinities times UP twice.  What no number gives is found in the results: 8 (4) of them a thread there,
-    // 64 (32) in the waves' accumulators, which took 0.6 us to look through.
+    // 64 (32) in the waves' accumulators, which took 0.8 us to look through in the first example above.
     // There a probability of zero takes a key out of the second product only while its value is finite.  What lies behind a
     // message's last token is (the store is kept that way), but a later token of the new message is the caller's own
     // data: in a tile on the causal limit an Inf or NaN is left out and added at the end, for the columns that see its key.

@@ -577,7 +577,8 @@ static void plan_f32(const pc_cache *c, const Planned &P, std::vector<PcCallDesc
 
 // Key-major work items of the gradient of an fp32 batch: 4 key tiles a workgroup (one a wave), which fills a compute unit,
 // and the column blocks that see them split until the chip is full twice over, two blocks a split at least (a split ends in
-// one atomic per element of its tiles' dK and dV, about what one more block costs), or one where even so the chip is not full once.
+// one atomic per element of its tiles' dK and dV, about what one more block costs), or into as many splits as fill the chip once, where that is
+// more (two calls of 11 and 14 blocks, 24 groups of four tiles: 10 splits, of which 6 and 7 have blocks to take, two each).
 static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vector<PcBwdKeyItem> &keys)
 {
     const int g = c->g;
