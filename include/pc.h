@@ -172,7 +172,8 @@ typedef struct {
  *   out  device, same shape and dtype as q.
  *   lse  device, optional fp32 [sum n_q, n_q_heads]: natural-log sum of exp(scores).
  * A row with nothing visible yields zeros and -inf.  PC_F32 caches: fp32 precision over the whole
- * range of fp32, but for values below 2^-134 (5e-41), which may count as zeros. */
+ * range of fp32, but for values below 2^-134 (5e-41), which may count as zeros, and for keys with
+ * probabilities below 2^-110, which lose bits: seen where values are 2^100 times the others'. */
 int32_t pc_attend(pc_cache *c, const pc_call *calls, int32_t n_calls,
                   const void *q, void *out, float *lse, void *stream);
 
