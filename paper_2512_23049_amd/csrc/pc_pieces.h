@@ -77,9 +77,8 @@ template <typename T> __device__ __forceinline__ T from_lds(unsigned at) { retur
 template <int D>
 struct RowTile {
     static constexpr int BYTES = 32 * D * 4, CHUNKS = D / 4;
-    unsigned char *at;
     unsigned lds, src;
-    __device__ RowTile(unsigned char *mem, int lane) : at(mem), lds((unsigned)(uintptr_t)mem),
+    __device__ RowTile(unsigned char *mem, int lane) : lds((unsigned)(uintptr_t)mem),
         src((lane / CHUNKS) * (D * 4) + (((lane % CHUNKS) ^ (lane / CHUNKS)) << 4)) {}
     __device__ void request(const float *rows) const     // (wave uniform)
     {
@@ -89,7 +88,6 @@ struct RowTile {
 #pragma unroll
         for (int i = 0; i < 32 / STEP; ++i) dma16(rows + STEP * i * D, src ^ (((STEP * i) % CHUNKS) << 4), lds + i * 1024);
     }
-    __device__ float4 chunk(int row, int c) const { return *reinterpret_cast<const float4 *>(at + row * (D * 4) + ((c ^ (row % CHUNKS)) << 4)); }
 };
 
 }  // namespace
