@@ -35,6 +35,44 @@ struct PcTokenItem {
     int32_t new_len;          // the message's length once this token is in
 };
 
+// (cos, sin) of a rotation by x radians, |x| < 2^30, rounded to fp32 from fp64: x is taken to the nearest multiple of pi/2 (two
+// pieces of it; the product by the first is exact inside the fused operation) and the Taylor series of both functions are summed on
+// [-pi/4, pi/4], to 4e-14.  The device library's sincos takes every argument and every bit: some three times the instructions, and
+// branches that wait for their code.  Positions are below 2^30 and frequencies at most 1 wherever this is called, see rope_turn.
+__device__ __forceinline__ float2 rope_small(double x)
+{
+    const double q = __builtin_rint(x * 0.63661977236758134308);              // 2 / pi
+    double r = __builtin_fma(-q, 1.57079632679489655800, x);                  // pi/2 in fp64, and what is left of it
+    r = __builtin_fma(-q, 6.12323399573676603587e-17, r);
+    const double z = r * r;
+    double s = __builtin_fma(z, 1. / 6227020800., -1. / 39916800.);
+    s = __builtin_fma(z, s, 1. / 362880.);
+    s = __builtin_fma(z, s, -1. / 5040.);
+    s = __builtin_fma(z, s, 1. / 120.);
+    s = __builtin_fma(z, s, -1. / 6.);
+    s = __builtin_fma(r * z, s, r);
+    double c = __builtin_fma(z, 1. / 479001600., -1. / 3628800.);
+    c = __builtin_fma(z, c, 1. / 40320.);
+    c = __builtin_fma(z, c, -1. / 720.);
+    c = __builtin_fma(z, c, 1. / 24.);
+    c = __builtin_fma(z, c, -0.5);
+    c = __builtin_fma(z, c, 1.);
+    const int n = (int)q;                                // quarter turns
+    const float fs = (float)((n & 1) ? c : s), fc = (float)((n & 1) ? s : c);
+    return make_float2(((n + 1) & 2) ? -fc : fc, (n & 2) ? -fs : fs);
+}
+// The rotation of a position by a frequency.  (A cache may be created with theta < 1, whose frequencies have no such bound.)
+__device__ __forceinline__ float2 rope_turn(int pos, double freq)
+{
+    const double x = (double)pos * freq;
+    if (__builtin_expect(!(__builtin_fabs(x) < 0x1.0p+30), 0)) {
+        double s, c;
+        sincos(x, &s, &c);
+        return make_float2((float)c, (float)s);
+    }
+    return rope_small(x);
+}
+
 // A decode step's token: one frequency's pair of its key, turned.  The launches that append tokens and the decode launch that
 // writes them itself store the same bits: the roundings are spelled out.
 __device__ __forceinline__ float2 turn_token(float x, float y, float c, float s)

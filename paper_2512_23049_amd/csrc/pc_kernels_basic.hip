@@ -268,10 +268,8 @@ __device__ __forceinline__ void append_token_thread(const PcTokenItem it, int j,
 {
     const int half = D / 2;
     if (h == 0 && i0 == 0) table[it.msg].len = it.new_len;      // every item of a message carries its final length
-    double s0, c0, s1, c1;
-    sincos((double)it.pos * inv_freq[i0], &s0, &c0);
-    sincos((double)it.pos * inv_freq[i0 + 1], &s1, &c1);
-    const float fc0 = (float)c0, fs0 = (float)s0, fc1 = (float)c1, fs1 = (float)s1;
+    const float2 cs0 = rope_turn(it.pos, inv_freq[i0]), cs1 = rope_turn(it.pos, inv_freq[i0 + 1]);
+    const float fc0 = cs0.x, fs0 = cs0.y, fc1 = cs1.x, fs1 = cs1.y;
     const T *ksrc = k + ((int64_t)j * n_kv_heads + h) * D;
     const T *vsrc = v + ((int64_t)j * n_kv_heads + h) * D;
     T *kdst = k_store + ((int64_t)h * slots + it.slot) * D;

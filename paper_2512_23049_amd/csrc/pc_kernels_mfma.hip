@@ -45,21 +45,33 @@ struct DecTile {
     bool self;          // a tile of the new message
 };
 
+// Sixteen loads whatever the tile: loads under conditions of their own make the compiler wait for all that is in flight, the next tile
+// included, before it uses any of it.  Keys and groups of values past the tile's end read the last one
+// that exists (no further line of memory); drop_dead takes the values out.  A uniform address and a 32-bit offset a lane.
 __device__ __forceinline__ void dec_load(DecTile &T, const uint16_t *__restrict__ kb, const uint16_t *__restrict__ vb,
                                          int slot0, int valid, int lane)
 {
-    const int m = lane & 15, a = lane >> 4;
-    const uint4 z = make_uint4(0, 0, 0, 0);
+    const int m = lane & 15, a = lane >> 4, last = max(valid - 1, 0);
+    const char *kt = reinterpret_cast<const char *>(kb + (int64_t)slot0 * PC_D), *vt = reinterpret_cast<const char *>(vb + (int64_t)slot0 * PC_D);
 #pragma unroll
     for (int tau = 0; tau < 2; ++tau) {
-        const int key = 8 * (m >> 2) + 4 * tau + (m & 3);
-        const uint16_t *row = kb + (int64_t)(slot0 + key) * PC_D + 8 * a;
+        const unsigned at = (unsigned)(min(8 * (m >> 2) + 4 * tau + (m & 3), last) * (PC_D * 2) + 16 * a);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) T.k[tau][ks] = (key < valid) ? ldg16(row + 32 * ks) : z;
+        for (int ks = 0; ks < 4; ++ks) T.k[tau][ks] = ldg16(kt + at + 64 * ks);
     }
-    const uint16_t *vg = vb + ((int64_t)(slot0 / PC_VGROUP + a) * PC_D + m) * PC_VGROUP;
+    const unsigned at = (unsigned)(min(a, last / PC_VGROUP) * (PC_D * PC_VGROUP * 2) + m * (PC_VGROUP * 2));
 #pragma unroll
-    for (int db = 0; db < 8; ++db) T.v[db] = (8 * a < valid) ? ldg16(vg + 16 * db * PC_VGROUP) : z;
+    for (int db = 0; db < 8; ++db) T.v[db] = ldg16(vt + at + 16 * db * (PC_VGROUP * 2));
+}
+// the groups of values that hold no token, as zeros: what stands in for them may be infinite, and their probabilities are zero
+__device__ __forceinline__ void drop_dead(DecTile &T, int lane)
+{
+    const bool dead = 8 * (lane >> 4) >= T.valid;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+        T.v[db].x = dead ? 0u : T.v[db].x; T.v[db].y = dead ? 0u : T.v[db].y;
+        T.v[db].z = dead ? 0u : T.v[db].z; T.v[db].w = dead ? 0u : T.v[db].w;
+    }
 }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -87,7 +99,7 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
 
     const uint16_t *kb = (const uint16_t *)L.k_store + (int64_t)kh * L.slots * PC_D;
     const uint16_t *vb = (const uint16_t *)L.v_store + (int64_t)kh * L.slots * PC_D;
-    auto fetch = [&](DecTile &T, int t) {                // t is the tile next_desc describes
+    auto fetch = [&](DecTile &T, int t) __attribute__((always_inline)) {       // t is the tile next_desc describes
         const i32x4 d = next_desc;
         next_desc = describe(t + 1);
         T.seg = d.z; T.key0 = d.y; T.valid = d.w & 0xFF; T.fresh = (d.w & PC_TILE_FRESH) != 0; T.self = (d.w & PC_TILE_SELF) != 0;
@@ -101,7 +113,10 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
         uint4 raw[2][2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) { raw[ks][0] = ldg16(qp + 32 * ks); raw[ks][1] = ldg16(qp + 32 * ks + 64); }
-        const float2 *rq = q_rot(col_ok ? qr : 0, [&]() { if (tile < tile_stop) fetch(A, tile); }) + 8 * a;
+        const float2 *rq = q_rot(col_ok ? qr : 0, [&]() __attribute__((always_inline)) {
+            if (tile < tile_stop) fetch(A, tile);
+            if (tile + 1 < tile_stop) fetch(B, tile + 1);
+        }) + 8 * a;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const uint4 lo = raw[ks][0], hi = raw[ks][1];
@@ -125,7 +140,7 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
 
     int cur_seg = -1;
     bf16x8 qop[4];
-    auto compute = [&](const DecTile &T) {
+    auto compute = [&](DecTile &T) __attribute__((always_inline)) {
         if (T.fresh || cur_seg < 0) {                    // turn the query by -(segment start - stored base): a new
             cur_seg = T.seg;                             // rotation starts here, or the wave starts inside a segment
             const float2 *rs = seg_rot(cur_seg) + 8 * a;
@@ -159,6 +174,7 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
         if (T.valid < PC_TILE || T.self) {      // ragged or causal tile (uniform over the wave): mask
 #pragma unroll
             for (int j = 0; j < 8; ++j) sc[j] = (8 * a + j < lim) ? sc[j] : -INFINITY;
+            drop_dead(T, lane);
         }
         float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
         mx = max_lanes_xor16(mx);
@@ -179,20 +195,34 @@ __device__ __forceinline__ void decode_walk(const PcLaunch &L, const DecCall cd,
         m_run = m_new;
         const bool rescale = __builtin_amdgcn_ballot_w64(alpha != 1.f) != 0;   // rare once the running maxima have settled
         const bf16x8 pop = __builtin_bit_cast(bf16x8, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+        if (rescale) {
 #pragma unroll
-        for (int db = 0; db < 8; ++db) {
-            if (rescale) acc[db] *= alpha;
-            acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, T.v[db]), pop, acc[db], 0, 0, 0);
+            for (int db = 0; db < 8; ++db) acc[db] *= alpha;
         }
+#pragma unroll
+        for (int db = 0; db < 8; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, T.v[db]), pop, acc[db], 0, 0, 0);
     };
 
-    while (tile < tile_stop) {
-        if (tile + 1 < tile_stop) fetch(B, tile + 1);
+    // A tile is requested as soon as its registers are free, two tiles ahead.  The long part of the walk has no way through it but one: where a
+    // path on which a tile was not requested joins, the compiler waits for all that is in flight.  (us a step: 64 calls over 146 tiles of 10
+    // messages each 131 -> 127, one over 770 of 151 26.3 -> 25.8, four over 24 of 5 10.9 -> 10.7.)
+    // (Not behind the plan builder, whose rotations come from memory: 11 registers too many.)
+    if (ONE && tile + 3 < tile_stop) {
+        __builtin_amdgcn_s_waitcnt(0x4F70);              // vmcnt(16): the first tile is there
+        do {
+            compute(A);
+            fetch(A, tile + 2);
+            compute(B);
+            fetch(B, tile + 3);
+            tile += 2;
+        } while (tile + 3 < tile_stop);
+    }
+    while (tile < tile_stop) {                           // three tiles or fewer, the first two of them requested
         compute(A);
-        ++tile;
-        if (tile >= tile_stop) break;
-        if (tile + 1 < tile_stop) fetch(A, tile + 1);
+        if (tile + 2 < tile_stop) fetch(A, tile + 2);
+        if (++tile >= tile_stop) break;
         compute(B);
+        if (!ONE && tile + 2 < tile_stop) fetch(B, tile + 2);
         ++tile;
     }
 
@@ -412,31 +442,30 @@ __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(c
         const int64_t row = ((int64_t)cd.tok * L.n_kv_heads + kh) * PC_D + lane;
         tok[0] = O.tok_k[row]; tok[1] = O.tok_k[row + PC_D / 2]; tok[2] = O.tok_v[row]; tok[3] = O.tok_v[row + PC_D / 2];
     }
-    auto prepare = [&](int r, auto first_tile) {
-        if (!token) first_tile();
+    // (the host keeps positions times frequencies below 2^28)
+    if (token) {
+        const int at = cd.self_len - 1;
+        const float2 cs = rope_small((double)(__builtin_amdgcn_readlane(m_base, self_lane) + at) * freq);
+        const int64_t slot = __builtin_amdgcn_readlane(m_slot, self_lane) + at;
+        const float2 turned = turn_token(bf_lo(tok[0]), bf_lo(tok[1]), cs.x, cs.y);
+        uint16_t *kd = (uint16_t *)const_cast<void *>(L.k_store) + (kh * L.slots + slot) * PC_D + lane;
+        kd[0] = to_bf16(turned.x);
+        kd[PC_D / 2] = to_bf16(turned.y);
+        uint16_t *vd = (uint16_t *)const_cast<void *>(L.v_store) + ((kh * L.slots + slot) / PC_VGROUP * PC_D + lane) * PC_VGROUP + slot % PC_VGROUP;
+        vd[0] = tok[2];
+        vd[PC_D / 2 * PC_VGROUP] = tok[3];
+        if (kh == 0 && lane == 0) O.table[__builtin_amdgcn_readlane(m, self_lane)].len = cd.self_len;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");              // the token is written before this wave reads its tile
+    }
+    auto prepare = [&](int r, auto first_tiles) __attribute__((always_inline)) {
+        first_tiles();
         typedef const __attribute__((address_space(4))) int32_t *KernArgInt;
         const KernArgInt q_pos = (KernArgInt)(args + O.off_q_pos) + cd.q_off;
         const int n_ent = item.n_seg + cd.n_q;
-        for (int e = token ? -1 : wave; e < n_ent; e = e < 0 ? wave : e + ONE_WAVES) {      // -1: the token
-            const int at = cd.self_len - 1;
-            const int pos = e < 0 ? __builtin_amdgcn_readlane(m_base, self_lane) + at : e < item.n_seg ? __builtin_amdgcn_readlane(m_rot, e) : q_pos[e - item.n_seg];
-            const double x = (double)pos * freq;
-            if (!(fabs(x) < 0x1.0p+30)) __builtin_unreachable();     // (the host keeps positions below that: no code for larger arguments)
-            double s, c;
-            sincos(x, &s, &c);
-            const float2 cs = make_float2((float)c, (float)s);
-            if (e >= 0) { s_rot[e < item.n_seg ? e : e - item.n_seg + PC_ONE_SEGS][lane] = cs; continue; }
-            const int64_t slot = __builtin_amdgcn_readlane(m_slot, self_lane) + at;
-            const float2 turned = turn_token(bf_lo(tok[0]), bf_lo(tok[1]), cs.x, cs.y);
-            uint16_t *kd = (uint16_t *)const_cast<void *>(L.k_store) + (kh * L.slots + slot) * PC_D + lane;
-            kd[0] = to_bf16(turned.x);
-            kd[PC_D / 2] = to_bf16(turned.y);
-            uint16_t *vd = (uint16_t *)const_cast<void *>(L.v_store) + ((kh * L.slots + slot) / PC_VGROUP * PC_D + lane) * PC_VGROUP + slot % PC_VGROUP;
-            vd[0] = tok[2];
-            vd[PC_D / 2 * PC_VGROUP] = tok[3];
-            if (kh == 0 && lane == 0) O.table[__builtin_amdgcn_readlane(m, self_lane)].len = cd.self_len;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // the token is written before this wave reads its tile
-            first_tile();
+#pragma unroll 1
+        for (int e = wave; e < n_ent; e += ONE_WAVES) {
+            const int pos = e < item.n_seg ? __builtin_amdgcn_readlane(m_rot, e) : q_pos[e - item.n_seg];
+            s_rot[e < item.n_seg ? e : e - item.n_seg + PC_ONE_SEGS][lane] = rope_small((double)pos * freq);
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): the rows are in LDS (tiles may still be on their way)
         asm volatile("s_barrier" ::: "memory");
