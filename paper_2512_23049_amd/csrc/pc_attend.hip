@@ -61,6 +61,23 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         }
         return PC_OK;
     }
+    if (P.runs_bytes > 0) {
+        {
+            ProfScope ps(c, 3, st);
+            pc_launch_decode_runs_bf16(L, P.runs, P.run_starts, st);
+            PC_HIP(c, hipGetLastError());
+        }
+        {
+            ProfScope ps(c, 4, st);
+            pc_launch_merge(c->cfg.dtype, (const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, 4, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
+            PC_HIP(c, hipGetLastError());
+        }
+        if (P.runs_slot) {                               // the ring slot is free again once the launches are done
+            PC_HIP(c, hipEventRecord(P.runs_slot->ev, st));
+            P.runs_slot->used = true;
+        }
+        return PC_OK;
+    }
     if (c->cfg.dtype == PC_F32) {
         {
             ProfScope ps(c, 5, st);

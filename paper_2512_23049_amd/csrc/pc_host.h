@@ -165,6 +165,8 @@ struct Planned {
     // A decode batch that goes to one launch (one_bytes > 0): nothing was staged or launched for it yet
     PcArgBlob one_blob; size_t one_bytes = 0; PcOne one{}; StageSlot *one_slot = nullptr;      // (one_slot: its lists are in the pinned ring)
     std::vector<char> recorded;                          // staged lists of a call that is recorded into a graph (see pc_recorded)
+    // A decode batch by message (runs_bytes > 0): its lists are staged, nothing was launched for it yet
+    size_t runs_bytes = 0; int n_runs = 0; PcRuns runs{}; PcRunStarts run_starts; StageSlot *runs_slot = nullptr;
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
     int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)

@@ -191,6 +191,20 @@ struct PcOneItem {
 #define PC_ONE_SEGS 64        // most of them (a wave holds them, one a lane)
 #define PC_ONE_COUNTERS 256   // (call, KV head) pairs of a batch whose calls are split (two splits each: two rounds of workgroups)
 
+// ---- a decode batch by message: a wave streams a run of tiles of one message for up to PC_RUN_ROWS of the one-row calls that list it ----
+#define PC_RUN_ROWS 4
+#define PC_RUN_WAVES 1024     // most waves a KV head's runs are shared out over (their first runs travel in the kernel's arguments)
+struct PcMsgRun {             // one cache line
+    int32_t msg;
+    int32_t tile0;            // first tile of the run within the message
+    int32_t size;             // tiles of the run | rows << 28
+    int32_t pad;
+    int32_t row[PC_RUN_ROWS];     // packed query rows
+    int32_t part[PC_RUN_ROWS];    // fp32 partial rows of the run's results
+    int32_t pos[PC_RUN_ROWS];     // the rows' positions minus the positions their calls give the message's first token
+};
+struct PcRunStarts { uint16_t first[PC_RUN_WAVES + 2]; };       // wave w of a KV head takes the runs [first[w], first[w + 1])
+
 #define PC_MERGE_WIDE 0x10000     // partial outputs in fp32 (bf16 caches)
 // One output row whose KV splits the merge kernel combines (staged by the host).
 struct PcMergeRow {
@@ -274,6 +288,14 @@ struct PcOne {
     const void   *lists;              // in pinned host memory or the workspace, or null: in the arguments
     int32_t       off_sel, off_q_pos, off_items;      // within the lists, in bytes
     int32_t       n_items;
+};
+
+// A decode batch by message: what the kernel needs besides PcLaunch.
+struct PcRuns {
+    const PcMsgEntry *table;
+    const PcMsgRun   *runs;
+    const float2     *rot;            // [run][PC_RUN_ROWS][D/2] (cos, sin) of the row's position as seen from the message's stored keys, times the scores' scale
+    int32_t           n_waves;
 };
 
 // Gradient of a bf16 batch: what its kernels need besides PcLaunch (whose items are the row-major kernels').  A unit is

@@ -680,6 +680,54 @@ __global__ __launch_bounds__(256) void pc_build_plan_arg_kernel(
                      total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks);
 }
 
+// What a decode batch by message needs in front of it: its lists, from pinned memory (where they are read) to the workspace, the rotations
+// of its runs' rows, and a step's new tokens.  Three kinds of blocks: four runs, one a wave (what is in pinned memory is read once, a line a run;
+// read by blocks of their own and again for the rotations, 900 runs took 8.3 us); rows to merge; tokens.
+__global__ __launch_bounds__(256) void pc_runs_prepare_kernel(const int32_t *__restrict__ lists, int32_t *__restrict__ to, int n_runs, int n_rest, int run_blocks, int rest_blocks,
+                                                              float scale, PcTokenWork tok, const double *__restrict__ inv_freq, PcMsgEntry *__restrict__ table,
+                                                              float2 *__restrict__ rot)
+{
+    constexpr int WORDS = sizeof(PcMsgRun) / 4;
+    int block = (int)blockIdx.x;
+    if (block < run_blocks) {
+        const int run = 4 * block + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+        if (run >= n_runs) return;
+        const int w = lane < WORDS ? lists[(int64_t)run * WORDS + lane] : 0;
+        const double freq = inv_freq[lane];
+        if (to && lane < WORDS) to[(int64_t)run * WORDS + lane] = w;
+        const int base = table[__builtin_amdgcn_readlane(w, offsetof(PcMsgRun, msg) / 4)].base_pos, n_rows = __builtin_amdgcn_readlane(w, offsetof(PcMsgRun, size) / 4) >> 28;
+#pragma unroll 1
+        for (int r = 0; r < n_rows; ++r) {
+            const float2 cs = rope_turn(__builtin_amdgcn_readlane(w, (int)offsetof(PcMsgRun, pos) / 4 + r) + base, freq);
+            rot[((int64_t)run * PC_RUN_ROWS + r) * 64 + lane] = make_float2(cs.x * scale, cs.y * scale);
+        }
+        return;
+    }
+    block -= run_blocks;
+    if (block < rest_blocks) {
+        const int i = n_runs * WORDS + block * 256 + (int)threadIdx.x;
+        if (i < n_runs * WORDS + n_rest) to[i] = lists[i];
+        return;
+    }
+    block -= rest_blocks;
+    const int per_row = tok.D / 4;
+    const int64_t tid = (int64_t)block * 256 + threadIdx.x;
+    if (tid >= (int64_t)tok.n * tok.n_kv_heads * per_row) return;
+    const int j = (int)(tid / ((int64_t)per_row * tok.n_kv_heads));
+    append_token_thread<uint16_t>(tok.items[j], j, (int)((tid / per_row) % tok.n_kv_heads), 2 * (int)(tid % per_row), (const uint16_t *)tok.k, (const uint16_t *)tok.v,
+                                  tok.n_kv_heads, tok.D, tok.slots, inv_freq, (uint16_t *)tok.k_store, (uint16_t *)tok.v_store, table);
+}
+
+void pc_launch_runs_prepare(const void *lists, void *to, size_t bytes, int n_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
+                            float2 *rot, hipStream_t st)
+{
+    const int n_rest = lists != to ? (int)(bytes / 4) - n_runs * (int)(sizeof(PcMsgRun) / 4) : 0;
+    const unsigned run_blocks = (unsigned)(n_runs + 3) / 4, rest_blocks = (unsigned)(n_rest + 255) / 256;
+    const unsigned tok_blocks = (unsigned)(((int64_t)tok.n * tok.n_kv_heads * (tok.D / 4) + 255) / 256);
+    pc_runs_prepare_kernel<<<run_blocks + rest_blocks + tok_blocks, 256, 0, st>>>((const int32_t *)lists, lists != to ? (int32_t *)to : nullptr, n_runs, n_rest, (int)run_blocks,
+                                                                                  (int)rest_blocks, scale, tok, inv_freq, table, rot);
+}
+
 static unsigned plan_blocks(int n_calls, int tile_blocks, int half, int total_seg, int total_q, const PcTokenWork &tok, int &tok_block0)
 {
     const int64_t n_rot = ((int64_t)total_seg + total_q) * half;
@@ -782,6 +830,7 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
 {
     constexpr int D = 128;
     constexpr int TPP = 16 * SL;                         // threads per (row, head)
+    constexpr int U = SL == 4 ? 8 : 4;                   // splits requested together
     const int pair = blockIdx.x * (256 / TPP) + (int)threadIdx.x / TPP;
     if (pair >= n_pairs) return;                         // (SL = 4: whole waves)
     const int sub = threadIdx.x & 15, sg = ((int)threadIdx.x % TPP) >> 4;
@@ -795,11 +844,11 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
     for (int j = 0; j < 8; ++j) o[j] = 0.f;
     auto fold = [&](auto is_wide) __attribute__((always_inline)) {
         constexpr int WIDE = decltype(is_wide)::value ? 1 : 0;
-        for (int s0 = s_begin; s0 < s_end; s0 += 4) {
-            float2 ml[4];
-            uint4 v[4][1 + WIDE];                        // eight fp16, or eight fp32
+        for (int s0 = s_begin; s0 < s_end; s0 += U) {
+            float2 ml[U];
+            uint4 v[U][1 + WIDE];                        // eight fp16, or eight fp32
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 ml[u] = make_float2(-INFINITY, 0.f);
 #pragma unroll
                 for (int k = 0; k <= WIDE; ++k) v[u][k] = make_uint4(0, 0, 0, 0);
@@ -813,7 +862,7 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
             }
             float m_new = m;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, ml[u].x);
+            for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, ml[u].x);
             if (m_new == -INFINITY) continue;
             const float keep = (m > -INFINITY) ? exp2f(m - m_new) : 0.f;
             l *= keep;
@@ -821,7 +870,7 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
             for (int j = 0; j < 8; ++j) o[j] *= keep;
             m = m_new;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {                // in split order
+            for (int u = 0; u < U; ++u) {                // in split order
                 const float w = (ml[u].x > -INFINITY) ? ml[u].y * exp2f(ml[u].x - m) : 0.f;
                 l += w;
                 const uint32_t d[4] = {v[u][0].x, v[u][0].y, v[u][0].z, v[u][0].w};

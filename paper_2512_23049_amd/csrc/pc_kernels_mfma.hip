@@ -35,6 +35,13 @@ __device__ __forceinline__ float max_lanes_xor32(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// One 16-byte-per-lane direct load: lane l's 16 bytes land at lds_wave_base + 16*l (see pc_kernels_prefill.hip)
+__device__ __forceinline__ void dma16(const void *gbase_uniform, unsigned lane_off, unsigned lds_wave_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 ::"s"(lds_wave_base), "v"(lane_off), "s"(gbase_uniform) : "memory", "m0");
+}
+
 struct DecTile {
     uint4 k[2][4];      // [16-key half][d step of 32]
     uint4 v[8];         // [16-d block]
@@ -42,7 +49,8 @@ struct DecTile {
     int key0;           // first in-message token of the tile
     int valid;          // tokens of the tile that exist (1..32)
     bool fresh;         // first tile of a segment whose query rotation differs from the one before
-    bool self;          // a tile of the new message
+    bool self;          // a tile of the new message (by message: a run's last one)
+    bool there;         // (by message) there is such a tile
 };
 
 // Sixteen loads whatever the tile: loads under conditions of their own make the compiler wait for all that is in flight, the next tile
@@ -500,6 +508,186 @@ void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaun
     if (O.lists) pc_decode_one_bf16_kernel<<<grid, 64 * ONE_WAVES, 0, st>>>(PcArgs<0>(), L, O);
     else if (bytes <= 768) launch(PcArgs<768>());
     else launch(PcArgs<PC_ARG_BYTES>());
+}
+
+__device__ __forceinline__ int pick(int i, int a, int b, int c, int d) { return i < 2 ? (i == 0 ? a : b) : (i == 2 ? c : d); }
+
+// A batch of one-row decode calls by message.  Calls that list the same messages out of step (64 calls over a common system message and
+// 8 of 512 others each) fetch most of them once per call when every call walks its own list, yet leave most of the 16 columns of the matrix
+// instructions empty.  Here the messages are the work: every wave streams an even share of all tiles, run after run in slot order,
+// and a run's columns are the heads of up to PC_RUN_ROWS calls that list the message.  A run ends in an fp32 part per (row, head), which
+// the merge launch adds in slot order.  Waves are on their own: no barrier, nothing shared but the L2s.
+__global__ __launch_bounds__(256, 2) void pc_decode_runs_bf16_kernel(const PcRunStarts starts, PcLaunch L, PcRuns O)
+{
+    // each wave's requested run: the rotations of its rows, and its columns' queries (chunk c of 16 bytes of column n at c ^ n)
+    __shared__ __attribute__((aligned(1024))) float2 s_rot[4][PC_RUN_ROWS][PC_D / 2];
+    __shared__ __attribute__((aligned(1024))) uint4 s_q[4][16][16];
+    typedef int i32x8 __attribute__((ext_vector_type(8)));
+    const int kh = blockIdx.x % L.n_kv_heads;            // consecutive workgroups (one per XCD) take different KV heads
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, a = lane >> 4;
+    const int w = 4 * (blockIdx.x / L.n_kv_heads) + wave;
+    if (w >= O.n_waves) return;
+    const auto *firsts = (const __attribute__((address_space(4))) uint16_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int first = __builtin_amdgcn_readfirstlane(firsts[w]), end = __builtin_amdgcn_readfirstlane(firsts[w + 1]);
+    if (first >= end) return;
+    // column n: row n / g of the run, head n % g of the group (g is 1, 2, 4 or 8 here)
+    const int g = L.n_q_heads / L.n_kv_heads, lg = __builtin_ctz(g);
+    auto fresh_lane = [&]() __attribute__((always_inline)) { int l = lane; asm volatile("" : "+v"(l)); return l; };
+    // (scalar loads; what is uniform over the wave is said to be, wherever the compiler cannot see it)
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    auto load_run = [&](int i) __attribute__((always_inline)) { return *reinterpret_cast<const __attribute__((address_space(4))) i32x8 *>(reinterpret_cast<uintptr_t>(O.runs + uniform(i))); };
+    auto load_parts = [&](int i) __attribute__((always_inline)) { return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(&O.runs[uniform(i)].part)); };
+    auto load_entry = [&](int m) __attribute__((always_inline)) { return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(O.table + uniform(m))); };
+
+    const uint16_t *kb = (const uint16_t *)L.k_store + (int64_t)kh * L.slots * PC_D;
+    const uint16_t *vb = (const uint16_t *)L.v_store + (int64_t)kh * L.slots * PC_D;
+    // The requests' place: the run being requested, and the one behind it.  A tile is requested while the one before it is computed.
+    int at_run = first, at_tile = 0, left = 0, slot = 0, len = 0, run_rows = 0;
+    i32x8 ahead = load_run(first);
+    i32x4 entry = load_entry(ahead[0]);
+    int rows = 0, p0 = 0, p1 = 0, p2 = 0, p3 = 0;        // of the run being computed, and their parts
+    const unsigned lds_rot = (unsigned)(size_t)&s_rot[0][0][0] + wave * (unsigned)sizeof(s_rot[0]);
+    const unsigned lds_q = (unsigned)(size_t)&s_q[0][0][0] + wave * (unsigned)sizeof(s_q[0]);
+    auto fetch = [&](DecTile &T) __attribute__((always_inline)) {
+        T.fresh = false;
+        if (left == 0 && at_run < end) {
+            T.fresh = true;
+            slot = uniform(entry.x); len = uniform(entry.y);
+            at_tile = uniform(ahead[1]); left = uniform(ahead[2]) & 0xFFFFFFF; run_rows = uniform(ahead[2]) >> 28;
+            // (the lane anew, here and below: held across the loop, addresses that follow from it cost registers that tiles in flight need)
+            const int ln = fresh_lane(), r0 = uniform(ahead[4]), r1 = uniform(ahead[5]), r2 = uniform(ahead[6]), r3 = uniform(ahead[7]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                // columns 4 i + lane / 16
+                const int col = 4 * i + (ln >> 4), cr = col >> lg, c0 = cr < run_rows ? cr : 0;
+                dma16(L.q, (unsigned)((pick(c0, r0, r1, r2, r3) * L.n_q_heads + kh * g + (col & (g - 1))) * (PC_D * 2) + (((ln & 15) ^ col) << 4)), lds_q + i * 1024);
+            }
+            const float2 *rot = O.rot + (int64_t)uniform(at_run) * PC_RUN_ROWS * (PC_D / 2);
+            dma16(rot, 16 * ln, lds_rot);                // rows 0 and 1, 2 and 3
+            dma16(rot + PC_D, 16 * ln, lds_rot + 1024);
+            if (++at_run < end) ahead = load_run(at_run);
+        }
+        // (behind the wave's last tile: a line of it)
+        T.there = left > 0;
+        const int key0 = T.there ? at_tile * PC_TILE : 0;
+        T.valid = T.there ? min(len - key0, PC_TILE) : 1;
+        dec_load(T, kb, vb, slot + key0, T.valid, lane);
+        ++at_tile;
+        T.self = --left == 0;                            // (the run's last tile)
+        left = max(left, 0);
+    };
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4 acc[8];
+    bf16x8 qop[4];
+    auto clear = [&]() __attribute__((always_inline)) {
+        m_run = -INFINITY; l_run = 0.f;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) acc[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
+    // the requested run becomes the computed one: its columns' queries turned by where their calls see them from the message, scaled
+    auto begin = [&]() __attribute__((always_inline)) {
+        rows = run_rows;
+        const i32x4 parts = load_parts(at_run - 1);
+        p0 = uniform(parts.x); p1 = uniform(parts.y); p2 = uniform(parts.z); p3 = uniform(parts.w);
+        // (in LDS once all but the 16 requests of the run's first tile, which are behind them, are done)
+        __builtin_amdgcn_s_waitcnt(0x4F70);              // vmcnt(16)
+        asm volatile("" ::: "memory");
+        const int ln = fresh_lane(), n = ln & 15, a = ln >> 4, ri = n >> lg;
+        const bool ok = ri < rows;
+        const float2 *rq = &s_rot[wave][ok ? ri : 0][8 * a];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint4 lo = s_q[wave][n][(4 * ks + a) ^ n], hi = s_q[wave][n][(4 * ks + a + 8) ^ n];
+            const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
+            uint32_t pl[4], ph[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float2 c0 = rq[32 * ks + 2 * j], c1 = rq[32 * ks + 2 * j + 1];
+                const float x0 = bf_lo(lw[j]), x1 = bf_hi(lw[j]), y0 = bf_lo(hw[j]), y1 = bf_hi(hw[j]);
+                pl[j] = ok ? pack_bf16(x0 * c0.x - y0 * c0.y, x1 * c1.x - y1 * c1.y) : 0u;
+                ph[j] = ok ? pack_bf16(x0 * c0.y + y0 * c0.x, x1 * c1.y + y1 * c1.x) : 0u;
+            }
+            qop[ks] = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+            qop[ks + 2] = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // (read before the next run's come)
+        if (at_run < end) entry = load_entry(ahead[0]);
+        clear();
+    };
+    auto compute = [&](DecTile &T) __attribute__((always_inline)) {
+        f32x4 s[2];
+#pragma unroll
+        for (int tau = 0; tau < 2; ++tau) {
+            s[tau] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                s[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, T.k[tau][ks]), qop[ks], s[tau], 0, 0, 0);
+        }
+        float sc[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sc[j] = s[j >> 2][j & 3];
+        if (T.valid < PC_TILE) {                         // (one row a call, its message's last token: a row sees all there is)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sc[j] = (8 * a + j < T.valid) ? sc[j] : -INFINITY;
+            drop_dead(T, lane);
+        }
+        float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+        mx = max_lanes_xor16(mx);
+        mx = max_lanes_xor32(mx);
+        const float m_new = fmaxf(m_run, mx);
+        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        uint32_t pk[4];
+        float ps = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {                    // (the row sum over the rounded probabilities, as in decode_walk)
+            pk[j] = pack_bf16(__builtin_amdgcn_exp2f(sc[2 * j] - m_safe), __builtin_amdgcn_exp2f(sc[2 * j + 1] - m_safe));
+            ps += bf_lo(pk[j]) + bf_hi(pk[j]);
+        }
+        l_run = l_run * alpha + ps;
+        m_run = m_new;
+        const bool rescale = __builtin_amdgcn_ballot_w64(alpha != 1.f) != 0;
+        const bf16x8 pop = __builtin_bit_cast(bf16x8, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+        if (rescale) {
+#pragma unroll
+            for (int db = 0; db < 8; ++db) acc[db] *= alpha;
+        }
+#pragma unroll
+        for (int db = 0; db < 8; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, T.v[db]), pop, acc[db], 0, 0, 0);
+        if (!T.self) return;
+        // the run's part
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        const int ln = fresh_lane(), ri = (ln & 15) >> lg, rh = ln & 15 & (g - 1), a = ln >> 4;
+        if (ri < rows) {
+            const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+            const int part = pick(ri, p0, p1, p2, p3);
+            const int h = kh * g + rh;
+            f32x4 *po = reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(L.part_o) + ((int64_t)part * L.n_q_heads + h) * PC_D + 4 * a);     // dims 16 db + 4 a + 0..3
+#pragma unroll
+            for (int db = 0; db < 8; ++db) po[4 * db] = acc[db] * inv;
+            if (a == 0) *reinterpret_cast<float2 *>(L.part_ml + (2 * (int64_t)part * L.n_q_heads + h) * 2) = make_float2(m_run, l_run);
+        }
+    };
+    // Two tiles are in flight.  A run's queries and rotations have one place in LDS: they are requested with its first tile, which is when the
+    // run before it, whose place it is, has been begun.
+    DecTile A, B;
+    fetch(A);
+    begin();
+    fetch(B);
+    do {                                                 // (one way out, as in decode_walk)
+        compute(A);
+        if (B.fresh) begin();
+        fetch(A);
+        if (B.there) compute(B);
+        if (A.fresh) begin();
+        fetch(B);
+    } while (A.there);
+}
+
+void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunStarts &starts, hipStream_t st)
+{
+    pc_decode_runs_bf16_kernel<<<(unsigned)((O.n_waves + 3) / 4 * L.n_kv_heads), 256, 0, st>>>(starts, L, O);
 }
 
 void pc_launch_decode_bf16(const PcLaunch &L, int n_items, hipStream_t st)

@@ -195,18 +195,121 @@ constexpr double SHARE_MIN = 6.0;
 // rows with more splits than this are merged by four lanes per 8 dimensions
 constexpr int MERGE_MANY_SPLITS = 8;
 
-static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vector<int> &q_off, int g, SharedPlan &sp)
+// The union of the lists of some one-row calls: which messages there are, who lists each, and where.
+struct Union {
+    struct Seg { int32_t msg, occ, len; int64_t slot; uint32_t vis[8]; };      // bit n of vis: row n lists it
+    std::vector<Seg> segs;                                // as they turn up
+    std::vector<int32_t> pos;                             // [seg][row] start - stored base, PC_SH_ABSENT where the row does not list it
+    std::vector<int32_t> order;                           // segs in cache-slot order
+    int n_rows = 0;
+    int64_t call_tiles = 0, tiles = 0;
+};
+
+// (false: more messages than segs_max.  Raw pointers, one pass: the lists of long calls are collected on every step of a decode loop)
+static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_rows, size_t segs_max, Union &un)
 {
+    const HostMsg *msgs = c->msgs.data();
+    std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> seg, for repeats within a call
+    un.segs.clear(); un.pos.clear();
+    un.n_rows = n_rows; un.call_tiles = 0;
+    const uint32_t epoch = new_marks(c);                 // value: the message's place in segs
+    pc_cache::Mark *marks = c->marks.data();
+    Union::Seg *segs = un.segs.data();
+    int32_t *pos = un.pos.data();
+    auto add = [&](int32_t m, int32_t occ) {
+        un.segs.push_back(Union::Seg{m, occ, msgs[m].len, msgs[m].slot_start, {0, 0, 0, 0, 0, 0, 0, 0}});
+        un.pos.resize(un.pos.size() + (size_t)n_rows, PC_SH_ABSENT);
+        segs = un.segs.data(); pos = un.pos.data();
+        return (int32_t)un.segs.size() - 1;
+    };
+    auto lookup = [&](int32_t m, int32_t occ) -> int32_t {
+        if (occ == 0) {
+            if (marks[m].epoch != epoch) marks[m] = pc_cache::Mark{epoch, add(m, 0)};
+            return marks[m].value;
+        }
+        const int64_t key = ((int64_t)m << 20) | occ;
+        for (auto &kv : extra) if (kv.first == key) return kv.second;
+        const int32_t u = add(m, occ);
+        extra.push_back({key, u});
+        return u;
+    };
+    for (int r = 0; r < n_rows; ++r) {
+        Resolved &rc = res[(size_t)(i + r)];
+        un.call_tiles += rc.tiles;
+        // the union is sorted once, below: a call's own list is needed in slot order only where it names a message
+        // twice (its occurrences are told apart by their starts)
+        int32_t self_occ = 0;
+        const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
+        uint32_t twice = 0;
+        for (const int2 *e = rc.sel.data(), *end = e + rc.sel.size(); e < end; ++e) {
+            const HostMsg &hm = msgs[e->x];
+            if (hm.len <= 0) continue;
+            self_occ += e->x == rc.self_msg;
+            const int32_t u = marks[e->x].epoch == epoch ? marks[e->x].value : lookup(e->x, 0);
+            uint32_t &vis = segs[u].vis[word];
+            twice |= vis & bit;
+            vis |= bit;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = e->y - hm.base_pos;
+        }
+        auto enter = [&](int32_t u, int32_t p) {
+            segs[u].vis[word] |= bit;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = p;
+        };
+        if (twice) {
+            for (size_t u = 0; u < un.segs.size(); ++u) {             // the row again, from nothing
+                segs[u].vis[word] &= ~bit;
+                pos[u * (size_t)n_rows + (size_t)r] = PC_SH_ABSENT;
+            }
+            sort_by_slot(c, rc);
+            int32_t prev = -1, occ = 0;
+            for (const int2 &e : rc.sel) {
+                occ = (e.x == prev) ? occ + 1 : 0;
+                prev = e.x;
+                if (msgs[e.x].len > 0) enter(lookup(e.x, occ), e.y - msgs[e.x].base_pos);
+            }
+        }
+        if (rc.self_msg >= 0 && rc.self_len > 0)      // the call's own tail: one row, one token from the end -> all of it visible
+            enter(lookup(rc.self_msg, self_occ), rc.self_start - msgs[rc.self_msg].base_pos);
+        if (un.segs.size() > segs_max) return false;
+    }
+    un.tiles = 0;
+    for (const Union::Seg &u : un.segs) un.tiles += (u.len + PC_TILE - 1) / PC_TILE;
+    return true;
+}
+
+static void order_union(Union &un)
+{
+    un.order.resize(un.segs.size());
+    for (size_t u = 0; u < un.segs.size(); ++u) un.order[u] = (int32_t)u;
+    const auto &usegs = un.segs;
+    std::sort(un.order.begin(), un.order.end(), [&](int32_t a, int32_t b) {
+        return usegs[(size_t)a].slot != usegs[(size_t)b].slot ? usegs[(size_t)a].slot < usegs[(size_t)b].slot
+                                                              : usegs[(size_t)a].occ < usegs[(size_t)b].occ; });
+}
+
+static bool plan_runs(pc_cache *c, Planned &P, Union &un, hipStream_t st, int32_t &rc);
+
+// rc != PC_OK: an error.  True: the whole batch goes by message (P.runs_*), and nothing else is to be planned
+static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, int g, SharedPlan &sp, hipStream_t st, int32_t &rc)
+{
+    std::vector<Resolved> &res = P.res;
     const int n_calls = (int)res.size();
     sp.in_shared.assign((size_t)n_calls, 0);
-    if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return;
+    if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
     const int rows_max = 32 * (8 / g);
-    struct USeg { int32_t occ, len; int64_t slot; uint32_t vis[8]; };
-    const HostMsg *msgs = c->msgs.data();
-    std::vector<USeg> usegs;                              // the union's messages as they turn up
-    std::vector<int32_t> pos;                             // [useg][row] rotation positions
-    std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> useg, for repeats within a call
-    std::vector<int32_t> order;
+    static thread_local Union un;                        // (at most half a million entries; kept: fresh pages for them cost more than filling them)
+    bool whole = false;                                  // un is that of the whole batch
+    if (c->decode_sharing == 0 && n_calls > 1 && n_calls <= 256 && c->decode_tiles_per_split == 0 && !c->host_only) {
+        whole = true;
+        size_t entries = 0;
+        for (const Resolved &r : res) { whole &= r.n_q == 1; entries += r.sel.size(); }
+        // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
+        // step, took 104 us and then 128)
+        whole = whole && (n_calls <= rows_max || entries <= 2048);
+        whole = whole && collect_union(c, res, 0, n_calls, ((size_t)1 << 19) / (size_t)n_calls, un);
+        if (whole && plan_runs(c, P, un, st, rc)) return true;
+        if (rc != PC_OK) return false;
+    }
     for (int i = 0; i < n_calls;) {
         if (res[i].n_q != 1) { ++i; continue; }
         int j = i;
@@ -217,95 +320,26 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
         for (int r = i; r < j; ++r) { sum_tiles += res[(size_t)r].tiles; longest = std::max<int64_t>(longest, res[(size_t)r].tiles); }
         if (c->decode_sharing != 2 && (double)sum_tiles < SHARE_MIN * (double)longest) { i = j; continue; }
         // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
-        const size_t usegs_max = ((size_t)1 << 19) / (size_t)n_rows;
-        usegs.clear(); pos.clear(); extra.clear();
-        const uint32_t epoch = new_marks(c);             // value: the message's place in usegs
-        int64_t call_tiles = 0;
-        auto add = [&](int32_t m, int32_t occ) {
-            const HostMsg &hm = c->msgs[(size_t)m];
-            usegs.push_back(USeg{occ, hm.len, hm.slot_start, {0, 0, 0, 0, 0, 0, 0, 0}});
-            pos.resize(pos.size() + (size_t)n_rows, PC_SH_ABSENT);
-            return (int32_t)usegs.size() - 1;
-        };
-        auto first_of = [&](int32_t m) -> int32_t {
-            pc_cache::Mark &mk = c->marks[(size_t)m];
-            if (mk.epoch != epoch) mk = pc_cache::Mark{epoch, add(m, 0)};
-            return mk.value;
-        };
-        auto lookup = [&](int32_t m, int32_t occ) -> int32_t {
-            if (occ == 0) return first_of(m);
-            const int64_t key = ((int64_t)m << 20) | occ;
-            for (auto &kv : extra) if (kv.first == key) return kv.second;
-            const int32_t u = add(m, occ);
-            extra.push_back({key, u});
-            return u;
-        };
-        auto enter = [&](int32_t u, int32_t r, int32_t p) {
-            usegs[(size_t)u].vis[r >> 5] |= 1u << (r & 31);
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = p;
-        };
-        for (int r = 0; r < n_rows && usegs.size() <= usegs_max; ++r) {
-            Resolved &rc = res[(size_t)(i + r)];
-            call_tiles += rc.tiles;
-            // the union is sorted once, below: a call's own list is needed in slot order only where it names a message
-            // twice (its occurrences are told apart by their starts)
-            int32_t self_occ = 0;
-            bool once = true;
-            const pc_cache::Mark *marks = c->marks.data();
-            const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
-            for (const int2 &e : rc.sel) {
-                const HostMsg &hm = msgs[e.x];
-                if (hm.len <= 0) continue;
-                self_occ += e.x == rc.self_msg;
-                const int32_t u = marks[e.x].epoch == epoch ? marks[e.x].value : first_of(e.x);
-                if (usegs.size() > usegs_max) break;
-                uint32_t &vis = usegs[(size_t)u].vis[word];
-                once &= (vis & bit) == 0;
-                vis |= bit;
-                pos[(size_t)u * (size_t)n_rows + (size_t)r] = e.y - hm.base_pos;
-            }
-            if (!once) {
-                for (size_t u = 0; u < usegs.size(); ++u) {               // the row again, from nothing
-                    usegs[u].vis[r >> 5] &= ~(1u << (r & 31));
-                    pos[u * (size_t)n_rows + (size_t)r] = PC_SH_ABSENT;
-                }
-                sort_by_slot(c, rc);
-                int32_t prev = -1, occ = 0;
-                for (const int2 &e : rc.sel) {
-                    occ = (e.x == prev) ? occ + 1 : 0;
-                    prev = e.x;
-                    if (c->msgs[(size_t)e.x].len > 0) enter(lookup(e.x, occ), r, e.y - c->msgs[(size_t)e.x].base_pos);
-                }
-            }
-            if (rc.self_msg >= 0 && rc.self_len > 0)      // the call's own tail: one row, one token from the end -> all of it visible
-                enter(lookup(rc.self_msg, self_occ), r, rc.self_start - c->msgs[(size_t)rc.self_msg].base_pos);
-        }
-        int64_t union_tiles = 0;
-        for (const USeg &u : usegs) union_tiles += (u.len + PC_TILE - 1) / PC_TILE;
-        const bool take = union_tiles > 0 && union_tiles < INT32_MAX / 2 && usegs.size() <= usegs_max &&
-                          (c->decode_sharing == 2 || (n_rows >= 2 && (double)call_tiles >= SHARE_MIN * (double)union_tiles));
+        const bool fits = (whole && n_rows == n_calls) || collect_union(c, res, i, n_rows, ((size_t)1 << 19) / (size_t)n_rows, un);
+        const bool take = fits && un.tiles > 0 && un.tiles < INT32_MAX / 2 &&
+                          (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles));
         if (take) {
-            // union in cache-slot order
-            order.resize(usegs.size());
-            for (size_t u = 0; u < usegs.size(); ++u) order[u] = (int32_t)u;
-            std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-                return usegs[(size_t)a].slot != usegs[(size_t)b].slot ? usegs[(size_t)a].slot < usegs[(size_t)b].slot
-                                                                      : usegs[(size_t)a].occ < usegs[(size_t)b].occ; });
+            order_union(un);
             PcShGroup gr{};
-            gr.seg_off = (int32_t)sp.segs.size(); gr.n_seg = (int32_t)usegs.size();
+            gr.seg_off = (int32_t)sp.segs.size(); gr.n_seg = (int32_t)un.segs.size();
             gr.row0 = q_off[(size_t)i]; gr.n_rows = n_rows; gr.rot_off = (int32_t)sp.pos.size();
             gr.n_splits = 1; gr.part_off = 0;
             int32_t tile_off = 0;
-            sp.segs.reserve(sp.segs.size() + usegs.size());
-            sp.pos.reserve(sp.pos.size() + pos.size());
-            for (int32_t k : order) {
-                const USeg &u = usegs[(size_t)k];
+            sp.segs.reserve(sp.segs.size() + un.segs.size());
+            sp.pos.reserve(sp.pos.size() + un.pos.size());
+            for (int32_t k : un.order) {
+                const Union::Seg &u = un.segs[(size_t)k];
                 PcShSeg sg{};
                 sg.slot_start = (int32_t)u.slot; sg.len = u.len; sg.tile_off = tile_off;
                 std::copy(u.vis, u.vis + 8, sg.vis);
                 tile_off += (u.len + PC_TILE - 1) / PC_TILE;
                 sp.segs.push_back(sg);
-                const int32_t *row = pos.data() + (size_t)k * (size_t)n_rows;
+                const int32_t *row = un.pos.data() + (size_t)k * (size_t)n_rows;
                 sp.pos.insert(sp.pos.end(), row, row + n_rows);
             }
             gr.n_tiles = tile_off;
@@ -314,6 +348,130 @@ static void plan_shared(pc_cache *c, std::vector<Resolved> &res, const std::vect
         }
         i = j;
     }
+    return false;
+}
+
+// A decode batch by message (pc_decode_runs_bf16_kernel), where that is the cheapest of its three ways.  us a step, each with launches and merge,
+// from 32 batches of 2 to 64 calls over 6 to 300 messages, at 4 and 8 heads a KV head; tiles (K and V of 32 keys, a KV head) are shared
+// out over the compute units:
+//   own walks     OWN_FIXED, TILE_NEW a tile of the union, TILE_STEP a further pass over a message that every call lists (they meet it in
+//                 step, in the L2), TILE_AGAIN one over any other
+//   by message    RUN_FIXED, RUN_PART a part of the row that has most, and TILE_NEW a tile of the union or TILE_PASS a pass of PC_RUN_ROWS rows (16 / g at most)
+//   shared walk   SHARED_FIXED and SHARED_TILE a tile of a workgroup
+// 64 calls over a system message and 8 of 512 others: 127 us by walks of their own, 111 by message; 8 over 100 of 300: 78 and 52; 16 over 20
+// of 60 and a system message: 40 shared, 30 by message; 8 over 30 of 60: 23 own, 28 by message.
+constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.4, TILE_STEP = 0.15, TILE_PASS = 0.33, OWN_FIXED = 5.0, RUN_FIXED = 20.5, RUN_PART = 0.045, SHARED_FIXED = 18.0, SHARED_TILE = 1.7;
+constexpr double RUN_START = 1.5;                        // a run's start and end, in tiles of its wave
+static bool plan_runs(pc_cache *c, Planned &P, Union &un, hipStream_t st, int32_t &rc)
+{
+    const int n_calls = un.n_rows, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads, per_run = std::min(PC_RUN_ROWS, 16 / c->g);
+    if (per_run < 2 || un.tiles == 0 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
+    auto rows_of = [&](const Union::Seg &u) { int k = 0; for (uint32_t v : u.vis) k += __builtin_popcount(v); return k; };
+    int64_t passes = 0, again = 0, in_step = 0, n_groups = 0, listed = 0;
+    for (const Union::Seg &u : un.segs) {
+        const int k = rows_of(u), t = (u.len + PC_TILE - 1) / PC_TILE, gr = (k + per_run - 1) / per_run;
+        passes += (int64_t)gr * t; n_groups += gr; listed += k;
+        (k == n_calls ? in_step : again) += (int64_t)(k - 1) * t;
+    }
+    const double per_cu = H_kv / 256.0;
+    const double own = OWN_FIXED + per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step);
+    const double by_message = RUN_FIXED + RUN_PART * (double)listed / n_calls + per_cu * std::max(TILE_PASS * (double)passes, TILE_NEW * (double)un.tiles);
+    const double shared = SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles;
+    if (by_message > 0.95 * ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles ? shared : own)) return false;
+
+    order_union(un);
+    // the least share of tiles, and of runs' starts and ends, with which so many waves take all of them
+    const double total = (double)passes + RUN_START * (double)n_groups;
+    const int most_waves = std::max(1, std::min(PC_RUN_WAVES, 2048 / H_kv));
+    auto take_of = [](double room, int left) { return std::min(left, std::max(1, (int)(room - RUN_START))); };
+    double share = std::max(6.0, total / most_waves + 0.5);
+    int n_waves = 0;
+    for (;; share *= 1.03) {
+        n_waves = 1;
+        double used = 0;
+        for (int32_t k : un.order) {
+            const Union::Seg &u = un.segs[(size_t)k];
+            const int T = (u.len + PC_TILE - 1) / PC_TILE;
+            for (int gr = (rows_of(u) + per_run - 1) / per_run; gr > 0; --gr)
+                for (int t = 0; t < T;) {
+                    if (used + RUN_START + 1 > share) { ++n_waves; used = 0; }         // (less than a start and a tile left: the next wave)
+                    const int take = take_of(share - used, T - t);
+                    used += RUN_START + take; t += take;
+                }
+        }
+        if (n_waves <= most_waves) break;
+    }
+    static thread_local std::vector<PcMsgRun> runs;
+    runs.clear();
+    std::vector<int32_t> parts((size_t)n_calls, 0);
+    int wave = 0;
+    double used = 0;
+    P.run_starts.first[0] = 0;
+    for (int32_t k : un.order) {
+        const Union::Seg &u = un.segs[(size_t)k];
+        const int32_t *pos = un.pos.data() + (size_t)k * (size_t)n_calls;
+        const int T = (u.len + PC_TILE - 1) / PC_TILE;
+        PcMsgRun run{};
+        run.msg = u.msg;
+        int n = 0;
+        auto emit = [&]() {
+            for (int t = 0; t < T;) {
+                if (used + RUN_START + 1 > share) { P.run_starts.first[++wave] = (uint16_t)runs.size(); used = 0; }
+                const int take = take_of(share - used, T - t);
+                run.tile0 = t; run.size = take | n << 28;
+                for (int i = 0; i < n; ++i) run.part[i] = parts[(size_t)run.row[i]]++;
+                runs.push_back(run);
+                used += RUN_START + take;
+                t += take;
+            }
+            n = 0;
+        };
+        for (int b = 0; b < (n_calls + 31) / 32; ++b)
+            for (uint32_t v = u.vis[b]; v; v &= v - 1) {
+                const int row = 32 * b + __builtin_ctz(v);
+                run.row[n] = row;
+                run.pos[n] = P.res[(size_t)row].q_pos[0] - (pos[row] + c->msgs[(size_t)u.msg].base_pos);
+                if (++n == per_run) emit();
+            }
+        if (n > 0) emit();
+    }
+    if (runs.size() >= 65535) return false;
+    P.run_starts.first[++wave] = (uint16_t)runs.size();
+    // a call's parts lie one after the other, in slot order
+    std::vector<int32_t> part0((size_t)n_calls);
+    int32_t part_rows = 0;
+    for (int i = 0; i < n_calls; ++i) { part0[(size_t)i] = part_rows; part_rows += parts[(size_t)i]; }
+    for (PcMsgRun &r : runs)
+        for (int i = 0; i < r.size >> 28; ++i) r.part[i] += part0[(size_t)r.row[i]];
+    const size_t off_merge = sizeof(PcMsgRun) * runs.size();
+    const size_t off_tok = align_up(off_merge + sizeof(PcMergeRow) * (size_t)n_calls, 16), bytes = off_tok + sizeof(PcTokenItem) * P.tok_items.size();
+    P.lay = PlanLayout{};
+    P.lay.part_ml = align_up(sizeof(float) * (size_t)part_rows * H_q * c->D, 256);
+    P.lay.calls = align_up(P.lay.part_ml + sizeof(float) * 4 * (size_t)part_rows * H_q, 256);    // the runs, then the rows to merge
+    P.lay.merge_rows = P.lay.calls + off_merge;
+    P.lay.rot_seg = align_up(P.lay.calls + bytes, 1024);
+    P.lay.total = P.lay.rot_seg + runs.size() * PC_RUN_ROWS * sizeof(float2) * 64;
+    P.n_runs = (int)runs.size();
+    if (bytes > HOST_READ_BYTES || P.lay.total > PC_STATIC_WS_BYTES || un.segs.size() * (size_t)n_calls > 32768) return false;
+    char *h;
+    const bool recorded = pc_recorded(st);
+    if (recorded) {
+        P.recorded.resize(align_up(bytes, 16));
+        h = P.recorded.data();
+    } else {
+        rc = pc_stage_acquire(c, bytes, &P.runs_slot);
+        if (rc != PC_OK) return false;
+        h = (char *)P.runs_slot->host;
+    }
+    std::memcpy(h, runs.data(), off_merge);
+    PcMergeRow *rows = (PcMergeRow *)(h + off_merge);
+    for (int i = 0; i < n_calls; ++i) rows[i] = PcMergeRow{i, 2 * part0[(size_t)i], parts[(size_t)i] | PC_MERGE_WIDE, 1};
+    P.runs_bytes = bytes;
+    P.n_merge_rows = n_calls; P.n_merge_few = 0;
+    if (!P.tok_items.empty()) std::memcpy(h + off_tok, P.tok_items.data(), sizeof(PcTokenItem) * P.tok_items.size());
+    P.lay.tok_items = off_tok;
+    P.runs = PcRuns{c->table_dev, nullptr, nullptr, n_waves};
+    return true;
 }
 
 // Tokens of a call's parents; tiles of its new message (its last extent)
@@ -729,6 +887,17 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
     return true;
 }
 
+// the tokens of a decode step, whose items lie at `items`, for a launch that appends them
+static PcTokenWork token_work(const pc_cache *c, const Planned &P, const PcTokenItem *items)
+{
+    PcTokenWork tok;
+    if (P.tok_items.empty()) return tok;
+    tok.items = items; tok.n = (int)P.tok_items.size();
+    tok.k = P.tok_k; tok.v = P.tok_v; tok.k_store = c->k_store; tok.v_store = c->v_store;
+    tok.slots = c->slots; tok.n_kv_heads = c->cfg.n_kv_heads; tok.D = c->D; tok.dtype = c->cfg.dtype;
+    return tok;
+}
+
 int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bool want_items,
                               hipStream_t st, Planned &P)
 {
@@ -749,15 +918,36 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     int64_t kg_tiles = 0;
     int64_t part_rows = 0, total_tiles = 0;
     int q_off = 0, seg_off = 0;
-    // groups of one-row calls that share enough of their messages take the shared walk
-    SharedPlan sp;
+    // groups of one-row calls that share enough of their messages take the shared walk, or the whole batch goes by message
+    int32_t rc = PC_OK;
+    static thread_local SharedPlan kept_plan;
+    SharedPlan &sp = kept_plan;
     sp.in_shared.assign((size_t)n_calls, 0);
+    sp.groups.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear();
     if (want_items && bf16) {
         std::vector<int> q_offs((size_t)n_calls);
         for (int i = 0, o = 0; i < n_calls; ++i) { q_offs[(size_t)i] = o; o += P.res[(size_t)i].n_q; }
-        plan_shared(c, P.res, q_offs, g, sp);
+        if (plan_shared(c, P, q_offs, g, sp, st, rc)) {
+            if (!P.fixed_ws) {
+                rc = pc_ensure_ws(c, P.lay.total, st);
+                if (rc != PC_OK) return rc;
+            }                                            // (it fits every fixed workspace, see plan_runs)
+            P.ws = P.fixed_ws ? P.fixed_ws : c->ws;
+            P.runs.runs = (const PcMsgRun *)((char *)P.ws + P.lay.calls);
+            P.runs.rot = (const float2 *)((char *)P.ws + P.lay.rot_seg);
+            ProfScope ps(c, 1, st);
+            char *lists = (char *)P.ws + P.lay.calls;
+            if (!P.runs_slot) pc_launch_store_args(P.recorded.data(), P.recorded.size(), lists, st);
+            char *from = P.runs_slot ? (char *)P.runs_slot->host : lists;
+            const PcTokenWork tok = token_work(c, P, (const PcTokenItem *)(from + P.lay.tok_items));
+            pc_launch_runs_prepare(from, lists, P.runs_bytes, P.n_runs, c->scale * 1.4426950408889634f, tok, c->inv_freq_dev, c->table_dev,
+                                   (float2 *)((char *)P.ws + P.lay.rot_seg), st);
+            PC_HIP(c, hipGetLastError());
+            P.tok_done = !P.tok_items.empty();
+            return PC_OK;
+        }
+        if (rc != PC_OK) return rc;
     }
-    int32_t rc = PC_OK;
     if (want_items && bf16 && !c->host_only && sp.groups.empty() && plan_one(c, P, st, rc)) {
         if (!P.fixed_ws) {
             rc = pc_ensure_ws(c, P.lay.total, st);
@@ -1086,12 +1276,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     {
         ProfScope ps(c, 1, st);
         char *w = (char *)P.ws, *from = in_place ? h : w;
-        PcTokenWork tok;
-        if (!P.tok_items.empty()) {
-            tok.items = (const PcTokenItem *)(from + P.lay.tok_items); tok.n = (int)P.tok_items.size();
-            tok.k = P.tok_k; tok.v = P.tok_v; tok.k_store = c->k_store; tok.v_store = c->v_store;
-            tok.slots = c->slots; tok.n_kv_heads = c->cfg.n_kv_heads; tok.D = c->D; tok.dtype = c->cfg.dtype;
-        }
+        const PcTokenWork tok = token_work(c, P, (const PcTokenItem *)(from + P.lay.tok_items));
         auto *calls_at = (const PcCallDesc *)(from + P.lay.calls);
         auto *sel_at = (const int2 *)(from + P.lay.sel);
         auto *q_pos_at = (const int32_t *)(from + P.lay.q_pos);

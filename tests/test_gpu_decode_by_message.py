@@ -1,0 +1,173 @@
+"""Decode batches that go by message (every wave streams runs of tiles of one message for up to four of the calls that list it), chosen in
+mode 0 of pc_set_decode_sharing where that is the cheapest way: against every call's own walk (mode 1) over shapes and forms at which a run or
+its parts can go wrong -- more rows of a message than a run holds and fewer, ragged last tiles, messages of one token, runs cut between
+waves, repeats within a call, stored bases, freed spans, calls without a message of their own, positions given -- and, for one batch,
+against the oracle.  A step's tokens reach the stores bit for bit."""
+import numpy as np
+import pytest
+
+import pc_inputs as gen
+from pc_inputs import Call
+
+pytestmark = pytest.mark.gpu
+D = 128
+
+
+class Batch:
+    def __init__(self, h_q, h_kv, lens, own, seed, extra=0):
+        import torch
+        from paper_2512_23049_amd import binding
+        self.t, self.h_q, self.h_kv = torch, h_q, h_kv
+        cap = sum((n + 31) // 32 * 32 for n in lens + [o + 40 for o in own]) + extra
+        self.arena = torch.zeros(2 * cap * h_kv * D, dtype=torch.bfloat16, device="cuda:0")
+        self.cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, 10000.0, cap, 4 * (len(lens) + len(own)) + 64, arena=self.arena.data_ptr(),
+                                   arena_bytes=2 * self.arena.numel())
+        self.g = torch.Generator(device="cuda:0").manual_seed(seed)
+        self.keep = []
+        self.ids = [self.append(n) for n in lens]
+        self.own = [self.append(n, n + 40) for n in own]
+
+    def normal(self, *shape):
+        self.keep.append(self.t.randn(shape, generator=self.g, device="cuda:0").to(self.t.bfloat16))
+        return self.keep[-1]
+
+    def append(self, n, reserve=0):
+        return self.cache.append_message(self.normal(n, self.h_kv, D).data_ptr(), self.normal(n, self.h_kv, D).data_ptr(), n, reserve)
+
+    def attend(self, calls, q, mode=0, step=None, static=False):
+        """(out, lse, by message): kernel class 1 runs in front of class 3 where a batch goes by message, class 3 alone on calls' own walks"""
+        out, lse = self.t.full_like(q, 7.0), self.t.full(q.shape[:2], 7.0, device="cuda:0")
+        self.cache.set_decode_sharing(mode)
+        if not static:
+            self.cache.profile_enable(True)
+            self.cache.profile_read(True)
+        if step:
+            self.cache.decode_step(step[0], step[1].data_ptr(), step[2].data_ptr(), calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        elif static:
+            self.cache.attend_static(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        else:
+            self.cache.attend(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        self.t.cuda.synchronize()
+        went = None
+        if not static:
+            ran = self.cache.profile_read(True)
+            went = (ran["plan"][1], ran["decode"][1], ran["merge"][1]) == (1, 1, 1)
+            self.cache.profile_enable(False)
+        self.cache.set_decode_sharing(0)
+        return out, lse, went
+
+
+def close(a, b):
+    (one, one_lse, _), (two, two_lse, _) = a, b
+    seen = two_lse.isfinite()
+    assert (one_lse.isfinite() == seen).all() and (one_lse[seen] - two_lse[seen]).abs().max().item() <= 2e-2
+    assert (one.float() - two.float()).abs().max().item() <= 2e-2       # (outputs below 4, rounded to bf16 on both sides)
+
+
+def fields(c):
+    return [c.sel, c.self_msg, c.self_start, c.n_q, c.q_pos]
+
+
+def spread(r, n_calls, pool, n_sel, own, far=3000):
+    return [Call([(int(m), int(r.integers(-50, far))) for m in r.permutation(pool)[:n_sel]], m, far + 500, 1, None) for m in own]
+
+
+# g = 1, 2, 4, 8; more calls than a group of the shared walk holds (8 heads: 32); a message every call lists (several runs of it) beside messages few list
+@pytest.mark.parametrize("h_q,h_kv,n_calls,n_sel,pool", [(8, 8, 12, 60, 160), (16, 8, 12, 60, 160), (32, 8, 9, 90, 260), (64, 8, 20, 30, 100), (64, 8, 40, 13, 120), (32, 8, 66, 9, 300),
+                                                          (8, 2, 14, 220, 700)])
+def test_against_own_walks(h_q, h_kv, n_calls, n_sel, pool):
+    r = np.random.default_rng(n_calls)
+    lens = [900] + [int(x) for x in r.integers(1, 400, pool)] + [1, 32, 33]
+    b = Batch(h_q, h_kv, lens, [int(x) for x in r.integers(1, 70, n_calls)], n_calls)
+    for m in b.ids[3:20:4]:
+        b.cache.reposition(m, int(r.integers(-900, 900)))
+    for reused in (False, True):
+        if reused:                                       # over freed and re-used spans
+            for m in b.ids[30:60:3]:
+                b.cache.message_free(m)
+            b.ids = [m for m in b.ids if m not in b.ids[30:60:3]] + [b.append(int(n)) for n in r.integers(1, 30, 10)]
+        calls = [Call([(b.ids[m], s) for m, s in f[0]], *f[1:]) for f in map(fields, spread(r, n_calls, len(b.ids), n_sel, b.own))]
+        for c in calls:
+            c.sel.insert(int(r.integers(0, n_sel)), (b.ids[0], 17))
+        calls[0].sel.append((b.ids[5], 8000))            # a message twice in a call
+        calls[0].sel.append((b.ids[5], 9000))
+        calls[1] = Call(calls[1].sel, -1, 70, 1, [4000])                             # nobody's message
+        calls[2] = Call([], -1, 0, 1, None)              # nothing to see
+        calls[3] = Call([], calls[3].self_msg, -3, 1, None)
+        q = b.normal(n_calls, h_q, D)
+        got = b.attend(calls, q)
+        assert got[2], "the batch was to go by message"
+        close(got, b.attend(calls, q, mode=1))
+        again = b.attend(calls, q)
+        assert (again[0] == got[0]).all() and (again[1] == got[1]).all()
+    b.cache.close()
+
+
+def test_steps_and_static():
+    """Three steps of tails that cross a tile: results, stores bit for bit those of the two separate calls, pc_attend_static's bits."""
+    r = np.random.default_rng(5)
+    lens = [int(x) for x in r.integers(30, 400, 200)]
+    own = [29 + i % 5 for i in range(10)]
+    stores = []
+    for fused in (True, False):
+        r2 = np.random.default_rng(6)
+        b = Batch(32, 8, lens, own, 3)
+        calls = spread(r2, 10, 200, 70, b.own)
+        for s in range(3):
+            tk, tv, q = b.normal(10, 8, D), b.normal(10, 8, D), b.normal(10, 32, D)
+            if fused:
+                got = b.attend(calls, q, step=(b.own, tk, tv))
+                assert got[2]
+                same = b.attend(calls, q, static=True)
+                assert (same[0] == got[0]).all() and (same[1] == got[1]).all()
+                close(got, b.attend(calls, q, mode=1))
+            else:
+                b.cache.append_tokens_batch(b.own, tk.data_ptr(), tv.data_ptr())
+                b.attend(calls, q)
+        stores.append(b.arena.view(b.t.int16).cpu())
+        b.cache.close()
+    assert b.t.equal(stores[0], stores[1])
+
+
+def test_against_the_oracle_and_replays():
+    import torch
+    from oracle import choreo_oracle as orc
+    from paper_2512_23049_amd import binding, harness as hip
+    r = np.random.default_rng(9)
+    rnd = lambda *s: gen.round_to_bf16(r.standard_normal(s).astype(np.float32))      # noqa: E731
+    h_q, h_kv, n_calls = 32, 8, 8
+    lens = [int(x) for x in r.integers(150, 300, 110)] + [3 + i for i in range(n_calls)]
+    ks, vs = [rnd(n, h_kv, D) for n in lens], [rnd(n, h_kv, D) for n in lens]
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, 10000.0, sum((n + 31) // 32 * 32 for n in lens), len(lens))
+    for k, v in zip(ks, vs):
+        kd, vd = hip.to_device(k, "bf16"), hip.to_device(v, "bf16")
+        cache.append_message(kd.data_ptr(), vd.data_ptr(), len(k))
+        torch.cuda.synchronize()
+    calls = spread(r, n_calls, 110, 60, list(range(110, 110 + n_calls)))
+    q = rnd(n_calls, h_q, D)
+    qd = hip.to_device(q, "bf16")
+    out, lse = torch.empty_like(qd), torch.empty((n_calls, h_q), device="cuda:0")
+    cache.attend(calls, qd.data_ptr(), out.data_ptr(), lse.data_ptr())
+    torch.cuda.synchronize()
+    for i in (0, 7):
+        o, l = orc.attend_call(ks, vs, calls[i].sel, calls[i].self_msg, calls[i].self_start, 1, None, q[i:i + 1], 10000.0, rows=[0])
+        d = np.abs(out[i:i + 1].float().cpu().numpy() - o)
+        assert d.max() <= 2e-2 and d.mean() <= 1e-3 and np.abs(lse[i:i + 1].cpu().numpy() - l).max() <= 2e-2
+    # recorded into a graph: its lists are the graph's own
+    stream, got = torch.cuda.Stream(), torch.empty_like(out)
+    with torch.cuda.stream(stream):
+        cache.attend_static(calls, qd.data_ptr(), got.data_ptr(), 0, stream.cuda_stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        cache.attend_static(calls, qd.data_ptr(), got.data_ptr(), 0, stream.cuda_stream)
+    for _ in range(3):
+        x = hip.to_device(rnd(n_calls, h_q, D), "bf16")
+        cache.attend(calls, x.data_ptr(), out.data_ptr())
+        torch.cuda.synchronize()
+        qd.copy_(x)
+        got.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), got.view(torch.int16))
+    cache.close()
