@@ -188,9 +188,19 @@ struct SharedPlan {
     std::vector<int32_t> pos;                    // rotation positions, PC_SH_ABSENT where a row does not list the message
 };
 
-// Calls that together list n times the tokens of the union gain from the shared walk once n
-// exceeds what a union tile costs there (a workgroup's pass over it for all rows: 8.7 ns per tile
-// and KV head with the chip full) relative to a tile streamed by one call (1.5 to 1.7 ns).
+// The ways of a batch of one-row calls, in us a step with launches and merge.  Tiles (K and V of 32 keys, a KV head) are shared out over the
+// compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 4 and 8 heads a KV head:
+//   own walks     OWN_FIXED, with lists in pinned memory OWN_PINNED; TILE_NEW a tile of the union, TILE_STEP a further pass over a message that
+//                 every call lists (they meet it in step, in the L2), TILE_AGAIN one over any other
+//   by message    RUN_FIXED, RUN_PART a part of the row that has most, and TILE_NEW a tile of the union or TILE_PASS a pass of PC_RUN_ROWS rows (16 / g at most)
+//   shared walk   SHARED_FIXED and SHARED_TILE a tile of the groups' unions
+// 64 calls over a system message and 8 of 512 others: 127 us by walks of their own, 111 by message; 8 over 100 of 300: 78 and 52; 16 over 20
+// of 60 and a system message: 40 shared, 30 by message; 44 over 21 of 23 short ones: 44 shared, 30 own; 6 over 250: 63 own, 54 shared.
+// In a batch with longer calls, whose launches are there anyway, a group takes the shared walk if its calls list SHARE_MIN times the
+// tokens of the union: a union tile costs a workgroup 8.7 ns with the chip full, a tile streamed by one call 1.5 to 1.7.
+constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS = 0.33, OWN_FIXED = 8.0, OWN_PINNED = 14.0, RUN_FIXED = 20.5, RUN_PART = 0.045,
+                 SHARED_FIXED = 30.0, SHARED_TILE = 1.1;
+constexpr double RUN_START = 1.5;                        // a run's start and end, in passes
 constexpr double SHARE_MIN = 6.0;
 // rows with more splits than this are merged by four lanes per 8 dimensions
 constexpr int MERGE_MANY_SPLITS = 8;
@@ -287,7 +297,29 @@ static void order_union(Union &un)
                                                               : usegs[(size_t)a].occ < usegs[(size_t)b].occ; });
 }
 
-static bool plan_runs(pc_cache *c, Planned &P, Union &un, hipStream_t st, int32_t &rc);
+static int rows_of(const Union::Seg &u) { int k = 0; for (uint32_t v : u.vis) k += __builtin_popcount(v); return k; }
+
+// what a batch's own walks and its runs by message cost
+struct DecodeCost { double own, by_message; int64_t passes, n_groups; };
+static DecodeCost decode_cost(const pc_cache *c, const Union &un)
+{
+    const int n_calls = un.n_rows, per_run = std::max(1, std::min(PC_RUN_ROWS, 16 / c->g));
+    const double per_cu = c->cfg.n_kv_heads / 256.0;
+    int64_t again = 0, in_step = 0, listed = 0;
+    DecodeCost k{0, 0, 0, 0};
+    for (const Union::Seg &u : un.segs) {
+        const int n = rows_of(u), t = (u.len + PC_TILE - 1) / PC_TILE, gr = (n + per_run - 1) / per_run;
+        k.passes += (int64_t)gr * t; k.n_groups += gr; listed += n;
+        (n == n_calls ? in_step : again) += (int64_t)(n - 1) * t;
+    }
+    const bool pinned = (sizeof(PcOneCall) + sizeof(PcOneItem) + 4) * (size_t)n_calls + sizeof(int2) * (size_t)listed > PC_ARG_BYTES;
+    k.own = (pinned ? OWN_PINNED : OWN_FIXED) + per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step);
+    k.by_message = RUN_FIXED + RUN_PART * (double)listed / n_calls + per_cu * std::max(TILE_PASS * ((double)k.passes + RUN_START * (double)k.n_groups), TILE_NEW * (double)un.tiles);
+    if (per_run < 2) k.by_message = 1e30;
+    return k;
+}
+
+static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost, hipStream_t st, int32_t &rc);
 
 // rc != PC_OK: an error.  True: the whole batch goes by message (P.runs_*), and nothing else is to be planned
 static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, int g, SharedPlan &sp, hipStream_t st, int32_t &rc)
@@ -297,32 +329,51 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     sp.in_shared.assign((size_t)n_calls, 0);
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
     const int rows_max = 32 * (8 / g);
+    const double per_cu = c->cfg.n_kv_heads / 256.0;
     static thread_local Union un;                        // (at most half a million entries; kept: fresh pages for them cost more than filling them)
-    bool whole = false;                                  // un is that of the whole batch
-    if (c->decode_sharing == 0 && n_calls > 1 && n_calls <= 256 && c->decode_tiles_per_split == 0 && !c->host_only) {
-        whole = true;
-        size_t entries = 0;
-        for (const Resolved &r : res) { whole &= r.n_q == 1; entries += r.sel.size(); }
-        // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
-        // step, took 104 us and then 128)
-        whole = whole && (n_calls <= rows_max || entries <= 2048);
-        whole = whole && collect_union(c, res, 0, n_calls, ((size_t)1 << 19) / (size_t)n_calls, un);
-        if (whole && plan_runs(c, P, un, st, rc)) return true;
+    // a batch of one-row calls alone goes the cheapest way
+    bool alone = c->decode_sharing == 0 && n_calls > 1 && c->decode_tiles_per_split == 0;
+    size_t entries = 0;
+    int64_t all_tiles = 0;
+    for (const Resolved &r : res) { alone = alone && r.n_q == 1; entries += r.sel.size(); all_tiles += r.tiles; }
+    // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
+    if (alone && OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return false;
+    // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
+    // step, took 104 us and then 128)
+    const bool whole = alone && n_calls <= 256 && (n_calls <= rows_max || entries <= 2048) && collect_union(c, res, 0, n_calls, ((size_t)1 << 19) / (size_t)n_calls, un);
+    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles;
+    if (whole) {
+        const DecodeCost cost = decode_cost(c, un);
+        const double shared = SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)((n_calls + rows_max - 1) / rows_max);
+        own = cost.own;
+        if (!c->host_only && cost.by_message < 0.95 * std::min(own, shared) && plan_runs(c, P, un, cost, st, rc)) return true;
         if (rc != PC_OK) return false;
+        if (own < SHARED_FIXED) return false;
     }
+    double shared = SHARED_FIXED;                        // with what does not take the walk beside it
     for (int i = 0; i < n_calls;) {
         if (res[i].n_q != 1) { ++i; continue; }
         int j = i;
-        while (j < n_calls && res[j].n_q == 1 && j - i < rows_max) ++j;
+        while (j < n_calls && res[j].n_q == 1 && (alone || j - i < rows_max)) ++j;
+        if (j - i > rows_max) {                          // groups of a size: two calls behind a full group would have walks, and launches, of their own
+            const int n_groups = (n_calls - i + rows_max - 1) / rows_max;
+            j = i + (n_calls - i + n_groups - 1) / n_groups;
+        }
         const int n_rows = j - i;
         // (the union holds each call's list: calls that list less than SHARE_MIN times the longest list cannot take this walk)
         int64_t sum_tiles = 0, longest = 0;
         for (int r = i; r < j; ++r) { sum_tiles += res[(size_t)r].tiles; longest = std::max<int64_t>(longest, res[(size_t)r].tiles); }
-        if (c->decode_sharing != 2 && (double)sum_tiles < SHARE_MIN * (double)longest) { i = j; continue; }
+        if (c->decode_sharing != 2 && !alone && (double)sum_tiles < SHARE_MIN * (double)longest) { i = j; continue; }
         // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
         const bool fits = (whole && n_rows == n_calls) || collect_union(c, res, i, n_rows, ((size_t)1 << 19) / (size_t)n_rows, un);
-        const bool take = fits && un.tiles > 0 && un.tiles < INT32_MAX / 2 &&
-                          (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles));
+        bool take = fits && un.tiles > 0 && un.tiles < INT32_MAX / 2;
+        if (alone) shared += take ? SHARED_TILE * per_cu * (double)un.tiles : OWN_FIXED + per_cu * TILE_AGAIN * (double)sum_tiles;
+        else take = take && (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles));
+        if (alone && own < shared) {                     // the batch's calls walk on their own after all
+            sp.in_shared.assign((size_t)n_calls, 0);
+            sp.groups.clear(); sp.segs.clear(); sp.pos.clear();
+            return false;
+        }
         if (take) {
             order_union(un);
             PcShGroup gr{};
@@ -351,37 +402,14 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     return false;
 }
 
-// A decode batch by message (pc_decode_runs_bf16_kernel), where that is the cheapest of its three ways.  us a step, each with launches and merge,
-// from 32 batches of 2 to 64 calls over 6 to 300 messages, at 4 and 8 heads a KV head; tiles (K and V of 32 keys, a KV head) are shared
-// out over the compute units:
-//   own walks     OWN_FIXED, TILE_NEW a tile of the union, TILE_STEP a further pass over a message that every call lists (they meet it in
-//                 step, in the L2), TILE_AGAIN one over any other
-//   by message    RUN_FIXED, RUN_PART a part of the row that has most, and TILE_NEW a tile of the union or TILE_PASS a pass of PC_RUN_ROWS rows (16 / g at most)
-//   shared walk   SHARED_FIXED and SHARED_TILE a tile of a workgroup
-// 64 calls over a system message and 8 of 512 others: 127 us by walks of their own, 111 by message; 8 over 100 of 300: 78 and 52; 16 over 20
-// of 60 and a system message: 40 shared, 30 by message; 8 over 30 of 60: 23 own, 28 by message.
-constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.4, TILE_STEP = 0.15, TILE_PASS = 0.33, OWN_FIXED = 5.0, RUN_FIXED = 20.5, RUN_PART = 0.045, SHARED_FIXED = 18.0, SHARED_TILE = 1.7;
-constexpr double RUN_START = 1.5;                        // a run's start and end, in tiles of its wave
-static bool plan_runs(pc_cache *c, Planned &P, Union &un, hipStream_t st, int32_t &rc)
+// A decode batch by message (pc_decode_runs_bf16_kernel), if its lists and parts fit what every caller has.
+static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost, hipStream_t st, int32_t &rc)
 {
     const int n_calls = un.n_rows, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads, per_run = std::min(PC_RUN_ROWS, 16 / c->g);
     if (per_run < 2 || un.tiles == 0 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
-    auto rows_of = [&](const Union::Seg &u) { int k = 0; for (uint32_t v : u.vis) k += __builtin_popcount(v); return k; };
-    int64_t passes = 0, again = 0, in_step = 0, n_groups = 0, listed = 0;
-    for (const Union::Seg &u : un.segs) {
-        const int k = rows_of(u), t = (u.len + PC_TILE - 1) / PC_TILE, gr = (k + per_run - 1) / per_run;
-        passes += (int64_t)gr * t; n_groups += gr; listed += k;
-        (k == n_calls ? in_step : again) += (int64_t)(k - 1) * t;
-    }
-    const double per_cu = H_kv / 256.0;
-    const double own = OWN_FIXED + per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step);
-    const double by_message = RUN_FIXED + RUN_PART * (double)listed / n_calls + per_cu * std::max(TILE_PASS * (double)passes, TILE_NEW * (double)un.tiles);
-    const double shared = SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles;
-    if (by_message > 0.95 * ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles ? shared : own)) return false;
-
     order_union(un);
     // the least share of tiles, and of runs' starts and ends, with which so many waves take all of them
-    const double total = (double)passes + RUN_START * (double)n_groups;
+    const double total = (double)cost.passes + RUN_START * (double)cost.n_groups;
     const int most_waves = std::max(1, std::min(PC_RUN_WAVES, 2048 / H_kv));
     auto take_of = [](double room, int left) { return std::min(left, std::max(1, (int)(room - RUN_START))); };
     double share = std::max(6.0, total / most_waves + 0.5);
