@@ -287,10 +287,11 @@ int32_t pc_grad_keys_finalize(pc_cache *c, float *d_k, void *stream)
         if (m.live && m.len > 0) live.push_back(PcMsgEntry{(int32_t)m.slot_start, m.len, m.base_pos, 0});
     if (live.empty()) return PC_OK;
     hipStream_t st = (hipStream_t)stream;
-    const int32_t rc = pc_stage_items(c, live.data(), sizeof(PcMsgEntry) * live.size(), st);
+    const bool in_args = sizeof(PcMsgEntry) * live.size() <= PC_ARG_BYTES;
+    const int32_t rc = in_args ? PC_OK : pc_stage_items(c, live.data(), sizeof(PcMsgEntry) * live.size(), st);
     if (rc != PC_OK) return rc;
     ProfScope ps(c, 5, st);
-    pc_launch_grad_keys_finalize((const PcMsgEntry *)c->tok_dev, (int)live.size(), c->cfg.n_kv_heads, c->D, c->inv_freq_dev, d_k, st);
+    pc_launch_grad_keys_finalize((const PcMsgEntry *)c->tok_dev, in_args ? live.data() : nullptr, (int)live.size(), c->cfg.n_kv_heads, c->D, c->inv_freq_dev, d_k, st);
     PC_HIP(c, hipGetLastError());
     return PC_OK;
 }

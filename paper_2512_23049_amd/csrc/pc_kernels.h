@@ -82,7 +82,8 @@ void pc_launch_attend_bwd_f32(const PcLaunch &L, int n_items, const PcBwdKeyItem
 // the same for bf16 caches on the matrix cores: the row blocks [B.rb0, B.rb0 + B.n_rb), their row-major work items L.items
 // and key-major work items B.key_items
 void pc_launch_attend_bwd_bf16(const PcLaunch &L, const PcBwd &B, int n_items, int n_key_items, hipStream_t st);
-void pc_launch_grad_keys_finalize(const PcMsgEntry *msgs, int n_msgs, int n_kv_heads, int D, const double *inv_freq,
+// (host_msgs: the same list in host memory, or null; short lists are passed in the kernel's arguments and `msgs` is not read)
+void pc_launch_grad_keys_finalize(const PcMsgEntry *msgs, const PcMsgEntry *host_msgs, int n_msgs, int n_kv_heads, int D, const double *inv_freq,
                                   float *d_k, hipStream_t st);
 
 // keys (turned to the positions their call gives them) and values of the listed calls, token after token, into

@@ -22,6 +22,9 @@
 // 1.8e-7 to 3.9e-7 over 67 others since its sums are centred and a tile's product is added to them.
 #include "pc_pieces.h"
 
+#include <cstring>
+#include <type_traits>
+
 #define MFMA_F32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0)
 
 namespace {
@@ -903,10 +906,16 @@ void pc_launch_attend_bwd_f32(const PcLaunch &L, int n_items, const PcBwdKeyItem
 // respect to k_t is R(base + t)^T of it (Sec. 2.4 "Position Updates", transposed).  blockIdx.y names the message; a thread
 // takes one rotation pair of a token and turns it for every KV head: the fp64 sincos is what the kernel spends its time on
 // (one per head and pair, as before, took 55 us for 5500 tokens x 8 heads; now 12).
-__global__ __launch_bounds__(256) void pc_grad_keys_finalize_kernel(const PcMsgEntry *__restrict__ msgs, int n_kv_heads, int D,
-                                                                    const double *__restrict__ inv_freq, float *__restrict__ d_k)
+// List: a device pointer, or the messages themselves as the kernel's first arguments (the copy of 12 of them and its event took 6 us of a step of 90).
+template <typename List>
+__global__ __launch_bounds__(256) void pc_grad_keys_finalize_kernel(const List msgs, int n_kv_heads, int D, const double *__restrict__ inv_freq, float *__restrict__ d_k)
 {
-    const PcMsgEntry m = msgs[blockIdx.y];
+    PcMsgEntry m;
+    if constexpr (std::is_same<List, PcArgBlob>::value) {
+        static_assert(sizeof(PcMsgEntry) == 16, "");
+        const auto *p = (const __attribute__((address_space(4))) int32_t *)__builtin_amdgcn_kernarg_segment_ptr() + 4 * blockIdx.y;
+        m.slot_start = p[0]; m.len = p[1]; m.base_pos = p[2];
+    } else m = msgs[blockIdx.y];
     const int half = D / 2;
     const int64_t n = (int64_t)m.len * half;
     for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * 256) {
@@ -924,12 +933,18 @@ __global__ __launch_bounds__(256) void pc_grad_keys_finalize_kernel(const PcMsgE
     }
 }
 
-void pc_launch_grad_keys_finalize(const PcMsgEntry *msgs, int n_msgs, int n_kv_heads, int D, const double *inv_freq,
+void pc_launch_grad_keys_finalize(const PcMsgEntry *msgs, const PcMsgEntry *host_msgs, int n_msgs, int n_kv_heads, int D, const double *inv_freq,
                                   float *d_k, hipStream_t st)
 {
+    if (host_msgs) {                                     // (the caller checked that they fit)
+        PcArgBlob blob;
+        std::memcpy(blob.w, host_msgs, sizeof(PcMsgEntry) * (size_t)n_msgs);
+        pc_grad_keys_finalize_kernel<PcArgBlob><<<dim3(64, (unsigned)n_msgs), 256, 0, st>>>(blob, n_kv_heads, D, inv_freq, d_k);
+        return;
+    }
     for (int first = 0; first < n_msgs; first += 65535) {              // grid.y is limited to 65535
         const int n = n_msgs - first < 65535 ? n_msgs - first : 65535;
         dim3 grid(64, (unsigned)n);                      // 256 tokens of 64 pairs a step
-        pc_grad_keys_finalize_kernel<<<grid, 256, 0, st>>>(msgs + first, n_kv_heads, D, inv_freq, d_k);
+        pc_grad_keys_finalize_kernel<const PcMsgEntry *><<<grid, 256, 0, st>>>(msgs + first, n_kv_heads, D, inv_freq, d_k);
     }
 }
