@@ -69,7 +69,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         }
         {
             ProfScope ps(c, 4, st);
-            pc_launch_merge(c->cfg.dtype, (const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, 4, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
+            pc_launch_merge(c->cfg.dtype, (const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, 4, true, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
             PC_HIP(c, hipGetLastError());
         }
         if (P.runs_slot) {                               // the ring slot is free again once the launches are done
@@ -82,7 +82,8 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         {
             ProfScope ps(c, 5, st);
             L.items = (const PcItem *)(w + P.lay.items_pre);
-            pc_launch_attend_f32(L, P.n_pre, c->D, st);
+            if (P.self.n16 > 0) pc_launch_attend_f32_self(P.one_blob, L, P.self, P.n_pre, c->D, st);
+            else pc_launch_attend_f32(L, P.n_pre, c->D, st);
             PC_HIP(c, hipGetLastError());
         }
         if (P.n_merge_rows > 0) {
@@ -144,8 +145,8 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     if (P.n_merge_rows > 0) {
         ProfScope ps(c, 4, st);
         const PcMergeRow *rows = (const PcMergeRow *)(w + P.lay.merge_rows);
-        pc_launch_merge(c->cfg.dtype, rows, P.n_merge_few, 1, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
-        pc_launch_merge(c->cfg.dtype, rows + P.n_merge_few, P.n_merge_rows - P.n_merge_few, 4, L.part_o, L.part_ml, out, lse,
+        pc_launch_merge(c->cfg.dtype, rows, P.n_merge_few, 1, false, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
+        pc_launch_merge(c->cfg.dtype, rows + P.n_merge_few, P.n_merge_rows - P.n_merge_few, 4, P.n_sh_items > 0, L.part_o, L.part_ml, out, lse,
                         c->cfg.n_q_heads, c->D, st);
         PC_HIP(c, hipGetLastError());
     }

@@ -167,6 +167,8 @@ struct Planned {
     std::vector<char> recorded;                          // staged lists of a call that is recorded into a graph (see pc_recorded)
     // A decode batch by message (runs_bytes > 0): its lists are staged, nothing was launched for it yet
     size_t runs_bytes = 0; int n_runs = 0; PcRuns runs{}; PcRunStarts run_starts; StageSlot *runs_slot = nullptr;
+    // A batch whose attention launch plans for itself (self.n16 > 0; its staged block: one_blob): the plan builder was not launched
+    PcSelf self{}; size_t self_at = 0;
     struct BwdChunk { int rb0, n_rb, item0, n_items, key0, n_keys; };
     std::vector<BwdChunk> chunks;
     int n_bwd_keys = 0;                                  // (fp32 batch: key-major work items, one launch)

@@ -298,6 +298,19 @@ struct PcRuns {
     int32_t           n_waves;
 };
 
+// An attention launch that plans for itself: every workgroup makes the tiles and rotations it needs, in a region of the workspace of its
+// own, from the batch's lists in the kernel's arguments (offsets of the staged block).
+struct PcSelf {
+    int32_t off_calls, off_items, off_sel, off_q_pos, n16;        // n16: pieces of 16 bytes in the block, which workgroup 0 leaves in the workspace for the merge
+    int32_t off_rot, off_rot_q;       // within a region: (cos, sin) of the call's entries, then of the workgroup's rows (its tiles come first)
+    int64_t stride;                   // bytes of a region
+    const PcMsgEntry *table;
+    const double *inv_freq;
+    uint4   *ws;
+    char    *regions;
+};
+#define PC_SELF_SEGS 64               // most entries of a call: a wave looks them up one a lane
+
 // Gradient of a bf16 batch: what its kernels need besides PcLaunch (whose items are the row-major kernels').  A unit is
 // a 32-row block of one head; the blocks [rb0, rb0 + n_rb) are processed by one set of launches, and the per-unit
 // buffers are indexed by (block - rb0) * n_q_heads + head.

@@ -66,12 +66,14 @@ void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, in
                              int32_t *kv_slot, int32_t *kv_pos, hipStream_t st);
 
 // split_lanes: 1, or 4 for rows with many splits (their splits are shared out over four lanes)
-void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, const uint16_t *part_o,
+void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, bool many, const uint16_t *part_o,
                      const float *part_ml, void *out, float *lse, int n_q_heads, int D, hipStream_t st);
 
 // fp32 caches: the work items L.items (unit0: block of 32 (row, head) columns of the KV head), partials in fp32; then the
 // rows whose tiles were split
 void pc_launch_attend_f32(const PcLaunch &L, int n_items, int D, hipStream_t st);
+// the same for a launch that plans for itself, from the staged block in its arguments
+void pc_launch_attend_f32_self(const PcArgBlob &blob, const PcLaunch &L, const PcSelf &S, int n_items, int D, hipStream_t st);
 void pc_launch_merge_f32(const PcMergeRow *rows, int n_rows, const void *part_o, const float *part_ml, void *out, float *lse, int n_q_heads, int D,
                          hipStream_t st);
 

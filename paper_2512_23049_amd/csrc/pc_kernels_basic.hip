@@ -822,7 +822,7 @@ void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, in
 // there are few levels of them: the row's descriptor, then the sums and outputs of up to four
 // splits together.
 // ----------------------------------------------------------------------------------
-template <int SL>
+template <int SL, int U>
 __global__ __launch_bounds__(256) void pc_merge_kernel(
     const PcMergeRow *__restrict__ merge_rows, const uint16_t *__restrict__ part_o,
     const float *__restrict__ part_ml, uint16_t *__restrict__ out, float *__restrict__ lse, int n_q_heads,
@@ -830,7 +830,6 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
 {
     constexpr int D = 128;
     constexpr int TPP = 16 * SL;                         // threads per (row, head)
-    constexpr int U = SL == 4 ? 8 : 4;                   // splits requested together
     const int pair = blockIdx.x * (256 / TPP) + (int)threadIdx.x / TPP;
     if (pair >= n_pairs) return;                         // (SL = 4: whole waves)
     const int sub = threadIdx.x & 15, sg = ((int)threadIdx.x % TPP) >> 4;
@@ -916,15 +915,18 @@ __global__ __launch_bounds__(256) void pc_merge_kernel(
 }
 
 // bf16 caches (D = 128; fp32: pc_launch_merge_f32)
-void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, const uint16_t *part_o,
+// many: eight splits a round instead of four (rows of a hundred: 11.6 -> 9.7 us; of nine: 0.4 us slower)
+void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, bool many, const uint16_t *part_o,
                      const float *part_ml, void *out, float *lse, int n_q_heads, int D, hipStream_t st)
 {
     if (n_merge_rows <= 0 || dtype != 1 || D != 128) return;
     const int n_pairs = n_merge_rows * n_q_heads;
-    if (split_lanes == 4)
-        pc_merge_kernel<4><<<(n_pairs + 3) / 4, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
+    if (split_lanes == 4 && many)
+        pc_merge_kernel<4, 8><<<(n_pairs + 3) / 4, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
+    else if (split_lanes == 4)
+        pc_merge_kernel<4, 4><<<(n_pairs + 3) / 4, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
     else
-        pc_merge_kernel<1><<<(n_pairs + 15) / 16, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
+        pc_merge_kernel<1, 4><<<(n_pairs + 15) / 16, 256, 0, st>>>(merge_rows, part_o, part_ml, (uint16_t *)out, lse, n_q_heads, n_pairs);
 }
 
 // ----------------------------------------------------------------------------------------

@@ -18,6 +18,7 @@
 // 13.0 -> 10.4 us, all of it latency.  Distance to fp64 in the 2-norm 1.7e-7 to 3.0e-7 over ten shapes (2.2e-7 to 3.7e-7 with the
 // fp32 instruction: its chains are four times as long).
 #include "pc_pieces.h"
+#include "pc_self_plan.h"
 
 #define NW 8                  // waves of a workgroup
 #define MFMA_F32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0)
@@ -37,8 +38,9 @@ template <> struct Vec<4> { using type = f32x4; };
 
 }  // namespace
 
-template <int D>
-__global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
+// SELF: the launch plans for itself
+template <int D, bool SELF>
+__device__ __forceinline__ void attend_f32(const PcLaunch &L, const PcSelf &S)
 {
     constexpr int NJ = D / 8, VW = D / 32, HALF = D / 2, PITCH = D + 4, NP = D / 32;        // NP: steps of 16 dims and their partners
     // during the walk: the columns' queries turned by their positions, in pieces, and each wave's present tile of keys; then the waves' results
@@ -51,25 +53,25 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     static_assert(sizeof(float) * NW * 32 * PITCH <= sizeof s_mem, "");
 
     const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
-    const PcItem item = L.items[blockIdx.x / L.n_kv_heads];
-    const PcCallDesc cd = L.calls[item.call];
+    const auto *args = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();      // SELF: the lists
+    PcItem item;
+    PcCallDesc cd;
+    if constexpr (SELF) {
+        item = self_item(args, S, blockIdx.x / L.n_kv_heads);
+        cd = self_call(args, S, item.call);
+    } else {
+        item = L.items[blockIdx.x / L.n_kv_heads];
+        cd = L.calls[item.call];
+    }
     const int g = L.n_q_heads / L.n_kv_heads;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hh = lane >> 5;
     const int n_cols = cd.n_q * g;
     const int col0 = item.unit0 * 32;       // column c: query row c / g, head c % g of the group
-
     // this wave's contiguous run of tiles
     const int n_tiles = item.tile_end - item.tile_begin;
     // (waves 0 to 3 are on four SIMDs: what does not divide by eight goes to the first ones)
     const int t0 = item.tile_begin + wave * (n_tiles / NW) + min(wave, n_tiles % NW), t1 = t0 + n_tiles / NW + (wave < n_tiles % NW);
-    const PcTile *tab = L.tiles + item.tile_tab0;
-    auto describe = [&](int t) {
-        const int tc = __builtin_amdgcn_readfirstlane(max(0, min(t, item.tile_end - 1)));
-        if (item.tile_end <= 0) return (i32x4){0, 0, 0, 0};                 // a call that sees nothing has no table
-        return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(tab + tc));
-    };
-    i32x4 next = describe(t0);                           // {slot0, key0, seg, valid | flags}
     if (threadIdx.x == 0) s_again = 0;
 
     using VV = typename Vec<VW>::type;
@@ -77,6 +79,29 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     const unsigned v_at = 4 * hh * D + VW * n;           // within a tile: the lane's dims VW n + 0..VW-1
     const RowTile<D> keys(s_mem + 3 * 2 * NP * 1024 + wave * RowTile<D>::BYTES, lane);      // the present tile's keys
     auto request_k = [&](int slot0) { keys.request(kb + (int64_t)slot0 * D); };
+    const PcTile *tab = L.tiles + item.tile_tab0;
+    const float2 *rot_seg = L.rot_seg + (int64_t)cd.seg_off * HALF, *rot_q = L.rot_q + (int64_t)cd.q_off * HALF;      // of the call's entries, of its rows
+    if constexpr (SELF) {
+        if (blockIdx.x == 0 && (int)threadIdx.x < S.n16) {
+            typedef int i32x4a __attribute__((ext_vector_type(4)));
+            const i32x4a w = reinterpret_cast<const __attribute__((address_space(4))) i32x4a *>(args)[threadIdx.x];
+            S.ws[threadIdx.x] = make_uint4((unsigned)w.x, (unsigned)w.y, (unsigned)w.z, (unsigned)w.w);
+        }
+        char *region = S.regions + (int64_t)blockIdx.x * S.stride;
+        const int row0 = col0 / g;
+        wg_plan<HALF, 64 * NW>(S, args, cd, item.tile_begin, item.tile_end, row0, min((col0 + 31) / g, cd.n_q - 1) - row0 + 1, region,
+                               [&](auto slot_of) __attribute__((always_inline)) { if (t0 < t1) request_k(slot_of(t0)); });
+        region = behind(region);
+        tab = reinterpret_cast<const PcTile *>(region) - item.tile_begin;
+        rot_seg = reinterpret_cast<const float2 *>(region + S.off_rot);
+        rot_q = reinterpret_cast<const float2 *>(region + S.off_rot_q) - row0 * HALF;
+    }
+    auto describe = [&](int t) {
+        const int tc = __builtin_amdgcn_readfirstlane(max(0, min(t, item.tile_end - 1)));
+        if (item.tile_end <= 0) return (i32x4){0, 0, 0, 0};                 // a call that sees nothing has no table
+        return *reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(tab + tc));
+    };
+    i32x4 next = describe(t0);                           // {slot0, key0, seg, valid | flags}
     f32x4 k[4];                                          // step p of the present tile: dims 16 p + 8 hh + 0..7 of the lane's key and their partners
     const unsigned row_at = keys.lds + ((n * (D * 4) + ((n % RowTile<D>::CHUNKS) << 4)) ^ (hh << 5));
     auto read_k = [&](int p) {
@@ -90,10 +115,10 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
     auto load_rot = [&](const i32x4 &d) {
         unsigned at = 16 * rot_at;
         asm volatile("" : "+v"(at));                     // (a 32-bit offset to a uniform address, not a pointer a lane)
-        rot = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + at);
+        rot = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(rot_seg + (int64_t)d.z * HALF) + at);
     };
     auto put_rot = [&]() { reinterpret_cast<f32x4 *>(s_rot[wave])[rot_at] = rot * UP; };     // (a wave's own LDS accesses are in order)
-    if (t0 < t1) { request_k(next.x); load_rot(next); }
+    if (t0 < t1) { if constexpr (!SELF) request_k(next.x); load_rot(next); }
 
     for (int e = threadIdx.x; e < 32 * (HALF / 8); e += 64 * NW) {          // 8 pairs of a column a step
         const int c = e / (HALF / 8), i = 8 * (e % (HALF / 8));
@@ -104,7 +129,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
             const int col = col0 + c;
             const int64_t R = cd.q_off + col / g;
             const float *q = (const float *)L.q + (R * L.n_q_heads + kh * g + col % g) * D + i;
-            const float4 *rot = reinterpret_cast<const float4 *>(L.rot_q + R * HALF + i);
+            const float4 *rot = reinterpret_cast<const float4 *>(rot_q + (int64_t)(col / g) * HALF + i);
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {
                 const float4 cs = up(rot[j / 2]);
@@ -374,7 +399,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         const bool there = col0 + n < n_cols;
         const int col = there ? col0 + n : col0;
         const float *qr = (const float *)L.q + ((int64_t)(cd.q_off + col / g) * L.n_q_heads + kh * g + col % g) * D + 4 * hh;
-        const float4 *rq = reinterpret_cast<const float4 *>(L.rot_q + (int64_t)(cd.q_off + col / g) * HALF) + 2 * hh;
+        const float4 *rq = reinterpret_cast<const float4 *>(rot_q + (int64_t)(col / g) * HALF) + 2 * hh;
         auto query = [&](float4 &a, float4 &b, int j) {  // dims 8 j + 4 hh + 0..3 of the lane's column and their partners, turned by its position
             a = b = make_float4(0.f, 0.f, 0.f, 0.f);
             if (!there) return;
@@ -388,7 +413,7 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         for (int t = t0; t < t1; ++t) {
             const i32x4 d = describe(t);
             const bool causal = on_limit(d);
-            const float4 *rs = reinterpret_cast<const float4 *>(L.rot_seg + (int64_t)(cd.seg_off + d.z) * HALF) + 2 * hh;
+            const float4 *rs = reinterpret_cast<const float4 *>(rot_seg + (int64_t)d.z * HALF) + 2 * hh;
             const float *kr = kb + ((int64_t)d.x + n) * D + 4 * hh, *vr = vb + (int64_t)d.x * D + v_at;
             f32x16 s, s1;                                // (two chains, as above)
 #pragma unroll
@@ -420,6 +445,12 @@ __global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L)
         }
     }
 }
+
+template <int D>
+__global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_kernel(PcLaunch L) { attend_f32<D, false>(L, PcSelf{}); }
+// (the lists come first: the start of the kernel's arguments)
+template <int D>
+__global__ __launch_bounds__(64 * NW, 1) void pc_attend_f32_self_kernel(const PcArgBlob blob, PcLaunch L, PcSelf S) { attend_f32<D, true>(L, S); }
 
 // The splits of a row added in order: one thread per (row, head, 4 dims), every split's sums and outputs requested before
 // any is used (four at a time).
@@ -472,6 +503,14 @@ void pc_launch_attend_f32(const PcLaunch &L, int n_items, int D, hipStream_t st)
     const unsigned grid = (unsigned)n_items * L.n_kv_heads, block = 64 * NW;
     if (D == 64) pc_attend_f32_kernel<64><<<grid, block, 0, st>>>(L);
     else pc_attend_f32_kernel<128><<<grid, block, 0, st>>>(L);
+}
+
+void pc_launch_attend_f32_self(const PcArgBlob &blob, const PcLaunch &L, const PcSelf &S, int n_items, int D, hipStream_t st)
+{
+    if (n_items <= 0) return;
+    const unsigned grid = (unsigned)n_items * L.n_kv_heads, block = 64 * NW;
+    if (D == 64) pc_attend_f32_self_kernel<64><<<grid, block, 0, st>>>(blob, L, S);
+    else pc_attend_f32_self_kernel<128><<<grid, block, 0, st>>>(blob, L, S);
 }
 
 void pc_launch_merge_f32(const PcMergeRow *rows, int n_rows, const void *part_o, const float *part_ml, void *out, float *lse, int n_q_heads, int D,

@@ -926,6 +926,14 @@ static PcTokenWork token_work(const pc_cache *c, const Planned &P, const PcToken
     return tok;
 }
 
+// every call's entries fit a wave, and their angles the short series (see rope_small)
+static bool self_plans(const pc_cache *c, const std::vector<PcCallDesc> &cds)
+{
+    if (c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
+    for (const PcCallDesc &cd : cds) if (cd.n_seg > PC_SELF_SEGS) return false;
+    return true;
+}
+
 int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bool want_items,
                               hipStream_t st, Planned &P)
 {
@@ -1218,6 +1226,26 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             P.lay = layout(0);
         }
     }
+    // An fp32 batch with short lists: the attention launch plans for itself.  (Rows and entries of a workgroup: a region of 20 KB or so each; not a decode
+    // step's, whose tokens the plan builder appends.)
+    if (want_items && !bf16 && !P.backward && !c->host_only && P.tok_items.empty() && P.lay.h2d_bytes <= PC_ARG_BYTES && self_plans(c, cds)) {
+        int most_seg = 1, most_tiles = 1;
+        for (const PcCallDesc &cd : cds) most_seg = std::max(most_seg, cd.n_seg);
+        for (const PcItem &it : pre) most_tiles = std::max(most_tiles, it.tile_end - it.tile_begin);
+        PcSelf S{};
+        S.off_rot = (int32_t)align_up(sizeof(PcTile) * (size_t)most_tiles, 256);
+        S.off_rot_q = S.off_rot + (int32_t)align_up(sizeof(float2) * (size_t)c->half * (size_t)most_seg, 256);
+        S.stride = S.off_rot_q + (int64_t)align_up(sizeof(float2) * (size_t)c->half * (size_t)(32 / g + 2), 256);
+        const size_t regions = (size_t)S.stride * pre.size() * (size_t)H_kv;
+        if (regions <= (size_t)8 << 20 && P.lay.total + regions <= PC_STATIC_WS_BYTES) {
+            S.n16 = (int32_t)((P.lay.h2d_bytes + 15) / 16);
+            S.off_calls = (int32_t)P.lay.calls; S.off_items = (int32_t)P.lay.items_pre; S.off_sel = (int32_t)P.lay.sel; S.off_q_pos = (int32_t)P.lay.q_pos;
+            S.table = c->table_dev; S.inv_freq = c->inv_freq_dev;
+            P.self = S;
+            P.self_at = P.lay.total;
+            P.lay.total += regions;
+        }
+    }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
     P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
@@ -1240,7 +1268,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         P.ws = c->ws;
     }
     StageSlot *slot = nullptr;
-    PcArgBlob blob;
+    PcArgBlob &blob = P.one_blob;
     // (Batches with shared groups stay with the ring, where they were measured: they need six calls at least over the same
     // messages, and their lists, 50 bytes a message and 4 more a row of it, seldom fit.)
     const bool in_args = P.lay.h2d_bytes <= PC_ARG_BYTES && P.n_sh_items == 0;
@@ -1288,6 +1316,11 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         std::memcpy(h + P.lay.sh_segs, sp.segs.data(), sizeof(PcShSeg) * sp.segs.size());
         std::memcpy(h + P.lay.sh_items, sp.items.data(), sizeof(PcShItem) * sp.items.size());
         std::memcpy(h + P.lay.sh_pos, sp.pos.data(), sizeof(int32_t) * sp.pos.size());
+    }
+    if (P.self.n16 > 0) {                                // (h2d_bytes fit the arguments, and the block starts the workspace: lists keep their offsets)
+        P.self.ws = (uint4 *)P.ws;
+        P.self.regions = (char *)P.ws + P.self_at;
+        return PC_OK;
     }
     // A block too large for the arguments is read by the plan builder where it is and copied to the workspace by further
     // blocks of the same launch (a copy in front of it took 4 us on the stream, 8 from 16 KB on, and a gap); beyond
