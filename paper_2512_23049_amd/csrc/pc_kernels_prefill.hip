@@ -315,11 +315,13 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
     const unsigned lds_k = (unsigned)(size_t)&s_k[0][0] + wave_lds, lds_v = (unsigned)(size_t)&s_v[0][0] + wave_lds;
     const unsigned lds_rot = (unsigned)(size_t)&s_rot[0][0];
     const unsigned char *rot_base = (const unsigned char *)(L.rot_seg + (int64_t)cd.seg_off * (PC_D / 2));
-    auto dma_k = [&](const Desc &d, int slot) {         // the rotation table first: it must be the oldest request
+    auto dma_rot = [&](const Desc &d, int slot) {       // in front of the tile's keys: it must be the oldest request
         if constexpr (!PACKED) {
             if (d.fresh() && threadIdx.x < 32)
                 dma16(rot_base + (int64_t)__builtin_amdgcn_readfirstlane(d.seg) * (PC_D / 2) * sizeof(float2), threadIdx.x * 16, lds_rot + slot * (unsigned)sizeof(s_rot[0]));
         }
+    };
+    auto dma_k = [&](const Desc &d, int slot) {
         dma16(kb + (int64_t)__builtin_amdgcn_readfirstlane(d.slot0) * 256, k_src_off, lds_k + slot * TILE_BYTES);
     };
     auto dma_v = [&](const Desc &d, int slot) {
@@ -550,12 +552,12 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
             const int n_all = p_tiles + (cd.self_len + PC_TILE - 1) / PC_TILE;
             for (int t = threadIdx.x; t < n_all; t += 512) kn2 = __builtin_fmaxf(kn2, kn[t]);
         }
-        dma_k(d0, 0); dma_v(d0, 0);
+        dma_rot(d0, 0); dma_k(d0, 0); dma_v(d0, 0);
         if constexpr (!PACKED) request_query();          // right behind the first tile: requests come back in order
-        dma_k(d1, 1); dma_v(d1, 1);
-        dma_k(d2, 2); dma_v(d2, 2);
-        dma_k(d3, 3); dma_v(d3, 3);
-        dma_k(d4, 4);
+        dma_rot(d1, 1); dma_k(d1, 1); dma_v(d1, 1);
+        dma_rot(d2, 2); dma_k(d2, 2); dma_v(d2, 2);
+        dma_rot(d3, 3); dma_k(d3, 3); dma_v(d3, 3);
+        dma_rot(d4, 4); dma_k(d4, 4);
         if constexpr (PACKED) load_query_direct();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if constexpr (!PACKED) finish_query();
@@ -611,6 +613,9 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
         auto iteration = [&](auto uc, auto plain_c, int i) {
             constexpr int u = decltype(uc)::value;
             constexpr int s0 = u, s1 = (u + 1) % RING, s2 = (u + 2) % RING, s4 = (u + 4) % RING;
+            // In front of phase A, not beside its keys: a branch inside would cut the phase in two for the scheduler, and the
+            // exponentials would crowd behind the last MFMAs (2,048 rows over 4,368: 100.7 us there, 100.3 here).
+            dma_rot(d5, s0);
             i32x4 raw6 = request_desc(min(tile0 + i + 6, last));     // first used in the next iteration's requests
             f32x16 sn = phase_a(s0, sc, [&] { dma_k(d5, s0); });             // K(i+5) takes the slot of K(i)
             // the descriptor is awaited here, where the wait costs nothing: it waits for every LDS
