@@ -62,9 +62,8 @@ __device__ __forceinline__ float2 rope_small(double x)
     return make_float2(((n + 1) & 2) ? -fc : fc, (n & 2) ? -fs : fs);
 }
 // The rotation of a position by a frequency.  (A cache may be created with theta < 1, whose frequencies have no such bound.)
-__device__ __forceinline__ float2 rope_turn(int pos, double freq)
+__device__ __forceinline__ float2 rope_angle(double x)
 {
-    const double x = (double)pos * freq;
     if (__builtin_expect(!(__builtin_fabs(x) < 0x1.0p+30), 0)) {
         double s, c;
         sincos(x, &s, &c);
@@ -72,6 +71,7 @@ __device__ __forceinline__ float2 rope_turn(int pos, double freq)
     }
     return rope_small(x);
 }
+__device__ __forceinline__ float2 rope_turn(int pos, double freq) { return rope_angle((double)pos * freq); }
 
 // A decode step's token: one frequency's pair of its key, turned.  The launches that append tokens and the decode launch that
 // writes them itself store the same bits: the roundings are spelled out.
@@ -249,7 +249,7 @@ struct PcShLaunch {
     const PcShGroup *groups;
     const PcShSeg   *segs;
     const PcShItem  *items;
-    const float2    *rot;     // [entries][D/2] (cos, sin)((start - stored base) * theta_i)
+    const float2    *rot;     // [entries][D/2] (cos, sin)((q_pos - start + stored base) * theta_i)
 };
 
 // Everything an attention kernel needs, passed by value.

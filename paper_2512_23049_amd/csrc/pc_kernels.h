@@ -105,7 +105,8 @@ void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunS
 void pc_launch_prefill_bf16(const PcLaunch &L, int n_items, bool packed, hipStream_t st);   // packed: the items of calls that gathered
 
 // shared decode: rotation table of the listed (message, row) pairs, then the attention kernel
-void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const double *inv_freq, int half, float2 *rot, hipStream_t st);
+void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const PcShGroup *groups, int n_groups, const int32_t *q_pos, const double *inv_freq, int half,
+                          float2 *rot, hipStream_t st);
 void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, hipStream_t st);
 
 #endif

@@ -8,8 +8,14 @@
 // rows times the g heads.  What differs from prefill:
 //   * a row sees a message only if its call lists it: one bit per (message, row);
 //   * each call places a message at its own start, so the queries are turned per (message, row)
-//     from a table of (cos, sin)((start - stored base) theta_i) the host lists and a small
-//     kernel fills;
+//     from a table of (cos, sin)((q_pos - start + stored base) theta_i) a small kernel fills from the
+//     host's list.  One rotation of the query as it came, kept in fp32 in registers: turned by its own
+//     position first and by the message's displacement then, its upper half stood in LDS and a turn
+//     took as many multiplications and eight more LDS reads (32 calls over 410 of 512 messages, g = 8,
+//     four steps: 602 us, now 563).  A turn is still some 13 of the walk's 95 us: all waves of a
+//     workgroup turn at once.  Spread over the tiles of the message before (four of sixteen pairs
+//     a unit, results in LDS) it took 669 us: a unit waits for its LDS reads in every wave, and beside
+//     the score MFMAs it does not fit the registers;
 //   * the rows are independent calls, so there is no causal structure: a call's own growing
 //     tail is just one more message that only its row sees.
 // K and V tiles go global -> LDS directly (16 bytes per lane, no staging registers) into a
@@ -63,32 +69,36 @@ __device__ __forceinline__ void sh_wait_landed()
 
 }  // namespace
 
-// (cos, sin)(pos * theta_i) for every listed (message, row) pair; PC_SH_ABSENT entries are skipped
-__global__ __launch_bounds__(256) void pc_shared_rot_kernel(const int32_t *__restrict__ pos, int64_t n_ent,
-                                                            const double *__restrict__ inv_freq, int half,
+// (cos, sin)((q_pos - pos) theta_i) for every listed (message, row) pair, q_pos being the row's; PC_SH_ABSENT entries are skipped
+__global__ __launch_bounds__(256) void pc_shared_rot_kernel(const int32_t *__restrict__ pos, int64_t n_ent, const PcShGroup *__restrict__ groups, int n_groups,
+                                                            const int32_t *__restrict__ q_pos, const double *__restrict__ inv_freq, int half,
                                                             float2 *__restrict__ rot)
 {
     const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (tid >= n_ent * half) return;
-    const int64_t ent = tid / half;
-    const int i = (int)(tid - ent * half);
+    const int ent = (int)(tid / half), i = (int)(tid - (int64_t)ent * half);
     const int p = pos[ent];
     if (p == PC_SH_ABSENT) return;
-    double s, c;
-    sincos((double)p * inv_freq[i], &s, &c);
-    rot[tid] = make_float2((float)c, (float)s);
+    int gi = 0;
+    while (gi + 1 < n_groups && groups[gi + 1].rot_off <= ent) ++gi;
+    const PcShGroup gr = groups[gi];
+    rot[tid] = rope_angle((double)((int64_t)q_pos[gr.row0 + (ent - gr.rot_off) % gr.n_rows] - p) * inv_freq[i]);
 }
 
+// TAB: a wave's part of a message's rotation table, in KB (32 / g rows of 512 bytes), fetched into LDS while the message before is
+// walked; 0: the turn reads it from memory.  32 calls over 150 of 200 messages, us a pass of four steps, from LDS / from memory: g = 8
+// 304 / 306, g = 4 274 / 276, g = 2 (whose wave has 16 rows) 271 / 266, so g >= 4 takes LDS.
+template <int TAB>
 __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch L, PcShLaunch S)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char s_k[SH_RING][8192];
     __shared__ __attribute__((aligned(1024))) unsigned char s_v[SH_RING][8192];
-    __shared__ __attribute__((aligned(16))) float4 s_qm[8][8][64];    // upper half (dims 64..127) of the fp32 query master
+    __shared__ __attribute__((aligned(1024))) unsigned char s_tab[TAB ? 8 : 1][TAB ? TAB * 1024 : 16];      // the next message's rotations, a wave's own rows
 
     const int kh = blockIdx.x % L.n_kv_heads;          // consecutive workgroups (one per XCD) take different KV heads
     const PcShItem item = S.items[blockIdx.x / L.n_kv_heads];
     const PcShGroup gr = S.groups[item.group];
-    const int g = L.n_q_heads / L.n_kv_heads;            // 1, 2, 4 or 8: a workgroup covers 8 / g blocks of 32 rows
+    const int g = TAB ? 16 / TAB : L.n_q_heads / L.n_kv_heads;      // 1, 2, 4 or 8: a workgroup covers 8 / g blocks of 32 rows
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 31, hh = lane >> 5;
     // A wave's 32 columns are 32 / g rows (calls) times the g heads of the KV head, head fastest: the lanes of
@@ -101,29 +111,19 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
     const bool row_ok = row < gr.n_rows;
     const int Rg = gr.row0 + (row_ok ? row : 0);         // the group's calls are consecutive one-row calls
 
-    // query turned by its own position, scaled by softmax_scale * log2(e), fp32: x[ks][j] is dim
-    // 16*ks + 8*hh + j (registers); its partner 64 dims up is kept in LDS (s_qm[wave][2*ks + j/4][lane],
-    // read back once per message): the registers are needed for the MFMA fragments
-    float x[4][8];
+    // the query as it came: x[ks][j] is dim 16*ks + 8*hh + j, y[ks][j] its partner 64 dims up
+    float x[4][8], y[4][8];
     {
         const uint16_t *qp = (const uint16_t *)L.q + ((int64_t)Rg * L.n_q_heads + h) * PC_D + 8 * hh;
-        const float2 *rq = L.rot_q + (int64_t)Rg * (PC_D / 2) + 8 * hh;
-        const float sc = row_ok ? L.scale_log2 : 0.f;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const uint4 lo = ldg16(qp + 16 * ks), hi = ldg16(qp + 16 * ks + 64);
             const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
-            float yy[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float a = ((j & 1) ? bf_hi(lw[j >> 1]) : bf_lo(lw[j >> 1])) * sc;
-                const float b = ((j & 1) ? bf_hi(hw[j >> 1]) : bf_lo(hw[j >> 1])) * sc;
-                const float2 cs = rq[16 * ks + j];
-                x[ks][j] = a * cs.x - b * cs.y;
-                yy[j] = a * cs.y + b * cs.x;
+                x[ks][j] = (j & 1) ? bf_hi(lw[j >> 1]) : bf_lo(lw[j >> 1]);
+                y[ks][j] = (j & 1) ? bf_hi(hw[j >> 1]) : bf_lo(hw[j >> 1]);
             }
-            s_qm[wave][2 * ks][lane] = make_float4(yy[0], yy[1], yy[2], yy[3]);
-            s_qm[wave][2 * ks + 1][lane] = make_float4(yy[4], yy[5], yy[6], yy[7]);
         }
     }
 
@@ -137,9 +137,7 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
     // of a lane are keys 8*hh + 0..7 / 16 + 8*hh + 0..7 (the layout the second MFMA's B operand wants)
     const int krow = 16 * (n >> 4) + 8 * ((n >> 2) & 1) + 4 * ((n >> 3) & 1) + (n & 3);
 
-    unsigned k_off[8];                                   // byte offset of K fragment ks within a tile, for this lane
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) k_off[ks] = (unsigned)(krow * 256 + (((2 * ks + hh) ^ (krow & 15)) << 4));
+    const unsigned k_off = (unsigned)(krow * 256 + ((hh ^ (krow & 15)) << 4));       // of this lane's K fragment 0 within a tile; fragment ks: ^ 32 ks
 
     // Softmax state of this lane's column, as in the prefill kernel: probabilities are 2^(score - m_ref)
     // with a reference that starts at 0 and moves only when it has to (a tile's maximum more than
@@ -192,43 +190,48 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
 
     bf16x8 qop[8];
     int cur_seg = -1;
-    // turn this lane's row by -(start - base) of the message for its call; rows that do not list the
-    // message keep whatever operands they have (their scores are masked)
-    bool vis = false;
-    auto turn = [&](int seg, unsigned vis_word) {
-        cur_seg = seg;
-        vis = row_ok && ((vis_word >> (row & 31)) & 1u);
-        if (vis) {
-            const float4 *rs = reinterpret_cast<const float4 *>(S.rot + ((int64_t)gr.rot_off + (int64_t)seg * gr.n_rows + row) * (PC_D / 2) + 8 * hh);
+    asm("" : "+s"(cur_seg));                             // (or the first message's start is peeled off the walk)
+    bool vis = false;                                    // this lane's row lists the message
+    auto sees = [&](unsigned word) { return row_ok && ((word >> (row & 31)) & 1u); };
+    // The turn of a row to a message's keys: by its own position less the message's displacement for its call, one rotation in fp32 of
+    // the query as it came, rounded to bf16 once (the softmax scale meets the scores).  rs: the (cos, sin) of this lane's pairs
+    auto turn = [&](const float4 *rs) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                uint32_t lo[4], hi[4];
+        for (int ks = 0; ks < 4; ++ks) {
+            uint32_t lo[4], hi[4];
 #pragma unroll
-                for (int j4 = 0; j4 < 2; ++j4) {
-                    const float4 c0 = rs[(16 * ks + 4 * j4) >> 1];          // (cos, sin) of pairs 4*j4, 4*j4 + 1
-                    const float4 c1 = rs[((16 * ks + 4 * j4) >> 1) + 1];    // ... 4*j4 + 2, 4*j4 + 3
-                    const float x0 = x[ks][4 * j4], x1 = x[ks][4 * j4 + 1], x2 = x[ks][4 * j4 + 2], x3 = x[ks][4 * j4 + 3];
-                    const float4 yv = s_qm[wave][2 * ks + j4][lane];
-                    lo[2 * j4] = pack_bf16(x0 * c0.x + yv.x * c0.y, x1 * c0.z + yv.y * c0.w);
-                    hi[2 * j4] = pack_bf16(yv.x * c0.x - x0 * c0.y, yv.y * c0.z - x1 * c0.w);
-                    lo[2 * j4 + 1] = pack_bf16(x2 * c1.x + yv.z * c1.y, x3 * c1.z + yv.w * c1.w);
-                    hi[2 * j4 + 1] = pack_bf16(yv.z * c1.x - x2 * c1.y, yv.w * c1.z - x3 * c1.w);
-                }
-                qop[ks] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
-                qop[ks + 4] = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+            for (int j = 0; j < 4; ++j) {
+                const float4 c = rs[8 * ks + j];         // of dims 2 j and 2 j + 1
+                const float x0 = x[ks][2 * j], x1 = x[ks][2 * j + 1], y0 = y[ks][2 * j], y1 = y[ks][2 * j + 1];
+                lo[j] = pack_bf16(x0 * c.x - y0 * c.y, x1 * c.z - y1 * c.w);
+                hi[j] = pack_bf16(x0 * c.y + y0 * c.x, x1 * c.w + y1 * c.z);
             }
+            qop[ks] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+            qop[ks + 4] = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
         }
     };
+    // The next message's table comes by direct loads into the wave's own part of LDS.  It is contiguous rows; a group's last waves may
+    // have fewer rows than lanes ask for, or none.
+    const unsigned lds_tab = __builtin_amdgcn_readfirstlane((unsigned)(size_t)&s_tab[TAB ? wave : 0][0]);
+    const int last_row = gr.n_rows - 1;
+    auto issue_table = [&](int seg) {
+        const unsigned char *from = (const unsigned char *)(S.rot + ((int64_t)gr.rot_off + (int64_t)min(seg, gr.n_seg - 1) * gr.n_rows) * (PC_D / 2));
+#pragma unroll
+        for (int j = 0; j < TAB; ++j)
+            sh_dma16(from, (unsigned)min(rpw * wave + 2 * j + (lane >> 5), last_row) * 512 + (lane & 31) * 16, lds_tab + j * 1024);
+    };
+    const unsigned char *tab = &s_tab[TAB ? wave : 0][0] + (n / g) * 512 + 64 * hh;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qop[ks] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
 
     auto compute = [&](int buf, int valid, int req_ring) {
-        const unsigned char *kt = &s_k[buf][0], *vt = &s_v[buf][0];
+        const unsigned kt = k_off + (unsigned)(buf * 8192);                // (bits 5..7 are the lane's own: the ring starts on a KB)
+        const unsigned char *vt = &s_v[buf][0];
         // all eight K fragments are requested up front; each is replaced by a V fragment as soon as its
         // MFMA has consumed it, so the P.V MFMAs find their operands in registers
         bf16x8 fr[8];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) fr[ks] = *reinterpret_cast<const bf16x8 *>(kt + k_off[ks]);
+        for (int ks = 0; ks < 8; ++ks) fr[ks] = *reinterpret_cast<const bf16x8 *>(&s_k[0][0] + (kt ^ (32u * ks)));
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(fr[ks]));      // (keeps the compiler from moving each read down to its MFMA)
         f32x16 s;
@@ -244,17 +247,18 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        if (valid < PC_TILE) {                           // ragged last tile of a message (uniform): keys past its end
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = 16 * (r >> 3) + 8 * hh + (r & 7);
-                s[r] = (key < valid) ? s[r] : -INFINITY;
-            }
-        }
-        {                                                // a row that does not list the message: every score to -inf
+        {                                                // scaled; a row that does not list the message: every score to -inf
             const float m_eff = vis ? m_ref : INFINITY;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] -= m_eff;
+            for (int r = 0; r < 16; ++r) s[r] = __builtin_fmaf(s[r], L.scale_log2, -m_eff);
+        }
+        if (valid < PC_TILE) {                           // ragged last tile of a message (uniform): keys past its end
+            const int limit = valid - 8 * hh;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = 16 * (r >> 3) + (r & 7);      // and 8 * hh, which stands with the limit
+                s[r] = (key < limit) ? s[r] : -INFINITY;
+            }
         }
         float mx = sh_max3(sh_max3(s[0], s[1], s[2]), s[3], s[4]);
         mx = sh_max3(sh_max3(mx, s[5], s[6]), s[7], s[8]);
@@ -306,15 +310,38 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
         TileD d[SH_AHEAD + 1];
 #pragma unroll
         for (int i = 0; i < SH_AHEAD; ++i) { d[i] = request(min(t0 + i, last)); issue_k(i); issue_v(i); }
-        sh_wait_landed();                                // the first tile has landed
+        int asked = t0 - 2;                              // the step that asked for the table
+        if constexpr (TAB > 0) {
+            issue_table(item.seg_begin);
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            asm volatile("" ::: "memory");
+        } else {
+            sh_wait_landed();                            // the first tile has landed
+        }
         sh_barrier();
         for (int t = t0; t < t1; ++t) {
             const int ring = (t - t0) & (SH_RING - 1);
-            // (the table loads of a turn go first: issued behind the new requests they would have to wait for them)
-            if (d[0].seg != cur_seg) turn(d[0].seg, d[0].vis);
+            if (d[0].seg != cur_seg) {                   // (a union has no empty messages: it is the one after)
+                cur_seg = d[0].seg;
+                if constexpr (TAB > 0) {
+                    // (the wait at the end of a step takes in what was asked for a step before; behind a message of one tile only that
+                    // step's two tile requests may still be on their way)
+                    if (t - asked < 2) { __builtin_amdgcn_s_waitcnt(0x0F72); asm volatile("" ::: "memory"); }
+                    vis = sees(d[0].vis);
+                    if (vis) turn(reinterpret_cast<const float4 *>(tab));
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the table is no longer read)
+                    issue_table(cur_seg + 1);
+                    asked = t;
+                } else {
+                    // (the table loads of a turn go first: issued behind the new requests they would have to wait for them)
+                    vis = sees(d[0].vis);
+                    if (vis) turn(reinterpret_cast<const float4 *>(S.rot + ((int64_t)gr.rot_off + (int64_t)cur_seg * gr.n_rows + row) * (PC_D / 2) + 8 * hh));
+                }
+            }
             // tile t + SH_AHEAD takes the slot of tile t - 1, which every wave left before the last barrier
             d[SH_AHEAD] = request(min(t + SH_AHEAD, last));
-            compute(ring, d[0].valid, (ring + SH_AHEAD) & (SH_RING - 1));
+            const int to = (ring + SH_AHEAD) & (SH_RING - 1);
+            compute(ring, d[0].valid, to);
             sh_wait_landed();                            // tile t + 1 has landed (the later ones may be in flight)
             sh_barrier();
 #pragma unroll
@@ -361,16 +388,21 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
     }
 }
 
-void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const double *inv_freq, int half, float2 *rot, hipStream_t st)
+void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const PcShGroup *groups, int n_groups, const int32_t *q_pos, const double *inv_freq, int half,
+                          float2 *rot, hipStream_t st)
 {
     if (n_ent <= 0) return;
     const int64_t n = n_ent * half;
-    pc_shared_rot_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(pos, n_ent, inv_freq, half, rot);
+    pc_shared_rot_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(pos, n_ent, groups, n_groups, q_pos, inv_freq, half, rot);
 }
 
 void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, hipStream_t st)
 {
     if (n_items <= 0) return;
     dim3 grid((unsigned)n_items * L.n_kv_heads);
-    pc_decode_shared_bf16_kernel<<<grid, 512, 0, st>>>(L, S);
+    switch (L.n_q_heads / L.n_kv_heads) {
+    case 8: pc_decode_shared_bf16_kernel<2><<<grid, 512, 0, st>>>(L, S); break;
+    case 4: pc_decode_shared_bf16_kernel<4><<<grid, 512, 0, st>>>(L, S); break;
+    default: pc_decode_shared_bf16_kernel<0><<<grid, 512, 0, st>>>(L, S);
+    }
 }

@@ -1248,7 +1248,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-    P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
+    P.n_sh_items = (int)sp.items.size(); P.n_sh_groups = (int)sp.groups.size(); P.n_sh_pos = sp.pos.size();
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
@@ -1363,8 +1363,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             slot->used = true;
         }
         if (P.n_sh_items > 0) {
-            pc_launch_shared_rot((const int32_t *)(w + P.lay.sh_pos), (int64_t)P.n_sh_pos, c->inv_freq_dev, c->half,
-                                 (float2 *)(w + P.lay.sh_rot), st);
+            pc_launch_shared_rot((const int32_t *)(w + P.lay.sh_pos), (int64_t)P.n_sh_pos, (const PcShGroup *)(w + P.lay.sh_groups), P.n_sh_groups,
+                                 (const int32_t *)(w + P.lay.q_pos), c->inv_freq_dev, c->half, (float2 *)(w + P.lay.sh_rot), st);
             PC_HIP(c, hipGetLastError());
         }
     }
