@@ -45,13 +45,15 @@ struct PcTokenWork {
     void *k_store = nullptr, *v_store = nullptr;
     int64_t slots = 0; int n_kv_heads = 0, D = 0, dtype = 0;
 };
+// The rotations of a shared decode walk: n positions, PC_SH_ABSENT where a row does not list the message, to [n][64] (cos, sin).
+struct PcShTurns { const int32_t *pos = nullptr; int n = 0; float2 *rot = nullptr; };
 // tile_blocks: blocks that share out a call's tile table
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
+                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const PcShTurns &turns, const void *staged, void *ws, size_t h2d_bytes,
                           hipStream_t st);
-// (staged != null: calls, sel, q_pos and tok.items lie in that block of pinned host memory, which the kernel copies to the workspace)
+// (staged != null: calls, sel, q_pos, tok.items and turns.pos lie in that block of pinned host memory, which the kernel copies to the workspace)
 // the same with the staged block (h2d_bytes <= PC_ARG_BYTES, at the start of the workspace) in the kernel's arguments: calls,
 // sel, q_pos and tok.items are addresses within the workspace, which the kernel fills for the kernels behind it
 void pc_launch_build_plan_arg(const PcArgBlob &blob, void *ws, size_t h2d_bytes, const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
@@ -105,8 +107,6 @@ void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunS
 void pc_launch_prefill_bf16(const PcLaunch &L, int n_items, bool packed, hipStream_t st);   // packed: the items of calls that gathered
 
 // shared decode: rotation table of the listed (message, row) pairs, then the attention kernel
-void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const PcShGroup *groups, int n_groups, const int32_t *q_pos, const double *inv_freq, int half,
-                          float2 *rot, hipStream_t st);
 void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, hipStream_t st);
 
 #endif

@@ -637,14 +637,31 @@ __device__ __forceinline__ void build_plan_block(
     }
 }
 
+constexpr int TURN_ROWS = 16;
+
 __global__ __launch_bounds__(256) void pc_build_plan_kernel(
     const PcCallDesc *__restrict__ calls, int n_calls, const int2 *__restrict__ sel,
     const int32_t *__restrict__ q_pos, PcMsgEntry *__restrict__ table,
     const double *__restrict__ inv_freq, int half, int total_seg, int total_q,
     PcSegment *__restrict__ segs, int32_t *__restrict__ seg_kvoff,
     float2 *__restrict__ rot_seg, float2 *__restrict__ rot_q, float2 *__restrict__ rot_qw, PcTile *__restrict__ tiles, PcTokenWork tok, int tok_block0, int tile_blocks,
-    const uint4 *__restrict__ staged, uint4 *__restrict__ ws, int n16, int copy_block0)
+    PcShTurns turns, int turn_block0, const uint4 *__restrict__ staged, uint4 *__restrict__ ws, int n16, int copy_block0)
 {
+    if ((int)blockIdx.x >= turn_block0 && (int)blockIdx.x < copy_block0) {
+        // A shared walk's rotations, a wave a position at a time.  16 positions a block, read as one line: they may lie in host memory.
+        // (As a launch of its own behind this one: 23 calls over 19 of 33 messages and a system message 32.9 us a step, here 29.3; 22 over
+        // 256 of 265 57.0 and 54.7.)
+        __shared__ int s_pos[TURN_ROWS];
+        const int at = ((int)blockIdx.x - turn_block0) * TURN_ROWS;
+        if ((int)threadIdx.x < TURN_ROWS) s_pos[threadIdx.x] = at + (int)threadIdx.x < turns.n ? turns.pos[at + threadIdx.x] : PC_SH_ABSENT;
+        __syncthreads();
+        const double freq = inv_freq[threadIdx.x & 63];
+        for (int k = (int)threadIdx.x >> 6; k < TURN_ROWS; k += 4) {
+            const int p = s_pos[k];
+            if (p != PC_SH_ABSENT) turns.rot[(int64_t)(at + k) * 64 + (threadIdx.x & 63)] = rope_turn(p, freq);
+        }
+        return;
+    }
     if ((int)blockIdx.x >= copy_block0) {                // the staged block, from host memory to the workspace
         const int i = ((int)blockIdx.x - copy_block0) * 256 + (int)threadIdx.x;
         if (i < n16) ws[i] = staged[i];
@@ -739,15 +756,15 @@ static unsigned plan_blocks(int n_calls, int tile_blocks, int half, int total_se
 void pc_launch_build_plan(const PcCallDesc *calls, int n_calls, const int2 *sel, const int32_t *q_pos,
                           PcMsgEntry *table, const double *inv_freq, int half, int total_seg,
                           int total_q, PcSegment *segs, int32_t *seg_kvoff, float2 *rot_seg,
-                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const void *staged, void *ws, size_t h2d_bytes,
+                          float2 *rot_q, float2 *rot_qw, PcTile *tiles, int tile_blocks, const PcTokenWork &tok, const PcShTurns &turns, const void *staged, void *ws, size_t h2d_bytes,
                           hipStream_t st)
 {
     int tok_block0 = 0;
     const unsigned grid = plan_blocks(n_calls, tile_blocks, half, total_seg, total_q, tok, tok_block0);
-    const unsigned n16 = staged ? (unsigned)((h2d_bytes + 15) / 16) : 0;
-    pc_build_plan_kernel<<<grid + (n16 + 255) / 256, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
+    const unsigned n16 = staged ? (unsigned)((h2d_bytes + 15) / 16) : 0, copy_block0 = grid + (unsigned)(turns.n + TURN_ROWS - 1) / TURN_ROWS;
+    pc_build_plan_kernel<<<copy_block0 + (n16 + 255) / 256, 256, 0, st>>>(calls, n_calls, sel, q_pos, table, inv_freq, half, total_seg,
                                                                    total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks,
-                                                                   (const uint4 *)staged, (uint4 *)ws, (int)n16, (int)grid);
+                                                                   turns, (int)grid, (const uint4 *)staged, (uint4 *)ws, (int)n16, (int)copy_block0);
 }
 
 // Lists of a call that is recorded into a graph: whatever pinned memory held them would have to stay as it is for as long as the

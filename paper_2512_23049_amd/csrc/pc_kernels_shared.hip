@@ -8,7 +8,7 @@
 // rows times the g heads.  What differs from prefill:
 //   * a row sees a message only if its call lists it: one bit per (message, row);
 //   * each call places a message at its own start, so the queries are turned per (message, row)
-//     from a table of (cos, sin)((q_pos - start + stored base) theta_i) a small kernel fills from the
+//     from a table of (cos, sin)((q_pos - start + stored base) theta_i) the plan builder fills from the
 //     host's list.  One rotation of the query as it came, kept in fp32 in registers: turned by its own
 //     position first and by the message's displacement then, its upper half stood in LDS and a turn
 //     took as many multiplications and eight more LDS reads (32 calls over 410 of 512 messages, g = 8,
@@ -68,22 +68,6 @@ __device__ __forceinline__ void sh_wait_landed()
 }
 
 }  // namespace
-
-// (cos, sin)((q_pos - pos) theta_i) for every listed (message, row) pair, q_pos being the row's; PC_SH_ABSENT entries are skipped
-__global__ __launch_bounds__(256) void pc_shared_rot_kernel(const int32_t *__restrict__ pos, int64_t n_ent, const PcShGroup *__restrict__ groups, int n_groups,
-                                                            const int32_t *__restrict__ q_pos, const double *__restrict__ inv_freq, int half,
-                                                            float2 *__restrict__ rot)
-{
-    const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (tid >= n_ent * half) return;
-    const int ent = (int)(tid / half), i = (int)(tid - (int64_t)ent * half);
-    const int p = pos[ent];
-    if (p == PC_SH_ABSENT) return;
-    int gi = 0;
-    while (gi + 1 < n_groups && groups[gi + 1].rot_off <= ent) ++gi;
-    const PcShGroup gr = groups[gi];
-    rot[tid] = rope_angle((double)((int64_t)q_pos[gr.row0 + (ent - gr.rot_off) % gr.n_rows] - p) * inv_freq[i]);
-}
 
 // TAB: a wave's part of a message's rotation table, in KB (32 / g rows of 512 bytes), fetched into LDS while the message before is
 // walked; 0: the turn reads it from memory.  32 calls over 150 of 200 messages, us a pass of four steps, from LDS / from memory: g = 8
@@ -386,14 +370,6 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
             L.part_ml[(pr * L.n_q_heads + h) * 2 + 1] = l;
         }
     }
-}
-
-void pc_launch_shared_rot(const int32_t *pos, int64_t n_ent, const PcShGroup *groups, int n_groups, const int32_t *q_pos, const double *inv_freq, int half,
-                          float2 *rot, hipStream_t st)
-{
-    if (n_ent <= 0) return;
-    const int64_t n = n_ent * half;
-    pc_shared_rot_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(pos, n_ent, groups, n_groups, q_pos, inv_freq, half, rot);
 }
 
 void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, hipStream_t st)

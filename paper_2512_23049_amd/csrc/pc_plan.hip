@@ -185,7 +185,7 @@ struct SharedPlan {
     std::vector<PcShGroup> groups;
     std::vector<PcShSeg> segs;
     std::vector<PcShItem> items;
-    std::vector<int32_t> pos;                    // rotation positions, PC_SH_ABSENT where a row does not list the message
+    std::vector<int32_t> pos;                    // rotation positions, q_pos - start + stored base, PC_SH_ABSENT where a row does not list the message
 };
 
 // The ways of a batch of one-row calls, in us a step with launches and merge.  Tiles (K and V of 32 keys, a KV head) are shared out over the
@@ -199,7 +199,11 @@ struct SharedPlan {
 // In a batch with longer calls, whose launches are there anyway, a group takes the shared walk if its calls list SHARE_MIN times the
 // tokens of the union: a union tile costs a workgroup 8.7 ns with the chip full, a tile streamed by one call 1.5 to 1.7.
 constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS = 0.33, OWN_FIXED = 8.0, OWN_PINNED = 14.0, RUN_FIXED = 20.5, RUN_PART = 0.045,
-                 SHARED_FIXED = 30.0, SHARED_TILE = 1.1;
+                 SHARED_FIXED = 30.0, SHARED_TILE = 1.05;
+// (the other two prices are the less certain the more often a tile is met again: 44 calls over 2 of 5 messages and a long system message, priced at 33
+// us by walks of their own, took 50, shared 38.  125 drawn batches of 6 to 64 calls: 1.25 times as fast as by the sharing ratio alone.  The
+// shared figures above were taken with the rotations in a launch of their own, 3 us more than now.)
+constexpr double SHARE_LEAN = 0.8;
 constexpr double RUN_START = 1.5;                        // a run's start and end, in passes
 constexpr double SHARE_MIN = 6.0;
 // rows with more splits than this are merged by four lanes per 8 dimensions
@@ -209,7 +213,7 @@ constexpr int MERGE_MANY_SPLITS = 8;
 struct Union {
     struct Seg { int32_t msg, occ, len; int64_t slot; uint32_t vis[8]; };      // bit n of vis: row n lists it
     std::vector<Seg> segs;                                // as they turn up
-    std::vector<int32_t> pos;                             // [seg][row] start - stored base, PC_SH_ABSENT where the row does not list it
+    std::vector<int32_t> pos;                             // [seg][row] q_pos - start + stored base, PC_SH_ABSENT where the row does not list it
     std::vector<int32_t> order;                           // segs in cache-slot order
     int n_rows = 0;
     int64_t call_tiles = 0, tiles = 0;
@@ -249,6 +253,7 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
         // the union is sorted once, below: a call's own list is needed in slot order only where it names a message
         // twice (its occurrences are told apart by their starts)
         int32_t self_occ = 0;
+        const int32_t q0 = rc.q_pos[0];
         const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
         uint32_t twice = 0;
         for (const int2 *e = rc.sel.data(), *end = e + rc.sel.size(); e < end; ++e) {
@@ -259,11 +264,11 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
             uint32_t &vis = segs[u].vis[word];
             twice |= vis & bit;
             vis |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = e->y - hm.base_pos;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = q0 - e->y + hm.base_pos;
         }
         auto enter = [&](int32_t u, int32_t p) {
             segs[u].vis[word] |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = p;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = q0 - p;
         };
         if (twice) {
             for (size_t u = 0; u < un.segs.size(); ++u) {             // the row again, from nothing
@@ -328,6 +333,7 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     const int n_calls = (int)res.size();
     sp.in_shared.assign((size_t)n_calls, 0);
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
+    if (c->cfg.max_position > INT32_MAX / 3) return false;            // a position less a start plus a stored base is listed in 32 bits
     const int rows_max = 32 * (8 / g);
     const double per_cu = c->cfg.n_kv_heads / 256.0;
     static thread_local Union un;                        // (at most half a million entries; kept: fresh pages for them cost more than filling them)
@@ -341,10 +347,11 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
     // step, took 104 us and then 128)
     const bool whole = alone && n_calls <= 256 && (n_calls <= rows_max || entries <= 2048) && collect_union(c, res, 0, n_calls, ((size_t)1 << 19) / (size_t)n_calls, un);
-    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles;
+    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles, lean = 1;
     if (whole) {
         const DecodeCost cost = decode_cost(c, un);
-        const double shared = SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)((n_calls + rows_max - 1) / rows_max);
+        if ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles) lean = SHARE_LEAN;
+        const double shared = lean * (SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)((n_calls + rows_max - 1) / rows_max));
         own = cost.own;
         if (!c->host_only && cost.by_message < 0.95 * std::min(own, shared) && plan_runs(c, P, un, cost, st, rc)) return true;
         if (rc != PC_OK) return false;
@@ -369,7 +376,7 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
         bool take = fits && un.tiles > 0 && un.tiles < INT32_MAX / 2;
         if (alone) shared += take ? SHARED_TILE * per_cu * (double)un.tiles : OWN_FIXED + per_cu * TILE_AGAIN * (double)sum_tiles;
         else take = take && (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles));
-        if (alone && own < shared) {                     // the batch's calls walk on their own after all
+        if (alone && own < lean * shared) {                     // the batch's calls walk on their own after all
             sp.in_shared.assign((size_t)n_calls, 0);
             sp.groups.clear(); sp.segs.clear(); sp.pos.clear();
             return false;
@@ -458,7 +465,7 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
             for (uint32_t v = u.vis[b]; v; v &= v - 1) {
                 const int row = 32 * b + __builtin_ctz(v);
                 run.row[n] = row;
-                run.pos[n] = P.res[(size_t)row].q_pos[0] - (pos[row] + c->msgs[(size_t)u.msg].base_pos);
+                run.pos[n] = pos[row] - c->msgs[(size_t)u.msg].base_pos;
                 if (++n == per_run) emit();
             }
         if (n > 0) emit();
@@ -1248,7 +1255,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-    P.n_sh_items = (int)sp.items.size(); P.n_sh_groups = (int)sp.groups.size(); P.n_sh_pos = sp.pos.size();
+    P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
@@ -1338,6 +1345,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         ProfScope ps(c, 1, st);
         char *w = (char *)P.ws, *from = in_place ? h : w;
         const PcTokenWork tok = token_work(c, P, (const PcTokenItem *)(from + P.lay.tok_items));
+        PcShTurns turns;
+        if (P.n_sh_items > 0) turns = PcShTurns{(const int32_t *)(from + P.lay.sh_pos), (int)P.n_sh_pos, (float2 *)(w + P.lay.sh_rot)};
         auto *calls_at = (const PcCallDesc *)(from + P.lay.calls);
         auto *sel_at = (const int2 *)(from + P.lay.sel);
         auto *q_pos_at = (const int32_t *)(from + P.lay.q_pos);
@@ -1355,17 +1364,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                                      P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, st);
         else
             pc_launch_build_plan(calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
+                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, turns, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
         if (in_place) {                                  // the ring slot is free again once the plan builder is done
             PC_HIP(c, hipEventRecord(slot->ev, st));
             slot->used = true;
-        }
-        if (P.n_sh_items > 0) {
-            pc_launch_shared_rot((const int32_t *)(w + P.lay.sh_pos), (int64_t)P.n_sh_pos, (const PcShGroup *)(w + P.lay.sh_groups), P.n_sh_groups,
-                                 (const int32_t *)(w + P.lay.q_pos), c->inv_freq_dev, c->half, (float2 *)(w + P.lay.sh_rot), st);
-            PC_HIP(c, hipGetLastError());
         }
     }
     return PC_OK;
