@@ -292,7 +292,9 @@ int32_t pc_cache_info(pc_cache *c, int32_t *n_messages, int64_t *slots_used,
  * work recorded so far, then returns per-kernel-class totals since the last reset.
  * Classes: 0 append, 1 plan builder, 2 prefill attention, 3 decode attention,
  * 4 split merge, 5 fp32 attention, 6 table expansion, 7 reposition, 8 key gather.
- * A decode batch that goes to one launch counts under 3 as a whole: plan, a step's tokens, attention and merge. */
+ * A decode batch that goes to one launch counts under 3 as a whole: plan, a step's tokens, attention and merge.  One that goes
+ * message by message: 1 its preparation (with a step's tokens), 3, 4.  fp32 batches with short lists plan in their attention
+ * launch: no 1. */
 #define PC_N_KERNEL_CLASSES 9
 int32_t pc_profile_enable(pc_cache *c, int32_t on);
 int32_t pc_profile_read(pc_cache *c, double ms_total[PC_N_KERNEL_CLASSES],
@@ -340,9 +342,12 @@ int32_t pc_grad_keys_finalize(pc_cache *c, float *d_k, void *stream);
  * messages).  Consecutive one-row calls of a pc_attend batch (up to 32 * 8 / g of them, g =
  * query heads per KV head, for g in {1, 2, 4, 8}) can be served as a group that reads the
  * union of their messages once per KV head instead of once per call; results are the same
- * up to rounding.  mode 0 (default): a group takes the shared walk when its calls together
- * list at least six times the tokens of the union; 1: never; 2: always when the shape
- * allows it.  Applies to PC_BF16 caches; other calls are unaffected. */
+ * up to rounding.  mode 0 (default): in a batch with longer calls a group takes the shared walk
+ * when its calls together list at least six times the tokens of the union; a batch of one-row
+ * calls alone goes whichever way is the cheapest for its lists (every call on its own, message
+ * by message for a few calls at a time, or the shared walk).  1: every call on its own; 2: the
+ * shared walk whenever the shape allows it.  Applies to PC_BF16 caches; other calls are
+ * unaffected. */
 int32_t pc_set_decode_sharing(pc_cache *c, int32_t mode);
 
 #ifdef __cplusplus

@@ -305,5 +305,5 @@ class Cache:
         self._check(lib().pc_set_key_gather(self.h, mode))
 
     def set_decode_sharing(self, mode: int = 0):
-        """0: shared walk when a group's calls overlap enough; 1: never; 2: whenever the shape allows."""
+        """0: whatever is cheapest for the lists (mixed batches: the shared walk where calls overlap enough); 1: every call on its own; 2: shared whenever the shape allows."""
         self._check(lib().pc_set_decode_sharing(self.h, mode))

@@ -12,7 +12,7 @@
 //     host's list.  One rotation of the query as it came, kept in fp32 in registers: turned by its own
 //     position first and by the message's displacement then, its upper half stood in LDS and a turn
 //     took as many multiplications and eight more LDS reads (32 calls over 410 of 512 messages, g = 8,
-//     four steps: 602 us, now 563).  A turn is still some 13 of the walk's 95 us: all waves of a
+//     four steps: 602 us, now 563).  Turns are still 12 us of a step's 140: all waves of a
 //     workgroup turn at once.  Spread over the tiles of the message before (four of sixteen pairs
 //     a unit, results in LDS) it took 669 us: a unit waits for its LDS reads in every wave, and beside
 //     the score MFMAs it does not fit the registers;
