@@ -33,6 +33,20 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     Planned own;
     Planned &P = with_tokens ? *with_tokens : own;       // (a decode step hands in the tokens that the attend's first launch appends)
     P.fixed_ws = fixed_ws; P.fixed_cap = fixed_cap;
+    P.merge_releases = c->cfg.dtype == PC_BF16;
+    // the ring slot is the merge's to release; on any way out without one, its event is
+    struct Release {
+        pc_cache *c; Planned &P; hipStream_t st;
+        ~Release() { if (P.merge_slot) { (void)pc_stage_release(c, P.merge_slot, st); P.merge_slot = nullptr; } }
+        PcMergeDone done() const
+        {
+            StageSlot *s = P.merge_slot;
+            if (!s) return PcMergeDone{};
+            if (++s->seq == 0) s->seq = 1;
+            return PcMergeDone{s->done, s->seq};
+        }
+        void launched(const PcMergeDone &d) { if (P.merge_slot) { P.merge_slot->used = true; P.merge_slot->awaited = d.value; P.merge_slot = nullptr; } }
+    } release{c, P, st};
     const int32_t rc = pc_plan_and_stage(c, calls, n_calls, true, st, P);
     if (rc != PC_OK || c->host_only) return rc;
 
@@ -62,6 +76,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         return PC_OK;
     }
     if (P.runs_bytes > 0) {
+        P.merge_slot = P.runs_slot;
         {
             ProfScope ps(c, 3, st);
             pc_launch_decode_runs_bf16(L, P.runs, P.run_starts, st);
@@ -69,12 +84,10 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         }
         {
             ProfScope ps(c, 4, st);
-            pc_launch_merge(c->cfg.dtype, (const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, 4, true, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
+            const PcMergeDone done = release.done();
+            pc_launch_merge(c->cfg.dtype, (const PcMergeRow *)(w + P.lay.merge_rows), P.n_merge_rows, 4, true, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, done, st);
             PC_HIP(c, hipGetLastError());
-        }
-        if (P.runs_slot) {                               // the ring slot is free again once the launches are done
-            PC_HIP(c, hipEventRecord(P.runs_slot->ev, st));
-            P.runs_slot->used = true;
+            release.launched(done);
         }
         return PC_OK;
     }
@@ -145,10 +158,12 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
     if (P.n_merge_rows > 0) {
         ProfScope ps(c, 4, st);
         const PcMergeRow *rows = (const PcMergeRow *)(w + P.lay.merge_rows);
-        pc_launch_merge(c->cfg.dtype, rows, P.n_merge_few, 1, false, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, st);
-        pc_launch_merge(c->cfg.dtype, rows + P.n_merge_few, P.n_merge_rows - P.n_merge_few, 4, P.n_sh_items > 0, L.part_o, L.part_ml, out, lse,
-                        c->cfg.n_q_heads, c->D, st);
+        const int few = P.n_merge_few, many = P.n_merge_rows - few;
+        const PcMergeDone done = release.done();         // (either launch comes behind what reads the slot)
+        pc_launch_merge(c->cfg.dtype, rows, few, 1, false, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, many > 0 ? PcMergeDone{} : done, st);
+        pc_launch_merge(c->cfg.dtype, rows + few, many, 4, P.n_sh_items > 0, L.part_o, L.part_ml, out, lse, c->cfg.n_q_heads, c->D, done, st);
         PC_HIP(c, hipGetLastError());
+        release.launched(done);
     }
     return PC_OK;
 }

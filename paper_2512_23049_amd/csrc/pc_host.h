@@ -11,6 +11,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <sched.h>
 #include <string>
 #include <vector>
 
@@ -22,7 +23,9 @@ struct HostMsg { int64_t slot_start; int32_t len; int32_t reserve; int32_t base_
                  int32_t next = -1; bool is_ext = false; };
 struct FreeSpan { int64_t start, size; };            // freed slots, multiples of PC_SLOT_ALIGN
 
-struct StageSlot { void *host = nullptr; size_t cap = 0; hipEvent_t ev = nullptr; bool used = false; };
+// A slot of the pinned ring.  used: what last read it ends with the event, or, if awaited is not 0, when the merge of its call has written
+// awaited to *done (pinned as well).
+struct StageSlot { void *host = nullptr; size_t cap = 0; hipEvent_t ev = nullptr; bool used = false; uint32_t *done = nullptr, seq = 0, awaited = 0; };
 
 struct ProfRec { int cls; hipEvent_t a, b; };
 
@@ -58,6 +61,7 @@ struct pc_cache {
     size_t ws_refused = SIZE_MAX;                        // a gradient's workspace the device had no room for
     void *tok_dev = nullptr; size_t tok_cap = 0;          // staged items of pc_append_tokens* / pc_reposition_batch (bytes)
     StageSlot stage[N_STAGE]; int stage_next = 0;
+    uint32_t *stage_done = nullptr;                     // what the slots' done point to
     // profiling
     bool prof = false;
     std::vector<ProfRec> prof_recs;
@@ -162,6 +166,9 @@ struct Planned {
     std::vector<Resolved> res;
     // The gradient of a bf16 batch (set backward before planning): its launches, each over a run of row blocks
     bool backward = false;
+    // A slot of the ring that the call's merge is to release, where the caller asks for it (merge_releases) and there is one: an event behind
+    // the launch that reads the slot holds up the launch after it for 2.1 us
+    bool merge_releases = false; StageSlot *merge_slot = nullptr;
     // A decode batch that goes to one launch (one_bytes > 0): nothing was staged or launched for it yet
     PcArgBlob one_blob; size_t one_bytes = 0; PcOne one{}; StageSlot *one_slot = nullptr;      // (one_slot: its lists are in the pinned ring)
     std::vector<char> recorded;                          // staged lists of a call that is recorded into a graph (see pc_recorded)
@@ -188,6 +195,7 @@ extern "C" int32_t pc_append_token_items(pc_cache *c, const std::vector<int32_t>
                                          std::vector<PcTokenItem> *defer);
 int32_t pc_ensure_ws(pc_cache *c, size_t bytes, hipStream_t st);
 int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out);
+int32_t pc_stage_release(pc_cache *c, StageSlot *s, hipStream_t st);      // what reads the slot has been enqueued on st: its event
 bool pc_recorded(hipStream_t st);
 extern "C" int32_t pc_stage_items(pc_cache *c, const void *items, size_t bytes, hipStream_t st);
 // pc_attend.hip: the address, on the current device, of the library's fixed scratch array (looked up once per device)

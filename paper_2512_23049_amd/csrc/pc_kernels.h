@@ -68,8 +68,10 @@ void pc_launch_expand_tables(const PcSegment *segs, const int32_t *seg_kvoff, in
                              int32_t *kv_slot, int32_t *kv_pos, hipStream_t st);
 
 // split_lanes: 1, or 4 for rows with many splits (their splits are shared out over four lanes)
+// done.at != null: done.value goes there (pinned host memory), as what came before this launch on the stream is done
+struct PcMergeDone { uint32_t *at = nullptr; uint32_t value = 0; };
 void pc_launch_merge(int dtype, const PcMergeRow *merge_rows, int n_merge_rows, int split_lanes, bool many, const uint16_t *part_o,
-                     const float *part_ml, void *out, float *lse, int n_q_heads, int D, hipStream_t st);
+                     const float *part_ml, void *out, float *lse, int n_q_heads, int D, const PcMergeDone &done, hipStream_t st);
 
 // fp32 caches: the work items L.items (unit0: block of 32 (row, head) columns of the KV head), partials in fp32; then the
 // rows whose tiles were split

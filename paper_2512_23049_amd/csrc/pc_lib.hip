@@ -67,7 +67,13 @@ int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out)
 {
     StageSlot &s = c->stage[c->stage_next];
     c->stage_next = (c->stage_next + 1) % N_STAGE;
-    if (s.used) PC_HIP(c, hipEventSynchronize(s.ev));
+    if (s.used && s.awaited) {
+        for (int k = 0; __atomic_load_n(s.done, __ATOMIC_ACQUIRE) != s.awaited; ++k) {
+            __builtin_ia32_pause();
+            if ((k & 1023) == 1023) sched_yield();
+        }
+    } else if (s.used) PC_HIP(c, hipEventSynchronize(s.ev));
+    s.used = false; s.awaited = 0;
     if (!s.ev) PC_HIP(c, hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
     if (bytes > s.cap) {
         if (s.host) PC_HIP(c, hipHostFree(s.host));
@@ -77,6 +83,13 @@ int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out)
         s.cap = cap;
     }
     *out = &s;
+    return PC_OK;
+}
+
+int32_t pc_stage_release(pc_cache *c, StageSlot *s, hipStream_t st)
+{
+    s->used = true; s->awaited = 0;
+    PC_HIP(c, hipEventRecord(s->ev, st));
     return PC_OK;
 }
 
@@ -139,9 +152,12 @@ int32_t pc_cache_create(const pc_config *cfg, pc_cache **out)
     c->ws_cap = (size_t)32 << 20;
     if (hipMalloc(&c->tok_dev, (size_t)1 << 16) != hipSuccess) return bail(PC_ERR_HIP);
     c->tok_cap = (size_t)1 << 16;
+    if (hipHostMalloc((void **)&c->stage_done, 64 * N_STAGE, hipHostMallocCoherent) != hipSuccess) return bail(PC_ERR_HIP);
+    std::memset(c->stage_done, 0, 64 * N_STAGE);
     for (int i = 0; i < N_STAGE; ++i) {
         if (hipHostMalloc(&c->stage[i].host, STAGE_BYTES, hipHostMallocCoherent) != hipSuccess) return bail(PC_ERR_HIP);
         c->stage[i].cap = STAGE_BYTES;
+        c->stage[i].done = c->stage_done + 16 * i;       // (a cache line each)
         if (hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming) != hipSuccess) return bail(PC_ERR_HIP);
     }
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) return bail(PC_ERR_HIP);
@@ -163,6 +179,7 @@ int32_t pc_cache_destroy(pc_cache *c)
         pc_prof_collect(c);
         for (auto e : c->ev_pool) (void)hipEventDestroy(e);
         for (auto &s : c->stage) { if (s.host) (void)hipHostFree(s.host); if (s.ev) (void)hipEventDestroy(s.ev); }
+        if (c->stage_done) (void)hipHostFree(c->stage_done);
         if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
         if (c->ev_join) (void)hipEventDestroy(c->ev_join);
         if (c->side) (void)hipStreamDestroy(c->side);

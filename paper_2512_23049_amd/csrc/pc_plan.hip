@@ -1338,8 +1338,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         PC_HIP(c, hipGetLastError());
     } else if (!in_args && !in_place) {
         PC_HIP(c, hipMemcpyAsync(P.ws, h, P.lay.h2d_bytes, hipMemcpyHostToDevice, st));
-        PC_HIP(c, hipEventRecord(slot->ev, st));
-        slot->used = true;
+        if (P.merge_releases && P.n_merge_rows > 0) P.merge_slot = slot;
+        else { const int32_t rc = pc_stage_release(c, slot, st); if (rc != PC_OK) return rc; }
     }
     {
         ProfScope ps(c, 1, st);
@@ -1368,8 +1368,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
         if (in_place) {                                  // the ring slot is free again once the plan builder is done
-            PC_HIP(c, hipEventRecord(slot->ev, st));
-            slot->used = true;
+            if (P.merge_releases && P.n_merge_rows > 0) P.merge_slot = slot;
+            else { const int32_t rc = pc_stage_release(c, slot, st); if (rc != PC_OK) return rc; }
         }
     }
     return PC_OK;
