@@ -341,7 +341,7 @@ def section_decode(cx):
                     "one query token per call; step = pc_attend",
         "value": b_logical / sec / 1e9, "unit": "GB/s (effective: logical bytes, 4096 B per call-selected token, over the step)",
         "ms_per_step": sec * 1e3, "B_logical": b_logical, "B_unique": b_unique,
-        "roofline": roofline_hbm("pc_decode_one_bf16_kernel<0>", b_logical, b_unique, k_dec, "parallel_decode"),
+        "roofline": roofline_hbm("pc_decode_runs_bf16_kernel", b_logical, b_unique, k_dec, "parallel_decode"),
         "kernels_us": {k: v["avg_us"] for k, v in kern.items()}, "ms_per_step_with_kernel_events": sec_prof * 1e3,
     }
     if cx.achievable and out["roofline"]["achieved"]:
