@@ -168,7 +168,8 @@ typedef struct {
 
 /* Batched choreographed attention (Sec. 2.4 "Parallel API Calls": a list of calls
  * that each see exactly what they list).
- *   q    device, [sum n_q, n_q_heads, head_dim], rows packed in call order, unrotated.
+ *   q    device, [sum n_q, n_q_heads, head_dim], rows packed in call order, unrotated; decode batches
+ *        go message by message (see pc_set_decode_sharing) only where it is 16-byte aligned.
  *   out  device, same shape and dtype as q.
  *   lse  device, optional fp32 [sum n_q, n_q_heads]: natural-log sum of exp(scores).
  * A row with nothing visible yields zeros and -inf.  PC_F32 caches: fp32 precision over the whole

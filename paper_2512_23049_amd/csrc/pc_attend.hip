@@ -32,7 +32,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
 {
     Planned own;
     Planned &P = with_tokens ? *with_tokens : own;       // (a decode step hands in the tokens that the attend's first launch appends)
-    P.fixed_ws = fixed_ws; P.fixed_cap = fixed_cap;
+    P.fixed_ws = fixed_ws; P.fixed_cap = fixed_cap; P.q = q;
     P.merge_releases = c->cfg.dtype == PC_BF16;
     // the ring slot is the merge's to release; on any way out without one, its event is
     struct Release {

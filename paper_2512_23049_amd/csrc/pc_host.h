@@ -164,6 +164,7 @@ struct Planned {
     size_t n_sh_pos = 0;
     int n_kg_items = 0; int64_t kg_tiles = 0;            // calls whose keys are gathered, and their tiles in all
     std::vector<Resolved> res;
+    const void *q = nullptr;                             // the caller's queries, where the way depends on their alignment
     // The gradient of a bf16 batch (set backward before planning): its launches, each over a run of row blocks
     bool backward = false;
     // A slot of the ring that the call's merge is to release, where the caller asks for it (merge_releases) and there is one: an event behind

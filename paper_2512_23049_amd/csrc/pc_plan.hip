@@ -413,6 +413,8 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
 static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost, hipStream_t st, int32_t &rc)
 {
     const int n_calls = un.n_rows, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads, per_run = std::min(PC_RUN_ROWS, 16 / c->g);
+    // (queries go to LDS by direct loads of 16 bytes, whose addresses have to be multiples of that; the other ways load them into registers)
+    if (((uintptr_t)P.q & 15) != 0) return false;
     if (per_run < 2 || un.tiles == 0 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
     order_union(un);
     // the least share of tiles, and of runs' starts and ends, with which so many waves take all of them

@@ -35,7 +35,7 @@ class Batch:
         return self.cache.append_message(self.normal(n, self.h_kv, D).data_ptr(), self.normal(n, self.h_kv, D).data_ptr(), n, reserve)
 
     def attend(self, calls, q, mode=0, step=None, static=False):
-        """(out, lse, by message): kernel class 1 runs in front of class 3 where a batch goes by message, class 3 alone on calls' own walks"""
+        """(out, lse, by message)"""
         out, lse = self.t.full_like(q, 7.0), self.t.full(q.shape[:2], 7.0, device="cuda:0")
         self.cache.set_decode_sharing(mode)
         if not static:
@@ -51,8 +51,15 @@ class Batch:
         went = None
         if not static:
             ran = self.cache.profile_read(True)
-            went = (ran["plan"][1], ran["decode"][1], ran["merge"][1]) == (1, 1, 1)
+            went = (ran["plan"][1], ran["decode"][1], ran["merge"][1]) == (1, 1, 1)      # (calls' own walks: class 3 alone; or behind the plan builder, see below)
             self.cache.profile_enable(False)
+        if mode == 0 and went:                           # three launches: neither of the other two ways' bits
+            for other in (1, 2):
+                bits = self.t.empty_like(q)
+                self.cache.set_decode_sharing(other)
+                self.cache.attend(calls, q.data_ptr(), bits.data_ptr())
+                self.t.cuda.synchronize()
+                went = went and not self.t.equal(bits, out)
         self.cache.set_decode_sharing(0)
         return out, lse, went
 
@@ -127,6 +134,25 @@ def test_steps_and_static():
         stores.append(b.arena.view(b.t.int16).cpu())
         b.cache.close()
     assert b.t.equal(stores[0], stores[1])
+
+
+@pytest.mark.parametrize("ahead", [1, 4, 8])
+def test_queries_at_any_element(ahead):
+    """Queries, and outputs, that start at any element of a larger tensor: decode by message takes them where they are on 16 bytes, another
+    way elsewhere."""
+    r = np.random.default_rng(2)
+    b = Batch(32, 8, [int(x) for x in r.integers(30, 400, 200)], [29] * 10, 3)
+    calls = spread(r, 10, 200, 70, b.own)
+    buf = b.normal(10 * 32 * D + 8)
+    q, outs = buf[ahead:][:10 * 32 * D].view(10, 32, D), b.t.full((10 * 32 * D + 9,), 7.0, dtype=b.t.bfloat16, device="cuda:0")
+    want = b.attend(calls, q.clone(), mode=1)
+    got = b.attend(calls, q)
+    assert got[2] == (ahead == 8)
+    close(got, want)
+    b.cache.attend(calls, q.data_ptr(), outs[1:].data_ptr())
+    b.t.cuda.synchronize()
+    assert b.t.equal(outs[1:-8].view(10, 32, D), got[0]) and (outs[[0] + list(range(-8, 0))] == 7.0).all()
+    b.cache.close()
 
 
 def test_against_the_oracle_and_replays():
