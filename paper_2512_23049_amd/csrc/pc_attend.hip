@@ -45,7 +45,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
             if (++s->seq == 0) s->seq = 1;
             return PcMergeDone{s->done, s->seq};
         }
-        void launched(const PcMergeDone &d) { if (P.merge_slot) { P.merge_slot->used = true; P.merge_slot->awaited = d.value; P.merge_slot = nullptr; } }
+        void launched(const PcMergeDone &d) { if (P.merge_slot) { P.merge_slot->used = true; P.merge_slot->awaited = d.value; P.merge_slot->stream = st; P.merge_slot = nullptr; } }
     } release{c, P, st};
     const int32_t rc = pc_plan_and_stage(c, calls, n_calls, true, st, P);
     if (rc != PC_OK || c->host_only) return rc;

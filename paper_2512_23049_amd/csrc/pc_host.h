@@ -7,6 +7,7 @@
 #include "pc_kernels.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -24,8 +25,8 @@ struct HostMsg { int64_t slot_start; int32_t len; int32_t reserve; int32_t base_
 struct FreeSpan { int64_t start, size; };            // freed slots, multiples of PC_SLOT_ALIGN
 
 // A slot of the pinned ring.  used: what last read it ends with the event, or, if awaited is not 0, when the merge of its call has written
-// awaited to *done (pinned as well).
-struct StageSlot { void *host = nullptr; size_t cap = 0; hipEvent_t ev = nullptr; bool used = false; uint32_t *done = nullptr, seq = 0, awaited = 0; };
+// awaited to *done (pinned as well) on that stream.
+struct StageSlot { void *host = nullptr; size_t cap = 0; hipEvent_t ev = nullptr; bool used = false; uint32_t *done = nullptr, seq = 0, awaited = 0; hipStream_t stream = nullptr; };
 
 struct ProfRec { int cls; hipEvent_t a, b; };
 

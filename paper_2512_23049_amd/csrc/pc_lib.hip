@@ -63,15 +63,45 @@ bool pc_recorded(hipStream_t st)
     return false;
 }
 
+// Waits for *at to become value.  The work that writes it may never run: every 20 ms without it state(ctx) is asked, which says 1 (at
+// work), 0 (done) or an error.  (Not more often: asking costs the stream a marker behind its last launch.)
+extern "C" int32_t pc_await_word(const uint32_t *at, uint32_t value, int32_t (*state)(void *), void *ctx)
+{
+    typedef std::chrono::steady_clock Clock;
+    auto there = [&]() { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == value; };
+    Clock::time_point asked = Clock::now();
+    for (int k = 1; !there(); ++k) {
+        __builtin_ia32_pause();
+        if ((k & 1023) != 0) continue;
+        sched_yield();
+        if (Clock::now() - asked < std::chrono::milliseconds(20)) continue;
+        const int32_t s = state(ctx);
+        if (s != 1) return there() ? PC_OK : s < 0 ? s : PC_ERR_HIP;
+        asked = Clock::now();
+    }
+    return PC_OK;
+}
+
+// state of pc_await_word for what was enqueued on a stream
+static int32_t stream_state(void *stream)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return 1;      // (a query would end the capture)
+    const hipError_t e = hipStreamQuery((hipStream_t)stream);
+    if (e == hipErrorNotReady) {
+        if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();      // (it would be taken for that of the next launch)
+        return 1;
+    }
+    return hipDeviceSynchronize() == hipSuccess ? 0 : PC_ERR_HIP;      // (the stream may be gone, or another one under its handle: whatever was enqueued)
+}
+
 int32_t pc_stage_acquire(pc_cache *c, size_t bytes, StageSlot **out)
 {
     StageSlot &s = c->stage[c->stage_next];
     c->stage_next = (c->stage_next + 1) % N_STAGE;
     if (s.used && s.awaited) {
-        for (int k = 0; __atomic_load_n(s.done, __ATOMIC_ACQUIRE) != s.awaited; ++k) {
-            __builtin_ia32_pause();
-            if ((k & 1023) == 1023) sched_yield();
-        }
+        if (pc_await_word(s.done, s.awaited, stream_state, s.stream) != PC_OK)
+            return pc_fail(c, PC_ERR_HIP, "the call whose lists lie in a staging slot has not run: %s", hipGetErrorString(hipGetLastError()));
     } else if (s.used) PC_HIP(c, hipEventSynchronize(s.ev));
     s.used = false; s.awaited = 0;
     if (!s.ev) PC_HIP(c, hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));

@@ -46,3 +46,39 @@ def test_calls_ahead_of_the_gpu(rows, sharing):
         assert torch.equal(x, y)
     assert not torch.equal(outs[0][0], outs[0][1])
     cache.close()
+
+
+def test_calls_far_ahead_of_the_gpu():
+    """The host waits for a slot for so long that it asks how the stream stands, which is busy."""
+    import time
+    import torch
+    from paper_2512_23049_amd.binding import PC_BF16, Cache
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(3)
+    k, v = (torch.randn((512, HKV, D), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    cache = Cache(HQ, HKV, D, PC_BF16, 10000.0, 2048, 4)
+    for i in range(4):
+        cache.append_message(k.data_ptr() + 2 * D * HKV * i, v.data_ptr() + 2 * D * HKV * i, 500)
+    q = torch.randn((40, HQ, D), generator=g, device="cuda:0").to(torch.bfloat16)
+    cache.set_decode_sharing(2)
+    calls = [[Call([(m, 600 * i + c) for m in range(4)], -1, 0, 1, np.asarray([9000], dtype=np.int32)) for c in range(40)] for i in range(6)]
+    outs = [[torch.empty_like(q) for _ in calls] for _ in range(2)]
+    for c, out in zip(calls, outs[0]):
+        cache.attend(c, q.data_ptr(), out.data_ptr())
+        torch.cuda.synchronize()
+    a = torch.randn((8192, 8192), generator=g, device="cuda:0", dtype=torch.float64)
+    a @ a
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        start = time.perf_counter()
+        for _ in range(6):
+            a @ a                                        # more than 100 ms
+        for c, out in zip(calls, outs[1]):
+            cache.attend(c, q.data_ptr(), out.data_ptr(), 0, stream.cuda_stream)
+        waited = time.perf_counter() - start
+    torch.cuda.synchronize()
+    assert waited > 0.04, waited
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
+    cache.close()

@@ -440,3 +440,32 @@ def test_random_walk_over_growing_freed_swapped_and_moved_messages(pc):
         starts, got_self, n_kv = c.resolve_call(Call(sel, m_self, s_self, 1, None))
         assert starts == [s for _, s in want_sel] and got_self == want_self
         assert n_kv == sum(lengths[m] for m, _ in sel) + lengths[m_self]
+
+
+def test_waiting_for_a_staging_slot_ends(pc):
+    """The wait for the word with which a call's merge releases its slot of the pinned ring: it returns when the word is there, and with an
+    error when the work that was to write it has failed, or is done and has not written it."""
+    lib = ctypes.CDLL(pc.binding.LIB_PATH)
+    state_fn = ctypes.CFUNCTYPE(ctypes.c_int32, ctypes.c_void_p)
+    lib.pc_await_word.restype = ctypes.c_int32
+    lib.pc_await_word.argtypes = [ctypes.POINTER(ctypes.c_uint32), ctypes.c_uint32, state_fn, ctypes.c_void_p]
+    word, asked = ctypes.c_uint32(6), []
+
+    def state(answers, write_at=None):
+        def f(_):
+            asked.append(1)
+            if len(asked) == write_at:
+                word.value = 7
+            return answers[min(len(asked), len(answers)) - 1]
+        return state_fn(f)
+
+    ok = pc.binding.PC_OK
+    assert lib.pc_await_word(word, 6, state([-5]), None) == ok and not asked                     # there already
+    for answers, write_at, want, calls in (([1, 1, -5], None, -5, 3),                            # an error ends the wait
+                                           ([1, 0], None, -5, 2),                                # done, and nothing was written
+                                           ([1, 0], 2, ok, 2),                                   # done, and written in between
+                                           ([1, 1, 1, 1], 2, ok, 2)):                            # written while at work
+        word.value = 6
+        asked.clear()
+        assert lib.pc_await_word(word, 7, state(answers, write_at), None) == want
+        assert len(asked) == calls
