@@ -206,6 +206,8 @@ constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS
 constexpr double SHARE_LEAN = 0.8;
 constexpr double RUN_START = 1.5;                        // a run's start and end, in passes
 constexpr double SHARE_MIN = 6.0;
+// entries of a group's rotation table, a row and a message of the union each: 512 bytes, 256 MB in all
+constexpr size_t UNION_ENTRIES = (size_t)1 << 19;
 // rows with more splits than this are merged by four lanes per 8 dimensions
 constexpr int MERGE_MANY_SPLITS = 8;
 
@@ -326,6 +328,108 @@ static DecodeCost decode_cost(const pc_cache *c, const Union &un)
 
 static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost, hipStream_t st, int32_t &rc);
 
+// the splits of a group's union: as many as fill the chip together
+static int shared_splits(const pc_cache *c, size_t n_groups, int T)
+{
+    const int64_t workgroups = (int64_t)n_groups * c->cfg.n_kv_heads;
+    const int ns = std::max(1, std::min(MAX_SPLITS, c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
+                                                                                  : (int)std::min<int64_t>((256 + workgroups - 1) / workgroups, std::max(1, T / 8))));
+    const int chunk = std::max(1, (T + ns - 1) / ns);
+    return std::max(1, (T + chunk - 1) / chunk);
+}
+
+// the calls of a union, the first of them `first`, as a group of the shared walk
+static void add_group(SharedPlan &sp, Union &un, int first, int row0)
+{
+    order_union(un);
+    const int n_rows = un.n_rows;
+    PcShGroup gr{};
+    gr.seg_off = (int32_t)sp.segs.size(); gr.n_seg = (int32_t)un.segs.size();
+    gr.row0 = row0; gr.n_rows = n_rows; gr.rot_off = (int32_t)sp.pos.size();
+    gr.n_splits = 1; gr.part_off = 0;
+    int32_t tile_off = 0;
+    sp.segs.reserve(sp.segs.size() + un.segs.size());
+    sp.pos.reserve(sp.pos.size() + un.pos.size());
+    for (int32_t k : un.order) {
+        const Union::Seg &u = un.segs[(size_t)k];
+        PcShSeg sg{};
+        sg.slot_start = (int32_t)u.slot; sg.len = u.len; sg.tile_off = tile_off;
+        std::copy(u.vis, u.vis + 8, sg.vis);
+        tile_off += (u.len + PC_TILE - 1) / PC_TILE;
+        sp.segs.push_back(sg);
+        const int32_t *row = un.pos.data() + (size_t)k * (size_t)n_rows;
+        sp.pos.insert(sp.pos.end(), row, row + n_rows);
+    }
+    gr.n_tiles = tile_off;
+    sp.groups.push_back(gr);
+    for (int k = 0; k < n_rows; ++k) sp.in_shared[(size_t)(first + k)] = 1;
+}
+
+static void drop_groups(SharedPlan &sp)
+{
+    std::fill(sp.in_shared.begin(), sp.in_shared.end(), 0);
+    sp.groups.clear(); sp.segs.clear(); sp.pos.clear();
+}
+
+// The table of a group has an entry for every row and message of the union, listed or not, so that a batch the calls' own walks have room
+// for may not fit: a batch of groups alone fits the fixed workspace.
+static bool groups_fit(const pc_cache *c, const SharedPlan &sp)
+{
+    size_t rows = 0, items = 0;
+    int64_t part_rows = 0;
+    for (const PcShGroup &gr : sp.groups) {
+        const int ns = shared_splits(c, sp.groups.size(), gr.n_tiles);
+        rows += (size_t)gr.n_rows; items += (size_t)ns;
+        if (ns > 1) part_rows += (int64_t)ns * gr.n_rows;
+    }
+    const PlanLayout l = make_layout((int)rows, (int)rows, 0, 0, 0, 0, part_rows, 0, c->cfg.n_q_heads, c->D, sp.groups.size(), sp.segs.size(), items, sp.pos.size(),
+                                     0, 0, c->cfg.n_kv_heads, 0, 0, 0, 0, 0, sizeof(uint16_t), rows);
+    return l.total <= PC_STATIC_WS_BYTES && l.h2d_bytes <= STAGE_BYTES;
+}
+
+enum class Way { OWN, BY_MESSAGE, SHARED, BY_RATIO };
+
+// The way of a batch of nothing but one-row calls (the shared walk's groups, or the runs, are planned when this returns); BY_RATIO: as in a mixed batch.
+static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, Union &un, hipStream_t st, int32_t &rc)
+{
+    std::vector<Resolved> &res = P.res;
+    const int n_calls = (int)res.size();
+    const double per_cu = c->cfg.n_kv_heads / 256.0;
+    size_t entries = 0;
+    int64_t all_tiles = 0;
+    for (const Resolved &r : res) { entries += r.sel.size(); all_tiles += r.tiles; }
+    // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
+    if (OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return Way::OWN;
+    const int n_groups = (n_calls + rows_max - 1) / rows_max;
+    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles, lean = 1;
+    // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
+    // step, took 104 us and then 128)
+    const bool whole = n_calls <= 256 && (n_groups == 1 || entries <= 2048);
+    if (whole) {
+        if (!collect_union(c, res, 0, n_calls, UNION_ENTRIES / (size_t)n_calls, un)) return n_groups == 1 ? Way::OWN : Way::BY_RATIO;
+        const DecodeCost cost = decode_cost(c, un);
+        if ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles) lean = SHARE_LEAN;
+        const double shared = lean * (SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)n_groups);
+        own = cost.own;
+        if (!c->host_only && cost.by_message < 0.95 * std::min(own, shared) && plan_runs(c, P, un, cost, st, rc)) return Way::BY_MESSAGE;
+        if (rc != PC_OK || own < SHARED_FIXED) return Way::OWN;
+    }
+    double shared = SHARED_FIXED;
+    bool as_by_ratio = n_calls <= rows_max || n_calls % rows_max == 0;      // the same groups, and every one of them shares enough
+    for (int i = 0; i < n_calls;) {
+        // (groups of a size: two calls behind a full group would have walks, and launches, of their own)
+        const int left = (n_calls - i + rows_max - 1) / rows_max, n_rows = (n_calls - i + left - 1) / left;
+        if (!(whole && n_rows == n_calls) && !collect_union(c, res, i, n_rows, UNION_ENTRIES / (size_t)n_rows, un)) return Way::BY_RATIO;
+        if (un.tiles == 0 || un.tiles >= INT32_MAX / 2) return Way::BY_RATIO;
+        as_by_ratio = as_by_ratio && n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles;
+        shared += SHARED_TILE * per_cu * (double)un.tiles;
+        if (own < lean * shared) return Way::OWN;
+        add_group(sp, un, i, i);
+        i += n_rows;
+    }
+    return as_by_ratio || groups_fit(c, sp) ? Way::SHARED : Way::BY_RATIO;
+}
+
 // rc != PC_OK: an error.  True: the whole batch goes by message (P.runs_*), and nothing else is to be planned
 static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, int g, SharedPlan &sp, hipStream_t st, int32_t &rc)
 {
@@ -335,75 +439,26 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
     if (c->cfg.max_position > INT32_MAX / 3) return false;            // a position less a start plus a stored base is listed in 32 bits
     const int rows_max = 32 * (8 / g);
-    const double per_cu = c->cfg.n_kv_heads / 256.0;
-    static thread_local Union un;                        // (at most half a million entries; kept: fresh pages for them cost more than filling them)
-    // a batch of one-row calls alone goes the cheapest way
+    static thread_local Union un;                        // (kept: fresh pages for it cost more than filling them)
     bool alone = c->decode_sharing == 0 && n_calls > 1 && c->decode_tiles_per_split == 0;
-    size_t entries = 0;
-    int64_t all_tiles = 0;
-    for (const Resolved &r : res) { alone = alone && r.n_q == 1; entries += r.sel.size(); all_tiles += r.tiles; }
-    // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
-    if (alone && OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return false;
-    // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
-    // step, took 104 us and then 128)
-    const bool whole = alone && n_calls <= 256 && (n_calls <= rows_max || entries <= 2048) && collect_union(c, res, 0, n_calls, ((size_t)1 << 19) / (size_t)n_calls, un);
-    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles, lean = 1;
-    if (whole) {
-        const DecodeCost cost = decode_cost(c, un);
-        if ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles) lean = SHARE_LEAN;
-        const double shared = lean * (SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)((n_calls + rows_max - 1) / rows_max));
-        own = cost.own;
-        if (!c->host_only && cost.by_message < 0.95 * std::min(own, shared) && plan_runs(c, P, un, cost, st, rc)) return true;
-        if (rc != PC_OK) return false;
-        if (own < SHARED_FIXED) return false;
+    for (const Resolved &r : res) alone = alone && r.n_q == 1;
+    if (alone) {
+        const Way way = cheapest_way(c, P, rows_max, sp, un, st, rc);
+        if (way != Way::SHARED) drop_groups(sp);
+        if (way != Way::BY_RATIO) return way == Way::BY_MESSAGE;
     }
-    double shared = SHARED_FIXED;                        // with what does not take the walk beside it
     for (int i = 0; i < n_calls;) {
         if (res[i].n_q != 1) { ++i; continue; }
         int j = i;
-        while (j < n_calls && res[j].n_q == 1 && (alone || j - i < rows_max)) ++j;
-        if (j - i > rows_max) {                          // groups of a size: two calls behind a full group would have walks, and launches, of their own
-            const int n_groups = (n_calls - i + rows_max - 1) / rows_max;
-            j = i + (n_calls - i + n_groups - 1) / n_groups;
-        }
+        while (j < n_calls && res[j].n_q == 1 && j - i < rows_max) ++j;
         const int n_rows = j - i;
         // (the union holds each call's list: calls that list less than SHARE_MIN times the longest list cannot take this walk)
         int64_t sum_tiles = 0, longest = 0;
         for (int r = i; r < j; ++r) { sum_tiles += res[(size_t)r].tiles; longest = std::max<int64_t>(longest, res[(size_t)r].tiles); }
-        if (c->decode_sharing != 2 && !alone && (double)sum_tiles < SHARE_MIN * (double)longest) { i = j; continue; }
-        // (the rotation table has one 512-byte row per (message, row) pair: keep it under 256 MB)
-        const bool fits = (whole && n_rows == n_calls) || collect_union(c, res, i, n_rows, ((size_t)1 << 19) / (size_t)n_rows, un);
-        bool take = fits && un.tiles > 0 && un.tiles < INT32_MAX / 2;
-        if (alone) shared += take ? SHARED_TILE * per_cu * (double)un.tiles : OWN_FIXED + per_cu * TILE_AGAIN * (double)sum_tiles;
-        else take = take && (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles));
-        if (alone && own < lean * shared) {                     // the batch's calls walk on their own after all
-            sp.in_shared.assign((size_t)n_calls, 0);
-            sp.groups.clear(); sp.segs.clear(); sp.pos.clear();
-            return false;
-        }
-        if (take) {
-            order_union(un);
-            PcShGroup gr{};
-            gr.seg_off = (int32_t)sp.segs.size(); gr.n_seg = (int32_t)un.segs.size();
-            gr.row0 = q_off[(size_t)i]; gr.n_rows = n_rows; gr.rot_off = (int32_t)sp.pos.size();
-            gr.n_splits = 1; gr.part_off = 0;
-            int32_t tile_off = 0;
-            sp.segs.reserve(sp.segs.size() + un.segs.size());
-            sp.pos.reserve(sp.pos.size() + un.pos.size());
-            for (int32_t k : un.order) {
-                const Union::Seg &u = un.segs[(size_t)k];
-                PcShSeg sg{};
-                sg.slot_start = (int32_t)u.slot; sg.len = u.len; sg.tile_off = tile_off;
-                std::copy(u.vis, u.vis + 8, sg.vis);
-                tile_off += (u.len + PC_TILE - 1) / PC_TILE;
-                sp.segs.push_back(sg);
-                const int32_t *row = un.pos.data() + (size_t)k * (size_t)n_rows;
-                sp.pos.insert(sp.pos.end(), row, row + n_rows);
-            }
-            gr.n_tiles = tile_off;
-            sp.groups.push_back(gr);
-            for (int k = i; k < j; ++k) sp.in_shared[(size_t)k] = 1;
-        }
+        if ((c->decode_sharing == 2 || (double)sum_tiles >= SHARE_MIN * (double)longest) &&
+            collect_union(c, res, i, n_rows, UNION_ENTRIES / (size_t)n_rows, un) && un.tiles > 0 && un.tiles < INT32_MAX / 2 &&
+            (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles)))
+            add_group(sp, un, i, q_off[(size_t)i]);
         i = j;
     }
     return false;
@@ -1145,12 +1200,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         for (size_t gi = 0; gi < sp.groups.size(); ++gi) {
             PcShGroup &gr = sp.groups[gi];
             const int T = gr.n_tiles;
-            int ns = c->decode_tiles_per_split > 0 ? (T + c->decode_tiles_per_split - 1) / c->decode_tiles_per_split
-                                                   : (int)std::min<int64_t>((256 + (int64_t)sp.groups.size() * H_kv - 1) / ((int64_t)sp.groups.size() * H_kv),
-                                                                            std::max(1, T / 8));
-            ns = std::max(1, std::min(MAX_SPLITS, ns));
-            const int chunk = std::max(1, (T + ns - 1) / ns);
-            ns = std::max(1, (T + chunk - 1) / chunk);
+            const int ns = shared_splits(c, sp.groups.size(), T), chunk = std::max(1, (T + ns - 1) / ns);
             gr.n_splits = ns;
             if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += (int64_t)ns * gr.n_rows; }
             int seg = 0;                                     // the message that owns a split's first tile (splits ascend)

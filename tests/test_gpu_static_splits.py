@@ -46,3 +46,33 @@ def test_bits_of_pc_attend(n_calls, n_q, parent):
         o, _ = orc.attend_call(ks, vs, c.sel, c.self_msg, c.self_start, n_q, None, q[n_q * i:n_q * (i + 1)], theta, rows=some)
         d = np.abs(got[[n_q * i + r for r in some]] - o)
         assert d.max() <= 2e-2 and d.mean() <= 1e-3, (i, d.max(), d.mean())
+
+
+# (heads, calls, messages, listed by each; the shared walk): one group, and two of 30 calls, whose tables pass the workspace; one that fits
+@pytest.mark.parametrize("h_q,n_calls,pool,n_sel,shared", [(32, 32, 2200, 240, False), (32, 16, 4400, 900, False), (64, 60, 1500, 200, False), (32, 32, 1500, 300, True)])
+def test_tables_beyond_the_workspace(h_q, n_calls, pool, n_sel, shared):
+    """Decode batches that the shared walk would serve at the least price, with a rotation for every row and message of the union, of which
+    each row lists few: where those pass the fixed workspace, both entry points take the calls' own walks."""
+    import torch
+    from paper_2512_23049_amd import binding
+    h_kv, D, L = 8, 128, 20
+    r, g = np.random.default_rng(n_calls), torch.Generator(device="cuda:0").manual_seed(pool)
+    k, v = (torch.randn((pool * L, h_kv, D), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, 10000.0, pool * 32, pool)
+    at = [2 * D * h_kv * L * i for i in range(pool)]
+    for i in range(0, pool, 100):
+        cache.append_messages([k.data_ptr() + a for a in at[i:i + 100]], [v.data_ptr() + a for a in at[i:i + 100]], [L] * 100)
+    calls = [Call([(int(m), int(r.integers(0, 9000))) for m in r.permutation(pool)[:n_sel]], -1, 9000 + i, 1, None) for i in range(n_calls)]
+    q = torch.randn((n_calls, h_q, D), generator=g, device="cuda:0").to(torch.bfloat16)
+
+    def run(entry, sharing=0):
+        out, lse = torch.full_like(q, 7.0), torch.full((n_calls, h_q), 7.0, device="cuda:0")
+        cache.set_decode_sharing(sharing)
+        entry(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        torch.cuda.synchronize()
+        return out.view(torch.int16), lse
+    got, static, own = run(cache.attend), run(cache.attend_static), run(cache.attend, 1)
+    assert torch.equal(got[0], static[0]) and torch.equal(got[1], static[1])
+    assert torch.equal(got[0], own[0]) != shared
+    assert (got[0].view(torch.bfloat16).float() - own[0].view(torch.bfloat16).float()).norm() <= 1e-2 * own[0].view(torch.bfloat16).float().norm()
+    cache.close()
