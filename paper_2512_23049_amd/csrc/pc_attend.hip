@@ -133,7 +133,7 @@ static int32_t attend_impl(pc_cache *c, const pc_call *calls, int32_t n_calls, c
         S.segs = (const PcShSeg *)(w + P.lay.sh_segs);
         S.items = (const PcShItem *)(w + P.lay.sh_items);
         S.rot = (const float2 *)(w + P.lay.sh_rot);
-        pc_launch_decode_shared_bf16(L, S, P.n_sh_items, st_dec);
+        pc_launch_decode_shared_bf16(L, S, P.n_sh_items, P.sh_wide, st_dec);
         PC_HIP(c, hipGetLastError());
     }
     if (fork) PC_HIP(c, hipEventRecord(c->ev_join, c->side));

@@ -161,7 +161,7 @@ struct Planned {
     PlanLayout lay;
     int n_calls = 0, total_q = 0, total_seg = 0, n_dec = 0, n_pre = 0, n_pre_pk = 0, pre_waves = 4;
     int n_merge_rows = 0, n_merge_few = 0;               // rows to merge; the first n_merge_few have few splits
-    int n_sh_items = 0;
+    int n_sh_items = 0; bool sh_wide = false;
     size_t n_sh_pos = 0;
     int n_kg_items = 0; int64_t kg_tiles = 0;            // calls whose keys are gathered, and their tiles in all
     std::vector<Resolved> res;

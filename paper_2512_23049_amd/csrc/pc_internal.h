@@ -233,7 +233,7 @@ struct PcShGroup {
     int32_t row0;             // packed query row of the group's first call
     int32_t n_rows;           // calls in the group (<= 32 * 8 / g)
     int32_t rot_off;          // entry (message s, row r) of the rotation table is rot_off + s * n_rows + r
-    int32_t part_off;         // first partial row when n_splits > 1 (split s is n_rows rows further)
+    int32_t part_off;         // first partial row when n_splits > 1 (split s is n_rows rows further; twice that if the rows are fp32)
     int32_t n_splits;
 };
 

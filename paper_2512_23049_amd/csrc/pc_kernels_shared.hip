@@ -29,6 +29,8 @@
 // layout) are those of the prefill kernel, so that split partials and the merge are shared.
 #include "pc_mfma_common.h"
 
+#include <type_traits>
+
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
 
 namespace {
@@ -72,7 +74,8 @@ __device__ __forceinline__ void sh_wait_landed()
 // TAB: a wave's part of a message's rotation table, in KB (32 / g rows of 512 bytes), fetched into LDS while the message before is
 // walked; 0: the turn reads it from memory.  32 calls over 150 of 200 messages, us a pass of four steps, from LDS / from memory: g = 8
 // 304 / 306, g = 4 274 / 276, g = 2 (whose wave has 16 rows) 271 / 266, so g >= 4 takes LDS.
-template <int TAB>
+// WIDE: partial outputs in fp32, a row takes two units of its group's part_off (by a flag instead, the walk's schedule changed: g = 4 253 / 256 us).
+template <int TAB, bool WIDE>
 __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch L, PcShLaunch S)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char s_k[SH_RING][8192];
@@ -353,17 +356,22 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
         if (L.lse && hh == 0)
             L.lse[(int64_t)Rg * L.n_q_heads + h] = (l > 0.f) ? (m_ref + log2f(l)) * 0.6931471805599453f : -INFINITY;
     } else {
-        const int64_t pr = (int64_t)gr.part_off + (int64_t)item.split * gr.n_rows + row;
-        uint16_t *o = L.part_o + (pr * L.n_q_heads + h) * PC_D;
+        const int64_t pr = (int64_t)gr.part_off + (((int64_t)item.split * gr.n_rows + row) << WIDE);
+        uint16_t *o = L.part_o + (pr * L.n_q_heads + ((int64_t)h << WIDE)) * PC_D;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int d = 32 * db + 8 * q4 + 4 * hh;
-                uint2 w;
-                w.x = pack_f16(acc[db][4 * q4] * inv, acc[db][4 * q4 + 1] * inv);
-                w.y = pack_f16(acc[db][4 * q4 + 2] * inv, acc[db][4 * q4 + 3] * inv);
-                *reinterpret_cast<uint2 *>(o + d) = w;
+                if constexpr (WIDE) {
+                    *reinterpret_cast<float4 *>(reinterpret_cast<float *>(o) + d) =
+                        make_float4(acc[db][4 * q4] * inv, acc[db][4 * q4 + 1] * inv, acc[db][4 * q4 + 2] * inv, acc[db][4 * q4 + 3] * inv);
+                } else {
+                    uint2 w;
+                    w.x = pack_f16(acc[db][4 * q4] * inv, acc[db][4 * q4 + 1] * inv);
+                    w.y = pack_f16(acc[db][4 * q4 + 2] * inv, acc[db][4 * q4 + 3] * inv);
+                    *reinterpret_cast<uint2 *>(o + d) = w;
+                }
             }
         if (hh == 0) {
             L.part_ml[(pr * L.n_q_heads + h) * 2] = (l > 0.f) ? m_ref : -INFINITY;
@@ -372,13 +380,18 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
     }
 }
 
-void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, hipStream_t st)
+void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, bool wide, hipStream_t st)
 {
     if (n_items <= 0) return;
     dim3 grid((unsigned)n_items * L.n_kv_heads);
-    switch (L.n_q_heads / L.n_kv_heads) {
-    case 8: pc_decode_shared_bf16_kernel<2><<<grid, 512, 0, st>>>(L, S); break;
-    case 4: pc_decode_shared_bf16_kernel<4><<<grid, 512, 0, st>>>(L, S); break;
-    default: pc_decode_shared_bf16_kernel<0><<<grid, 512, 0, st>>>(L, S);
-    }
+    auto launch = [&](auto is_wide) {
+        constexpr bool W = decltype(is_wide)::value;
+        switch (L.n_q_heads / L.n_kv_heads) {
+        case 8: pc_decode_shared_bf16_kernel<2, W><<<grid, 512, 0, st>>>(L, S); break;
+        case 4: pc_decode_shared_bf16_kernel<4, W><<<grid, 512, 0, st>>>(L, S); break;
+        default: pc_decode_shared_bf16_kernel<0, W><<<grid, 512, 0, st>>>(L, S);
+        }
+    };
+    if (wide) launch(std::true_type{});
+    else launch(std::false_type{});
 }

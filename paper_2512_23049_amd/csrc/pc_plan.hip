@@ -185,6 +185,7 @@ struct SharedPlan {
     std::vector<PcShGroup> groups;
     std::vector<PcShSeg> segs;
     std::vector<PcShItem> items;
+    bool wide = false;                           // partial outputs in fp32
     std::vector<int32_t> pos;                    // rotation positions, q_pos - start + stored base, PC_SH_ABSENT where a row does not list the message
 };
 
@@ -368,7 +369,7 @@ static void add_group(SharedPlan &sp, Union &un, int first, int row0)
 static void drop_groups(SharedPlan &sp)
 {
     std::fill(sp.in_shared.begin(), sp.in_shared.end(), 0);
-    sp.groups.clear(); sp.segs.clear(); sp.pos.clear();
+    sp.groups.clear(); sp.segs.clear(); sp.pos.clear(); sp.wide = false;
 }
 
 // The table of a group has an entry for every row and message of the union, listed or not, so that a batch the calls' own walks have room
@@ -380,7 +381,7 @@ static bool groups_fit(const pc_cache *c, const SharedPlan &sp)
     for (const PcShGroup &gr : sp.groups) {
         const int ns = shared_splits(c, sp.groups.size(), gr.n_tiles);
         rows += (size_t)gr.n_rows; items += (size_t)ns;
-        if (ns > 1) part_rows += (int64_t)ns * gr.n_rows;
+        if (ns > 1) part_rows += ((int64_t)ns * gr.n_rows) << sp.wide;
     }
     const PlanLayout l = make_layout((int)rows, (int)rows, 0, 0, 0, 0, part_rows, 0, c->cfg.n_q_heads, c->D, sp.groups.size(), sp.segs.size(), items, sp.pos.size(),
                                      0, 0, c->cfg.n_kv_heads, 0, 0, 0, 0, 0, sizeof(uint16_t), rows);
@@ -415,7 +416,9 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
         if (rc != PC_OK || own < SHARED_FIXED) return Way::OWN;
     }
     double shared = SHARED_FIXED;
-    bool as_by_ratio = n_calls <= rows_max || n_calls % rows_max == 0;      // the same groups, and every one of them shares enough
+    // Where the ratio alone would have formed other groups, or not have given one of them this walk, partial outputs stay in fp32, as those of the
+    // calls' own walks do (6 calls over 300 messages of 5 tiles, each listed by 5 of them, 8 heads a KV head: 118 us a step).
+    bool as_by_ratio = n_calls <= rows_max || n_calls % rows_max == 0;
     for (int i = 0; i < n_calls;) {
         // (groups of a size: two calls behind a full group would have walks, and launches, of their own)
         const int left = (n_calls - i + rows_max - 1) / rows_max, n_rows = (n_calls - i + left - 1) / left;
@@ -427,6 +430,7 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
         add_group(sp, un, i, i);
         i += n_rows;
     }
+    sp.wide = !as_by_ratio;
     return as_by_ratio || groups_fit(c, sp) ? Way::SHARED : Way::BY_RATIO;
 }
 
@@ -1023,7 +1027,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     static thread_local SharedPlan kept_plan;
     SharedPlan &sp = kept_plan;
     sp.in_shared.assign((size_t)n_calls, 0);
-    sp.groups.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear();
+    sp.groups.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear(); sp.wide = false;
     if (want_items && bf16) {
         std::vector<int> q_offs((size_t)n_calls);
         for (int i = 0, o = 0; i < n_calls; ++i) { q_offs[(size_t)i] = o; o += P.res[(size_t)i].n_q; }
@@ -1202,7 +1206,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             const int T = gr.n_tiles;
             const int ns = shared_splits(c, sp.groups.size(), T), chunk = std::max(1, (T + ns - 1) / ns);
             gr.n_splits = ns;
-            if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += (int64_t)ns * gr.n_rows; }
+            if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += ((int64_t)ns * gr.n_rows) << sp.wide; }
             int seg = 0;                                     // the message that owns a split's first tile (splits ascend)
             for (int sidx = 0; sidx < ns; ++sidx) {
                 const int t0 = sidx * chunk;
@@ -1264,7 +1268,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 else n_pre += (size_t)(ns = prefill_splits(r.tiles, false)) * (size_t)pre_groups_of(r);
                 if (ns > 1) { rows += (int64_t)ns * r.n_q; n_merge += (size_t)r.n_q; }
             }
-            for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) { rows += (int64_t)gr.n_splits * gr.n_rows; n_merge += (size_t)gr.n_rows; }
+            for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) { rows += ((int64_t)gr.n_splits * gr.n_rows) << sp.wide; n_merge += (size_t)gr.n_rows; }
             const PlanLayout plain = layout_of(n_dec, n_pre, rows, n_merge, 0);
             const bool refused = P.fixed_ws && (plain.total > P.fixed_cap || plain.h2d_bytes > c->stage[c->stage_next].cap);
             if (refused) plan_items(false, INT64_MAX);
@@ -1307,7 +1311,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-    P.n_sh_items = (int)sp.items.size(); P.n_sh_pos = sp.pos.size();
+    P.n_sh_items = (int)sp.items.size(); P.sh_wide = sp.wide; P.n_sh_pos = sp.pos.size();
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
@@ -1360,7 +1364,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             for (const PcMergeRow &mr : tail_rows) hm[P.n_merge_rows++] = mr;
         for (const PcShGroup &gr : sp.groups)
             if (wanted(gr.n_splits))
-                for (int q = 0; q < gr.n_rows; ++q) hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + q, gr.n_splits, gr.n_rows};
+                for (int q = 0; q < gr.n_rows; ++q)
+                    hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + (q << sp.wide), gr.n_splits | (sp.wide ? PC_MERGE_WIDE : 0), gr.n_rows};
         if (pass == 0) P.n_merge_few = P.n_merge_rows;
     }
     if (!dec.empty()) std::memcpy(h + P.lay.items_dec, dec.data(), sizeof(PcItem) * dec.size());

@@ -159,3 +159,38 @@ def test_union_as_long_as_its_table_and_longer(hip, per_row):
     assert float(d.max()) <= 2e-2 and float(d.mean()) <= 1e-3
     if per_row == 9:
         assert not d.any() and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("n_calls,n_msgs,n_sel", [(6, 300, 250), (34, 60, 50)], ids=["less than six times the union", "two groups of 17"])
+def test_partial_outputs_of_batches_that_go_there_by_price(n_calls, n_msgs, n_sel):
+    """One-row calls that take the shared walk because it is the cheapest way, where the ratio of their lists to the union, in groups of 32,
+    would leave them (or the last two) to walks of their own, whose partial outputs are fp32: values beyond the largest fp16
+    number, and below the least, come out as from there."""
+    import torch
+    from paper_2512_23049_amd import binding
+    h_q, h_kv, D, L = 64, 8, 128, 150
+    r, g = np.random.default_rng(1), torch.Generator(device="cuda:0").manual_seed(1)
+    k = torch.randn((n_msgs * L, h_kv, D), generator=g, device="cuda:0").to(torch.bfloat16)
+    q = torch.randn((n_calls, h_q, D), generator=g, device="cuda:0").to(torch.bfloat16)
+    calls = [Call([(int(m), int(r.integers(0, 40000))) for m in r.permutation(n_msgs)[:n_sel]], -1, 40000 + i, 1, None) for i in range(n_calls)]
+    for factor in (2.0 ** 30, 2.0 ** -40):
+        v = (torch.randn((n_msgs * L, h_kv, D), generator=g, device="cuda:0") * factor).to(torch.bfloat16)
+        cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, 10000.0, n_msgs * 160, n_msgs)
+        for m in range(n_msgs):
+            cache.append_message(k[m * L:].data_ptr(), v[m * L:].data_ptr(), L)
+        res = []
+        for mode in (0, 1):
+            out, lse = torch.full_like(q, 7.0), torch.full((n_calls, h_q), 7.0, device="cuda:0")
+            cache.set_decode_sharing(mode)
+            cache.profile_enable(True)
+            cache.profile_read(True)
+            cache.attend(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+            torch.cuda.synchronize()
+            ran = cache.profile_read(True)
+            res.append((out.double() / factor, lse, (ran["plan"][1], ran["decode"][1], ran["merge"][1])))
+        cache.close()
+        (got, got_lse, ran), (want, want_lse, _) = res
+        assert ran == (1, 1, 1)
+        assert got.isfinite().all() and (got_lse - want_lse).abs().max() <= 2e-2
+        # rounded queries and probabilities on both sides (4e-3 between two walks), which one with sixteen bits less exponent is far from
+        assert ((got - want).norm() / want.norm()).item() <= 1e-2
