@@ -347,7 +347,8 @@ int32_t pc_grad_keys_finalize(pc_cache *c, float *d_k, void *stream);
  * when its calls together list at least six times the tokens of the union; a batch of one-row
  * calls alone goes whichever way is the cheapest for its lists (every call on its own, message
  * by message for a few calls at a time, or the shared walk).  1: every call on its own; 2: the
- * shared walk whenever the shape allows it.  Applies to PC_BF16 caches; other calls are
+ * shared walk whenever the shape allows it.  (Calls whose query position, less a message's start,
+ * plus the position its keys are stored at does not fit 32 bits walk on their own.)  Applies to PC_BF16 caches; other calls are
  * unaffected. */
 int32_t pc_set_decode_sharing(pc_cache *c, int32_t mode);
 

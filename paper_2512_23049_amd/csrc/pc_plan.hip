@@ -222,13 +222,18 @@ struct Union {
     int64_t call_tiles = 0, tiles = 0;
 };
 
-// (false: more messages than segs_max.  Raw pointers, one pass: the lists of long calls are collected on every step of a decode loop)
+// (false: more messages than segs_max, or a position that 32 bits do not hold.  Raw pointers, one pass: the lists of long calls are collected on every step of a decode loop)
 static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_rows, size_t segs_max, Union &un)
 {
     const HostMsg *msgs = c->msgs.data();
     std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> seg, for repeats within a call
     un.segs.clear(); un.pos.clear();
     un.n_rows = n_rows; un.call_tiles = 0;
+    bool far = false;
+    auto as_listed = [&](int64_t p) {                    // (INT32_MIN is PC_SH_ABSENT)
+        far |= p < -INT32_MAX || p > INT32_MAX;
+        return (int32_t)p;
+    };
     const uint32_t epoch = new_marks(c);                 // value: the message's place in segs
     pc_cache::Mark *marks = c->marks.data();
     Union::Seg *segs = un.segs.data();
@@ -256,7 +261,7 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
         // the union is sorted once, below: a call's own list is needed in slot order only where it names a message
         // twice (its occurrences are told apart by their starts)
         int32_t self_occ = 0;
-        const int32_t q0 = rc.q_pos[0];
+        const int64_t q0 = rc.q_pos[0];
         const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
         uint32_t twice = 0;
         for (const int2 *e = rc.sel.data(), *end = e + rc.sel.size(); e < end; ++e) {
@@ -267,11 +272,11 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
             uint32_t &vis = segs[u].vis[word];
             twice |= vis & bit;
             vis |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = q0 - e->y + hm.base_pos;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - e->y + hm.base_pos);
         }
-        auto enter = [&](int32_t u, int32_t p) {
+        auto enter = [&](int32_t u, int32_t start, int32_t base) {
             segs[u].vis[word] |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = q0 - p;
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - start + base);
         };
         if (twice) {
             for (size_t u = 0; u < un.segs.size(); ++u) {             // the row again, from nothing
@@ -283,12 +288,12 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
             for (const int2 &e : rc.sel) {
                 occ = (e.x == prev) ? occ + 1 : 0;
                 prev = e.x;
-                if (msgs[e.x].len > 0) enter(lookup(e.x, occ), e.y - msgs[e.x].base_pos);
+                if (msgs[e.x].len > 0) enter(lookup(e.x, occ), e.y, msgs[e.x].base_pos);
             }
         }
         if (rc.self_msg >= 0 && rc.self_len > 0)      // the call's own tail: one row, one token from the end -> all of it visible
-            enter(lookup(rc.self_msg, self_occ), rc.self_start - msgs[rc.self_msg].base_pos);
-        if (un.segs.size() > segs_max) return false;
+            enter(lookup(rc.self_msg, self_occ), rc.self_start, msgs[rc.self_msg].base_pos);
+        if (un.segs.size() > segs_max || far) return false;
     }
     un.tiles = 0;
     for (const Union::Seg &u : un.segs) un.tiles += (u.len + PC_TILE - 1) / PC_TILE;
@@ -441,7 +446,6 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     const int n_calls = (int)res.size();
     sp.in_shared.assign((size_t)n_calls, 0);
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
-    if (c->cfg.max_position > INT32_MAX / 3) return false;            // a position less a start plus a stored base is listed in 32 bits
     const int rows_max = 32 * (8 / g);
     static thread_local Union un;                        // (kept: fresh pages for it cost more than filling them)
     bool alone = c->decode_sharing == 0 && n_calls > 1 && c->decode_tiles_per_split == 0;

@@ -194,3 +194,32 @@ def test_partial_outputs_of_batches_that_go_there_by_price(n_calls, n_msgs, n_se
         assert got.isfinite().all() and (got_lse - want_lse).abs().max() <= 2e-2
         # rounded queries and probabilities on both sides (4e-3 between two walks), which one with sixteen bits less exponent is far from
         assert ((got - want).norm() / want.norm()).item() <= 1e-2
+
+
+def test_caches_of_any_largest_position():
+    """The shared walk with a largest position close to what 32 bits hold: taken as with any other, but where a call's position, less a
+    message's start, plus its stored base passes 32 bits (then the calls walk on their own)."""
+    import torch
+    from paper_2512_23049_amd import binding
+    h_q, h_kv, D, n, most = 32, 8, 128, 12, 2000000000
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    k, v = (torch.randn((n, 70, h_kv, D), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((n, h_q, D), generator=g, device="cuda:0").to(torch.bfloat16)
+    cache = binding.Cache(h_q, h_kv, D, binding.PC_BF16, 10000.0, n * 96, n, most)
+    for m in range(n):
+        cache.append_message(k[m].data_ptr(), v[m].data_ptr(), 70)
+
+    def run(calls, mode):
+        out, lse = torch.empty_like(q), torch.empty((n, h_q), device="cuda:0")
+        cache.set_decode_sharing(mode)
+        cache.attend(calls, q.data_ptr(), out.data_ptr(), lse.data_ptr())
+        torch.cuda.synchronize()
+        return out, lse
+    for at, far in ((5000, False), (900000000, False), (1999999000, True)):      # (the query at `at`, one message at -at)
+        calls = [Call([(m, 80 * m - (at if m == 5 else 0)) for m in range(n)], -1, 0, 1, [at - i]) for i in range(n)]
+        (got, got_lse), (want, want_lse) = run(calls, ALWAYS), run(calls, NEVER)
+        assert torch.equal(got, want) == far, at
+        assert (got.float() - want.float()).norm() <= 1e-2 * want.float().norm() and (got_lse - want_lse).abs().max() <= 1e-2
+    cache.reposition(3, 1500000000)                      # 1500000000 + 900000000
+    assert torch.equal(run(calls := [Call([(m, 80 * m) for m in range(n)], -1, 0, 1, [900000000]) for i in range(n)], ALWAYS)[0], run(calls, NEVER)[0])
+    cache.close()
