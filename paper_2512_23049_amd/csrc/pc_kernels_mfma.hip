@@ -450,7 +450,7 @@ __global__ __launch_bounds__(64 * ONE_WAVES, 2) void pc_decode_one_bf16_kernel(c
         const int64_t row = ((int64_t)cd.tok * L.n_kv_heads + kh) * PC_D + lane;
         tok[0] = O.tok_k[row]; tok[1] = O.tok_k[row + PC_D / 2]; tok[2] = O.tok_v[row]; tok[3] = O.tok_v[row + PC_D / 2];
     }
-    // (the host keeps positions times frequencies below 2^28)
+    // (the host keeps positions below 2^28 and frequencies at most 1: a start less a stored base stays below 2^29, or 2^30 behind a message of 2^28 tokens)
     if (token) {
         const int at = cd.self_len - 1;
         const float2 cs = rope_small((double)(__builtin_amdgcn_readlane(m_base, self_lane) + at) * freq);

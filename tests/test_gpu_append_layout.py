@@ -132,3 +132,31 @@ def test_reused_span_is_zero_behind_the_last_token(dtype, batch):
         assert (v[:, s0:s0 + L] == 1).all() and (k[:, s0, :] == 1).all()       # (token 0 sits at position 0: not turned)
     assert torch.isnan(k[:, end:704]).sum() == torch.isnan(k[:, end:700]).numel()
     cache.close()
+
+
+def test_rotations_of_appended_tokens_are_the_nearest_fp32_numbers():
+    """Tokens appended at positions that are their own angles (one frequency for all dimensions), stored in fp32: keys (1, 0) are left as
+    the cosine and sine of their position, rounded from 64 bits.  With them the five whole numbers below 2^24 at which a cosine series
+    without its term in x^14 rounds to another fp32 number, odd and even quarter turns, and the ends of the range."""
+    import torch
+    from paper_2512_23049_amd import binding
+    D, h_kv = 64, 2
+    pos = [180212, 1074636, 1981306, 3329500, 5866457, 1, 2, 3, 11, 1000, (1 << 24) - 1, -1, -180212, -(1 << 24) + 1]
+    cap = 32 * len(pos)
+    arena = torch.zeros((2, h_kv, cap, D), dtype=torch.float32, device="cuda:0")
+    cache = binding.Cache(h_kv, h_kv, D, binding.PC_F32, 1.0, cap, len(pos), arena=arena.data_ptr(), arena_bytes=4 * arena.numel())
+    k = torch.zeros((1, h_kv, D), device="cuda:0")
+    k[..., :D // 2] = 1
+    ids = [cache.append_message(k.data_ptr(), k.data_ptr(), 1, 3) for _ in pos]
+    for m, p in zip(ids, pos):
+        cache.reposition(m, p - 1)                       # the token at index 1 is turned to p
+    for m in ids[:7]:
+        cache.append_tokens(m, k.data_ptr(), k.data_ptr(), 1)
+    both = k.repeat(len(ids) - 7, 1, 1)
+    cache.append_tokens_batch(ids[7:], both.data_ptr(), both.data_ptr())
+    torch.cuda.synchronize()
+    keys = arena[0].cpu().numpy()
+    for i, p in enumerate(pos):
+        cos, sin = np.float32(np.cos(np.float64(p))), np.float32(np.sin(np.float64(p)))
+        assert (keys[:, 32 * i + 1, :D // 2] == cos).all() and (keys[:, 32 * i + 1, D // 2:] == sin).all(), p
+    cache.close()
