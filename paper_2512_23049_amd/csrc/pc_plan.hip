@@ -244,14 +244,13 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
         segs = un.segs.data(); pos = un.pos.data();
         return (int32_t)un.segs.size() - 1;
     };
-    auto lookup = [&](int32_t m, int32_t occ) -> int32_t {
-        if (occ == 0) {
-            if (marks[m].epoch != epoch) marks[m] = pc_cache::Mark{epoch, add(m, 0)};
-            return marks[m].value;
-        }
+    auto lookup = [&](int32_t m, int32_t occ) -> int32_t {              // -1: one too many
+        if (occ == 0 && marks[m].epoch == epoch) return marks[m].value;
         const int64_t key = ((int64_t)m << 20) | occ;
-        for (auto &kv : extra) if (kv.first == key) return kv.second;
+        if (occ > 0) for (auto &kv : extra) if (kv.first == key) return kv.second;
+        if (un.segs.size() >= segs_max) return -1;
         const int32_t u = add(m, occ);
+        if (occ == 0) { marks[m] = pc_cache::Mark{epoch, u}; return u; }
         extra.push_back({key, u});
         return u;
     };
@@ -269,14 +268,17 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
             if (hm.len <= 0) continue;
             self_occ += e->x == rc.self_msg;
             const int32_t u = marks[e->x].epoch == epoch ? marks[e->x].value : lookup(e->x, 0);
+            if (u < 0) return false;                     // (here: a row's list may be as long as the table of messages)
             uint32_t &vis = segs[u].vis[word];
             twice |= vis & bit;
             vis |= bit;
             pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - e->y + hm.base_pos);
         }
         auto enter = [&](int32_t u, int32_t start, int32_t base) {
+            if (u < 0) return false;
             segs[u].vis[word] |= bit;
             pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - start + base);
+            return true;
         };
         if (twice) {
             for (size_t u = 0; u < un.segs.size(); ++u) {             // the row again, from nothing
@@ -288,12 +290,12 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
             for (const int2 &e : rc.sel) {
                 occ = (e.x == prev) ? occ + 1 : 0;
                 prev = e.x;
-                if (msgs[e.x].len > 0) enter(lookup(e.x, occ), e.y, msgs[e.x].base_pos);
+                if (msgs[e.x].len > 0 && !enter(lookup(e.x, occ), e.y, msgs[e.x].base_pos)) return false;
             }
         }
-        if (rc.self_msg >= 0 && rc.self_len > 0)      // the call's own tail: one row, one token from the end -> all of it visible
-            enter(lookup(rc.self_msg, self_occ), rc.self_start, msgs[rc.self_msg].base_pos);
-        if (un.segs.size() > segs_max || far) return false;
+        // the call's own tail: one row, one token from the end -> all of it visible
+        if (rc.self_msg >= 0 && rc.self_len > 0 && !enter(lookup(rc.self_msg, self_occ), rc.self_start, msgs[rc.self_msg].base_pos)) return false;
+        if (far) return false;
     }
     un.tiles = 0;
     for (const Union::Seg &u : un.segs) un.tiles += (u.len + PC_TILE - 1) / PC_TILE;

@@ -469,3 +469,34 @@ def test_waiting_for_a_staging_slot_ends(pc):
         asked.clear()
         assert lib.pc_await_word(word, 7, state(answers, write_at), None) == want
         assert len(asked) == calls
+
+
+def in_a_process_of_its_own(code):
+    """What `code` prints, run with the library imported as m and rss(), peak() in MB."""
+    import subprocess
+    import sys
+    head = ("import resource, sys\nsys.path.insert(0, %r)\nimport paper_2512_23049_amd as m\nfrom pc_inputs import Call\n"
+            "from paper_2512_23049_amd.binding import marshal_calls\n"
+            "rss = lambda: int(open('/proc/self/statm').read().split()[1]) * resource.getpagesize() / 1e6\n"
+            "peak = lambda: resource.getrusage(resource.RUSAGE_SELF).ru_maxrss * 1024 / 1e6\n" % ROOT)
+    r = subprocess.run([sys.executable, "-c", head + code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    return [float(x) for x in r.stdout.split()]
+
+
+def test_one_very_long_list_among_short_ones(pc):
+    """A batch of one-row calls of which one lists 200 thousand messages: the union of the lists is given up where it passes the table it is
+    collected for (half a million entries, a row and a message each), not behind the row that passes it (80 MB)."""
+    grown, = in_a_process_of_its_own("""
+n = 200000
+c = m.Cache(16, 8, 128, m.PC_BF16, 1e4, n * 32, n, flags=m.PC_FLAG_HOST_ONLY)
+for i in range(0, n, 1000):
+    c.append_messages([0] * 1000, [0] * 1000, [1] * 1000)
+calls = [Call([(i, 0) for i in range(n)], -1, 5, 1, None)] + [Call([(i, 0)], -1, 5, 1, None) for i in range(100)]
+made, few = marshal_calls(calls), marshal_calls(calls[1:])
+c.attend(calls[1:], 0, 0, 0, 0, few)
+before = peak()
+c.attend(calls, 0, 0, 0, 0, made)
+print(peak() - before)
+""")
+    assert grown < 40, grown
