@@ -314,11 +314,42 @@ static void order_union(Union &un)
 
 static int rows_of(const Union::Seg &u) { int k = 0; for (uint32_t v : u.vis) k += __builtin_popcount(v); return k; }
 
-// what a batch's own walks and its runs by message cost
-struct DecodeCost { double own, by_message; int64_t passes, n_groups; };
-static DecodeCost decode_cost(const pc_cache *c, const Union &un)
+static int rows_per_run(const pc_cache *c) { return std::max(1, std::min(PC_RUN_ROWS, 16 / c->g)); }
+
+// Decode by message: what it needs whatever its runs are.  Queries go to LDS by direct loads of 16 bytes, whose addresses have to be multiples of
+// that (the other ways load them into registers); angles are those of the short series.
+static bool runs_possible(const pc_cache *c, const Planned &P, const Union &un)
 {
-    const int n_calls = un.n_rows, per_run = std::max(1, std::min(PC_RUN_ROWS, 16 / c->g));
+    return rows_per_run(c) >= 2 && un.tiles > 0 && ((uintptr_t)P.q & 15) == 0 && c->cfg.max_position < 1 << 28 && c->cfg.rope_theta >= 1.f &&
+           un.segs.size() * (size_t)un.n_rows <= 32768;
+}
+static size_t runs_layout(const pc_cache *c, int n_calls, size_t n_runs, int64_t n_parts, size_t n_tok, PlanLayout &L)
+{
+    const size_t off_merge = sizeof(PcMsgRun) * n_runs, off_tok = align_up(off_merge + sizeof(PcMergeRow) * (size_t)n_calls, 16);
+    const size_t H_q = (size_t)c->cfg.n_q_heads;
+    L = PlanLayout{};
+    L.part_ml = align_up(sizeof(float) * (size_t)n_parts * H_q * (size_t)c->D, 256);
+    L.calls = align_up(L.part_ml + sizeof(float) * 4 * (size_t)n_parts * H_q, 256);      // the runs, then the rows to merge
+    L.merge_rows = L.calls + off_merge;
+    const size_t bytes = off_tok + sizeof(PcTokenItem) * n_tok;
+    L.rot_seg = align_up(L.calls + bytes, 1024);
+    L.total = L.rot_seg + n_runs * PC_RUN_ROWS * sizeof(float2) * 64;
+    L.tok_items = off_tok;
+    return bytes;
+}
+// the lists and parts fit what every caller has (a step's tokens left out: with them or without, a batch goes the same way)
+static bool runs_fit(const pc_cache *c, int n_calls, size_t n_runs, int64_t n_parts)
+{
+    PlanLayout L;
+    return n_runs < 65535 && runs_layout(c, n_calls, n_runs, n_parts, 0, L) <= HOST_READ_BYTES && L.total <= PC_STATIC_WS_BYTES;
+}
+
+// what a batch's own walks and its runs by message cost
+constexpr double NOT_BY_MESSAGE = 1e30;
+struct DecodeCost { double own, by_message; int64_t passes, n_groups; };
+static DecodeCost decode_cost(const pc_cache *c, const Planned &P, const Union &un)
+{
+    const int n_calls = un.n_rows, per_run = rows_per_run(c);
     const double per_cu = c->cfg.n_kv_heads / 256.0;
     int64_t again = 0, in_step = 0, listed = 0;
     DecodeCost k{0, 0, 0, 0};
@@ -330,7 +361,9 @@ static DecodeCost decode_cost(const pc_cache *c, const Union &un)
     const bool pinned = (sizeof(PcOneCall) + sizeof(PcOneItem) + 4) * (size_t)n_calls + sizeof(int2) * (size_t)listed > PC_ARG_BYTES;
     k.own = (pinned ? OWN_PINNED : OWN_FIXED) + per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step);
     k.by_message = RUN_FIXED + RUN_PART * (double)listed / n_calls + per_cu * std::max(TILE_PASS * ((double)k.passes + RUN_START * (double)k.n_groups), TILE_NEW * (double)un.tiles);
-    if (per_run < 2) k.by_message = 1e30;
+    // (a part per row that lists a message, and a run per group of them, are the least there is: for long lists that is all it takes to know, and
+    // the search for the runs is not begun)
+    if (!runs_possible(c, P, un) || !runs_fit(c, n_calls, (size_t)k.n_groups, listed)) k.by_message = NOT_BY_MESSAGE;
     return k;
 }
 
@@ -415,7 +448,7 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
     const bool whole = n_calls <= 256 && (n_groups == 1 || entries <= 2048);
     if (whole) {
         if (!collect_union(c, res, 0, n_calls, UNION_ENTRIES / (size_t)n_calls, un)) return n_groups == 1 ? Way::OWN : Way::BY_RATIO;
-        const DecodeCost cost = decode_cost(c, un);
+        const DecodeCost cost = decode_cost(c, P, un);
         if ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles) lean = SHARE_LEAN;
         const double shared = lean * (SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)n_groups);
         own = cost.own;
@@ -474,13 +507,10 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     return false;
 }
 
-// A decode batch by message (pc_decode_runs_bf16_kernel), if its lists and parts fit what every caller has.
+// A decode batch by message (pc_decode_runs_bf16_kernel), if its lists and parts fit (decode_cost has seen to the rest).
 static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost, hipStream_t st, int32_t &rc)
 {
-    const int n_calls = un.n_rows, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads, per_run = std::min(PC_RUN_ROWS, 16 / c->g);
-    // (queries go to LDS by direct loads of 16 bytes, whose addresses have to be multiples of that; the other ways load them into registers)
-    if (((uintptr_t)P.q & 15) != 0) return false;
-    if (per_run < 2 || un.tiles == 0 || c->cfg.max_position >= 1 << 28 || c->cfg.rope_theta < 1.f) return false;
+    const int n_calls = un.n_rows, H_kv = c->cfg.n_kv_heads, per_run = rows_per_run(c);
     order_union(un);
     // the least share of tiles, and of runs' starts and ends, with which so many waves take all of them
     const double total = (double)cost.passes + RUN_START * (double)cost.n_groups;
@@ -488,21 +518,25 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
     auto take_of = [](double room, int left) { return std::min(left, std::max(1, (int)(room - RUN_START))); };
     double share = std::max(6.0, total / most_waves + 0.5);
     int n_waves = 0;
+    size_t n_runs = 0;
+    int64_t n_parts = 0;
     for (;; share *= 1.03) {
-        n_waves = 1;
+        n_waves = 1; n_runs = 0; n_parts = 0;
         double used = 0;
         for (int32_t k : un.order) {
             const Union::Seg &u = un.segs[(size_t)k];
             const int T = (u.len + PC_TILE - 1) / PC_TILE;
-            for (int gr = (rows_of(u) + per_run - 1) / per_run; gr > 0; --gr)
+            for (int left = rows_of(u); left > 0; left -= per_run)
                 for (int t = 0; t < T;) {
                     if (used + RUN_START + 1 > share) { ++n_waves; used = 0; }         // (less than a start and a tile left: the next wave)
                     const int take = take_of(share - used, T - t);
                     used += RUN_START + take; t += take;
+                    ++n_runs; n_parts += std::min(left, per_run);
                 }
         }
         if (n_waves <= most_waves) break;
     }
+    if (!runs_fit(c, n_calls, n_runs, n_parts)) return false;
     static thread_local std::vector<PcMsgRun> runs;
     runs.clear();
     std::vector<int32_t> parts((size_t)n_calls, 0);
@@ -537,7 +571,6 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
             }
         if (n > 0) emit();
     }
-    if (runs.size() >= 65535) return false;
     P.run_starts.first[++wave] = (uint16_t)runs.size();
     // a call's parts lie one after the other, in slot order
     std::vector<int32_t> part0((size_t)n_calls);
@@ -545,16 +578,8 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
     for (int i = 0; i < n_calls; ++i) { part0[(size_t)i] = part_rows; part_rows += parts[(size_t)i]; }
     for (PcMsgRun &r : runs)
         for (int i = 0; i < r.size >> 28; ++i) r.part[i] += part0[(size_t)r.row[i]];
-    const size_t off_merge = sizeof(PcMsgRun) * runs.size();
-    const size_t off_tok = align_up(off_merge + sizeof(PcMergeRow) * (size_t)n_calls, 16), bytes = off_tok + sizeof(PcTokenItem) * P.tok_items.size();
-    P.lay = PlanLayout{};
-    P.lay.part_ml = align_up(sizeof(float) * (size_t)part_rows * H_q * c->D, 256);
-    P.lay.calls = align_up(P.lay.part_ml + sizeof(float) * 4 * (size_t)part_rows * H_q, 256);    // the runs, then the rows to merge
-    P.lay.merge_rows = P.lay.calls + off_merge;
-    P.lay.rot_seg = align_up(P.lay.calls + bytes, 1024);
-    P.lay.total = P.lay.rot_seg + runs.size() * PC_RUN_ROWS * sizeof(float2) * 64;
+    const size_t bytes = runs_layout(c, n_calls, runs.size(), part_rows, P.tok_items.size(), P.lay), off_merge = P.lay.merge_rows - P.lay.calls, off_tok = P.lay.tok_items;
     P.n_runs = (int)runs.size();
-    if (bytes > HOST_READ_BYTES || P.lay.total > PC_STATIC_WS_BYTES || un.segs.size() * (size_t)n_calls > 32768) return false;
     char *h;
     const bool recorded = pc_recorded(st);
     if (recorded) {
@@ -571,7 +596,6 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
     P.runs_bytes = bytes;
     P.n_merge_rows = n_calls; P.n_merge_few = 0;
     if (!P.tok_items.empty()) std::memcpy(h + off_tok, P.tok_items.data(), sizeof(PcTokenItem) * P.tok_items.size());
-    P.lay.tok_items = off_tok;
     P.runs = PcRuns{c->table_dev, nullptr, nullptr, n_waves};
     return true;
 }

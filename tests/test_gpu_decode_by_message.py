@@ -109,6 +109,21 @@ def test_against_own_walks(h_q, h_kv, n_calls, n_sel, pool):
     b.cache.close()
 
 
+@pytest.mark.parametrize("n_sel,by_message", [(50, True), (110, False)])
+def test_parts_that_fill_the_fixed_workspace(n_sel, by_message):
+    """A batch whose parts (a row of 64 heads is 32 KB) would pass the fixed workspace goes another way, in every entry point; a shorter one by message."""
+    r = np.random.default_rng(1)
+    b = Batch(64, 8, [int(x) for x in r.integers(60, 250, 330)], [1] * 12, 3)
+    calls = spread(r, 12, 330, n_sel, b.own)
+    q = b.normal(12, 64, D)
+    got = b.attend(calls, q)
+    assert got[2] == by_message
+    same = b.attend(calls, q, static=True)
+    assert (same[0] == got[0]).all() and (same[1] == got[1]).all()
+    close(got, b.attend(calls, q, mode=1))
+    b.cache.close()
+
+
 def test_steps_and_static():
     """Three steps of tails that cross a tile: results, stores bit for bit those of the two separate calls, pc_attend_static's bits."""
     r = np.random.default_rng(5)
