@@ -229,9 +229,11 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
     std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> seg, for repeats within a call
     un.segs.clear(); un.pos.clear();
     un.n_rows = n_rows; un.call_tiles = 0;
+    // (a position, less a start, plus a base, which for a further extent lies up to three largest positions out; INT32_MIN is PC_SH_ABSENT)
+    const bool may_be_far = c->cfg.max_position > INT32_MAX / 6;
     bool far = false;
-    auto as_listed = [&](int64_t p) {                    // (INT32_MIN is PC_SH_ABSENT)
-        far |= p < -INT32_MAX || p > INT32_MAX;
+    auto as_listed = [&](int64_t p) {
+        if (may_be_far) far |= p < -INT32_MAX || p > INT32_MAX;
         return (int32_t)p;
     };
     const uint32_t epoch = new_marks(c);                 // value: the message's place in segs
@@ -471,7 +473,8 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
         i += n_rows;
     }
     sp.wide = !as_by_ratio;
-    return as_by_ratio || groups_fit(c, sp) ? Way::SHARED : Way::BY_RATIO;
+    if (as_by_ratio || groups_fit(c, sp)) return Way::SHARED;
+    return n_groups == 1 ? Way::OWN : Way::BY_RATIO;     // (the ratio of a single group is known)
 }
 
 // rc != PC_OK: an error.  True: the whole batch goes by message (P.runs_*), and nothing else is to be planned
