@@ -244,7 +244,8 @@ struct PcShItem {
     int32_t tile_begin, tile_end;     // range of the union's tiles
     int32_t split;
     int32_t seg_begin;                // message of the union that owns tile_begin
-    int32_t pad[3];
+    int32_t part_wide;                // 1 = partial outputs in fp32, a row takes two units of its group's part_off
+    int32_t pad[2];
 };
 
 struct PcShLaunch {

@@ -108,7 +108,7 @@ void pc_launch_runs_prepare(const void *lists, void *to, size_t bytes, int n_run
 void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunStarts &starts, hipStream_t st);
 void pc_launch_prefill_bf16(const PcLaunch &L, int n_items, bool packed, hipStream_t st);   // packed: the items of calls that gathered
 
-// shared decode (wide: partial outputs in fp32)
+// shared decode (wide: some items have part_wide set)
 void pc_launch_decode_shared_bf16(const PcLaunch &L, const PcShLaunch &S, int n_items, bool wide, hipStream_t st);
 
 #endif

@@ -74,7 +74,7 @@ __device__ __forceinline__ void sh_wait_landed()
 // TAB: a wave's part of a message's rotation table, in KB (32 / g rows of 512 bytes), fetched into LDS while the message before is
 // walked; 0: the turn reads it from memory.  32 calls over 150 of 200 messages, us a pass of four steps, from LDS / from memory: g = 8
 // 304 / 306, g = 4 274 / 276, g = 2 (whose wave has 16 rows) 271 / 266, so g >= 4 takes LDS.
-// WIDE: partial outputs in fp32, a row takes two units of its group's part_off (by a flag instead, the walk's schedule changed: g = 4 253 / 256 us).
+// WIDE: some items write partial outputs in fp32 (one kernel for all launches: its walk is scheduled otherwise, g = 4 253 / 256 us).
 template <int TAB, bool WIDE>
 __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch L, PcShLaunch S)
 {
@@ -356,14 +356,15 @@ __global__ __launch_bounds__(512, 1) void pc_decode_shared_bf16_kernel(PcLaunch 
         if (L.lse && hh == 0)
             L.lse[(int64_t)Rg * L.n_q_heads + h] = (l > 0.f) ? (m_ref + log2f(l)) * 0.6931471805599453f : -INFINITY;
     } else {
-        const int64_t pr = (int64_t)gr.part_off + (((int64_t)item.split * gr.n_rows + row) << WIDE);
-        uint16_t *o = L.part_o + (pr * L.n_q_heads + ((int64_t)h << WIDE)) * PC_D;
+        const int wide = WIDE ? item.part_wide : 0;
+        const int64_t pr = (int64_t)gr.part_off + (((int64_t)item.split * gr.n_rows + row) << wide);
+        uint16_t *o = L.part_o + (pr * L.n_q_heads + ((int64_t)h << wide)) * PC_D;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int d = 32 * db + 8 * q4 + 4 * hh;
-                if constexpr (WIDE) {
+                if (wide) {
                     *reinterpret_cast<float4 *>(reinterpret_cast<float *>(o) + d) =
                         make_float4(acc[db][4 * q4] * inv, acc[db][4 * q4 + 1] * inv, acc[db][4 * q4 + 2] * inv, acc[db][4 * q4 + 3] * inv);
                 } else {

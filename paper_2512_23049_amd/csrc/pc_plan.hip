@@ -3,6 +3,7 @@
 #include "pc_host.h"
 
 #include <numeric>
+#include <type_traits>
 
 int32_t pc_resolve(pc_cache *c, const pc_call *call, int idx, Resolved &out)
 {
@@ -185,7 +186,7 @@ struct SharedPlan {
     std::vector<PcShGroup> groups;
     std::vector<PcShSeg> segs;
     std::vector<PcShItem> items;
-    bool wide = false;                           // partial outputs in fp32
+    std::vector<char> wide;                      // per group: partial outputs in fp32
     std::vector<int32_t> pos;                    // rotation positions, q_pos - start + stored base, PC_SH_ABSENT where a row does not list the message
 };
 
@@ -229,11 +230,9 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
     std::vector<std::pair<int64_t, int32_t>> extra;       // (msg << 20 | occurrence) -> seg, for repeats within a call
     un.segs.clear(); un.pos.clear();
     un.n_rows = n_rows; un.call_tiles = 0;
-    // (a position, less a start, plus a base, which for a further extent lies up to three largest positions out; INT32_MIN is PC_SH_ABSENT)
-    const bool may_be_far = c->cfg.max_position > INT32_MAX / 6;
     bool far = false;
-    auto as_listed = [&](int64_t p) {
-        if (may_be_far) far |= p < -INT32_MAX || p > INT32_MAX;
+    auto listed = [&](int64_t p) {                       // (INT32_MIN is PC_SH_ABSENT)
+        far |= p < -INT32_MAX || p > INT32_MAX;
         return (int32_t)p;
     };
     const uint32_t epoch = new_marks(c);                 // value: the message's place in segs
@@ -265,21 +264,28 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
         const int64_t q0 = rc.q_pos[0];
         const uint32_t word = (uint32_t)r >> 5, bit = 1u << (r & 31);
         uint32_t twice = 0;
-        for (const int2 *e = rc.sel.data(), *end = e + rc.sel.size(); e < end; ++e) {
-            const HostMsg &hm = msgs[e->x];
-            if (hm.len <= 0) continue;
-            self_occ += e->x == rc.self_msg;
-            const int32_t u = marks[e->x].epoch == epoch ? marks[e->x].value : lookup(e->x, 0);
-            if (u < 0) return false;                     // (here: a row's list may be as long as the table of messages)
-            uint32_t &vis = segs[u].vis[word];
-            twice |= vis & bit;
-            vis |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - e->y + hm.base_pos);
-        }
+        auto walk = [&](auto bounded) {                  // (bounded: every sum of a position, a start and a base fits 32 bits)
+            for (const int2 *e = rc.sel.data(), *end = e + rc.sel.size(); e < end; ++e) {
+                const HostMsg &hm = msgs[e->x];
+                if (hm.len <= 0) continue;
+                self_occ += e->x == rc.self_msg;
+                int32_t u = marks[e->x].value;
+                if (marks[e->x].epoch != epoch && (u = lookup(e->x, 0)) < 0) return false;      // (here: a row's list may be as long as the table of messages)
+                uint32_t &vis = segs[u].vis[word];
+                twice |= vis & bit;
+                vis |= bit;
+                int32_t &at = pos[(size_t)u * (size_t)n_rows + (size_t)r];
+                if constexpr (decltype(bounded)::value) at = (int32_t)q0 - e->y + hm.base_pos;
+                else at = listed(q0 - e->y + hm.base_pos);
+            }
+            return true;
+        };
+        // (a base is at most three largest positions out: that of a further extent)
+        if (!(c->cfg.max_position <= INT32_MAX / 6 ? walk(std::true_type{}) : walk(std::false_type{}))) return false;
         auto enter = [&](int32_t u, int32_t start, int32_t base) {
             if (u < 0) return false;
             segs[u].vis[word] |= bit;
-            pos[(size_t)u * (size_t)n_rows + (size_t)r] = as_listed(q0 - start + base);
+            pos[(size_t)u * (size_t)n_rows + (size_t)r] = listed(q0 - start + base);
             return true;
         };
         if (twice) {
@@ -297,8 +303,8 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
         }
         // the call's own tail: one row, one token from the end -> all of it visible
         if (rc.self_msg >= 0 && rc.self_len > 0 && !enter(lookup(rc.self_msg, self_occ), rc.self_start, msgs[rc.self_msg].base_pos)) return false;
-        if (far) return false;
     }
+    if (far) return false;
     un.tiles = 0;
     for (const Union::Seg &u : un.segs) un.tiles += (u.len + PC_TILE - 1) / PC_TILE;
     return true;
@@ -382,7 +388,7 @@ static int shared_splits(const pc_cache *c, size_t n_groups, int T)
 }
 
 // the calls of a union, the first of them `first`, as a group of the shared walk
-static void add_group(SharedPlan &sp, Union &un, int first, int row0)
+static void add_group(SharedPlan &sp, Union &un, int first, int row0, bool wide)
 {
     order_union(un);
     const int n_rows = un.n_rows;
@@ -405,29 +411,43 @@ static void add_group(SharedPlan &sp, Union &un, int first, int row0)
     }
     gr.n_tiles = tile_off;
     sp.groups.push_back(gr);
+    sp.wide.push_back(wide);
     for (int k = 0; k < n_rows; ++k) sp.in_shared[(size_t)(first + k)] = 1;
 }
 
 static void drop_groups(SharedPlan &sp)
 {
     std::fill(sp.in_shared.begin(), sp.in_shared.end(), 0);
-    sp.groups.clear(); sp.segs.clear(); sp.pos.clear(); sp.wide = false;
+    sp.groups.clear(); sp.wide.clear(); sp.segs.clear(); sp.pos.clear();
 }
 
 // The table of a group has an entry for every row and message of the union, listed or not, so that a batch the calls' own walks have room
-// for may not fit: a batch of groups alone fits the fixed workspace.
-static bool groups_fit(const pc_cache *c, const SharedPlan &sp)
+// for may not fit the fixed workspace.
+static bool groups_fit(const pc_cache *c, size_t n_groups, size_t rows, size_t segs, size_t entries, size_t items, int64_t part_rows)
 {
-    size_t rows = 0, items = 0;
-    int64_t part_rows = 0;
-    for (const PcShGroup &gr : sp.groups) {
-        const int ns = shared_splits(c, sp.groups.size(), gr.n_tiles);
-        rows += (size_t)gr.n_rows; items += (size_t)ns;
-        if (ns > 1) part_rows += ((int64_t)ns * gr.n_rows) << sp.wide;
-    }
-    const PlanLayout l = make_layout((int)rows, (int)rows, 0, 0, 0, 0, part_rows, 0, c->cfg.n_q_heads, c->D, sp.groups.size(), sp.segs.size(), items, sp.pos.size(),
+    const PlanLayout l = make_layout((int)rows, (int)rows, 0, 0, 0, 0, part_rows, 0, c->cfg.n_q_heads, c->D, n_groups, segs, items, entries,
                                      0, 0, c->cfg.n_kv_heads, 0, 0, 0, 0, 0, sizeof(uint16_t), rows);
     return l.total <= PC_STATIC_WS_BYTES && l.h2d_bytes <= STAGE_BYTES;
+}
+// the groups so far, and one more of a union (null: none), as groups of a batch of n_groups
+static bool groups_fit(const pc_cache *c, const SharedPlan &sp, size_t n_groups, const Union *more)
+{
+    size_t rows = 0, items = 0, segs = sp.segs.size(), entries = sp.pos.size();
+    int64_t part_rows = 0;
+    auto add = [&](int tiles, int n, int wide) {
+        const int ns = shared_splits(c, n_groups, tiles);
+        rows += (size_t)n; items += (size_t)ns;
+        if (ns > 1) part_rows += ((int64_t)ns * n) << wide;
+    };
+    for (size_t i = 0; i < sp.groups.size(); ++i) add(sp.groups[i].n_tiles, sp.groups[i].n_rows, sp.wide[i]);
+    if (more) { add((int)more->tiles, more->n_rows, 1); segs += more->segs.size(); entries += more->pos.size(); }
+    return groups_fit(c, n_groups, rows, segs, entries, items, part_rows);
+}
+// the same for n_calls calls in n_groups groups of a size, each with a union of so many messages and tiles and fp32 parts
+static bool even_groups_fit(const pc_cache *c, size_t n_calls, size_t n_groups, size_t segs, int64_t tiles)
+{
+    const int ns = shared_splits(c, n_groups, (int)std::min<int64_t>(tiles, INT32_MAX / 2));
+    return groups_fit(c, n_groups, n_calls, n_groups * segs, n_calls * segs, n_groups * (size_t)ns, ns > 1 ? 2 * (int64_t)ns * (int64_t)n_calls : 0);
 }
 
 enum class Way { OWN, BY_MESSAGE, SHARED, BY_RATIO };
@@ -438,9 +458,12 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
     std::vector<Resolved> &res = P.res;
     const int n_calls = (int)res.size();
     const double per_cu = c->cfg.n_kv_heads / 256.0;
-    size_t entries = 0;
+    size_t entries = 0, most_sel = 0;
     int64_t all_tiles = 0;
-    for (const Resolved &r : res) { entries += r.sel.size(); all_tiles += r.tiles; }
+    int32_t most_tiles = 0;
+    for (const Resolved &r : res) {
+        entries += r.sel.size(); most_sel = std::max(most_sel, r.sel.size()); all_tiles += r.tiles; most_tiles = std::max(most_tiles, r.tiles);
+    }
     // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
     if (OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return Way::OWN;
     const int n_groups = (n_calls + rows_max - 1) / rows_max;
@@ -457,24 +480,34 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
         if (!c->host_only && cost.by_message < 0.95 * std::min(own, shared) && plan_runs(c, P, un, cost, st, rc)) return Way::BY_MESSAGE;
         if (rc != PC_OK || own < SHARED_FIXED) return Way::OWN;
     }
-    double shared = SHARED_FIXED;
-    // Where the ratio alone would have formed other groups, or not have given one of them this walk, partial outputs stay in fp32, as those of the
-    // calls' own walks do (6 calls over 300 messages of 5 tiles, each listed by 5 of them, 8 heads a KV head: 118 us a step).
-    bool as_by_ratio = n_calls <= rows_max || n_calls % rows_max == 0;
-    for (int i = 0; i < n_calls;) {
-        // (groups of a size: two calls behind a full group would have walks, and launches, of their own)
-        const int left = (n_calls - i + rows_max - 1) / rows_max, n_rows = (n_calls - i + left - 1) / left;
+    // Groups of a size, or full ones and a rest, as the ratio forms them.  One that the ratio would not have formed, or not have given this walk (two calls
+    // behind a full group: walks, and a launch, of their own), keeps its partial outputs in fp32, as the calls' own walks do, and takes it if
+    // there is room for that.  (6 calls over 300 messages of 5 tiles, each listed by 5 of them, 8 heads a KV head: 118 us a step on their own.
+    // 101 calls over 152 of 170, three groups and five calls: 176, with these in the walk 101.  139 over 14 of 15, 4 heads and 4 KV heads: in
+    // groups of 64, 64 and 11 45, of 47 and 46 41.)
+    bool even = n_groups > 1 && n_calls % rows_max != 0 && even_groups_fit(c, (size_t)n_calls, (size_t)n_groups, most_sel, most_tiles);
+    double shared = SHARED_FIXED;                        // with what does not take the walk beside it
+    bool any_wide = false, any_own = false;
+    for (int i = 0, n_rows; i < n_calls; i += n_rows) {
+        const int left = (n_calls - i + rows_max - 1) / rows_max;
+        n_rows = even ? (n_calls - i + left - 1) / left : std::min(rows_max, n_calls - i);
         if (!(whole && n_rows == n_calls) && !collect_union(c, res, i, n_rows, UNION_ENTRIES / (size_t)n_rows, un)) return Way::BY_RATIO;
-        if (un.tiles == 0 || un.tiles >= INT32_MAX / 2) return Way::BY_RATIO;
-        as_by_ratio = as_by_ratio && n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles;
-        shared += SHARED_TILE * per_cu * (double)un.tiles;
+        if (even && i == 0 && !even_groups_fit(c, (size_t)n_calls, (size_t)n_groups, un.segs.size(), un.tiles)) {
+            even = false;                                // (known from the first of them)
+            n_rows = 0;
+            continue;
+        }
+        const bool enough = !even && n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles;
+        const bool take = un.tiles > 0 && un.tiles < INT32_MAX / 2 && (enough || groups_fit(c, sp, (size_t)n_groups, &un));
+        shared += take ? SHARED_TILE * per_cu * (double)un.tiles : OWN_FIXED + per_cu * TILE_AGAIN * (double)un.call_tiles;
         if (own < lean * shared) return Way::OWN;
-        add_group(sp, un, i, i);
-        i += n_rows;
+        if (take) add_group(sp, un, i, i, !enough);
+        any_wide = any_wide || (take && !enough);
+        any_own = any_own || !take;
     }
-    sp.wide = !as_by_ratio;
-    if (as_by_ratio || groups_fit(c, sp)) return Way::SHARED;
-    return n_groups == 1 ? Way::OWN : Way::BY_RATIO;     // (the ratio of a single group is known)
+    if (sp.groups.empty()) return Way::OWN;
+    // (with calls on their own beside it a group has more splits than was assumed)
+    return any_wide && (any_own || !groups_fit(c, sp, sp.groups.size(), nullptr)) ? Way::BY_RATIO : Way::SHARED;
 }
 
 // rc != PC_OK: an error.  True: the whole batch goes by message (P.runs_*), and nothing else is to be planned
@@ -504,7 +537,7 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
         if ((c->decode_sharing == 2 || (double)sum_tiles >= SHARE_MIN * (double)longest) &&
             collect_union(c, res, i, n_rows, UNION_ENTRIES / (size_t)n_rows, un) && un.tiles > 0 && un.tiles < INT32_MAX / 2 &&
             (c->decode_sharing == 2 || (n_rows >= 2 && (double)un.call_tiles >= SHARE_MIN * (double)un.tiles)))
-            add_group(sp, un, i, q_off[(size_t)i]);
+            add_group(sp, un, i, q_off[(size_t)i], false);
         i = j;
     }
     return false;
@@ -1060,7 +1093,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     static thread_local SharedPlan kept_plan;
     SharedPlan &sp = kept_plan;
     sp.in_shared.assign((size_t)n_calls, 0);
-    sp.groups.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear(); sp.wide = false;
+    sp.groups.clear(); sp.wide.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear();
     if (want_items && bf16) {
         std::vector<int> q_offs((size_t)n_calls);
         for (int i = 0, o = 0; i < n_calls; ++i) { q_offs[(size_t)i] = o; o += P.res[(size_t)i].n_q; }
@@ -1239,12 +1272,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             const int T = gr.n_tiles;
             const int ns = shared_splits(c, sp.groups.size(), T), chunk = std::max(1, (T + ns - 1) / ns);
             gr.n_splits = ns;
-            if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += ((int64_t)ns * gr.n_rows) << sp.wide; }
+            if (ns > 1) { gr.part_off = (int32_t)part_rows; part_rows += ((int64_t)ns * gr.n_rows) << sp.wide[gi]; }
             int seg = 0;                                     // the message that owns a split's first tile (splits ascend)
             for (int sidx = 0; sidx < ns; ++sidx) {
                 const int t0 = sidx * chunk;
                 while (seg + 1 < gr.n_seg && sp.segs[(size_t)gr.seg_off + (size_t)seg + 1].tile_off <= t0) ++seg;
-                sp.items.push_back(PcShItem{(int32_t)gi, t0, std::min(T, (sidx + 1) * chunk), sidx, seg, {0, 0, 0}});
+                sp.items.push_back(PcShItem{(int32_t)gi, t0, std::min(T, (sidx + 1) * chunk), sidx, seg, sp.wide[gi], {0, 0}});
             }
         }
     };
@@ -1301,7 +1334,10 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                 else n_pre += (size_t)(ns = prefill_splits(r.tiles, false)) * (size_t)pre_groups_of(r);
                 if (ns > 1) { rows += (int64_t)ns * r.n_q; n_merge += (size_t)r.n_q; }
             }
-            for (const PcShGroup &gr : sp.groups) if (gr.n_splits > 1) { rows += ((int64_t)gr.n_splits * gr.n_rows) << sp.wide; n_merge += (size_t)gr.n_rows; }
+            for (size_t i = 0; i < sp.groups.size(); ++i) {
+                const PcShGroup &gr = sp.groups[i];
+                if (gr.n_splits > 1) { rows += ((int64_t)gr.n_splits * gr.n_rows) << sp.wide[i]; n_merge += (size_t)gr.n_rows; }
+            }
             const PlanLayout plain = layout_of(n_dec, n_pre, rows, n_merge, 0);
             const bool refused = P.fixed_ws && (plain.total > P.fixed_cap || plain.h2d_bytes > c->stage[c->stage_next].cap);
             if (refused) plan_items(false, INT64_MAX);
@@ -1344,7 +1380,7 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     }
     P.total_seg = seg_off;
     P.n_dec = (int)dec.size(); P.n_pre = (int)pre.size(); P.n_pre_pk = (int)pre_pk.size();
-    P.n_sh_items = (int)sp.items.size(); P.sh_wide = sp.wide; P.n_sh_pos = sp.pos.size();
+    P.n_sh_items = (int)sp.items.size(); P.sh_wide = std::find(sp.wide.begin(), sp.wide.end(), 1) != sp.wide.end(); P.n_sh_pos = sp.pos.size();
     P.n_kg_items = (int)kg.size(); P.kg_tiles = kg_tiles;
     if (part_rows > INT32_MAX) return pc_fail(c, PC_ERR_SHAPE, "attend: partial buffer too large");
     if (total_tiles > INT32_MAX / 2) return pc_fail(c, PC_ERR_SHAPE, "attend: too many KV tiles");
@@ -1395,10 +1431,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
                                                       cds[i].n_splits | (cds[i].part_wide ? PC_MERGE_WIDE : 0), P.res[i].n_q};
         if (!tail_rows.empty() && wanted(tail.second))
             for (const PcMergeRow &mr : tail_rows) hm[P.n_merge_rows++] = mr;
-        for (const PcShGroup &gr : sp.groups)
+        for (size_t i = 0; i < sp.groups.size(); ++i) {
+            const PcShGroup &gr = sp.groups[i];
             if (wanted(gr.n_splits))
                 for (int q = 0; q < gr.n_rows; ++q)
-                    hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + (q << sp.wide), gr.n_splits | (sp.wide ? PC_MERGE_WIDE : 0), gr.n_rows};
+                    hm[P.n_merge_rows++] = PcMergeRow{gr.row0 + q, gr.part_off + (q << sp.wide[i]), gr.n_splits | (sp.wide[i] ? PC_MERGE_WIDE : 0), gr.n_rows};
+        }
         if (pass == 0) P.n_merge_few = P.n_merge_rows;
     }
     if (!dec.empty()) std::memcpy(h + P.lay.items_dec, dec.data(), sizeof(PcItem) * dec.size());
