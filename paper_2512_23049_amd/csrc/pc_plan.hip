@@ -206,6 +206,10 @@ constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS
 // us by walks of their own, took 50, shared 38.  125 drawn batches of 6 to 64 calls: 1.25 times as fast as by the sharing ratio alone.  The
 // shared figures above were taken with the rotations in a launch of their own, 3 us more than now.)
 constexpr double SHARE_LEAN = 0.8;
+// What a step takes the host, in us, without a union: resolving, sorting and staging the lists of calls that walk on their own in one launch, and
+// enqueuing it.  (With one, and walks of their own after all: 5 calls over 996 of 1,228 messages, one KV head, 52 us a step for 36; 54 over 110
+// of 157, two, 56 for 41.  Fitted to 18 batches of 5 to 155 calls, 775 to 16 thousand entries.)
+constexpr double HOST_FIXED = 6.0, HOST_CALL = 0.1, HOST_ENTRY = 0.0055;
 constexpr double RUN_START = 1.5;                        // a run's start and end, in passes
 constexpr double SHARE_MIN = 6.0;
 // entries of a group's rotation table, a row and a message of the union each: 512 bytes, 256 MB in all
@@ -461,11 +465,22 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
     size_t entries = 0, most_sel = 0;
     int64_t all_tiles = 0;
     int32_t most_tiles = 0;
+    bool one_launch = true;                              // as far as lists go that a wave cannot hold
+    const size_t most_entries = (size_t)PC_ONE_SEGS * (size_t)std::max(1, std::min(MAX_SPLITS, 2 * PC_ONE_COUNTERS / (n_calls * c->cfg.n_kv_heads)));
     for (const Resolved &r : res) {
         entries += r.sel.size(); most_sel = std::max(most_sel, r.sel.size()); all_tiles += r.tiles; most_tiles = std::max(most_tiles, r.tiles);
+        one_launch = one_launch && r.sel.size() < most_entries;
     }
     // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
     if (OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return Way::OWN;
+    // The longest list is the least a union can be, and the other two ways gain the most on walks of their own there
+    const double longest = (double)most_tiles;
+    const double on_own = OWN_PINNED + per_cu * (TILE_NEW * longest + TILE_AGAIN * ((double)all_tiles - longest));
+    const double by_shared = ((double)all_tiles >= SHARE_MIN * longest ? SHARE_LEAN : 1.0) * (SHARED_FIXED + SHARED_TILE * per_cu * longest);
+    const double by_message = RUN_FIXED + RUN_PART * (double)entries / n_calls + TILE_NEW * per_cu * longest;
+    if (on_own < by_shared && 0.95 * on_own < by_message) return Way::OWN;
+    // Long lists of short messages under few KV heads: the host takes longer than the GPU whichever way it is, and least if nothing is collected
+    if (one_launch && OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles < HOST_FIXED + HOST_CALL * n_calls + HOST_ENTRY * (double)entries) return Way::OWN;
     const int n_groups = (n_calls + rows_max - 1) / rows_max;
     double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles, lean = 1;
     // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
