@@ -217,6 +217,11 @@ constexpr size_t UNION_ENTRIES = (size_t)1 << 19;
 // rows with more splits than this are merged by four lanes per 8 dimensions
 constexpr int MERGE_MANY_SPLITS = 8;
 
+// Lists that a thread keeps from one call to the next (fresh pages for them cost more than filling them) are given back when a batch made them
+// longer than KEPT_BYTES each.
+constexpr size_t KEPT_BYTES = (size_t)4 << 20;
+template <typename T> static void keep(std::vector<T> &v) { if (v.capacity() * sizeof(T) > KEPT_BYTES) std::vector<T>().swap(v); }
+
 // The union of the lists of some one-row calls: which messages there are, who lists each, and where.
 struct Union {
     struct Seg { int32_t msg, occ, len; int64_t slot; uint32_t vis[8]; };      // bit n of vis: row n lists it
@@ -533,7 +538,8 @@ static bool plan_shared(pc_cache *c, Planned &P, const std::vector<int> &q_off, 
     sp.in_shared.assign((size_t)n_calls, 0);
     if (c->decode_sharing == 1 || !(g == 1 || g == 2 || g == 4 || g == 8)) return false;
     const int rows_max = 32 * (8 / g);
-    static thread_local Union un;                        // (kept: fresh pages for it cost more than filling them)
+    static thread_local Union un;
+    struct Kept { ~Kept() { keep(un.segs); keep(un.pos); keep(un.order); } } kept;
     bool alone = c->decode_sharing == 0 && n_calls > 1 && c->decode_tiles_per_split == 0;
     for (const Resolved &r : res) alone = alone && r.n_q == 1;
     if (alone) {
@@ -1105,8 +1111,8 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
     int q_off = 0, seg_off = 0;
     // groups of one-row calls that share enough of their messages take the shared walk, or the whole batch goes by message
     int32_t rc = PC_OK;
-    static thread_local SharedPlan kept_plan;
-    SharedPlan &sp = kept_plan;
+    static thread_local SharedPlan sp;
+    struct Kept { ~Kept() { keep(sp.segs); keep(sp.pos); } } kept;
     sp.in_shared.assign((size_t)n_calls, 0);
     sp.groups.clear(); sp.wide.clear(); sp.segs.clear(); sp.items.clear(); sp.pos.clear();
     if (want_items && bf16) {

@@ -500,3 +500,21 @@ c.attend(calls, 0, 0, 0, 0, made)
 print(peak() - before)
 """)
     assert grown < 40, grown
+
+
+def test_long_lists_are_given_back(pc):
+    """A batch of 40 groups of 256 calls whose unions have 2000 messages each: what planning it took (a table of 80 MB) does not stay with the thread."""
+    grown, = in_a_process_of_its_own("""
+n = 2000
+c = m.Cache(8, 8, 128, m.PC_BF16, 1e4, n * 32, n, flags=m.PC_FLAG_HOST_ONLY)
+for i in range(0, n, 1000):
+    c.append_messages([0] * 1000, [0] * 1000, [1] * 1000)
+c.set_decode_sharing(2)
+calls = [Call([(i, 0) for i in range(n)] if k % 256 == 0 else [(k % n, 0)], -1, 5, 1, None) for k in range(40 * 256)]
+made = marshal_calls(calls)
+c.attend(calls[:2], 0, 0, 0, 0, marshal_calls(calls[:2]))
+before = rss()
+c.attend(calls, 0, 0, 0, 0, made)
+print(rss() - before)
+""")
+    assert grown < 40, grown
