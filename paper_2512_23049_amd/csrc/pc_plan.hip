@@ -1508,12 +1508,14 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
         int longest = 0;
         for (const PcCallDesc &cd : cds) if (cd.n_seg > 0) longest = std::max(longest, P.res[(size_t)(&cd - cds.data())].tiles);
         const int tile_blocks = std::max(1, std::min((longest + 255) / 256, std::max(1, 256 / n_calls)));
+        // (the shared walk turns a query by its whole angle: where nothing else is launched no row's own rotation is read)
+        const int rot_rows = P.n_sh_items > 0 && P.n_dec == 0 && P.n_pre == 0 && P.n_pre_pk == 0 ? 0 : P.total_q;
         if (in_args)
             pc_launch_build_plan_arg(blob, P.ws, P.lay.h2d_bytes, calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                                     P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, st);
+                                     rot_rows, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, st);
         else
             pc_launch_build_plan(calls_at, n_calls, sel_at, q_pos_at, c->table_dev, c->inv_freq_dev, c->half, P.total_seg,
-                                 P.total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, turns, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
+                                 rot_rows, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tile_blocks, tok, turns, in_place ? h : nullptr, P.ws, P.lay.h2d_bytes, st);
         PC_HIP(c, hipGetLastError());
         P.tok_done = !P.tok_items.empty();
         if (in_place) {                                  // the ring slot is free again once the plan builder is done
