@@ -192,8 +192,9 @@ struct SharedPlan {
 
 // The ways of a batch of one-row calls, in us a step with launches and merge.  Tiles (K and V of 32 keys, a KV head) are shared out over the
 // compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 4 and 8 heads a KV head:
-//   own walks     OWN_FIXED, with lists in pinned memory OWN_PINNED; TILE_NEW a tile of the union, TILE_STEP a further pass over a message that
-//                 every call lists (they meet it in step, in the L2), TILE_AGAIN one over any other
+//   own walks     OWN_FIXED, with lists in pinned memory OWN_PINNED, and the longer of what one compute unit has to do (see one_splits) and the tiles:
+//                 TILE_NEW a tile of the union, TILE_STEP a further pass over a message that every call lists (they meet it in step, in the L2),
+//                 TILE_AGAIN one over any other
 //   by message    RUN_FIXED, RUN_PART a part of the row that has most, and TILE_NEW a tile of the union or TILE_PASS a pass of PC_RUN_ROWS rows (16 / g at most)
 //   shared walk   SHARED_FIXED and SHARED_TILE a tile of the groups' unions
 // 64 calls over a system message and 8 of 512 others: 127 us by walks of their own, 111 by message; 8 over 100 of 300: 78 and 52; 16 over 20
@@ -361,10 +362,56 @@ static bool runs_fit(const pc_cache *c, int n_calls, size_t n_runs, int64_t n_pa
     return n_runs < 65535 && runs_layout(c, n_calls, n_runs, n_parts, 0, L) <= HOST_READ_BYTES && L.total <= PC_STATIC_WS_BYTES;
 }
 
+// The splits of a call over T tiles in the one launch of a batch with so many (call, KV head) pairs: those with the least of ONE_TILE us a tile for each
+// round of 256 workgroups, plus, if there is more than one, a merge of ONE_MERGE and ONE_PART a workgroup (us; 1 to 16 calls over 8 to 400 tiles, 1 to 32 splits:
+// this choice is within 5 % of the best of them.  One call over 200 tiles: 63 us unsplit, 13.6 in 32; eight over 16: 11.7 unsplit, 13.3 in 2 or 4).
+// (two rounds; further splits never pay.  Above PC_ONE_COUNTERS pairs there is none, and no counter in use)
+constexpr double ONE_TILE = 0.28, ONE_MERGE = 2.0, ONE_PART = 0.009;
+static int one_splits(int pairs, int T)
+{
+    const int most = std::min(std::max(1, std::min(MAX_SPLITS, 2 * PC_ONE_COUNTERS / pairs)), std::max(1, T / 4));
+    int best = 1;
+    double best_us = 1e30;
+    for (int ns = 1; ns <= most; ++ns) {
+        const int wgs = pairs * ns;
+        const double us = ONE_TILE * ((T + ns - 1) / ns) * ((wgs + 255) / 256) + (ns > 1 ? ONE_MERGE + ONE_PART * wgs : 0.0);
+        if (us < best_us) { best_us = us; best = ns; }
+    }
+    const int chunk = std::max(1, (T + best - 1) / best);
+    return std::max(1, (T + chunk - 1) / chunk);
+}
+
+// What a batch's own walks cost: the launch, and the least that their tiles take, which is what the busiest compute unit has to do.  Under few KV heads
+// that is more than the tiles shared out evenly: 36 calls over 3 of 10 messages and a long system message, 4 KV heads, 42 us for 27.  (510 drawn
+// batches over 17 pairs of 1 to 32 KV heads and 1 to 8 heads a KV head: measured 0.88 to 1.56 times the price, pair by pair, by the tiles alone; so 0.85 to 1.09.)
+struct OwnCost {
+    double fixed, busiest;
+    bool one_launch;                                     // as far as lists go that a wave cannot hold
+    double with(double tiles_us) const { return fixed + std::max(busiest, tiles_us); }
+};
+static OwnCost own_cost(const pc_cache *c, const std::vector<Resolved> &res, size_t entries, int64_t all_tiles)
+{
+    const int n_calls = (int)res.size(), H_kv = c->cfg.n_kv_heads;
+    size_t items = 0;
+    int longest = 0;                                     // tiles of a split
+    OwnCost k{0, 0, true};
+    for (const Resolved &r : res) {
+        const int ns = one_splits(n_calls * H_kv, r.tiles);
+        items += (size_t)ns;
+        longest = std::max(longest, (r.tiles + ns - 1) / ns);
+        k.one_launch = k.one_launch && r.sel.size() < (size_t)ns * PC_ONE_SEGS;
+    }
+    const double wgs = (double)items * H_kv, rounds = std::ceil(wgs / 256);
+    const bool pinned = (sizeof(PcOneCall) + 4) * (size_t)n_calls + sizeof(int2) * entries + sizeof(PcOneItem) * items > PC_ARG_BYTES;
+    k.fixed = pinned ? OWN_PINNED : OWN_FIXED;
+    k.busiest = ONE_TILE * std::max((double)longest, rounds * (double)all_tiles / (double)items) + (items > (size_t)n_calls ? ONE_MERGE + ONE_PART * wgs : 0.0);
+    return k;
+}
+
 // what a batch's own walks and its runs by message cost
 constexpr double NOT_BY_MESSAGE = 1e30;
 struct DecodeCost { double own, by_message; int64_t passes, n_groups; };
-static DecodeCost decode_cost(const pc_cache *c, const Planned &P, const Union &un)
+static DecodeCost decode_cost(const pc_cache *c, const Planned &P, const Union &un, const OwnCost &oc)
 {
     const int n_calls = un.n_rows, per_run = rows_per_run(c);
     const double per_cu = c->cfg.n_kv_heads / 256.0;
@@ -375,8 +422,7 @@ static DecodeCost decode_cost(const pc_cache *c, const Planned &P, const Union &
         k.passes += (int64_t)gr * t; k.n_groups += gr; listed += n;
         (n == n_calls ? in_step : again) += (int64_t)(n - 1) * t;
     }
-    const bool pinned = (sizeof(PcOneCall) + sizeof(PcOneItem) + 4) * (size_t)n_calls + sizeof(int2) * (size_t)listed > PC_ARG_BYTES;
-    k.own = (pinned ? OWN_PINNED : OWN_FIXED) + per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step);
+    k.own = oc.with(per_cu * (TILE_NEW * (double)un.tiles + TILE_AGAIN * (double)again + TILE_STEP * (double)in_step));
     k.by_message = RUN_FIXED + RUN_PART * (double)listed / n_calls + per_cu * std::max(TILE_PASS * ((double)k.passes + RUN_START * (double)k.n_groups), TILE_NEW * (double)un.tiles);
     // (a part per row that lists a message, and a run per group of them, are the least there is: for long lists that is all it takes to know, and
     // the search for the runs is not begun)
@@ -470,30 +516,28 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
     size_t entries = 0, most_sel = 0;
     int64_t all_tiles = 0;
     int32_t most_tiles = 0;
-    bool one_launch = true;                              // as far as lists go that a wave cannot hold
-    const size_t most_entries = (size_t)PC_ONE_SEGS * (size_t)std::max(1, std::min(MAX_SPLITS, 2 * PC_ONE_COUNTERS / (n_calls * c->cfg.n_kv_heads)));
     for (const Resolved &r : res) {
-        entries += r.sel.size(); most_sel = std::max(most_sel, r.sel.size()); all_tiles += r.tiles; most_tiles = std::max(most_tiles, r.tiles);
-        one_launch = one_launch && r.sel.size() < most_entries;
+        entries += r.sel.size() + (r.self_msg >= 0 ? 1 : 0); most_sel = std::max(most_sel, r.sel.size()); all_tiles += r.tiles; most_tiles = std::max(most_tiles, r.tiles);
     }
     // (what no other way can undercut, whatever its calls share, is not collected: 0.5 to 1.5 us of a step of 10 to 30 short calls)
     if (OWN_PINNED + per_cu * TILE_NEW * (double)all_tiles < 1.2 * RUN_FIXED) return Way::OWN;
     // The longest list is the least a union can be, and the other two ways gain the most on walks of their own there
+    const OwnCost oc = own_cost(c, res, entries, all_tiles);
     const double longest = (double)most_tiles;
-    const double on_own = OWN_PINNED + per_cu * (TILE_NEW * longest + TILE_AGAIN * ((double)all_tiles - longest));
+    const double on_own = oc.with(per_cu * (TILE_NEW * longest + TILE_AGAIN * ((double)all_tiles - longest)));
     const double by_shared = ((double)all_tiles >= SHARE_MIN * longest ? SHARE_LEAN : 1.0) * (SHARED_FIXED + SHARED_TILE * per_cu * longest);
     const double by_message = RUN_FIXED + RUN_PART * (double)entries / n_calls + TILE_NEW * per_cu * longest;
     if (on_own < by_shared && 0.95 * on_own < by_message) return Way::OWN;
     // Long lists of short messages under few KV heads: the host takes longer than the GPU whichever way it is, and least if nothing is collected
-    if (one_launch && OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles < HOST_FIXED + HOST_CALL * n_calls + HOST_ENTRY * (double)entries) return Way::OWN;
+    if (oc.one_launch && oc.with(per_cu * TILE_AGAIN * (double)all_tiles) < HOST_FIXED + HOST_CALL * n_calls + HOST_ENTRY * (double)entries) return Way::OWN;
     const int n_groups = (n_calls + rows_max - 1) / rows_max;
-    double own = OWN_PINNED + per_cu * TILE_AGAIN * (double)all_tiles, lean = 1;
+    double own = oc.with(per_cu * TILE_AGAIN * (double)all_tiles), lean = 1;
     // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
     // step, took 104 us and then 128)
     const bool whole = n_calls <= 256 && (n_groups == 1 || entries <= 2048);
     if (whole) {
         if (!collect_union(c, res, 0, n_calls, UNION_ENTRIES / (size_t)n_calls, un)) return n_groups == 1 ? Way::OWN : Way::BY_RATIO;
-        const DecodeCost cost = decode_cost(c, P, un);
+        const DecodeCost cost = decode_cost(c, P, un, oc);
         if ((double)un.call_tiles >= SHARE_MIN * (double)un.tiles) lean = SHARE_LEAN;
         const double shared = lean * (SHARED_FIXED + SHARED_TILE * per_cu * (double)un.tiles * (double)n_groups);
         own = cost.own;
@@ -948,10 +992,6 @@ static void plan_backward_keys_f32(const pc_cache *c, const Planned &P, std::vec
 // it refuses what it refused.  rc != PC_OK: an error; else false: the plan builder's way.  Fills P.one_*.
 // (us a step of 64 calls over 9 messages each: 136 the plan builder's way, 131; of 5 over 220: 141 and 93.  Batches that share
 // enough stay with the shared walk: 14 calls over 27 messages each of 40: 38 us there, 47 in one launch of their own walks.)
-// Splits: those with the least of ONE_TILE us a tile for each round of 256 workgroups, plus, if there is more than one, a merge
-// of ONE_MERGE and ONE_PART a workgroup (us; 1 to 16 calls over 8 to 400 tiles, 1 to 32 splits: this choice is within 5 % of the
-// best of them.  One call over 200 tiles: 63 us unsplit, 13.6 in 32; eight over 16: 11.7 unsplit, 13.3 in 2 or 4).
-constexpr double ONE_TILE = 0.28, ONE_MERGE = 2.0, ONE_PART = 0.009;
 static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
 {
     const int n_calls = (int)P.res.size(), g = c->g, H_kv = c->cfg.n_kv_heads, H_q = c->cfg.n_q_heads;
@@ -968,23 +1008,10 @@ static bool plan_one(pc_cache *c, Planned &P, hipStream_t st, int32_t &rc)
         const size_t tables = n_seg * 548 + n_q * (1536 + 4 * (size_t)H_q) + n_tiles * sizeof(PcTile) + wgs * 16 * 264;
         if (staged > HOST_READ_BYTES || staged + tables > PC_STATIC_WS_BYTES - (1 << 20)) return false;
     }
-    // (two rounds; further splits never pay.  Above PC_ONE_COUNTERS pairs of a call and a KV head there is none, and no counter in use)
-    const int most = std::max(1, std::min(MAX_SPLITS, 2 * PC_ONE_COUNTERS / (n_calls * H_kv)));
-    auto splits_of = [&](int T) {
-        int best = 1;
-        double best_us = 1e30;
-        for (int ns = 1; ns <= std::min(most, std::max(1, T / 4)); ++ns) {
-            const int wgs = n_calls * H_kv * ns;
-            const double us = ONE_TILE * ((T + ns - 1) / ns) * ((wgs + 255) / 256) + (ns > 1 ? ONE_MERGE + ONE_PART * wgs : 0.0);
-            if (us < best_us) { best_us = us; best = ns; }
-        }
-        const int chunk = std::max(1, (T + best - 1) / best);
-        return std::max(1, (T + chunk - 1) / chunk);
-    };
     size_t n_items = 0;
     std::vector<int> splits((size_t)n_calls);
     for (int i = 0; i < n_calls; ++i) {
-        n_items += (size_t)(splits[(size_t)i] = splits_of(P.res[(size_t)i].tiles));
+        n_items += (size_t)(splits[(size_t)i] = one_splits(n_calls * H_kv, P.res[(size_t)i].tiles));
         // (some split has more: known here before any list is sorted)
         if (P.res[(size_t)i].sel.size() + (P.res[(size_t)i].self_msg >= 0 ? 1 : 0) > (size_t)splits[(size_t)i] * PC_ONE_SEGS) return false;
     }

@@ -252,6 +252,21 @@ def test_against_the_oracle_and_replays(h_q):
     cache.close()
 
 
+@pytest.mark.parametrize("h_q,h_kv,n_calls,n_sel,pool,first", [(4, 4, 36, 3, 10, 3511), (4, 4, 27, 5, 25, 3793)])
+def test_walks_that_few_compute_units_share_are_not_priced_as_if_all_did(h_q, h_kv, n_calls, n_sel, pool, first):
+    """A long message that every call lists, under few KV heads: walks of their own split into a few workgroups a call take longer than their tiles shared out
+    evenly would, and the batch does not go that way (where it took 42 us against 25 of the shared walk, 37 against 26)."""
+    r = np.random.default_rng(0)
+    b = Batch(h_q, h_kv, [first] + [int(x) for x in r.integers(350, 440, pool)], [1] * n_calls, 1)
+    calls = spread(r, n_calls, pool, n_sel, b.own)
+    calls = [Call([(0, 0)] + [(m + 1, s) for m, s in c.sel], *fields(c)[1:]) for c in calls]
+    q = b.normal(n_calls, h_q, D)
+    own, got = b.attend(calls, q, mode=1), b.attend(calls, q)
+    assert not b.t.equal(got[1], own[1])
+    close(got, own)
+    b.cache.close()
+
+
 def test_lists_that_bind_the_host_are_not_collected():
     """Five calls over a thousand messages each under one KV head: walks of their own in any case, and the host's time for them without the union of
     their lists, within what mode 1 (which never collects it) takes.  Collected, the least of many was 1.5 times that."""
