@@ -191,7 +191,8 @@ struct SharedPlan {
 };
 
 // The ways of a batch of one-row calls, in us a step with launches and merge.  Tiles (K and V of 32 keys, a KV head) are shared out over the
-// compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 4 and 8 heads a KV head:
+// compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 4 and 8 heads a KV head; with them 1,020 others, of 1 to 32 KV heads and 1 to 8
+// heads a KV head, take 1.028 times the best of the three ways, 1.01 to 1.04 for each such pair, and none over 15 us more than 1.03 times what the sharing ratio alone gave:
 //   own walks     OWN_FIXED, with lists in pinned memory OWN_PINNED, and the longer of what one compute unit has to do (see one_splits) and the tiles:
 //                 TILE_NEW a tile of the union, TILE_STEP a further pass over a message that every call lists (they meet it in step, in the L2),
 //                 TILE_AGAIN one over any other
@@ -207,10 +208,10 @@ constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS
 // us by walks of their own, took 50, shared 38.  125 drawn batches of 6 to 64 calls: 1.25 times as fast as by the sharing ratio alone.  The
 // shared figures above were taken with the rotations in a launch of their own, 3 us more than now.)
 constexpr double SHARE_LEAN = 0.8;
-// What a step takes the host, in us, without a union: resolving, sorting and staging the lists of calls that walk on their own in one launch, and
-// enqueuing it.  (With one, and walks of their own after all: 5 calls over 996 of 1,228 messages, one KV head, 52 us a step for 36; 54 over 110
-// of 157, two, 56 for 41.  Fitted to 18 batches of 5 to 155 calls, 775 to 16 thousand entries.)
-constexpr double HOST_FIXED = 6.0, HOST_CALL = 0.1, HOST_ENTRY = 0.0055;
+// What a step takes the host, in us: resolving, sorting and staging the lists of calls that walk on their own in one launch, and enqueuing it; and
+// COLLECT_ENTRY for a union.  (5 calls over 996 of 1,228 messages, one KV head: 36 us a step, 52 with a union and walks of their own after all; 54
+// over 110 of 157, two, 41 and 56; 20 over 298 of 1,154, two, 48 and 75.  Fitted to 18 batches of 5 to 155 calls, 775 to 16 thousand entries.)
+constexpr double HOST_FIXED = 6.0, HOST_CALL = 0.1, HOST_ENTRY = 0.0055, COLLECT_ENTRY = 0.0045;
 constexpr double RUN_START = 1.5;                        // a run's start and end, in passes
 constexpr double SHARE_MIN = 6.0;
 // entries of a group's rotation table, a row and a message of the union each: 512 bytes, 256 MB in all
@@ -225,7 +226,7 @@ template <typename T> static void keep(std::vector<T> &v) { if (v.capacity() * s
 
 // The union of the lists of some one-row calls: which messages there are, who lists each, and where.
 struct Union {
-    struct Seg { int32_t msg, occ, len; int64_t slot; uint32_t vis[8]; };      // bit n of vis: row n lists it
+    struct Seg { int32_t msg, occ, len, rows; int64_t slot; uint32_t vis[8]; };      // bit n of vis: row n lists it; rows: how many do
     std::vector<Seg> segs;                                // as they turn up
     std::vector<int32_t> pos;                             // [seg][row] q_pos - start + stored base, PC_SH_ABSENT where the row does not list it
     std::vector<int32_t> order;                           // segs in cache-slot order
@@ -250,7 +251,7 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
     Union::Seg *segs = un.segs.data();
     int32_t *pos = un.pos.data();
     auto add = [&](int32_t m, int32_t occ) {
-        un.segs.push_back(Union::Seg{m, occ, msgs[m].len, msgs[m].slot_start, {0, 0, 0, 0, 0, 0, 0, 0}});
+        un.segs.push_back(Union::Seg{m, occ, msgs[m].len, 0, msgs[m].slot_start, {0, 0, 0, 0, 0, 0, 0, 0}});
         un.pos.resize(un.pos.size() + (size_t)n_rows, PC_SH_ABSENT);
         segs = un.segs.data(); pos = un.pos.data();
         return (int32_t)un.segs.size() - 1;
@@ -316,7 +317,11 @@ static bool collect_union(pc_cache *c, std::vector<Resolved> &res, int i, int n_
     }
     if (far) return false;
     un.tiles = 0;
-    for (const Union::Seg &u : un.segs) un.tiles += (u.len + PC_TILE - 1) / PC_TILE;
+    const int words = (n_rows + 31) / 32;                // (counted once, in the words there are: the processor's own count is not in the baseline this is built for)
+    for (Union::Seg &u : un.segs) {
+        un.tiles += (u.len + PC_TILE - 1) / PC_TILE;
+        for (int w = 0; w < words; ++w) u.rows += __builtin_popcount(u.vis[w]);
+    }
     return true;
 }
 
@@ -329,8 +334,6 @@ static void order_union(Union &un)
         return usegs[(size_t)a].slot != usegs[(size_t)b].slot ? usegs[(size_t)a].slot < usegs[(size_t)b].slot
                                                               : usegs[(size_t)a].occ < usegs[(size_t)b].occ; });
 }
-
-static int rows_of(const Union::Seg &u) { int k = 0; for (uint32_t v : u.vis) k += __builtin_popcount(v); return k; }
 
 static int rows_per_run(const pc_cache *c) { return std::max(1, std::min(PC_RUN_ROWS, 16 / c->g)); }
 
@@ -418,7 +421,7 @@ static DecodeCost decode_cost(const pc_cache *c, const Planned &P, const Union &
     int64_t again = 0, in_step = 0, listed = 0;
     DecodeCost k{0, 0, 0, 0};
     for (const Union::Seg &u : un.segs) {
-        const int n = rows_of(u), t = (u.len + PC_TILE - 1) / PC_TILE, gr = (n + per_run - 1) / per_run;
+        const int n = u.rows, t = (u.len + PC_TILE - 1) / PC_TILE, gr = (n + per_run - 1) / per_run;
         k.passes += (int64_t)gr * t; k.n_groups += gr; listed += n;
         (n == n_calls ? in_step : again) += (int64_t)(n - 1) * t;
     }
@@ -505,6 +508,20 @@ static bool even_groups_fit(const pc_cache *c, size_t n_calls, size_t n_groups, 
     return groups_fit(c, n_groups, n_calls, n_groups * segs, n_calls * segs, n_groups * (size_t)ns, ns > 1 ? 2 * (int64_t)ns * (int64_t)n_calls : 0);
 }
 
+// What calls list together in tiles, over the tiles of their union, if any two have as much in common as the one with the longest list and the next one
+static double likely_ratio(pc_cache *c, const std::vector<Resolved> &res)
+{
+    size_t at = 0;
+    for (size_t i = 1; i < res.size(); ++i) if (res[i].tiles > res[at].tiles) at = i;
+    const Resolved &a = res[at], &b = res[(at + 1) % res.size()];
+    const uint32_t epoch = new_marks(c);
+    for (const int2 &e : a.sel) c->marks[(size_t)e.x].epoch = epoch;
+    int64_t common = 0;
+    for (const int2 &e : b.sel) common += c->marks[(size_t)e.x].epoch == epoch ? (c->msgs[(size_t)e.x].len + PC_TILE - 1) / PC_TILE : 0;
+    const double n = (double)res.size(), p = (double)common / std::max(1, b.tiles);
+    return p > 0 ? n * std::min(p, 1.0) / (1 - std::pow(1 - std::min(p, 1.0), n)) : 1;
+}
+
 enum class Way { OWN, BY_MESSAGE, SHARED, BY_RATIO };
 
 // The way of a batch of nothing but one-row calls (the shared walk's groups, or the runs, are planned when this returns); BY_RATIO: as in a mixed batch.
@@ -529,7 +546,10 @@ static Way cheapest_way(pc_cache *c, Planned &P, int rows_max, SharedPlan &sp, U
     const double by_message = RUN_FIXED + RUN_PART * (double)entries / n_calls + TILE_NEW * per_cu * longest;
     if (on_own < by_shared && 0.95 * on_own < by_message) return Way::OWN;
     // Long lists of short messages under few KV heads: the host takes longer than the GPU whichever way it is, and least if nothing is collected
-    if (oc.one_launch && oc.with(per_cu * TILE_AGAIN * (double)all_tiles) < HOST_FIXED + HOST_CALL * n_calls + HOST_ENTRY * (double)entries) return Way::OWN;
+    const double host = HOST_FIXED + HOST_CALL * n_calls + HOST_ENTRY * (double)entries;
+    if (oc.one_launch && oc.with(per_cu * TILE_AGAIN * (double)all_tiles) < host) return Way::OWN;
+    // (where it takes longer with a union, the union is collected if two of the lists have so much in common that it may be short)
+    if (oc.one_launch && on_own < host + COLLECT_ENTRY * (double)entries && likely_ratio(c, res) < SHARE_MIN) return Way::OWN;
     const int n_groups = (n_calls + rows_max - 1) / rows_max;
     double own = oc.with(per_cu * TILE_AGAIN * (double)all_tiles), lean = 1;
     // (calls that make several groups of the shared walk are collected once more for it: 53 calls over 234 messages, whose host work is all of a
@@ -627,7 +647,7 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
         for (int32_t k : un.order) {
             const Union::Seg &u = un.segs[(size_t)k];
             const int T = (u.len + PC_TILE - 1) / PC_TILE;
-            for (int left = rows_of(u); left > 0; left -= per_run)
+            for (int left = u.rows; left > 0; left -= per_run)
                 for (int t = 0; t < T;) {
                     if (used + RUN_START + 1 > share) { ++n_waves; used = 0; }         // (less than a start and a tile left: the next wave)
                     const int take = take_of(share - used, T - t);

@@ -267,15 +267,18 @@ def test_walks_that_few_compute_units_share_are_not_priced_as_if_all_did(h_q, h_
     b.cache.close()
 
 
-def test_lists_that_bind_the_host_are_not_collected():
-    """Five calls over a thousand messages each under one KV head: walks of their own in any case, and the host's time for them without the union of
-    their lists, within what mode 1 (which never collects it) takes.  Collected, the least of many was 1.5 times that."""
+@pytest.mark.parametrize("h_q,h_kv,n_calls,n_sel,pool,n,by_shared", [(1, 1, 5, 996, 1228, 52, False), (1, 1, 7, 400, 1300, 100, False), (4, 2, 20, 298, 1154, 50, False),
+                                                                      (8, 2, 28, 247, 260, 100, True)])
+def test_lists_that_bind_the_host_are_not_collected(h_q, h_kv, n_calls, n_sel, pool, n, by_shared):
+    """Calls over hundreds of messages each under few KV heads: where their lists have little in common, walks of their own in any case, and the host's time for them
+    without the union of their lists, within what mode 1 (which never collects it) takes.  Collected, the least of many was 1.4 to 1.5 times that.  Where they
+    have nearly all in common, the shared walk."""
     import time
     from paper_2512_23049_amd.binding import marshal_calls
     r = np.random.default_rng(2)
-    b = Batch(1, 1, [int(x) for x in r.integers(48, 57, 1228)], [1] * 5, 2)
-    calls = spread(r, 5, 1228, 996, b.own, far=60000)
-    q, made = b.normal(5, 1, D), marshal_calls(calls)
+    b = Batch(h_q, h_kv, [int(x) for x in r.integers(n - 4, n + 5, pool)], [1] * n_calls, 2)
+    calls = spread(r, n_calls, pool, n_sel, b.own, far=60000)
+    q, made = b.normal(n_calls, h_q, D), marshal_calls(calls)
     out, least = b.t.empty_like(q), [1e9, 1e9]
     outs = []
     for _ in range(60):
@@ -286,7 +289,7 @@ def test_lists_that_bind_the_host_are_not_collected():
             least[mode] = min(least[mode], time.thread_time_ns() - start)
             b.t.cuda.synchronize()
             outs.append(out.clone())
-    assert all(b.t.equal(o, outs[0]) for o in outs)
+    assert all(b.t.equal(o, outs[i % 2]) for i, o in enumerate(outs)) and b.t.equal(outs[0], outs[1]) != by_shared
     print("host us, mode 0 and 1:", least[0] / 1e3, least[1] / 1e3)
-    assert least[0] <= 1.25 * least[1], least
+    assert by_shared or least[0] <= 1.25 * least[1], least
     b.cache.close()
