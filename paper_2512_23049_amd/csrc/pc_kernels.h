@@ -104,7 +104,7 @@ void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaun
 // lists (runs first), in pinned memory or already there, to the workspace, the runs' rotations, and a step's tokens into the cache, in one launch
 void pc_launch_runs_prepare(const void *lists, void *to, size_t bytes, int n_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
                             float2 *rot, hipStream_t st);
-// a decode batch by message (H_kv n_waves waves); its parts are added by pc_launch_merge over O.merge_to
+// a decode batch by message (H_kv n_waves waves); its parts, fp32, are added by pc_launch_merge
 void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunStarts &starts, hipStream_t st);
 void pc_launch_prefill_bf16(const PcLaunch &L, int n_items, bool packed, hipStream_t st);   // packed: the items of calls that gathered
 

@@ -614,7 +614,7 @@ __global__ __launch_bounds__(512, 1) void pc_prefill_bf16_kernel(PcLaunch L)
             constexpr int u = decltype(uc)::value;
             constexpr int s0 = u, s1 = (u + 1) % RING, s2 = (u + 2) % RING, s4 = (u + 4) % RING;
             // In front of phase A, not beside its keys: a branch inside would cut the phase in two for the scheduler, and the
-            // exponentials would crowd behind the last MFMAs (2,048 rows over 4,368: 100.7 us there, 100.3 here).
+            // exponentials would crowd behind the last MFMAs (no difference in time: 2,048 rows over 4,368 100.7 us there, 100.3 here).
             dma_rot(d5, s0);
             i32x4 raw6 = request_desc(min(tile0 + i + 6, last));     // first used in the next iteration's requests
             f32x16 sn = phase_a(s0, sc, [&] { dma_k(d5, s0); });             // K(i+5) takes the slot of K(i)

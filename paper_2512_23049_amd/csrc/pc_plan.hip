@@ -191,8 +191,7 @@ struct SharedPlan {
 };
 
 // The ways of a batch of one-row calls, in us a step with launches and merge.  Tiles (K and V of 32 keys, a KV head) are shared out over the
-// compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 4 and 8 heads a KV head; with them 1,020 others, of 1 to 32 KV heads and 1 to 8
-// heads a KV head, take 1.028 times the best of the three ways, 1.01 to 1.04 for each such pair, and none over 15 us more than 1.03 times what the sharing ratio alone gave:
+// compute units.  From 70 batches of 2 to 64 calls over 1 to 400 messages, 8 KV heads, 4 and 8 heads a KV head:
 //   own walks     OWN_FIXED, with lists in pinned memory OWN_PINNED, and the longer of what one compute unit has to do (see one_splits) and the tiles:
 //                 TILE_NEW a tile of the union, TILE_STEP a further pass over a message that every call lists (they meet it in step, in the L2),
 //                 TILE_AGAIN one over any other
@@ -204,9 +203,10 @@ struct SharedPlan {
 // tokens of the union: a union tile costs a workgroup 8.7 ns with the chip full, a tile streamed by one call 1.5 to 1.7.
 constexpr double TILE_NEW = 0.79, TILE_AGAIN = 0.36, TILE_STEP = 0.15, TILE_PASS = 0.33, OWN_FIXED = 8.0, OWN_PINNED = 14.0, RUN_FIXED = 20.5, RUN_PART = 0.045,
                  SHARED_FIXED = 30.0, SHARED_TILE = 1.05;
-// (the other two prices are the less certain the more often a tile is met again: 44 calls over 2 of 5 messages and a long system message, priced at 33
-// us by walks of their own, took 50, shared 38.  125 drawn batches of 6 to 64 calls: 1.25 times as fast as by the sharing ratio alone.  The
-// shared figures above were taken with the rotations in a launch of their own, 3 us more than now.)
+// What they were not taken from: 1,020 drawn batches, 60 for each of 17 pairs of 1 to 32 KV heads and 1 to 8 heads a KV head, every one timed all three ways.
+// The way chosen takes 1.028 times the least of the three in the mean (1.01 to 1.04 pair by pair, 1.73 at most), and 0.78 of what the sharing ratio
+// alone had chosen; none over 15 us takes more than 1.03 of that.  One price is 14 to 25 % off (one deviation), the shared walk's too high where lists share
+// much: SHARE_LEAN (it was taken with the rotations in a launch of their own, 3 us more).
 constexpr double SHARE_LEAN = 0.8;
 // What a step takes the host, in us: resolving, sorting and staging the lists of calls that walk on their own in one launch, and enqueuing it; and
 // COLLECT_ENTRY for a union.  (5 calls over 996 of 1,228 messages, one KV head: 36 us a step, 52 with a union and walks of their own after all; 54
