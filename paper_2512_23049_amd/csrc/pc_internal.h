@@ -205,6 +205,8 @@ struct PcMsgRun {             // one cache line
     int32_t part[PC_RUN_ROWS];    // fp32 partial rows of the run's results
     int32_t pos[PC_RUN_ROWS];     // the rows' positions minus the positions their calls give the message's first token
 };
+// The same for lists that are recorded into a graph, whose launches each bring PC_ARG_BYTES of them (0.9 us a launch): 40 bytes
+struct PcMsgRunShort { int32_t msg, tile0, size; uint8_t row[PC_RUN_ROWS]; uint16_t part[PC_RUN_ROWS]; int32_t pos[PC_RUN_ROWS]; };
 struct PcRunStarts { uint16_t first[PC_RUN_WAVES + 2]; };       // wave w of a KV head takes the runs [first[w], first[w + 1])
 
 #define PC_MERGE_WIDE 0x10000     // partial outputs in fp32 (bf16 caches)

@@ -101,8 +101,8 @@ void pc_launch_gather(const PcLaunch &L, const PcGatherItem *items, int n_items,
 void pc_launch_decode_bf16(const PcLaunch &L, int n_items, hipStream_t st);
 // a batch of decode calls: plan, token append, attention and merge in one launch (blob: bytes of its lists, unless O.lists has them)
 void pc_launch_decode_one_bf16(const PcArgBlob &blob, size_t bytes, const PcLaunch &L, const PcOne &O, hipStream_t st);
-// lists (runs first), in pinned memory or already there, to the workspace, the runs' rotations, and a step's tokens into the cache, in one launch
-void pc_launch_runs_prepare(const void *lists, void *to, size_t bytes, int n_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
+// lists (runs first, `rest` bytes behind them; short_runs: as PcMsgRunShort) to the workspace, the runs' rotations, and a step's tokens into the cache, in one launch
+void pc_launch_runs_prepare(const void *lists, void *to, size_t rest, int n_runs, bool short_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
                             float2 *rot, hipStream_t st);
 // a decode batch by message (H_kv n_waves waves); its parts, fp32, are added by pc_launch_merge
 void pc_launch_decode_runs_bf16(const PcLaunch &L, const PcRuns &O, const PcRunStarts &starts, hipStream_t st);

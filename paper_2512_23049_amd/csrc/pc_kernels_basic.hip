@@ -697,21 +697,28 @@ __global__ __launch_bounds__(256) void pc_build_plan_arg_kernel(
                      total_q, segs, seg_kvoff, rot_seg, rot_q, rot_qw, tiles, tok, tok_block0, tile_blocks);
 }
 
-// What a decode batch by message needs in front of it: its lists, from pinned memory (where they are read) to the workspace, the rotations
-// of its runs' rows, and a step's new tokens.  Three kinds of blocks: four runs, one a wave (what is in pinned memory is read once, a line a run;
+// What a decode batch by message needs in front of it: its lists, from pinned memory (where they are read; SHORT: from where a recorded call's
+// launches left them, see PcMsgRunShort) to the workspace, the rotations of its runs' rows, and a step's new tokens.  Three kinds of blocks: four runs, one a wave (what is in pinned memory is read once, a line a run;
 // read by blocks of their own and again for the rotations, 900 runs took 8.3 us); rows to merge; tokens.
+template <bool SHORT>
 __global__ __launch_bounds__(256) void pc_runs_prepare_kernel(const int32_t *__restrict__ lists, int32_t *__restrict__ to, int n_runs, int n_rest, int run_blocks, int rest_blocks,
                                                               float scale, PcTokenWork tok, const double *__restrict__ inv_freq, PcMsgEntry *__restrict__ table,
                                                               float2 *__restrict__ rot)
 {
-    constexpr int WORDS = sizeof(PcMsgRun) / 4;
+    constexpr int WORDS = sizeof(PcMsgRun) / 4, FROM = SHORT ? sizeof(PcMsgRunShort) / 4 : WORDS;
+    static_assert(sizeof(PcMsgRunShort) == 40 && sizeof(PcMsgRun) == 64, "");
     int block = (int)blockIdx.x;
     if (block < run_blocks) {
         const int run = 4 * block + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
         if (run >= n_runs) return;
-        const int w = lane < WORDS ? lists[(int64_t)run * WORDS + lane] : 0;
+        int w = lane < FROM ? lists[(int64_t)run * FROM + lane] : 0;
         const double freq = inv_freq[lane];
-        if (to && lane < WORDS) to[(int64_t)run * WORDS + lane] = w;
+        if constexpr (SHORT) {                           // lanes 0 to 15 take the words of a PcMsgRun: msg, tile0, size, pad, row, part, pos
+            const int i = lane & 3;
+            const int x = __shfl(w, lane < 3 ? lane : lane < 8 ? 3 : lane < 12 ? 4 + (i >> 1) : 6 + i);
+            w = lane < 3 || lane >= 12 ? x : lane == 3 ? 0 : lane < 8 ? (x >> (8 * i)) & 0xFF : (x >> (16 * (i & 1))) & 0xFFFF;
+        }
+        if (lane < WORDS) to[(int64_t)run * WORDS + lane] = w;
         const int base = table[__builtin_amdgcn_readlane(w, offsetof(PcMsgRun, msg) / 4)].base_pos, n_rows = __builtin_amdgcn_readlane(w, offsetof(PcMsgRun, size) / 4) >> 28;
 #pragma unroll 1
         for (int r = 0; r < n_rows; ++r) {
@@ -722,8 +729,8 @@ __global__ __launch_bounds__(256) void pc_runs_prepare_kernel(const int32_t *__r
     }
     block -= run_blocks;
     if (block < rest_blocks) {
-        const int i = n_runs * WORDS + block * 256 + (int)threadIdx.x;
-        if (i < n_runs * WORDS + n_rest) to[i] = lists[i];
+        const int i = block * 256 + (int)threadIdx.x;
+        if (i < n_rest) to[n_runs * WORDS + i] = lists[n_runs * FROM + i];
         return;
     }
     block -= rest_blocks;
@@ -735,14 +742,18 @@ __global__ __launch_bounds__(256) void pc_runs_prepare_kernel(const int32_t *__r
                                   tok.n_kv_heads, tok.D, tok.slots, inv_freq, (uint16_t *)tok.k_store, (uint16_t *)tok.v_store, table);
 }
 
-void pc_launch_runs_prepare(const void *lists, void *to, size_t bytes, int n_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
+void pc_launch_runs_prepare(const void *lists, void *to, size_t rest, int n_runs, bool short_runs, float scale, const PcTokenWork &tok, const double *inv_freq, PcMsgEntry *table,
                             float2 *rot, hipStream_t st)
 {
-    const int n_rest = lists != to ? (int)(bytes / 4) - n_runs * (int)(sizeof(PcMsgRun) / 4) : 0;
+    const int n_rest = (int)(rest / 4);
     const unsigned run_blocks = (unsigned)(n_runs + 3) / 4, rest_blocks = (unsigned)(n_rest + 255) / 256;
     const unsigned tok_blocks = (unsigned)(((int64_t)tok.n * tok.n_kv_heads * (tok.D / 4) + 255) / 256);
-    pc_runs_prepare_kernel<<<run_blocks + rest_blocks + tok_blocks, 256, 0, st>>>((const int32_t *)lists, lists != to ? (int32_t *)to : nullptr, n_runs, n_rest, (int)run_blocks,
-                                                                                  (int)rest_blocks, scale, tok, inv_freq, table, rot);
+    auto launch = [&](auto kernel) {
+        kernel<<<run_blocks + rest_blocks + tok_blocks, 256, 0, st>>>((const int32_t *)lists, (int32_t *)to, n_runs, n_rest, (int)run_blocks, (int)rest_blocks, scale, tok,
+                                                                      inv_freq, table, rot);
+    };
+    if (short_runs) launch(pc_runs_prepare_kernel<true>);
+    else launch(pc_runs_prepare_kernel<false>);
 }
 
 static unsigned plan_blocks(int n_calls, int tile_blocks, int half, int total_seg, int total_q, const PcTokenWork &tok, int &tok_block0)

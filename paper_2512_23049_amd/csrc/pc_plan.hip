@@ -350,9 +350,11 @@ static size_t runs_layout(const pc_cache *c, int n_calls, size_t n_runs, int64_t
     const size_t H_q = (size_t)c->cfg.n_q_heads;
     L = PlanLayout{};
     L.part_ml = align_up(sizeof(float) * (size_t)n_parts * H_q * (size_t)c->D, 256);
-    L.calls = align_up(L.part_ml + sizeof(float) * 4 * (size_t)n_parts * H_q, 256);      // the runs, then the rows to merge
-    L.merge_rows = L.calls + off_merge;
     const size_t bytes = off_tok + sizeof(PcTokenItem) * n_tok;
+    // (a recorded call's launches leave its lists, the runs short, where the parts will be)
+    const size_t parts = L.part_ml + sizeof(float) * 4 * (size_t)n_parts * H_q, recorded = align_up(sizeof(PcMsgRunShort) * n_runs + bytes - off_merge, 16);
+    L.calls = align_up(std::max(parts, recorded), 256);  // the runs, then the rows to merge
+    L.merge_rows = L.calls + off_merge;
     L.rot_seg = align_up(L.calls + bytes, 1024);
     L.total = L.rot_seg + n_runs * PC_RUN_ROWS * sizeof(float2) * 64;
     L.tok_items = off_tok;
@@ -701,22 +703,29 @@ static bool plan_runs(pc_cache *c, Planned &P, Union &un, const DecodeCost &cost
         for (int i = 0; i < r.size >> 28; ++i) r.part[i] += part0[(size_t)r.row[i]];
     const size_t bytes = runs_layout(c, n_calls, runs.size(), part_rows, P.tok_items.size(), P.lay), off_merge = P.lay.merge_rows - P.lay.calls, off_tok = P.lay.tok_items;
     P.n_runs = (int)runs.size();
-    char *h;
-    const bool recorded = pc_recorded(st);
-    if (recorded) {
-        P.recorded.resize(align_up(bytes, 16));
-        h = P.recorded.data();
+    char *rest;                                          // what is behind the runs
+    if (pc_recorded(st)) {
+        static_assert(PC_STATIC_WS_BYTES / (4 * 128 + 16) < 1 << 16, "a part's number in 16 bits: those of 128 dimensions and one head that fit");
+        const size_t off_rest = sizeof(PcMsgRunShort) * runs.size();
+        P.recorded.resize(align_up(off_rest + bytes - off_merge, 16));
+        PcMsgRunShort *to = (PcMsgRunShort *)P.recorded.data();
+        for (const PcMsgRun &r : runs) {
+            PcMsgRunShort s{r.msg, r.tile0, r.size, {}, {}, {}};
+            for (int i = 0; i < r.size >> 28; ++i) { s.row[i] = (uint8_t)r.row[i]; s.part[i] = (uint16_t)r.part[i]; s.pos[i] = r.pos[i]; }
+            *to++ = s;
+        }
+        rest = P.recorded.data() + off_rest;
     } else {
         rc = pc_stage_acquire(c, bytes, &P.runs_slot);
         if (rc != PC_OK) return false;
-        h = (char *)P.runs_slot->host;
+        std::memcpy(P.runs_slot->host, runs.data(), off_merge);
+        rest = (char *)P.runs_slot->host + off_merge;
     }
-    std::memcpy(h, runs.data(), off_merge);
-    PcMergeRow *rows = (PcMergeRow *)(h + off_merge);
+    PcMergeRow *rows = (PcMergeRow *)rest;
     for (int i = 0; i < n_calls; ++i) rows[i] = PcMergeRow{i, 2 * part0[(size_t)i], parts[(size_t)i] | PC_MERGE_WIDE, 1};
     P.runs_bytes = bytes;
     P.n_merge_rows = n_calls; P.n_merge_few = 0;
-    if (!P.tok_items.empty()) std::memcpy(h + off_tok, P.tok_items.data(), sizeof(PcTokenItem) * P.tok_items.size());
+    if (!P.tok_items.empty()) std::memcpy(rest + (off_tok - off_merge), P.tok_items.data(), sizeof(PcTokenItem) * P.tok_items.size());
     P.runs = PcRuns{c->table_dev, nullptr, nullptr, n_waves};
     return true;
 }
@@ -1174,11 +1183,12 @@ int32_t pc_plan_and_stage(pc_cache *c, const pc_call *calls, int32_t n_calls, bo
             P.runs.runs = (const PcMsgRun *)((char *)P.ws + P.lay.calls);
             P.runs.rot = (const float2 *)((char *)P.ws + P.lay.rot_seg);
             ProfScope ps(c, 1, st);
-            char *lists = (char *)P.ws + P.lay.calls;
-            if (!P.runs_slot) pc_launch_store_args(P.recorded.data(), P.recorded.size(), lists, st);
-            char *from = P.runs_slot ? (char *)P.runs_slot->host : lists;
-            const PcTokenWork tok = token_work(c, P, (const PcTokenItem *)(from + P.lay.tok_items));
-            pc_launch_runs_prepare(from, lists, P.runs_bytes, P.n_runs, c->scale * 1.4426950408889634f, tok, c->inv_freq_dev, c->table_dev,
+            const bool recorded = !P.runs_slot;
+            if (recorded) pc_launch_store_args(P.recorded.data(), P.recorded.size(), P.ws, st);
+            char *from = recorded ? (char *)P.ws : (char *)P.runs_slot->host, *lists = (char *)P.ws + P.lay.calls;
+            const size_t off_rest = sizeof(PcMsgRun) * (size_t)P.n_runs, saved = recorded ? (sizeof(PcMsgRun) - sizeof(PcMsgRunShort)) * (size_t)P.n_runs : 0;
+            const PcTokenWork tok = token_work(c, P, (const PcTokenItem *)(from + P.lay.tok_items - saved));
+            pc_launch_runs_prepare(from, lists, P.runs_bytes - off_rest, P.n_runs, recorded, c->scale * 1.4426950408889634f, tok, c->inv_freq_dev, c->table_dev,
                                    (float2 *)((char *)P.ws + P.lay.rot_seg), st);
             PC_HIP(c, hipGetLastError());
             P.tok_done = !P.tok_items.empty();

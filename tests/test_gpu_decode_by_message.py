@@ -252,6 +252,38 @@ def test_against_the_oracle_and_replays(h_q):
     cache.close()
 
 
+@pytest.mark.parametrize("h_q,h_kv,n_calls,n_sel,pool,own", [(8, 8, 250, 2, 130, False), (8, 2, 14, 120, 700, True), (64, 8, 40, 13, 120, True)])
+def test_replays_of_many_runs(h_q, h_kv, n_calls, n_sel, pool, own):
+    """Recorded into a graph, whose launches bring the runs in short: rows up to 249, parts beyond 255, one to eight heads a KV head.  Replays beside calls with
+    other lists, after messages were moved: what an ordinary call returns, bit for bit."""
+    r = np.random.default_rng(7)
+    b = Batch(h_q, h_kv, [700] + [int(x) for x in r.integers(*((100, 400) if own else (300, 900)), pool - 1)], [1 + i % 40 for i in range(n_calls)] if own else [], 5)
+    calls = spread(r, n_calls, pool, n_sel, b.own or [-1] * n_calls)
+    calls = [Call([(0, 3)] * own + c.sel, c.self_msg, c.self_start, 1, None if own else [4000 + i]) for i, c in enumerate(calls)]
+    others = [Call(c.sel[::2], *fields(c)[1:]) for c in calls]
+    q = b.normal(n_calls, h_q, D)
+    want, got, stream = b.t.empty_like(q), b.t.empty_like(q), b.t.cuda.Stream()
+    assert b.attend(calls, q)[2]
+    with b.t.cuda.stream(stream):
+        b.cache.attend_static(calls, q.data_ptr(), got.data_ptr(), 0, stream.cuda_stream)
+    b.t.cuda.synchronize()
+    graph = b.t.cuda.CUDAGraph()
+    with b.t.cuda.graph(graph, stream=stream):
+        b.cache.attend_static(calls, q.data_ptr(), got.data_ptr(), 0, stream.cuda_stream)
+    for turn in range(4):
+        b.cache.attend_static(others, q.data_ptr(), got.data_ptr())
+        for m in b.ids[turn:9]:
+            b.cache.reposition(m, 100 * turn - 50)
+        q.copy_(b.normal(n_calls, h_q, D))
+        b.cache.attend(calls, q.data_ptr(), want.data_ptr())
+        b.t.cuda.synchronize()
+        got.fill_(7.0)
+        graph.replay()
+        b.t.cuda.synchronize()
+        assert b.t.equal(want.view(b.t.int16), got.view(b.t.int16)), turn
+    b.cache.close()
+
+
 @pytest.mark.parametrize("h_q,h_kv,n_calls,n_sel,pool,first", [(4, 4, 36, 3, 10, 3511), (4, 4, 27, 5, 25, 3793)])
 def test_walks_that_few_compute_units_share_are_not_priced_as_if_all_did(h_q, h_kv, n_calls, n_sel, pool, first):
     """A long message that every call lists, under few KV heads: walks of their own split into a few workgroups a call take longer than their tiles shared out
